@@ -110,8 +110,8 @@ size_t lsp_workspace_bytes(int64_t m, int64_t n, int32_t r, int32_t d, lsp_dtype
  * problem, valid until the projector arrays change (every CheckFreq steps at most, Alg. 1).
  * It lives entirely in a caller-owned device buffer of lsp_plan_bytes() bytes; there is no
  * host handle.  Building a plan only sorts and packs the projector entries (no arithmetic on
- * G, W or S) and happens on the device, where the projectors live: a radix sort of one key per
- * stored entry and a handful of small kernels (tens of microseconds; nothing is copied to the host).
+ * G, W or S) and happens on the device, where the projectors live: three small kernels (about
+ * twenty microseconds; nothing is copied to the host).
  *
  * lsp_plan_build_async only enqueues that work on `stream`; it needs device scratch of
  * lsp_plan_build_workspace_bytes() and reports what only the data can show -- an index outside

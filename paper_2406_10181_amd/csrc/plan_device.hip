@@ -5,15 +5,16 @@
 // change when MaybeUpdate (Alg. 1) replaces them, and their values change in every iteration of
 // the fitting loop, so a plan has to be cheap to make where the projectors live: on the GPU.
 //
-// Build.  The same bytes as the host builder, from kernels only, asynchronously on one stream:
-//   1. one 64-bit key per stored entry, (chunk, subspace column, flat ELL position) for Q and
-//      (subspace row, flat ELL position) for P, sorted by the device radix sort; the keys are
-//      unique, so the sorted order is the (column, row, k) order of the host's counting sorts;
-//   2. list boundaries by binary search; owners per column of T (long lists are shared between
-//      lanes, spare lanes go to the longest lists), virtual columns, slots;
-//   3. per chunk: the 512 lists dealt to the waves by length (rank by counting), segment lengths;
-//   4. the waves' stream positions, then the interleaved (LDS offset, value) rows;
-//   5. the rows of P^T cut into pieces.
+// Build.  The same bytes as the host builder, from three kernels, asynchronously on one stream:
+//   1. k_plan_sort: the stored entries of a tile of 2048 rows (a chunk of Q, or as many rows of P) in the order of the
+//      host's counting sorts, (subspace column, row, k), by a stable counting sort in LDS;
+//   2. k_plan_deal: owners per column of T (long lists are shared between lanes, spare lanes go to the longest
+//      lists), virtual columns, slots; per chunk the lists dealt to the waves by length; the pieces of the rows of P^T;
+//   3. k_plan_rows: the waves' stream positions, the interleaved (LDS offset, value) rows, the entries of P^T.
+// What bounds a build is not bytes (a few MB) but the chain of launches and of dependent loads inside them, so the
+// work is cut into few kernels, and small sums are taken again by every workgroup that needs them.  The form before
+// this one (64-bit keys, two device-wide radix sorts, 17 to 23 launches) took 96 us of host time alone for a
+// 4096 x 4096 matrix with r = 512 and d = 8.
 // Errors that only the data can show (an index outside [0, r), columns too skewed for a plan) are
 // left in a device status word and invalidate the plan's magic, so that a later compress call
 // with it fills S with NaN instead of following it.
@@ -21,8 +22,6 @@
 // Values-only refresh.  The plan records, for every value it holds, the flat ELL position it came
 // from, so new values are dropped in place by one small kernel.
 #include <algorithm>
-
-#include <rocprim/device/device_radix_sort.hpp>
 
 #include "lsp_internal.h"
 
@@ -59,89 +58,164 @@ hipError_t launch_plan_refresh(uint8_t* plan, const float* P_val, const float* Q
 }
 
 // ---------------------------------------------------------------------------------------------
-// Build.  Scratch (device, caller's workspace), carved by build_scratch():
+// Build.  Scratch (device, caller's workspace), carved by build_scratch().  Tiles are the nchunks chunks of Q, then the
+// ptiles runs of kChunk rows of P.
 struct BuildScratch {
-    uint64_t* keys_a;      // max(n, m) * d
-    uint64_t* keys_b;      // max(n, m) * d
-    uint32_t* start_q;     // nchunks * r + 1: first sorted position of each (chunk, column) list
-    uint32_t* start_p;     // r + 1
-    int32_t*  owners;      // r
-    int32_t*  first_v;     // r + 1
-    int32_t*  v_col;       // kMaxSlots * 512: column of a virtual column, -1 if none
-    int32_t*  v_own;       // kMaxSlots * 512: which owner of its column it is
-    uint32_t* seg_start;   // nchunks * kMaxSlots * 8: first stream row of each segment
-    int32_t*  item_base;   // r + 1
-    int32_t*  status;      // [0] lsp_status of the build, [1] nslots, [2] total rows, [3] build abandoned
-    void*     sort_tmp;
-    size_t    sort_tmp_bytes;
+    uint32_t* sorted_q;    // n * d: flat ELL positions j * d + k, per chunk in the order (column, j, k)
+    uint32_t* sorted_p;    // m * d: the same per tile of P
+    uint32_t* start;       // [tile][r + 1]: first position of each column's list inside its tile
+    int32_t*  bad;         // [tile][kSubTiles]: an index outside [0, r) was seen
+    int32_t*  seg_lo;      // [chunk][slot][512]: first entry (of sorted_q) of the list thread t walks
+    int32_t*  seg_n;       // ... and its length
+    int32_t*  p_shift;     // [tile of P][r]: position of an entry in p_ent less its position in its tile
 };
-
-static int bits_for(uint64_t count) { int b = 1; while (b < 63 && ((uint64_t)1 << b) < count) ++b; return b; }
-
-static size_t sort_tmp_bytes(size_t count) {
-    size_t bytes = 0;
-    uint64_t* none = nullptr;
-    (void)rocprim::radix_sort_keys(nullptr, bytes, none, none, count, 0u, 64u, (hipStream_t)0, false);   // size query only
-    return bytes;
-}
+constexpr int kSubTiles = 8;                       // workgroups that share a tile in k_plan_sort
+constexpr int kThreadsSort = 1024;
+constexpr int kWavesSort = kThreadsSort / kWave;
 
 static size_t build_scratch(uint8_t* base, int64_t m, int64_t n, int32_t r, int32_t d, BuildScratch* out) {
-    const size_t nchunks = (size_t)((n + kChunk - 1) / kChunk);
-    const size_t maxn = (size_t)std::max(m, n) * (size_t)d;
+    const size_t nchunks = (size_t)((n + kChunk - 1) / kChunk), ptiles = (size_t)((m + kChunk - 1) / kChunk);
     size_t o = 0;
     auto take = [&](size_t bytes) { const size_t at = o; o = align_up(o + bytes, 256); return base ? base + at : nullptr; };
     BuildScratch s;
-    s.keys_a = reinterpret_cast<uint64_t*>(take(maxn * 8));
-    s.keys_b = reinterpret_cast<uint64_t*>(take(maxn * 8));
-    s.start_q = reinterpret_cast<uint32_t*>(take((nchunks * (size_t)r + 1) * 4));
-    s.start_p = reinterpret_cast<uint32_t*>(take(((size_t)r + 1) * 4));
-    s.owners = reinterpret_cast<int32_t*>(take((size_t)r * 4));
-    s.first_v = reinterpret_cast<int32_t*>(take(((size_t)r + 1) * 4));
-    s.v_col = reinterpret_cast<int32_t*>(take((size_t)kMaxSlots * kThreadsGQ * 4));
-    s.v_own = reinterpret_cast<int32_t*>(take((size_t)kMaxSlots * kThreadsGQ * 4));
-    s.seg_start = reinterpret_cast<uint32_t*>(take(nchunks * kMaxSlots * kWavesGQ * 4));
-    s.item_base = reinterpret_cast<int32_t*>(take(((size_t)r + 1) * 4));
-    s.status = reinterpret_cast<int32_t*>(take(256));
-    s.sort_tmp_bytes = sort_tmp_bytes(maxn);
-    s.sort_tmp = take(s.sort_tmp_bytes);
+    s.sorted_q = reinterpret_cast<uint32_t*>(take((size_t)n * (size_t)d * 4));
+    s.sorted_p = reinterpret_cast<uint32_t*>(take((size_t)m * (size_t)d * 4));
+    s.start = reinterpret_cast<uint32_t*>(take((nchunks + ptiles) * ((size_t)r + 1) * 4));
+    s.bad = reinterpret_cast<int32_t*>(take((nchunks + ptiles) * kSubTiles * 4));
+    s.seg_lo = reinterpret_cast<int32_t*>(take(nchunks * kMaxSlots * kThreadsGQ * 4));
+    s.seg_n = reinterpret_cast<int32_t*>(take(nchunks * kMaxSlots * kThreadsGQ * 4));
+    s.p_shift = reinterpret_cast<int32_t*>(take(ptiles * (size_t)r * 4));
     if (out) *out = s;
     return o;
 }
 
 size_t plan_build_workspace_bytes(int64_t m, int64_t n, int32_t r, int32_t d) { return build_scratch(nullptr, m, n, r, d, nullptr); }
 
-typedef PlanLayout DevLayout;
-
-__global__ __launch_bounds__(256) void k_fill_u32(uint32_t* __restrict__ p, int64_t count, uint32_t v) {
-    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < count; k += (int64_t)gridDim.x * 256) p[k] = v;
-}
-
-// key of stored entry e = row * d + k: (list << ebits) | e, list = chunk * r + column for Q (chunk_rows = kChunk)
-// and the subspace row for P (chunk_rows = 0).  An index outside [0, r) is recorded and replaced by 0.
-__global__ __launch_bounds__(256) void k_build_keys(const int32_t* __restrict__ idx, int64_t count, int d, int r, int chunk_rows,
-                                                    int ebits, uint64_t* __restrict__ keys, int32_t* __restrict__ status) {
-    bool bad = false;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < count; e += (int64_t)gridDim.x * 256) {
-        int b = idx[e];
-        if (b < 0 || b >= r) { bad = true; b = 0; }
-        const int64_t row = e / d;
-        const uint64_t list = (chunk_rows ? (uint64_t)(row / chunk_rows) * (uint64_t)r : 0u) + (uint64_t)b;
-        keys[e] = (list << ebits) | (uint64_t)e;
+// Exclusive sum of x over the threads of the workgroup (NW waves); total: the sum of all.  `part` is LDS for NW words.
+template <int NW>
+__device__ __forceinline__ int32_t block_exclusive(int32_t x, int32_t* part, int32_t& total) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int32_t inc = x;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int32_t y = __shfl_up(inc, off);
+        if (lane >= off) inc += y;
     }
-    if (bad) status[0] = LSP_ERR_INDEX;
+    __syncthreads();                                                 // the last call's parts have been read
+    if (lane == kWave - 1) part[w] = inc;
+    __syncthreads();
+    int32_t before = 0, all = 0;
+#pragma unroll
+    for (int k = 0; k < NW; ++k) {
+        const int32_t y = part[k];
+        before += k < w ? y : 0;
+        all += y;
+    }
+    total = all;
+    return before + inc - x;
 }
 
-// start[l] = first sorted position whose list is >= l, for l = 0 .. nlists
-__global__ __launch_bounds__(256) void k_list_bounds(const uint64_t* __restrict__ sorted, int64_t count, int ebits, int64_t nlists,
-                                                     uint32_t* __restrict__ start) {
-    for (int64_t l = (int64_t)blockIdx.x * 256 + threadIdx.x; l <= nlists; l += (int64_t)gridDim.x * 256) {
-        const uint64_t want = (uint64_t)l << ebits;
-        int64_t lo = 0, hi = count;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (sorted[mid] < want) lo = mid + 1; else hi = mid;
+// Stable counting sort of a tile's entries by column.  kSubTiles workgroups share a tile: each counts all of the tile's
+// columns (LDS atomics; the counts do not depend on their order), which gives it the lists' first positions and what the
+// parts before its own have put there, and then places its own part: every wave takes a contiguous run, counts it, and
+// walks it 64 entries at a time; entries of one column among the 64 find their order by ballots over the column's bits.
+// Sharing a tile shortens the serial walk to 2 steps of 64 at d = 8.  An index outside [0, r) is recorded and taken as 0.
+// Workgroups past the tiles clear the parts of the plan that no later kernel fills completely.
+__global__ __launch_bounds__(kThreadsSort) void k_plan_sort(uint8_t* __restrict__ plan, PlanLayout L, BuildScratch s, const int32_t* __restrict__ P_idx,
+                                                            const int32_t* __restrict__ Q_idx, int m, int n, int r, int d,
+                                                            int nchunks, int ptiles, int64_t max_rows) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    __shared__ int32_t s_part[kWavesSort];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tile = blockIdx.x / kSubTiles, sub = blockIdx.x % kSubTiles;
+    if (tile >= nchunks + ptiles) {
+        const int first = (nchunks + ptiles) * kSubTiles;
+        const size_t rows_end = L.off_q_rows + (size_t)max_rows * kWave * sizeof(uint2), src_end = L.off_q_src + (size_t)max_rows * kWave * 4;
+        const size_t np = (size_t)m * d;
+        const size_t lo[] = {0, rows_end, L.off_p_ent + np * sizeof(uint2), src_end, L.off_p_src + np * 4};
+        const size_t hi[] = {L.off_q_rows, L.off_p_ent, L.off_q_src, L.off_p_src, L.total};
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+            for (size_t at = lo[k] + ((size_t)(blockIdx.x - first) * kThreadsSort + tid) * 4; at < hi[k]; at += (size_t)(gridDim.x - first) * kThreadsSort * 4)
+                *reinterpret_cast<uint32_t*>(plan + at) = 0u;
+        return;
+    }
+    const bool is_q = tile < nchunks;
+    const int t = is_q ? tile : tile - nchunks;
+    const int32_t* __restrict__ idx = is_q ? Q_idx : P_idx;
+    const int64_t base = (int64_t)t * kChunk * d;                    // first entry of the tile
+    const int count = (int)(((int64_t)(is_q ? n : m) * d - base) < (int64_t)kChunk * d ? (int64_t)(is_q ? n : m) * d - base : (int64_t)kChunk * d);
+    const int part = kChunk / kSubTiles * d;                         // entries of a workgroup's part
+    const int run = (part / kWavesSort + kWave - 1) / kWave * kWave; // entries of a wave's run
+    const int my_lo = min(sub * part, count), my_hi = min(my_lo + part, count);
+    int32_t* all = reinterpret_cast<int32_t*>(smem);                 // [r] entries of the tile, then first position
+    int32_t* before = all + r;                                       // [r] entries of the tile before this part
+    int32_t* mine = before + r;                                      // [wave][r] entries of the wave's run, then where the next one goes
+    for (int k = tid; k < (2 + kWavesSort) * r; k += kThreadsSort) all[k] = 0;
+    __syncthreads();
+    bool bad = false;
+    constexpr int kAhead = 8;                                        // loads in flight per thread
+    for (int e0 = 0; e0 < count; e0 += kAhead * kThreadsSort) {
+        int32_t b[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const int e = e0 + k * kThreadsSort + tid;
+            b[k] = e < count ? idx[base + e] : 0;
         }
-        start[l] = (uint32_t)lo;
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const int e = e0 + k * kThreadsSort + tid;
+            if (e >= count) continue;
+            if (b[k] < 0 || b[k] >= r) { bad = true; b[k] = 0; }
+            atomicAdd(&all[b[k]], 1);
+            if (e < my_lo) atomicAdd(&before[b[k]], 1);
+            else if (e < my_hi) atomicAdd(&mine[((e - my_lo) / run) * r + b[k]], 1);
+        }
+    }
+    bad = __syncthreads_or(bad);
+    if (tid == 0) s.bad[tile * kSubTiles + sub] = bad ? 1 : 0;
+    uint32_t* start = s.start + (size_t)tile * (r + 1);
+    int32_t carry = 0;
+    for (int b0 = 0; b0 < r; b0 += kThreadsSort) {
+        const int b = b0 + tid;
+        const int32_t len = b < r ? all[b] : 0;
+        int32_t total;
+        int32_t at = carry + block_exclusive<kWavesSort>(len, s_part, total);
+        carry += total;
+        if (b < r) {
+            if (sub == 0) start[b] = (uint32_t)at;
+            at += before[b];
+#pragma unroll
+            for (int v = 0; v < kWavesSort; ++v) {
+                const int32_t c = mine[v * r + b];
+                mine[v * r + b] = at;
+                at += c;
+            }
+        }
+    }
+    if (sub == 0 && tid == 0) start[r] = (uint32_t)carry;
+    __syncthreads();
+    uint32_t* out = (is_q ? s.sorted_q : s.sorted_p) + base;
+    int32_t* next = mine + w * r;
+    const int bits = 32 - __builtin_clz((unsigned)r);                // columns are < r < 2^bits
+    for (int e0 = my_lo + w * run; e0 < min(my_lo + (w + 1) * run, my_hi); e0 += kWave) {
+        const int e = e0 + lane;
+        const bool live = e < my_hi;
+        int32_t b = live ? idx[base + e] : 0;
+        if (b < 0 || b >= r) b = 0;
+        uint64_t same = __ballot(live);
+        for (int k = 0; k < bits; ++k) {
+            const bool bit = (b >> k) & 1;
+            const uint64_t with = __ballot(bit);
+            same &= bit ? with : ~with;
+        }
+        const int rank = __builtin_popcountll(same & (((uint64_t)1 << lane) - 1));
+        if (live) {
+            const int32_t at = next[b];
+            out[at + rank] = (uint32_t)(base + e);
+            if (rank == 0) next[b] = at + __builtin_popcountll(same);
+        }
+        __builtin_amdgcn_wave_barrier();                             // the next 64 entries read what this step has left
     }
 }
 
@@ -152,29 +226,76 @@ __device__ __forceinline__ void share_of(uint32_t s0, uint32_t s1, int o, int k,
     hi = (int32_t)s0 + (int32_t)(len * (o + 1) / k);
 }
 
-// Owners per column, virtual columns, header: one workgroup of 512 threads.
-__global__ __launch_bounds__(kThreadsGQ) void k_q_owners(uint8_t* __restrict__ plan, DevLayout L, int m, int n, int r, int d, int nchunks,
-                                                         int cap, const uint32_t* __restrict__ start_q, int32_t* __restrict__ owners_g,
-                                                         int32_t* __restrict__ first_v_g, int32_t* __restrict__ v_col,
-                                                         int32_t* __restrict__ v_own, int32_t* __restrict__ status) {
-    __shared__ int32_t s_own[LSP_MAX_R], s_long[LSP_MAX_R], s_first[LSP_MAX_R + 1];
-    __shared__ int32_t s_part[kThreadsGQ];
-    __shared__ int32_t s_vneed;
+// Rows of P^T: pieces of at most kRowPiece entries (one workgroup).
+__device__ __forceinline__ void deal_p(uint8_t* __restrict__ plan, const PlanLayout& L, const BuildScratch& s, int r, int nchunks, int ptiles, int32_t* part) {
     const int tid = threadIdx.x;
-    int mine = 0;
-    for (int b = tid; b < r; b += kThreadsGQ) {
-        int32_t longest = 0;
-        for (int c = 0; c < nchunks; ++c)
-            longest = max(longest, (int32_t)(start_q[(int64_t)c * r + b + 1] - start_q[(int64_t)c * r + b]));
-        s_long[b] = longest;
-        s_own[b] = max(1, (longest + cap - 1) / cap);
-        mine += s_own[b];
+    const uint32_t* start = s.start + (size_t)nchunks * (r + 1);
+    RowItem* items = reinterpret_cast<RowItem*>(plan + L.off_p_item);
+    int32_t entries = 0, pieces = 0;
+    int any = 0;
+    for (int a0 = 0; a0 < r; a0 += kThreadsGQ) {
+        const int a = a0 + tid;
+        int32_t len = 0;
+        if (a < r)
+            for (int t = 0; t < ptiles; ++t) len += (int32_t)(start[(size_t)t * (r + 1) + a + 1] - start[(size_t)t * (r + 1) + a]);
+        int32_t total;
+        const int32_t s0 = entries + block_exclusive<kWavesGQ>(len, part, total);
+        entries += total;
+        const int32_t cut = a < r ? max(1, (len + kRowPiece - 1) / kRowPiece) : 0;
+        int32_t at = pieces + block_exclusive<kWavesGQ>(cut, part, total);
+        pieces += total;
+        if (a < r) {
+            int32_t pos = s0;
+            for (int t = 0; t < ptiles; ++t) {
+                const uint32_t lo = start[(size_t)t * (r + 1) + a], hi = start[(size_t)t * (r + 1) + a + 1];
+                s.p_shift[(size_t)t * r + a] = pos - (int32_t)lo;
+                pos += (int32_t)(hi - lo);
+            }
+            const int split = len > kRowPiece;
+            any |= split;
+            if (len == 0) items[at] = RowItem{a, s0, 0, 0};
+            for (int32_t x = 0; x < len; x += kRowPiece) items[at++] = RowItem{a, s0 + x, min((int32_t)kRowPiece, len - x), split};
+        }
     }
-    s_part[tid] = mine;
+    any = __syncthreads_or(any);
+    if (tid == 0) {
+        PlanHeader* H = reinterpret_cast<PlanHeader*>(plan);
+        H->p_nitems = pieces; H->p_any_split = any ? 1 : 0;
+    }
+}
+
+// One workgroup of 512 threads per chunk, and one for P.  Every chunk's workgroup finds the owners of all columns (they
+// depend on all chunks) and the virtual columns, then deals its chunk's lists to the waves; the first one also writes
+// the tables and the header.  A plan that cannot be (an index outside [0, r), more lists than the lanes can carry) is
+// left without its magic, so that compress calls with this buffer fill S with NaN.
+__global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ plan, PlanLayout L, BuildScratch s, int m, int n, int r, int d, int nchunks,
+                                                          int ptiles, int cap, int32_t* __restrict__ status_out) {
+    __shared__ int32_t s_own[LSP_MAX_R], s_first[LSP_MAX_R], s_part[kWavesGQ];
+    __shared__ int16_t s_vcol[kMaxSlots * kThreadsGQ];
+    __shared__ int32_t s_vown[kMaxSlots * kThreadsGQ], s_longest[kThreadsGQ];
+    __shared__ uint32_t s_key[kThreadsGQ];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    if ((int)blockIdx.x == nchunks) { deal_p(plan, L, s, r, nchunks, ptiles, s_part); return; }
+    const int c = blockIdx.x;
+    int32_t vneed = 0;
+    for (int b0 = 0; b0 < r; b0 += kThreadsGQ) {
+        const int b = b0 + tid;
+        int32_t longest = 0;
+        if (b < r) {
+#pragma unroll 8
+            for (int k = 0; k < nchunks; ++k) {
+                const uint32_t* st = s.start + (size_t)k * (r + 1) + b;
+                longest = max(longest, (int32_t)(st[1] - st[0]));
+            }
+        }
+        const int32_t own = b < r ? max(1, (longest + cap - 1) / cap) : 0;
+        if (b < r) s_own[b] = own;
+        if (b0 == 0) s_longest[tid] = longest;
+        int32_t total;
+        (void)block_exclusive<kWavesGQ>(own, s_part, total);
+        vneed += total;
+    }
     __syncthreads();
-    if (tid == 0) { int t = 0; for (int k = 0; k < kThreadsGQ; ++k) t += s_part[k]; s_vneed = t; }
-    __syncthreads();
-    const int vneed = s_vneed;
     // lanes left over go, one at a time, to the column whose owners have the longest share (ties: the lower
     // column), as long as that share is at least 64 pairs.  One wave does it, each lane keeping its columns
     // (b = lane + 64 q; r < 512 here, because every column has an owner already) in registers.
@@ -183,7 +304,7 @@ __global__ __launch_bounds__(kThreadsGQ) void k_q_owners(uint8_t* __restrict__ p
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int b = tid + kWave * q;
-            own_l[q] = b < r ? s_own[b] : 1; long_l[q] = b < r ? s_long[b] : -1;
+            own_l[q] = b < r ? s_own[b] : 1; long_l[q] = b < r ? s_longest[b] : -1;
         }
         for (int spare = kThreadsGQ - vneed; spare > 0; --spare) {
             double best = -1.0; int best_b = 0x7FFFFFFF;
@@ -210,269 +331,226 @@ __global__ __launch_bounds__(kThreadsGQ) void k_q_owners(uint8_t* __restrict__ p
         }
     }
     __syncthreads();
-    if (tid == 0) {                                                  // first virtual column of each column
-        int t = 0;
-        for (int b = 0; b < r; ++b) { s_first[b] = t; t += s_own[b]; }
-        s_first[r] = t;
-    }
-    __syncthreads();
-    const int V = s_first[r];
-    PlanHeader* H = reinterpret_cast<PlanHeader*>(plan);
-    if (V > kMaxSlots * kThreadsGQ) {                                // more lists than the lanes can carry: no plan
-        if (tid == 0) {
-            if (status[0] == LSP_OK) status[0] = LSP_ERR_SKEW;
-            status[3] = 1;                                           // the later kernels of the build do nothing
-        }
-        return;
-    }
-    const int nslots = max(1, (V + kThreadsGQ - 1) / kThreadsGQ);
-    for (int v = tid; v < kMaxSlots * kThreadsGQ; v += kThreadsGQ) { v_col[v] = -1; v_own[v] = 0; }
-    __syncthreads();
+    int32_t V = 0;
     int shared = 0;
-    for (int b = tid; b < r; b += kThreadsGQ) {
-        owners_g[b] = s_own[b];
-        first_v_g[b] = s_first[b];
-        shared |= s_own[b] > 1;
-        for (int o = 0; o < s_own[b]; ++o) { v_col[s_first[b] + o] = b; v_own[s_first[b] + o] = o; }
+    for (int b0 = 0; b0 < r; b0 += kThreadsGQ) {                     // first virtual column of each column
+        const int b = b0 + tid;
+        const int32_t own = b < r ? s_own[b] : 0;
+        int32_t total;
+        const int32_t first = V + block_exclusive<kWavesGQ>(own, s_part, total);
+        if (b < r) s_first[b] = first;
+        V += total;
+        shared |= own > 1;
     }
-    if (tid == 0) first_v_g[r] = V;
     shared = __syncthreads_or(shared);
-    uint16_t* vcol = reinterpret_cast<uint16_t*>(plan + L.off_q_vcol);
-    uint16_t* vcnt = reinterpret_cast<uint16_t*>(plan + L.off_q_vcnt);
-    for (int v = tid; v < nslots * kThreadsGQ; v += kThreadsGQ) {
-        const int b = v_col[v];
-        vcol[v] = b < 0 ? (uint16_t)kNoColumn : (uint16_t)((uint32_t)b | (s_own[b] > 1 ? kSharedColumn : 0u));
-        vcnt[v] = (b >= 0 && v_own[v] == 0) ? (uint16_t)s_own[b] : (uint16_t)0;
+    int bad = 0;
+    for (int k = tid; k < (nchunks + ptiles) * kSubTiles; k += kThreadsGQ) bad |= s.bad[k];
+    bad = __syncthreads_or(bad);
+    const int32_t status = bad ? LSP_ERR_INDEX : V > kMaxSlots * kThreadsGQ ? LSP_ERR_SKEW : LSP_OK;
+    if (status_out && c == 0 && tid == 0) *status_out = status;
+    if (status != LSP_OK) return;                                    // the magic has been cleared with the rest of the header
+    for (int v = tid; v < kMaxSlots * kThreadsGQ; v += kThreadsGQ) { s_vcol[v] = -1; s_vown[v] = 0; }
+    __syncthreads();
+    for (int b = tid; b < r; b += kThreadsGQ)
+        for (int o = 0; o < s_own[b]; ++o) { s_vcol[s_first[b] + o] = (int16_t)b; s_vown[s_first[b] + o] = o; }
+    __syncthreads();
+    const int nslots = max(1, (V + kThreadsGQ - 1) / kThreadsGQ);
+    if (c == 0) {
+        uint16_t* vcol = reinterpret_cast<uint16_t*>(plan + L.off_q_vcol);
+        uint16_t* vcnt = reinterpret_cast<uint16_t*>(plan + L.off_q_vcnt);
+        for (int v = tid; v < nslots * kThreadsGQ; v += kThreadsGQ) {
+            const int b = s_vcol[v];
+            vcol[v] = b < 0 ? (uint16_t)kNoColumn : (uint16_t)((uint32_t)b | (s_own[b] > 1 ? kSharedColumn : 0u));
+            vcnt[v] = (b >= 0 && s_vown[v] == 0) ? (uint16_t)s_own[b] : (uint16_t)0;
+        }
+        if (tid == 0) {
+            PlanHeader* H = reinterpret_cast<PlanHeader*>(plan);
+            H->magic = kPlanMagic; H->m = m; H->n = n; H->r = r; H->d = d; H->nchunks = nchunks;
+            H->nslots = nslots; H->nvcols = V; H->list_cap = cap;
+            H->q_any_shared = shared ? 1 : 0; H->q_permuted = nslots == 1 ? 1 : 0;
+            H->off_q_seg = L.off_q_seg; H->off_q_vcol = L.off_q_vcol; H->off_q_vcnt = L.off_q_vcnt; H->off_q_perm = L.off_q_perm;
+            H->off_q_rows = L.off_q_rows; H->off_p_item = L.off_p_item; H->off_p_ent = L.off_p_ent; H->total_bytes = L.total;
+            H->off_q_src = L.off_q_src; H->off_p_src = L.off_p_src;
+        }
     }
-    if (tid == 0) {
-        H->magic = kPlanMagic; H->m = m; H->n = n; H->r = r; H->d = d; H->nchunks = nchunks;
-        H->nslots = nslots; H->nvcols = V; H->list_cap = cap;
-        H->q_any_shared = shared ? 1 : 0; H->q_permuted = nslots == 1 ? 1 : 0;
-        H->off_q_seg = L.off_q_seg; H->off_q_vcol = L.off_q_vcol; H->off_q_vcnt = L.off_q_vcnt; H->off_q_perm = L.off_q_perm;
-        H->off_q_rows = L.off_q_rows; H->off_p_item = L.off_p_item; H->off_p_ent = L.off_p_ent; H->total_bytes = L.total;
-        H->off_q_src = L.off_q_src; H->off_p_src = L.off_p_src;
-        status[1] = nslots;
-    }
-}
-
-// Per chunk: which virtual column each thread walks (lists dealt to the waves by length when there is one
-// slot) and the segment lengths.  One workgroup of 512 threads per chunk.
-__global__ __launch_bounds__(kThreadsGQ) void k_q_deal(uint8_t* __restrict__ plan, DevLayout L, int r, const uint32_t* __restrict__ start_q,
-                                                       const int32_t* __restrict__ owners, const int32_t* __restrict__ v_col,
-                                                       const int32_t* __restrict__ v_own, const int32_t* __restrict__ status) {
-    if (status[3]) return;
-    const int nslots = status[1];
-    const int c = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    __shared__ int32_t s_len[kThreadsGQ];
-    __shared__ uint16_t s_order[kThreadsGQ];
+    // which virtual column each thread walks (lists dealt to the waves by length when there is one slot)
     uint32_t* seg = reinterpret_cast<uint32_t*>(plan + L.off_q_seg);
     uint16_t* perm = reinterpret_cast<uint16_t*>(plan + L.off_q_perm);
-    auto len_of = [&](int v) -> int32_t {
-        const int b = v_col[v];
-        if (b < 0) return 0;
-        int32_t lo, hi;
-        share_of(start_q[(int64_t)c * r + b], start_q[(int64_t)c * r + b + 1], v_own[v], owners[b], lo, hi);
-        return hi - lo;
+    const uint32_t* start = s.start + (size_t)c * (r + 1);
+    auto list_of = [&](int v, int32_t& lo, int32_t& hi) {
+        const int b = s_vcol[v];
+        lo = hi = 0;
+        if (b >= 0) share_of(start[b], start[b + 1], s_vown[v], s_own[b], lo, hi);
     };
     const bool permuted = nslots == 1;
     const int k_of_w = w < kWavesGQ / 2 ? w : kWavesGQ + kWavesGQ / 2 - 1 - w;      // group of 64 lists that wave w walks
+    int32_t lo, hi;
+    list_of(tid, lo, hi);
+    // longest first; equal lengths keep their order: a bitonic sort of distinct keys
+    uint32_t key = permuted ? ((uint32_t)(hi - lo) << 9) | (uint32_t)(kThreadsGQ - 1 - tid) : (uint32_t)(kThreadsGQ - 1 - tid);
     if (permuted) {
-        const int32_t mylen = len_of(tid);
-        s_len[tid] = mylen;
-        __syncthreads();
-        int rank = 0;                                                // longest first; equal lengths keep their order
-        for (int u = 0; u < kThreadsGQ; ++u) {
-            const int32_t lu = s_len[u];
-            rank += (lu > mylen) || (lu == mylen && u < tid);
-        }
-        s_order[rank] = (uint16_t)tid;
-        __syncthreads();
-    } else {
-        s_order[tid] = (uint16_t)tid;
-        __syncthreads();
-    }
-    const int walked_p = s_order[k_of_w * kWave + lane];
-    perm[(size_t)c * kThreadsGQ + tid] = (uint16_t)walked_p;
-    for (int s = 0; s < nslots; ++s) {
-        const int v = permuted ? walked_p : s * kThreadsGQ + tid;
-        int32_t longest = len_of(v);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off));
-        if (lane == 0) seg[((size_t)c * nslots + s) * kWavesGQ + w] = (uint32_t)((longest + kSegBatch - 1) / kSegBatch * kSegBatch);
-    }
-}
-
-// Stream positions: wave w's rows are contiguous over all chunks and slots, followed by kStreamSlack padding rows.
-__global__ __launch_bounds__(64) void k_q_rowstart(uint8_t* __restrict__ plan, DevLayout L, int nchunks, uint32_t* __restrict__ seg_start,
-                                                   int32_t* __restrict__ status) {
-    if (status[3]) return;
-    const int nslots = status[1];
-    const uint32_t* seg = reinterpret_cast<const uint32_t*>(plan + L.off_q_seg);
-    __shared__ uint32_t s_total[kWavesGQ];
-    const int w = threadIdx.x;
-    if (w < kWavesGQ) {
-        uint32_t t = 0;
-        for (int cs = 0; cs < nchunks * nslots; ++cs) t += seg[(size_t)cs * kWavesGQ + w];
-        s_total[w] = t + kStreamSlack;
+        for (int size = 2; size <= kThreadsGQ; size <<= 1)
+            for (int step = size >> 1; step > 0; step >>= 1) {
+                uint32_t other;
+                if (step < kWave) {
+                    other = (uint32_t)__shfl_xor((int)key, step);
+                } else {
+                    __syncthreads();
+                    s_key[tid] = key;
+                    __syncthreads();
+                    other = s_key[tid ^ step];
+                }
+                const bool larger = ((tid & step) == 0) == ((tid & size) == 0);     // this place takes the larger of the two
+                key = (key > other) == larger ? key : other;
+            }
     }
     __syncthreads();
-    if (w < kWavesGQ) {
-        uint32_t row = 0;
-        for (int k = 0; k < w; ++k) row += s_total[k];
-        PlanHeader* H = reinterpret_cast<PlanHeader*>(plan);
-        H->q_stream_row[w] = row;
-        for (int cs = 0; cs < nchunks * nslots; ++cs) {
-            seg_start[(size_t)cs * kWavesGQ + w] = row;
-            row += seg[(size_t)cs * kWavesGQ + w];
-        }
-        if (w == kWavesGQ - 1) { H->q_total_rows = (int32_t)(row + kStreamSlack); status[2] = (int32_t)(row + kStreamSlack); }
+    s_key[tid] = key;
+    __syncthreads();
+    const int walked_p = kThreadsGQ - 1 - (int)(s_key[k_of_w * kWave + lane] & (kThreadsGQ - 1));
+    perm[(size_t)c * kThreadsGQ + tid] = (uint16_t)walked_p;
+    for (int slot = 0; slot < nslots; ++slot) {
+        list_of(permuted ? walked_p : slot * kThreadsGQ + tid, lo, hi);
+        const size_t at = ((size_t)c * nslots + slot) * kThreadsGQ + tid;
+        s.seg_lo[at] = lo;
+        s.seg_n[at] = hi - lo;
+        int32_t longest = hi - lo;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off));
+        if (lane == 0) seg[((size_t)c * nslots + slot) * kWavesGQ + w] = (uint32_t)((longest + kSegBatch - 1) / kSegBatch * kSegBatch);
     }
 }
 
-// The interleaved rows: block (cs, w) writes one segment; blocks past the segments write a wave's slack rows.
-__global__ __launch_bounds__(256) void k_q_rows(uint8_t* __restrict__ plan, DevLayout L, int r, int d, int nchunks, int ebits,
-                                                const uint64_t* __restrict__ sorted, const float* __restrict__ Q_val,
-                                                const uint32_t* __restrict__ start_q, const int32_t* __restrict__ owners,
-                                                const int32_t* __restrict__ v_col, const int32_t* __restrict__ v_own,
-                                                const uint32_t* __restrict__ seg_start, const int32_t* __restrict__ status) {
-    if (status[3]) return;
-    const int nslots = status[1];
+// First row of segment cs of wave w's stream: the streams follow one another, each behind kStreamSlack padding rows of
+// the one before.  (w = kWavesGQ, cs = 0: all rows.)  Summed anew by every workgroup, all of its threads together.
+constexpr int kThreadsRows = 512;
+__device__ __forceinline__ uint32_t stream_row(const uint32_t* __restrict__ seg, int ncs, int w, int cs, int32_t* part) {
+    int32_t sum = 0;
+    for (int k = threadIdx.x; k < ncs * kWavesGQ; k += kThreadsRows) {
+        const int kw = k % kWavesGQ, kc = k / kWavesGQ;
+        if (kw < w || (kw == w && kc < cs)) sum += (int32_t)seg[k];
+    }
+    int32_t total;
+    (void)block_exclusive<kThreadsRows / kWave>(sum, part, total);
+    return (uint32_t)total + (uint32_t)w * kStreamSlack;
+}
+
+// The interleaved rows: workgroup cs * 8 + w writes one segment, the next eight the waves' slack rows (and the header's stream
+// positions), `pblocks` the entries of P^T, the rest clears what lies behind the last row.
+__global__ __launch_bounds__(kThreadsRows) void k_plan_rows(uint8_t* __restrict__ plan, PlanLayout L, BuildScratch s, const int32_t* __restrict__ P_idx,
+                                                            const float* __restrict__ P_val, const float* __restrict__ Q_val, int m, int r, int d,
+                                                            int nchunks, int pblocks, int64_t max_rows) {
+    PlanHeader* H = reinterpret_cast<PlanHeader*>(plan);
+    if (H->magic != kPlanMagic) return;
+    __shared__ int32_t s_part[kThreadsRows / kWave];
+    __shared__ int32_t s_lo[kWave], s_n[kWave];
+    const int tid = threadIdx.x;
+    const int nslots = H->nslots, ncs = nchunks * nslots;
     const uint32_t* seg = reinterpret_cast<const uint32_t*>(plan + L.off_q_seg);
-    const uint16_t* perm = reinterpret_cast<const uint16_t*>(plan + L.off_q_perm);
     uint2* rows = reinterpret_cast<uint2*>(plan + L.off_q_rows);
     uint32_t* qsrc = reinterpret_cast<uint32_t*>(plan + L.off_q_src);
-    const uint2 pad_pair = make_uint2((uint32_t)kChunk * 16u, 0u);
-    auto slot_of = [](size_t rw, int lane) { return ((rw >> 1) * kWave + (size_t)lane) * 2 + (rw & 1); };
-    const int nseg = nchunks * nslots * kWavesGQ;
-    const int blk = blockIdx.x;
-    if (blk >= nseg + kWavesGQ) return;
-    if (blk >= nseg) {                                               // slack rows behind wave w's stream
-        const int w = blk - nseg;
-        const PlanHeader* H = reinterpret_cast<const PlanHeader*>(plan);
-        const uint32_t end = w + 1 < kWavesGQ ? H->q_stream_row[w + 1] : (uint32_t)status[2];
-        for (int q = threadIdx.x; q < kStreamSlack * kWave; q += 256) {
-            const size_t slot = slot_of((size_t)end - kStreamSlack + q / kWave, q % kWave);
-            rows[slot] = pad_pair; qsrc[slot] = kNoSource;
+    const uint32_t pad = (uint32_t)kChunk * 16u;
+    int blk = blockIdx.x;
+    const int segments = nchunks * kMaxSlots * kWavesGQ;
+    if (blk < segments) {
+        if (blk >= ncs * kWavesGQ) return;
+        const int cs = blk / kWavesGQ, w = blk % kWavesGQ, c = cs / nslots;
+        if (tid < kWave) {
+            const size_t at = (size_t)cs * kThreadsGQ + w * kWave + tid;
+            s_lo[tid] = s.seg_lo[at]; s_n[tid] = s.seg_n[at];
+        }
+        const int len = (int)seg[(size_t)cs * kWavesGQ + w];
+        const uint32_t row0 = stream_row(seg, ncs, w, cs, s_part);   // (its barriers also order s_lo and s_n)
+        const uint32_t* sorted = s.sorted_q + (size_t)c * kChunk * d;
+        // a thread takes rows 2 p and 2 p + 1 of a lane, eight entries in flight
+        constexpr int kAhead = 4;
+        for (int q0 = 0; q0 < len / 2 * kWave; q0 += kAhead * kThreadsRows) {
+            uint32_t src[kAhead][2];
+            float val[kAhead][2];
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                const int q = q0 + k * kThreadsRows + tid, lane = q % kWave, e = q / kWave * 2;
+                const bool in = e < len;
+                src[k][0] = in && e < s_n[lane] ? sorted[s_lo[lane] + e] : kNoSource;
+                src[k][1] = in && e + 1 < s_n[lane] ? sorted[s_lo[lane] + e + 1] : kNoSource;
+            }
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) val[k][h] = src[k][h] != kNoSource ? Q_val[src[k][h]] : 0.0f;
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                const int q = q0 + k * kThreadsRows + tid, lane = q % kWave, e = q / kWave * 2;
+                if (e >= len) continue;
+                uint32_t off[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) off[h] = src[k][h] != kNoSource ? chunk_col_offset(src[k][h] / (uint32_t)d - (uint32_t)c * kChunk) : pad;
+                const size_t slot = ((size_t)((row0 + e) >> 1) * kWave + lane) * 2;
+                *reinterpret_cast<uint4*>(rows + slot) = make_uint4(off[0], __float_as_uint(val[k][0]), off[1], __float_as_uint(val[k][1]));
+                *reinterpret_cast<uint2*>(qsrc + slot) = make_uint2(src[k][0], src[k][1]);
+            }
         }
         return;
     }
-    const int cs = blk / kWavesGQ, w = blk % kWavesGQ, c = cs / nslots, s = cs % nslots;
-    const int len = (int)seg[(size_t)cs * kWavesGQ + w];
-    const uint32_t row0 = seg_start[(size_t)cs * kWavesGQ + w];
-    __shared__ int32_t s_lo[kWave], s_n[kWave];
-    if (threadIdx.x < kWave) {
-        const int lane = threadIdx.x;
-        const int v = nslots == 1 ? (int)perm[(size_t)c * kThreadsGQ + w * kWave + lane] : s * kThreadsGQ + w * kWave + lane;
-        const int b = v_col[v];
-        int32_t lo = 0, hi = 0;
-        if (b >= 0) share_of(start_q[(int64_t)c * r + b], start_q[(int64_t)c * r + b + 1], v_own[v], owners[b], lo, hi);
-        s_lo[lane] = lo; s_n[lane] = hi - lo;
-    }
-    __syncthreads();
-    const uint64_t emask = ((uint64_t)1 << ebits) - 1;
-    for (int q = threadIdx.x; q < len * kWave; q += 256) {
-        const int e = q / kWave, lane = q % kWave;
-        const size_t slot = slot_of((size_t)row0 + e, lane);
-        if (e < s_n[lane]) {
-            const uint32_t src = (uint32_t)(sorted[s_lo[lane] + e] & emask);       // flat position j * d + k
-            const uint32_t jl = (src / (uint32_t)d) - (uint32_t)c * kChunk;
-            rows[slot] = make_uint2(chunk_col_offset(jl), __float_as_uint(Q_val[src]));
-            qsrc[slot] = src;
-        } else {
-            rows[slot] = pad_pair; qsrc[slot] = kNoSource;
+    blk -= segments;
+    if (blk < kWavesGQ) {                                            // slack rows behind wave w's stream
+        const uint32_t first = stream_row(seg, ncs, blk, 0, s_part), next = stream_row(seg, ncs, blk + 1, 0, s_part);
+        for (int q = tid; q < kStreamSlack / 2 * kWave; q += kThreadsRows) {
+            const size_t slot = ((size_t)((next - kStreamSlack) >> 1) * kWave + q) * 2;
+            *reinterpret_cast<uint4*>(rows + slot) = make_uint4(pad, 0u, pad, 0u);
+            *reinterpret_cast<uint2*>(qsrc + slot) = make_uint2(kNoSource, kNoSource);
         }
+        if (tid == 0) {
+            H->q_stream_row[blk] = first;
+            if (blk == kWavesGQ - 1) H->q_total_rows = (int32_t)next;
+        }
+        return;
     }
-}
-
-// Rows of P^T: pieces of at most kRowPiece entries; one workgroup.
-__global__ __launch_bounds__(kThreadsGQ) void k_p_items(uint8_t* __restrict__ plan, DevLayout L, int r, const uint32_t* __restrict__ start_p,
-                                                        int32_t* __restrict__ item_base, const int32_t* __restrict__ status) {
-    if (status[3]) return;
-    __shared__ int32_t s_cnt[LSP_MAX_R];
-    __shared__ int32_t s_any;
-    const int tid = threadIdx.x;
-    if (tid == 0) s_any = 0;
-    __syncthreads();
-    for (int a = tid; a < r; a += kThreadsGQ) {
-        const int32_t n_a = (int32_t)(start_p[a + 1] - start_p[a]);
-        s_cnt[a] = max(1, (n_a + kRowPiece - 1) / kRowPiece);
-        if (n_a > kRowPiece) s_any = 1;
+    blk -= kWavesGQ;
+    if (blk < pblocks) {
+        uint2* pent = reinterpret_cast<uint2*>(plan + L.off_p_ent);
+        uint32_t* psrc = reinterpret_cast<uint32_t*>(plan + L.off_p_src);
+        const int64_t np = (int64_t)m * d;
+        for (int64_t p = (int64_t)blk * kThreadsRows + tid; p < np; p += (int64_t)pblocks * kThreadsRows) {
+            const uint32_t src = s.sorted_p[p];
+            const int64_t t = p / ((int64_t)kChunk * d);
+            const int64_t at = p - t * kChunk * d + s.p_shift[t * r + P_idx[src]];
+            pent[at] = make_uint2(src / (uint32_t)d, __float_as_uint(P_val[src]));
+            psrc[at] = src;
+        }
+        return;
     }
-    __syncthreads();
-    if (tid == 0) {
-        int t = 0;
-        for (int a = 0; a < r; ++a) { item_base[a] = t; t += s_cnt[a]; }
-        item_base[r] = t;
-        PlanHeader* H = reinterpret_cast<PlanHeader*>(plan);
-        H->p_nitems = t; H->p_any_split = s_any;
+    blk -= pblocks;
+    const int zblocks = (int)gridDim.x - segments - kWavesGQ - pblocks;
+    const int64_t used = (int64_t)stream_row(seg, ncs, kWavesGQ, 0, s_part) * kWave, most = max_rows * kWave;
+    for (int64_t k = used / 2 + (int64_t)blk * kThreadsRows + tid; k < most / 2; k += (int64_t)zblocks * kThreadsRows) {
+        reinterpret_cast<uint4*>(rows)[k] = make_uint4(0u, 0u, 0u, 0u);
+        reinterpret_cast<uint2*>(qsrc)[k] = make_uint2(0u, 0u);
     }
-    __syncthreads();
-    RowItem* items = reinterpret_cast<RowItem*>(plan + L.off_p_item);
-    for (int a = tid; a < r; a += kThreadsGQ) {
-        const int32_t s0 = (int32_t)start_p[a], s1 = (int32_t)start_p[a + 1];
-        const int split = (s1 - s0) > kRowPiece;
-        int at = item_base[a];
-        if (s1 == s0) { items[at] = RowItem{a, s0, 0, 0}; continue; }
-        for (int32_t s = s0; s < s1; s += kRowPiece) items[at++] = RowItem{a, s, min((int32_t)kRowPiece, s1 - s), split};
-    }
-}
-
-__global__ __launch_bounds__(256) void k_p_entries(uint8_t* __restrict__ plan, DevLayout L, int64_t count, int d, int ebits,
-                                                   const uint64_t* __restrict__ sorted, const float* __restrict__ P_val,
-                                                   const int32_t* __restrict__ status) {
-    if (status[3]) return;
-    uint2* pent = reinterpret_cast<uint2*>(plan + L.off_p_ent);
-    uint32_t* psrc = reinterpret_cast<uint32_t*>(plan + L.off_p_src);
-    const uint64_t emask = ((uint64_t)1 << ebits) - 1;
-    for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < count; p += (int64_t)gridDim.x * 256) {
-        const uint32_t src = (uint32_t)(sorted[p] & emask);
-        pent[p] = make_uint2(src / (uint32_t)d, __float_as_uint(P_val[src]));
-        psrc[p] = src;
-    }
-}
-
-// A failed build leaves no plan behind: the magic is cleared, so compress calls with this buffer fill S with NaN.
-__global__ void k_plan_seal(uint8_t* __restrict__ plan, const int32_t* __restrict__ status, int32_t* __restrict__ status_out) {
-    if (status[0] != LSP_OK) reinterpret_cast<PlanHeader*>(plan)->magic = 0u;
-    if (status_out) *status_out = status[0];
 }
 
 hipError_t launch_plan_build(const int32_t* P_idx, const float* P_val, const int32_t* Q_idx, const float* Q_val,
                              int64_t m, int64_t n, int32_t r, int32_t d, uint8_t* plan, uint8_t* workspace,
                              int32_t* status_out, hipStream_t st) {
-    BuildScratch S;
-    build_scratch(workspace, m, n, r, d, &S);
-    const DevLayout L = plan_layout(m, n, r, d);
-    const int nchunks = (int)((n + kChunk - 1) / kChunk);
-    const int cap = plan_list_cap(r, d);
-    const int64_t nq = n * d, np = m * d;
-    const int ebits_q = bits_for((uint64_t)nq), ebits_p = bits_for((uint64_t)np);
-    const int lbits_q = bits_for((uint64_t)nchunks * (uint64_t)r + 1), lbits_p = bits_for((uint64_t)r + 1);
-    auto grid_for = [](int64_t count) { return dim3((unsigned)std::min<int64_t>((count + 255) / 256, 4096)); };
+    BuildScratch s;
+    build_scratch(workspace, m, n, r, d, &s);
+    const PlanLayout L = plan_layout(m, n, r, d);
+    const int nchunks = (int)((n + kChunk - 1) / kChunk), ptiles = (int)((m + kChunk - 1) / kChunk);
+    const int64_t max_rows = (int64_t)plan_max_rows(n, r, d);
     hipError_t e;
-    hipLaunchKernelGGL(k_fill_u32, grid_for((int64_t)(L.total / 4)), dim3(256), 0, st, reinterpret_cast<uint32_t*>(plan), (int64_t)(L.total / 4), 0u);
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, st, reinterpret_cast<uint32_t*>(S.status), (int64_t)64, 0u);
-    // ---- Q
-    hipLaunchKernelGGL(k_build_keys, grid_for(nq), dim3(256), 0, st, Q_idx, nq, (int)d, (int)r, (int)kChunk, ebits_q, S.keys_a, S.status);
+    const size_t lds = (size_t)(2 + kWavesSort) * r * sizeof(int32_t);
+    if ((e = allow_dynamic_lds<k_plan_sort>((size_t)(2 + kWavesSort) * LSP_MAX_R * sizeof(int32_t))) != hipSuccess) return e;
+    const unsigned clear = (unsigned)std::min<size_t>((L.off_q_rows + (L.off_p_ent - L.off_p_item)) / (4 * kThreadsSort) + 1, 256);
+    hipLaunchKernelGGL(k_plan_sort, dim3((unsigned)(nchunks + ptiles) * kSubTiles + clear), dim3(kThreadsSort), lds, st, plan, L, s, P_idx, Q_idx,
+                       (int)m, (int)n, (int)r, (int)d, nchunks, ptiles, max_rows);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    size_t tmp = S.sort_tmp_bytes;
-    if ((e = rocprim::radix_sort_keys(S.sort_tmp, tmp, S.keys_a, S.keys_b, (size_t)nq, 0u, (unsigned)(ebits_q + lbits_q), st, false)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_list_bounds, grid_for((int64_t)nchunks * r + 1), dim3(256), 0, st, S.keys_b, nq, ebits_q, (int64_t)nchunks * r, S.start_q);
-    hipLaunchKernelGGL(k_q_owners, dim3(1), dim3(kThreadsGQ), 0, st, plan, L, (int)m, (int)n, (int)r, (int)d, nchunks, cap, S.start_q,
-                       S.owners, S.first_v, S.v_col, S.v_own, S.status);
-    hipLaunchKernelGGL(k_q_deal, dim3((unsigned)nchunks), dim3(kThreadsGQ), 0, st, plan, L, (int)r, S.start_q, S.owners, S.v_col, S.v_own, S.status);
-    hipLaunchKernelGGL(k_q_rowstart, dim3(1), dim3(64), 0, st, plan, L, nchunks, S.seg_start, S.status);
-    hipLaunchKernelGGL(k_q_rows, dim3((unsigned)(nchunks * kMaxSlots * kWavesGQ + kWavesGQ)), dim3(256), 0, st, plan, L, (int)r, (int)d, nchunks,
-                       ebits_q, S.keys_b, Q_val, S.start_q, S.owners, S.v_col, S.v_own, S.seg_start, S.status);
+    hipLaunchKernelGGL(k_plan_deal, dim3((unsigned)nchunks + 1), dim3(kThreadsGQ), 0, st, plan, L, s, (int)m, (int)n, (int)r, (int)d, nchunks, ptiles,
+                       plan_list_cap(r, d), status_out);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    // ---- P (the key buffers are free again: work on one stream is ordered)
-    hipLaunchKernelGGL(k_build_keys, grid_for(np), dim3(256), 0, st, P_idx, np, (int)d, (int)r, 0, ebits_p, S.keys_a, S.status);
-    tmp = S.sort_tmp_bytes;
-    if ((e = rocprim::radix_sort_keys(S.sort_tmp, tmp, S.keys_a, S.keys_b, (size_t)np, 0u, (unsigned)(ebits_p + lbits_p), st, false)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_list_bounds, grid_for((int64_t)r + 1), dim3(256), 0, st, S.keys_b, np, ebits_p, (int64_t)r, S.start_p);
-    hipLaunchKernelGGL(k_p_items, dim3(1), dim3(kThreadsGQ), 0, st, plan, L, (int)r, S.start_p, S.item_base, S.status);
-    hipLaunchKernelGGL(k_p_entries, grid_for(np), dim3(256), 0, st, plan, L, np, (int)d, ebits_p, S.keys_b, P_val, S.status);
-    hipLaunchKernelGGL(k_plan_seal, dim3(1), dim3(1), 0, st, plan, S.status, status_out);
+    const int pblocks = (int)std::min<int64_t>((m * d + kThreadsRows - 1) / kThreadsRows, 512);
+    const int zblocks = (int)std::min<int64_t>((max_rows * kWave / 2 + 4 * kThreadsRows - 1) / (4 * kThreadsRows), 512);
+    hipLaunchKernelGGL(k_plan_rows, dim3((unsigned)(nchunks * kMaxSlots * kWavesGQ + kWavesGQ + pblocks + zblocks)), dim3(kThreadsRows), 0, st, plan, L, s,
+                       P_idx, P_val, Q_val, (int)m, (int)r, (int)d, nchunks, pblocks, max_rows);
     return hipGetLastError();
 }
 

@@ -53,6 +53,21 @@ def test_device_plan_equals_host_plan(m, n, r, d, dist):
     assert bad.size == 0, f"{bad.size} bytes differ, first at offset {bad[:4]}"
 
 
+@pytest.mark.parametrize("m,n,r,d,dist", [
+    (2049, 2047, 33, 1, "uniform"),     # a tile of one row; a part of the sort smaller than one wave's step
+    (257, 2304, 1, 1, "uniform"),       # one column: every entry of a step of 64 meets every other
+    (300, 2303, 2048, 64, "uniform"),   # the most columns and the most entries a tile can have
+    (4097, 513, 512, 3, "zipf"),        # three tiles of P, parts that end inside a step
+])
+def test_device_plan_at_the_edges_of_the_sort(m, n, r, d, dist):
+    print(f"[case] device plan m={m} n={n} r={r} d={d} {dist}", flush=True)
+    rc_host, host, rc_dev, dev_plan, _ = _both(m, n, r, d, dist, seed=77 + m + n + r)
+    assert rc_host == rc_dev
+    if rc_host == 0:
+        bad = np.flatnonzero(host != dev_plan)
+        assert bad.size == 0, f"{bad.size} bytes differ, first at offset {bad[:4]}"
+
+
 def test_device_plan_reports_skew_and_bad_indices():
     import torch
     import paper_2406_10181_amd as L
