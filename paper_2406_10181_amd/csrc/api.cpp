@@ -238,20 +238,8 @@ int lsp_decompress_apply_grouped(const lsp_apply_item* items, int32_t count, int
         g.m[p] = (int32_t)it.m; g.n[p] = (int32_t)it.n;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (lsp::apply_group_uniform(g, r, d)) {
-        hipError_t e = lsp::launch_decompress(g, r, d, dtype, st);
-        return e == hipSuccess ? LSP_OK : fail_launch(e);
-    }
-    for (int p = 0; p < count; ++p) {
-        lsp::ApplyGroup one;
-        std::memset(&one, 0, sizeof(one));
-        one.count = 1;
-        one.W[0] = g.W[p]; one.S[0] = g.S[p]; one.P_idx[0] = g.P_idx[p]; one.P_val[0] = g.P_val[p];
-        one.Q_idx[0] = g.Q_idx[p]; one.Q_val[0] = g.Q_val[p]; one.m[0] = g.m[p]; one.n[0] = g.n[p];
-        hipError_t e = lsp::launch_decompress(one, r, d, dtype, st);
-        if (e != hipSuccess) return fail_launch(e);
-    }
-    return LSP_OK;
+    hipError_t e = lsp::launch_decompress(g, r, d, dtype, st);
+    return e == hipSuccess ? LSP_OK : fail_launch(e);
 }
 
 int lsp_decompress_apply(void* W, const float* S, const int32_t* P_idx, const float* P_val,

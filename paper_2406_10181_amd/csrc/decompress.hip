@@ -11,13 +11,13 @@
 // makes in Alg. 1): with S = P^T G Q they rebuild P S Q^T tile by tile in registers, read G where
 // the apply step reads W, and instead of storing anything add up (P S Q^T - G)^2 and G^2; every
 // workgroup leaves its two sums in a list that k_bias_finish adds in a fixed order.
+#include <type_traits>
 #include <utility>
 
 #include "lsp_internal.h"
 
 namespace lsp {
 
-constexpr int kThreadsD = 256;   // generic kernel
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 template <typename D, int CPT> struct Vec;     // CPT consecutive elements of W
@@ -79,144 +79,156 @@ __device__ __forceinline__ void block_sum2(float x, float y, float2* red, float2
     }
 }
 
-// phase 1 (generic kernel):  Us[plane][b] (float4 = 4 rows) = sum_k P_val[i][k] S[P_idx[i][k]][b]
-// `plane` is the distance between planes in float4 units (>= r).
-template <int RG>
-__device__ __forceinline__ void build_u_tile(float4* Us, const float* __restrict__ S,
+// Phase 1, for d = DD in steps of AHEAD (or, with DD = 0, any d): the R * d (row of S, value) pairs of the tile go to LDS first, then every
+// work item (row of the tile, 4 consecutive columns b) issues its 128-bit loads of S back to back, so the whole gather
+// costs few memory round trips.  A row's last quad starts at r - 4 when r is no multiple of 4: some columns are then
+// made twice, with the same result.  Us[plane][b] is a float4 over the plane's 4 rows: element (b, t) lives at float
+// index 4 b + t.
+template <int RG, int DD, int AHEAD, int PS, int NT>
+__device__ __forceinline__ void build_u_tile(uint8_t* smem, int2* pent, const float* __restrict__ S,
                                              const int32_t* __restrict__ P_idx, const float* __restrict__ P_val,
-                                             int64_t i0, int m, int r, int d, int plane) {
-    for (int b = threadIdx.x; b < r; b += kThreadsD) {
-#pragma unroll
-        for (int g = 0; g < RG; ++g) {
-            float u[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int64_t i = i0 + g * 4 + t;
-                if (i < m) {
-                    for (int k = 0; k < d; ++k) {
-                        const int a = P_idx[i * d + k];           // uniform over the workgroup
-                        const float v = P_val[i * d + k];
-                        u[t] = fmaf(v, S[(int64_t)a * r + b], u[t]);
-                    }
-                }
-            }
-            Us[g * plane + b] = make_float4(u[0], u[1], u[2], u[3]);
-        }
-    }
-}
-
-// phase 1 (fast kernel, r % 4 == 0): the R*DD (row of S, value) pairs of the tile go to LDS first,
-// then every work item (row t of the tile, 4 consecutive columns b) issues its DD 128-bit loads of
-// S back to back, so the whole gather costs two memory round trips.
-template <int RG, int DD, int PS, int NT>
-__device__ __forceinline__ void build_u_tile_fast(uint8_t* smem, int2* pent, const float* __restrict__ S,
-                                                  const int32_t* __restrict__ P_idx, const float* __restrict__ P_val,
-                                                  int64_t i0, int m, int r) {
+                                             int64_t i0, int m, int r, int dim) {
+    typedef f32x4 loose __attribute__((aligned(4)));
     constexpr int R = 4 * RG;
-    for (int q = threadIdx.x; q < R * DD; q += NT) {
-        const int64_t i = i0 + q / DD;
+    const int d = DD > 0 ? DD : dim;
+    for (int q = threadIdx.x; q < R * d; q += NT) {
+        const int64_t at = i0 * d + q;
         int2 e = make_int2(0, 0);                                   // rows past m: value 0, row 0 of S
-        if (i < m) e = make_int2(P_idx[i * DD + q % DD], __float_as_int(P_val[i * DD + q % DD]));
+        if (at < (int64_t)m * d) e = make_int2(P_idx[at], __float_as_int(P_val[at]));
         pent[q] = e;
     }
     __syncthreads();
-    const int r4 = r >> 2;
-    for (int q = threadIdx.x; q < r4 * R; q += NT) {
-        const int row = q / r4, b4 = q - row * r4;                  // row of the tile, column quad
-        f32x4 x[DD];
-#pragma unroll
-        for (int k = 0; k < DD; ++k)
-            x[k] = *reinterpret_cast<const f32x4*>(S + (int64_t)pent[row * DD + k].x * r + b4 * 4);
-        f32x4 u = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int k = 0; k < DD; ++k) {
-            const float v = __int_as_float(pent[row * DD + k].y);
-            u.x = fmaf(v, x[k].x, u.x); u.y = fmaf(v, x[k].y, u.y);
-            u.z = fmaf(v, x[k].z, u.z); u.w = fmaf(v, x[k].w, u.w);
+    if (r < 4) {
+        for (int q = threadIdx.x; q < R * r; q += NT) {
+            const int row = q / r, b = q - row * r;
+            float u = 0.0f;
+            for (int k = 0; k < d; ++k) u = fmaf(__int_as_float(pent[row * d + k].y), S[pent[row * d + k].x * r + b], u);
+            reinterpret_cast<float*>(smem + (row >> 2) * PS)[b * 4 + (row & 3)] = u;
         }
-        // Us[plane][b] is a float4 over the plane's 4 rows: element (b, t) lives at float index 4 b + t
-        float* dst = reinterpret_cast<float*>(smem + (row >> 2) * PS) + (b4 * 4) * 4 + (row & 3);
+        return;
+    }
+    const int quads = (r + 3) >> 2;
+    for (int q = threadIdx.x; q < quads * R; q += NT) {
+        const int row = q / quads, b4 = q - row * quads;            // row of the tile, column quad
+        const int b = min(b4 * 4, r - 4);
+        f32x4 u = {0.0f, 0.0f, 0.0f, 0.0f};
+        auto add = [&](int k0, auto count) {
+            constexpr int N = decltype(count)::value;
+            f32x4 x[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) x[k] = *reinterpret_cast<const loose*>(S + (int64_t)pent[row * d + k0 + k].x * r + b);
+#pragma unroll
+            for (int k = 0; k < N; ++k) {
+                const float v = __int_as_float(pent[row * d + k0 + k].y);
+                u.x = fmaf(v, x[k].x, u.x); u.y = fmaf(v, x[k].y, u.y);
+                u.z = fmaf(v, x[k].z, u.z); u.w = fmaf(v, x[k].w, u.w);
+            }
+        };
+        if constexpr (DD > 0) {
+#pragma unroll
+            for (int k = 0; k < DD; k += AHEAD) add(k, std::integral_constant<int, AHEAD>{});
+        } else {
+            int k = 0;
+            for (; k + 8 <= d; k += 8) add(k, std::integral_constant<int, 8>{});
+            for (; k + 4 <= d; k += 4) add(k, std::integral_constant<int, 4>{});
+            for (; k < d; ++k) add(k, std::integral_constant<int, 1>{});
+        }
+        float* dst = reinterpret_cast<float*>(smem + (row >> 2) * PS) + b * 4 + (row & 3);
         dst[0] = u.x; dst[4] = u.y; dst[8] = u.z; dst[12] = u.w;
     }
 }
 
-// Fast kernel: DD = compile-time d, CPT columns per thread, n % CPT == 0, r % 4 == 0.  PS = bytes
-// between the 4-row planes of U in LDS, a compile-time constant >= 16 r so that the plane offset
-// folds into the immediate offset of the LDS read and a gather costs no address arithmetic.
-// All loads of a pass (the thread's rows of Q and its R x CPT patch of W) are issued before the
-// gathers start, so one pass costs one HBM round trip; many waves per CU overlap the passes.
-template <typename D, int RG, int DD, int PS, int NT, int CPT, int kDepth, bool NORMS>
-__global__ __launch_bounds__(NT) void k_decompress(const ApplyGroup grp, int r, float2* __restrict__ partial, int split_from) {
+// The rows of a block of W (or G) as buffers of their own: lanes past a row's end load zero and store nothing, and so does
+// a whole row past the matrix, without a branch.  Branches around loads and stores are what the kernel below must not have: the
+// compiler counts the memory operations in flight over every path to a use, and an operation that one path skips makes
+// the use wait for younger ones as well.
+typedef __amdgpu_buffer_rsrc_t RowBuffer;
+template <typename D> struct RowBlock {
+    char* base;                                                     // first row of the block
+    int64_t stride;                                                 // bytes from row to row
+    int rows;                                                       // rows of the block inside the matrix
+    int n;
+    // row t from column col on (a pass: at most a few thousand columns)
+    __device__ __forceinline__ RowBuffer from(int t, int col) const {
+        const int left = n - col < 65536 ? n - col : 65536;
+        return __builtin_amdgcn_make_buffer_rsrc(base + t * stride + (int64_t)col * D::size, 0, t < rows ? left * D::size : 0, 0x00027000);
+    }
+};
+constexpr int kNonTemporal = 2;                                     // cache policy of the streaming accesses
+template <typename V> __device__ __forceinline__ V row_load(RowBuffer b, uint32_t offset) {
+    V out;
+    if constexpr (sizeof(V) == 2) { const uint16_t t = __builtin_amdgcn_raw_buffer_load_b16(b, (int)offset, 0, kNonTemporal); __builtin_memcpy(&out, &t, 2); }
+    else if constexpr (sizeof(V) == 4) { const uint32_t t = __builtin_amdgcn_raw_buffer_load_b32(b, (int)offset, 0, kNonTemporal); __builtin_memcpy(&out, &t, 4); }
+    else { const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(b, (int)offset, 0, kNonTemporal); __builtin_memcpy(&out, &t, 8); }
+    return out;
+}
+template <typename V> __device__ __forceinline__ void row_store(RowBuffer b, uint32_t offset, const V& v) {
+    if constexpr (sizeof(V) == 2) { uint16_t t; __builtin_memcpy(&t, &v, 2); __builtin_amdgcn_raw_buffer_store_b16(t, b, (int)offset, 0, kNonTemporal); }
+    else if constexpr (sizeof(V) == 4) { uint32_t t; __builtin_memcpy(&t, &v, 4); __builtin_amdgcn_raw_buffer_store_b32(t, b, (int)offset, 0, kNonTemporal); }
+    else { u32x2 t; __builtin_memcpy(&t, &v, 8); __builtin_amdgcn_raw_buffer_store_b64(t, b, (int)offset, 0, kNonTemporal); }
+}
+
+// Fast kernel: DD = compile-time d, two columns per thread, n even.  PS = bytes between the 4-row planes of U in
+// LDS, a compile-time constant >= 16 r so that the plane offset folds into the immediate offset of the LDS read and a
+// gather costs no address arithmetic.
+// A thread's patch of W (R rows x 2 columns) for the next pass is loaded plane by plane into the registers that the
+// plane just finished has left, so a whole pass is in flight at any time at the cost of one patch; the rows of Q follow
+// at the end of the pass.
+template <typename D, int RG, int DD, int PS, int NT, bool NORMS>
+__global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const ApplyGroup grp, int r, float2* __restrict__ partial) {
     extern __shared__ __align__(16) uint8_t smem[];
+    constexpr int CPT = 2;
     constexpr int R = 4 * RG;
     constexpr int NE = CPT * DD;                                    // entries owned by a thread in one pass
     static_assert(NE % 4 == 0, "entries are loaded 4 at a time");
-    // Row blocks from split_from on are shared by two workgroups, each with half of the passes (both build
-    // the tile of U): the last workgroups of a launch are then half as long, and the CUs finish closer together.
-    int bx = (int)blockIdx.x, half = 0, halves = 1;
-    if (bx >= split_from) {
-        const int t = bx - split_from;
-        bx = split_from + (t >> 1); half = t & 1; halves = 2;
-    }
-    const int prob = group_find(grp.first, grp.count, bx);
-    typename D::elem* __restrict__ W = static_cast<typename D::elem*>(grp.W[prob]);
+    typedef Vec<D, CPT> Patch;
+    // a row block is shared by `parts` workgroups, each with its share of the passes (all build the tile of U)
+    const int prob = group_find(grp.first, grp.count, (int)blockIdx.x);
+    const int unit = (int)blockIdx.x - grp.first[prob], parts = grp.parts[prob];
+    const int block = unit / parts, part = unit - block * parts;
     const float* __restrict__ S = grp.S[prob];
     const int32_t* __restrict__ P_idx = grp.P_idx[prob];
     const float* __restrict__ P_val = grp.P_val[prob];
     const int32_t* __restrict__ Q_idx = grp.Q_idx[prob];
     const float* __restrict__ Q_val = grp.Q_val[prob];
     const int m = grp.m[prob], n = grp.n[prob];
-    const int block = bx - grp.first[prob];
     const int64_t i0 = (int64_t)block * R;
     int2* pent = reinterpret_cast<int2*>(smem + RG * PS);
     const f32x4* Us4 = reinterpret_cast<const f32x4*>(smem);
 
-    // one pass = this thread's CPT columns: their rows of Q (NE pairs, flat index c * DD + k) and
-    // the R x CPT patch of W
-    struct Pass { int4 qi[NE / 4]; f32x4 qv[NE / 4]; Vec<D, CPT> wv[R]; };
-    auto load_pass = [&](int64_t j0, Pass& p) {
-        const int4* qip = reinterpret_cast<const int4*>(Q_idx + j0 * DD);
-        const f32x4* qvp = reinterpret_cast<const f32x4*>(Q_val + j0 * DD);
-#pragma unroll
-        for (int k = 0; k < NE / 4; ++k) {
-            if constexpr (kNoApplyQ) {
-                p.qi[k] = make_int4((int)(threadIdx.x + k) & 255, (int)(threadIdx.x * 3 + k) & 255, (int)(threadIdx.x * 5 + k) & 255, (int)(threadIdx.x * 7 + k) & 255);
-                p.qv[k] = f32x4{0.1f, 0.2f, 0.3f, 0.4f};
-            } else {
-                p.qi[k] = qip[k];
-                p.qv[k] = qvp[k];
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < R; ++t) {
-            const int64_t i = i0 + t < m ? i0 + t : m - 1;         // rows past m: any valid row, never stored
-            p.wv[t] = stream_load(reinterpret_cast<const Vec<D, CPT>*>(W + i * (int64_t)n + j0));
-        }
-    };
-    auto idx_of = [](const Pass& p, int e) -> uint32_t {
-        const int4 q = p.qi[e >> 2];
-        return (uint32_t)((e & 3) == 0 ? q.x : (e & 3) == 1 ? q.y : (e & 3) == 2 ? q.z : q.w);
-    };
-    auto val_of = [](const Pass& p, int e) -> float {
-        const f32x4 q = p.qv[e >> 2];
-        return (e & 3) == 0 ? q.x : (e & 3) == 1 ? q.y : (e & 3) == 2 ? q.z : q.w;
-    };
-
     // Passes are visited in an order rotated by the workgroup's position inside its XCD
     // (workgroups are dealt to the 8 XCDs round-robin): all workgroups read the same Q arrays, and
     // without the rotation they would all ask the same few L2 channels for the same lines at once.
-    const int64_t step = (int64_t)NT * CPT;
-    const int npass_all = (int)((n + step - 1) / step);
-    const int p_lo = half * ((npass_all + 1) / 2);
-    const int npass = halves == 1 ? npass_all : (half == 0 ? (npass_all + 1) / 2 : npass_all / 2);   // passes of this workgroup
-    const int rot = (int)((block / 8) % npass_all);
-    auto pass_col = [&](int p) -> int64_t {
+    constexpr int step = NT * CPT;
+    const int npass_all = (int)(((int64_t)n + step - 1) / step);
+    const int p_lo = (int)((int64_t)npass_all * part / parts), npass = (int)((int64_t)npass_all * (part + 1) / parts) - p_lo;
+    const int rot = (block / 8) % npass_all;
+    auto pass_col = [&](int p) -> int {                             // the pass's first column
         int q = p_lo + p + rot;
         if (q >= npass_all) q -= npass_all;
-        return (int64_t)q * step + (int64_t)threadIdx.x * CPT;
+        return q * step;
+    };
+    const int lane_col = (int)threadIdx.x * CPT;                    // of the pass; past n: nothing there for this thread
+    const RowBlock<D> rows{static_cast<char*>(grp.W[prob]) + i0 * n * D::size, (int64_t)n * D::size, m - i0 < R ? (int)(m - i0) : R, n};
+
+    Patch w[R];
+    int4 qi[NE / 4];
+    f32x4 qv[NE / 4];
+    auto load_w = [&](int t, int col) { w[t] = row_load<Patch>(rows.from(t, col), (uint32_t)lane_col * D::size); };
+    auto load_q = [&](int col) {
+        const int jq = col < n - lane_col ? col + lane_col : n - CPT;
+        const int4* qip = reinterpret_cast<const int4*>(Q_idx + (int64_t)jq * DD);
+        const f32x4* qvp = reinterpret_cast<const f32x4*>(Q_val + (int64_t)jq * DD);
+#pragma unroll
+        for (int k = 0; k < NE / 4; ++k) { qi[k] = qip[k]; qv[k] = qvp[k]; }
+    };
+    auto idx_of = [&](int e) -> uint32_t {
+        const int4 q = qi[e >> 2];
+        return (uint32_t)((e & 3) == 0 ? q.x : (e & 3) == 1 ? q.y : (e & 3) == 2 ? q.z : q.w);
     };
     float num = 0.0f, den = 0.0f;                                   // NORMS: this thread's sums of squares
-    auto compute_pass = [&](const Pass& cur, int64_t j0) {
+    // the pass at column col; more: the patch of the pass at column next is loaded behind it
+    auto pass = [&](int col, int next, auto more) {
 #pragma unroll
         for (int g = 0; g < RG; ++g) {
             float acc[4][CPT];
@@ -224,120 +236,179 @@ __global__ __launch_bounds__(NT) void k_decompress(const ApplyGroup grp, int r, 
             for (int t = 0; t < 4; ++t)
 #pragma unroll
                 for (int c = 0; c < CPT; ++c) acc[t][c] = 0.0f;
-            if constexpr (kNoApplyMath) acc[0][0] = val_of(cur, 0) + __int_as_float((int)idx_of(cur, 0));
-            else
 #pragma unroll
-            for (int c = 0; c < CPT; ++c)
+            for (int c = 0; c < CPT; ++c) {
 #pragma unroll
                 for (int k = 0; k < DD; ++k) {
-                    const uint32_t unit = kNoConflicts ? ((idx_of(cur, c * DD + k) & ~15u) | (threadIdx.x & 15u)) : idx_of(cur, c * DD + k);
-                    const f32x4 u = Us4[unit + g * (PS / 16)];
-                    const float v = val_of(cur, c * DD + k);
+                    const f32x4 u = Us4[idx_of(c * DD + k) + g * (PS / 16)];
+                    const float v = qv[(c * DD + k) >> 2][(c * DD + k) & 3];
                     acc[0][c] = fmaf(v, u.x, acc[0][c]);
                     acc[1][c] = fmaf(v, u.y, acc[1][c]);
                     acc[2][c] = fmaf(v, u.z, acc[2][c]);
                     acc[3][c] = fmaf(v, u.w, acc[3][c]);
-                }
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int64_t i = i0 + g * 4 + t;
-                if (i < m) {
-                    float w[CPT];
-                    vec_widen<D, CPT>(cur.wv[g * 4 + t], w);
-                    if constexpr (NORMS) {
-#pragma unroll
-                        for (int c = 0; c < CPT; ++c) {
-                            const float diff = acc[t][c] - w[c];
-                            num = fmaf(diff, diff, num);
-                            den = fmaf(w[c], w[c], den);
-                        }
-                    } else {
-#pragma unroll
-                        for (int c = 0; c < CPT; ++c) w[c] -= acc[t][c];
-                        stream_store(reinterpret_cast<Vec<D, CPT>*>(W + i * (int64_t)n + j0), vec_narrow<D, CPT>(w));
-                    }
+                    if constexpr (DD >= 8) if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);   // eight gathers in flight: more would not fit the registers
                 }
             }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                float x[CPT];
+                vec_widen<D, CPT>(w[g * 4 + t], x);
+                if constexpr (NORMS) {
+                    const bool on = col < n - lane_col && g * 4 + t < rows.rows;
+#pragma unroll
+                    for (int c = 0; c < CPT; ++c) {
+                        const float diff = acc[t][c] - x[c];
+                        num = on ? fmaf(diff, diff, num) : num;
+                        den = on ? fmaf(x[c], x[c], den) : den;
+                    }
+                } else {
+#pragma unroll
+                    for (int c = 0; c < CPT; ++c) x[c] -= acc[t][c];
+                    row_store(rows.from(g * 4 + t, col), (uint32_t)lane_col * D::size, vec_narrow<D, CPT>(x));
+                }
+                if constexpr (decltype(more)::value) load_w(g * 4 + t, next);
+            }
         }
+        if constexpr (decltype(more)::value) load_q(next);
     };
 
-    // kDepth passes live in fixed register slots: one being computed, the others in flight.
-    // (Copying a slot to another would wait for its loads.)
-    Pass slot[kDepth];
-    auto load_if = [&](int p, Pass& s) {
-        if (p < npass) {
-            const int64_t j = pass_col(p);
-            if (j < n) load_pass(j, s);
-        }
-    };
-    auto compute_if = [&](int p, const Pass& s) {
-        if (p < npass) {
-            const int64_t j = pass_col(p);
-            if (j < n) compute_pass(s, j);
-        }
-    };
+    int col = pass_col(0);
 #pragma unroll
-    for (int k = 0; k + 1 < kDepth; ++k) load_if(k, slot[k]);       // in flight while the U tile is built
-    if constexpr (!kNoApplyU) build_u_tile_fast<RG, DD, PS, NT>(smem, pent, S, P_idx, P_val, i0, m, r);
+    for (int t = 0; t < R; ++t) load_w(t, col);                     // in flight while the U tile is built
+    load_q(col);
+    build_u_tile<RG, DD, (DD > 4 && D::size == 4 ? 4 : DD > 8 ? 8 : DD), PS, NT>(smem, pent, S, P_idx, P_val, i0, m, r, DD);
     __syncthreads();
-    for (int p = 0; p < npass; p += kDepth) {
-#pragma unroll
-        for (int k = 0; k < kDepth; ++k) {
-            load_if(p + k + kDepth - 1, slot[(k + kDepth - 1) % kDepth]);
-            compute_if(p + k, slot[k]);
-        }
+    for (int p = 1; p < npass; ++p) {
+        const int next = pass_col(p);
+        pass(col, next, std::true_type{});
+        col = next;
     }
+    if (npass > 0) pass(col, col, std::false_type{});
     if constexpr (NORMS) block_sum2<NT>(num, den, reinterpret_cast<float2*>(smem), partial + blockIdx.x);
 }
 
-// Generic kernel: any n and d, one column per thread.
-template <typename D, int RG, bool NORMS>
-__global__ __launch_bounds__(kThreadsD) void k_decompress_any(typename D::elem* __restrict__ W, const float* __restrict__ S,
-                                                             const int32_t* __restrict__ P_idx, const float* __restrict__ P_val,
-                                                             const int32_t* __restrict__ Q_idx, const float* __restrict__ Q_val,
-                                                             int m, int n, int r, int d, float2* __restrict__ partial) {
+// General kernel: any n and d.  A thread has two columns of a pass: neighbours (PAIR, n even), or columns 64 apart, each
+// loaded and stored by itself.  The entries of Q are taken four at a time for the whole patch (R x 2 sums in registers),
+// the next four in flight; the next pass's first four are asked for before its patch of W, because loads return in order.
+template <typename D, int RG, int PS, int NT, bool PAIR, bool NORMS>
+__global__ __launch_bounds__(NT, (NORMS ? 3 : 4)) void k_decompress_any(const ApplyGroup grp, int r, int d, float2* __restrict__ partial) {
     extern __shared__ __align__(16) uint8_t smem[];
-    float4* Us = reinterpret_cast<float4*>(smem);
+    typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+    typedef i32x4 loose_i __attribute__((aligned(4)));
+    typedef f32x4 loose_f __attribute__((aligned(4)));
     constexpr int R = 4 * RG;
-    const int64_t i0 = (int64_t)blockIdx.x * R;
-    build_u_tile<RG>(Us, S, P_idx, P_val, i0, m, r, d, r);
-    __syncthreads();
-    float num = 0.0f, den = 0.0f;                                   // NORMS: this thread's sums of squares
-    for (int64_t j = threadIdx.x; j < n; j += kThreadsD) {
-        float acc[RG][4];
+    const int prob = group_find(grp.first, grp.count, (int)blockIdx.x);
+    const int unit = (int)blockIdx.x - grp.first[prob], parts = grp.parts[prob];
+    const int block = unit / parts, part = unit - block * parts;
+    const int32_t* __restrict__ Q_idx = grp.Q_idx[prob];
+    const float* __restrict__ Q_val = grp.Q_val[prob];
+    const int m = grp.m[prob], n = grp.n[prob];
+    const int64_t i0 = (int64_t)block * R;
+    const f32x4* Us4 = reinterpret_cast<const f32x4*>(smem);
+    constexpr int step = NT * 2;
+    const int npass_all = (int)(((int64_t)n + step - 1) / step);
+    const int p_lo = (int)((int64_t)npass_all * part / parts), npass = (int)((int64_t)npass_all * (part + 1) / parts) - p_lo;
+    const int rot = (block / 8) % npass_all;
+    auto pass_col = [&](int p) -> int {                             // the pass's first column
+        int q = p_lo + p + rot;
+        if (q >= npass_all) q -= npass_all;
+        return q * step;
+    };
+    const int lane_col = PAIR ? (int)threadIdx.x * 2 : ((int)threadIdx.x >> 6) * 128 + ((int)threadIdx.x & 63);
+    constexpr int kApart = PAIR ? 1 : kWave;                        // from the first column to the second
+    const RowBlock<D> rows{static_cast<char*>(grp.W[prob]) + i0 * n * D::size, (int64_t)n * D::size, m - i0 < R ? (int)(m - i0) : R, n};
+
+    typedef typename std::conditional<PAIR, Vec<D, 2>, typename D::elem>::type Piece;
+    constexpr int NP = PAIR ? 1 : 2;
+    Piece w[R][NP];
+    i32x4 qi[2][2];                                                 // [buffer][column]
+    f32x4 qv[2][2];
+    auto load_w = [&](int col) {
 #pragma unroll
-        for (int g = 0; g < RG; ++g) acc[g][0] = acc[g][1] = acc[g][2] = acc[g][3] = 0.0f;
-        for (int k = 0; k < d; ++k) {
-            const int b = Q_idx[j * d + k];
-            const float v = Q_val[j * d + k];
+        for (int t = 0; t < R; ++t)
 #pragma unroll
-            for (int g = 0; g < RG; ++g) {
-                const float4 u = Us[g * r + b];
-                acc[g][0] = fmaf(v, u.x, acc[g][0]); acc[g][1] = fmaf(v, u.y, acc[g][1]);
-                acc[g][2] = fmaf(v, u.z, acc[g][2]); acc[g][3] = fmaf(v, u.w, acc[g][3]);
+            for (int c = 0; c < NP; ++c) w[t][c] = row_load<Piece>(rows.from(t, col), (uint32_t)(lane_col + c * kApart) * D::size);
+    };
+    auto load_q = [&](int buf, int col, int k0) {                     // entries k0 .. of both columns; past d: not touched
+        const int count = d - k0;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int jc = col < n - lane_col - c * kApart ? col + lane_col + c * kApart : n - 1;
+            const int64_t at = (int64_t)jc * d + k0;
+            if (count >= 4) {
+                qi[buf][c] = *reinterpret_cast<const loose_i*>(Q_idx + at);
+                qv[buf][c] = *reinterpret_cast<const loose_f*>(Q_val + at);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    if (k < count) { qi[buf][c][k] = Q_idx[at + k]; qv[buf][c][k] = Q_val[at + k]; }
             }
         }
+    };
+    float num = 0.0f, den = 0.0f;                                   // NORMS: this thread's sums of squares
+    float acc[R][2];
+    auto take = [&](int buf, int count) {
 #pragma unroll
-        for (int g = 0; g < RG; ++g)
+        for (int k = 0; k < 4; ++k) {
+            if (k > 0 && k >= count) break;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int64_t i = i0 + g * 4 + t;
-                if (i < m) {
-                    typename D::elem* p = W + i * (int64_t)n + j;
-                    if constexpr (NORMS) {
-                        const float w = widen<D>(*p), diff = acc[g][t] - w;
-                        num = fmaf(diff, diff, num);
-                        den = fmaf(w, w, den);
-                    } else {
-                        *p = narrow<D>(widen<D>(*p) - acc[g][t]);
-                    }
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int g = 0; g < RG; ++g) {
+                    const f32x4 u = Us4[(uint32_t)qi[buf][c][k] + g * (PS / 16)];
+                    const float v = qv[buf][c][k];
+                    acc[g * 4 + 0][c] = fmaf(v, u.x, acc[g * 4 + 0][c]);
+                    acc[g * 4 + 1][c] = fmaf(v, u.y, acc[g * 4 + 1][c]);
+                    acc[g * 4 + 2][c] = fmaf(v, u.z, acc[g * 4 + 2][c]);
+                    acc[g * 4 + 3][c] = fmaf(v, u.w, acc[g * 4 + 3][c]);
+                }
+        }
+    };
+    int col = pass_col(0);
+    load_q(0, col, 0);
+    load_w(col);
+    build_u_tile<RG, 0, 0, PS, NT>(smem, reinterpret_cast<int2*>(smem + RG * PS), grp.S[prob], grp.P_idx[prob], grp.P_val[prob], i0, m, r, d);
+    __syncthreads();
+    for (int p = 0; p < npass; ++p) {
+#pragma unroll
+        for (int t = 0; t < R; ++t) acc[t][0] = acc[t][1] = 0.0f;
+        for (int k0 = 0;; k0 += 8) {                                // buffers 0 and 1 in turn
+            if (k0 + 4 < d) load_q(1, col, k0 + 4);
+            take(0, d - k0);
+            if (k0 + 4 >= d) break;
+            if (k0 + 8 < d) load_q(0, col, k0 + 8);
+            take(1, d - k0 - 4);
+            if (k0 + 8 >= d) break;
+        }
+        const int next = p + 1 < npass ? pass_col(p + 1) : col;
+        if (p + 1 < npass) load_q(0, next, 0);
+#pragma unroll
+        for (int t = 0; t < R; ++t) {
+            float x[2];
+            if constexpr (PAIR) vec_widen<D, 2>(w[t][0], x);
+            else { x[0] = widen<D>(w[t][0]); x[1] = widen<D>(w[t][1]); }
+            if constexpr (NORMS) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const bool on = col < n - lane_col - c * kApart && t < rows.rows;
+                    const float diff = acc[t][c] - x[c];
+                    num = on ? fmaf(diff, diff, num) : num;
+                    den = on ? fmaf(x[c], x[c], den) : den;
+                }
+            } else {
+                x[0] -= acc[t][0]; x[1] -= acc[t][1];
+                if constexpr (PAIR) {
+                    row_store(rows.from(t, col), (uint32_t)lane_col * D::size, vec_narrow<D, 2>(x));
+                } else {
+                    row_store(rows.from(t, col), (uint32_t)lane_col * D::size, narrow<D>(x[0]));
+                    row_store(rows.from(t, col), (uint32_t)(lane_col + kApart) * D::size, narrow<D>(x[1]));
                 }
             }
+        }
+        if (p + 1 < npass) load_w(next);
+        col = next;
     }
-    if constexpr (NORMS) {
-        __syncthreads();                                            // the tile of U is no longer read
-        block_sum2<kThreadsD>(num, den, reinterpret_cast<float2*>(smem), partial + blockIdx.x);
-    }
+    if constexpr (NORMS) block_sum2<NT>(num, den, reinterpret_cast<float2*>(smem), partial + blockIdx.x);
 }
 
 // Adds the workgroups' sums in order (in double) and forms the bias:
@@ -358,26 +429,11 @@ __global__ __launch_bounds__(256) void k_bias_finish(const float2* __restrict__ 
     }
 }
 
-// The fast kernel needs n % 4 == 0, r % 4 == 0 and d in {2, 4, 8, 16}; a group takes it only if all
-// of its problems qualify.
-static bool fast_shape(int32_t n, int32_t r, int32_t d) {
-    return (n % 4) == 0 && (r % 4) == 0 && (d == 2 || d == 4 || d == 8 || d == 16);
-}
-bool apply_group_uniform(const ApplyGroup& g, int32_t r, int32_t d) {
-    for (int p = 1; p < g.count; ++p)
-        if (fast_shape(g.n[p], r, d) != fast_shape(g.n[0], r, d)) return false;
-    return g.count == 1 || fast_shape(g.n[0], r, d);                // the generic kernel takes one problem at a time
-}
+// The fast kernel needs an even n and d in {2, 4, 8, 16}; a group takes it only if all of its problems qualify.
+static bool fast_shape(int32_t n, int32_t d) { return (n % 2) == 0 && (d == 2 || d == 4 || d == 8 || d == 16); }
 
-// Row blocks at the end of a big launch of 32-row workgroups that are shared by two workgroups each: half a
-// round of the 256 CUs (measured on the seven matrices of a 6.7B-style layer: 0 / 96 / 128 / 160 / 192 / 256
-// blocks give 216 / 214 / 212 / 212 / 219 / 217 us per launch -- beyond that the second build of U costs more
-// than the shorter tail saves).
-constexpr int kTailSplitBlocks = 128;
-
-template <typename D, int RG, int PS, int NT, int CPT, int DEPTH, bool NORMS = false>
-static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, hipStream_t st, float2* partial = nullptr) {
-    using E = typename D::elem;
+template <typename D, int RG, int PS, int NT, bool NORMS = false>
+static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipStream_t st, float2* partial = nullptr) {
     // widest matrices first: workgroups are started in index order as CUs fall free, and a workgroup's
     // run time grows with n, so the long ones should not be the last to start
     for (int a = 1; a < g.count; ++a)
@@ -386,62 +442,70 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, hipStream_t st, 
             std::swap(g.P_val[b], g.P_val[b - 1]); std::swap(g.Q_idx[b], g.Q_idx[b - 1]); std::swap(g.Q_val[b], g.Q_val[b - 1]);
             std::swap(g.m[b], g.m[b - 1]); std::swap(g.n[b], g.n[b - 1]);
         }
+    bool fast = true, pair = true;
     g.first[0] = 0;
-    for (int p = 0; p < g.count; ++p) g.first[p + 1] = g.first[p] + (g.m[p] + RG * 4 - 1) / (RG * 4);
-    const int row_blocks = g.first[g.count];
-    // big launches of 32-row workgroups: the last row blocks go to two workgroups each (see the kernel)
-    const int tail = (!NORMS && RG == 8) ? std::min(row_blocks, kTailSplitBlocks) : 0;
-    const int split_from = row_blocks - tail;
-    const unsigned grid = (unsigned)(row_blocks + tail);
+    for (int p = 0; p < g.count; ++p) {                             // about `passes` passes for every workgroup
+        fast = fast && fast_shape(g.n[p], d);
+        pair = pair && g.n[p] % 2 == 0;
+        g.parts[p] = (int32_t)((((int64_t)g.n[p] + 2 * NT - 1) / (2 * NT) + passes - 1) / passes);
+        g.first[p + 1] = g.first[p] + (g.m[p] + RG * 4 - 1) / (RG * 4) * g.parts[p];
+    }
+    const unsigned grid = (unsigned)g.first[g.count];
     hipError_t e;
-    // d = 16: a pass holds 32 (column, value) pairs per thread, so only one pass fits the registers
 #define LSP_LAUNCH_FAST(DDV)                                                                                   \
     do {                                                                                                       \
-        constexpr auto kern = k_decompress<D, RG, DDV, PS, NT, CPT, (DDV == 16 ? 1 : DEPTH), NORMS>;                  \
+        constexpr auto kern = k_decompress<D, RG, DDV, PS, NT, NORMS>;                                         \
         constexpr size_t lds = (size_t)RG * PS + (size_t)RG * 4 * DDV * sizeof(int2);                          \
         if ((e = allow_dynamic_lds<kern>(lds)) != hipSuccess) return e;                                        \
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, g, (int)r, partial, split_from);               \
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, g, (int)r, partial);                            \
+        return hipGetLastError();                                                                              \
     } while (0)
-    if (!fast_shape(g.n[0], r, d)) {
-        constexpr auto kern = k_decompress_any<D, RG, NORMS>;
-        const size_t lds = (size_t)RG * r * 16;
-        if ((e = allow_dynamic_lds<kern>((size_t)RG * LSP_MAX_R * 16)) != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreadsD), lds, st, static_cast<E*>(g.W[0]), g.S[0], g.P_idx[0], g.P_val[0],
-                           g.Q_idx[0], g.Q_val[0], (int)g.m[0], (int)g.n[0], (int)r, (int)d, partial);
-    }
-    else if (d == 2) LSP_LAUNCH_FAST(2);
-    else if (d == 4) LSP_LAUNCH_FAST(4);
-    else if (d == 8) LSP_LAUNCH_FAST(8);
-    else LSP_LAUNCH_FAST(16);
+    if (fast && d == 2) LSP_LAUNCH_FAST(2);
+    if (fast && d == 4) LSP_LAUNCH_FAST(4);
+    if (fast && d == 8) LSP_LAUNCH_FAST(8);
+    if (fast && d == 16) LSP_LAUNCH_FAST(16);
 #undef LSP_LAUNCH_FAST
-    return hipGetLastError();
+    if constexpr (RG <= 4) {
+#define LSP_LAUNCH_ANY(PAIRV)                                                                                  \
+    do {                                                                                                       \
+        constexpr auto kern = k_decompress_any<D, RG, PS, NT, PAIRV, NORMS>;                                   \
+        if ((e = allow_dynamic_lds<kern>((size_t)RG * PS + (size_t)RG * 4 * LSP_MAX_D * sizeof(int2))) != hipSuccess) return e; \
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), (size_t)RG * PS + (size_t)RG * 4 * d * sizeof(int2), st, g, (int)r, (int)d, partial); \
+        return hipGetLastError();                                                                              \
+    } while (0)
+        if (pair) LSP_LAUNCH_ANY(true);
+        LSP_LAUNCH_ANY(false);
+#undef LSP_LAUNCH_ANY
+    }
+    return hipErrorInvalidValue;                                    // (32-row workgroups are for the fast kernel)
 }
 
-// Rows per workgroup: 16 (four planes of U in LDS), 8 when the tile of U would not fit otherwise.
-// Passes held in registers: three when the grid is small (few workgroups per CU, so each has to
-// keep more bytes in flight itself), two otherwise.  Big grids (grouped calls) use workgroups of
-// 256 threads, two of which share a CU and cover each other's set-up phase; when the tile of U
-// allows it (256 < r <= 512) they use 32 rows per workgroup instead, so that the rows of Q are
-// streamed from L2 half as often, with 512 threads: a row of the patch of W is then a 2 KB piece
-// per pass, and the read-modify-write stream of W runs measurably faster on longer pieces (plain
-// streaming kernels with this access pattern: 4.9 TB/s with 1 KB pieces, 5.4 TB/s with 2 KB ones).
+// Rows per workgroup: 16 (four planes of U in LDS) and 512 threads, except
+//   * r > 1024: 8 rows, or the tile of U would take the whole LDS;
+//   * fewer than 256 blocks of 16 rows: 8 rows, so that all CUs get work (2048 x 2048, r = 256: 10.4 -> 8.5 us);
+//   * 1024 or more blocks, 16-bit storage, 256 < r <= 512: 32 rows, so that the rows of Q are streamed from L2 half as
+//     often (the seven matrices of a 6.7B-style layer: 234 -> 226 us); fp32 patches of 32 rows would not fit the registers;
+//   * 512 or more blocks and r <= 512: 256 threads with at most eight passes each; four such workgroups share a CU and
+//     cover each other's set-up (11008 x 4096: 64 -> 57 us).
 template <typename D>
 static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_t st) {
-    constexpr int NT = 512, CPT = 2;
+    constexpr int kAll = 1 << 30;                                   // no row block is shared
     int64_t blocks = 0;
-    for (int p = 0; p < g.count; ++p) blocks += (g.m[p] + 15) / 16;
-    const bool deep = blocks <= 512;
-    const bool many = blocks >= 1024;
-#define LSP_D_CASE(RGV, PSV)                                                          \
-    return many ? launch_d<D, RGV, PSV, 256, CPT, 3>(g, r, d, st) :                   \
-           deep ? launch_d<D, RGV, PSV, NT, CPT, 3>(g, r, d, st)                      \
-                : launch_d<D, RGV, PSV, NT, CPT, 2>(g, r, d, st)
-    if (r <= 256) LSP_D_CASE(4, 4096);
-    if (256 < r && r <= 512 && many) return launch_d<D, 8, 8192, NT, CPT, 2>(g, r, d, st);    // 32 rows per workgroup
-    if (r <= 512) LSP_D_CASE(4, 8192);
-    if (r <= 1024) LSP_D_CASE(4, 16384);
-    LSP_D_CASE(2, 32768);
-#undef LSP_D_CASE
+    bool fast = true;
+    for (int p = 0; p < g.count; ++p) {
+        blocks += (g.m[p] + 15) / 16;
+        fast = fast && fast_shape(g.n[p], d);
+    }
+    if (r > 1024) return launch_d<D, 2, 32768, 512>(g, r, d, kAll, st);
+    if (fast && blocks < 256)
+        return r <= 256 ? launch_d<D, 2, 4096, 512>(g, r, d, kAll, st) : r <= 512 ? launch_d<D, 2, 8192, 512>(g, r, d, kAll, st)
+                                                                                 : launch_d<D, 2, 16384, 512>(g, r, d, kAll, st);
+    if constexpr (D::size == 2)
+        if (fast && d <= 8 && blocks >= 1024 && 256 < r && r <= 512) return launch_d<D, 8, 8192, 512>(g, r, d, kAll, st);
+    if (fast && d <= 8 && blocks >= 512 && r <= 512)
+        return r <= 256 ? launch_d<D, 4, 4096, 256>(g, r, d, 8, st) : launch_d<D, 4, 8192, 256>(g, r, d, 8, st);
+    return r <= 256 ? launch_d<D, 4, 4096, 512>(g, r, d, kAll, st) : r <= 512 ? launch_d<D, 4, 8192, 512>(g, r, d, kAll, st)
+                                                                             : launch_d<D, 4, 16384, 512>(g, r, d, kAll, st);
 }
 
 // Estimation bias: one problem, 16 (or 8) rows per workgroup, two passes deep.
@@ -449,10 +513,10 @@ int64_t bias_blocks(int64_t m, int32_t r) { return r <= 1024 ? (m + 15) / 16 : (
 
 template <typename D>
 static hipError_t launch_bias_shape(ApplyGroup& g, int32_t r, int32_t d, float2* partial, hipStream_t st) {
-    if (r <= 256)  return launch_d<D, 4, 4096, 512, 2, 2, true>(g, r, d, st, partial);
-    if (r <= 512)  return launch_d<D, 4, 8192, 512, 2, 2, true>(g, r, d, st, partial);
-    if (r <= 1024) return launch_d<D, 4, 16384, 512, 2, 2, true>(g, r, d, st, partial);
-    return launch_d<D, 2, 32768, 512, 2, 2, true>(g, r, d, st, partial);
+    if (r <= 256)  return launch_d<D, 4, 4096, 512, true>(g, r, d, 1 << 30, st, partial);
+    if (r <= 512)  return launch_d<D, 4, 8192, 512, true>(g, r, d, 1 << 30, st, partial);
+    if (r <= 1024) return launch_d<D, 4, 16384, 512, true>(g, r, d, 1 << 30, st, partial);
+    return launch_d<D, 2, 32768, 512, true>(g, r, d, 1 << 30, st, partial);
 }
 
 hipError_t launch_bias(ApplyGroup& g, int32_t r, int32_t d, lsp_dtype dtype, float* partial, float* out, hipStream_t st) {

@@ -160,6 +160,7 @@ struct ApplyGroup {
     const float*   Q_val[kMaxGroup];
     int32_t        m[kMaxGroup], n[kMaxGroup];
     int32_t        first[kMaxGroup + 1];
+    int32_t        parts[kMaxGroup];             // workgroups that share a row block
     int32_t        count;
 };
 
@@ -195,10 +196,9 @@ __device__ __forceinline__ int group_find(const int32_t* first, int count, int b
 // ------------------------------------------------------------------------------------------
 // Kernel launchers (each returns hipSuccess or the launch error).  The group launchers fill in
 // first_* themselves; all problems of a group must agree on what selects the kernel variant
-// (see compress_group_uniform / apply_group_uniform).
+// (see compress_group_uniform).
 // ------------------------------------------------------------------------------------------
 bool       compress_group_uniform(const CompressGroup& g);
-bool       apply_group_uniform(const ApplyGroup& g, int32_t r, int32_t d);
 hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st);
 // Scatter form on raw ELL arrays.  gate (device, may be null): the kernels run only if *gate == LSP_ERR_SKEW.
 hipError_t launch_compress_raw(const void* G, const int32_t* P_idx, const float* P_val,

@@ -127,6 +127,27 @@ def test_edge_shapes(m, n, r, d, dtype):
     _full_check(pb)
 
 
+@pytest.mark.parametrize("m,n,r,d,dtype", [
+    (33, 1025, 67, 1, "bf16"),       # odd n, one column in the second pass
+    (9, 1027, 3, 3, "f16"),          # fewer than four columns of U
+    (40, 2047, 250, 5, "f32"),       # entries left over behind a batch of four, r no multiple of 4
+    (17, 1, 9, 9, "bf16"),           # one column
+    (20, 4097, 130, 13, "f16"),
+    (24, 1026, 1026, 7, "bf16"),     # even n, 8-row workgroups
+    (16, 130, 200, 64, "bf16"),      # the most entries per row
+    (300, 1022, 251, 8, "bf16"),     # fast kernel, r no multiple of 4, pass with idle lanes
+    (8400, 520, 130, 2, "f32"),      # 256-thread workgroups
+])
+def test_apply_and_bias_at_the_edges_of_the_passes(m, n, r, d, dtype):
+    import gpu_util as gu
+    pb = syn.make_problem(f"pass_{m}x{n}_r{r}_d{d}", m, n, r, d, dtype, seed=350 + m + n, g_std=0.5,
+                          index_dist="uniform" if d < r else "distinct")
+    print(f"[case] {pb.name} {dtype}", flush=True)
+    Wp, Wr = oracle.decompress_apply(pb.W, dtype, pb.S_in, pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val, threads=THREADS)
+    gu.check_decompress(_dp(pb).decompress(pb.S_in), pb.W, Wp, Wr, dtype, pb.name)
+    _bias_check(pb)
+
+
 def test_zero_and_identity_cases():
     pb = syn.make_problem("zero", 64, 2048, 128, 4, "bf16", seed=42)
     dp = _dp(pb)
