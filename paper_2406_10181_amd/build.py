@@ -14,7 +14,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "liblsp_hip.so")
 OBJDIR = os.path.join(PKG, "_build")
-SOURCES = ["compress_gq16_bf16.hip", "compress_gq16_f16.hip", "compress_gq32.hip", "plan_device.hip", "decompress.hip",
+SOURCES = ["compress_gq_bf16.hip", "compress_gq_f16.hip", "compress_gq_f32.hip", "plan_device.hip", "decompress.hip",
            "compress.hip", "api.cpp", "plan.cpp", "reproject.hip", "dense.hip", "fitgrad.hip", "noalloc.hip", "probe.hip"]
 
 HIPCC_FLAGS = [

@@ -192,19 +192,8 @@ int lsp_compress_planned_grouped(const lsp_compress_item* items, int32_t count, 
         g.m[p] = (int32_t)it.m; g.n[p] = (int32_t)it.n;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (lsp::compress_group_uniform(g)) {
-        hipError_t e = lsp::launch_compress_planned(g, r, d, dtype, st);
-        return e == hipSuccess ? LSP_OK : fail_launch(e);
-    }
-    for (int p = 0; p < count; ++p) {                          // mixed kernel variants: one launch per problem
-        lsp::CompressGroup one;
-        std::memset(&one, 0, sizeof(one));
-        one.count = 1;
-        one.G[0] = g.G[p]; one.plan[0] = g.plan[p]; one.T[0] = g.T[p]; one.S[0] = g.S[p]; one.m[0] = g.m[p]; one.n[0] = g.n[p];
-        hipError_t e = lsp::launch_compress_planned(one, r, d, dtype, st);
-        if (e != hipSuccess) return fail_launch(e);
-    }
-    return LSP_OK;
+    hipError_t e = lsp::launch_compress_planned(g, r, d, dtype, st);
+    return e == hipSuccess ? LSP_OK : fail_launch(e);
 }
 
 int lsp_compress_planned(const void* G, const void* plan, int64_t m, int64_t n, int32_t r, int32_t d,

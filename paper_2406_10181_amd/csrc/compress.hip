@@ -1,17 +1,16 @@
 // Compress: S = P^T G Q  (Alg. 1, compress step; Alg. 3, projected gradient of a layer).
 //
 // Two kernels per call, both gather-form and free of global atomics in the common case:
-//   A  T = G Q     one workgroup per block of 16 rows of G; G is streamed once from HBM in
-//                  chunks of kChunk columns and staged in LDS transposed, one 16-byte unit per
-//                  column and group of rows (8 rows in storage precision for fp16 / bf16, 4 rows
-//                  widened to fp32 otherwise), so one 128-bit LDS read serves 8 (4) rows; each
+//   A  T = G Q     one workgroup per block of 8 rows of G (4 of fp32); G is streamed once from HBM in
+//                  chunks of kChunk columns and staged in LDS transposed, as it is stored, one 16-byte
+//                  unit per column, so one 128-bit LDS read serves all rows of the block; each
 //                  lane owns one column b of T and walks the plan's list of (column of G, value)
 //                  pairs of b, accumulating in registers.  With one column per lane the plan deals
 //                  the lists of every chunk to the waves by length, and the partial sums change
 //                  lanes between chunks (swap_owner).
 //   B  S = P^T T   one wave per piece of a row of P^T and 1/8 of the columns; reads rows of T.
-// The path streams G once; its main loop is bound by vector-ALU issue (16 widenings and 16 FMAs
-// per pair and 16 rows for bf16), not by HBM.  No matrix cores are involved because the
+// The path streams G once; its main loop is bound by vector-ALU issue (8 widenings and 8 FMAs
+// per pair and 8 rows for bf16), not by HBM.  No matrix cores are involved because the
 // projectors are sparse (d entries per row, Def. 1) and the work is gather + fp32 FMA.
 
 #include "compress_common.h"
@@ -19,7 +18,7 @@
 namespace lsp {
 
 // ----------------------------------------------------------------------------------------------
-// Kernel B, general variant (any r): S[a][stripe] (+)= sum_e v_e T[i_e][stripe] for one piece of a
+// Kernel B for r < 4: S[a][stripe] (+)= sum_e v_e T[i_e][stripe] for one piece of a
 // row of P^T and one stripe of 256 columns, one column per thread.
 constexpr int kThreadsB = 256;
 constexpr int kStripeQuads = 64;                              // column quads (float4) per stripe
@@ -47,13 +46,14 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt(const CompressGroup g
     }
 }
 
-// Kernel B, the usual variant (r % 4 == 0), XCD-aware.  The columns of T are cut into 8 stripes, one per XCD:
+// Kernel B, the usual variant (r >= 4), XCD-aware.  The columns of T are cut into 8 stripes, one per XCD:
 // workgroups are dealt to the 8 XCDs round-robin, so with stripe = blockIdx % 8 an XCD only ever
 // touches its own m x r/8 slice of T, which fits its 4 MB L2 -- T comes from HBM once instead of
 // once per use (each row of T is used by d rows of S).  Each of the 4 waves of a workgroup takes
 // one piece of a row of P^T; its 64 lanes form 64/LG groups of LG lanes (LG = 16, 32 or 64 >= quads
 // per stripe), group g takes entries g, g + groups, ...; the groups' sums meet through lane
-// exchanges in a fixed order.
+// exchanges in a fixed order.  A row's last quad starts at r - 4 when r is no multiple of 4 and stores only what the
+// quad before it has not (3001 rows, r = 250, d = 5: 26 us one column a thread, now 6).
 template <int LG>
 __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup grp, int r, int d, int sq) {
     constexpr int NG = kWave / LG;                            // entry groups per wave
@@ -73,8 +73,10 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup 
     const int lane = threadIdx.x & 63;
     const int grp_e = lane / LG, ql = lane % LG;
     const int b4 = stripe * sq + ql;
-    const bool live = ql < sq && b4 < (r >> 2);
-    const float* Tcol = T + (live ? b4 * 4 : 0);
+    const bool live = ql < sq && b4 * 4 < r;
+    const int b = live ? min(b4 * 4, r - 4) : 0;                      // first column of this lane's quad
+    typedef f32x4 loose __attribute__((aligned(4)));
+    const float* Tcol = T + b;
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
     // The piece's entries are loaded once, 64 at a time (one per lane), and handed to the groups by
     // lane exchange, so that the loads of T do not each wait for a load of their entry and can
@@ -94,7 +96,7 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup 
                 v[k] = __uint_as_float((uint32_t)__shfl((int)mine.y, src));
                 const bool on = k0 + k < steps && (k0 + k) * NG + grp_e < kWave;
                 if (!on) v[k] = 0.0f;
-                x[k] = *reinterpret_cast<const f32x4*>(Tcol + (int64_t)(on ? row : 0u) * r);
+                x[k] = *reinterpret_cast<const loose*>(Tcol + (int64_t)(on ? row : 0u) * r);
             }
 #pragma unroll
             for (int k = 0; k < kBlock; ++k) {
@@ -109,11 +111,14 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup 
         acc.z += __shfl_xor(acc.z, step); acc.w += __shfl_xor(acc.w, step);
     }
     if (lane < LG && live) {
-        float* dst = S + (int64_t)it.a * r + b4 * 4;
+        float* dst = S + (int64_t)it.a * r + b;
+        const int have = b4 * 4 - b;                                  // elements that the quad before stores
         if (it.atomic) {
-            atomicAdd(dst + 0, acc.x); atomicAdd(dst + 1, acc.y); atomicAdd(dst + 2, acc.z); atomicAdd(dst + 3, acc.w);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k >= have) atomicAdd(dst + k, acc[k]);
         } else {
-            *reinterpret_cast<f32x4*>(dst) = acc;
+            *reinterpret_cast<loose*>(dst) = acc;                     // (the same sums where quads overlap)
         }
     }
 }
@@ -167,29 +172,19 @@ __global__ __launch_bounds__(256) void k_raw_pt(const float* __restrict__ T, con
 }
 
 // ----------------------------------------------------------------------------------------------
-bool compress_group_uniform(const CompressGroup& g) {
-    for (int p = 1; p < g.count; ++p)
-        if ((g.n[p] % 8 == 0) != (g.n[0] % 8 == 0)) return false;     // selects vector or element-wise loads
-    return true;
-}
-
-// Row blocks per workgroup of kernel A: several on big grids (grouped calls) of the 16-bit kernel
-static int gq_blocks_per_wg(const CompressGroup& g, lsp_dtype dtype) {
-    if (dtype == LSP_F32 || g.n[0] % 8 != 0) return 1;
+// Row blocks per workgroup of kernel A: several on big grids (grouped calls)
+static int gq_blocks_per_wg(const CompressGroup& g) {
     int64_t rows = 0;
     for (int p = 0; p < g.count; ++p) rows += g.m[p];
     return rows >= 16384 ? 2 : 1;
 }
 
-// Rows of a row block of kernel A: the 16-bit kernel and the 32-bit-staged kernel differ
-static int gq_block_rows(const CompressGroup& g, lsp_dtype dtype) {
-    return (dtype != LSP_F32 && g.n[0] % 8 == 0) ? kRowsGQ16 : kRowsGQ;
-}
-
-static hipError_t launch_gq(const CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, lsp_dtype dtype, hipStream_t st) {
-    if (dtype != LSP_F32 && g.n[0] % 8 == 0)
-        return dtype == LSP_F16 ? launch_gq16_f16(g, r, d, blocks_per_wg, st) : launch_gq16_bf16(g, r, d, blocks_per_wg, st);
-    return launch_gq_staged32(g, r, d, dtype, st);
+static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, lsp_dtype dtype, hipStream_t st) {
+    switch (dtype) {
+        case LSP_F32:  return launch_gq_f32(g, r, d, blocks_per_wg, st);
+        case LSP_F16:  return launch_gq_f16(g, r, d, blocks_per_wg, st);
+        default:       return launch_gq_bf16(g, r, d, blocks_per_wg, st);
+    }
 }
 
 // The hardware hands the workgroups of a launch to the CUs in index order as CUs fall free, so the
@@ -206,20 +201,18 @@ static void longest_first(CompressGroup& g) {
 
 hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st) {
     const int nstripes = (r + kStripeQuads * 4 - 1) / (kStripeQuads * 4);
-    const bool striped = (r % 4) == 0;
+    const bool striped = r >= 4;
     longest_first(g);
-    const int bpw = gq_blocks_per_wg(g, dtype), rows = gq_block_rows(g, dtype);
-    g.first_gq[0] = g.first_pt[0] = 0;
+    g.first_pt[0] = 0;
     for (int p = 0; p < g.count; ++p) {
-        g.first_gq[p + 1] = g.first_gq[p] + (int32_t)(((g.m[p] + rows - 1) / rows + bpw - 1) / bpw);
         const int32_t items = (int32_t)plan_max_items(g.m[p], r, d);
         g.first_pt[p + 1] = g.first_pt[p] + (striped ? ((items + 3) / 4) * 8 : items * nstripes);
     }
-    hipError_t e = launch_gq(g, r, d, bpw, dtype, st);
+    hipError_t e = launch_gq(g, r, d, gq_blocks_per_wg(g), dtype, st);
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)g.first_pt[g.count];
     if (striped) {
-        const int sq = ((r >> 2) + 7) / 8;
+        const int sq = ((r + 3) / 4 + 7) / 8;
         if (sq <= 16)      hipLaunchKernelGGL(k_compress_pt8<16>, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, sq);
         else if (sq <= 32) hipLaunchKernelGGL(k_compress_pt8<32>, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, sq);
         else               hipLaunchKernelGGL(k_compress_pt8<64>, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, sq);

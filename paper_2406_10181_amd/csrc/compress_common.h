@@ -24,16 +24,13 @@ __device__ __forceinline__ void poison_s(float* __restrict__ S, int r, int block
 }
 
 
-// Kernel A: one workgroup = 16 rows of G, 512 threads, one lane per (virtual) column of T.
-constexpr int kPlanes = 4;                                    // 4-row planes of an fp32-staged chunk
-constexpr int kRowsGQ = 4 * kPlanes;
 constexpr int kBatchLoads = kSegBatch / 2;                    // 128-bit loads per batch of plan rows
 
-// Partial sums of several owners of one column meet in LDS: every lane parks its 16 sums at its
-// virtual column, [16][nslots * 512] floats; the first owner of a column then adds the owners'
+// Partial sums of several owners of one column meet in LDS: every lane parks its R sums at its
+// virtual column, [R][nslots * 512] floats; the first owner of a column then adds the owners'
 // sums in owner order (they sit side by side) and stores the column of T.  No atomics, so the
 // result does not depend on timing.  Called by all threads of the workgroup.
-template <int NS, int R = kRowsGQ>
+template <int NS, int R>
 __device__ __forceinline__ void write_tile_shared(uint8_t* smem, const uint8_t* plan, PlanHeaderPtr H, float* __restrict__ T,
                                                   const float (&acc)[NS][R], int nslots, int64_t i0, int m, int r, int tid) {
     __syncthreads();                                                  // the staged chunk is no longer read
@@ -88,11 +85,10 @@ __device__ __forceinline__ void swap_owner(uint8_t* area, float (&acc)[R], uint3
     __syncthreads();
 }
 
-// Launchers of kernel A (first_gq filled in): fp16 / bf16 with rows of whole 8-element groups, and the rest.
-// rows of G per row block of the 16-bit kernel (a workgroup holds that many rows of two chunks in LDS)
-constexpr int kRowsGQ16 = 8;
-hipError_t launch_gq16_bf16(const CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, hipStream_t st);
-hipError_t launch_gq16_f16(const CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, hipStream_t st);
-hipError_t launch_gq_staged32(const CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st);
+// Launchers of kernel A (they fill in first_gq): one workgroup = a block of rows of G at a time, 512 threads, one lane
+// per (virtual) column of T.
+hipError_t launch_gq_bf16(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, hipStream_t st);
+hipError_t launch_gq_f16(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, hipStream_t st);
+hipError_t launch_gq_f32(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, hipStream_t st);
 
 }  // namespace lsp

@@ -1,5 +1,5 @@
-// Compress, kernel A, 16-bit variant (fp16 / bf16 storage, rows of whole 8-element groups): the template
-// code; compress_gq16_bf16.hip and compress_gq16_f16.hip instantiate it.  See compress.hip for the path as a whole.
+// Compress, kernel A: T = G Q, the template code; compress_gq_bf16.hip, compress_gq_f16.hip and compress_gq_f32.hip
+// instantiate it.  See compress.hip for the path as a whole.
 #pragma once
 
 #include "compress_common.h"
@@ -7,13 +7,16 @@
 namespace lsp {
 
 // ----------------------------------------------------------------------------------------------
-// 16-bit storage types (fp16, bf16), n % 8 == 0: G is staged as it is stored, 8 rows to a 16-byte LDS
-// unit ([plane of 8 rows][column][8 rows]), so one 128-bit gather serves eight rows, and the LDS holds two
-// chunks, the one being consumed and the one being staged, with one barrier per chunk.  The elements are
-// widened in registers when they are used (exact: a shift or mask for bf16, a conversion for fp16).
-// RP = planes of 8 rows per workgroup.  With RP = 1 (8 rows, 64 KB of LDS, at most 128 registers per lane) two
-// workgroups share a CU, four waves per SIMD: a single wave issues a vector instruction only every 5 to 6
-// cycles, so a SIMD needs more than two resident waves to stay busy while some of them wait at a barrier.
+// G is staged as it is stored, in 16-byte LDS units of one column and the rows of a plane (8 rows of fp16 / bf16, 4 of fp32:
+// [plane][column][rows]), so one 128-bit gather serves them all; 16-bit elements are widened in registers when they are
+// used (exact: a shift or mask for bf16, a conversion for fp16).
+// A workgroup has a block of one plane and holds two chunks, the one being consumed and the one being staged.  That is
+// 64 KB of LDS, and with at most 128 registers per lane two workgroups share a CU, four waves per SIMD: a single wave
+// issues a vector instruction only every 5 to 6 cycles, so a SIMD needs more than two resident waves to stay busy
+// while some of them wait at a barrier.  (fp32 with 16-row blocks in four planes and one workgroup a CU took
+// 40.5 us on 4096 x 4096, r = 512, d = 8, now 29; with two planes of one chunk the sums and the rows in flight
+// did not fit 128 registers.)
+template <typename D> constexpr int kRowsGQ = 16 / D::size;           // rows of a block
 template <typename D> __device__ __forceinline__ void widen2(uint32_t w, float& lo, float& hi);
 template <> __device__ __forceinline__ void widen2<BF16>(uint32_t w, float& lo, float& hi) {
     lo = __uint_as_float(w << 16); hi = __uint_as_float(w & 0xFFFF0000u);
@@ -30,112 +33,124 @@ __device__ __forceinline__ uint32_t pair_rows(uint32_t a, uint32_t b, bool odd_c
     return __builtin_amdgcn_perm(b, a, odd_column ? 0x07060302u : 0x05040100u);
 }
 
-// Fetches and stages a chunk of 8 RP rows.  Rows past the matrix are read from its last row and columns
-// past it from its first ones (always a valid address): what they hold is never used, as the plan
-// has no entry for such a column and the sums of such a row are not stored.  The rows of a thread
-// are the same for the whole wave, so the row addresses are scalar.
-template <int RP> struct ChunkStager16;
+// Fetches and stages a chunk of the block's rows, 4 columns a thread: 512 threads cover the 2048 columns.  Rows past the matrix
+// are read from its last row and columns past it from its first ones or from the next row (always a valid address): what
+// they hold is never used, as the plan has no entry for such a column and the sums of such a row are not stored.
+// WHOLE: n % 4 == 0.  Otherwise a piece that would end behind the matrix's last element is read from where it ends with
+// it and put right when it is staged.
+template <typename D, bool WHOLE> struct ChunkStager {
+    static constexpr int R = kRowsGQ<D>;
+    static constexpr int kPieceDwords = D::size;                      // 4 elements
+    typedef uint32_t Piece __attribute__((ext_vector_type(kPieceDwords)));
+    typedef Piece Loose __attribute__((aligned(WHOLE ? 4 * D::size : D::size)));
+    Piece pre[R];
+    int late, late_from;                                              // rows from late_from on were read `late` elements early
 
-// RP = 2: a thread fetches 8 rows x 8 columns (one 16-byte load per row)
-template <> struct ChunkStager16<2> {
-    u32x4 pre[8];                                                     // 8 rows x 8 columns, as stored
-
-    template <typename E>
-    __device__ __forceinline__ void fetch(const E* __restrict__ G, int64_t i0, int m, int n, int c, int tid, int wave) {
-        const int plane = wave / (kWavesGQ / 2), oct = tid % (kChunk / 8);
-        const uint32_t col0 = (uint32_t)c * kChunk + (uint32_t)oct * 8;
-        const uint32_t byte0 = (col0 < (uint32_t)n ? col0 : 0u) * (uint32_t)sizeof(E);
-        const int64_t first = i0 + plane * 8;                        // may lie past the matrix (second plane of a ragged block)
-        const int64_t top = first < m ? first : (int64_t)m - 1;
-        const int last = (int)(m - 1 - top < 7 ? m - 1 - top : 7);   // rows of this plane inside the matrix, less one
-        const char* base = reinterpret_cast<const char*>(G + top * (int64_t)n) + byte0;
-        const uint64_t stride = (uint64_t)n * sizeof(E);
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            pre[t] = stream_load(reinterpret_cast<const u32x4*>(base));
-            base += t < last ? stride : 0;
-        }
-    }
-    // transposes the 8x8 block and writes its 8 units (column q: rows 0..7) into buffer `buf`
-    __device__ __forceinline__ void stage(uint8_t* smem, int buf, int tid) {
-        const int plane = tid / (kChunk / 8), oct = tid % (kChunk / 8);
-        uint8_t* base = smem + buf * (2 * kPlaneStride) + plane * kPlaneStride + oct * 16;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            u32x4 unit;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) unit[k] = pair_rows(pre[2 * k][q >> 1], pre[2 * k + 1][q >> 1], q & 1);
-            *reinterpret_cast<u32x4*>(base + q * (kChunk / 8) * 16) = unit;
-        }
-    }
-};
-
-// RP = 1: a thread fetches 8 rows x 4 columns (one 8-byte load per row): 512 threads cover the 2048 columns
-template <> struct ChunkStager16<1> {
-    u32x2 pre[8];
-
-    template <typename E>
-    __device__ __forceinline__ void fetch(const E* __restrict__ G, int64_t i0, int m, int n, int c, int tid, int) {
+    __device__ __forceinline__ void fetch(const typename D::elem* __restrict__ G, int64_t i0, int m, int n, int c, int tid) {
+        typedef typename D::elem E;
         const uint32_t col0 = (uint32_t)c * kChunk + (uint32_t)tid * 4;
-        const uint32_t byte0 = (col0 < (uint32_t)n ? col0 : 0u) * (uint32_t)sizeof(E);   // n % 8 == 0
-        const int last = (int)(m - 1 - i0 < 7 ? m - 1 - i0 : 7);     // rows of the block inside the matrix, less one (i0 < m)
+        const uint32_t byte0 = (col0 < (uint32_t)n ? col0 : 0u) * (uint32_t)sizeof(E);
+        const int last = (int)(m - 1 - i0 < R - 1 ? m - 1 - i0 : R - 1);   // rows of the block inside the matrix, less one (i0 < m)
         const char* base = reinterpret_cast<const char*>(G + i0 * (int64_t)n) + byte0;
         const uint64_t stride = (uint64_t)n * sizeof(E);
+        if constexpr (WHOLE) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            pre[t] = stream_load(reinterpret_cast<const u32x2*>(base));
-            base += t < last ? stride : 0;
+            for (int t = 0; t < R; ++t) {
+                pre[t] = __builtin_nontemporal_load(reinterpret_cast<const Loose*>(base));
+                base += t < last ? stride : 0;
+            }
+        } else {
+            late = 0; late_from = R;
+            if (n < 4) {                                              // element by element
+#pragma unroll
+                for (int t = 0; t < R; ++t) {
+                    E x[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) x[q] = G[(i0 + (t < last ? t : last)) * n + (q < n ? q : n - 1)];
+                    __builtin_memcpy(&pre[t], x, sizeof(x));
+                }
+                return;
+            }
+            if (i0 + last == m - 1) {
+                late_from = last;
+                if (col0 < (uint32_t)n && col0 + 4 > (uint32_t)n) late = (int)(col0 + 4 - (uint32_t)n);
+            }
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+                pre[t] = __builtin_nontemporal_load(reinterpret_cast<const Loose*>(base - (t >= late_from ? late : 0) * (int)sizeof(E)));
+                base += t < last ? stride : 0;
+            }
         }
     }
-    // transposes the 8x4 block and writes its 4 units (column q: rows 0..7) into buffer `buf`
+    // transposes the block and writes its 4 units (column q: all rows) into buffer `buf`
     __device__ __forceinline__ void stage(uint8_t* smem, int buf, int tid) {
+        if constexpr (!WHOLE)
+            if (late != 0) {
+#pragma unroll
+                for (int t = 0; t < R; ++t)
+                    if (t >= late_from) pre[t] = drop_elements(pre[t], late);
+            }
         // local column j = 4 tid + q sits at unit (j & 7) * (kChunk / 8) + (j >> 3)
         uint8_t* base = smem + buf * kPlaneStride + ((4 * (tid & 1)) * (kChunk / 8) + (tid >> 1)) * 16;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             u32x4 unit;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) unit[k] = pair_rows(pre[2 * k][q >> 1], pre[2 * k + 1][q >> 1], q & 1);
+            for (int k = 0; k < 4; ++k) {
+                if constexpr (D::size == 2) unit[k] = pair_rows(pre[2 * k][q >> 1], pre[2 * k + 1][q >> 1], q & 1);
+                else unit[k] = pre[k][q];
+            }
             *reinterpret_cast<u32x4*>(base + q * (kChunk / 8) * 16) = unit;
         }
     }
+    // the piece without its first `by` (1 to 3) elements
+    static __device__ __forceinline__ Piece drop_elements(const Piece& x, int by) {
+        Piece o;
+        if constexpr (D::size == 2) {
+            const uint64_t v = (((uint64_t)x[1] << 32) | x[0]) >> (16 * by);
+            o[0] = (uint32_t)v; o[1] = (uint32_t)(v >> 32);
+        } else {
+            o[0] = by == 1 ? x[1] : by == 2 ? x[2] : x[3];
+            o[1] = by == 1 ? x[2] : x[3];
+            o[2] = o[3] = x[3];
+        }
+        return o;
+    }
 };
 
-template <int RP>
-__device__ __forceinline__ void gather_pair16(const uint8_t* buf, const u32x4 e, u32x4 (&x)[2][RP]) {
+__device__ __forceinline__ void gather_pair(const uint8_t* buf, const u32x4 e, u32x4 (&x)[2]) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int g = 0; g < RP; ++g)
-            x[h][g] = *reinterpret_cast<const u32x4*>(buf + (h ? e.z : e.x) + g * kPlaneStride);
+    for (int h = 0; h < 2; ++h) x[h] = *reinterpret_cast<const u32x4*>(buf + (h ? e.z : e.x));
 }
-template <typename D, int RP>
-__device__ __forceinline__ void fma_pair16(const u32x4 e, const u32x4 (&x)[2][RP], float (&acc)[8 * RP]) {
+template <typename D>
+__device__ __forceinline__ void fma_pair(const u32x4 e, const u32x4 (&x)[2], float (&acc)[kRowsGQ<D>]) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const float v = __uint_as_float(h ? e.w : e.y);
 #pragma unroll
-        for (int g = 0; g < RP; ++g)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < 4; ++k) {
+            if constexpr (D::size == 2) {
                 float lo, hi;
-                widen2<D>(x[h][g][k], lo, hi);
-                acc[g * 8 + 2 * k]     = fmaf(v, lo, acc[g * 8 + 2 * k]);
-                acc[g * 8 + 2 * k + 1] = fmaf(v, hi, acc[g * 8 + 2 * k + 1]);
+                widen2<D>(x[h][k], lo, hi);
+                acc[2 * k]     = fmaf(v, lo, acc[2 * k]);
+                acc[2 * k + 1] = fmaf(v, hi, acc[2 * k + 1]);
+            } else {
+                acc[k] = fmaf(v, __uint_as_float(x[h][k]), acc[k]);
             }
+        }
     }
 }
 
-// One workgroup walks `nblk` consecutive blocks of 16 rows (several when the grid is big: the first
+// One workgroup walks `nblk` consecutive row blocks (several when the grid is big: the first
 // chunk of the next block is fetched and staged while the last chunk of the current one is
 // consumed, and the stores of T go out under the next block's work, so that the set-up and the
 // tail of a block cost nothing but for the first and the last one).
-template <typename D, int RP>
-__device__ __forceinline__ void gq16_one_slot(ChunkStager16<RP>& stg, uint8_t* smem, const typename D::elem* __restrict__ G,
+template <typename D, bool WHOLE>
+__device__ __forceinline__ void gq_one_slot(ChunkStager<D, WHOLE>& stg, uint8_t* smem, const typename D::elem* __restrict__ G,
                                               const uint8_t* __restrict__ plan, PlanHeaderPtr H,
                                               float* __restrict__ T, int64_t i0, int nblk, int m, int n, int r,
                                               int tid, int lane, int wave) {
-    constexpr int R = 8 * RP;                                         // rows of a row block
+    constexpr int R = kRowsGQ<D>;
     const int nchunks = H->nchunks;
     const auto* seg = as_const<uint32_t>(plan + H->off_q_seg) + wave;
     const u32x4* rp0 = reinterpret_cast<const u32x4*>(plan + H->off_q_rows) + (size_t)(H->q_stream_row[wave] >> 1) * kWave + lane;
@@ -164,13 +179,13 @@ __device__ __forceinline__ void gq16_one_slot(ChunkStager16<RP>& stg, uint8_t* s
 
     const uint8_t* buf = smem;
     auto step = [&](u32x4 (&slot)[kBatchLoads]) {
-        u32x4 x[2][2][RP];
-        gather_pair16<RP>(buf, slot[0], x[0]);
+        u32x4 x[2][2];
+        gather_pair(buf, slot[0], x[0]);
 #pragma unroll
         for (int q = 0; q < kBatchLoads; ++q) {
-            if (q + 1 < kBatchLoads) gather_pair16<RP>(buf, slot[q + 1], x[(q + 1) & 1]);
+            if (q + 1 < kBatchLoads) gather_pair(buf, slot[q + 1], x[(q + 1) & 1]);
             __builtin_amdgcn_sched_barrier(0);
-            fma_pair16<D, RP>(slot[q], x[q & 1], acc[0]);
+            fma_pair<D>(slot[q], x[q & 1], acc[0]);
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
@@ -192,8 +207,8 @@ __device__ __forceinline__ void gq16_one_slot(ChunkStager16<RP>& stg, uint8_t* s
         const int nb = nb_next;
         nb_next = (int)(seg[(last_chunk ? 0 : c + 1) * kWavesGQ] / kSegBatch);   // arrives while this chunk is walked
         if (u + 1 < units)                                            // next chunk, maybe of the next block: lands while this one is consumed
-            stg.fetch(G, i0 + (int64_t)(last_chunk ? blk + 1 : blk) * R, m, n, last_chunk ? 0 : c + 1, tid, wave);
-        buf = smem + (u & 1) * (RP * kPlaneStride);
+            stg.fetch(G, i0 + (int64_t)(last_chunk ? blk + 1 : blk) * R, m, n, last_chunk ? 0 : c + 1, tid);
+        buf = smem + (u & 1) * kPlaneStride;
         const bool more = u + 1 < units;
         // The next chunk is staged (into the buffer nobody reads now) in the middle of this one's
         // work rather than at its end, where every wave would wait for it; only a block's last
@@ -222,7 +237,7 @@ __device__ __forceinline__ void gq16_one_slot(ChunkStager16<RP>& stg, uint8_t* s
         // The sums move to the lanes that walk the columns in the next chunk; after the last chunk
         // of a block they go home (thread t: virtual column t) and out to T.
         if (last_chunk && more) { ring_restart(); rot = 0; }          // the stream starts over; in flight during the stores
-        swap_owner<R>(smem + (u & 1) * (RP * kPlaneStride), acc[0], walked, next);
+        swap_owner<R>(smem + (u & 1) * kPlaneStride, acc[0], walked, next);
         if (last_chunk) {
             const int64_t ib = i0 + (int64_t)blk * R;
             if (shared) {
@@ -251,15 +266,15 @@ __device__ __forceinline__ void gq16_one_slot(ChunkStager16<RP>& stg, uint8_t* s
 }
 
 // Several columns per lane (r > 512, or columns used so unevenly that they were split), 16-bit
-// storage: the same staging, plan ring and block walk as gq16_one_slot, the lane's columns taken
+// storage: the same staging, plan ring and block walk as gq_one_slot, the lane's columns taken
 // slot by slot inside each chunk.  A lane keeps its columns for all chunks (no dealing by length:
 // the sums of NS columns per lane would not fit through LDS cheaply).
-template <typename D, int NS, int RP>
-__device__ __forceinline__ void gq16_multi_slot(ChunkStager16<RP>& stg, uint8_t* smem, const typename D::elem* __restrict__ G,
+template <typename D, int NS, bool WHOLE>
+__device__ __forceinline__ void gq_multi_slot(ChunkStager<D, WHOLE>& stg, uint8_t* smem, const typename D::elem* __restrict__ G,
                                                 const uint8_t* __restrict__ plan, PlanHeaderPtr H,
                                                 float* __restrict__ T, int64_t i0, int nblk, int m, int n, int r,
                                                 int tid, int lane, int wave) {
-    constexpr int R = 8 * RP;                                         // rows of a row block
+    constexpr int R = kRowsGQ<D>;
     const int nchunks = H->nchunks, nslots = H->nslots;
     const auto* seg = as_const<uint32_t>(plan + H->off_q_seg) + wave;
     const u32x4* rp0 = reinterpret_cast<const u32x4*>(plan + H->off_q_rows) + (size_t)(H->q_stream_row[wave] >> 1) * kWave + lane;
@@ -286,13 +301,13 @@ __device__ __forceinline__ void gq16_multi_slot(ChunkStager16<RP>& stg, uint8_t*
 
     const uint8_t* buf = smem;
     auto step = [&](u32x4 (&slot)[kBatchLoads], float (&a)[R]) {
-        u32x4 x[2][2][RP];
-        gather_pair16<RP>(buf, slot[0], x[0]);
+        u32x4 x[2][2];
+        gather_pair(buf, slot[0], x[0]);
 #pragma unroll
         for (int q = 0; q < kBatchLoads; ++q) {
-            if (q + 1 < kBatchLoads) gather_pair16<RP>(buf, slot[q + 1], x[(q + 1) & 1]);
+            if (q + 1 < kBatchLoads) gather_pair(buf, slot[q + 1], x[(q + 1) & 1]);
             __builtin_amdgcn_sched_barrier(0);
-            fma_pair16<D, RP>(slot[q], x[q & 1], a);
+            fma_pair<D>(slot[q], x[q & 1], a);
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
@@ -326,8 +341,8 @@ __device__ __forceinline__ void gq16_multi_slot(ChunkStager16<RP>& stg, uint8_t*
         const bool last_chunk = c + 1 == nchunks;
         const bool more = u + 1 < units;
         if (more)
-            stg.fetch(G, i0 + (int64_t)(last_chunk ? blk + 1 : blk) * R, m, n, last_chunk ? 0 : c + 1, tid, wave);
-        buf = smem + (u & 1) * (RP * kPlaneStride);
+            stg.fetch(G, i0 + (int64_t)(last_chunk ? blk + 1 : blk) * R, m, n, last_chunk ? 0 : c + 1, tid);
+        buf = smem + (u & 1) * kPlaneStride;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             if (s < nslots) {
@@ -349,7 +364,7 @@ __device__ __forceinline__ void gq16_multi_slot(ChunkStager16<RP>& stg, uint8_t*
                 write_tile_shared<NS, R>(smem, plan, H, T, acc, nslots, ib, m, r, tid);   // uses the LDS of both chunk buffers
                 if (more) {
                     __syncthreads();                                  // before that LDS is staged into again
-                    if (tid < 2 * RP) *reinterpret_cast<f32x4*>(smem + tid * kPlaneStride + kChunk * 16) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                    if (tid < 2) *reinterpret_cast<f32x4*>(smem + tid * kPlaneStride + kChunk * 16) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
                 }
             } else {
 #pragma unroll
@@ -370,15 +385,14 @@ __device__ __forceinline__ void gq16_multi_slot(ChunkStager16<RP>& stg, uint8_t*
         } else {
             ++c;
         }
-        if (more) stg.stage(smem, (u + 1) & 1, tid);                  // the other buffer: nobody reads it now
+        if (more) stg.stage(smem, (u + 1) & 1, tid);               // the other buffer: nobody reads it now
         __syncthreads();                                              // the next chunk is staged; this one is no longer read
     }
 }
 
-// Kernel A for fp16 / bf16 with n % 8 == 0: R = 8 RP rows per row block.
-template <typename D, int RP>
-__global__ __launch_bounds__(kThreadsGQ, RP == 1 ? 4 : 1) void k_compress_gq16(const CompressGroup grp, int r, int d, int blocks_per_wg) {
-    constexpr int R = 8 * RP;
+template <typename D, bool WHOLE>
+__global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGroup grp, int r, int d, int blocks_per_wg) {
+    constexpr int R = kRowsGQ<D>;
     extern __shared__ __align__(16) uint8_t smem[];
     const CompressProblem pr = group_pick(grp, (int)blockIdx.x, false);
     const typename D::elem* __restrict__ G = static_cast<const typename D::elem*>(pr.G);
@@ -393,8 +407,8 @@ __global__ __launch_bounds__(kThreadsGQ, RP == 1 ? 4 : 1) void k_compress_gq16(c
     const int64_t i0 = (int64_t)block * blocks_per_wg * R;
     const int nblk = min(blocks_per_wg, (int)((m - i0 + R - 1) / R));   // row blocks of this workgroup
 
-    ChunkStager16<RP> stg;
-    stg.fetch(G, i0, m, n, 0, tid, wave);                             // in flight while the plan's header arrives
+    ChunkStager<D, WHOLE> stg;
+    stg.fetch(G, i0, m, n, 0, tid);                             // in flight while the plan's header arrives
     PlanHeaderPtr H = as_const<PlanHeader>(plan);
     if (!plan_matches(H, m, n, r, d)) {                               // not a plan for this problem
         poison_s(S, r, block, nblocks, tid, kThreadsGQ);
@@ -404,20 +418,30 @@ __global__ __launch_bounds__(kThreadsGQ, RP == 1 ? 4 : 1) void k_compress_gq16(c
         const int64_t total = (int64_t)r * r;
         for (int64_t k = (int64_t)block * kThreadsGQ + tid; k < total; k += (int64_t)nblocks * kThreadsGQ) S[k] = 0.0f;
     }
-    if (tid < 2 * RP) *reinterpret_cast<f32x4*>(smem + tid * kPlaneStride + kChunk * 16) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    if (H->nslots == 1)      gq16_one_slot<D, RP>(stg, smem, G, plan, H, T, i0, nblk, m, n, r, tid, lane, wave);
-    else if (H->nslots == 2) gq16_multi_slot<D, 2, RP>(stg, smem, G, plan, H, T, i0, nblk, m, n, r, tid, lane, wave);
-    else                     gq16_multi_slot<D, kMaxSlots, RP>(stg, smem, G, plan, H, T, i0, nblk, m, n, r, tid, lane, wave);
+    if (tid < 2) *reinterpret_cast<f32x4*>(smem + tid * kPlaneStride + kChunk * 16) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    if (H->nslots == 1)      gq_one_slot<D, WHOLE>(stg, smem, G, plan, H, T, i0, nblk, m, n, r, tid, lane, wave);
+    else if (H->nslots == 2) gq_multi_slot<D, 2, WHOLE>(stg, smem, G, plan, H, T, i0, nblk, m, n, r, tid, lane, wave);
+    else                     gq_multi_slot<D, kMaxSlots, WHOLE>(stg, smem, G, plan, H, T, i0, nblk, m, n, r, tid, lane, wave);
 }
 
-
 template <typename D>
-static hipError_t launch_gq16(const CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, hipStream_t st) {
-    constexpr int RP = kRowsGQ16 / 8;
-    constexpr size_t lds = (size_t)2 * RP * kPlaneStride;    // two chunk buffers of RP 8-row planes
+static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, hipStream_t st) {
+    constexpr size_t lds = (size_t)2 * kPlaneStride;                  // two chunk buffers
+    bool whole = true;
+    g.first_gq[0] = 0;
+    for (int p = 0; p < g.count; ++p) {
+        g.first_gq[p + 1] = g.first_gq[p] + ((g.m[p] + kRowsGQ<D> - 1) / kRowsGQ<D> + blocks_per_wg - 1) / blocks_per_wg;
+        whole = whole && g.n[p] % 4 == 0;
+    }
+    const dim3 grid((unsigned)g.first_gq[g.count]);
     hipError_t e;
-    if ((e = allow_dynamic_lds<k_compress_gq16<D, RP>>(lds)) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_compress_gq16<D, RP>), dim3((unsigned)g.first_gq[g.count]), dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, blocks_per_wg);
+    if (whole) {
+        if ((e = allow_dynamic_lds<k_compress_gq<D, true>>(lds)) != hipSuccess) return e;
+        hipLaunchKernelGGL((k_compress_gq<D, true>), grid, dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, blocks_per_wg);
+    } else {
+        if ((e = allow_dynamic_lds<k_compress_gq<D, false>>(lds)) != hipSuccess) return e;
+        hipLaunchKernelGGL((k_compress_gq<D, false>), grid, dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, blocks_per_wg);
+    }
     return hipGetLastError();
 }
 

@@ -1,0 +1,8 @@
+// Kernel A of the compress path for fp32 storage (see compress_gq.h).
+#include "compress_gq.h"
+
+namespace lsp {
+hipError_t launch_gq_f32(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, hipStream_t st) {
+    return launch_gq<F32>(g, r, d, blocks_per_wg, st);
+}
+}  // namespace lsp

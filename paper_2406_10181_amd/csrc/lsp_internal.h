@@ -177,10 +177,8 @@ __device__ __forceinline__ int group_find(const int32_t* first, int count, int b
 
 // ------------------------------------------------------------------------------------------
 // Kernel launchers (each returns hipSuccess or the launch error).  The group launchers fill in
-// first_* themselves; all problems of a group must agree on what selects the kernel variant
-// (see compress_group_uniform).
+// first_* themselves.
 // ------------------------------------------------------------------------------------------
-bool       compress_group_uniform(const CompressGroup& g);
 hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st);
 // Scatter form on raw ELL arrays.  gate (device, may be null): the kernels run only if *gate == LSP_ERR_SKEW.
 hipError_t launch_compress_raw(const void* G, const int32_t* P_idx, const float* P_val,

@@ -127,6 +127,23 @@ def test_edge_shapes(m, n, r, d, dtype):
     _full_check(pb)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("m,n,r,d", [
+    (9, 1, 1, 1), (8, 2, 2, 1), (5, 3, 3, 2),            # pieces of G shorter than four elements
+    (17, 2049, 6, 3), (16, 2050, 7, 3), (19, 2051, 9, 3),   # one, two, three elements in the last piece, rows left over
+    (12, 4093, 515, 4),                                  # two columns per lane
+    (1200, 61, 5, 2),                                    # rows of P^T cut into pieces that add up, overlapping quads of S
+])
+def test_compress_at_the_edges_of_the_pieces(m, n, r, d, dtype):
+    import gpu_util as gu
+    pb = syn.make_problem(f"piece_{m}x{n}_r{r}_d{d}", m, n, r, d, dtype, seed=370 + m + n, g_std=0.5, index_dist="uniform")
+    print(f"[case] {pb.name} {dtype}", flush=True)
+    S_o = oracle.compress(pb.G, dtype, pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val, r, threads=THREADS)
+    dp = _dp(pb)
+    gu.check_compress(dp.compress_planned(), S_o, pb.name)
+    gu.check_compress(dp.compress_raw(), S_o, pb.name + " raw")
+
+
 @pytest.mark.parametrize("m,n,r,d,dtype", [
     (33, 1025, 67, 1, "bf16"),       # odd n, one column in the second pass
     (9, 1027, 3, 3, "f16"),          # fewer than four columns of U
