@@ -10,6 +10,7 @@
 //      and the two independent products of each stage share a launch.
 // Runs once per change of projectors; nothing here is on the per-step path.
 #include <algorithm>
+#include <type_traits>
 
 #include "lsp_internal.h"
 
@@ -27,7 +28,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // index outside [0, r) are skipped.  The order of the LDS additions varies: results can differ in the last
 // bits from run to run.
 constexpr int kGramThreads = 1024, kGramAccFloats = 12288, kGramQueue = 4096, kGramInFlight = 8;
-__global__ __launch_bounds__(kGramThreads) void k_gram(const GramBatch batch, int d, int r, int block_rows) {
+__global__ __launch_bounds__(kGramThreads) void k_gram(const GramBatch batch, int d, int r, int block_rows, const GramClear clear) {
     __shared__ float acc[kGramAccFloats];
     __shared__ int queue[kGramQueue];
     __shared__ int queued;
@@ -47,29 +48,38 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(const GramBatch batch, in
         if (v != 0.0f && (unsigned)b < (unsigned)r) atomicAdd(&acc[(a - a0) * r + b], v * x);
     };
     const int total = (int)(P.rows * d);                            // < 2^31, checked by the host
-    for (int t0 = 0; t0 < total; t0 += kGramThreads * kGramInFlight) {       // uniform trip count: the ballots need whole waves
-        int a[kGramInFlight];
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    typedef i32x4 loose __attribute__((aligned(4)));
+    auto scan = [&](int t, int a) {
+        const bool hit = a >= a0 && a < a1;
+        const uint64_t mask = __ballot(hit);
+        if (mask == 0) return;
+        int base = 0;
+        if (lane == __ffsll((long long)mask) - 1) base = atomicAdd(&queued, __popcll(mask));
+        base = __shfl(base, __ffsll((long long)mask) - 1);
+        if (hit) {
+            const int slot = base + __popcll(mask & ((1ull << lane) - 1));
+            if (slot < kGramQueue) queue[slot] = t;
+            else
+                for (int k2 = 0; k2 < d; ++k2) add_entry(t, a, k2);
+        }
+    };
+    const int quads = total >> 2;
+    for (int t0 = 0; t0 < quads; t0 += kGramThreads * kGramInFlight) {       // uniform trip count: the ballots need whole waves
+        i32x4 a[kGramInFlight];
 #pragma unroll
         for (int u = 0; u < kGramInFlight; ++u) {
             const int t = t0 + u * kGramThreads + (int)threadIdx.x;
-            a[u] = t < total ? P.L_idx[t] : -1;
+            a[u] = t < quads ? *reinterpret_cast<const loose*>(P.L_idx + 4 * (int64_t)t) : i32x4{-1, -1, -1, -1};
         }
 #pragma unroll
-        for (int u = 0; u < kGramInFlight; ++u) {
-            const bool hit = a[u] >= a0 && a[u] < a1;
-            const uint64_t mask = __ballot(hit);
-            if (mask == 0) continue;
-            int base = 0;
-            if (lane == __ffsll((long long)mask) - 1) base = atomicAdd(&queued, __popcll(mask));
-            base = __shfl(base, __ffsll((long long)mask) - 1);
-            if (hit) {
-                const int t = t0 + u * kGramThreads + (int)threadIdx.x;
-                const int slot = base + __popcll(mask & ((1ull << lane) - 1));
-                if (slot < kGramQueue) queue[slot] = t;
-                else
-                    for (int k2 = 0; k2 < d; ++k2) add_entry(t, a[u], k2);
-            }
-        }
+        for (int u = 0; u < kGramInFlight; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) scan(4 * (t0 + u * kGramThreads + (int)threadIdx.x) + q, a[u][q]);
+    }
+    if (threadIdx.x < kWave) {                                      // what is left of the last four
+        const int t = 4 * quads + lane;
+        scan(t, t < total ? P.L_idx[t] : -1);
     }
     __syncthreads();
     const int work = min(queued, kGramQueue) * d;
@@ -96,10 +106,13 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(const GramBatch batch, in
     }
     __syncthreads();
     for (int q = threadIdx.x; q < mine; q += kGramThreads) P.C[(int64_t)a0 * r + q] = acc[q];
-}
-
-__global__ __launch_bounds__(256) void k_zero(float* __restrict__ p, int64_t count) {
-    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < count; k += (int64_t)gridDim.x * 256) p[k] = 0.0f;
+    if (clear.p) {
+        PlanHeaderPtr H = as_const<PlanHeader>(clear.plan);
+        if (H->magic == kPlanMagic && H->p_any_split)
+            for (int64_t k = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kGramThreads + threadIdx.x; k < clear.count;
+                 k += (int64_t)gridDim.x * gridDim.y * kGramThreads)
+                clear.p[k] = 0.0f;
+    }
 }
 
 // C = op(A) op(B) + beta E, all r x r row-major fp32; op squares every element (sqa, sqb) or transposes the
@@ -184,6 +197,7 @@ __global__ __launch_bounds__(256) void k_gemm_rr(const GemmBatch batch, int r) {
             if (i < r && j < r) {
                 if (P.E) sum = fmaf(P.beta, P.E[(int64_t)i * r + j], sum);
                 P.C[(int64_t)i * r + j] = sum;
+                if (P.Ct) P.Ct[(int64_t)j * r + i] = sum;
             }
         }
     }
@@ -227,38 +241,38 @@ __global__ __launch_bounds__(256) void k_gemm_rr4(const GemmBatch batch, int r) 
     float* const as0 = As + a_mn * kTileRow4 + a_k;
     float* const bs0 = Bs + b_mn * kTileRow4 + b_k;
     const int as_step = a_kc ? 8 * kTileRow4 : 32, bs_step = b_kc ? 8 * kTileRow4 : 32;
-    f32x4 an[kTileGroups], bn[kTileGroups];
+    f32x4 an[2][kTileGroups], bn[2][kTileGroups];                   // the next two tiles
     const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-    auto fetch = [&](int k0) {
+    auto fetch = [&](auto set, int k0) {
+        constexpr int Z = decltype(set)::value;
 #pragma unroll
         for (int e = 0; e < kTileGroups; ++e) {
             const bool aok = row0 + a_mn + (a_kc ? 8 * e : 0) < r && k0 + a_k + (a_kc ? 0 : 32 * e) < r;
-            const f32x4 a = aok ? *reinterpret_cast<const f32x4*>(A + a_off + e * a_step + k0 * a_kstep) : zero4;
-            an[e] = sqa ? a * a : a;
+            an[Z][e] = aok ? *reinterpret_cast<const f32x4*>(A + a_off + e * a_step + k0 * a_kstep) : zero4;
             const bool bok = col0 + b_mn + (b_kc ? 8 * e : 0) < r && k0 + b_k + (b_kc ? 0 : 32 * e) < r;
-            const f32x4 b = bok ? *reinterpret_cast<const f32x4*>(B + b_off + e * b_step + k0 * b_kstep) : zero4;
-            bn[e] = sqb ? b * b : b;
+            bn[Z][e] = bok ? *reinterpret_cast<const f32x4*>(B + b_off + e * b_step + k0 * b_kstep) : zero4;
         }
     };
-    fetch(0);
     const float* ap = As + (lane & 31) * kTileRow4 + wave * (kTileK / 4) + 4 * (lane >> 5);
     const float* bp = Bs + (lane & 31) * kTileRow4 + wave * (kTileK / 4) + 4 * (lane >> 5);
-    for (int k0 = 0; k0 < r; k0 += kTileK) {
+    auto tile = [&](auto set, int k0) {
+        constexpr int Z = decltype(set)::value;
 #pragma unroll
         for (int e = 0; e < kTileGroups; ++e) {
-            if (a_kc) *reinterpret_cast<f32x4*>(as0 + e * as_step) = an[e];
+            const f32x4 a = sqa ? an[Z][e] * an[Z][e] : an[Z][e], b = sqb ? bn[Z][e] * bn[Z][e] : bn[Z][e];
+            if (a_kc) *reinterpret_cast<f32x4*>(as0 + e * as_step) = a;
             else {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) as0[e * as_step + s * kTileRow4] = an[e][s];
+                for (int s = 0; s < 4; ++s) as0[e * as_step + s * kTileRow4] = a[s];
             }
-            if (b_kc) *reinterpret_cast<f32x4*>(bs0 + e * bs_step) = bn[e];
+            if (b_kc) *reinterpret_cast<f32x4*>(bs0 + e * bs_step) = b;
             else {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) bs0[e * bs_step + s * kTileRow4] = bn[e][s];
+                for (int s = 0; s < 4; ++s) bs0[e * bs_step + s * kTileRow4] = b[s];
             }
         }
         __syncthreads();
-        if (k0 + kTileK < r) fetch(k0 + kTileK);
+        fetch(set, k0 + 2 * kTileK);                                // past r: nothing is read
 #pragma unroll
         for (int g = 0; g < kTileK / 4 / 8; ++g) {                  // a wave's quarter of the tile, 8 k at a time
             const f32x4 a = *reinterpret_cast<const f32x4*>(ap + 8 * g);
@@ -267,6 +281,14 @@ __global__ __launch_bounds__(256) void k_gemm_rr4(const GemmBatch batch, int r) 
             for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b[s], acc, 0, 0, 0);
         }
         __syncthreads();
+    };
+    constexpr std::integral_constant<int, 0> kEven{};
+    constexpr std::integral_constant<int, 1> kOdd{};
+    fetch(kEven, 0);
+    fetch(kOdd, kTileK);
+    for (int k0 = 0; k0 < r; k0 += 2 * kTileK) {
+        tile(kEven, k0);
+        tile(kOdd, k0 + kTileK);                                    // past r: all zeros
     }
 #pragma unroll
     for (int v = 0; v < 16; ++v) Cs[wave][v][lane] = acc[v];
@@ -280,19 +302,13 @@ __global__ __launch_bounds__(256) void k_gemm_rr4(const GemmBatch batch, int r) 
             if (i < r && j < r) {
                 if (P.E) sum = fmaf(P.beta, P.E[(int64_t)i * r + j], sum);
                 P.C[(int64_t)i * r + j] = sum;
+                if (P.Ct) P.Ct[(int64_t)j * r + i] = sum;
             }
         }
     }
 }
 
-static dim3 blocks_for(int64_t count) { return dim3((unsigned)((count + 255) / 256 > 2048 ? 2048 : (count + 255) / 256)); }
-
-hipError_t launch_zero(float* p, int64_t count, hipStream_t st) {
-    hipLaunchKernelGGL(k_zero, blocks_for(count), dim3(256), 0, st, p, count);
-    return hipGetLastError();
-}
-
-hipError_t launch_gram(const GramBatch& batch, int count, int32_t d, int32_t r, hipStream_t st) {
+hipError_t launch_gram(const GramBatch& batch, int count, int32_t d, int32_t r, const GramClear* clear, hipStream_t st) {
     if (count < 1 || count > 2 || r > kGramAccFloats) return hipErrorInvalidValue;
     for (int z = 0; z < count; ++z)
         if (batch.p[z].rows * d > INT32_MAX) return hipErrorInvalidValue;
@@ -300,7 +316,7 @@ hipError_t launch_gram(const GramBatch& batch, int count, int32_t d, int32_t r, 
     // per CU rather than packed into as few as LDS allows (each workgroup scans all of L_idx either way)
     const int block_rows = std::max(1, std::min(kGramAccFloats / (int)r, ((int)r * count + 255) / 256));
     hipLaunchKernelGGL(k_gram, dim3((unsigned)((r + block_rows - 1) / block_rows), (unsigned)count), dim3(kGramThreads), 0, st,
-                       batch, (int)d, (int)r, block_rows);
+                       batch, (int)d, (int)r, block_rows, clear ? *clear : GramClear{});
     return hipGetLastError();
 }
 
@@ -328,15 +344,15 @@ hipError_t launch_reproject(const int32_t* P_idx, const float* P_val, const int3
     GramBatch grams{};
     grams.p[0] = GramPair{P_idx, P_val, Pp_idx, Pp_val, m, A};
     grams.p[1] = GramPair{Qp_idx, Qp_val, Q_idx, Q_val, n, B};
-    hipError_t e = launch_gram(grams, 2, d, r, st);
+    hipError_t e = launch_gram(grams, 2, d, r, nullptr, st);
     if (e != hipSuccess) return e;
     // X = A M and X2 = (A o A) V in one launch, then M = X B and V = X2 (B o B) in another
     float* X2 = workspace + 3 * rr;
     GemmBatch left{}, right{};
-    left.p[0] = GemmProblem{A, M, X, nullptr, 0.0f, 0};
-    left.p[1] = GemmProblem{A, V, X2, nullptr, 0.0f, kGemmSqA};
-    right.p[0] = GemmProblem{X, B, M, nullptr, 0.0f, 0};
-    right.p[1] = GemmProblem{X2, B, V, nullptr, 0.0f, kGemmSqB};
+    left.p[0] = GemmProblem{A, M, X, nullptr, 0.0f, 0, nullptr};
+    left.p[1] = GemmProblem{A, V, X2, nullptr, 0.0f, kGemmSqA, nullptr};
+    right.p[0] = GemmProblem{X, B, M, nullptr, 0.0f, 0, nullptr};
+    right.p[1] = GemmProblem{X2, B, V, nullptr, 0.0f, kGemmSqB, nullptr};
     if ((e = launch_gemm_rr_batch(left, V ? 2 : 1, r, st)) != hipSuccess) return e;
     return launch_gemm_rr_batch(right, V ? 2 : 1, r, st);
 }
