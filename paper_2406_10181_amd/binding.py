@@ -115,11 +115,24 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+_call = None
+
+
+def _bound():
+    """The call module (csrc/pycall.cpp) with the library's per-step entry points; like the library, it has no fallback."""
+    global _call
+    if _call is None:
+        L = lib()
+        from . import _call as module
+        module.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            L.lsp_compress_planned, L.lsp_decompress_apply, L.lsp_compress_planned_grouped, L.lsp_decompress_apply_grouped)))
+        _call = module
+    return _call
+
+
 def _ptr(x) -> Optional[int]:
     """Device (or host) address of a torch tensor / numpy array / raw int; None stays NULL."""
-    if x is None:
-        return None
-    if isinstance(x, int):
+    if x is None or isinstance(x, int):
         return x
     if hasattr(x, "data_ptr"):
         return x.data_ptr()
@@ -129,9 +142,7 @@ def _ptr(x) -> Optional[int]:
 
 
 def _stream(stream) -> Optional[int]:
-    if stream is None:
-        return None
-    if isinstance(stream, int):
+    if stream is None or isinstance(stream, int):
         return stream
     return stream.cuda_stream          # torch.cuda.Stream
 
@@ -210,9 +221,8 @@ def lsp_plan_build_host(P_idx, P_val, Q_idx, Q_val, m, n, r, d, plan_host, plan_
 
 def lsp_compress_planned(G, plan, m, n, r, d, S, dtype: int, workspace, workspace_bytes, stream=None,
                          check: bool = True) -> int:
-    rc = lib().lsp_compress_planned(_ptr(G), _ptr(plan), m, n, r, d, _ptr(S), dtype, _ptr(workspace),
-                                    workspace_bytes, _stream(stream))
-    if check:
+    rc = (_call or _bound()).compress_planned(G, plan, m, n, r, d, S, dtype, workspace, workspace_bytes, stream)
+    if check and rc:
         _check(rc, "lsp_compress_planned")
     return rc
 
@@ -230,9 +240,8 @@ def lsp_compress_planned_static(G, plan, m, n, r, d, S, dtype: int, stream=None,
 
 def lsp_decompress_apply(W, S, P_idx, P_val, Q_idx, Q_val, m, n, r, d, dtype: int, stream=None,
                          check: bool = True) -> int:
-    rc = lib().lsp_decompress_apply(_ptr(W), _ptr(S), _ptr(P_idx), _ptr(P_val), _ptr(Q_idx), _ptr(Q_val),
-                                    m, n, r, d, dtype, _stream(stream))
-    if check:
+    rc = (_call or _bound()).decompress_apply(W, S, P_idx, P_val, Q_idx, Q_val, m, n, r, d, dtype, stream)
+    if check and rc:
         _check(rc, "lsp_decompress_apply")
     return rc
 
@@ -298,18 +307,16 @@ def apply_items(problems):
 
 def lsp_compress_planned_grouped(items, count, r, d, dtype: int, stream=None, check: bool = True) -> int:
     """items: a ctypes array from compress_items() (kept alive by the caller for the call)."""
-    rc = lib().lsp_compress_planned_grouped(ctypes.addressof(items) if items is not None else None, count, r, d, dtype,
-                                            _stream(stream))
-    if check:
+    rc = (_call or _bound()).compress_planned_grouped(ctypes.addressof(items) if items is not None else None, count, r, d, dtype, stream)
+    if check and rc:
         _check(rc, "lsp_compress_planned_grouped")
     return rc
 
 
 def lsp_decompress_apply_grouped(items, count, r, d, dtype: int, stream=None, check: bool = True) -> int:
     """items: a ctypes array from apply_items()."""
-    rc = lib().lsp_decompress_apply_grouped(ctypes.addressof(items) if items is not None else None, count, r, d, dtype,
-                                            _stream(stream))
-    if check:
+    rc = (_call or _bound()).decompress_apply_grouped(ctypes.addressof(items) if items is not None else None, count, r, d, dtype, stream)
+    if check and rc:
         _check(rc, "lsp_decompress_apply_grouped")
     return rc
 

@@ -1,18 +1,20 @@
 """Builds the HIP library in-tree with hipcc for gfx950 (cross-compiles without a GPU).
 
 Every source is compiled to an object of its own (in parallel) and the objects are linked into
-liblsp_hip.so beside this file."""
+liblsp_hip.so beside this file; the Python side's call module is built beside it."""
 from __future__ import annotations
 
 import concurrent.futures
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "liblsp_hip.so")
+CALL_MODULE = os.path.join(PKG, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 OBJDIR = os.path.join(PKG, "_build")
 SOURCES = ["compress_gq_bf16.hip", "compress_gq_f16.hip", "compress_gq_f32.hip", "plan_device.hip", "decompress.hip",
            "compress.hip", "api.cpp", "plan.cpp", "reproject.hip", "dense.hip", "fitgrad.hip", "noalloc.hip", "probe.hip"]
@@ -70,7 +72,22 @@ def build(verbose: bool = True, save_temps: bool = False, out: str = LIB, define
     if verbose:
         print(" ".join(link), flush=True)
     subprocess.check_call(link, cwd=objdir)
+    if out == LIB:
+        build_call_module(verbose, incremental)
     return out
+
+
+def build_call_module(verbose: bool = True, incremental: bool = False) -> str:
+    """The CPython module with the argument marshalling of the per-step entry points."""
+    src = os.path.join(CSRC, "pycall.cpp")
+    if incremental and os.path.exists(CALL_MODULE) and os.path.getmtime(CALL_MODULE) > os.path.getmtime(src):
+        return CALL_MODULE
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I", sysconfig.get_paths()["include"],
+           "-I", os.path.join(ROOT, "include"), src, "-o", CALL_MODULE]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    return CALL_MODULE
 
 
 if __name__ == "__main__":
