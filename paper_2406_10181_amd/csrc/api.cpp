@@ -82,8 +82,8 @@ int lsp_compress(const void* G, const int32_t* P_idx, const float* P_val, const 
     if (!aligned16(workspace)) return LSP_ERR_WORKSPACE;
     if (!aligned16(G) || !aligned16(S) || !aligned16(P_idx) || !aligned16(P_val) || !aligned16(Q_idx) || !aligned16(Q_val))
         return LSP_ERR_ALIGN;
-    // A plan is built on the device into the workspace, the planned kernels run on it, and the scatter-form
-    // kernels follow, which do their work only if the build found the columns too skewed for a plan.
+    // A plan is built on the device into the workspace, the planned kernels run on it, and the scatter form
+    // follows, which works only if the build found the columns too skewed for a plan.
     uint8_t* ws = static_cast<uint8_t*>(workspace);
     float* T = reinterpret_cast<float*>(ws);
     uint8_t* plan = ws + t_bytes(m, r);
@@ -95,8 +95,8 @@ int lsp_compress(const void* G, const int32_t* P_idx, const float* P_val, const 
     lsp::CompressGroup g;
     std::memset(&g, 0, sizeof(g));
     g.count = 1; g.G[0] = G; g.plan[0] = plan; g.T[0] = T; g.S[0] = S; g.m[0] = (int32_t)m; g.n[0] = (int32_t)n;
-    if ((e = lsp::launch_compress_planned(g, r, d, dtype, st)) != hipSuccess) return fail_launch(e);
-    e = lsp::launch_compress_raw(G, P_idx, P_val, Q_idx, Q_val, m, n, r, d, S, dtype, T, status, st);
+    if ((e = lsp::launch_compress_planned(g, r, d, dtype, st, 0.0f)) != hipSuccess) return fail_launch(e);
+    e = lsp::launch_compress_raw(G, P_idx, P_val, Q_idx, Q_val, m, n, r, d, S, dtype, status, st);
     return e == hipSuccess ? LSP_OK : fail_launch(e);
 }
 

@@ -124,20 +124,22 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup 
 }
 
 // ----------------------------------------------------------------------------------------------
-// Plan-free variant used by the raw-ELL entry: same mathematics in scatter form.
-//   T tile in LDS, every (row, column j, entry k) adds G[i][j] * Q_val[j][k] to T[i][Q_idx[j][k]];
-//   then S[P_idx[i][k]][:] += P_val[i][k] * T[i][:] with global atomics (the first kernel zeroes S).
-// Behind a plan build they are launched with a gate and nearly always have nothing to do, so they are two small launches.
+// Scatter form behind a plan build that found the columns too skewed (`status`); S has been set to zero by kernel A.
+// The same mathematics: with a tile of T in LDS, every (row, column j, entry k) adds G[i][j] * Q_val[j][k] to
+// T[i][Q_idx[j][k]]; then S[P_idx[i][k]][:] += P_val[i][k] * T[i][:] with global atomics.  Nearly always there is nothing
+// to do, so it is one launch.  A build that met an index outside [0, r) leaves S full of NaN.
 constexpr int kRawRows = 16;
 template <typename D>
-__global__ __launch_bounds__(256) void k_raw_gq(const typename D::elem* __restrict__ G,
-                                               const int32_t* __restrict__ Q_idx, const float* __restrict__ Q_val,
-                                               float* __restrict__ T, float* __restrict__ S, int m, int n, int r, int d,
-                                               const int32_t* __restrict__ gate) {
+__global__ __launch_bounds__(256) void k_raw(const typename D::elem* __restrict__ G, const int32_t* __restrict__ P_idx, const float* __restrict__ P_val,
+                                            const int32_t* __restrict__ Q_idx, const float* __restrict__ Q_val, float* __restrict__ S,
+                                            int m, int n, int r, int d, const int32_t* __restrict__ status) {
     extern __shared__ __align__(16) uint8_t smem[];
-    if (gate && *gate != LSP_ERR_SKEW) return;                        // the planned kernels have done the work
+    if (*status == LSP_OK) return;                                    // the planned kernels have done the work
+    if (*status != LSP_ERR_SKEW) {
+        fill_s(S, __builtin_nanf(""), r, blockIdx.x, gridDim.x, threadIdx.x, 256);
+        return;
+    }
     float* Tl = reinterpret_cast<float*>(smem);
-    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < (int64_t)r * r; k += (int64_t)gridDim.x * 256) S[k] = 0.0f;
     const int64_t i0 = (int64_t)blockIdx.x * kRawRows;
     for (int k = threadIdx.x; k < kRawRows * r; k += 256) Tl[k] = 0.0f;
     __syncthreads();
@@ -153,21 +155,11 @@ __global__ __launch_bounds__(256) void k_raw_gq(const typename D::elem* __restri
         }
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < kRawRows * r; k += 256) {
-        const int t = k / r;
-        if (i0 + t < m) T[(i0 + t) * (int64_t)r + (k - t * r)] = Tl[k];
-    }
-}
-
-__global__ __launch_bounds__(256) void k_raw_pt(const float* __restrict__ T, const int32_t* __restrict__ P_idx,
-                                               const float* __restrict__ P_val, float* __restrict__ S, int m, int r, int d,
-                                               const int32_t* __restrict__ gate) {
-    if (gate && *gate != LSP_ERR_SKEW) return;
-    for (int64_t i = blockIdx.x; i < m; i += gridDim.x)
+    for (int t = 0; t < kRawRows && i0 + t < m; ++t)
         for (int k = 0; k < d; ++k) {
-            const int a = P_idx[i * d + k];
-            const float v = P_val[i * d + k];
-            for (int b = threadIdx.x; b < r; b += 256) atomicAdd(&S[(int64_t)a * r + b], v * T[i * r + b]);
+            const int a = P_idx[(i0 + t) * d + k];
+            const float v = P_val[(i0 + t) * d + k];
+            for (int b = threadIdx.x; b < r; b += 256) atomicAdd(&S[(int64_t)a * r + b], v * Tl[t * r + b]);
         }
 }
 
@@ -179,11 +171,11 @@ static int gq_blocks_per_wg(const CompressGroup& g) {
     return rows >= 16384 ? 2 : 1;
 }
 
-static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, lsp_dtype dtype, hipStream_t st) {
+static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, float unplanned, lsp_dtype dtype, hipStream_t st) {
     switch (dtype) {
-        case LSP_F32:  return launch_gq_f32(g, r, d, blocks_per_wg, st);
-        case LSP_F16:  return launch_gq_f16(g, r, d, blocks_per_wg, st);
-        default:       return launch_gq_bf16(g, r, d, blocks_per_wg, st);
+        case LSP_F32:  return launch_gq_f32(g, r, d, blocks_per_wg, unplanned, st);
+        case LSP_F16:  return launch_gq_f16(g, r, d, blocks_per_wg, unplanned, st);
+        default:       return launch_gq_bf16(g, r, d, blocks_per_wg, unplanned, st);
     }
 }
 
@@ -199,7 +191,7 @@ static void longest_first(CompressGroup& g) {
         }
 }
 
-hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st) {
+hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st, float unplanned) {
     const int nstripes = (r + kStripeQuads * 4 - 1) / (kStripeQuads * 4);
     const bool striped = r >= 4;
     longest_first(g);
@@ -208,7 +200,7 @@ hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_d
         const int32_t items = (int32_t)plan_max_items(g.m[p], r, d);
         g.first_pt[p + 1] = g.first_pt[p] + (striped ? ((items + 3) / 4) * 8 : items * nstripes);
     }
-    hipError_t e = launch_gq(g, r, d, gq_blocks_per_wg(g), dtype, st);
+    hipError_t e = launch_gq(g, r, d, gq_blocks_per_wg(g), unplanned, dtype, st);
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)g.first_pt[g.count];
     if (striped) {
@@ -223,29 +215,22 @@ hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_d
 }
 
 template <typename D>
-static hipError_t launch_raw_gq(const void* G, const int32_t* Q_idx, const float* Q_val, float* T, float* S,
-                                int64_t m, int64_t n, int32_t r, int32_t d, const int32_t* gate, hipStream_t st) {
-    const size_t lds = (size_t)kRawRows * r * sizeof(float);
-    hipError_t e = allow_dynamic_lds<k_raw_gq<D>>((size_t)kRawRows * LSP_MAX_R * sizeof(float));
+static hipError_t launch_raw(const void* G, const int32_t* P_idx, const float* P_val, const int32_t* Q_idx, const float* Q_val,
+                             int64_t m, int64_t n, int32_t r, int32_t d, float* S, const int32_t* status, hipStream_t st) {
+    hipError_t e = allow_dynamic_lds<k_raw<D>>((size_t)kRawRows * LSP_MAX_R * sizeof(float));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_raw_gq<D>, dim3((unsigned)((m + kRawRows - 1) / kRawRows)), dim3(256), lds, st,
-                       reinterpret_cast<const typename D::elem*>(G), Q_idx, Q_val, T, S, (int)m, (int)n, (int)r, (int)d, gate);
+    hipLaunchKernelGGL(k_raw<D>, dim3((unsigned)((m + kRawRows - 1) / kRawRows)), dim3(256), (size_t)kRawRows * r * sizeof(float), st,
+                       static_cast<const typename D::elem*>(G), P_idx, P_val, Q_idx, Q_val, S, (int)m, (int)n, (int)r, (int)d, status);
     return hipGetLastError();
 }
 
-hipError_t launch_compress_raw(const void* G, const int32_t* P_idx, const float* P_val,
-                               const int32_t* Q_idx, const float* Q_val,
-                               int64_t m, int64_t n, int32_t r, int32_t d,
-                               float* S, lsp_dtype dtype, float* T, const int32_t* gate, hipStream_t st) {
-    hipError_t e;
+hipError_t launch_compress_raw(const void* G, const int32_t* P_idx, const float* P_val, const int32_t* Q_idx, const float* Q_val,
+                               int64_t m, int64_t n, int32_t r, int32_t d, float* S, lsp_dtype dtype, const int32_t* status, hipStream_t st) {
     switch (dtype) {
-        case LSP_F32:  e = launch_raw_gq<F32>(G, Q_idx, Q_val, T, S, m, n, r, d, gate, st); break;
-        case LSP_F16:  e = launch_raw_gq<F16>(G, Q_idx, Q_val, T, S, m, n, r, d, gate, st); break;
-        default:       e = launch_raw_gq<BF16>(G, Q_idx, Q_val, T, S, m, n, r, d, gate, st); break;
+        case LSP_F32:  return launch_raw<F32>(G, P_idx, P_val, Q_idx, Q_val, m, n, r, d, S, status, st);
+        case LSP_F16:  return launch_raw<F16>(G, P_idx, P_val, Q_idx, Q_val, m, n, r, d, S, status, st);
+        default:       return launch_raw<BF16>(G, P_idx, P_val, Q_idx, Q_val, m, n, r, d, S, status, st);
     }
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_raw_pt, dim3((unsigned)std::min<int64_t>(m, 2048)), dim3(256), 0, st, T, P_idx, P_val, S, (int)m, (int)r, (int)d, gate);
-    return hipGetLastError();
 }
 
 }  // namespace lsp

@@ -13,14 +13,14 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // A plan is only followed when its header names this very problem: the offsets and counts in it
 // index S and T with the call's r and m, so a plan built for other sizes (or a buffer that holds no
-// plan at all) must not be walked.  Kernel A then fills S with NaN, which is how the caller sees
-// the mistake, and kernel B does nothing; all kernels exit normally.
+// plan at all) must not be walked.  Kernel A then fills S with `unplanned` -- NaN, which is how the caller sees
+// the mistake, or zero when the scatter form follows -- and kernel B does nothing; all kernels exit normally.
 __device__ __forceinline__ bool plan_matches(PlanHeaderPtr H, int m, int n, int r, int d) {
     return H->magic == kPlanMagic && H->m == m && H->n == n && H->r == r && H->d == d;
 }
-__device__ __forceinline__ void poison_s(float* __restrict__ S, int r, int block, int nblocks, int tid, int nthreads) {
+__device__ __forceinline__ void fill_s(float* __restrict__ S, float x, int r, int block, int nblocks, int tid, int nthreads) {
     const int64_t total = (int64_t)r * r;
-    for (int64_t k = (int64_t)block * nthreads + tid; k < total; k += (int64_t)nblocks * nthreads) S[k] = __builtin_nanf("");
+    for (int64_t k = (int64_t)block * nthreads + tid; k < total; k += (int64_t)nblocks * nthreads) S[k] = x;
 }
 
 
@@ -87,8 +87,8 @@ __device__ __forceinline__ void swap_owner(uint8_t* area, float (&acc)[R], uint3
 
 // Launchers of kernel A (they fill in first_gq): one workgroup = a block of rows of G at a time, 512 threads, one lane
 // per (virtual) column of T.
-hipError_t launch_gq_bf16(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, hipStream_t st);
-hipError_t launch_gq_f16(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, hipStream_t st);
-hipError_t launch_gq_f32(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, hipStream_t st);
+hipError_t launch_gq_bf16(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, float unplanned, hipStream_t st);
+hipError_t launch_gq_f16(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, float unplanned, hipStream_t st);
+hipError_t launch_gq_f32(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, float unplanned, hipStream_t st);
 
 }  // namespace lsp

@@ -391,7 +391,7 @@ __device__ __forceinline__ void gq_multi_slot(ChunkStager<D, WHOLE>& stg, uint8_
 }
 
 template <typename D, bool WHOLE>
-__global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGroup grp, int r, int d, int blocks_per_wg) {
+__global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGroup grp, int r, int d, int blocks_per_wg, float unplanned) {
     constexpr int R = kRowsGQ<D>;
     extern __shared__ __align__(16) uint8_t smem[];
     const CompressProblem pr = group_pick(grp, (int)blockIdx.x, false);
@@ -411,7 +411,7 @@ __global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGro
     stg.fetch(G, i0, m, n, 0, tid);                             // in flight while the plan's header arrives
     PlanHeaderPtr H = as_const<PlanHeader>(plan);
     if (!plan_matches(H, m, n, r, d)) {                               // not a plan for this problem
-        poison_s(S, r, block, nblocks, tid, kThreadsGQ);
+        fill_s(S, unplanned, r, block, nblocks, tid, kThreadsGQ);
         return;
     }
     if (H->p_any_split) {
@@ -425,7 +425,7 @@ __global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGro
 }
 
 template <typename D>
-static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, hipStream_t st) {
+static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, float unplanned, hipStream_t st) {
     constexpr size_t lds = (size_t)2 * kPlaneStride;                  // two chunk buffers
     bool whole = true;
     g.first_gq[0] = 0;
@@ -437,10 +437,10 @@ static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, int blocks_p
     hipError_t e;
     if (whole) {
         if ((e = allow_dynamic_lds<k_compress_gq<D, true>>(lds)) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_compress_gq<D, true>), grid, dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, blocks_per_wg);
+        hipLaunchKernelGGL((k_compress_gq<D, true>), grid, dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, blocks_per_wg, unplanned);
     } else {
         if ((e = allow_dynamic_lds<k_compress_gq<D, false>>(lds)) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_compress_gq<D, false>), grid, dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, blocks_per_wg);
+        hipLaunchKernelGGL((k_compress_gq<D, false>), grid, dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, blocks_per_wg, unplanned);
     }
     return hipGetLastError();
 }

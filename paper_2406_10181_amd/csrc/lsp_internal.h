@@ -179,12 +179,14 @@ __device__ __forceinline__ int group_find(const int32_t* first, int count, int b
 // Kernel launchers (each returns hipSuccess or the launch error).  The group launchers fill in
 // first_* themselves.
 // ------------------------------------------------------------------------------------------
-hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st);
-// Scatter form on raw ELL arrays.  gate (device, may be null): the kernels run only if *gate == LSP_ERR_SKEW.
+// unplanned: what S is filled with if the plan turns out not to be one for the problem.
+hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st, float unplanned = __builtin_nanf(""));
+// Scatter form on raw ELL arrays, behind a planned compress that left zeros: it works only if *status (device, of the
+// plan build) is LSP_ERR_SKEW, and fills S with NaN if it is another error.
 hipError_t launch_compress_raw(const void* G, const int32_t* P_idx, const float* P_val,
                                const int32_t* Q_idx, const float* Q_val,
                                int64_t m, int64_t n, int32_t r, int32_t d,
-                               float* S, lsp_dtype dtype, float* T, const int32_t* gate, hipStream_t st);
+                               float* S, lsp_dtype dtype, const int32_t* status, hipStream_t st);
 hipError_t launch_decompress(ApplyGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st);
 // Dense-projector ablation of compress on the matrix cores (dense.hip): Pt = P^T [r][m], Qt = Q^T [r][n] in the
 // storage type of G (fp16 / bf16); workspace of dense_workspace_bytes(m, r); shapes must pass dense_shape_ok.
