@@ -148,10 +148,10 @@ __global__ __launch_bounds__(kThreadsSort) void k_plan_sort(uint8_t* __restrict_
     const int part = kChunk / kSubTiles * d;                         // entries of a workgroup's part
     const int run = (part / kWavesSort + kWave - 1) / kWave * kWave; // entries of a wave's run
     const int my_lo = min(sub * part, count), my_hi = min(my_lo + part, count);
-    int32_t* all = reinterpret_cast<int32_t*>(smem);                 // [r] entries of the tile, then first position
-    int32_t* before = all + r;                                       // [r] entries of the tile before this part
+    int32_t* after = reinterpret_cast<int32_t*>(smem);               // [r] entries of the tile behind this part
+    int32_t* before = after + r;                                     // [r] and before it
     int32_t* mine = before + r;                                      // [wave][r] entries of the wave's run, then where the next one goes
-    for (int k = tid; k < (2 + kWavesSort) * r; k += kThreadsSort) all[k] = 0;
+    for (int k = tid; k < (2 + kWavesSort) * r; k += kThreadsSort) after[k] = 0;
     __syncthreads();
     bool bad = false;
     constexpr int kAhead = 8;                                        // loads in flight per thread
@@ -167,9 +167,8 @@ __global__ __launch_bounds__(kThreadsSort) void k_plan_sort(uint8_t* __restrict_
             const int e = e0 + k * kThreadsSort + tid;
             if (e >= count) continue;
             if (b[k] < 0 || b[k] >= r) { bad = true; b[k] = 0; }
-            atomicAdd(&all[b[k]], 1);
-            if (e < my_lo) atomicAdd(&before[b[k]], 1);
-            else if (e < my_hi) atomicAdd(&mine[((e - my_lo) / run) * r + b[k]], 1);
+            int32_t* which = e < my_lo ? before : e < my_hi ? mine + ((e - my_lo) / run) * r : after;
+            atomicAdd(&which[b[k]], 1);
         }
     }
     bad = __syncthreads_or(bad);
@@ -178,7 +177,12 @@ __global__ __launch_bounds__(kThreadsSort) void k_plan_sort(uint8_t* __restrict_
     int32_t carry = 0;
     for (int b0 = 0; b0 < r; b0 += kThreadsSort) {
         const int b = b0 + tid;
-        const int32_t len = b < r ? all[b] : 0;
+        int32_t len = 0;
+        if (b < r) {
+            len = before[b] + after[b];
+#pragma unroll
+            for (int v = 0; v < kWavesSort; ++v) len += mine[v * r + b];
+        }
         int32_t total;
         int32_t at = carry + block_exclusive<kWavesSort>(len, s_part, total);
         carry += total;
@@ -273,10 +277,13 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
     __shared__ int32_t s_own[LSP_MAX_R], s_first[LSP_MAX_R], s_part[kWavesGQ];
     __shared__ int16_t s_vcol[kMaxSlots * kThreadsGQ];
     __shared__ int32_t s_vown[kMaxSlots * kThreadsGQ], s_longest[kThreadsGQ];
+    __shared__ int32_t s_start[LSP_MAX_R], s_end[LSP_MAX_R];         // this chunk's lists
     __shared__ uint32_t s_key[kThreadsGQ];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if ((int)blockIdx.x == nchunks) { deal_p(plan, L, s, r, nchunks, ptiles, s_part); return; }
     const int c = blockIdx.x;
+    int bad = 0;
+    for (int k = tid; k < (nchunks + ptiles) * kSubTiles; k += kThreadsGQ) bad |= s.bad[k];
     int32_t vneed = 0;
     for (int b0 = 0; b0 < r; b0 += kThreadsGQ) {
         const int b = b0 + tid;
@@ -285,7 +292,9 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
 #pragma unroll 8
             for (int k = 0; k < nchunks; ++k) {
                 const uint32_t* st = s.start + (size_t)k * (r + 1) + b;
-                longest = max(longest, (int32_t)(st[1] - st[0]));
+                const int32_t lo = (int32_t)st[0], hi = (int32_t)st[1];
+                longest = max(longest, hi - lo);
+                if (k == c) { s_start[b] = lo; s_end[b] = hi; }
             }
         }
         const int32_t own = b < r ? max(1, (longest + cap - 1) / cap) : 0;
@@ -343,8 +352,6 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
         shared |= own > 1;
     }
     shared = __syncthreads_or(shared);
-    int bad = 0;
-    for (int k = tid; k < (nchunks + ptiles) * kSubTiles; k += kThreadsGQ) bad |= s.bad[k];
     bad = __syncthreads_or(bad);
     const int32_t status = bad ? LSP_ERR_INDEX : V > kMaxSlots * kThreadsGQ ? LSP_ERR_SKEW : LSP_OK;
     if (status_out && c == 0 && tid == 0) *status_out = status;
@@ -376,11 +383,10 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
     // which virtual column each thread walks (lists dealt to the waves by length when there is one slot)
     uint32_t* seg = reinterpret_cast<uint32_t*>(plan + L.off_q_seg);
     uint16_t* perm = reinterpret_cast<uint16_t*>(plan + L.off_q_perm);
-    const uint32_t* start = s.start + (size_t)c * (r + 1);
     auto list_of = [&](int v, int32_t& lo, int32_t& hi) {
         const int b = s_vcol[v];
         lo = hi = 0;
-        if (b >= 0) share_of(start[b], start[b + 1], s_vown[v], s_own[b], lo, hi);
+        if (b >= 0) share_of((uint32_t)s_start[b], (uint32_t)s_end[b], s_vown[v], s_own[b], lo, hi);
     };
     const bool permuted = nslots == 1;
     const int k_of_w = w < kWavesGQ / 2 ? w : kWavesGQ + kWavesGQ / 2 - 1 - w;      // group of 64 lists that wave w walks

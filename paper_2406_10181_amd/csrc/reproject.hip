@@ -50,36 +50,49 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(const GramBatch batch, in
     const int total = (int)(P.rows * d);                            // < 2^31, checked by the host
     typedef int i32x4 __attribute__((ext_vector_type(4)));
     typedef i32x4 loose __attribute__((aligned(4)));
-    auto scan = [&](int t, int a) {
-        const bool hit = a >= a0 && a < a1;
-        const uint64_t mask = __ballot(hit);
-        if (mask == 0) return;
-        int base = 0;
-        if (lane == __ffsll((long long)mask) - 1) base = atomicAdd(&queued, __popcll(mask));
-        base = __shfl(base, __ffsll((long long)mask) - 1);
-        if (hit) {
-            const int slot = base + __popcll(mask & ((1ull << lane) - 1));
-            if (slot < kGramQueue) queue[slot] = t;
-            else
-                for (int k2 = 0; k2 < d; ++k2) add_entry(t, a, k2);
-        }
-    };
-    const int quads = total >> 2;
-    for (int t0 = 0; t0 < quads; t0 += kGramThreads * kGramInFlight) {       // uniform trip count: the ballots need whole waves
+    const int quads = (total + 3) >> 2;
+    static_assert(4 * kGramInFlight == 32, "one bit for every entry of a batch");
+    for (int t0 = 0; t0 < quads; t0 += kGramThreads * kGramInFlight) {       // uniform trip count: the exchanges need whole waves
         i32x4 a[kGramInFlight];
 #pragma unroll
         for (int u = 0; u < kGramInFlight; ++u) {
             const int t = t0 + u * kGramThreads + (int)threadIdx.x;
-            a[u] = t < quads ? *reinterpret_cast<const loose*>(P.L_idx + 4 * (int64_t)t) : i32x4{-1, -1, -1, -1};
+            a[u] = i32x4{-1, -1, -1, -1};
+            if (4 * t + 3 < total) a[u] = *reinterpret_cast<const loose*>(P.L_idx + 4 * (int64_t)t);
+            else
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    if (4 * t + q < total) a[u][q] = P.L_idx[4 * t + q];
         }
+        uint32_t hits = 0;
 #pragma unroll
         for (int u = 0; u < kGramInFlight; ++u)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) scan(4 * (t0 + u * kGramThreads + (int)threadIdx.x) + q, a[u][q]);
-    }
-    if (threadIdx.x < kWave) {                                      // what is left of the last four
-        const int t = 4 * quads + lane;
-        scan(t, t < total ? P.L_idx[t] : -1);
+            for (int q = 0; q < 4; ++q) hits |= (unsigned)(a[u][q] - a0) < (unsigned)(a1 - a0) ? 1u << (4 * u + q) : 0u;
+        if (__ballot(hits != 0) == 0) continue;
+        // a wave takes its places in the queue at once (one per entry that falls in the block, by an addition of its
+        // own each, cost more than the scan)
+        const int have = __popc(hits);
+        int at = have;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int y = __shfl_up(at, off);
+            if (lane >= off) at += y;
+        }
+        int base = 0;
+        if (lane == kWave - 1) base = atomicAdd(&queued, at);
+        at += __shfl(base, kWave - 1) - have;
+        while (hits) {
+            const int k = __ffs((int)hits) - 1;
+            hits &= hits - 1;
+            const int t = 4 * (t0 + (k >> 2) * kGramThreads + (int)threadIdx.x) + (k & 3);
+            if (at < kGramQueue) queue[at] = t;
+            else {
+                const int row = P.L_idx[t];
+                for (int k2 = 0; k2 < d; ++k2) add_entry(t, row, k2);
+            }
+            ++at;
+        }
     }
     __syncthreads();
     const int work = min(queued, kGramQueue) * d;
