@@ -201,17 +201,15 @@ __global__ __launch_bounds__(256) void k_gemm_rr(const GemmBatch batch, int r) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) Cs[wave][v][lane] = acc[v];
     __syncthreads();
-    if (wave == 0) {
-        const int j = col0 + (lane & 31);
+    const int j = col0 + (lane & 31);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int i = row0 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-            float sum = ((Cs[0][v][lane] + Cs[1][v][lane]) + Cs[2][v][lane]) + Cs[3][v][lane];
-            if (i < r && j < r) {
-                if (P.E) sum = fmaf(P.beta, P.E[(int64_t)i * r + j], sum);
-                P.C[(int64_t)i * r + j] = sum;
-                if (P.Ct) P.Ct[(int64_t)j * r + i] = sum;
-            }
+    for (int q = 0; q < 4; ++q) {                                   // a wave adds up a quarter of the tile
+        const int v = 4 * wave + q, i = row0 + 8 * wave + 4 * (lane >> 5) + q;
+        float sum = ((Cs[0][v][lane] + Cs[1][v][lane]) + Cs[2][v][lane]) + Cs[3][v][lane];
+        if (i < r && j < r) {
+            if (P.E) sum = fmaf(P.beta, P.E[(int64_t)i * r + j], sum);
+            P.C[(int64_t)i * r + j] = sum;
+            if (P.Ct) P.Ct[(int64_t)j * r + i] = sum;
         }
     }
 }
@@ -243,10 +241,12 @@ __global__ __launch_bounds__(256) void k_gemm_rr4(const GemmBatch batch, int r) 
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
     // Group q = tid + 256 e of a tile.  k contiguous in memory: row q / 32, k = 4 (q % 32) .. + 3 (rows step by 8
-    // with e).  Rows contiguous in memory: k = q / 8, rows 4 (q % 8) .. + 3 (k steps by 32 with e).
+    // with e).  Rows contiguous in memory: a wave takes 16 rows (four groups) of 16 k, so that it reads 64-byte pieces and
+    // its 4-byte stores meet no bank twice (with 32 rows of 8 k: four lanes to a bank); k steps by 32 with e.
     const bool a_kc = !ta, b_kc = tb;
-    const int a_mn = a_kc ? tid / 32 : 4 * (tid % 8), a_k = a_kc ? 4 * (tid % 32) : tid / 8;
-    const int b_mn = b_kc ? tid / 32 : 4 * (tid % 8), b_k = b_kc ? 4 * (tid % 32) : tid / 8;
+    const int t_mn = 4 * ((lane & 3) + 4 * (wave & 1)), t_k = (lane >> 2) + 16 * (wave >> 1);
+    const int a_mn = a_kc ? tid / 32 : t_mn, a_k = a_kc ? 4 * (tid % 32) : t_k;
+    const int b_mn = b_kc ? tid / 32 : t_mn, b_k = b_kc ? 4 * (tid % 32) : t_k;
     const int a_off = a_kc ? (row0 + a_mn) * r + a_k : a_k * r + row0 + a_mn;    // r * r < 2^31
     const int b_off = b_kc ? (col0 + b_mn) * r + b_k : b_k * r + col0 + b_mn;
     const int a_step = (a_kc ? 8 : 32) * r, b_step = (b_kc ? 8 : 32) * r;
@@ -306,17 +306,15 @@ __global__ __launch_bounds__(256) void k_gemm_rr4(const GemmBatch batch, int r) 
 #pragma unroll
     for (int v = 0; v < 16; ++v) Cs[wave][v][lane] = acc[v];
     __syncthreads();
-    if (wave == 0) {
-        const int j = col0 + (lane & 31);
+    const int j = col0 + (lane & 31);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int i = row0 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-            float sum = ((Cs[0][v][lane] + Cs[1][v][lane]) + Cs[2][v][lane]) + Cs[3][v][lane];
-            if (i < r && j < r) {
-                if (P.E) sum = fmaf(P.beta, P.E[(int64_t)i * r + j], sum);
-                P.C[(int64_t)i * r + j] = sum;
-                if (P.Ct) P.Ct[(int64_t)j * r + i] = sum;
-            }
+    for (int q = 0; q < 4; ++q) {                                   // a wave adds up a quarter of the tile
+        const int v = 4 * wave + q, i = row0 + 8 * wave + 4 * (lane >> 5) + q;
+        float sum = ((Cs[0][v][lane] + Cs[1][v][lane]) + Cs[2][v][lane]) + Cs[3][v][lane];
+        if (i < r && j < r) {
+            if (P.E) sum = fmaf(P.beta, P.E[(int64_t)i * r + j], sum);
+            P.C[(int64_t)i * r + j] = sum;
+            if (P.Ct) P.Ct[(int64_t)j * r + i] = sum;
         }
     }
 }
