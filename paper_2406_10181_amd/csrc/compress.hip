@@ -164,18 +164,11 @@ __global__ __launch_bounds__(256) void k_raw(const typename D::elem* __restrict_
 }
 
 // ----------------------------------------------------------------------------------------------
-// Row blocks per workgroup of kernel A: several on big grids (grouped calls)
-static int gq_blocks_per_wg(const CompressGroup& g) {
-    int64_t rows = 0;
-    for (int p = 0; p < g.count; ++p) rows += g.m[p];
-    return rows >= 16384 ? 2 : 1;
-}
-
-static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, float unplanned, lsp_dtype dtype, hipStream_t st) {
+static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, float unplanned, lsp_dtype dtype, hipStream_t st) {
     switch (dtype) {
-        case LSP_F32:  return launch_gq_f32(g, r, d, blocks_per_wg, unplanned, st);
-        case LSP_F16:  return launch_gq_f16(g, r, d, blocks_per_wg, unplanned, st);
-        default:       return launch_gq_bf16(g, r, d, blocks_per_wg, unplanned, st);
+        case LSP_F32:  return launch_gq_f32(g, r, d, unplanned, st);
+        case LSP_F16:  return launch_gq_f16(g, r, d, unplanned, st);
+        default:       return launch_gq_bf16(g, r, d, unplanned, st);
     }
 }
 
@@ -200,7 +193,7 @@ hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_d
         const int32_t items = (int32_t)plan_max_items(g.m[p], r, d);
         g.first_pt[p + 1] = g.first_pt[p] + (striped ? ((items + 3) / 4) * 8 : items * nstripes);
     }
-    hipError_t e = launch_gq(g, r, d, gq_blocks_per_wg(g), unplanned, dtype, st);
+    hipError_t e = launch_gq(g, r, d, unplanned, dtype, st);
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)g.first_pt[g.count];
     if (striped) {

@@ -85,10 +85,10 @@ __device__ __forceinline__ void swap_owner(uint8_t* area, float (&acc)[R], uint3
     __syncthreads();
 }
 
-// Launchers of kernel A (they fill in first_gq): one workgroup = a block of rows of G at a time, 512 threads, one lane
+// Launchers of kernel A (they fill in first_gq and blocks_gq): one workgroup = a block of rows of G at a time, 512 threads, one lane
 // per (virtual) column of T.
-hipError_t launch_gq_bf16(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, float unplanned, hipStream_t st);
-hipError_t launch_gq_f16(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, float unplanned, hipStream_t st);
-hipError_t launch_gq_f32(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, float unplanned, hipStream_t st);
+hipError_t launch_gq_bf16(CompressGroup& g, int32_t r, int32_t d, float unplanned, hipStream_t st);
+hipError_t launch_gq_f16(CompressGroup& g, int32_t r, int32_t d, float unplanned, hipStream_t st);
+hipError_t launch_gq_f32(CompressGroup& g, int32_t r, int32_t d, float unplanned, hipStream_t st);
 
 }  // namespace lsp

@@ -2,6 +2,8 @@
 // instantiate it.  See compress.hip for the path as a whole.
 #pragma once
 
+#include <algorithm>
+
 #include "compress_common.h"
 
 namespace lsp {
@@ -391,7 +393,7 @@ __device__ __forceinline__ void gq_multi_slot(ChunkStager<D, WHOLE>& stg, uint8_
 }
 
 template <typename D, bool WHOLE>
-__global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGroup grp, int r, int d, int blocks_per_wg, float unplanned) {
+__global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGroup grp, int r, int d, float unplanned) {
     constexpr int R = kRowsGQ<D>;
     extern __shared__ __align__(16) uint8_t smem[];
     const CompressProblem pr = group_pick(grp, (int)blockIdx.x, false);
@@ -400,7 +402,7 @@ __global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGro
     float* __restrict__ T = pr.T;
     float* __restrict__ S = pr.S;
     const int m = pr.m, n = pr.n;
-    const int block = pr.block_gq, nblocks = pr.nblocks_gq;
+    const int block = pr.block_gq, nblocks = pr.nblocks_gq, blocks_per_wg = pr.blocks_gq;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -424,23 +426,55 @@ __global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGro
     else                     gq_multi_slot<D, kMaxSlots, WHOLE>(stg, smem, G, plan, H, T, i0, nblk, m, n, r, tid, lane, wave);
 }
 
+// How many row blocks a workgroup takes.  A workgroup's next block is fetched while it walks the last chunk of the one
+// before, so only its first block waits for memory and for the plan.  If equal shares of chunks (row blocks times chunks of
+// a row) can be had from no more workgroups than the chip holds at a time, one share each: every CU is busy from start to
+// end, and nothing is set up twice (kernels A and B: 2048 x 8192 and 8192 x 2048 together 45.0 -> 40.7 us, 11008 x 4096
+// 66.0 -> 61.7).  Shares of more than eight chunks are halved and so on, because the two workgroups of a CU do not
+// advance at the same speed.  Otherwise the workgroups are taken up as CUs fall free, and small ones even out the end:
+// two blocks each on big grids, else one.
+template <int R> static void share_blocks(CompressGroup& g) {
+    constexpr int64_t kResident = 512;                                // two on each of 256 CUs
+    int64_t work = 0, rows = 0;
+    for (int p = 0; p < g.count; ++p) {
+        work += (int64_t)((g.m[p] + R - 1) / R) * ((g.n[p] + kChunk - 1) / kChunk);
+        rows += g.m[p];
+    }
+    auto fill = [&](auto&& blocks_of) {
+        int64_t longest = 0;
+        g.first_gq[0] = 0;
+        for (int p = 0; p < g.count; ++p) {
+            const int64_t chunks = (g.n[p] + kChunk - 1) / kChunk, blocks = (g.m[p] + R - 1) / R;
+            const int64_t each = blocks_of(chunks);
+            g.blocks_gq[p] = (int32_t)each;
+            g.first_gq[p + 1] = g.first_gq[p] + (int32_t)((blocks + each - 1) / each);
+            longest = std::max(longest, each * chunks);
+        }
+        return longest;
+    };
+    for (int64_t rounds = 1; rounds <= 4; ++rounds) {
+        const int64_t share = (work + rounds * kResident - 1) / (rounds * kResident);
+        if (share > 8) continue;
+        const int64_t longest = fill([&](int64_t chunks) { return (share + chunks - 1) / chunks; });
+        if (g.first_gq[g.count] <= rounds * kResident && longest * 8 <= share * 9) return;
+    }
+    fill([&](int64_t) { return (int64_t)(rows >= 16384 ? 2 : 1); });
+}
+
 template <typename D>
-static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, int blocks_per_wg, float unplanned, hipStream_t st) {
+static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, float unplanned, hipStream_t st) {
     constexpr size_t lds = (size_t)2 * kPlaneStride;                  // two chunk buffers
     bool whole = true;
-    g.first_gq[0] = 0;
-    for (int p = 0; p < g.count; ++p) {
-        g.first_gq[p + 1] = g.first_gq[p] + ((g.m[p] + kRowsGQ<D> - 1) / kRowsGQ<D> + blocks_per_wg - 1) / blocks_per_wg;
-        whole = whole && g.n[p] % 4 == 0;
-    }
+    share_blocks<kRowsGQ<D>>(g);
+    for (int p = 0; p < g.count; ++p) whole = whole && g.n[p] % 4 == 0;
     const dim3 grid((unsigned)g.first_gq[g.count]);
     hipError_t e;
     if (whole) {
         if ((e = allow_dynamic_lds<k_compress_gq<D, true>>(lds)) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_compress_gq<D, true>), grid, dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, blocks_per_wg, unplanned);
+        hipLaunchKernelGGL((k_compress_gq<D, true>), grid, dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, unplanned);
     } else {
         if ((e = allow_dynamic_lds<k_compress_gq<D, false>>(lds)) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_compress_gq<D, false>), grid, dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, blocks_per_wg, unplanned);
+        hipLaunchKernelGGL((k_compress_gq<D, false>), grid, dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, unplanned);
     }
     return hipGetLastError();
 }

@@ -130,6 +130,7 @@ struct CompressGroup {
     float*         S[kMaxGroup];
     int32_t        m[kMaxGroup], n[kMaxGroup];
     int32_t        first_gq[kMaxGroup + 1];      // workgroups of the T = G Q kernel
+    int32_t        blocks_gq[kMaxGroup];         // row blocks of each of them
     int32_t        first_pt[kMaxGroup + 1];      // workgroups of the S = P^T T kernel
     int32_t        count;
 };
@@ -152,15 +153,15 @@ struct ApplyGroup {
 // every address derived from it into a per-lane (vector) value, so that the small uniform loads of
 // the kernels (plan header, segment table) would go through the vector memory path and wait for
 // all the data loads in flight.  Everything returned is wave-uniform and lives in scalar registers.
-struct CompressProblem { const void* G; const uint8_t* plan; float* T; float* S; int32_t m, n, block_gq, nblocks_gq, block_pt; };
+struct CompressProblem { const void* G; const uint8_t* plan; float* T; float* S; int32_t m, n, block_gq, nblocks_gq, blocks_gq, block_pt; };
 __device__ __forceinline__ CompressProblem group_pick(const CompressGroup& g, int block, bool kernel_b) {
-    CompressProblem o{g.G[0], g.plan[0], g.T[0], g.S[0], g.m[0], g.n[0], block, g.first_gq[1], block};
+    CompressProblem o{g.G[0], g.plan[0], g.T[0], g.S[0], g.m[0], g.n[0], block, g.first_gq[1], g.blocks_gq[0], block};
 #pragma unroll
     for (int p = 1; p < kMaxGroup; ++p) {
         const bool hit = p < g.count && block >= (kernel_b ? g.first_pt[p] : g.first_gq[p]);
         if (hit) {
             o.G = g.G[p]; o.plan = g.plan[p]; o.T = g.T[p]; o.S = g.S[p]; o.m = g.m[p]; o.n = g.n[p];
-            o.block_gq = block - g.first_gq[p]; o.nblocks_gq = g.first_gq[p + 1] - g.first_gq[p];
+            o.blocks_gq = g.blocks_gq[p]; o.block_gq = block - g.first_gq[p]; o.nblocks_gq = g.first_gq[p + 1] - g.first_gq[p];
             o.block_pt = block - g.first_pt[p];
         }
     }
