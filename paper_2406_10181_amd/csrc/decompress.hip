@@ -168,6 +168,29 @@ template <typename V> __device__ __forceinline__ void row_store(RowBuffer b, uin
     else { u32x2 t; __builtin_memcpy(&t, &v, 8); __builtin_amdgcn_raw_buffer_store_b64(t, b, (int)offset, 0, kNonTemporal); }
 }
 
+// The passes of a workgroup: `count` of the row block's, from `first` on, in an order rotated by the workgroup's position
+// inside its XCD (workgroups are dealt to the 8 XCDs round-robin): all workgroups read the same Q arrays, and without
+// the rotation they would all ask the same few L2 channels for the same lines at once.  (The divisions, which the first
+// loads wait for, are left out where there is nothing to divide.)
+struct Passes {
+    int all, first, count, rot;
+    __device__ __forceinline__ Passes(int n, int step, int block, int part, int parts) {
+        all = n / step + (n % step != 0);                           // step is a power of two
+        first = 0; count = all; rot = 0;
+        if (parts > 1) {
+            const int each = all / parts, more = all - each * parts;
+            first = part * each + min(part, more);
+            count = each + (part < more ? 1 : 0);
+        }
+        if (all > 1) rot = (int)((unsigned)(block / 8) % (unsigned)all);
+    }
+    __device__ __forceinline__ int at(int p) const {
+        int q = first + p + rot;
+        if (q >= all) q -= all;
+        return q;
+    }
+};
+
 // Fast kernel: DD = compile-time d, two columns per thread, n even.  PS = bytes between the 4-row planes of U in
 // LDS, a compile-time constant >= 16 r so that the plane offset folds into the immediate offset of the LDS read and a
 // gather costs no address arithmetic.
@@ -185,7 +208,7 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
     // a row block is shared by `parts` workgroups, each with its share of the passes (all build the tile of U)
     const int prob = group_find(grp.first, grp.count, (int)blockIdx.x);
     const int unit = (int)blockIdx.x - grp.first[prob], parts = grp.parts[prob];
-    const int block = unit / parts, part = unit - block * parts;
+    const int block = parts > 1 ? unit / parts : unit, part = unit - block * parts;
     const float* __restrict__ S = grp.S[prob];
     const int32_t* __restrict__ P_idx = grp.P_idx[prob];
     const float* __restrict__ P_val = grp.P_val[prob];
@@ -196,18 +219,10 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
     int2* pent = reinterpret_cast<int2*>(smem + RG * PS);
     const f32x4* Us4 = reinterpret_cast<const f32x4*>(smem);
 
-    // Passes are visited in an order rotated by the workgroup's position inside its XCD
-    // (workgroups are dealt to the 8 XCDs round-robin): all workgroups read the same Q arrays, and
-    // without the rotation they would all ask the same few L2 channels for the same lines at once.
     constexpr int step = NT * CPT;
-    const int npass_all = (int)(((int64_t)n + step - 1) / step);
-    const int p_lo = (int)((int64_t)npass_all * part / parts), npass = (int)((int64_t)npass_all * (part + 1) / parts) - p_lo;
-    const int rot = (block / 8) % npass_all;
-    auto pass_col = [&](int p) -> int {                             // the pass's first column
-        int q = p_lo + p + rot;
-        if (q >= npass_all) q -= npass_all;
-        return q * step;
-    };
+    const Passes passes(n, step, block, part, parts);
+    const int npass = passes.count;
+    auto pass_col = [&](int p) -> int { return passes.at(p) * step; };   // the pass's first column
     const int lane_col = (int)threadIdx.x * CPT;                    // of the pass; past n: nothing there for this thread
     const RowBlock<D> rows{static_cast<char*>(grp.W[prob]) + i0 * n * D::size, (int64_t)n * D::size, m - i0 < R ? (int)(m - i0) : R, n};
 
@@ -299,21 +314,16 @@ __global__ __launch_bounds__(NT, (NORMS ? 3 : 4)) void k_decompress_any(const Ap
     constexpr int R = 4 * RG;
     const int prob = group_find(grp.first, grp.count, (int)blockIdx.x);
     const int unit = (int)blockIdx.x - grp.first[prob], parts = grp.parts[prob];
-    const int block = unit / parts, part = unit - block * parts;
+    const int block = parts > 1 ? unit / parts : unit, part = unit - block * parts;
     const int32_t* __restrict__ Q_idx = grp.Q_idx[prob];
     const float* __restrict__ Q_val = grp.Q_val[prob];
     const int m = grp.m[prob], n = grp.n[prob];
     const int64_t i0 = (int64_t)block * R;
     const f32x4* Us4 = reinterpret_cast<const f32x4*>(smem);
     constexpr int step = NT * 2;
-    const int npass_all = (int)(((int64_t)n + step - 1) / step);
-    const int p_lo = (int)((int64_t)npass_all * part / parts), npass = (int)((int64_t)npass_all * (part + 1) / parts) - p_lo;
-    const int rot = (block / 8) % npass_all;
-    auto pass_col = [&](int p) -> int {                             // the pass's first column
-        int q = p_lo + p + rot;
-        if (q >= npass_all) q -= npass_all;
-        return q * step;
-    };
+    const Passes passes(n, step, block, part, parts);
+    const int npass = passes.count;
+    auto pass_col = [&](int p) -> int { return passes.at(p) * step; };   // the pass's first column
     const int lane_col = PAIR ? (int)threadIdx.x * 2 : ((int)threadIdx.x >> 6) * 128 + ((int)threadIdx.x & 63);
     constexpr int kApart = PAIR ? 1 : kWave;                        // from the first column to the second
     const RowBlock<D> rows{static_cast<char*>(grp.W[prob]) + i0 * n * D::size, (int64_t)n * D::size, m - i0 < R ? (int)(m - i0) : R, n};
@@ -480,9 +490,12 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
     return hipErrorInvalidValue;                                    // (32-row workgroups are for the fast kernel)
 }
 
+static bool few_blocks(int64_t blocks, int32_t r) { return blocks <= 128 || (r <= 512 && blocks < 256); }
+
 // Rows per workgroup: 16 (four planes of U in LDS) and 512 threads, except
 //   * r > 1024: 8 rows, or the tile of U would take the whole LDS;
-//   * fewer than 256 blocks of 16 rows: 8 rows, so that all CUs get work (2048 x 2048, r = 256: 10.4 -> 8.5 us);
+//   * at most 128 blocks of 16 rows (with r <= 512, where building U costs less, fewer than 256): 8 rows, so that more
+//     CUs get work (2048 x 2048, r = 256: 10.4 -> 8.5 us);
 //   * 1024 or more blocks, 16-bit storage, 256 < r <= 512: 32 rows, so that the rows of Q are streamed from L2 half as
 //     often (the seven matrices of a 6.7B-style layer: 234 -> 226 us); fp32 patches of 32 rows would not fit the registers;
 //   * 512 or more blocks and r <= 512: 256 threads with at most eight passes each; four such workgroups share a CU and
@@ -497,7 +510,7 @@ static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_
         fast = fast && fast_shape(g.n[p], d);
     }
     if (r > 1024) return launch_d<D, 2, 32768, 512>(g, r, d, kAll, st);
-    if (fast && blocks < 256)
+    if (fast && few_blocks(blocks, r))
         return r <= 256 ? launch_d<D, 2, 4096, 512>(g, r, d, kAll, st) : r <= 512 ? launch_d<D, 2, 8192, 512>(g, r, d, kAll, st)
                                                                                  : launch_d<D, 2, 16384, 512>(g, r, d, kAll, st);
     if constexpr (D::size == 2)
@@ -508,15 +521,18 @@ static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_
                                                                              : launch_d<D, 4, 16384, 512>(g, r, d, kAll, st);
 }
 
-// Estimation bias: one problem, 16 (or 8) rows per workgroup, two passes deep.
-int64_t bias_blocks(int64_t m, int32_t r) { return r <= 1024 ? (m + 15) / 16 : (m + 7) / 8; }
+// Estimation bias: one problem, 16 rows per workgroup, or 8 as in the apply step.
+static bool bias_small(int64_t m, int32_t r) { return r > 1024 || few_blocks((m + 15) / 16, r); }
+int64_t bias_blocks(int64_t m, int32_t r) { return bias_small(m, r) ? (m + 7) / 8 : (m + 15) / 16; }
 
 template <typename D>
 static hipError_t launch_bias_shape(ApplyGroup& g, int32_t r, int32_t d, float2* partial, hipStream_t st) {
+    if (bias_small(g.m[0], r))
+        return r <= 256 ? launch_d<D, 2, 4096, 512, true>(g, r, d, 1 << 30, st, partial) : r <= 512 ? launch_d<D, 2, 8192, 512, true>(g, r, d, 1 << 30, st, partial)
+             : r <= 1024 ? launch_d<D, 2, 16384, 512, true>(g, r, d, 1 << 30, st, partial) : launch_d<D, 2, 32768, 512, true>(g, r, d, 1 << 30, st, partial);
     if (r <= 256)  return launch_d<D, 4, 4096, 512, true>(g, r, d, 1 << 30, st, partial);
     if (r <= 512)  return launch_d<D, 4, 8192, 512, true>(g, r, d, 1 << 30, st, partial);
-    if (r <= 1024) return launch_d<D, 4, 16384, 512, true>(g, r, d, 1 << 30, st, partial);
-    return launch_d<D, 2, 32768, 512, true>(g, r, d, 1 << 30, st, partial);
+    return launch_d<D, 4, 16384, 512, true>(g, r, d, 1 << 30, st, partial);
 }
 
 hipError_t launch_bias(ApplyGroup& g, int32_t r, int32_t d, lsp_dtype dtype, float* partial, float* out, hipStream_t st) {
