@@ -33,14 +33,16 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // dispatcher deals workgroups round-robin), and the grid is laid out so that one XCD takes every a for a column tile
 // before its next tile, so a tile of G (m rows of 256 elements, 2 MB at m = 4096) stays in that XCD's L2 for its
 // d visits.  With a workgroup a piece (four waves, a quarter of the entries each, 8 bytes a lane) it took 34 us there, now 24.
-// A row's last piece starts at n - VEC when n is no multiple of VEC; n < VEC: one column a lane (VEC = 1).
+// A row's last piece starts at n - VEC when n is no multiple of VEC, up to VEC - 1 columns before its tile if the tile has
+// fewer than VEC columns: the wave's sums have room for them in front.  n < VEC: one column a lane (VEC = 1).
 constexpr int kThreadsY = 256, kWavesY = kThreadsY / kWave, kXcds = 8, kTileY = 256;
 template <typename D, int VEC>
 __global__ __launch_bounds__(kThreadsY) void k_gather_rows(const typename D::elem* __restrict__ G, const uint8_t* __restrict__ plan,
                                                           float* __restrict__ Y, int m, int n, int r, int d, int item_groups, int tiles) {
     constexpr int LG = VEC == 1 ? kWave : kTileY / VEC < kWave ? kTileY / VEC : kWave;   // lanes of an entry
     constexpr int NG = kWave / LG;                                  // entries a wave takes at a time
-    __shared__ __align__(16) float part[kWavesY][kTileY];
+    constexpr int kLead = VEC;                                      // room in front of a tile (VEC - 1, rounded up to whole pieces)
+    __shared__ __align__(16) float part[kWavesY][kLead + kTileY];
     typedef typename D::elem Piece __attribute__((ext_vector_type(VEC)));
     typedef Piece Loose __attribute__((aligned(D::size)));
     PlanHeaderPtr H = as_const<PlanHeader>(plan);
@@ -91,7 +93,7 @@ __global__ __launch_bounds__(kThreadsY) void k_gather_rows(const typename D::ele
     }
     if (grp == 0 && live) {
 #pragma unroll
-        for (int q = 0; q < VEC; ++q) part[wave][at - tile0 + q] = acc[q];   // (the same sums where pieces overlap)
+        for (int q = 0; q < VEC; ++q) part[wave][kLead + at - tile0 + q] = acc[q];   // (the same sums where pieces overlap)
     }
     __syncthreads();
     const int c = threadIdx.x, j = tile0 + c;
@@ -106,15 +108,15 @@ __global__ __launch_bounds__(kThreadsY) void k_gather_rows(const typename D::ele
         plain = plain && a[w] == a[0] + w && p[3] == 0;
     }
     if (plain && ((a[0] | r) & 3) == 0) {
-        *reinterpret_cast<f32x4*>(out + a[0]) = f32x4{part[0][c], part[1][c], part[2][c], part[3][c]};
+        *reinterpret_cast<f32x4*>(out + a[0]) = f32x4{part[0][kLead + c], part[1][kLead + c], part[2][kLead + c], part[3][kLead + c]};
         return;
     }
 #pragma unroll
     for (int w = 0; w < kWavesY; ++w) {
         if (a[w] < 0) continue;
         const auto* p = as_const<int32_t>(plan + H->off_p_item) + 4 * (item0 + w);
-        if (p[3]) atomicAdd(out + a[w], part[w][c]);
-        else out[a[w]] = part[w][c];
+        if (p[3]) atomicAdd(out + a[w], part[w][kLead + c]);
+        else out[a[w]] = part[w][kLead + c];
     }
 }
 

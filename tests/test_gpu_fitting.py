@@ -58,6 +58,14 @@ def test_bias_gradient_against_oracle(m, n, r, d, dtype, dist):
     _check_gradient(syn.make_problem("grad", m, n, r, d, dtype, seed=5100 + m + n, g_std=1.0, index_dist=dist))
 
 
+@pytest.mark.parametrize("n,dtype", [(257, "bf16"), (259, "f16"), (261, "bf16"), (263, "f16"), (257, "f32"), (259, "f32"), (1283, "bf16")])
+@pytest.mark.parametrize("r", [24, 22])         # rows of Y written 16 bytes at a time, and one by one
+def test_bias_gradient_where_the_last_tile_is_shorter_than_a_piece(n, dtype, r):
+    # the row gather of Y = G^T P goes by tiles of 256 columns in pieces of 16 bytes: here the last piece of a row starts in
+    # the tile before its own
+    _check_gradient(syn.make_problem("grad_tail", 70, n, r, 3, dtype, seed=5600 + n + r, g_std=1.0))
+
+
 def test_bias_gradient_config4_shape():
     # one 4096 x 4096 bf16 matrix of the 6.7B-style stack, r = 512, d = 8, with gradients of training scale
     _check_gradient(syn.config4_matrix(31, 3))
