@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(const GramBatch batch, in
     const int total = (int)(P.rows * d);                            // < 2^31, checked by the host
     typedef int i32x4 __attribute__((ext_vector_type(4)));
     typedef i32x4 loose __attribute__((aligned(4)));
-    const int quads = (total + 3) >> 2;
+    const int whole = total >> 2, rest = total & 3, quads = whole + (rest ? 1 : 0);   // (total + 3 could pass 2^31 - 1)
     static_assert(4 * kGramInFlight == 32, "one bit for every entry of a batch");
     for (int t0 = 0; t0 < quads; t0 += kGramThreads * kGramInFlight) {       // uniform trip count: the exchanges need whole waves
         i32x4 a[kGramInFlight];
@@ -58,11 +58,11 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(const GramBatch batch, in
         for (int u = 0; u < kGramInFlight; ++u) {
             const int t = t0 + u * kGramThreads + (int)threadIdx.x;
             a[u] = i32x4{-1, -1, -1, -1};
-            if (4 * t + 3 < total) a[u] = *reinterpret_cast<const loose*>(P.L_idx + 4 * (int64_t)t);
-            else
+            if (t < whole) a[u] = *reinterpret_cast<const loose*>(P.L_idx + 4 * (int64_t)t);
+            else if (t == whole)
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
-                    if (4 * t + q < total) a[u][q] = P.L_idx[4 * t + q];
+                    if (q < rest) a[u][q] = P.L_idx[4 * (int64_t)t + q];
         }
         uint32_t hits = 0;
 #pragma unroll

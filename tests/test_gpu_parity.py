@@ -488,6 +488,45 @@ def test_reproject_state_concentrated_columns():
     assert eM <= 2e-5 and eV <= 2e-5, (eM, eV)
 
 
+@pytest.mark.parametrize("m,d", [
+    (134217727, 16),      # 2^31 - 16 entries, whole groups of four
+    (2147483647, 1),      # 2^31 - 1, the most there can be: three left over
+])
+def test_reproject_state_with_the_most_entries_a_projector_can_have(m, d):
+    """Only the first and the last few rows of P and P_prev have values, so the oracle gets those rows."""
+    import torch
+    import paper_2406_10181_amd as L
+    n, r, ends = 40, 16, 5
+    print(f"[case] reproject m={m} n={n} r={r} d={d}", flush=True)
+    rng = np.random.default_rng(6100 + d)
+    few = [syn.ell_projector(rows, r, d, rng, "uniform") for rows in (2 * ends, 2 * ends, n, n)]     # P, P_prev (ends only), Q, Q_prev
+    M = rng.standard_normal((r, r)).astype(np.float32)
+    V = (rng.standard_normal((r, r)) ** 2).astype(np.float32)
+    Mo, Vo = oracle.reproject_state(*few[0], *few[1], *few[2], *few[3], r, M, V)
+
+    def tall(idx, val):
+        ti, tv = torch.empty(m * d, dtype=torch.int32, device="cuda"), torch.zeros(m * d, dtype=torch.float32, device="cuda")
+        for k in range(0, m * d, 1 << 28):                     # columns 0 .. 15 in turn, values 0
+            ti[k:k + (1 << 28)] = torch.arange(min(1 << 28, m * d - k), dtype=torch.int32, device="cuda") % r
+        for rows, part in ((slice(0, ends * d), slice(0, ends)), (slice((m - ends) * d, m * d), slice(ends, 2 * ends))):
+            ti[rows] = torch.from_numpy(np.ascontiguousarray(idx[part]).reshape(-1)).cuda()
+            tv[rows] = torch.from_numpy(np.ascontiguousarray(val[part]).reshape(-1)).cuda()
+        return ti, tv
+
+    dev = [*tall(*few[0]), *tall(*few[1])] + [torch.from_numpy(x).cuda() for pair in few[2:] for x in pair]
+    Md, Vd = torch.from_numpy(M).cuda(), torch.from_numpy(V).cuda()
+    nb = L.lsp_reproject_state_workspace_bytes(r)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    L.lsp_reproject_state(*dev, m, n, r, d, Md, Vd, ws, nb, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    del dev
+    torch.cuda.empty_cache()                                   # 34 GB
+    eM = np.abs(Md.cpu().numpy() - Mo).max() / np.abs(Mo).max()
+    eV = np.abs(Vd.cpu().numpy() - Vo).max() / np.abs(Vo).max()
+    print(f"[ok]   reproject: rel err M {eM:.2e} V {eV:.2e}", flush=True)
+    assert eM <= 2e-5 and eV <= 2e-5, (eM, eV)
+
+
 def test_reproject_state_exact_on_relabelled_projectors():
     """New projectors that relabel the old columns: P^T P_prev and Q_prev^T Q are permutation matrices and
     the moments are permuted, bit for bit."""
