@@ -15,43 +15,41 @@ PyObject* g_data_ptr;      // interned names
 PyObject* g_cuda_stream;
 PyObject* g_ctypes;
 PyObject* g_data;
+PyObject* g_argument_error;   // ctypes.ArgumentError
 
 decltype(&lsp_compress_planned) g_compress_planned;
 decltype(&lsp_decompress_apply) g_decompress_apply;
 decltype(&lsp_compress_planned_grouped) g_compress_grouped;
 decltype(&lsp_decompress_apply_grouped) g_apply_grouped;
 
-// Converts one argument after another; the first failure leaves a Python exception and ok = false.
+// Converts one argument after another, to what ctypes makes of it; the first failure leaves a Python exception and ok = false.
 struct Args {
-    PyObject* const* a;
+    PyObject* const* first;
+    PyObject* const* a = first;
     bool ok = true;
 
-    long long integer() {
+    explicit Args(PyObject* const* args) : first(args) {}
+    void refuse() {                                    // the argument before `a`
+        PyErr_Format(g_argument_error, "argument %zd: TypeError: wrong type", (Py_ssize_t)(a - first));
+        ok = false;
+    }
+    // the low bits of an integer, however large: a value that makes no sense is the library's to refuse
+    uint64_t integer() {
         PyObject* x = *a++;
         if (!ok) return 0;
-        long long v;
-        if (PyLong_Check(x)) {
-            v = PyLong_AsLongLong(x);
-        } else {
-            PyObject* i = PyNumber_Index(x);
-            if (!i) { ok = false; return 0; }
-            v = PyLong_AsLongLong(i);
-            Py_DECREF(i);
-        }
-        if (v == -1 && PyErr_Occurred()) ok = false;
+        const uint64_t v = PyLong_AsUnsignedLongLongMask(x);
+        if (v == (uint64_t)-1 && PyErr_Occurred()) { PyErr_Clear(); refuse(); }
         return v;
     }
-    int32_t int32() {
-        const long long v = integer();
-        if (ok && (v < INT32_MIN || v > INT32_MAX)) { PyErr_SetString(PyExc_OverflowError, "argument out of range"); ok = false; }
-        return (int32_t)v;
-    }
-    // address held by a Python int, and gives the reference up
+    int64_t int64() { return (int64_t)integer(); }
+    int32_t int32() { return (int32_t)integer(); }
+    // address held by a Python int (None: NULL), and gives the reference up
     void* taken(PyObject* i) {
         if (!i) { ok = false; return nullptr; }
-        void* p = PyLong_AsVoidPtr(i);
+        void* p = nullptr;
+        if (PyLong_Check(i)) p = reinterpret_cast<void*>((uintptr_t)PyLong_AsUnsignedLongLongMask(i));
+        else if (i != Py_None) refuse();
         Py_DECREF(i);
-        if (!p && PyErr_Occurred()) ok = false;
         return p;
     }
     // a tensor, a numpy array, an address or None
@@ -97,14 +95,14 @@ template <typename F> PyObject* without_gil(F&& call) {
 // (G, plan, m, n, r, d, S, dtype, workspace, workspace_bytes, stream)
 PyObject* compress_planned(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     if (!count_is(nargs, 11)) return nullptr;
-    Args a{args};
+    Args a(args);
     const void* G = a.pointer(); const void* plan = a.pointer();
-    const int64_t m = a.integer(), n = a.integer();
+    const int64_t m = a.int64(), n = a.int64();
     const int32_t r = a.int32(), d = a.int32();
     float* S = static_cast<float*>(a.pointer());
     const int32_t dtype = a.int32();
     void* ws = a.pointer();
-    const size_t bytes = (size_t)a.integer();
+    const size_t bytes = a.integer();
     void* st = a.stream();
     if (!a.ok) return nullptr;
     return without_gil([&] { return g_compress_planned(G, plan, m, n, r, d, S, static_cast<lsp_dtype>(dtype), ws, bytes, st); });
@@ -113,14 +111,14 @@ PyObject* compress_planned(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
 // (W, S, P_idx, P_val, Q_idx, Q_val, m, n, r, d, dtype, stream)
 PyObject* decompress_apply(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     if (!count_is(nargs, 12)) return nullptr;
-    Args a{args};
+    Args a(args);
     void* W = a.pointer();
     const float* S = static_cast<const float*>(a.pointer());
     const int32_t* P_idx = static_cast<const int32_t*>(a.pointer());
     const float* P_val = static_cast<const float*>(a.pointer());
     const int32_t* Q_idx = static_cast<const int32_t*>(a.pointer());
     const float* Q_val = static_cast<const float*>(a.pointer());
-    const int64_t m = a.integer(), n = a.integer();
+    const int64_t m = a.int64(), n = a.int64();
     const int32_t r = a.int32(), d = a.int32(), dtype = a.int32();
     void* st = a.stream();
     if (!a.ok) return nullptr;
@@ -130,7 +128,7 @@ PyObject* decompress_apply(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
 // (address of the items, count, r, d, dtype, stream)
 template <typename Item, typename Entry> PyObject* grouped(Entry entry, PyObject* const* args, Py_ssize_t nargs) {
     if (!count_is(nargs, 6)) return nullptr;
-    Args a{args};
+    Args a(args);
     const Item* items = static_cast<const Item*>(a.pointer());
     const int32_t count = a.int32(), r = a.int32(), d = a.int32(), dtype = a.int32();
     void* st = a.stream();
@@ -143,7 +141,7 @@ PyObject* decompress_apply_grouped(PyObject*, PyObject* const* args, Py_ssize_t 
 // (addresses of the four functions, in the order of the methods)
 PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     if (!count_is(nargs, 4)) return nullptr;
-    Args a{args};
+    Args a(args);
     void* p[4];
     for (void*& x : p) x = a.pointer();
     if (!a.ok) return nullptr;
@@ -171,5 +169,10 @@ PyMODINIT_FUNC PyInit__call(void) {
     g_cuda_stream = PyUnicode_InternFromString("cuda_stream");
     g_ctypes = PyUnicode_InternFromString("ctypes");
     g_data = PyUnicode_InternFromString("data");
+    PyObject* ctypes = PyImport_ImportModule("ctypes");
+    if (!ctypes) return nullptr;
+    g_argument_error = PyObject_GetAttrString(ctypes, "ArgumentError");
+    Py_DECREF(ctypes);
+    if (!g_argument_error) return nullptr;
     return PyModule_Create(&g_module);
 }

@@ -99,6 +99,37 @@ def test_argument_errors_without_gpu():
         L.lsp_compress(None, fake, fake, fake, fake, 64, 64, 16, 2, fake, 0, fake, big)
 
 
+def _outcome(call, *a):
+    try:
+        return call(*a)
+    except Exception as e:
+        return type(e)
+
+
+@pytest.mark.parametrize("value", [1 << 31, (1 << 32) + 16, -(1 << 31) - 1, 1 << 63, (1 << 64) - 1, 1 << 70, -1, True, np.int64(64), np.int32(2),
+                                   4.0, None, "16"])
+def test_the_call_module_converts_arguments_as_ctypes_does(value):
+    """Any integer reaches the library (its low bits, as ctypes passes them) and is the library's to refuse; other types
+    raise what ctypes raises.  A NULL plan or S keeps every call from going further than the checks."""
+    fake = 0x1000
+    ctypes_call = {name: getattr(L.lib(), name) for name in ("lsp_compress_planned", "lsp_decompress_apply", "lsp_compress_planned_grouped")}
+    planned = [fake, None, 64, 64, 16, 2, fake, 0, fake, 1 << 20, None]
+    apply = [fake, None, fake, fake, fake, fake, 64, 64, 16, 2, 0, None]
+    grouped = [fake, 0, 16, 2, 0, None]                       # (no items: LSP_ERR_SHAPE)
+    module = L.binding._bound()
+    for name, call, args in (("lsp_compress_planned", module.compress_planned, planned), ("lsp_decompress_apply", module.decompress_apply, apply),
+                             ("lsp_compress_planned_grouped", module.compress_planned_grouped, grouped)):
+        for k, kind in enumerate(ctypes_call[name].argtypes):
+            if kind is ctypes.c_void_p and not (isinstance(value, int) or value is None):
+                continue                                      # (addresses: tensors and arrays go through _ptr on the other path)
+            if name == "lsp_compress_planned_grouped" and k < 2:
+                continue
+            changed = args[:k] + [value] + args[k + 1:]
+            if name != "lsp_compress_planned_grouped" and changed[1] is not None:
+                changed[0] = None                             # NULL in another place
+            assert _outcome(call, *changed) == _outcome(ctypes_call[name], *changed), (name, k, value)
+
+
 def test_grouped_argument_errors_without_gpu():
     fake, big = 0x1000, 1 << 20
     one = L.compress_items([(fake, fake, fake, fake, big, 64, 64)])
