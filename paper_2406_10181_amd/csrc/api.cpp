@@ -242,7 +242,7 @@ int lsp_decompress_apply(void* W, const float* S, const int32_t* P_idx, const fl
 
 size_t lsp_estimation_bias_workspace_bytes(int64_t m, int64_t n, int32_t r, int32_t d) {
     if (check_shape(m, n, r, d) != LSP_OK) return 0;
-    return lsp::align_up((size_t)lsp::bias_blocks(m, r) * 2 * sizeof(float), 256);
+    return lsp::align_up((size_t)lsp::bias_blocks(m, n, r, d) * 2 * sizeof(float), 256);
 }
 
 int lsp_estimation_bias(const void* G, const float* S, const int32_t* P_idx, const float* P_val,

@@ -490,27 +490,45 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
     return hipErrorInvalidValue;                                    // (32-row workgroups are for the fast kernel)
 }
 
-static bool few_blocks(int64_t blocks, int32_t r) { return blocks <= 128 || (r <= 512 && blocks < 256); }
+// Workgroups of 8 rows instead of 16, given the number of blocks of 16 rows (n: the widest matrix).  With 8 rows there are twice as
+// many workgroups, but each reads all of Q.  (us, 8 rows | 16 rows, apply and bias pass, W and G from HBM.)
+//   * At most 128 blocks, half of the CUs idle otherwise: 8 rows.
+//       1000 x 2048, r = 128, d = 2, bf16     6.8 |  7.5     9.1 |  9.6        2048 x 2048, r = 512, d = 8, bf16    10.9 | 14.0    13.1 | 16.3
+//       2048 x 16384, r = 256, d = 4, bf16   30.9 | 45.8    27.8 | 40.2        2048 x 8192, r = 256, d = 16, fp32   55.7 | 69.6    53.9 | 70.9
+//       2048 x 2047, r = 250, d = 5, bf16    10.1 | 12.6    11.4 | 14.8        2040 x 8191, r = 900, d = 7, bf16    35.4 | 50.0    32.8 | 44.9
+//     (Rows of 16 KB are the exception: 2048 x 4096, r = 512, d = 8, fp32     28.6 | 26.0    22.5 | 23.0.)
+//   * 129 to 255 blocks: some CUs have two workgroups of 8 rows and others one.  16 rows, the more so the larger d is:
+//       2064 x 4096, r = 512, d = 8, bf16    22.5 | 20.4    22.6 | 21.7        3072 x 16384, r = 512, d = 8, bf16   73.5 | 67.4    60.6 | 57.6
+//       4080 x 4096, r = 512, d = 8, fp32    45.8 | 33.0    33.4 | 24.1        4080 x 8192, r = 256, d = 16, bf16   90.8 | 67.5    94.9 | 69.5
+//       4073 x 8191, r = 250, d = 3, bf16        (general kernel)  32.0 | 29.3     d = 7    49.1 | 39.8
+//     but 8 rows where the passes are short, or the bias pass has few gathers and no stores to cover its loads with:
+//       4080 x 2048, r = 128, d = 2, fp32    16.1 | 23.8    12.8 | 17.7        4080 x 3072, r = 256, d = 4, fp32    23.0 | 27.0    16.0 | 17.5
+//       2064 x 8192, r = 128, d = 2, bf16       (bias)      15.7 | 19.0        3072 x 16384, r = 256, d = 4, bf16   (bias)         38.1 | 40.7
+static bool eight_rows(int64_t blocks, int64_t n, int32_t r, int32_t d, int elem_size, bool fast, bool norms) {
+    if (r > 1024 || blocks <= 128) return true;                     // (r > 1024: 16 rows of U would take the whole LDS)
+    if (blocks > 255 || r > 512 || !fast) return false;
+    return elem_size == 4 ? n < 4096 && d <= 8 : norms && n >= 4096 && d <= 4;
+}
 
-// Rows per workgroup: 16 (four planes of U in LDS) and 512 threads, except
-//   * r > 1024: 8 rows, or the tile of U would take the whole LDS;
-//   * at most 128 blocks of 16 rows (with r <= 512, where building U costs less, fewer than 256): 8 rows, so that more
-//     CUs get work (2048 x 2048, r = 256: 10.4 -> 8.5 us);
+// Rows per workgroup: 16 (four planes of U in LDS) or 8 (above), and 512 threads, except
 //   * 1024 or more blocks, 16-bit storage, 256 < r <= 512: 32 rows, so that the rows of Q are streamed from L2 half as
-//     often (the seven matrices of a 6.7B-style layer: 234 -> 226 us); fp32 patches of 32 rows would not fit the registers;
+//     often (the seven matrices of a 6.7B-style layer, one call: 220 us, with 16 rows of 256 threads 235, of 512 threads 226;
+//     16384 x 4096, r = 512, d = 8: 69, 74, 76); fp32 patches of 32 rows would not fit the registers;
 //   * 512 or more blocks and r <= 512: 256 threads with at most eight passes each; four such workgroups share a CU and
-//     cover each other's set-up (11008 x 4096: 64 -> 57 us).
+//     cover each other's set-up.  It is even with 512 threads in 16 bits at d = 8 (11008 x 4096, r = 512: 55.6 | 56.0; 8192 x 4096:
+//     40.3 | 39.6), ahead in fp32 (81.0 | 83.4; 16384 x 4096: 112 | 116) and behind at d = 4 (16384 x 4096, r = 256: 59.1 | 55.8).
 template <typename D>
 static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_t st) {
     constexpr int kAll = 1 << 30;                                   // no row block is shared
-    int64_t blocks = 0;
+    int64_t blocks = 0, widest = 0;
     bool fast = true;
     for (int p = 0; p < g.count; ++p) {
         blocks += (g.m[p] + 15) / 16;
+        widest = g.n[p] > widest ? g.n[p] : widest;
         fast = fast && fast_shape(g.n[p], d);
     }
     if (r > 1024) return launch_d<D, 2, 32768, 512>(g, r, d, kAll, st);
-    if (fast && few_blocks(blocks, r))
+    if (eight_rows(blocks, widest, r, d, D::size, fast, false))
         return r <= 256 ? launch_d<D, 2, 4096, 512>(g, r, d, kAll, st) : r <= 512 ? launch_d<D, 2, 8192, 512>(g, r, d, kAll, st)
                                                                                  : launch_d<D, 2, 16384, 512>(g, r, d, kAll, st);
     if constexpr (D::size == 2)
@@ -521,31 +539,37 @@ static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_
                                                                              : launch_d<D, 4, 16384, 512>(g, r, d, kAll, st);
 }
 
-// Estimation bias: one problem, 16 rows per workgroup, or 8 as in the apply step.
-static bool bias_small(int64_t m, int32_t r) { return r > 1024 || few_blocks((m + 15) / 16, r); }
-int64_t bias_blocks(int64_t m, int32_t r) { return bias_small(m, r) ? (m + 7) / 8 : (m + 15) / 16; }
+// Estimation bias: one problem, one pair of sums per workgroup.
+static bool bias_eight_rows(int64_t m, int64_t n, int32_t r, int32_t d, int elem_size) {
+    return eight_rows((m + 15) / 16, n, r, d, elem_size, fast_shape((int32_t)n, d), true);
+}
+int64_t bias_blocks(int64_t m, int64_t n, int32_t r, int32_t d) {
+    return bias_eight_rows(m, n, r, d, 2) || bias_eight_rows(m, n, r, d, 4) ? (m + 7) / 8 : (m + 15) / 16;
+}
 
 template <typename D>
-static hipError_t launch_bias_shape(ApplyGroup& g, int32_t r, int32_t d, float2* partial, hipStream_t st) {
-    if (bias_small(g.m[0], r))
-        return r <= 256 ? launch_d<D, 2, 4096, 512, true>(g, r, d, 1 << 30, st, partial) : r <= 512 ? launch_d<D, 2, 8192, 512, true>(g, r, d, 1 << 30, st, partial)
-             : r <= 1024 ? launch_d<D, 2, 16384, 512, true>(g, r, d, 1 << 30, st, partial) : launch_d<D, 2, 32768, 512, true>(g, r, d, 1 << 30, st, partial);
-    if (r <= 256)  return launch_d<D, 4, 4096, 512, true>(g, r, d, 1 << 30, st, partial);
-    if (r <= 512)  return launch_d<D, 4, 8192, 512, true>(g, r, d, 1 << 30, st, partial);
-    return launch_d<D, 4, 16384, 512, true>(g, r, d, 1 << 30, st, partial);
+static hipError_t launch_bias_shape(ApplyGroup& g, int32_t r, int32_t d, float2* partial, float* out, hipStream_t st) {
+    constexpr int kAll = 1 << 30;
+    const int64_t m = g.m[0];
+    const bool eight = bias_eight_rows(m, g.n[0], r, d, D::size);
+    hipError_t e;
+    if (r > 1024)   e = launch_d<D, 2, 32768, 512, true>(g, r, d, kAll, st, partial);
+    else if (eight) e = r <= 256 ? launch_d<D, 2, 4096, 512, true>(g, r, d, kAll, st, partial) : r <= 512 ? launch_d<D, 2, 8192, 512, true>(g, r, d, kAll, st, partial)
+                                                                                                     : launch_d<D, 2, 16384, 512, true>(g, r, d, kAll, st, partial);
+    else            e = r <= 256 ? launch_d<D, 4, 4096, 512, true>(g, r, d, kAll, st, partial) : r <= 512 ? launch_d<D, 4, 8192, 512, true>(g, r, d, kAll, st, partial)
+                                                                                                     : launch_d<D, 4, 16384, 512, true>(g, r, d, kAll, st, partial);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_bias_finish, dim3(1), dim3(256), 0, st, partial, (int)(eight ? (m + 7) / 8 : (m + 15) / 16), out);
+    return hipGetLastError();
 }
 
 hipError_t launch_bias(ApplyGroup& g, int32_t r, int32_t d, lsp_dtype dtype, float* partial, float* out, hipStream_t st) {
     float2* part = reinterpret_cast<float2*>(partial);
-    hipError_t e;
     switch (dtype) {
-        case LSP_F32:  e = launch_bias_shape<F32>(g, r, d, part, st); break;
-        case LSP_F16:  e = launch_bias_shape<F16>(g, r, d, part, st); break;
-        default:       e = launch_bias_shape<BF16>(g, r, d, part, st); break;
+        case LSP_F32:  return launch_bias_shape<F32>(g, r, d, part, out, st);
+        case LSP_F16:  return launch_bias_shape<F16>(g, r, d, part, out, st);
+        default:       return launch_bias_shape<BF16>(g, r, d, part, out, st);
     }
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bias_finish, dim3(1), dim3(256), 0, st, part, (int)bias_blocks(g.m[0], r), out);
-    return hipGetLastError();
 }
 
 hipError_t launch_decompress(ApplyGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st) {

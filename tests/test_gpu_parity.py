@@ -165,6 +165,25 @@ def test_apply_and_bias_at_the_edges_of_the_passes(m, n, r, d, dtype):
     _bias_check(pb)
 
 
+@pytest.mark.parametrize("m,n,r,d,dtype", [
+    (2048, 515, 300, 3, "bf16"),     # general kernel, 128 blocks of 16 rows: 8 rows a workgroup
+    (2049, 515, 300, 3, "bf16"),     # one more: 16 rows
+    (41, 261, 900, 5, "f16"),        # the same two with r > 512
+    (2051, 262, 900, 5, "f16"),
+    (2049, 1026, 130, 4, "f32"),     # fast kernel, 129 blocks: 8 rows in fp32 with short rows
+    (2049, 4100, 130, 4, "f32"),     # 16 rows with long ones
+    (4080, 4100, 60, 2, "bf16"),     # 255 blocks: 16 rows in the apply step, 8 in the bias pass
+    (4081, 4100, 60, 2, "bf16"),     # 256 blocks: 16 rows in both
+])
+def test_apply_and_bias_on_both_sides_of_the_rules_for_the_rows_of_a_workgroup(m, n, r, d, dtype):
+    import gpu_util as gu
+    pb = syn.make_problem(f"rows_{m}x{n}_r{r}_d{d}", m, n, r, d, dtype, seed=390 + m + n, g_std=0.5)
+    print(f"[case] {pb.name} {dtype}", flush=True)
+    Wp, Wr = oracle.decompress_apply(pb.W, dtype, pb.S_in, pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val, threads=THREADS)
+    gu.check_decompress(_dp(pb).decompress(pb.S_in), pb.W, Wp, Wr, dtype, pb.name)
+    _bias_check(pb)
+
+
 def test_zero_and_identity_cases():
     pb = syn.make_problem("zero", 64, 2048, 128, 4, "bf16", seed=42)
     dp = _dp(pb)
