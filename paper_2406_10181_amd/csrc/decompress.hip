@@ -20,13 +20,8 @@ namespace lsp {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-template <typename D, int CPT> struct Vec;     // CPT consecutive elements of W
-template <> struct Vec<F32, 4>  { f32x4 v; };
-template <> struct Vec<F32, 2>  { float x, y; };
-template <> struct Vec<F16, 4>  { uint32_t x, y; };
-template <> struct Vec<BF16, 4> { uint32_t x, y; };
-template <> struct Vec<F16, 2>  { uint32_t x; };
-template <> struct Vec<BF16, 2> { uint32_t x; };
+template <typename D> struct Pair { uint32_t x; };                 // two neighbouring elements of W
+template <> struct Pair<F32> { float x, y; };
 
 template <typename D> __device__ __forceinline__ void pair_widen(uint32_t p, float& lo, float& hi);
 template <> __device__ __forceinline__ void pair_widen<F16>(uint32_t p, float& lo, float& hi) {
@@ -39,25 +34,13 @@ template <typename D> __device__ __forceinline__ uint32_t pair_narrow(float lo, 
     return (uint32_t)narrow<D>(lo) | ((uint32_t)narrow<D>(hi) << 16);
 }
 
-template <typename D, int CPT> __device__ __forceinline__ void vec_widen(const Vec<D, CPT>& x, float* out) {
-    if constexpr (D::size == 4) {
-        if constexpr (CPT == 4) { out[0] = x.v.x; out[1] = x.v.y; out[2] = x.v.z; out[3] = x.v.w; }
-        else { out[0] = x.x; out[1] = x.y; }
-    } else {
-        pair_widen<D>(x.x, out[0], out[1]);
-        if constexpr (CPT == 4) pair_widen<D>(x.y, out[2], out[3]);
-    }
+template <typename D> __device__ __forceinline__ void widen_pair(const Pair<D>& p, float* out) {
+    if constexpr (D::size == 4) { out[0] = p.x; out[1] = p.y; }
+    else pair_widen<D>(p.x, out[0], out[1]);
 }
-template <typename D, int CPT> __device__ __forceinline__ Vec<D, CPT> vec_narrow(const float* in) {
-    Vec<D, CPT> o;
-    if constexpr (D::size == 4) {
-        if constexpr (CPT == 4) { o.v.x = in[0]; o.v.y = in[1]; o.v.z = in[2]; o.v.w = in[3]; }
-        else { o.x = in[0]; o.y = in[1]; }
-    } else {
-        o.x = pair_narrow<D>(in[0], in[1]);
-        if constexpr (CPT == 4) o.y = pair_narrow<D>(in[2], in[3]);
-    }
-    return o;
+template <typename D> __device__ __forceinline__ Pair<D> narrow_pair(const float* in) {
+    if constexpr (D::size == 4) return Pair<D>{in[0], in[1]};
+    else return Pair<D>{pair_narrow<D>(in[0], in[1])};
 }
 
 // Sums x and y over the workgroup (NT threads) and lets thread 0 store them; `red` is LDS nobody
@@ -204,7 +187,7 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
     constexpr int R = 4 * RG;
     constexpr int NE = CPT * DD;                                    // entries owned by a thread in one pass
     static_assert(NE % 4 == 0, "entries are loaded 4 at a time");
-    typedef Vec<D, CPT> Patch;
+    typedef Pair<D> Patch;
     // a row block is shared by `parts` workgroups, each with its share of the passes (all build the tile of U)
     const int prob = group_find(grp.first, grp.count, (int)blockIdx.x);
     const int unit = (int)blockIdx.x - grp.first[prob], parts = grp.parts[prob];
@@ -267,7 +250,7 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
                 float x[CPT];
-                vec_widen<D, CPT>(w[g * 4 + t], x);
+                widen_pair<D>(w[g * 4 + t], x);
                 if constexpr (NORMS) {
                     const bool on = col < n - lane_col && g * 4 + t < rows.rows;
 #pragma unroll
@@ -279,7 +262,7 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
                 } else {
 #pragma unroll
                     for (int c = 0; c < CPT; ++c) x[c] -= acc[t][c];
-                    row_store(rows.from(g * 4 + t, col), (uint32_t)lane_col * D::size, vec_narrow<D, CPT>(x));
+                    row_store(rows.from(g * 4 + t, col), (uint32_t)lane_col * D::size, narrow_pair<D>(x));
                 }
                 if constexpr (decltype(more)::value) load_w(g * 4 + t, next);
             }
@@ -328,7 +311,7 @@ __global__ __launch_bounds__(NT, (NORMS ? 3 : 4)) void k_decompress_any(const Ap
     constexpr int kApart = PAIR ? 1 : kWave;                        // from the first column to the second
     const RowBlock<D> rows{static_cast<char*>(grp.W[prob]) + i0 * n * D::size, (int64_t)n * D::size, m - i0 < R ? (int)(m - i0) : R, n};
 
-    typedef typename std::conditional<PAIR, Vec<D, 2>, typename D::elem>::type Piece;
+    typedef typename std::conditional<PAIR, Pair<D>, typename D::elem>::type Piece;
     constexpr int NP = PAIR ? 1 : 2;
     Piece w[R][NP];
     i32x4 qi[2][2];                                                 // [buffer][column]
@@ -395,7 +378,7 @@ __global__ __launch_bounds__(NT, (NORMS ? 3 : 4)) void k_decompress_any(const Ap
 #pragma unroll
         for (int t = 0; t < R; ++t) {
             float x[2];
-            if constexpr (PAIR) vec_widen<D, 2>(w[t][0], x);
+            if constexpr (PAIR) widen_pair<D>(w[t][0], x);
             else { x[0] = widen<D>(w[t][0]); x[1] = widen<D>(w[t][1]); }
             if constexpr (NORMS) {
 #pragma unroll
@@ -408,7 +391,7 @@ __global__ __launch_bounds__(NT, (NORMS ? 3 : 4)) void k_decompress_any(const Ap
             } else {
                 x[0] -= acc[t][0]; x[1] -= acc[t][1];
                 if constexpr (PAIR) {
-                    row_store(rows.from(t, col), (uint32_t)lane_col * D::size, vec_narrow<D, 2>(x));
+                    row_store(rows.from(t, col), (uint32_t)lane_col * D::size, narrow_pair<D>(x));
                 } else {
                     row_store(rows.from(t, col), (uint32_t)lane_col * D::size, narrow<D>(x[0]));
                     row_store(rows.from(t, col), (uint32_t)(lane_col + kApart) * D::size, narrow<D>(x[1]));
@@ -473,9 +456,8 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
     if (fast && d == 2) LSP_LAUNCH_FAST(2);
     if (fast && d == 4) LSP_LAUNCH_FAST(4);
     if (fast && d == 8) LSP_LAUNCH_FAST(8);
-    if (fast && d == 16) LSP_LAUNCH_FAST(16);
-#undef LSP_LAUNCH_FAST
-    if constexpr (RG <= 4) {
+    if constexpr (RG <= 4 && NT == 512) {                           // the others are for the fast kernel at d <= 8
+        if (fast && d == 16) LSP_LAUNCH_FAST(16);
 #define LSP_LAUNCH_ANY(PAIRV)                                                                                  \
     do {                                                                                                       \
         constexpr auto kern = k_decompress_any<D, RG, PS, NT, PAIRV, NORMS>;                                   \
@@ -487,7 +469,8 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
         LSP_LAUNCH_ANY(false);
 #undef LSP_LAUNCH_ANY
     }
-    return hipErrorInvalidValue;                                    // (32-row workgroups are for the fast kernel)
+#undef LSP_LAUNCH_FAST
+    return hipErrorInvalidValue;
 }
 
 // Workgroups of 8 rows instead of 16, given the number of blocks of 16 rows (n: the widest matrix).  With 8 rows there are twice as
