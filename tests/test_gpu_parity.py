@@ -295,11 +295,30 @@ def test_grouped_calls_mixed_shapes():
     _grouped_case(pbs)
 
 
-def test_grouped_calls_fall_back_when_kernel_variants_differ():
-    # n % 8 != 0 in one problem (element-wise loads, generic decompress): the call serves them one by one
-    pbs = [syn.make_problem("grpmix_a", 64, 1030, 64, 3, "f16", seed=911),
-           syn.make_problem("grpmix_b", 40, 2048, 64, 3, "f16", seed=912)]
-    _grouped_case(pbs)
+@pytest.mark.parametrize("n,d,dtype", [
+    (1030, 3, "f16"),        # n % 4 != 0: one launch of the kernel for unaligned pieces serves both in compress
+    (1031, 8, "bf16"),       # odd n: the general kernel serves both in the apply step, where the other one alone would not need it
+    (1031, 2, "f32"),
+])
+def test_grouped_calls_take_the_kernel_that_every_matrix_can_use(n, d, dtype):
+    _grouped_case([syn.make_problem("grpmix_a", 64, n, 64, d, dtype, seed=911),
+                   syn.make_problem("grpmix_b", 40, 2048, 64, d, dtype, seed=912)])
+
+
+@pytest.mark.parametrize("m,n,r,d,dtype,dist", [
+    (4077, 2604, 96, 4, "f32", "zipf"),        # fp32, columns shared between lanes: their sums meet in the LDS of a chunk
+    (4077, 2603, 512, 2, "f32", "uniform"),    # rows of G at any address
+    (4077, 2603, 700, 4, "f32", "zipf"),       # the same with several columns a lane
+    (8155, 2603, 96, 4, "bf16", "zipf"),
+    (8155, 2603, 700, 4, "f16", "zipf"),
+])
+def test_compress_with_two_row_blocks_a_workgroup_in_a_single_call(m, n, r, d, dtype, dist):
+    # two chunks a row and just under 1024 row blocks: shares of two blocks for 512 workgroups, the last block ragged
+    import gpu_util as gu
+    pb = syn.make_problem(f"share_{m}x{n}_r{r}_d{d}", m, n, r, d, dtype, seed=960 + r + n, g_std=0.5, index_dist=dist)
+    print(f"[case] {pb.name} {dtype} {dist}", flush=True)
+    S_o = oracle.compress(pb.G, dtype, pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val, r, threads=THREADS)
+    gu.check_compress(_dp(pb).compress_planned(), S_o, pb.name, 2e-4)
 
 
 def test_big_grid_with_ragged_last_row_block():

@@ -96,3 +96,23 @@ def test_device_plan_reports_skew_and_bad_indices():
     bad[5, 1] = r
     assert L.lsp_plan_build(dev[0], dev[1], bad, dev[3], m, n, r, d, plan, nb, torch.cuda.current_stream(), check=False) == -6
     assert int(plan[:4].view(torch.int32).item()) == 0
+
+
+@pytest.mark.parametrize("m,r,dtype", [(1, 2048, "bf16"), (16, 2046, "f32"), (17, 2048, "f16"), (75, 2047, "bf16")])
+def test_raw_entry_on_columns_too_skewed_for_a_plan(m, r, dtype):
+    """The scatter form by blocks of 16 rows: one row, a whole block, one row more, five blocks."""
+    import gpu_util as gu
+    import oracle
+    import paper_2406_10181_amd as L
+    n, d = 2500, 4
+    rng = np.random.default_rng(9000 + m)
+    P_idx, P_val = syn.ell_projector(m, r, d, rng)
+    Q_idx, Q_val = syn.ell_projector(n, r, d, rng)
+    Q_idx[:, 0] = np.arange(n) % 2                                  # two columns take a quarter of the entries
+    nb = L.lsp_plan_bytes(m, n, r, d)
+    G = syn.gaussian_matrix(m, n, 1.0, dtype, rng)
+    pb = syn.Problem("skew", m, n, r, d, dtype, G, G.copy(), P_idx, P_val, Q_idx, Q_val, np.zeros((r, r), np.float32))
+    print(f"[case] raw entry, skewed m={m} r={r} {dtype}", flush=True)
+    assert L.lsp_plan_build_host(P_idx, P_val, Q_idx, Q_val, m, n, r, d, np.zeros(nb, dtype=np.uint8), nb, check=False) == -8
+    S_o = oracle.compress(G, dtype, P_idx, P_val, Q_idx, Q_val, r)
+    gu.check_compress(gu.DeviceProblem(pb).compress_raw(), S_o, "raw entry on unplannable projectors", 2e-4)
