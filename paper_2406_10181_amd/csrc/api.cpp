@@ -58,11 +58,10 @@ size_t lsp_compress_planned_workspace_bytes(int64_t m, int64_t n, int32_t r, int
 
 size_t lsp_workspace_bytes(int64_t m, int64_t n, int32_t r, int32_t d, lsp_dtype dtype) {
     if (check_shape(m, n, r, d) != LSP_OK || check_dtype(dtype) != LSP_OK) return 0;
-    size_t need = t_bytes(m, r);                                                    // both compress entries
-    need = std::max(need, lsp_estimation_bias_workspace_bytes(m, n, r, d));
-    need = std::max(need, lsp_reproject_state_workspace_bytes(r));
-    need = std::max(need, lsp_bias_gradient_workspace_bytes(m, n, r, d));
-    return need;
+    return std::max({lsp_compress_workspace_bytes(m, n, r, d),                      // T and a plan, and scratch to build it: more than
+                     lsp_compress_dense_workspace_bytes(m, n, r),                   // lsp_compress_planned or a plan build need
+                     lsp_estimation_bias_workspace_bytes(m, n, r, d), lsp_reproject_state_workspace_bytes(r),
+                     lsp_bias_gradient_workspace_bytes(m, n, r, d)});
 }
 
 size_t lsp_plan_bytes(int64_t m, int64_t n, int32_t r, int32_t d) {

@@ -99,6 +99,15 @@ def test_argument_errors_without_gpu():
         L.lsp_compress(None, fake, fake, fake, fake, 64, 64, 16, 2, fake, 0, fake, big)
 
 
+@pytest.mark.parametrize("m,n,r,d", [(4096, 4096, 512, 8), (256, 256, 16, 2), (1, 1, 1, 1), (128, 16384, 512, 8), (300, 20000, 64, 64), (16384, 64, 2048, 1)])
+def test_the_one_workspace_size_serves_every_call(m, n, r, d):
+    one = L.lsp_workspace_bytes(m, n, r, d, 2)
+    needs = {q: getattr(L, f"lsp_{q}_workspace_bytes")(m, n, r, d)
+             for q in ("compress", "compress_planned", "plan_build", "estimation_bias", "bias_gradient")}
+    needs.update(reproject_state=L.lsp_reproject_state_workspace_bytes(r), compress_dense=L.lsp_compress_dense_workspace_bytes(m, n, r))
+    assert one == max(needs.values()), needs
+
+
 def _outcome(call, *a):
     try:
         return call(*a)
