@@ -360,7 +360,7 @@ def main():
                     "decompress_GB/s": round(dbytes / (ms_gdeco * 1e-3) / 1e9, 1)},
         # dominant by GPU time: the two kernels of one grouped compress call (seven matrices), timed
         # together (one API call) on one stream
-        "roofline": {"kernel": "k_compress_gq16<bf16> + k_compress_pt8 (one lsp_compress_planned_grouped call, 7 matrices)",
+        "roofline": {"kernel": "k_compress_gq<bf16> + k_compress_pt8 (one lsp_compress_planned_grouped call, 7 matrices)",
                      "bound": "hbm", "achieved": round(cbytes / (ms_gcomp1 * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(cbytes / (ms_gcomp1 * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                      "traffic": traffic_gc, "traffic_source": "profiles/traffic_compress_cfg4.json (rocprofv3 --pmc runs, not live)",
@@ -391,7 +391,7 @@ def main():
                             "TFLOP/s": round(8 * r ** 3 / (ms_rep * 1e-3) / 1e12, 2), "peak_fp32_TFLOP/s": 157.3},
         # one fitting iteration on a 4096 x 4096 matrix: values-only plan refresh + gradient of the bias loss (G is
         # streamed twice: 2 x 33.6 MB algorithmic)
-        "fitting_gradient": {"kernel": "k_plan_refresh + compress kernels + k_gram + k_gemm_rr4 x2 (five products) + k_gather_rows + k_grad_left/right "
+        "fitting_gradient": {"kernel": "k_plan_refresh + compress kernels + k_gram + k_gemm_rr4 x2 (five products) + k_gather_rows + k_grad "
                                        "(lsp_plan_refresh_values + lsp_bias_gradient, 4096 x 4096, r=512, d=8)",
                              "us_per_iteration": round(ms_fit * 1e3, 1), "plan_refresh_us": round(ms_refresh * 1e3, 1),
                              "GB/s_on_two_reads_of_G": round(2 * 4096 * 4096 * sz / (ms_fit * 1e-3) / 1e9, 1)},

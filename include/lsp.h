@@ -30,9 +30,8 @@
  * Errors.  Every call returns LSP_OK (0) or a negative lsp_status.  All argument checks are
  * made before the first HIP call: on LSP_ERR_NULL / SHAPE / DTYPE / WORKSPACE / ALIGN nothing has
  * been enqueued and no output has been touched.  LSP_ERR_LAUNCH means the HIP runtime refused a
- * launch (or, in the set-up calls, a copy); a call that consists of several kernels, or a grouped
- * call that serves its problems one by one, may then have enqueued part of its work already, and
- * its outputs are undefined.
+ * launch (or, in the set-up calls, a copy); a call that consists of several kernels may then have
+ * enqueued part of its work already, and its outputs are undefined.
  */
 #ifndef LSP_H
 #define LSP_H
@@ -111,7 +110,7 @@ size_t lsp_workspace_bytes(int64_t m, int64_t n, int32_t r, int32_t d, lsp_dtype
  * It lives entirely in a caller-owned device buffer of lsp_plan_bytes() bytes; there is no
  * host handle.  Building a plan only sorts and packs the projector entries (no arithmetic on
  * G, W or S) and happens on the device, where the projectors live: three small kernels (about
- * twenty microseconds; nothing is copied to the host).
+ * 25 microseconds; nothing is copied to the host).
  *
  * lsp_plan_build_async only enqueues that work on `stream`; it needs device scratch of
  * lsp_plan_build_workspace_bytes() and reports what only the data can show -- an index outside
@@ -207,8 +206,9 @@ int lsp_decompress_apply(void* W, const float* S,
  *   r, d, dtype  shared by all problems of the group; m and n are per problem
  * Problems of a group run concurrently: every item needs its own S and its own workspace
  * (LSP_ERR_WORKSPACE otherwise), and a W may appear only once (LSP_ERR_SHAPE).  Errors are
- * those of the single calls; on any error nothing is enqueued.  When the problems need different
- * kernel variants (e.g. some n divisible by 8 and some not) the call enqueues them one by one.
+ * those of the single calls; on any error nothing is enqueued.  The kernel variant is one that all
+ * problems can use: an n that is no multiple of 4 (compress) or odd (apply) takes the whole group to the
+ * variant for such rows.
  */
 typedef struct {
     const void* G;            /* device, m*n elements of `dtype` */

@@ -1,5 +1,5 @@
-// Pieces shared by the translation units of the compress path (kernel A in its 16-bit and its
-// fp32-staged variants, kernel B and the launchers).
+// Pieces shared by the translation units of the compress path (kernel A, instantiated once per storage
+// type, kernel B and the launchers).
 #pragma once
 
 #include <utility>
@@ -22,7 +22,6 @@ __device__ __forceinline__ void fill_s(float* __restrict__ S, float x, int r, in
     const int64_t total = (int64_t)r * r;
     for (int64_t k = (int64_t)block * nthreads + tid; k < total; k += (int64_t)nblocks * nthreads) S[k] = x;
 }
-
 
 constexpr int kBatchLoads = kSegBatch / 2;                    // 128-bit loads per batch of plan rows
 

@@ -163,7 +163,8 @@ __device__ __forceinline__ void gq_one_slot(ChunkStager<D, WHOLE>& stg, uint8_t*
     const uint32_t first = perm[0];
     uint32_t walked = first;                                          // virtual column whose list this thread walks
 
-    // ring of kPrefetch batches of plan rows in fixed register slots (see gq_one_slot)
+    // ring of kPrefetch batches of plan rows in fixed register slots: a slot is consumed, then refilled with the batch four
+    // further on (shifting the ring's registers would make every batch wait for its newest load)
     u32x4 ring[kPrefetch][kBatchLoads];
     auto ring_restart = [&]() {
         rp = rp0;
@@ -267,9 +268,8 @@ __device__ __forceinline__ void gq_one_slot(ChunkStager<D, WHOLE>& stg, uint8_t*
     }
 }
 
-// Several columns per lane (r > 512, or columns used so unevenly that they were split), 16-bit
-// storage: the same staging, plan ring and block walk as gq_one_slot, the lane's columns taken
-// slot by slot inside each chunk.  A lane keeps its columns for all chunks (no dealing by length:
+// Several columns per lane (r > 512, or columns used so unevenly that they were split): the same staging,
+// plan ring and block walk as gq_one_slot, the lane's columns taken slot by slot inside each chunk.  A lane keeps its columns for all chunks (no dealing by length:
 // the sums of NS columns per lane would not fit through LDS cheaply).
 template <typename D, int NS, bool WHOLE>
 __device__ __forceinline__ void gq_multi_slot(ChunkStager<D, WHOLE>& stg, uint8_t* smem, const typename D::elem* __restrict__ G,
@@ -359,7 +359,7 @@ __device__ __forceinline__ void gq_multi_slot(ChunkStager<D, WHOLE>& stg, uint8_
                 if (rot > 2) step(ring[2], acc[s]);
             }
         }
-        if (last_chunk) {                                             // the block's 16 sums per column are complete
+        if (last_chunk) {                                             // the block's sums are complete
             const int64_t ib = i0 + (int64_t)blk * R;
             if (more) { ring_restart(); rot = 0; }                    // the stream starts over; in flight during the stores
             if (shared) {

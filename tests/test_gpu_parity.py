@@ -117,7 +117,7 @@ def test_selection_projectors_block_sums_bit_exact():
     (16, 1024, 16, 2, "bf16"),       # exactly one tile, one chunk
     (15, 1025, 12, 4, "bf16"),       # one row short, one column over a chunk
     (130, 4100, 256, 4, "f16"),
-    (40, 2048, 2048, 8, "bf16"),     # largest subspace (two-plane kernels)
+    (40, 2048, 2048, 8, "bf16"),     # largest subspace (8-row workgroups)
     (33, 520, 1030, 2, "bf16"),      # r not a multiple of 4 above 1024
     (24, 64, 1000, 16, "f32"),
 ])
@@ -330,8 +330,7 @@ def test_big_grid_with_ragged_last_row_block():
 
 
 def test_big_grid_with_an_odd_number_of_passes():
-    # 32-row apply workgroups of 512 threads take 1024 columns per pass: three passes here, and the last row
-    # blocks of the launch are shared by two workgroups with two passes and one
+    # 32-row apply workgroups of 512 threads take 1024 columns per pass: three passes here
     pb = syn.make_problem("big_odd", 16 * 1030 + 9, 3072, 512, 8, "bf16", seed=925)
     _grouped_case([pb])
     _full_check(pb, raw=False)
@@ -422,9 +421,9 @@ def _bias_check(pb, tol=2e-4):
     (256, 256, 16, 2, "f32", "distinct"),        # config 1
     (512, 2048, 256, 4, "f16", "uniform"),
     (203, 3000, 512, 8, "bf16", "uniform"),      # ragged last row block, several passes over the columns
-    (100, 1030, 64, 3, "bf16", "uniform"),       # generic kernel (d = 3, n % 4 != 0)
+    (100, 1030, 64, 3, "bf16", "uniform"),       # general kernel (d = 3)
     (96, 1024, 1500, 2, "bf16", "uniform"),      # 8 rows per workgroup
-    (64, 2048, 256, 16, "f16", "zipf"),          # d = 16: one pass in registers
+    (64, 2048, 256, 16, "f16", "zipf"),          # d = 16
 ])
 def test_estimation_bias_against_oracle(m, n, r, d, dtype, dist):
     _bias_check(syn.make_problem("bias", m, n, r, d, dtype, seed=4000 + m + n, g_std=1.0, index_dist=dist))
