@@ -83,23 +83,28 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup 
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
     // The piece's entries are loaded once, 64 at a time (one per lane), and handed to the groups by
     // lane exchange, so that the loads of T do not each wait for a load of their entry and can
-    // all be in flight together.
+    // all be in flight together.  Places behind the last entry read zeros (with a row of T, even times zero, an infinity there
+    // would reach this row of S): always the same ones, the plan's bytes behind its header, because a row of T costs L2 traffic.
+    constexpr uint32_t kNoRow = 0xFFFFFFFFu;
+    const float* zeros = reinterpret_cast<const float*>(plan + sizeof(PlanHeader));
+    static_assert(sizeof(PlanHeader) + 16 <= kPlanHeaderBytes, "both builders clear what is behind the header");
     for (int base = 0; base < it.len; base += kWave) {
         const int e_mine = base + lane;
-        const uint2 mine = e_mine < it.len ? ent[e_mine] : make_uint2(0u, 0u);
+        const uint2 mine = e_mine < it.len ? ent[e_mine] : make_uint2(kNoRow, 0u);
         const int steps = (min(it.len - base, (int)kWave) + NG - 1) / NG;      // uniform over the wave
-        constexpr int kBlock = 16;                                              // loads of T in flight per lane
+        // loads of T in flight per lane: 64 registers, seven waves a SIMD (sixteen: 100 and four; seven matrices of a
+        // 6.7B-style layer, the step 428 instead of 418 us; 4096 x 4096, r = 2048, d = 8: 108.6 instead of 104.3)
+        constexpr int kBlock = 8;
+        static_assert(kWave / NG % kBlock == 0, "a block of steps ends with the wave's entries");
         for (int k0 = 0; k0 < steps; k0 += kBlock) {
             f32x4 x[kBlock];
             float v[kBlock];
 #pragma unroll
             for (int k = 0; k < kBlock; ++k) {
-                const int src = min((k0 + k) * NG + grp_e, (int)kWave - 1);     // lane holding entry base + (k0+k)*NG + grp
+                const int src = (k0 + k) * NG + grp_e;                          // lane holding entry base + (k0+k)*NG + grp
                 const uint32_t row = (uint32_t)__shfl((int)mine.x, src);
                 v[k] = __uint_as_float((uint32_t)__shfl((int)mine.y, src));
-                const bool on = k0 + k < steps && (k0 + k) * NG + grp_e < kWave;
-                if (!on) v[k] = 0.0f;
-                x[k] = *reinterpret_cast<const loose*>(Tcol + (int64_t)(on ? row : 0u) * r);
+                x[k] = *reinterpret_cast<const loose*>(row != kNoRow ? Tcol + (int64_t)row * r : zeros);
             }
 #pragma unroll
             for (int k = 0; k < kBlock; ++k) {

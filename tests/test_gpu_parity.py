@@ -383,6 +383,27 @@ def test_fp16_subnormals_are_not_flushed():
     gu.check_compress(dp.compress_raw(), S_o, "fp16 subnormal raw", tight=1e-6)
 
 
+@pytest.mark.parametrize("m,n,r,d,dtype", [(300, 520, 64, 2, "bf16"), (90, 300, 40, 1, "f32"), (200, 261, 33, 3, "f16")])
+def test_an_infinity_stays_in_the_rows_of_s_it_belongs_to(m, n, r, d, dtype):
+    """Row 0 of G overflowed: only the rows of S that row 0 of P names may notice (places of a wave without an entry of
+    their own must not bring other rows in, not even times zero)."""
+    pb = syn.make_problem("inf", m, n, r, d, dtype, seed=1000 + m, g_std=1.0)
+    G = pb.G.copy()
+    G[0, :] = 0x7F80 if dtype == "bf16" else np.inf
+    touched = np.unique(pb.P_idx[0])
+    assert touched.size < r
+    rest = pb.G.copy()
+    rest[0, :] = 0
+    S_o = oracle.compress(rest, dtype, pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val, r)
+    pb.G = G
+    dp = _dp(pb)
+    for S in (dp.compress_planned(), dp.compress_raw()):
+        others = np.setdiff1d(np.arange(r), touched)
+        assert np.isfinite(S[others]).all(), f"{(~np.isfinite(S[others])).any(axis=1).sum()} of {others.size} rows of S are not finite"
+        assert np.abs(S[others] - S_o[others]).max() <= 5e-5 * np.abs(S_o).max()
+        assert not np.isfinite(S[touched]).all()
+
+
 def test_validate_projector_and_plan_index_error():
     import torch
     import paper_2406_10181_amd as L
