@@ -15,10 +15,19 @@
 namespace lsp {
 
 // Longest list one lane may have to walk in one chunk: twice the mean list of a uniformly used
-// column (so uniformly drawn projectors are never split), at least 16.
+// column and 8, at least 16, so that uniformly drawn projectors are hardly ever split.
+// Hardly ever is not enough where every lane has a column and a split leaves no plan: r = 2048, d = 8 had a list of more than 24
+// in one chunk of 400, which was LSP_ERR_SKEW.  With fewer than 8 lanes to spare it is the mean, six times its root (the lists'
+// standard deviation) and 8, if that is more: one chunk in 10^7 or fewer.
 int plan_list_cap(int32_t r, int32_t d) {
     const int64_t mean = ((int64_t)kChunk * d + r - 1) / r;
-    return (int)std::max<int64_t>(16, 2 * mean + 8);
+    int64_t cap = std::max<int64_t>(16, 2 * mean + 8);
+    if (r > kMaxSlots * kThreadsGQ - 8) {
+        int64_t six_roots = 0;
+        while (six_roots * six_roots < 36 * mean) ++six_roots;
+        cap = std::max(cap, mean + six_roots + 8);
+    }
+    return (int)cap;
 }
 
 size_t plan_max_rows(int64_t n, int32_t r, int32_t d) {

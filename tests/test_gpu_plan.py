@@ -116,3 +116,23 @@ def test_raw_entry_on_columns_too_skewed_for_a_plan(m, r, dtype):
     assert L.lsp_plan_build_host(P_idx, P_val, Q_idx, Q_val, m, n, r, d, np.zeros(nb, dtype=np.uint8), nb, check=False) == -8
     S_o = oracle.compress(G, dtype, P_idx, P_val, Q_idx, Q_val, r)
     gu.check_compress(gu.DeviceProblem(pb).compress_raw(), S_o, "raw entry on unplannable projectors", 2e-4)
+
+
+def test_device_plan_and_compress_with_every_lane_taken_and_one_long_list():
+    import torch
+    import gpu_util as gu
+    import oracle
+    import paper_2406_10181_amd as L
+    m, n, r, d = 40, 4096, 2048, 8
+    pb = syn.make_problem("full", m, n, r, d, "bf16", seed=9100, g_std=1.0, index_dist="distinct")
+    rows = [j for j in range(2048, n) if 7 not in pb.Q_idx[j]][:30 - int((pb.Q_idx[2048:] == 7).sum())]
+    pb.Q_idx[rows, 0] = 7                                           # 30 entries in the second chunk, where 8 are usual
+    print("[case] device plan, every lane taken", flush=True)
+    nb = L.lsp_plan_bytes(m, n, r, d)
+    host = np.zeros(nb, dtype=np.uint8)
+    assert L.lsp_plan_build_host(pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val, m, n, r, d, host, nb, check=False) == 0
+    dp = gu.DeviceProblem(pb)
+    S = dp.compress_planned()
+    assert np.array_equal(dp.plan.cpu().numpy(), host)
+    S_o = oracle.compress(pb.G, "bf16", pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val, r)
+    gu.check_compress(S, S_o, "every lane taken")

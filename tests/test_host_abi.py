@@ -361,6 +361,19 @@ def test_plan_build_reports_unplannable_skew():
     assert "unevenly" in L.lsp_strerror(-8)
 
 
+@pytest.mark.parametrize("d,longest", [(8, 30), (4, 20), (16, 48)])
+def test_plan_with_every_lane_taken_carries_the_lists_that_uniform_columns_have(d, longest):
+    # r = 2048 leaves no lane for a second owner, and of 2048 lists of d entries on average one is now and then more than twice as
+    # long: such a projector has to be planned all the same
+    pb = syn.make_problem("full", 12, 2048, 2048, d, "f32", seed=88 + d, g_std=1.0, index_dist="distinct")
+    rows = [j for j in range(2048) if 7 not in pb.Q_idx[j]][:longest - int((pb.Q_idx == 7).sum())]
+    pb.Q_idx[rows, 0] = 7
+    assert int((pb.Q_idx == 7).sum()) == longest
+    T, S = _replay_plan(_build_host_plan(pb), pb)
+    G, Ph, Qh = pb.G.astype(np.float64), _dense(pb.P_idx, pb.P_val, pb.r), _dense(pb.Q_idx, pb.Q_val, pb.r)
+    np.testing.assert_allclose(S, Ph.T @ G @ Qh, rtol=0, atol=1e-10 * max(1.0, np.abs(S).max()))
+
+
 # ------------------------------------------------------------------ entry order inside projector rows
 def _gather_cost(idx):
     """Modelled cycles of the decompress kernels' 128-bit LDS gathers: lane l of a wave owns columns 2l, 2l+1 of a
