@@ -30,8 +30,8 @@
  * Errors.  Every call returns LSP_OK (0) or a negative lsp_status.  All argument checks are
  * made before the first HIP call: on LSP_ERR_NULL / SHAPE / DTYPE / WORKSPACE / ALIGN nothing has
  * been enqueued and no output has been touched.  LSP_ERR_LAUNCH means the HIP runtime refused a
- * launch (or, in the set-up calls, a copy); a call that consists of several kernels may then have
- * enqueued part of its work already, and its outputs are undefined.
+ * launch (or, in the set-up calls, a copy, or the host ran out of memory); a call that consists of
+ * several kernels may then have enqueued part of its work already, and its outputs are undefined.
  */
 #ifndef LSP_H
 #define LSP_H

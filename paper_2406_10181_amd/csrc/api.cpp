@@ -1,6 +1,7 @@
 // extern "C" entry points: argument checks, workspace carving, kernel launches.
 #include <algorithm>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "lsp_internal.h"
@@ -33,6 +34,15 @@ int check_shape(int64_t m, int64_t n, int32_t r, int32_t d) {
 }
 
 int check_dtype(lsp_dtype t) { return (t == LSP_F32 || t == LSP_F16 || t == LSP_BF16) ? LSP_OK : LSP_ERR_DTYPE; }
+
+// The calls that work on the host allocate host memory; running out of it is a status and no exception at the C boundary.
+template <typename F> int with_host_memory(F&& work) {
+    try {
+        return work();
+    } catch (const std::bad_alloc&) {
+        return fail_launch(hipErrorOutOfMemory);
+    }
+}
 
 size_t t_bytes(int64_t m, int32_t r) { return lsp::align_up((size_t)m * (size_t)r * sizeof(float), 256); }
 
@@ -146,7 +156,7 @@ int lsp_plan_build_host(const int32_t* P_idx, const float* P_val, const int32_t*
     if (!plan_host || plan_bytes < lsp::plan_bytes(m, n, r, d)) return LSP_ERR_WORKSPACE;
     for (int64_t k = 0; k < m * d; ++k) if (P_idx[k] < 0 || P_idx[k] >= r) return LSP_ERR_INDEX;
     for (int64_t k = 0; k < n * d; ++k) if (Q_idx[k] < 0 || Q_idx[k] >= r) return LSP_ERR_INDEX;
-    return lsp::build_plan_host(P_idx, P_val, Q_idx, Q_val, m, n, r, d, static_cast<uint8_t*>(plan_host));
+    return with_host_memory([&] { return lsp::build_plan_host(P_idx, P_val, Q_idx, Q_val, m, n, r, d, static_cast<uint8_t*>(plan_host)); });
 }
 
 size_t lsp_compress_dense_workspace_bytes(int64_t m, int64_t n, int32_t r) {
@@ -272,7 +282,7 @@ int lsp_projector_reorder_host(const int32_t* idx, const float* val, int64_t row
     if (!idx || !val || !idx_out || !val_out) return LSP_ERR_NULL;
     if (rows <= 0 || d <= 0 || r <= 0 || d > r || r > LSP_MAX_R || d > LSP_MAX_D || rows * d > INT32_MAX) return LSP_ERR_SHAPE;
     if (idx == idx_out || val == val_out) return LSP_ERR_SHAPE;
-    return lsp::reorder_rows_host(idx, val, rows, d, r, idx_out, val_out);
+    return with_host_memory([&] { return lsp::reorder_rows_host(idx, val, rows, d, r, idx_out, val_out); });
 }
 
 int lsp_projector_reorder(const int32_t* idx, const float* val, int64_t rows, int32_t d, int32_t r,
@@ -285,15 +295,17 @@ int lsp_projector_reorder(const int32_t* idx, const float* val, int64_t rows, in
     hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail_launch(e);
     const size_t count = (size_t)rows * (size_t)d;
-    std::vector<int32_t> hi(count), ho(count);
-    std::vector<float> hv(count), hw(count);
-    if ((e = hipMemcpy(hi.data(), idx, count * 4, hipMemcpyDeviceToHost)) != hipSuccess) return fail_launch(e);
-    if ((e = hipMemcpy(hv.data(), val, count * 4, hipMemcpyDeviceToHost)) != hipSuccess) return fail_launch(e);
-    const int rc = lsp::reorder_rows_host(hi.data(), hv.data(), rows, d, r, ho.data(), hw.data());
-    if (rc != LSP_OK) return rc;
-    if ((e = hipMemcpy(idx_out, ho.data(), count * 4, hipMemcpyHostToDevice)) != hipSuccess) return fail_launch(e);
-    if ((e = hipMemcpy(val_out, hw.data(), count * 4, hipMemcpyHostToDevice)) != hipSuccess) return fail_launch(e);
-    return LSP_OK;
+    return with_host_memory([&]() -> int {
+        std::vector<int32_t> hi(count), ho(count);
+        std::vector<float> hv(count), hw(count);
+        if ((e = hipMemcpy(hi.data(), idx, count * 4, hipMemcpyDeviceToHost)) != hipSuccess) return fail_launch(e);
+        if ((e = hipMemcpy(hv.data(), val, count * 4, hipMemcpyDeviceToHost)) != hipSuccess) return fail_launch(e);
+        const int rc = lsp::reorder_rows_host(hi.data(), hv.data(), rows, d, r, ho.data(), hw.data());
+        if (rc != LSP_OK) return rc;
+        if ((e = hipMemcpy(idx_out, ho.data(), count * 4, hipMemcpyHostToDevice)) != hipSuccess) return fail_launch(e);
+        if ((e = hipMemcpy(val_out, hw.data(), count * 4, hipMemcpyHostToDevice)) != hipSuccess) return fail_launch(e);
+        return LSP_OK;
+    });
 }
 
 size_t lsp_reproject_state_workspace_bytes(int32_t r) {

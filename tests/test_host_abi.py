@@ -346,6 +346,30 @@ def test_plan_build_host_rejects_bad_index_and_small_buffer():
                                  check=False) == -4
 
 
+def test_plan_build_host_out_of_memory_is_a_status():
+    # in a process of its own, with hardly any address space left once the arrays are there
+    import subprocess
+    import sys
+    code = """
+import resource, sys
+sys.path.insert(0, %r)
+import numpy as np
+import paper_2406_10181_amd as L
+m, n, r, d = 16, 1 << 20, 2048, 8
+idx = lambda rows: np.tile(np.arange(d, dtype=np.int32), (rows, 1))
+P, Q = (idx(m), np.ones((m, d), np.float32)), (idx(n), np.ones((n, d), np.float32))
+nb = L.lsp_plan_bytes(m, n, r, d)
+plan = np.zeros(nb, dtype=np.uint8)
+L.lib()
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + (24 << 20),) * 2)
+rc = L.lsp_plan_build_host(*P, *Q, m, n, r, d, plan, nb, check=False)
+print("status", rc, L.lib().lsp_last_hip_error())
+""" % ROOT
+    out = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+    assert out.stdout.strip() == "status -5 2", (out.returncode, out.stdout, out.stderr[-400:])     # hipErrorOutOfMemory
+
+
 def test_plan_build_reports_unplannable_skew():
     # r = 2048 uniformly used columns already fill all 4 x 512 lanes; one hot column on top of
     # that needs extra owners that do not exist -> LSP_ERR_SKEW (the caller falls back to lsp_compress)
