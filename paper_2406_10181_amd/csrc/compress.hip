@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup 
     PlanHeaderPtr H = as_const<PlanHeader>(plan);
     if (!plan_matches(H, pr.m, pr.n, r, d)) return;                   // kernel A has filled S with NaN
     const int stripe = block & 7;
-    const int item = (block >> 3) * (kThreadsB / kWave) + (int)(threadIdx.x >> 6);
+    const int item = (block >> 3) * (kThreadsB / kWave) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (item >= H->p_nitems) return;
     const auto* itp = as_const<int32_t>(plan + H->off_p_item) + 4 * item;    // RowItem, field by field
     const RowItem it{itp[0], itp[1], itp[2], itp[3]};
@@ -83,35 +83,43 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup 
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
     // The piece's entries are loaded once, 64 at a time (one per lane), and handed to the groups by
     // lane exchange, so that the loads of T do not each wait for a load of their entry and can
-    // all be in flight together.  Places behind the last entry read zeros (with a row of T, even times zero, an infinity there
-    // would reach this row of S): always the same ones, the plan's bytes behind its header, because a row of T costs L2 traffic.
-    constexpr uint32_t kNoRow = 0xFFFFFFFFu;
-    const float* zeros = reinterpret_cast<const float*>(plan + sizeof(PlanHeader));
-    static_assert(sizeof(PlanHeader) + 16 <= kPlanHeaderBytes, "both builders clear what is behind the header");
-    for (int base = 0; base < it.len; base += kWave) {
-        const int e_mine = base + lane;
-        const uint2 mine = e_mine < it.len ? ent[e_mine] : make_uint2(kNoRow, 0u);
-        const int steps = (min(it.len - base, (int)kWave) + NG - 1) / NG;      // uniform over the wave
-        // loads of T in flight per lane: 64 registers, seven waves a SIMD (sixteen: 100 and four; seven matrices of a
-        // 6.7B-style layer, the step 428 instead of 418 us; 4096 x 4096, r = 2048, d = 8: 108.6 instead of 104.3)
-        constexpr int kBlock = 8;
-        static_assert(kWave / NG % kBlock == 0, "a block of steps ends with the wave's entries");
-        for (int k0 = 0; k0 < steps; k0 += kBlock) {
-            f32x4 x[kBlock];
-            float v[kBlock];
+    // all be in flight together.  Groups without an entry in the last step take the last entry's row again, times zero: with a row
+    // of another piece an infinity there would reach this row of S.
+    // Eight loads of T in flight per lane: 56 to 68 registers, seven waves a SIMD.  (Sixteen take 100 and more and leave four: the step over
+    // seven matrices of a 6.7B-style layer 428 instead of 418 us; 4096 x 4096, r = 2048, d = 8, compress alone 60.9 -> 55.4.)
+    constexpr int kSteps = kWave / NG, kAhead = 8;
+    static_assert(kSteps % kAhead == 0, "a block of steps ends with the wave's entries");
+    auto take = [&](const uint2 mine, int k0, int steps) {                       // steps k0 .. k0 + kAhead - 1 of the 64 entries, less than `steps`
+        f32x4 x[kAhead];
+        float v[kAhead];
 #pragma unroll
-            for (int k = 0; k < kBlock; ++k) {
+        for (int k = 0; k < kAhead; ++k) {
+            x[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            v[k] = 0.0f;
+            if (k0 + k < steps) {                                               // uniform over the wave
                 const int src = (k0 + k) * NG + grp_e;                          // lane holding entry base + (k0+k)*NG + grp
                 const uint32_t row = (uint32_t)__shfl((int)mine.x, src);
                 v[k] = __uint_as_float((uint32_t)__shfl((int)mine.y, src));
-                x[k] = *reinterpret_cast<const loose*>(row != kNoRow ? Tcol + (int64_t)row * r : zeros);
-            }
-#pragma unroll
-            for (int k = 0; k < kBlock; ++k) {
-                acc.x = fmaf(v[k], x[k].x, acc.x); acc.y = fmaf(v[k], x[k].y, acc.y);
-                acc.z = fmaf(v[k], x[k].z, acc.z); acc.w = fmaf(v[k], x[k].w, acc.w);
+                x[k] = *reinterpret_cast<const loose*>(Tcol + (int64_t)row * r);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);                                      // all of them in flight before the first is used
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            acc.x = fmaf(v[k], x[k].x, acc.x); acc.y = fmaf(v[k], x[k].y, acc.y);
+            acc.z = fmaf(v[k], x[k].z, acc.z); acc.w = fmaf(v[k], x[k].w, acc.w);
+        }
+    };
+    int base = 0;
+    for (; base + kWave <= it.len; base += kWave) {
+        const uint2 mine = ent[base + lane];
+        for (int k0 = 0; k0 < kSteps; k0 += kAhead) take(mine, k0, k0 + kAhead);
+    }
+    if (base < it.len) {
+        uint2 mine = ent[min(base + lane, it.len - 1)];
+        if (base + lane >= it.len) mine.y = 0u;
+        const int steps = (it.len - base + NG - 1) / NG;
+        for (int k0 = 0; k0 < steps; k0 += kAhead) take(mine, k0, steps);
     }
 #pragma unroll
     for (int step = LG; step < kWave; step *= 2) {            // group g adds group g ^ (step / LG)
