@@ -91,21 +91,20 @@ int lsp_compress(const void* G, const int32_t* P_idx, const float* P_val, const 
     if (!aligned16(workspace)) return LSP_ERR_WORKSPACE;
     if (!aligned16(G) || !aligned16(S) || !aligned16(P_idx) || !aligned16(P_val) || !aligned16(Q_idx) || !aligned16(Q_val))
         return LSP_ERR_ALIGN;
-    // A plan is built on the device into the workspace, the planned kernels run on it, and the scatter form
-    // follows, which works only if the build found the columns too skewed for a plan.
+    // A plan is built on the device into the workspace and the planned kernels run on it; where the build found the columns too
+    // skewed for a plan they take the scatter form.
     uint8_t* ws = static_cast<uint8_t*>(workspace);
     float* T = reinterpret_cast<float*>(ws);
     uint8_t* plan = ws + t_bytes(m, r);
     uint8_t* scratch = plan + lsp::align_up(lsp::plan_bytes(m, n, r, d), 256);
     int32_t* status = reinterpret_cast<int32_t*>(scratch + lsp::plan_build_workspace_bytes(m, n, r, d));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipError_t e = lsp::launch_plan_build(P_idx, P_val, Q_idx, Q_val, m, n, r, d, plan, scratch, status, st);
+    hipError_t e = lsp::launch_plan_build(P_idx, P_val, Q_idx, Q_val, m, n, r, d, plan, scratch, status, st, S);
     if (e != hipSuccess) return fail_launch(e);
     lsp::CompressGroup g;
     std::memset(&g, 0, sizeof(g));
     g.count = 1; g.G[0] = G; g.plan[0] = plan; g.T[0] = T; g.S[0] = S; g.m[0] = (int32_t)m; g.n[0] = (int32_t)n;
-    if ((e = lsp::launch_compress_planned(g, r, d, dtype, st, 0.0f)) != hipSuccess) return fail_launch(e);
-    e = lsp::launch_compress_raw(G, P_idx, P_val, Q_idx, Q_val, m, n, r, d, S, dtype, status, st);
+    e = lsp::launch_compress_planned(g, r, d, dtype, st, lsp::RawCall{P_idx, P_val, Q_idx, Q_val, status});
     return e == hipSuccess ? LSP_OK : fail_launch(e);
 }
 

@@ -140,53 +140,11 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup 
 }
 
 // ----------------------------------------------------------------------------------------------
-// Scatter form behind a plan build that found the columns too skewed (`status`); S has been set to zero by kernel A.
-// The same mathematics: with a tile of T in LDS, every (row, column j, entry k) adds G[i][j] * Q_val[j][k] to
-// T[i][Q_idx[j][k]]; then S[P_idx[i][k]][:] += P_val[i][k] * T[i][:] with global atomics.  Nearly always there is nothing
-// to do, so it is one launch.  A build that met an index outside [0, r) leaves S full of NaN.
-// Where it works (whole lsp_compress calls): 4096 x 4096, r = 2048, d = 8, one hot column: 938 us, and 1074 with a launch for each half
-// (the second one with a workgroup a row); 256 x 2048, r = 2048, d = 4: 266, 321.
-constexpr int kRawRows = 16;
-template <typename D>
-__global__ __launch_bounds__(256) void k_raw(const typename D::elem* __restrict__ G, const int32_t* __restrict__ P_idx, const float* __restrict__ P_val,
-                                            const int32_t* __restrict__ Q_idx, const float* __restrict__ Q_val, float* __restrict__ S,
-                                            int m, int n, int r, int d, const int32_t* __restrict__ status) {
-    extern __shared__ __align__(16) uint8_t smem[];
-    if (*status == LSP_OK) return;                                    // the planned kernels have done the work
-    if (*status != LSP_ERR_SKEW) {
-        fill_s(S, __builtin_nanf(""), r, blockIdx.x, gridDim.x, threadIdx.x, 256);
-        return;
-    }
-    float* Tl = reinterpret_cast<float*>(smem);
-    const int64_t i0 = (int64_t)blockIdx.x * kRawRows;
-    for (int k = threadIdx.x; k < kRawRows * r; k += 256) Tl[k] = 0.0f;
-    __syncthreads();
-    for (int64_t j = threadIdx.x; j < n; j += 256) {
-        float g[kRawRows];
-#pragma unroll
-        for (int t = 0; t < kRawRows; ++t) g[t] = (i0 + t < m) ? widen<D>(G[(i0 + t) * (int64_t)n + j]) : 0.0f;
-        for (int k = 0; k < d; ++k) {
-            const int b = Q_idx[j * d + k];
-            const float v = Q_val[j * d + k];
-#pragma unroll
-            for (int t = 0; t < kRawRows; ++t) atomicAdd(&Tl[t * r + b], g[t] * v);
-        }
-    }
-    __syncthreads();
-    for (int t = 0; t < kRawRows && i0 + t < m; ++t)
-        for (int k = 0; k < d; ++k) {
-            const int a = P_idx[(i0 + t) * d + k];
-            const float v = P_val[(i0 + t) * d + k];
-            for (int b = threadIdx.x; b < r; b += 256) atomicAdd(&S[(int64_t)a * r + b], v * Tl[t * r + b]);
-        }
-}
-
-// ----------------------------------------------------------------------------------------------
-static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, float unplanned, lsp_dtype dtype, hipStream_t st) {
+static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, lsp_dtype dtype, hipStream_t st) {
     switch (dtype) {
-        case LSP_F32:  return launch_gq_f32(g, r, d, unplanned, st);
-        case LSP_F16:  return launch_gq_f16(g, r, d, unplanned, st);
-        default:       return launch_gq_bf16(g, r, d, unplanned, st);
+        case LSP_F32:  return launch_gq_f32(g, r, d, raw, st);
+        case LSP_F16:  return launch_gq_f16(g, r, d, raw, st);
+        default:       return launch_gq_bf16(g, r, d, raw, st);
     }
 }
 
@@ -202,7 +160,7 @@ static void longest_first(CompressGroup& g) {
         }
 }
 
-hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st, float unplanned) {
+hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st, const RawCall& raw) {
     const int nstripes = (r + kStripeQuads * 4 - 1) / (kStripeQuads * 4);
     const bool striped = r >= 4;
     longest_first(g);
@@ -211,7 +169,7 @@ hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_d
         const int32_t items = (int32_t)plan_max_items(g.m[p], r, d);
         g.first_pt[p + 1] = g.first_pt[p] + (striped ? ((items + 3) / 4) * 8 : items * nstripes);
     }
-    hipError_t e = launch_gq(g, r, d, unplanned, dtype, st);
+    hipError_t e = launch_gq(g, r, d, raw, dtype, st);
     if (e != hipSuccess) return e;
     const unsigned blocks = (unsigned)g.first_pt[g.count];
     if (striped) {
@@ -223,25 +181,6 @@ hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_d
     }
     hipLaunchKernelGGL(k_compress_pt, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, nstripes);
     return hipGetLastError();
-}
-
-template <typename D>
-static hipError_t launch_raw(const void* G, const int32_t* P_idx, const float* P_val, const int32_t* Q_idx, const float* Q_val,
-                             int64_t m, int64_t n, int32_t r, int32_t d, float* S, const int32_t* status, hipStream_t st) {
-    hipError_t e = allow_dynamic_lds<k_raw<D>>((size_t)kRawRows * LSP_MAX_R * sizeof(float));
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_raw<D>, dim3((unsigned)((m + kRawRows - 1) / kRawRows)), dim3(256), (size_t)kRawRows * r * sizeof(float), st,
-                       static_cast<const typename D::elem*>(G), P_idx, P_val, Q_idx, Q_val, S, (int)m, (int)n, (int)r, (int)d, status);
-    return hipGetLastError();
-}
-
-hipError_t launch_compress_raw(const void* G, const int32_t* P_idx, const float* P_val, const int32_t* Q_idx, const float* Q_val,
-                               int64_t m, int64_t n, int32_t r, int32_t d, float* S, lsp_dtype dtype, const int32_t* status, hipStream_t st) {
-    switch (dtype) {
-        case LSP_F32:  return launch_raw<F32>(G, P_idx, P_val, Q_idx, Q_val, m, n, r, d, S, status, st);
-        case LSP_F16:  return launch_raw<F16>(G, P_idx, P_val, Q_idx, Q_val, m, n, r, d, S, status, st);
-        default:       return launch_raw<BF16>(G, P_idx, P_val, Q_idx, Q_val, m, n, r, d, S, status, st);
-    }
 }
 
 }  // namespace lsp

@@ -13,14 +13,51 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // A plan is only followed when its header names this very problem: the offsets and counts in it
 // index S and T with the call's r and m, so a plan built for other sizes (or a buffer that holds no
-// plan at all) must not be walked.  Kernel A then fills S with `unplanned` -- NaN, which is how the caller sees
-// the mistake, or zero when the scatter form follows -- and kernel B does nothing; all kernels exit normally.
+// plan at all) must not be walked.  Kernel A then fills S with NaN, which is how the caller sees
+// the mistake (or takes the scatter form, raw calls), and kernel B does nothing; all kernels exit normally.
 __device__ __forceinline__ bool plan_matches(PlanHeaderPtr H, int m, int n, int r, int d) {
     return H->magic == kPlanMagic && H->m == m && H->n == n && H->r == r && H->d == d;
 }
 __device__ __forceinline__ void fill_s(float* __restrict__ S, float x, int r, int block, int nblocks, int tid, int nthreads) {
     const int64_t total = (int64_t)r * r;
     for (int64_t k = (int64_t)block * nthreads + tid; k < total; k += (int64_t)nblocks * nthreads) S[k] = x;
+}
+
+// Scatter form of the raw calls, for projectors whose columns are too skewed for a plan: the same mathematics.  With a tile of T in
+// LDS, every (row, column j, entry k) adds G[i][j] * Q_val[j][k] to T[i][Q_idx[j][k]]; then S[P_idx[i][k]][:] += P_val[i][k] * T[i][:]
+// with global atomics.  Nearly always there is nothing to do, so it has no launch of its own (4 us of some 50 on 4096 x 4096): kernel A does
+// it where it finds no plan.  Called by all threads of the workgroup; lds: kScatterRows * r floats.
+constexpr int kScatterRows = 8;
+template <typename D>
+__device__ __forceinline__ void scatter_blocks(const typename D::elem* __restrict__ G, const RawCall& raw, float* __restrict__ S, float* Tl, int m, int n, int r, int d,
+                                               int block, int nblocks, int tid, int nthreads) {
+    if (*raw.status != LSP_ERR_SKEW) {                                // an index outside [0, r)
+        fill_s(S, __builtin_nanf(""), r, block, nblocks, tid, nthreads);
+        return;
+    }
+    for (int64_t i0 = (int64_t)block * kScatterRows; i0 < m; i0 += (int64_t)nblocks * kScatterRows) {
+        __syncthreads();
+        for (int k = tid; k < kScatterRows * r; k += nthreads) Tl[k] = 0.0f;
+        __syncthreads();
+        for (int64_t j = tid; j < n; j += nthreads) {
+            float g[kScatterRows];
+#pragma unroll
+            for (int t = 0; t < kScatterRows; ++t) g[t] = (i0 + t < m) ? widen<D>(G[(i0 + t) * (int64_t)n + j]) : 0.0f;
+            for (int k = 0; k < d; ++k) {
+                const int b = raw.Q_idx[j * d + k];
+                const float v = raw.Q_val[j * d + k];
+#pragma unroll
+                for (int t = 0; t < kScatterRows; ++t) atomicAdd(&Tl[t * r + b], g[t] * v);
+            }
+        }
+        __syncthreads();
+        for (int t = 0; t < kScatterRows && i0 + t < m; ++t)
+            for (int k = 0; k < d; ++k) {
+                const int a = raw.P_idx[(i0 + t) * d + k];
+                const float v = raw.P_val[(i0 + t) * d + k];
+                for (int b = tid; b < r; b += nthreads) atomicAdd(&S[(int64_t)a * r + b], v * Tl[t * r + b]);
+            }
+    }
 }
 
 constexpr int kBatchLoads = kSegBatch / 2;                    // 128-bit loads per batch of plan rows
@@ -86,8 +123,8 @@ __device__ __forceinline__ void swap_owner(uint8_t* area, float (&acc)[R], uint3
 
 // Launchers of kernel A (they fill in first_gq and blocks_gq): one workgroup = a block of rows of G at a time, 512 threads, one lane
 // per (virtual) column of T.
-hipError_t launch_gq_bf16(CompressGroup& g, int32_t r, int32_t d, float unplanned, hipStream_t st);
-hipError_t launch_gq_f16(CompressGroup& g, int32_t r, int32_t d, float unplanned, hipStream_t st);
-hipError_t launch_gq_f32(CompressGroup& g, int32_t r, int32_t d, float unplanned, hipStream_t st);
+hipError_t launch_gq_bf16(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st);
+hipError_t launch_gq_f16(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st);
+hipError_t launch_gq_f32(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st);
 
 }  // namespace lsp

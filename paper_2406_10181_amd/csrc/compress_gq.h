@@ -392,8 +392,9 @@ __device__ __forceinline__ void gq_multi_slot(ChunkStager<D, WHOLE>& stg, uint8_
     }
 }
 
-template <typename D, bool WHOLE>
-__global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGroup grp, int r, int d, float unplanned) {
+// RAW: for a call on raw ELL arrays.  (With the scatter form in the one kernel for all, the planned calls lost 1 %.)
+template <typename D, bool WHOLE, bool RAW>
+__global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGroup grp, int r, int d, const RawCall raw) {
     constexpr int R = kRowsGQ<D>;
     extern __shared__ __align__(16) uint8_t smem[];
     const CompressProblem pr = group_pick(grp, (int)blockIdx.x, false);
@@ -413,7 +414,8 @@ __global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGro
     stg.fetch(G, i0, m, n, 0, tid);                             // in flight while the plan's header arrives
     PlanHeaderPtr H = as_const<PlanHeader>(plan);
     if (!plan_matches(H, m, n, r, d)) {                               // not a plan for this problem
-        fill_s(S, unplanned, r, block, nblocks, tid, kThreadsGQ);
+        if constexpr (RAW) scatter_blocks<D>(G, raw, S, reinterpret_cast<float*>(smem), m, n, r, d, block, nblocks, tid, kThreadsGQ);
+        else fill_s(S, __builtin_nanf(""), r, block, nblocks, tid, kThreadsGQ);
         return;
     }
     if (H->p_any_split) {
@@ -461,22 +463,22 @@ template <int R> static void share_blocks(CompressGroup& g) {
     fill([&](int64_t) { return (int64_t)(rows >= 16384 ? 2 : 1); });
 }
 
-template <typename D>
-static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, float unplanned, hipStream_t st) {
+template <typename D, bool WHOLE, bool RAW>
+static hipError_t launch_gq(const CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st) {
     constexpr size_t lds = (size_t)2 * kPlaneStride;                  // two chunk buffers
-    bool whole = true;
-    share_blocks<kRowsGQ<D>>(g);
-    for (int p = 0; p < g.count; ++p) whole = whole && g.n[p] % 4 == 0;
-    const dim3 grid((unsigned)g.first_gq[g.count]);
+    static_assert(lds >= (size_t)kScatterRows * LSP_MAX_R * sizeof(float), "room for scatter_blocks");
     hipError_t e;
-    if (whole) {
-        if ((e = allow_dynamic_lds<k_compress_gq<D, true>>(lds)) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_compress_gq<D, true>), grid, dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, unplanned);
-    } else {
-        if ((e = allow_dynamic_lds<k_compress_gq<D, false>>(lds)) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_compress_gq<D, false>), grid, dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, unplanned);
-    }
+    if ((e = allow_dynamic_lds<k_compress_gq<D, WHOLE, RAW>>(lds)) != hipSuccess) return e;
+    hipLaunchKernelGGL((k_compress_gq<D, WHOLE, RAW>), dim3((unsigned)g.first_gq[g.count]), dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, raw);
     return hipGetLastError();
 }
 
+template <typename D>
+static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st) {
+    bool whole = true;
+    share_blocks<kRowsGQ<D>>(g);
+    for (int p = 0; p < g.count; ++p) whole = whole && g.n[p] % 4 == 0;
+    if (raw.status) return whole ? launch_gq<D, true, true>(g, r, d, raw, st) : launch_gq<D, false, true>(g, r, d, raw, st);
+    return whole ? launch_gq<D, true, false>(g, r, d, raw, st) : launch_gq<D, false, false>(g, r, d, raw, st);
+}
 }  // namespace lsp

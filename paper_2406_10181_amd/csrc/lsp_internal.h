@@ -180,14 +180,14 @@ __device__ __forceinline__ int group_find(const int32_t* first, int count, int b
 // Kernel launchers (each returns hipSuccess or the launch error).  The group launchers fill in
 // first_* themselves.
 // ------------------------------------------------------------------------------------------
-// unplanned: what S is filled with if the plan turns out not to be one for the problem.
-hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st, float unplanned = __builtin_nanf(""));
-// Scatter form on raw ELL arrays, behind a planned compress that left zeros: it works only if *status (device, of the
-// plan build) is LSP_ERR_SKEW, and fills S with NaN if it is another error.
-hipError_t launch_compress_raw(const void* G, const int32_t* P_idx, const float* P_val,
-                               const int32_t* Q_idx, const float* Q_val,
-                               int64_t m, int64_t n, int32_t r, int32_t d,
-                               float* S, lsp_dtype dtype, const int32_t* status, hipStream_t st);
+// A call on raw ELL arrays, whose plan was built just before on the same stream: kernel A looks here where it finds no plan.
+// If *status (device, of the plan build) is LSP_ERR_SKEW it adds to S in scatter form (the build has set S to zero), any other error
+// makes S NaN.
+struct RawCall {
+    const int32_t* P_idx; const float* P_val; const int32_t* Q_idx; const float* Q_val;
+    const int32_t* status;                         // null: not such a call, no plan makes S NaN
+};
+hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st, const RawCall& raw = RawCall{});
 hipError_t launch_decompress(ApplyGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st);
 // Dense-projector ablation of compress on the matrix cores (dense.hip): Pt = P^T [r][m], Qt = Q^T [r][n] in the
 // storage type of G (fp16 / bf16); workspace of dense_workspace_bytes(m, r); shapes must pass dense_shape_ok.
@@ -209,10 +209,11 @@ hipError_t launch_plan_refresh(uint8_t* plan, const float* P_val, const float* Q
                                int64_t m, int64_t n, int32_t r, int32_t d, hipStream_t st);
 // Device-side plan build (plan_device.hip): the bytes of build_plan_host, from kernels on `st`; workspace of
 // plan_build_workspace_bytes(); status_out (device, may be null) receives LSP_OK / LSP_ERR_INDEX / LSP_ERR_SKEW.
+// zero: r x r floats to set to zero if there is no plan to be made of these projectors.
 size_t     plan_build_workspace_bytes(int64_t m, int64_t n, int32_t r, int32_t d);
 hipError_t launch_plan_build(const int32_t* P_idx, const float* P_val, const int32_t* Q_idx, const float* Q_val,
                              int64_t m, int64_t n, int32_t r, int32_t d, uint8_t* plan, uint8_t* workspace,
-                             int32_t* status_out, hipStream_t st);
+                             int32_t* status_out, hipStream_t st, float* zero = nullptr);
 // C = op(A) op(B) + beta E on r x r fp32 matrices (matrix cores): up to kMaxGemmBatch independent products of
 // one size in a launch (no product may read what another of the same launch writes).  flags: transpose an
 // operand (not both), square an operand element by element; E may be null.

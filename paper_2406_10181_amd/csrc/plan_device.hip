@@ -448,9 +448,13 @@ __device__ __forceinline__ uint32_t stream_row(const uint32_t* __restrict__ seg,
 // positions), `pblocks` the entries of P^T, the rest clears what lies behind the last row.
 __global__ __launch_bounds__(kThreadsRows) void k_plan_rows(uint8_t* __restrict__ plan, PlanLayout L, BuildScratch s, const int32_t* __restrict__ P_idx,
                                                             const float* __restrict__ P_val, const float* __restrict__ Q_val, int m, int r, int d,
-                                                            int nchunks, int pblocks, int64_t max_rows) {
+                                                            int nchunks, int pblocks, int64_t max_rows, float* __restrict__ zero) {
     PlanHeader* H = reinterpret_cast<PlanHeader*>(plan);
-    if (H->magic != kPlanMagic) return;
+    if (H->magic != kPlanMagic) {
+        if (zero)
+            for (int k = (int)blockIdx.x * kThreadsRows + threadIdx.x; k < r * r; k += (int)gridDim.x * kThreadsRows) zero[k] = 0.0f;
+        return;
+    }
     __shared__ int32_t s_part[kThreadsRows / kWave];
     __shared__ int32_t s_lo[kWave], s_n[kWave];
     const int tid = threadIdx.x;
@@ -540,7 +544,7 @@ __global__ __launch_bounds__(kThreadsRows) void k_plan_rows(uint8_t* __restrict_
 
 hipError_t launch_plan_build(const int32_t* P_idx, const float* P_val, const int32_t* Q_idx, const float* Q_val,
                              int64_t m, int64_t n, int32_t r, int32_t d, uint8_t* plan, uint8_t* workspace,
-                             int32_t* status_out, hipStream_t st) {
+                             int32_t* status_out, hipStream_t st, float* zero) {
     BuildScratch s;
     build_scratch(workspace, m, n, r, d, &s);
     const PlanLayout L = plan_layout(m, n, r, d);
@@ -559,7 +563,7 @@ hipError_t launch_plan_build(const int32_t* P_idx, const float* P_val, const int
     const int pblocks = (int)std::min<int64_t>((m * d + kThreadsRows - 1) / kThreadsRows, 512);
     const int zblocks = (int)std::min<int64_t>((max_rows * kWave / 2 + 4 * kThreadsRows - 1) / (4 * kThreadsRows), 512);
     hipLaunchKernelGGL(k_plan_rows, dim3((unsigned)(nchunks * kMaxSlots * kWavesGQ + kWavesGQ + pblocks + zblocks)), dim3(kThreadsRows), 0, st, plan, L, s,
-                       P_idx, P_val, Q_val, (int)m, (int)r, (int)d, nchunks, pblocks, max_rows);
+                       P_idx, P_val, Q_val, (int)m, (int)r, (int)d, nchunks, pblocks, max_rows, zero);
     return hipGetLastError();
 }
 
