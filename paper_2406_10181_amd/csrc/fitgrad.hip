@@ -32,11 +32,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // 4096 x 4096, d = 8, 16-bit) is what the kernel's time is made of.  HBM sees G once: workgroup b runs on XCD b % 8 (the
 // dispatcher deals workgroups round-robin), and the grid is laid out so that one XCD takes every a for a column tile
 // before its next tile, so a tile of G (m rows of 256 elements, 2 MB at m = 4096) stays in that XCD's L2 for its
-// d visits.  With a workgroup a piece (four waves, a quarter of the entries each, 8 bytes a lane) it took 34 us there, now 24.
+// d visits.  With a workgroup a piece (four waves, a quarter of the entries each, 8 bytes a lane) it took 34 us there, now 23 (24 with the address of a row made anew for every load: BELOW_4G, a 32-bit offset).
 // A row's last piece starts at n - VEC when n is no multiple of VEC, up to VEC - 1 columns before its tile if the tile has
 // fewer than VEC columns: the wave's sums have room for them in front.  n < VEC: one column a lane (VEC = 1).
 constexpr int kThreadsY = 256, kWavesY = kThreadsY / kWave, kXcds = 8, kTileY = 256;
-template <typename D, int VEC>
+template <typename D, int VEC, bool BELOW_4G>
 __global__ __launch_bounds__(kThreadsY) void k_gather_rows(const typename D::elem* __restrict__ G, const uint8_t* __restrict__ plan,
                                                           float* __restrict__ Y, int m, int n, int r, int d, int item_groups, int tiles) {
     constexpr int LG = VEC == 1 ? kWave : kTileY / VEC < kWave ? kTileY / VEC : kWave;   // lanes of an entry
@@ -59,25 +59,26 @@ __global__ __launch_bounds__(kThreadsY) void k_gather_rows(const typename D::ele
     const int j0 = tile0 + ql * VEC;                                // this lane's columns
     const bool live = j0 < n && ql * VEC < kTileY;
     const int at = live ? min(j0, n - VEC) : 0;                     // where its piece starts
-    const typename D::elem* Gc = G + at;
     float acc[VEC];
 #pragma unroll
     for (int q = 0; q < VEC; ++q) acc[q] = 0.0f;
     for (int base = 0; base < it.len; base += kWave) {
         uint2 mine = ent[min(base + lane, it.len - 1)];              // behind the last entry: its row again, times zero
         if (base + lane >= it.len) mine.y = 0u;
+        if constexpr (BELOW_4G) mine.x *= (uint32_t)n * D::size;     // the row's offset in G, once per entry and not per load
         const int steps = (min(it.len - base, (int)kWave) + NG - 1) / NG;
         constexpr int kInFlight = 8;
+        static_assert(kWave / NG % kInFlight == 0, "the loads of a batch all have an entry");
         for (int k0 = 0; k0 < steps; k0 += kInFlight) {
             Piece x[kInFlight];
             float v[kInFlight];
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
-                const int src = min((k0 + u) * NG + grp, (int)kWave - 1);
+                const int src = (k0 + u) * NG + grp;
                 const uint32_t row = (uint32_t)__shfl((int)mine.x, src);
-                const bool on = k0 + u < steps;
-                v[u] = on ? __uint_as_float((uint32_t)__shfl((int)mine.y, src)) : 0.0f;
-                x[u] = *reinterpret_cast<const Loose*>(Gc + (int64_t)row * n);
+                v[u] = __uint_as_float((uint32_t)__shfl((int)mine.y, src));
+                if constexpr (BELOW_4G) x[u] = *reinterpret_cast<const Loose*>(reinterpret_cast<const char*>(G) + (row + (uint32_t)at * D::size));
+                else x[u] = *reinterpret_cast<const Loose*>(G + at + (int64_t)row * n);
             }
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u)
@@ -195,9 +196,11 @@ static hipError_t launch_gather(const void* G, const uint8_t* plan, float* Y, in
         const int tiles = (int)((n + kTileY - 1) / kTileY);          // (VEC = 1: one tile of n < 8 columns)
         const int64_t grid = (int64_t)groups * ((tiles + kXcds - 1) / kXcds) * kXcds;
         if (grid > INT32_MAX) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((k_gather_rows<D, VEC>), dim3((unsigned)grid), dim3(kThreadsY), 0, st, static_cast<const E*>(G), plan, Y,
-                           (int)m, (int)n, (int)r, (int)d, groups, tiles);
-        return hipGetLastError();
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreadsY), 0, st, static_cast<const E*>(G), plan, Y, (int)m, (int)n, (int)r, (int)d, groups, tiles);
+            return hipGetLastError();
+        };
+        return m * n * D::size <= (int64_t)UINT32_MAX ? go(k_gather_rows<D, VEC, true>) : go(k_gather_rows<D, VEC, false>);
     };
     constexpr int kPiece = 16 / D::size;
     if (n >= kPiece) return launch(std::integral_constant<int, kPiece>{});
