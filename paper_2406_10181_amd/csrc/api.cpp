@@ -99,7 +99,7 @@ int lsp_compress(const void* G, const int32_t* P_idx, const float* P_val, const 
     uint8_t* scratch = plan + lsp::align_up(lsp::plan_bytes(m, n, r, d), 256);
     int32_t* status = reinterpret_cast<int32_t*>(scratch + lsp::plan_build_workspace_bytes(m, n, r, d));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipError_t e = lsp::launch_plan_build(P_idx, P_val, Q_idx, Q_val, m, n, r, d, plan, scratch, status, st, S);
+    hipError_t e = lsp::launch_plan_build(P_idx, P_val, Q_idx, Q_val, m, n, r, d, plan, scratch, status, st, false, S);
     if (e != hipSuccess) return fail_launch(e);
     lsp::CompressGroup g;
     std::memset(&g, 0, sizeof(g));

@@ -1,7 +1,8 @@
 // Compress: S = P^T G Q  (Alg. 1, compress step; Alg. 3, projected gradient of a layer).
 //
 // Two kernels per call, both gather-form and free of global atomics in the common case:
-//   A  T = G Q     one workgroup per block of 8 rows of G (4 of fp32); G is streamed once from HBM in
+//   A  T = G Q     (fp16 and fp32, and some bf16; most bf16: compress_mm.hip)
+//                  one workgroup per block of 8 rows of G (4 of fp32); G is streamed once from HBM in
 //                  chunks of kChunk columns and staged in LDS transposed, as it is stored, one 16-byte
 //                  unit per column, so one 128-bit LDS read serves all rows of the block; each
 //                  lane owns one column b of T and walks the plan's list of (column of G, value)
@@ -10,11 +11,9 @@
 //                  lanes between chunks (swap_owner).
 //   B  S = P^T T   one wave per piece of a row of P^T and 1/8 of the columns; reads rows of T.
 // The path streams G once.  Kernel A is nearest to the vector ALUs' issue rate (8 widenings and 8 FMAs per pair and 8 rows
-// for bf16), not to HBM: in the launch of the seven matrices of a 6.7B-style layer (bf16, r = 512, d = 8; 180 us) the
-// vector ALUs issue in 67 % of the cycles, the LDS works 45 %, L2 hands out 2.5 GB (14 TB/s; 1.8 GB of it the plan, which
-// every block of 8 rows reads again) and HBM moves 520 MB (2.9 TB/s); the waves (3.3 a SIMD, 4 fit) wait for data 42 % of their
-// time.  No matrix cores are involved because the projectors are sparse (d entries per row, Def. 1) and the work is
-// gather + fp32 FMA.
+// of 16-bit storage), not to HBM: the vector ALUs issue in 67 % of the cycles, the LDS works 45 %, and L2 hands out the plan once per
+// block of 8 rows; the waves (3.3 a SIMD, 4 fit) wait for data 42 % of their time.  For bf16 the matrix cores take the sums over
+// (compress_mm.hip); fp16's exponents do not reach far enough for exact parts of an fp32 value, and fp32 has no such instruction.
 
 #include "compress_common.h"
 
@@ -144,7 +143,7 @@ static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, const RawCal
     switch (dtype) {
         case LSP_F32:  return launch_gq_f32(g, r, d, raw, st);
         case LSP_F16:  return launch_gq_f16(g, r, d, raw, st);
-        default:       return launch_gq_bf16(g, r, d, raw, st);
+        default:       return raw.status || !mm_bf16_suits(g, r) ? launch_gq_bf16(g, r, d, raw, st) : launch_mm_bf16(g, r, d, st);
     }
 }
 

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <algorithm>
+#include <type_traits>
 
 #include "compress_common.h"
 
@@ -392,9 +393,10 @@ __device__ __forceinline__ void gq_multi_slot(ChunkStager<D, WHOLE>& stg, uint8_
     }
 }
 
+struct NoRawCall {};
 // RAW: for a call on raw ELL arrays.  (With the scatter form in the one kernel for all, the planned calls lost 1 %.)
 template <typename D, bool WHOLE, bool RAW>
-__global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGroup grp, int r, int d, const RawCall raw) {
+__global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGroup grp, int r, int d, const std::conditional_t<RAW, RawCall, NoRawCall> raw) {
     constexpr int R = kRowsGQ<D>;
     extern __shared__ __align__(16) uint8_t smem[];
     const CompressProblem pr = group_pick(grp, (int)blockIdx.x, false);
@@ -467,9 +469,11 @@ template <typename D, bool WHOLE, bool RAW>
 static hipError_t launch_gq(const CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st) {
     constexpr size_t lds = (size_t)2 * kPlaneStride;                  // two chunk buffers
     static_assert(lds >= (size_t)kScatterRows * LSP_MAX_R * sizeof(float), "room for scatter_blocks");
+    std::conditional_t<RAW, RawCall, NoRawCall> args{};
+    if constexpr (RAW) args = raw;
     hipError_t e;
     if ((e = allow_dynamic_lds<k_compress_gq<D, WHOLE, RAW>>(lds)) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_compress_gq<D, WHOLE, RAW>), dim3((unsigned)g.first_gq[g.count]), dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, raw);
+    hipLaunchKernelGGL((k_compress_gq<D, WHOLE, RAW>), dim3((unsigned)g.first_gq[g.count]), dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, args);
     return hipGetLastError();
 }
 
@@ -478,7 +482,7 @@ static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, const RawCal
     bool whole = true;
     share_blocks<kRowsGQ<D>>(g);
     for (int p = 0; p < g.count; ++p) whole = whole && g.n[p] % 4 == 0;
-    if (raw.status) return whole ? launch_gq<D, true, true>(g, r, d, raw, st) : launch_gq<D, false, true>(g, r, d, raw, st);
-    return whole ? launch_gq<D, true, false>(g, r, d, raw, st) : launch_gq<D, false, false>(g, r, d, raw, st);
+    if (!raw.status) return whole ? launch_gq<D, true, false>(g, r, d, raw, st) : launch_gq<D, false, false>(g, r, d, raw, st);
+    return whole ? launch_gq<D, true, true>(g, r, d, raw, st) : launch_gq<D, false, true>(g, r, d, raw, st);
 }
 }  // namespace lsp

@@ -23,6 +23,13 @@ constexpr int kSegBatch   = 4;     // segment lengths are multiples of this many
 constexpr int kPrefetch   = 4;     // batches of plan rows a wave holds in registers (one consumed, the rest in flight)
 constexpr int kStreamSlack = kPrefetch * kSegBatch;   // readable padding rows after the last segment
 constexpr int kRowPiece   = 256;   // a row list of P^T longer than this is cut into pieces
+// bf16 goes through matrix instructions (compress_mm.hip): tiles of 32 lists, two sets of 16, four entries of each a step
+constexpr int kSetCols    = 16;    // lists of a set: the 16 blocks of v_mfma_f32_4x4x4_16b_bf16
+constexpr int kTileCols   = 2 * kSetCols;
+constexpr int kStepEntries = 4;    // entries of every list a step takes: the K of a block
+constexpr int kWavesMM    = 8;     // waves of that kernel that walk the lists
+constexpr int kWaveTiles  = kMaxSlots * kThreadsGQ / kTileCols / kWavesMM;   // most tiles of a wave in one chunk
+constexpr int kStepsAhead = 10;     // steps a wave holds in registers (8: 1.5 % slower on a 6.7B layer, 12: spills); so many readable ones follow the last
 constexpr uint32_t kNoColumn = 0xFFFFu;      // virtual column slot without a column
 constexpr uint32_t kSharedColumn = 0x8000u;  // flag: the column is owned by several lanes
 
@@ -37,6 +44,9 @@ int note_hip_error(hipError_t e);
 __host__ __device__ static inline uint32_t chunk_col_offset(uint32_t j) {
     return (((j & 7u) * (kChunk / 8)) + (j >> 3)) * 16u;
 }
+
+// The same for the bf16 kernel, whose chunks lie in planes of 4 rows x 16 bits: a column is an 8-byte unit of each plane.
+__host__ __device__ static inline uint32_t chunk_unit_offset(uint32_t j) { return chunk_col_offset(j) / 2; }
 
 // ------------------------------------------------------------------------------------------
 // Plan: column-sorted projector copies, laid out for the compress kernels.
@@ -59,6 +69,15 @@ __host__ __device__ static inline uint32_t chunk_col_offset(uint32_t j) {
 // 64 x (LDS offset, value bits, LDS offset, value bits), one 128-bit load per lane.
 // The rows of one wave are contiguous over all chunks and slots (chunk-major), so a wave reads
 // one linear stream.
+//
+// The lists once more for the bf16 kernel.  Per chunk all virtual columns are sorted by length, longest first, and cut into
+// tiles of 32; they are dealt to 8 waves in rounds, some backwards (tile_of_wave), so that the waves get about the same number of
+// steps.  A step is four entries of every list of a tile: 64 x 16 bytes, the first 8 for lists 0..15 and the others for 16..31.
+// In each half, with 4-lane group b = lane / 4 and s = lane % 4:
+//   s < 3    part s of the values of list b's four entries (v = v0 + v1 + v2 exactly, bf16 each: the B operand as it is)
+//   s = 3    the LDS offsets of entry b % 4 of the four lists b / 4 * 4 .. + 3 (the transposing LDS read takes the entries of
+//            a list from lanes 4 apart)
+// A list shorter than the tile's longest is filled up with zero values at the always-zero unit.
 // ------------------------------------------------------------------------------------------
 struct PlanHeader {            // first 256 bytes of the plan buffer
     uint32_t magic;            // kPlanMagic
@@ -87,14 +106,48 @@ struct PlanHeader {            // first 256 bytes of the plan buffer
     // the values of the projectors change (lsp_plan_refresh_values): flat ELL positions row * d + k
     uint64_t off_q_src;        // uint32[q_total_rows][64], laid out like q_rows; kNoSource for padding pairs
     uint64_t off_p_src;        // uint32[m*d], parallel to p_ent
-    uint64_t pad2[2];
+    // tiles of lists (bf16)
+    uint64_t off_m_seg;        // TileSeg[nchunks][kWavesMM]
+    uint64_t off_m_cols;       // uint16[nchunks][kWavesMM][16][kWaveTiles][2]   virtual columns of lists b and 16 + b of the wave's tile t; lists
+                               // that fill up the last tile count on from nvcols
+    uint64_t off_m_steps;      // uint4[m_total_steps][64]
+    uint64_t off_m_src;        // uint32[m_total_steps][2][16][4]     flat ELL position of entry k of list 16 h + b; kNoSource: none
+    uint32_t m_total_steps;    // kStepsAhead readable ones behind the last included
+    uint32_t pad2;
 };
-static_assert(sizeof(PlanHeader) == 192, "PlanHeader layout");
+static_assert(sizeof(PlanHeader) == 216, "PlanHeader layout");
 constexpr uint32_t kPlanMagic = 0x4C535038u;   // "LSP8"
 constexpr uint32_t kNoSource = 0xFFFFFFFFu;    // q_src of a padding pair
 constexpr size_t   kPlanHeaderBytes = 256;
 
 struct RowItem   { int32_t a; int32_t start; int32_t len; int32_t atomic; };
+
+// What wave w does in chunk c: its steps (consecutive) and how many of them each of its tiles has.
+struct TileSeg   { uint32_t first_step; uint32_t steps; uint16_t len[kWaveTiles]; uint32_t pad[2]; };
+static_assert(sizeof(TileSeg) == 32, "one scalar load");
+// Tile i of wave w, as a position in the sorted order (0: the longest lists).  Round i goes backwards where i has an odd number of
+// bits set: no wave is first or last in most rounds.
+__host__ __device__ static inline int tile_of_wave(int i, int w) { return kWavesMM * i + (((0x6996 >> i) & 1) ? kWavesMM - 1 - w : w); }
+
+// The three bf16 parts of a value, highest first: each takes the leading 8 significant bits of what is left, so they add up to
+// v exactly (but for bits below 2^-133).  An infinity or NaN is its first part.
+__host__ __device__ static inline void value_parts(float v, uint16_t (&part)[3]) {
+    uint32_t u;
+    __builtin_memcpy(&u, &v, 4);
+    if ((u & 0x7F800000u) == 0x7F800000u) {
+        part[0] = (uint16_t)((u >> 16) | ((u & 0x007FFFFFu) ? 0x40u : 0u));
+        part[1] = part[2] = 0;
+        return;
+    }
+    for (int k = 0; k < 3; ++k) {
+        __builtin_memcpy(&u, &v, 4);
+        part[k] = (uint16_t)(u >> 16);
+        u &= 0xFFFF0000u;
+        float head;
+        __builtin_memcpy(&head, &u, 4);
+        v -= head;
+    }
+}
 
 // Copy of an ELL projector with the entries of each row ordered against LDS bank conflicts in the
 // decompress kernels (host arrays; the matrix itself is unchanged).
@@ -102,12 +155,14 @@ int reorder_rows_host(const int32_t* idx, const float* val, int64_t rows, int32_
                       int32_t* idx_out, float* val_out);
 
 // Byte offsets of the plan's sections (they depend on the shape only).
-struct PlanLayout { size_t off_q_seg, off_q_vcol, off_q_vcnt, off_q_perm, off_q_rows, off_p_item, off_p_ent, off_q_src, off_p_src, total; };
+struct PlanLayout { size_t off_q_seg, off_q_vcol, off_q_vcnt, off_q_perm, off_q_rows, off_p_item, off_p_ent, off_q_src, off_p_src,
+                           off_m_seg, off_m_cols, off_m_steps, off_m_src, total; };
 PlanLayout plan_layout(int64_t m, int64_t n, int32_t r, int32_t d);
 
 // Upper bounds (depend on shapes only) used to size the plan buffer.
 int    plan_list_cap(int32_t r, int32_t d);
 size_t plan_max_rows(int64_t n, int32_t r, int32_t d);
+size_t plan_max_steps(int64_t n, int32_t r, int32_t d);
 size_t plan_max_items(int64_t m, int32_t r, int32_t d);
 size_t plan_bytes(int64_t m, int64_t n, int32_t r, int32_t d);
 
@@ -129,7 +184,7 @@ struct CompressGroup {
     float*         T[kMaxGroup];
     float*         S[kMaxGroup];
     int32_t        m[kMaxGroup], n[kMaxGroup];
-    int32_t        first_gq[kMaxGroup + 1];      // workgroups of the T = G Q kernel
+    int32_t        first_gq[kMaxGroup + 1];      // workgroups of the T = G Q kernel (bf16: row blocks)
     int32_t        blocks_gq[kMaxGroup];         // row blocks of each of them
     int32_t        first_pt[kMaxGroup + 1];      // workgroups of the S = P^T T kernel
     int32_t        count;
@@ -209,11 +264,12 @@ hipError_t launch_plan_refresh(uint8_t* plan, const float* P_val, const float* Q
                                int64_t m, int64_t n, int32_t r, int32_t d, hipStream_t st);
 // Device-side plan build (plan_device.hip): the bytes of build_plan_host, from kernels on `st`; workspace of
 // plan_build_workspace_bytes(); status_out (device, may be null) receives LSP_OK / LSP_ERR_INDEX / LSP_ERR_SKEW.
-// zero: r x r floats to set to zero if there is no plan to be made of these projectors.
 size_t     plan_build_workspace_bytes(int64_t m, int64_t n, int32_t r, int32_t d);
+// with_tiles: false for a plan that the bf16 kernel will not follow.
+// zero: r x r floats to set to zero if there is no plan to be made of these projectors.
 hipError_t launch_plan_build(const int32_t* P_idx, const float* P_val, const int32_t* Q_idx, const float* Q_val,
                              int64_t m, int64_t n, int32_t r, int32_t d, uint8_t* plan, uint8_t* workspace,
-                             int32_t* status_out, hipStream_t st, float* zero = nullptr);
+                             int32_t* status_out, hipStream_t st, bool with_tiles = true, float* zero = nullptr);
 // C = op(A) op(B) + beta E on r x r fp32 matrices (matrix cores): up to kMaxGemmBatch independent products of
 // one size in a launch (no product may read what another of the same launch writes).  flags: transpose an
 // operand (not both), square an operand element by element; E may be null.

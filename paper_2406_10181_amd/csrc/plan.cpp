@@ -36,6 +36,14 @@ size_t plan_max_rows(int64_t n, int32_t r, int32_t d) {
     return (size_t)(nchunks * kMaxSlots * kWavesGQ * seg + kWavesGQ * kStreamSlack);
 }
 
+// Steps of the tiles: of a chunk's tiles, sorted by length, the longest list of one is no longer than the mean of the one before.
+size_t plan_max_steps(int64_t n, int32_t r, int32_t d) {
+    const int64_t nchunks = (n + kChunk - 1) / kChunk;
+    const int64_t per_chunk = kWavesMM * kWaveTiles + (plan_list_cap(r, d) + kStepEntries - 1) / kStepEntries +
+                              ((int64_t)kChunk * d + kTileCols * kStepEntries - 1) / (kTileCols * kStepEntries);
+    return (size_t)(nchunks * per_chunk + kStepsAhead);
+}
+
 size_t plan_max_items(int64_t m, int32_t r, int32_t d) {
     return (size_t)((int64_t)r + (m * d + kRowPiece - 1) / kRowPiece + 1);
 }
@@ -53,9 +61,14 @@ PlanLayout plan_layout(int64_t m, int64_t n, int32_t r, int32_t d) {
     L.off_p_ent  = o; o = align_up(o + (size_t)(m * d) * sizeof(uint2), 256);
     L.off_q_src  = o; o = align_up(o + plan_max_rows(n, r, d) * kWave * sizeof(uint32_t), 256);
     L.off_p_src  = o; o = align_up(o + (size_t)(m * d) * sizeof(uint32_t), 256);
+    L.off_m_seg   = o; o = align_up(o + nchunks * kWavesMM * sizeof(TileSeg), 256);
+    L.off_m_cols  = o; o = align_up(o + nchunks * kWavesMM * kTileCols * kWaveTiles * sizeof(uint16_t), 256);
+    L.off_m_steps = o; o = align_up(o + plan_max_steps(n, r, d) * kWave * sizeof(uint4), 256);
+    L.off_m_src   = o; o = align_up(o + plan_max_steps(n, r, d) * kWave * 2 * sizeof(uint32_t), 256);
     L.total = o;
     return L;
 }
+
 namespace {
 uint32_t float_bits(float f) { uint32_t u; std::memcpy(&u, &f, 4); return u; }
 }  // namespace
@@ -226,6 +239,59 @@ int build_plan_host(const int32_t* P_idx, const float* P_val, const int32_t* Q_i
             }
     }
     H->q_total_rows = (int32_t)row;
+
+    // ---- tiles of 16 lists (bf16) -----------------------------------------------------------------
+    H->off_m_seg = L.off_m_seg; H->off_m_cols = L.off_m_cols; H->off_m_steps = L.off_m_steps; H->off_m_src = L.off_m_src;
+    TileSeg*  mseg = reinterpret_cast<TileSeg*>(out + L.off_m_seg);
+    uint16_t* mcols = reinterpret_cast<uint16_t*>(out + L.off_m_cols);
+    uint16_t* msteps = reinterpret_cast<uint16_t*>(out + L.off_m_steps);
+    uint32_t* msrc = reinterpret_cast<uint32_t*>(out + L.off_m_src);
+    const int ntiles = (V + kTileCols - 1) / kTileCols;
+    std::vector<int32_t> by_len((size_t)nchunks * (size_t)V);
+    auto length_of = [&](int c, int v) { int32_t lo, hi; share(c, v_col[(size_t)v], v_own[(size_t)v], lo, hi); return hi - lo; };
+    for (int c = 0; c < nchunks; ++c) {
+        int32_t* o = by_len.data() + (size_t)c * (size_t)V;
+        for (int v = 0; v < V; ++v) o[v] = v;
+        std::stable_sort(o, o + V, [&](int32_t x, int32_t y) { return length_of(c, x) > length_of(c, y); });
+    }
+    uint32_t at_step = 0;
+    for (int c = 0; c < nchunks; ++c)
+        for (int w = 0; w < kWavesMM; ++w) {
+            const int32_t* o = by_len.data() + (size_t)c * (size_t)V;
+            TileSeg& sg = mseg[(size_t)c * kWavesMM + (size_t)w];
+            sg.first_step = at_step;
+            for (int i = 0; i < kWaveTiles; ++i) {
+                const int t = tile_of_wave(i, w);
+                const int lists = t < ntiles ? std::min(kTileCols, V - t * kTileCols) : 0;
+                const int steps = lists > 0 ? (length_of(c, o[t * kTileCols]) + kStepEntries - 1) / kStepEntries : 0;
+                sg.len[i] = (uint16_t)steps;
+                for (int bb = 0; bb < kTileCols; ++bb) {
+                    const int h = bb / kSetCols, b = bb % kSetCols;
+                    const int v = bb < lists ? o[t * kTileCols + bb] : -1;
+                    mcols[((((size_t)c * kWavesMM + (size_t)w) * kSetCols + (size_t)b) * kWaveTiles + (size_t)i) * 2 + (size_t)h] =
+                        (uint16_t)(t >= ntiles ? 0 : v < 0 ? t * kTileCols + bb : v);
+                    int32_t lo = 0, hi = 0;
+                    if (v >= 0) share(c, v_col[(size_t)v], v_own[(size_t)v], lo, hi);
+                    for (int e = 0; e < steps * kStepEntries; ++e) {
+                        const size_t step = at_step + (size_t)(e / kStepEntries);
+                        const int k = e % kStepEntries;
+                        const uint32_t src = e < hi - lo ? sorted_src[(size_t)c][(size_t)(lo + e)] : kNoSource;
+                        uint16_t part[3] = {0, 0, 0};
+                        if (src != kNoSource) value_parts(Q_val[src], part);
+                        auto place = [&](int lane) { return msteps + ((step * kWave + (size_t)lane) * 2 + (size_t)h) * 4; };
+                        for (int s = 0; s < 3; ++s) place(4 * b + s)[k] = part[s];
+                        place(4 * (b / 4 * 4 + k) + 3)[b % 4] =
+                            (uint16_t)(src != kNoSource ? chunk_unit_offset((uint32_t)(src / (uint32_t)d) - (uint32_t)c * kChunk) : (uint32_t)kChunk * 8u);
+                        msrc[(step * 2 + (size_t)h) * kWave + (size_t)b * 4 + (size_t)k] = src;
+                    }
+                }
+                at_step += (uint32_t)steps;
+            }
+            sg.steps = at_step - sg.first_step;
+        }
+    for (int k = 0; k < kStepsAhead * kWave * 2; ++k) msrc[(size_t)at_step * kWave * 2 + (size_t)k] = kNoSource;
+    at_step += kStepsAhead;
+    H->m_total_steps = at_step;
 
     // ---- P^T: for each subspace row a, the (row of G, value) pairs, cut into pieces -------------
     RowItem* items = reinterpret_cast<RowItem*>(out + L.off_p_item);

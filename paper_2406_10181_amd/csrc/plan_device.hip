@@ -10,11 +10,11 @@
 //      host's counting sorts, (subspace column, row, k), by a stable counting sort in LDS;
 //   2. k_plan_deal: owners per column of T (long lists are shared between lanes, spare lanes go to the longest
 //      lists), virtual columns, slots; per chunk the lists dealt to the waves by length; the pieces of the rows of P^T;
-//   3. k_plan_rows: the waves' stream positions, the interleaved (LDS offset, value) rows, the entries of P^T.
+//   3. k_plan_rows: the waves' stream positions, the interleaved (LDS offset, value) rows, the entries of P^T, the steps of the tiles.
 // What bounds a build is not bytes (a few MB) but the chain of launches and of dependent loads inside them, so the
 // work is cut into few kernels, and small sums are taken again by every workgroup that needs them.  The form before
 // this one (64-bit keys, two device-wide radix sorts, 17 to 23 launches) took 96 us of host time alone for a
-// 4096 x 4096 matrix with r = 512 and d = 8; this one is done after 24 us.
+// 4096 x 4096 matrix with r = 512 and d = 8; this one is done after 26 us (24 of them before there were tiles).
 // The sums that are taken again (all chunks' longest lists in k_plan_deal, all segments in k_plan_rows) grow with the square of
 // the chunks, and show only far beyond weight matrices: n = 131072 (64 chunks) 62 us, 1M 0.44 ms, 4M 2.5 ms (r = 512, d = 8; the
 // form before: 275 us, 1.0 ms, 3.6 ms), and 16.8M (8192 chunks, r = 64, d = 2) 12.3 ms against 11.1.
@@ -30,31 +30,58 @@
 
 namespace lsp {
 
+// What bounds it is the launch and one chain of three trips to memory (header, positions, values), so a thread takes four values at a time
+// and all are in flight: 4096 x 4096, d = 8 stays at 4 us (one value a thread in the lists and four in the tiles, the lists' copy for bf16: 4.7).
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_plan_refresh(uint8_t* __restrict__ plan, const float* __restrict__ P_val,
                                                       const float* __restrict__ Q_val, int m, int n, int r, int d) {
     const PlanHeader* H = reinterpret_cast<const PlanHeader*>(plan);
     if (H->magic != kPlanMagic || H->m != m || H->n != n || H->r != r || H->d != d) return;   // not this problem's plan
-    const int64_t nq = (int64_t)H->q_total_rows * kWave, np = (int64_t)m * d;
+    const int64_t nq = (int64_t)H->q_total_rows * kWave / 4, np = (int64_t)m * d, np4 = (np + 3) / 4;
+    const int64_t nt = H->off_m_steps != 0 ? (int64_t)H->m_total_steps * kTileCols : 0;
     uint2* rows = reinterpret_cast<uint2*>(plan + H->off_q_rows);
-    const uint32_t* qsrc = reinterpret_cast<const uint32_t*>(plan + H->off_q_src);
+    const uint4* qsrc = reinterpret_cast<const uint4*>(plan + H->off_q_src);
     uint2* pent = reinterpret_cast<uint2*>(plan + H->off_p_ent);
     const uint32_t* psrc = reinterpret_cast<const uint32_t*>(plan + H->off_p_src);
-    const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < nq + np; k += stride) {
-        if (k < nq) {
-            const uint32_t s = qsrc[k];
-            if (s != kNoSource) rows[k].y = __float_as_uint(Q_val[s]);
+    uint16_t* msteps = reinterpret_cast<uint16_t*>(plan + H->off_m_steps);
+    const uint4* msrc = reinterpret_cast<const uint4*>(plan + H->off_m_src);
+    for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < nt + nq + np4; k += (int64_t)gridDim.x * 256) {
+        if (k < nt) {                                                // four entries of one list of a tile
+            const uint4 x = msrc[k];                                 // [step][h][b]
+            const uint32_t src[kStepEntries] = {x.x, x.y, x.z, x.w};
+            if (src[0] == kNoSource) continue;                       // (a list's entries come first)
+            uint16_t parts[kStepEntries][3];
+#pragma unroll
+            for (int e = 0; e < kStepEntries; ++e) value_parts(src[e] != kNoSource ? Q_val[src[e]] : 0.0f, parts[e]);
+            const int b = (int)(k % kSetCols), h = (int)(k / kSetCols % 2);
+            uint16_t* out = msteps + k / kTileCols * kWave * 8 + h * 4;
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                *reinterpret_cast<uint2*>(out + (4 * b + q) * 8) = make_uint2(parts[0][q] | (uint32_t)parts[1][q] << 16, parts[2][q] | (uint32_t)parts[3][q] << 16);
+        } else if (k < nt + nq) {
+            const uint4 x = qsrc[k - nt];
+            const uint32_t src[4] = {x.x, x.y, x.z, x.w};
+            float val[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) val[e] = src[e] != kNoSource ? Q_val[src[e]] : 0.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (src[e] != kNoSource) rows[(k - nt) * 4 + e].y = __float_as_uint(val[e]);
         } else {
-            const int64_t e = k - nq;
-            pent[e].y = __float_as_uint(P_val[psrc[e]]);
+            const int64_t p0 = (k - nt - nq) * 4;
+            float val[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) val[e] = p0 + e < np ? P_val[psrc[p0 + e]] : 0.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (p0 + e < np) pent[p0 + e].y = __float_as_uint(val[e]);
         }
     }
 }
 
 hipError_t launch_plan_refresh(uint8_t* plan, const float* P_val, const float* Q_val,
                                int64_t m, int64_t n, int32_t r, int32_t d, hipStream_t st) {
-    const int64_t work = (int64_t)plan_max_rows(n, r, d) * kWave + m * d;
+    const int64_t work = (int64_t)plan_max_rows(n, r, d) * kWave / 4 + (int64_t)plan_max_steps(n, r, d) * kTileCols + (m * d + 3) / 4;
     const unsigned blocks = (unsigned)std::min<int64_t>((work + 255) / 256, 2048);
     hipLaunchKernelGGL(k_plan_refresh, dim3(blocks), dim3(256), 0, st, plan, P_val, Q_val, (int)m, (int)n, (int)r, (int)d);
     return hipGetLastError();
@@ -71,6 +98,8 @@ struct BuildScratch {
     int32_t*  seg_lo;      // [chunk][slot][512]: first entry (of sorted_q) of the list thread t walks
     int32_t*  seg_n;       // ... and its length
     int32_t*  p_shift;     // [tile of P][r]: position of an entry in p_ent less its position in its tile
+    int32_t*  by_len_lo;   // [chunk][kMaxSlots * 512]: first entry (of sorted_q) of the lists in the order of their length, longest first
+    int32_t*  by_len_n;    // ... and their length
 };
 constexpr int kSubTiles = 8;                       // workgroups that share a tile in k_plan_sort
 constexpr int kThreadsSort = 1024;
@@ -88,6 +117,8 @@ static size_t build_scratch(uint8_t* base, int64_t m, int64_t n, int32_t r, int3
     s.seg_lo = reinterpret_cast<int32_t*>(take(nchunks * kMaxSlots * kThreadsGQ * 4));
     s.seg_n = reinterpret_cast<int32_t*>(take(nchunks * kMaxSlots * kThreadsGQ * 4));
     s.p_shift = reinterpret_cast<int32_t*>(take(ptiles * (size_t)r * 4));
+    s.by_len_lo = reinterpret_cast<int32_t*>(take(nchunks * kMaxSlots * kThreadsGQ * 4));
+    s.by_len_n = reinterpret_cast<int32_t*>(take(nchunks * kMaxSlots * kThreadsGQ * 4));
     if (out) *out = s;
     return o;
 }
@@ -136,7 +167,7 @@ __global__ __launch_bounds__(kThreadsSort) void k_plan_sort(uint8_t* __restrict_
         const size_t rows_end = L.off_q_rows + (size_t)max_rows * kWave * sizeof(uint2), src_end = L.off_q_src + (size_t)max_rows * kWave * 4;
         const size_t np = (size_t)m * d;
         const size_t lo[] = {0, rows_end, L.off_p_ent + np * sizeof(uint2), src_end, L.off_p_src + np * 4};
-        const size_t hi[] = {L.off_q_rows, L.off_p_ent, L.off_q_src, L.off_p_src, L.total};
+        const size_t hi[] = {L.off_q_rows, L.off_p_ent, L.off_q_src, L.off_p_src, L.off_m_steps};
 #pragma unroll
         for (int k = 0; k < 5; ++k)
             for (size_t at = lo[k] + ((size_t)(blockIdx.x - first) * kThreadsSort + tid) * 4; at < hi[k]; at += (size_t)(gridDim.x - first) * kThreadsSort * 4)
@@ -271,8 +302,9 @@ __device__ __forceinline__ void deal_p(uint8_t* __restrict__ plan, const PlanLay
     }
 }
 
-// One workgroup of 512 threads per chunk, and one for P.  Every chunk's workgroup finds the owners of all columns (they
-// depend on all chunks) and the virtual columns, then deals its chunk's lists to the waves; the first one also writes
+// One workgroup of 512 threads per chunk, one for P, and, if there are to be tiles, one more per chunk for their tables (in the first
+// one they would be another 1.3 of then 10 us).  Every chunk's workgroup finds the owners of all columns (they
+// depend on all chunks) and the virtual columns, then deals its chunk's lists to the waves, or sorts them into tiles; the first one also writes
 // the tables and the header.  A plan that cannot be (an index outside [0, r), more lists than the lanes can carry) is
 // left without its magic, so that compress calls with this buffer fill S with NaN.
 __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ plan, PlanLayout L, BuildScratch s, int m, int n, int r, int d, int nchunks,
@@ -281,10 +313,11 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
     __shared__ int16_t s_vcol[kMaxSlots * kThreadsGQ];
     __shared__ int32_t s_vown[kMaxSlots * kThreadsGQ], s_longest[kThreadsGQ];
     __shared__ int32_t s_start[LSP_MAX_R], s_end[LSP_MAX_R];         // this chunk's lists
-    __shared__ uint32_t s_key[kThreadsGQ];
+    __shared__ uint32_t s_key[kThreadsGQ], s_all[kMaxSlots * kThreadsGQ];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if ((int)blockIdx.x == nchunks) { deal_p(plan, L, s, r, nchunks, ptiles, s_part); return; }
-    const int c = blockIdx.x;
+    const bool for_tiles = (int)blockIdx.x > nchunks;                 // this workgroup writes the chunk's tile tables, otherwise its lists'
+    const int c = for_tiles ? (int)blockIdx.x - nchunks - 1 : (int)blockIdx.x;
     int bad = 0;
     for (int k = tid; k < (nchunks + ptiles) * kSubTiles; k += kThreadsGQ) bad |= s.bad[k];
     int32_t vneed = 0;
@@ -357,7 +390,8 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
     shared = __syncthreads_or(shared);
     bad = __syncthreads_or(bad);
     const int32_t status = bad ? LSP_ERR_INDEX : V > kMaxSlots * kThreadsGQ ? LSP_ERR_SKEW : LSP_OK;
-    if (status_out && c == 0 && tid == 0) *status_out = status;
+    const bool first_one = c == 0 && !for_tiles;
+    if (status_out && first_one && tid == 0) *status_out = status;
     if (status != LSP_OK) return;                                    // the magic has been cleared with the rest of the header
     for (int v = tid; v < kMaxSlots * kThreadsGQ; v += kThreadsGQ) { s_vcol[v] = -1; s_vown[v] = 0; }
     __syncthreads();
@@ -365,7 +399,7 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
         for (int o = 0; o < s_own[b]; ++o) { s_vcol[s_first[b] + o] = (int16_t)b; s_vown[s_first[b] + o] = o; }
     __syncthreads();
     const int nslots = max(1, (V + kThreadsGQ - 1) / kThreadsGQ);
-    if (c == 0) {
+    if (first_one) {
         uint16_t* vcol = reinterpret_cast<uint16_t*>(plan + L.off_q_vcol);
         uint16_t* vcnt = reinterpret_cast<uint16_t*>(plan + L.off_q_vcnt);
         for (int v = tid; v < nslots * kThreadsGQ; v += kThreadsGQ) {
@@ -381,6 +415,9 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
             H->off_q_seg = L.off_q_seg; H->off_q_vcol = L.off_q_vcol; H->off_q_vcnt = L.off_q_vcnt; H->off_q_perm = L.off_q_perm;
             H->off_q_rows = L.off_q_rows; H->off_p_item = L.off_p_item; H->off_p_ent = L.off_p_ent; H->total_bytes = L.total;
             H->off_q_src = L.off_q_src; H->off_p_src = L.off_p_src;
+            if (gridDim.x > (unsigned)nchunks + 1) {                 // (the header has been cleared)
+                H->off_m_seg = L.off_m_seg; H->off_m_cols = L.off_m_cols; H->off_m_steps = L.off_m_steps; H->off_m_src = L.off_m_src;
+            }
         }
     }
     // which virtual column each thread walks (lists dealt to the waves by length when there is one slot)
@@ -416,17 +453,71 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
     __syncthreads();
     s_key[tid] = key;
     __syncthreads();
-    const int walked_p = kThreadsGQ - 1 - (int)(s_key[k_of_w * kWave + lane] & (kThreadsGQ - 1));
-    perm[(size_t)c * kThreadsGQ + tid] = (uint16_t)walked_p;
-    for (int slot = 0; slot < nslots; ++slot) {
-        list_of(permuted ? walked_p : slot * kThreadsGQ + tid, lo, hi);
-        const size_t at = ((size_t)c * nslots + slot) * kThreadsGQ + tid;
-        s.seg_lo[at] = lo;
-        s.seg_n[at] = hi - lo;
-        int32_t longest = hi - lo;
+    if (!for_tiles) {
+        const int walked_p = kThreadsGQ - 1 - (int)(s_key[k_of_w * kWave + lane] & (kThreadsGQ - 1));
+        perm[(size_t)c * kThreadsGQ + tid] = (uint16_t)walked_p;
+        for (int slot = 0; slot < nslots; ++slot) {
+            list_of(permuted ? walked_p : slot * kThreadsGQ + tid, lo, hi);
+            const size_t at = ((size_t)c * nslots + slot) * kThreadsGQ + tid;
+            s.seg_lo[at] = lo;
+            s.seg_n[at] = hi - lo;
+            int32_t longest = hi - lo;
+    #pragma unroll
+            for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off));
+            if (lane == 0) seg[((size_t)c * nslots + slot) * kWavesGQ + w] = (uint32_t)((longest + kSegBatch - 1) / kSegBatch * kSegBatch);
+        }
+        return;
+    }
+    // tiles of 32 lists: all lists by length.  With one slot they have just been sorted; several slots' lists are sorted here.
+    const int sorted = nslots == 1 ? kThreadsGQ : nslots == 2 ? 2 * kThreadsGQ : kMaxSlots * kThreadsGQ;
+    if (!permuted) {
+        for (int v = tid; v < sorted; v += kThreadsGQ) {
+            lo = hi = 0;
+            if (v < nslots * kThreadsGQ) list_of(v, lo, hi);
+            s_all[v] = ((uint32_t)(hi - lo) << 11) | (uint32_t)(kMaxSlots * kThreadsGQ - 1 - v);
+        }
+        for (int size = 2; size <= sorted; size <<= 1)
+            for (int step = size >> 1; step > 0; step >>= 1) {
+                __syncthreads();
+                for (int pair = tid; pair < sorted / 2; pair += kThreadsGQ) {
+                    const int i = 2 * pair - (pair & (step - 1)), j = i + step;
+                    const uint32_t x = s_all[i], y = s_all[j];
+                    if ((x < y) == ((i & size) == 0)) { s_all[i] = y; s_all[j] = x; }
+                }
+            }
+        __syncthreads();
+    }
+    auto by_len = [&](int place) -> int {                             // virtual column at a place of the sorted order
+        return permuted ? kThreadsGQ - 1 - (int)(s_key[place] & (kThreadsGQ - 1)) : kMaxSlots * kThreadsGQ - 1 - (int)(s_all[place] & (kMaxSlots * kThreadsGQ - 1));
+    };
+    auto length_at = [&](int place) -> int { return (int)(permuted ? s_key[place] >> 9 : s_all[place] >> 11); };
+    const int ntiles = (V + kTileCols - 1) / kTileCols;
+    for (int place = tid; place < ntiles * kTileCols; place += kThreadsGQ) {
+        lo = hi = 0;
+        if (place < V) list_of(by_len(place), lo, hi);
+        const size_t at = (size_t)c * kMaxSlots * kThreadsGQ + place;
+        s.by_len_lo[at] = lo;
+        s.by_len_n[at] = hi - lo;
+    }
+    uint32_t* cols = reinterpret_cast<uint32_t*>(plan + L.off_m_cols) + (size_t)c * kWavesMM * kSetCols * kWaveTiles;
+    for (int k = tid; k < kWavesMM * kSetCols * kWaveTiles; k += kThreadsGQ) {
+        const int i = k % kWaveTiles, b = k / kWaveTiles % kSetCols, wave = k / kWaveTiles / kSetCols, t = tile_of_wave(i, wave);
+        uint32_t x = 0;
+        if (t < ntiles) {
+            const int p0 = t * kTileCols + b, p1 = p0 + kSetCols;
+            x = (uint32_t)(p0 < V ? by_len(p0) : p0) | (uint32_t)(p1 < V ? by_len(p1) : p1) << 16;
+        }
+        cols[k] = x;
+    }
+    if (tid < kWavesMM) {
+        TileSeg sg{};
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off));
-        if (lane == 0) seg[((size_t)c * nslots + slot) * kWavesGQ + w] = (uint32_t)((longest + kSegBatch - 1) / kSegBatch * kSegBatch);
+        for (int i = 0; i < kWaveTiles; ++i) {
+            const int t = tile_of_wave(i, tid);
+            sg.len[i] = (uint16_t)(t < ntiles ? (length_at(t * kTileCols) + kStepEntries - 1) / kStepEntries : 0);
+            sg.steps += sg.len[i];
+        }
+        reinterpret_cast<TileSeg*>(plan + L.off_m_seg)[(size_t)c * kWavesMM + tid] = sg;   // (first_step: k_plan_rows)
     }
 }
 
@@ -444,11 +535,73 @@ __device__ __forceinline__ uint32_t stream_row(const uint32_t* __restrict__ seg,
     return (uint32_t)total + (uint32_t)w * kStreamSlack;
 }
 
+// Sum over the calling thread's share of the steps of the tiles before wave w's in chunk c (all: w = 0, c = nchunks).
+__device__ __forceinline__ int32_t steps_before(const TileSeg* __restrict__ seg, int w, int c) {
+    int32_t sum = 0;
+    for (int k = threadIdx.x; k < c * kWavesMM + w; k += kThreadsRows) sum += (int32_t)seg[k].steps;
+    return sum;
+}
+
+// The steps of a wave's tiles in one chunk, dealt to kTileParts workgroups in runs of 16.  A thread makes the four entries of one list in
+// one step.  What bounds this is the chain segment -> list -> entries -> values -> store, each link a trip to memory that another XCD
+// has just written (1 us and more), so a thread has one chain only, and the sum that says where the steps go hides behind it.
+constexpr int kTileParts = 2;
+__device__ __forceinline__ void plan_tiles(uint8_t* __restrict__ plan, const PlanLayout& L, const BuildScratch& s, const float* __restrict__ Q_val, int d, int c, int w,
+                                           int tile_part, int32_t* part) {
+    constexpr int kRun = kThreadsRows / kTileCols;
+    TileSeg* seg = reinterpret_cast<TileSeg*>(plan + L.off_m_seg);
+    uint16_t* steps_out = reinterpret_cast<uint16_t*>(plan + L.off_m_steps);
+    uint32_t* src_out = reinterpret_cast<uint32_t*>(plan + L.off_m_src);
+    const TileSeg sg = seg[(size_t)c * kWavesMM + w];
+    const int32_t sum = steps_before(seg, w, c);
+    const uint32_t* sorted = s.sorted_q + (size_t)c * kChunk * d;
+    const int bb = threadIdx.x % kTileCols, h = bb / kSetCols, b = bb % kSetCols;
+    uint32_t first = 0;
+    for (int step0 = tile_part * kRun; step0 == tile_part * kRun || step0 < (int)sg.steps; step0 += kTileParts * kRun) {
+        const int step = step0 + (int)threadIdx.x / kTileCols;
+        uint32_t src[kStepEntries] = {kNoSource, kNoSource, kNoSource, kNoSource};
+        float val[kStepEntries];
+        if (step < (int)sg.steps) {
+            int tile = 0, before = 0, end = 0;                        // before: steps of the tiles before
+#pragma unroll
+            for (int i = 0; i < kWaveTiles - 1; ++i) {
+                end += sg.len[i];
+                if (step >= end) { tile = i + 1; before = end; }
+            }
+            const size_t place = (size_t)c * kMaxSlots * kThreadsGQ + (size_t)tile_of_wave(tile, w) * kTileCols + bb;
+            const int lo = s.by_len_lo[place], n = s.by_len_n[place], e0 = (step - before) * kStepEntries;
+#pragma unroll
+            for (int k = 0; k < kStepEntries; ++k) src[k] = e0 + k < n ? sorted[lo + e0 + k] : kNoSource;
+        }
+#pragma unroll
+        for (int k = 0; k < kStepEntries; ++k) val[k] = src[k] != kNoSource ? Q_val[src[k]] : 0.0f;
+        if (step0 == tile_part * kRun) {                              // all threads are here
+            int32_t total;
+            (void)block_exclusive<kThreadsRows / kWave>(sum, part, total);
+            first = (uint32_t)total;
+            if (tile_part == 0 && threadIdx.x == 0) seg[(size_t)c * kWavesMM + w].first_step = first;
+        }
+        if (step >= (int)sg.steps) continue;
+        uint16_t parts[kStepEntries][3];
+#pragma unroll
+        for (int k = 0; k < kStepEntries; ++k) value_parts(val[k], parts[k]);
+        uint16_t* out = steps_out + (size_t)(first + step) * kWave * 8 + h * 4;                 // [lane][h][4]
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+            *reinterpret_cast<uint2*>(out + (4 * b + q) * 8) = make_uint2(parts[0][q] | (uint32_t)parts[1][q] << 16, parts[2][q] | (uint32_t)parts[3][q] << 16);
+#pragma unroll
+        for (int k = 0; k < kStepEntries; ++k)
+            out[(4 * (b / 4 * 4 + k) + 3) * 8 + b % 4] =
+                (uint16_t)(src[k] != kNoSource ? chunk_unit_offset(src[k] / (uint32_t)d - (uint32_t)c * kChunk) : (uint32_t)kChunk * 8u);
+        *reinterpret_cast<uint4*>(src_out + ((size_t)(first + step) * 2 + h) * kWave + b * 4) = make_uint4(src[0], src[1], src[2], src[3]);
+    }
+}
+
 // The interleaved rows: workgroup cs * 8 + w writes one segment, the next eight the waves' slack rows (and the header's stream
-// positions), `pblocks` the entries of P^T, the rest clears what lies behind the last row.
+// positions), `pblocks` the entries of P^T, nchunks * 16 the tiles' steps (if there are to be any), the rest clears what lies behind the last row and the last step.
 __global__ __launch_bounds__(kThreadsRows) void k_plan_rows(uint8_t* __restrict__ plan, PlanLayout L, BuildScratch s, const int32_t* __restrict__ P_idx,
                                                             const float* __restrict__ P_val, const float* __restrict__ Q_val, int m, int r, int d,
-                                                            int nchunks, int pblocks, int64_t max_rows, float* __restrict__ zero) {
+                                                            int nchunks, int pblocks, int64_t max_rows, bool with_tiles, float* __restrict__ zero) {
     PlanHeader* H = reinterpret_cast<PlanHeader*>(plan);
     if (H->magic != kPlanMagic) {
         if (zero)
@@ -464,7 +617,8 @@ __global__ __launch_bounds__(kThreadsRows) void k_plan_rows(uint8_t* __restrict_
     uint32_t* qsrc = reinterpret_cast<uint32_t*>(plan + L.off_q_src);
     const uint32_t pad = (uint32_t)kChunk * 16u;
     int blk = blockIdx.x;
-    const int segments = nchunks * kMaxSlots * kWavesGQ;
+    const int segments = nchunks * kMaxSlots * kWavesGQ, slack = kWavesGQ;
+    const int tiles = with_tiles ? nchunks * kWavesMM * kTileParts : 0;
     if (blk < segments) {
         if (blk >= ncs * kWavesGQ) return;
         const int cs = blk / kWavesGQ, w = blk % kWavesGQ, c = cs / nslots;
@@ -506,7 +660,7 @@ __global__ __launch_bounds__(kThreadsRows) void k_plan_rows(uint8_t* __restrict_
         return;
     }
     blk -= segments;
-    if (blk < kWavesGQ) {                                            // slack rows behind wave w's stream
+    if (blk < slack) {                                               // slack rows behind wave w's stream
         const uint32_t first = stream_row(seg, ncs, blk, 0, s_part), next = stream_row(seg, ncs, blk + 1, 0, s_part);
         for (int q = tid; q < kStreamSlack / 2 * kWave; q += kThreadsRows) {
             const size_t slot = ((size_t)((next - kStreamSlack) >> 1) * kWave + q) * 2;
@@ -519,7 +673,7 @@ __global__ __launch_bounds__(kThreadsRows) void k_plan_rows(uint8_t* __restrict_
         }
         return;
     }
-    blk -= kWavesGQ;
+    blk -= slack;
     if (blk < pblocks) {
         uint2* pent = reinterpret_cast<uint2*>(plan + L.off_p_ent);
         uint32_t* psrc = reinterpret_cast<uint32_t*>(plan + L.off_p_src);
@@ -534,17 +688,35 @@ __global__ __launch_bounds__(kThreadsRows) void k_plan_rows(uint8_t* __restrict_
         return;
     }
     blk -= pblocks;
-    const int zblocks = (int)gridDim.x - segments - kWavesGQ - pblocks;
-    const int64_t used = (int64_t)stream_row(seg, ncs, kWavesGQ, 0, s_part) * kWave, most = max_rows * kWave;
+    if (blk < tiles) {
+        plan_tiles(plan, L, s, Q_val, d, blk / kTileParts / kWavesMM, blk / kTileParts % kWavesMM, blk % kTileParts, s_part);
+        return;
+    }
+    blk -= tiles;
+    const int zblocks = (int)gridDim.x - segments - slack - pblocks - tiles;
+    // (both sums first: their barriers would wait for the stores)
+    int32_t steps = with_tiles ? steps_before(reinterpret_cast<const TileSeg*>(plan + L.off_m_seg), 0, nchunks) : 0;
+    const int64_t used = (int64_t)stream_row(seg, ncs, kWavesGQ, 0, s_part) * kWave, most = with_tiles ? max_rows * kWave : 0;
+    (void)block_exclusive<kThreadsRows / kWave>(steps, s_part, steps);
     for (int64_t k = used / 2 + (int64_t)blk * kThreadsRows + tid; k < most / 2; k += (int64_t)zblocks * kThreadsRows) {
         reinterpret_cast<uint4*>(rows)[k] = make_uint4(0u, 0u, 0u, 0u);
         reinterpret_cast<uint2*>(qsrc)[k] = make_uint2(0u, 0u);
+    }
+    if (!with_tiles) return;
+    if (blk == 0 && tid == 0) H->m_total_steps = (uint32_t)(steps + kStepsAhead);
+    uint4* msteps = reinterpret_cast<uint4*>(plan + L.off_m_steps);
+    uint2* msrc = reinterpret_cast<uint2*>(plan + L.off_m_src);
+    const int64_t steps_end = (int64_t)(L.off_m_src - L.off_m_steps) / 16, src_end = (int64_t)(L.total - L.off_m_src) / 8;
+    for (int64_t k = (int64_t)steps * kWave + (int64_t)blk * kThreadsRows + tid; k < steps_end; k += (int64_t)zblocks * kThreadsRows) {
+        msteps[k] = make_uint4(0u, 0u, 0u, 0u);
+        const uint32_t none = k < (int64_t)(steps + kStepsAhead) * kWave ? kNoSource : 0u;
+        if (k < src_end) msrc[k] = make_uint2(none, none);
     }
 }
 
 hipError_t launch_plan_build(const int32_t* P_idx, const float* P_val, const int32_t* Q_idx, const float* Q_val,
                              int64_t m, int64_t n, int32_t r, int32_t d, uint8_t* plan, uint8_t* workspace,
-                             int32_t* status_out, hipStream_t st, float* zero) {
+                             int32_t* status_out, hipStream_t st, bool with_tiles, float* zero) {
     BuildScratch s;
     build_scratch(workspace, m, n, r, d, &s);
     const PlanLayout L = plan_layout(m, n, r, d);
@@ -557,13 +729,15 @@ hipError_t launch_plan_build(const int32_t* P_idx, const float* P_val, const int
     hipLaunchKernelGGL(k_plan_sort, dim3((unsigned)(nchunks + ptiles) * kSubTiles + clear), dim3(kThreadsSort), lds, st, plan, L, s, P_idx, Q_idx,
                        (int)m, (int)n, (int)r, (int)d, nchunks, ptiles, max_rows);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_plan_deal, dim3((unsigned)nchunks + 1), dim3(kThreadsGQ), 0, st, plan, L, s, (int)m, (int)n, (int)r, (int)d, nchunks, ptiles,
+    hipLaunchKernelGGL(k_plan_deal, dim3((unsigned)nchunks * (with_tiles ? 2 : 1) + 1), dim3(kThreadsGQ), 0, st, plan, L, s, (int)m, (int)n, (int)r, (int)d, nchunks, ptiles,
                        plan_list_cap(r, d), status_out);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int pblocks = (int)std::min<int64_t>((m * d + kThreadsRows - 1) / kThreadsRows, 512);
-    const int zblocks = (int)std::min<int64_t>((max_rows * kWave / 2 + 4 * kThreadsRows - 1) / (4 * kThreadsRows), 512);
-    hipLaunchKernelGGL(k_plan_rows, dim3((unsigned)(nchunks * kMaxSlots * kWavesGQ + kWavesGQ + pblocks + zblocks)), dim3(kThreadsRows), 0, st, plan, L, s,
-                       P_idx, P_val, Q_val, (int)m, (int)r, (int)d, nchunks, pblocks, max_rows, zero);
+    // (a plan without tiles is used at once and never compared: nothing behind its last row is cleared)
+    const int zblocks = with_tiles ? (int)std::min<int64_t>((max_rows * kWave / 2 + 4 * kThreadsRows - 1) / (4 * kThreadsRows), 512) : 1;
+    const int segments = nchunks * kMaxSlots * kWavesGQ + kWavesGQ, tiles = with_tiles ? nchunks * kWavesMM * kTileParts : 0;
+    hipLaunchKernelGGL(k_plan_rows, dim3((unsigned)(segments + pblocks + tiles + zblocks)), dim3(kThreadsRows), 0, st, plan, L, s,
+                       P_idx, P_val, Q_val, (int)m, (int)r, (int)d, nchunks, pblocks, max_rows, with_tiles, zero);
     return hipGetLastError();
 }
 
