@@ -66,7 +66,7 @@ __device__ __forceinline__ void block_sum2(float x, float y, float2* red, float2
     }
 }
 
-// Phase 1, for d = DD in steps of AHEAD (or, with DD = 0, any d): the R * d (row of S, value) pairs of the tile go to LDS first, then every
+// Phase 1, for d = DD (or, with DD = 0, any d), AHEAD loads in flight: the R * d (row of S, value) pairs of the tile go to LDS first, then every
 // work item (row of the tile, 4 consecutive columns b) issues its 128-bit loads of S back to back, so the whole gather
 // costs few memory round trips.  A row's last quad starts at r - 4 when r is no multiple of 4: some columns are then
 // made twice, with the same result.  Us[plane][b] is a float4 over the plane's 4 rows: element (b, t) lives at float
@@ -95,8 +95,50 @@ __device__ __forceinline__ void build_u_tile(uint8_t* smem, int2* pent, const fl
         return;
     }
     const int quads = (r + 3) >> 2;
-    for (int q = threadIdx.x; q < quads * R; q += NT) {
-        const int row = q / quads, b4 = q - row * quads;            // row of the tile, column quad
+    // row of the tile and column quad of this thread's next item (a division for each item would take as long as its sums)
+    int row = (int)threadIdx.x / quads, b4 = (int)threadIdx.x - row * quads;
+    const int row_step = NT / quads, b4_step = NT - row_step * quads;
+    auto advance = [&]() {
+        row += row_step; b4 += b4_step;
+        if (b4 >= quads) { b4 -= quads; ++row; }
+    };
+    auto store = [&](int at_row, int b, const f32x4& u) {
+        float* dst = reinterpret_cast<float*>(smem + (at_row >> 2) * PS) + b * 4 + (at_row & 3);
+        dst[0] = u.x; dst[4] = u.y; dst[8] = u.z; dst[12] = u.w;
+    };
+    // d < AHEAD: several items at a time, while there are more than one for every thread (the step of the MLP pair, fp16, d = 4: 75.7 us one by
+    // one, now 75.0; also where a thread has one item only: the attention matrices 22.2, now 22.0, with two 22.6)
+    if constexpr (DD > 0 && DD < AHEAD) {
+        constexpr int ITEMS = AHEAD / DD;
+        for (int left = quads * R; left > NT; left -= ITEMS * NT) {
+            f32x4 x[ITEMS][DD];
+            float v[ITEMS][DD];
+            int at[ITEMS], b[ITEMS];
+#pragma unroll
+            for (int u = 0; u < ITEMS; ++u) {
+                at[u] = min(row, R - 1);                             // past the last item: some of the last row once more
+                b[u] = min(b4 * 4, r - 4);
+                advance();
+#pragma unroll
+                for (int k = 0; k < DD; ++k) {
+                    const int2 e = pent[at[u] * DD + k];
+                    v[u][k] = __int_as_float(e.y);
+                    x[u][k] = *reinterpret_cast<const loose*>(S + (int64_t)e.x * r + b[u]);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < ITEMS; ++u) {
+                f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int k = 0; k < DD; ++k) {
+                    sum.x = fmaf(v[u][k], x[u][k].x, sum.x); sum.y = fmaf(v[u][k], x[u][k].y, sum.y);
+                    sum.z = fmaf(v[u][k], x[u][k].z, sum.z); sum.w = fmaf(v[u][k], x[u][k].w, sum.w);
+                }
+                store(at[u], b[u], sum);
+            }
+        }
+    }
+    for (; row < R; advance()) {
         const int b = min(b4 * 4, r - 4);
         f32x4 u = {0.0f, 0.0f, 0.0f, 0.0f};
         auto add = [&](int k0, auto count) {
@@ -113,15 +155,14 @@ __device__ __forceinline__ void build_u_tile(uint8_t* smem, int2* pent, const fl
         };
         if constexpr (DD > 0) {
 #pragma unroll
-            for (int k = 0; k < DD; k += AHEAD) add(k, std::integral_constant<int, AHEAD>{});
+            for (int k = 0; k < DD; k += min(DD, AHEAD)) add(k, std::integral_constant<int, (DD < AHEAD ? DD : AHEAD)>{});
         } else {
             int k = 0;
             for (; k + 8 <= d; k += 8) add(k, std::integral_constant<int, 8>{});
             for (; k + 4 <= d; k += 4) add(k, std::integral_constant<int, 4>{});
             for (; k < d; ++k) add(k, std::integral_constant<int, 1>{});
         }
-        float* dst = reinterpret_cast<float*>(smem + (row >> 2) * PS) + b * 4 + (row & 3);
-        dst[0] = u.x; dst[4] = u.y; dst[8] = u.z; dst[12] = u.w;
+        store(row, b, u);
     }
 }
 
@@ -278,7 +319,7 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
 #pragma unroll
     for (int t = 0; t < R; ++t) load_w(t, col);                     // in flight while the U tile is built
     load_q(col);
-    build_u_tile<RG, DD, (DD > 4 && D::size == 4 ? 4 : DD > 8 ? 8 : DD), PS, NT>(smem, pent, S, P_idx, P_val, i0, m, r, DD);
+    build_u_tile<RG, DD, (D::size == 4 && (RG > 2 || DD == 8) ? 4 : 8), PS, NT>(smem, pent, S, P_idx, P_val, i0, m, r, DD);
     __syncthreads();
     for (int p = 1; p < npass; ++p) {
         const int next = pass_col(p);
