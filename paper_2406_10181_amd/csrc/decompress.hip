@@ -95,19 +95,32 @@ __device__ __forceinline__ void build_u_tile(uint8_t* smem, int2* pent, const fl
         return;
     }
     const int quads = (r + 3) >> 2;
-    // row of the tile and column quad of this thread's next item (a division for each item would take as long as its sums)
-    int row = (int)threadIdx.x / quads, b4 = (int)threadIdx.x - row * quads;
-    const int row_step = NT / quads, b4_step = NT - row_step * quads;
+    // Row of the tile and column quad of this thread's next item (a division for each item would take as long as its sums).
+    // Beyond r = 1024 S does not fit the L2 of an XCD (4 MB), and row by row most of its rows come from further away each time: then the waves
+    // take one stripe of 64 quads of all rows after the other, as all workgroups do at about the same time, so that a stripe (2 MB at r = 2048) is
+    // shared in L2 (4096 x 4096, r = 2048, d = 8, bf16: 47.7 -> 44.9 us; r = 1536, d = 16, fp16, 1000 x 2048: 24.5 -> 24.0).  Not where the
+    // last stripe would leave more than an eighth of the lanes idle (r = 1100: 32.4, with stripes 32.7); at r = 1024 and below it is even.
+    constexpr int WAVES = NT / kWave;
+    static_assert(R % WAVES == 0, "every wave has the same number of rows of a stripe");
+    const bool stripes = r > 1024 && (quads + kWave - 1) / kWave * kWave * 8 <= quads * 9;
+    const int row0 = stripes ? (int)threadIdx.x / kWave : (int)threadIdx.x / quads;
+    int row = row0, b4 = stripes ? (int)threadIdx.x % kWave : (int)threadIdx.x - row0 * quads;
+    const int row_step = stripes ? WAVES : NT / quads, b4_step = stripes ? 0 : NT - NT / quads * quads;
     auto advance = [&]() {
         row += row_step; b4 += b4_step;
-        if (b4 >= quads) { b4 -= quads; ++row; }
+        if (stripes) {
+            if (row >= R) {
+                row = row0; b4 += kWave;
+                if (b4 >= quads) { row = R; b4 = quads; }
+            }
+        } else if (b4 >= quads) { b4 -= quads; ++row; }
     };
     auto store = [&](int at_row, int b, const f32x4& u) {
         float* dst = reinterpret_cast<float*>(smem + (at_row >> 2) * PS) + b * 4 + (at_row & 3);
         dst[0] = u.x; dst[4] = u.y; dst[8] = u.z; dst[12] = u.w;
     };
     // d < AHEAD: several items at a time, while there are more than one for every thread (the step of the MLP pair, fp16, d = 4: 75.7 us one by
-    // one, now 75.0; also where a thread has one item only: the attention matrices 22.2, now 22.0, with two 22.6)
+    // one, now 75.0; where a thread has one item only it would be work for nothing: the attention matrices 22.1, with two items 22.6)
     if constexpr (DD > 0 && DD < AHEAD) {
         constexpr int ITEMS = AHEAD / DD;
         for (int left = quads * R; left > NT; left -= ITEMS * NT) {

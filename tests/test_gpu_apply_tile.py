@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("m,r", [
     (13, 9), (13, 255), (13, 256), (13, 257), (13, 514), (13, 1021),     # 8 rows: up to 256 columns there is one item a thread
     (2069, 9), (2069, 128), (2069, 130), (2069, 384), (2069, 511),      # 16 rows: up to 128 columns
+    (13, 1025), (13, 1100), (13, 1400), (13, 2047), (13, 2048), (2069, 1536),   # row by row, or in stripes of 256 columns
 ])
 def test_apply_with_few_and_many_items_a_thread(m, r, d, dtype):
     import gpu_util as gu
