@@ -360,7 +360,7 @@ def main():
                     "decompress_GB/s": round(dbytes / (ms_gdeco * 1e-3) / 1e9, 1)},
         # dominant by GPU time: the two kernels of one grouped compress call (seven matrices), timed
         # together (one API call) on one stream
-        "roofline": {"kernel": "k_compress_gq<bf16> + k_compress_pt8 (one lsp_compress_planned_grouped call, 7 matrices)",
+        "roofline": {"kernel": "k_compress_mm + k_compress_pt8 (one lsp_compress_planned_grouped call, 7 matrices)",
                      "bound": "hbm", "achieved": round(cbytes / (ms_gcomp1 * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(cbytes / (ms_gcomp1 * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                      "traffic": traffic_gc, "traffic_source": "profiles/traffic_compress_cfg4.json (rocprofv3 --pmc runs, not live)",
