@@ -102,7 +102,8 @@ __device__ __forceinline__ void build_u_tile(uint8_t* smem, int2* pent, const fl
     // last stripe would leave more than an eighth of the lanes idle (r = 1100: 32.4, with stripes 32.7); at r = 1024 and below it is even.
     constexpr int WAVES = NT / kWave;
     static_assert(R % WAVES == 0, "every wave has the same number of rows of a stripe");
-    const bool stripes = r > 1024 && (quads + kWave - 1) / kWave * kWave * 8 <= quads * 9;
+    // (PS: so the rest has no code for it)
+    const bool stripes = PS > 16384 && r > 1024 && (quads + kWave - 1) / kWave * kWave * 8 <= quads * 9;
     const int row0 = stripes ? (int)threadIdx.x / kWave : (int)threadIdx.x / quads;
     int row = row0, b4 = stripes ? (int)threadIdx.x % kWave : (int)threadIdx.x - row0 * quads;
     const int row_step = stripes ? WAVES : NT / quads, b4_step = stripes ? 0 : NT - NT / quads * quads;
