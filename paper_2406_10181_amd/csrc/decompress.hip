@@ -106,7 +106,8 @@ __device__ __forceinline__ void build_u_tile(uint8_t* smem, int2* pent, const fl
     const bool stripes = PS > 16384 && r > 1024 && (quads + kWave - 1) / kWave * kWave * 8 <= quads * 9;
     const int row0 = stripes ? (int)threadIdx.x / kWave : (int)threadIdx.x / quads;
     int row = row0, b4 = stripes ? (int)threadIdx.x % kWave : (int)threadIdx.x - row0 * quads;
-    const int row_step = stripes ? WAVES : NT / quads, b4_step = stripes ? 0 : NT - NT / quads * quads;
+    int row_step = stripes ? WAVES : R, b4_step = 0;                 // (one item a thread: no second division)
+    if (!stripes && quads * R > NT) { row_step = NT / quads; b4_step = NT - row_step * quads; }
     auto advance = [&]() {
         row += row_step; b4 += b4_step;
         if (stripes) {
