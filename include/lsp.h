@@ -207,8 +207,8 @@ int lsp_decompress_apply(void* W, const float* S,
  * Problems of a group run concurrently: every item needs its own S and its own workspace
  * (LSP_ERR_WORKSPACE otherwise), and a W may appear only once (LSP_ERR_SHAPE).  Errors are
  * those of the single calls; on any error nothing is enqueued.  The kernel variant is one that all
- * problems can use: an n that is no multiple of 4 (compress) or odd (apply) takes the whole group to the
- * variant for such rows.
+ * problems can use: an n that is no multiple of 4 (compress; bf16: of 8) or odd (apply) takes the whole group
+ * to the variant for such rows (which gives the same results).
  */
 typedef struct {
     const void* G;            /* device, m*n elements of `dtype` */

@@ -1,7 +1,7 @@
 // Compress: S = P^T G Q  (Alg. 1, compress step; Alg. 3, projected gradient of a layer).
 //
 // Two kernels per call, both gather-form and free of global atomics in the common case:
-//   A  T = G Q     (fp16 and fp32, and some bf16; most bf16: compress_mm.hip)
+//   A  T = G Q     (fp16, fp32 and raw calls; bf16 with a kept plan: compress_mm.hip)
 //                  one workgroup per block of 8 rows of G (4 of fp32); G is streamed once from HBM in
 //                  chunks of kChunk columns and staged in LDS transposed, as it is stored, one 16-byte
 //                  unit per column, so one 128-bit LDS read serves all rows of the block; each
@@ -12,8 +12,9 @@
 //   B  S = P^T T   one wave per piece of a row of P^T and 1/8 of the columns; reads rows of T.
 // The path streams G once.  Kernel A is nearest to the vector ALUs' issue rate (8 widenings and 8 FMAs per pair and 8 rows
 // of 16-bit storage), not to HBM: the vector ALUs issue in 67 % of the cycles, the LDS works 45 %, and L2 hands out the plan once per
-// block of 8 rows; the waves (3.3 a SIMD, 4 fit) wait for data 42 % of their time.  For bf16 the matrix cores take the sums over
-// (compress_mm.hip); fp16's exponents do not reach far enough for exact parts of an fp32 value, and fp32 has no such instruction.
+// block of 8 rows; the waves (3.3 a SIMD, 4 fit) wait for data 42 % of their time (bf16, the matrices of a 6.7B-style layer).  For bf16 with a
+// kept plan the matrix cores take the sums over (compress_mm.hip).  For fp16 they do not yet: three fp16 parts of an fp32 value are exact only if each has
+// a power of two of its own (in a column of its own that is possible) and the values lie within 2^29 of the largest.  fp32 has no such instruction.
 
 #include "compress_common.h"
 
@@ -143,7 +144,7 @@ static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, const RawCal
     switch (dtype) {
         case LSP_F32:  return launch_gq_f32(g, r, d, raw, st);
         case LSP_F16:  return launch_gq_f16(g, r, d, raw, st);
-        default:       return raw.status || !mm_bf16_suits(g, r) ? launch_gq_bf16(g, r, d, raw, st) : launch_mm_bf16(g, r, d, st);
+        default:       return raw.status ? launch_gq_bf16(g, r, d, raw, st) : launch_mm_bf16(g, r, d, st);   // (plans of raw calls have no tiles)
     }
 }
 

@@ -126,7 +126,6 @@ __device__ __forceinline__ void swap_owner(uint8_t* area, float (&acc)[R], uint3
 hipError_t launch_gq_bf16(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st);
 hipError_t launch_gq_f16(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st);
 hipError_t launch_gq_f32(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st);
-bool mm_bf16_suits(const CompressGroup& g, int32_t r);       // whether kernel A of compress_mm.hip is the better one for a call that is not raw
-hipError_t launch_mm_bf16(CompressGroup& g, int32_t r, int32_t d, hipStream_t st);
+hipError_t launch_mm_bf16(CompressGroup& g, int32_t r, int32_t d, hipStream_t st);   // kept plans (compress_mm.hip)
 
 }  // namespace lsp

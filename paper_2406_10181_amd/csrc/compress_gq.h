@@ -482,7 +482,8 @@ static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, const RawCal
     bool whole = true;
     share_blocks<kRowsGQ<D>>(g);
     for (int p = 0; p < g.count; ++p) whole = whole && g.n[p] % 4 == 0;
-    if (!raw.status) return whole ? launch_gq<D, true, false>(g, r, d, raw, st) : launch_gq<D, false, false>(g, r, d, raw, st);
+    if constexpr (!std::is_same_v<D, BF16>)                           // bf16 with a kept plan: compress_mm.hip
+        if (!raw.status) return whole ? launch_gq<D, true, false>(g, r, d, raw, st) : launch_gq<D, false, false>(g, r, d, raw, st);
     return whole ? launch_gq<D, true, true>(g, r, d, raw, st) : launch_gq<D, false, true>(g, r, d, raw, st);
 }
 }  // namespace lsp

@@ -1,6 +1,5 @@
-// Kernel A of the compress path for bf16 storage (see compress_gq.h) where that of compress_mm.hip is not better: some row counts
-// (mm_bf16_suits), and calls on raw projectors, whose plan is used once and is built sooner without the tiles (4096 x 4096, r = 512, d = 8,
-// raw: 50.6 us, with tiles and that kernel 55.2).
+// Kernel A of the compress path for bf16 storage (see compress_gq.h) in calls on raw projectors, whose plan is used once and is built sooner without
+// the tiles that compress_mm.hip walks (4096 x 4096, r = 512, d = 8, raw: 50.6 us, with tiles and that kernel 55.2).
 #include "compress_gq.h"
 
 namespace lsp {

@@ -492,16 +492,13 @@ static bool narrow_blocks(const CompressGroup& g, int32_t r) {
     return r > 1024 || blocks <= kResidentMM;
 }
 
-// The blocks of 16 go in rounds of one for every CU, and where the last of them is nearly empty k_compress_gq with its finer grain (8 rows, two
-// workgroups a CU) is better: n = 4096, r = 512, d = 8, rows 4200 38.3 us and there 35.2, 5000 39.2 and 36.9, 6000 (73 % of two rounds) 40.8 and
-// 39.0, 8192 44.6 and 46.3, 11008 (90 % of three) 59.3 and 61.9; within the first round it is not (2100 rows 23.0 and 23.7).
-bool mm_bf16_suits(const CompressGroup& g, int32_t r) {
-    int64_t blocks = 0;
-    for (int p = 0; p < g.count; ++p) blocks += (g.m[p] + 15) / 16;
-    const int64_t rounds = (blocks + kResidentMM - 1) / kResidentMM;
-    return narrow_blocks(g, r) || rounds == 1 || 5 * blocks >= 4 * rounds * kResidentMM;
-}
-
+// Every bf16 call with a kept plan comes here, whatever its rows: the sums of a row do not depend on the blocks it is in, so a matrix has the same
+// result alone and in any group, which a second kernel with sums in another order would end.  The blocks of 16 go in rounds of one for every CU, and
+// where the last round is nearly empty, k_compress_gq with its finer grain (8 rows, two workgroups a CU) is up to 12 % faster if the lists are
+// long and even, and 10 to 30 % slower otherwise (us with kernel B, here and there; single matrices, r = 512, d = 8 unless said otherwise):
+//   5120 x 4096  38.9 and 36.9, zipf 54.1 and 63.7, r = 256, d = 4 28.2 and 32.0, r = 1024, d = 4 39.5 and 42.2
+//   5120 x 13824 89.1 and 80.4, zipf 113.7 and 118.8, r = 256, d = 4 59.2 and 72.5, r = 1024, d = 4 82.9 and 83.1
+//   6500 x 4096  40.1 and 41.0; 9000 x 2048 38.5 and 38.6; seven matrices of 5120 and 13824 rows and columns 292 and 319
 hipError_t launch_mm_bf16(CompressGroup& g, int32_t r, int32_t d, hipStream_t st) {
     return narrow_blocks(g, r) ? launch_mm_rows<2>(g, r, d, st) : launch_mm_rows<4>(g, r, d, st);
 }

@@ -8,14 +8,19 @@ import lsp_synth as syn
 pytestmark = pytest.mark.gpu
 
 
-def _problem(m, n, r, seed, dist):
-    """One entry a row; row i of P names column i % r, with value one."""
+def _problem(m, n, r, seed, dist, d=1):
+    """d entries a row of Q; row i of P names column i % r, with value one (and zeros in further entries).  dist "hot": nearly all entries of a
+    chunk are in one column, another one in every chunk, so that there are many more lists than columns."""
     rng = np.random.default_rng(seed)
-    Q_idx, Q_val = syn.ell_projector(n, r, 1, rng, dist)
-    P_idx = (np.arange(m, dtype=np.int32) % r)[:, None].copy()
-    P_val = np.ones((m, 1), np.float32)
+    Q_idx, Q_val = syn.ell_projector(n, r, d, rng, "uniform" if dist == "hot" else dist)
+    if dist == "hot":
+        rows = np.flatnonzero(rng.random(n) < 0.95)
+        Q_idx[rows] = (rows // 2048 % r)[:, None]
+    P_idx = np.repeat((np.arange(m, dtype=np.int32) % r)[:, None], d, axis=1).copy()
+    P_val = np.zeros((m, d), np.float32)
+    P_val[:, 0] = 1.0
     G = syn.to_storage(rng.standard_normal((m, n)).astype(np.float32), "bf16")
-    return syn.Problem("mm", m, n, r, 1, "bf16", G, G.copy(), P_idx, P_val, Q_idx, Q_val, np.zeros((r, r), np.float32))
+    return syn.Problem("mm", m, n, r, d, "bf16", G, G.copy(), P_idx, P_val, Q_idx, Q_val, np.zeros((r, r), np.float32))
 
 
 def _exact(pb):
@@ -23,13 +28,14 @@ def _exact(pb):
     G = syn.storage_to_f64(pb.G, "bf16")
     T, A = np.zeros((pb.m, pb.r)), np.zeros((pb.m, pb.r))
     with np.errstate(invalid="ignore"):
-        GQ = G * pb.Q_val[:, 0].astype(np.float64)
-        np.add.at(T.T, pb.Q_idx[:, 0], GQ.T)
-        np.add.at(A.T, pb.Q_idx[:, 0], np.abs(GQ).T)
+        for k in range(pb.d):
+            GQ = G * pb.Q_val[:, k].astype(np.float64)
+            np.add.at(T.T, pb.Q_idx[:, k], GQ.T)
+            np.add.at(A.T, pb.Q_idx[:, k], np.abs(GQ).T)
         S, B = np.zeros((pb.r, pb.r)), np.zeros((pb.r, pb.r))
         np.add.at(S, pb.P_idx[:, 0], T)
         np.add.at(B, pb.P_idx[:, 0], A)
-    terms = np.bincount(pb.Q_idx[:, 0]).max() + np.bincount(pb.P_idx[:, 0]).max()
+    terms = np.bincount(pb.Q_idx.reshape(-1)).max() + np.bincount(pb.P_idx.reshape(-1)).max()
     return S, B, int(terms)
 
 
@@ -41,9 +47,10 @@ SHAPES = [
     (40, 2500, 2048, "uniform"), (50, 4096, 20, "zipf"),          # all tiles of a wave; shared columns
     (2048, 264, 48, "uniform"), (2049, 264, 48, "zipf"),          # the last with blocks of 8 rows, the first with blocks of 16
     (4081, 520, 64, "uniform"), (4096, 2056, 96, "zipf"),         # one 16-row block a workgroup
-    (4097, 300, 33, "uniform"), (6544, 67, 33, "uniform"),        # k_compress_gq takes these: the last round is too empty
+    (4097, 300, 33, "uniform"), (6544, 67, 33, "uniform"),        # a last round of one block, and a little over half full
     (6545, 67, 33, "uniform"), (8192, 264, 48, "zipf"),           # two 16-row blocks a workgroup, not for all and for all; n % 8 != 0
-    (4096, 300, 1024, "uniform"), (4096, 2100, 1024, "zipf"),     # the most columns 16-row blocks are used for; more sums than the LDS holds
+    (4096, 300, 1024, "uniform"), (4096, 2100, 1024, "zipf"),     # the most columns 16-row blocks are used for; some of them shared
+    (2061, 10245, 1024, "hot"),                                   # more than 1535 lists: the sums of 16 rows do not fit the LDS, blocks go in halves
 ]
 
 
@@ -75,3 +82,63 @@ def test_bf16_compress_with_infinities_and_nan(m, n, r, dist):
     finite = np.isfinite(S)
     assert np.array_equal(np.isfinite(got), finite)
     assert (np.abs(got[finite] - S[finite]) <= (terms + 4) * 2.0 ** -24 * B[finite] + 1e-35).all()
+
+
+@pytest.mark.parametrize("m,n,r,d,dist", [(2049, 520, 64, 8, "uniform"), (33, 4103, 512, 16, "zipf"), (50, 2500, 2048, 4, "uniform"), (4100, 264, 96, 3, "zipf")])
+def test_bf16_compress_with_several_entries_a_row(m, n, r, d, dist):
+    import gpu_util as gu
+    pb = _problem(m, n, r, 7200 + m + n + r, dist, d)
+    print(f"[case] mm m={m} n={n} r={r} d={d} {dist}", flush=True)
+    S, B, terms = _exact(pb)
+    got = gu.DeviceProblem(pb).compress_planned().astype(np.float64)
+    assert (np.abs(got - S) <= (terms + 4) * 2.0 ** -24 * B + 1e-35).all(), (np.abs(got - S) / (B + 1e-30)).max() * 2 ** 24
+
+
+def _group(dps, r, d, plans=None):
+    """S of a grouped call, each filled with ones before."""
+    import torch
+    import paper_2406_10181_amd as L
+    for dp in dps:
+        dp.S.fill_(1.0)
+    items = L.compress_items([(dp.G, plans[k] if plans and k in plans else dp.plan, dp.S, dp.ws, dp.ws_bytes, dp.pb.m, dp.pb.n) for k, dp in enumerate(dps)])
+    L.lsp_compress_planned_grouped(items, len(dps), r, d, 2, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    return [dp.S.cpu().numpy() for dp in dps]
+
+
+@pytest.mark.parametrize("shapes,r,d", [
+    ([(5120, 264, "uniform")] * 2, 48, 1),                                           # the second round of the 16-row blocks: a quarter full, and half
+    ([(5120, 2056, "zipf"), (2112, 264, "uniform"), (2112, 2050, "uniform")], 512, 8),   # a round of 8-row blocks each; n % 8 != 0 for one
+    ([(40, 2500, "uniform"), (2048, 264, "uniform"), (4096, 300, "uniform")], 1024, 2),   # 8-row blocks alone, 16-row blocks together
+    ([(300, 520, "uniform"), (1001, 10240, "hot"), (4096, 264, "uniform")], 1024, 1),    # sums of 16 rows that fit the LDS, and some that go in halves
+    ([(300, 520, "uniform"), (17, 4103, "uniform")], 2048, 3),                       # 8-row blocks throughout
+])
+def test_bf16_compress_in_a_group_is_that_of_the_single_calls(shapes, r, d):
+    import gpu_util as gu
+    print(f"[case] mm group {shapes} r={r} d={d}", flush=True)
+    dps = [gu.DeviceProblem(_problem(m, n, r, 7300 + k + m + n, dist, d)) for k, (m, n, dist) in enumerate(shapes)]
+    singles = [dp.compress_planned() for dp in dps]
+    for single, grouped in zip(singles, _group(dps, r, d)):
+        assert np.isfinite(single).all() and np.array_equal(single, grouped), np.abs(single - grouped).max()
+
+
+@pytest.mark.parametrize("foreign", [0, 1, 2])
+def test_bf16_compress_with_a_foreign_plan_in_a_group(foreign):
+    """Its S is NaN and its workspace untouched; the others are served as if it were not there."""
+    import torch
+    import gpu_util as gu
+    r, d = 64, 2
+    shapes = [(300, 4100), (4096, 520), (2049, 264)]
+    print(f"[case] mm group, plan {foreign} is foreign", flush=True)
+    dps = [gu.DeviceProblem(_problem(m, n, r, 7400 + m, "uniform", d)) for m, n in shapes]
+    singles = [dp.compress_planned() for dp in dps]
+    m, n = shapes[foreign]
+    other = gu.DeviceProblem(_problem(m + 8, n, r, 7500, "uniform", d))
+    other.build_plan()
+    dps[foreign].ws.fill_(0x5A)
+    grouped = _group(dps, r, d, {foreign: other.plan})
+    for k in range(3):
+        if k == foreign:
+            assert np.isnan(grouped[k]).all() and bool((dps[k].ws == 0x5A).all())
+        else:
+            assert np.array_equal(singles[k], grouped[k])
