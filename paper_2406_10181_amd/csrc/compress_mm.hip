@@ -3,7 +3,7 @@
 // A column of T is a sum over a list of (column of G, value), and the lists share nothing, so this is no matrix product.  But
 // v_mfma_f32_4x4x4_16b_bf16 is 16 independent products [4 x 4] [4 x 4], and each can serve a list: its A operand is four columns of G
 // from the list (4 rows; gathered by transposing LDS reads, which hand a lane one row's four values), its B operand their four values
-// as three bf16 parts that add up to the fp32 value exactly (in three of its columns).  So a product of 16 bits by 24 is taken exactly, and
+// as three bf16 parts that add up, each times its power of two, to the fp32 value exactly (in three of its columns).  So a product of 16 bits by 24 is taken exactly, and
 // the three sums are added at the end: the error against 64 bits is 0.3 to 0.6 of that of a chain of fp32 FMAs.  An instruction does
 // 4 rows x 64 entries; the vector ALUs took 8 widenings and FMAs for 8 rows x 64 entries.
 //
@@ -153,6 +153,13 @@ template <int R> __device__ __forceinline__ uint8_t* piece_of(uint8_t* sums, uin
     return sums + v * (R * 4) + ((x + v / (256 / (R * 4))) & 3) * R;
 }
 
+// The sum of a list from the sums over the parts of its values.  (Not two FMAs: with those the 16-row form spilled 16 registers, and
+// seven matrices of a 6.7B-style layer took 50 us more.)
+__device__ __forceinline__ float sum_of_parts(float first, float second, float third) {
+    const float rest = fmaf(third, 1.0f / (1 << (kPartShift[2] - kPartShift[1])), second);
+    return __builtin_amdgcn_ldexpf(rest, -kPartShift[1]) + first;
+}
+
 // A wave's tiles of one staged chunk.
 template <int NP>
 __device__ __forceinline__ void walk_tiles(WaveChunk& w, uint8_t* sums, bool first_chunk, int mytiles, int lane) {
@@ -191,7 +198,7 @@ __device__ __forceinline__ void walk_tiles(WaveChunk& w, uint8_t* sums, bool fir
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
-                keep[h][p] = (X[p][2] + X[p][1]) + X[p][0];
+                keep[h][p] = sum_of_parts(X[p][0], X[p][1], X[p][2]);
                 odd += fabsf(keep[h][p]);
             }
         }
@@ -205,7 +212,7 @@ __device__ __forceinline__ void walk_tiles(WaveChunk& w, uint8_t* sums, bool fir
                     float own, head;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const float y = D[h][p][q], first = quad_lane<0>(y), sum = (quad_lane<2>(y) + quad_lane<1>(y)) + first;
+                        const float y = D[h][p][q], first = quad_lane<0>(y), sum = sum_of_parts(first, quad_lane<1>(y), quad_lane<2>(y));
                         own = q == 0 || part == q ? sum : own;
                         head = q == 0 || part == q ? first : head;
                     }
@@ -332,7 +339,7 @@ template <int NP, bool HALVES> struct BlockWalk {
         for (block = from; block < blocks; block += gridDim.x) {
             pr = problem_of(block);
             H = as_const<PlanHeader>(pr.plan);
-            const bool planned = plan_matches(H, pr.m, pr.n, r, d) && H->off_m_steps != 0;
+            const bool planned = plan_matches(H, pr.m, pr.n, r, d) && H->m_format == kTileFormat;
             visit(pr, H, planned);
             if (!planned) continue;
             nchunks = H->nchunks;

@@ -74,7 +74,7 @@ __host__ __device__ static inline uint32_t chunk_unit_offset(uint32_t j) { retur
 // tiles of 32; they are dealt to 8 waves in rounds, some backwards (tile_of_wave), so that the waves get about the same number of
 // steps.  A step is four entries of every list of a tile: 64 x 16 bytes, the first 8 for lists 0..15 and the others for 16..31.
 // In each half, with 4-lane group b = lane / 4 and s = lane % 4:
-//   s < 3    part s of the values of list b's four entries (v = v0 + v1 + v2 exactly, bf16 each: the B operand as it is)
+//   s < 3    part s of the values of list b's four entries (value_parts, bf16 each: the B operand as it is)
 //   s = 3    the LDS offsets of entry b % 4 of the four lists b / 4 * 4 .. + 3 (the transposing LDS read takes the entries of
 //            a list from lanes 4 apart)
 // A list shorter than the tile's longest is filled up with zero values at the always-zero unit.
@@ -113,7 +113,7 @@ struct PlanHeader {            // first 256 bytes of the plan buffer
     uint64_t off_m_steps;      // uint4[m_total_steps][64]
     uint64_t off_m_src;        // uint32[m_total_steps][2][16][4]     flat ELL position of entry k of list 16 h + b; kNoSource: none
     uint32_t m_total_steps;    // kStepsAhead readable ones behind the last included
-    uint32_t pad2;
+    uint32_t m_format;         // kTileFormat if there are tiles
 };
 static_assert(sizeof(PlanHeader) == 216, "PlanHeader layout");
 constexpr uint32_t kPlanMagic = 0x4C535038u;   // "LSP8"
@@ -129,8 +129,12 @@ static_assert(sizeof(TileSeg) == 32, "one scalar load");
 // bits set: no wave is first or last in most rounds.
 __host__ __device__ static inline int tile_of_wave(int i, int w) { return kWavesMM * i + (((0x6996 >> i) & 1) ? kWavesMM - 1 - w : w); }
 
-// The three bf16 parts of a value, highest first: each takes the leading 8 significant bits of what is left, so they add up to
-// v exactly (but for bits below 2^-133).  An infinity or NaN is its first part.
+// The three bf16 parts of a value, highest first: v = part[0] + 2^-kPartShift[1] part[1] + 2^-kPartShift[2] part[2].  Each takes the leading 8 significant
+// bits of what is left, which is scaled by a power of two so that it is about as large as v, and no larger (so products and sums of a part
+// overflow only where those of v could): exact for |v| >= 2^-125, and for smaller ones but for a last bit of 2^-149.  (Not scaled, the parts of
+// values below 2^-110 would lose what lies under the smallest bf16, 2^-133.)  An infinity or NaN is its first part.
+constexpr int kPartShift[3] = {0, 7, 15};
+constexpr uint32_t kTileFormat = 1;            // PlanHeader::m_format of tiles with parts of this kind
 __host__ __device__ static inline void value_parts(float v, uint16_t (&part)[3]) {
     uint32_t u;
     __builtin_memcpy(&u, &v, 4);
@@ -140,6 +144,7 @@ __host__ __device__ static inline void value_parts(float v, uint16_t (&part)[3])
         return;
     }
     for (int k = 0; k < 3; ++k) {
+        if (k > 0) v *= (float)(1 << (kPartShift[k] - kPartShift[k - 1]));
         __builtin_memcpy(&u, &v, 4);
         part[k] = (uint16_t)(u >> 16);
         u &= 0xFFFF0000u;

@@ -142,3 +142,28 @@ def test_bf16_compress_with_a_foreign_plan_in_a_group(foreign):
             assert np.isnan(grouped[k]).all() and bool((dps[k].ws == 0x5A).all())
         else:
             assert np.array_equal(singles[k], grouped[k])
+
+
+@pytest.mark.parametrize("g_exp,v_exp", [
+    (0, -100), (60, -118), (60, -124),        # values whose lower parts, as they are, would be subnormal or gone
+    (100, -132), (100, -140),                 # subnormal values
+    (-126, 60), (-133, 40),                   # gradients partly and all subnormal
+    (-126, 0), (-130, 2), (-60, -60), (-64, -75),   # sums that are subnormal in fp32, in part and all
+    (120, 0), (64, 55),                       # sums near the largest number
+])
+def test_bf16_compress_at_the_ends_of_the_exponents(g_exp, v_exp):
+    import gpu_util as gu
+    pb = _problem(40, 2500, 96, 7600, "uniform")
+    rng = np.random.default_rng(7600 - g_exp)
+    G = np.ldexp(rng.uniform(0.5, 2.0, (pb.m, pb.n)) * rng.choice([-1.0, 1.0], (pb.m, pb.n)), g_exp)
+    pb.G = syn.to_storage(G.astype(np.float32), "bf16")
+    pb.Q_val = np.ldexp(rng.uniform(0.5, 2.0, pb.Q_val.shape) * rng.choice([-1.0, 1.0], pb.Q_val.shape), v_exp).astype(np.float32)
+    print(f"[case] mm exponents {g_exp} {v_exp}", flush=True)
+    S, B, terms = _exact(pb)
+    assert np.abs(S).max() > 0 and B.max() < 2.0 ** 127
+    got = gu.DeviceProblem(pb).compress_planned().astype(np.float64)
+    # half a unit in the last place for every addition and for adding the parts, and where sums are subnormal that is 2^-150 at the least;
+    # the stored parts leave out a last bit of 2^-149 of values below 2^-125
+    lost = 2.0 ** -149 * np.abs(syn.storage_to_f64(pb.G, "bf16")).max() * terms if v_exp < -124 else 0.0
+    bound = (terms + 4) * (2.0 ** -24 * B + 2.0 ** -150) + lost
+    assert (np.abs(got - S) <= bound).all(), (np.abs(got - S) / bound).max()

@@ -333,6 +333,62 @@ def test_plan_replay_matches_dense_definition(m, n, r, d, dist):
     np.testing.assert_allclose(S, ref, rtol=0, atol=1e-10 * max(1.0, np.abs(ref).max()))
 
 
+@pytest.mark.parametrize("m,n,r,d,dist", [
+    (9, 4103, 250, 3, "uniform"),       # three chunks, the last of seven columns; a last tile of 26 lists
+    (9, 2500, 96, 8, "zipf"),           # shared columns
+    (9, 2100, 1024, 2, "zipf"),         # several slots
+    (9, 7, 3, 1, "uniform"),
+])
+def test_tiles_of_the_plan_hold_every_value_exactly_and_once(m, n, r, d, dist):
+    """The lists as the matrix instructions take them (lsp_internal.h): three bf16 parts of each value, the second to be scaled by 2^-7 and the
+    third by 2^-15, of every magnitude that fp32 has."""
+    pb = syn.make_problem("t", m, n, r, d, "bf16", seed=177 + m, index_dist=dist)
+    rng = np.random.default_rng(178 + n)
+    pb.Q_val = np.ldexp(rng.uniform(1.0, 2.0, (n, d)), rng.integers(-149, 128, (n, d))).astype(np.float32) * rng.choice([-1.0, 1.0], (n, d)).astype(np.float32)
+    pb.Q_val.reshape(-1)[:5] = [0.0, np.float32(2.0 ** -149), np.finfo(np.float32).max, -np.finfo(np.float32).tiny, np.float32(2.0 - 2.0 ** -23)]
+    buf = _build_host_plan(pb)
+    nchunks, nslots, nvcols = [int(x) for x in buf[20:32].view(np.int32)]
+    o_seg, o_cols, o_steps, o_src = [int(x) for x in buf[176:208].view(np.uint64)]
+    total = int(buf[208:212].view(np.uint32)[0])
+    seg = buf[o_seg:o_seg + nchunks * 8 * 32].view(np.uint32).reshape(nchunks, 8, 8)
+    lens = buf[o_seg:o_seg + nchunks * 8 * 32].view(np.uint16).reshape(nchunks, 8, 16)[:, :, 4:12]
+    cols = buf[o_cols:o_cols + nchunks * 8 * 16 * 8 * 2 * 2].view(np.uint16).reshape(nchunks, 8, 16, 8, 2)
+    steps = buf[o_steps:o_steps + total * 1024].view(np.uint16).reshape(total, 64, 2, 4)
+    src = buf[o_src:o_src + total * 512].view(np.uint32).reshape(total, 2, 16, 4)
+    o_vcol = int(buf[104:112].view(np.uint64)[0])
+    vcol = buf[o_vcol:o_vcol + nslots * 1024].view(np.uint16)
+    part = (steps.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    quads = np.arange(16) * 4
+    value = part[:, quads] + 2.0 ** -7 * part[:, quads + 1] + 2.0 ** -15 * part[:, quads + 2]      # [step][list b][h][entry k]
+    value = value.transpose(0, 2, 1, 3)
+    used = src != 0xFFFFFFFF
+    want = np.where(used, pb.Q_val.reshape(-1)[np.where(used, src, 0)], 0.0).astype(np.float64)
+    big = np.abs(want) >= 2.0 ** -125
+    assert np.array_equal(value[big], want[big]) and np.all(np.abs(value - want) <= 2.0 ** -149)
+    assert np.all(np.abs(part[:, quads[:, None] + np.arange(3)].transpose(0, 3, 1, 4, 2)) <= np.abs(want)[..., None] + 2.0 ** -125), "no part above its value"
+    assert sorted(src[used].tolist()) == list(range(n * d))
+    assert not used[total - 10:].any()
+    at = 0
+    for c in range(nchunks):
+        for w in range(8):
+            first, count = int(seg[c, w, 0]), int(seg[c, w, 1])
+            assert first == at and count == int(lens[c, w].sum())
+            at += count
+            tile = np.repeat(np.arange(8), lens[c, w])
+            for k in range(count):
+                for h in range(2):
+                    for b in range(16):
+                        s = src[first + k, h, b]
+                        off = np.array([steps[first + k, 4 * (b // 4 * 4 + e) + 3, h, b % 4] for e in range(4)], np.int64)
+                        on = s != 0xFFFFFFFF
+                        assert np.all(off[~on] == CHUNK * 8)
+                        if on.any():
+                            v = int(cols[c, w, b, tile[k], h])
+                            assert v < nvcols and np.all(pb.Q_idx.reshape(-1)[s[on]] == (int(vcol[v]) & 0x7FFF))
+                            assert np.array_equal([c * CHUNK + _decode_col(int(x) * 2) for x in off[on]], (s[on] // d).tolist())
+    assert at + 10 == total
+
+
 def test_plan_build_host_rejects_bad_index_and_small_buffer():
     pb = syn.make_problem("t", 16, 16, 8, 2, "f32", seed=5)
     nbytes = L.lsp_plan_bytes(16, 16, 8, 2)
