@@ -68,6 +68,31 @@ def test_device_plan_at_the_edges_of_the_sort(m, n, r, d, dist):
         assert bad.size == 0, f"{bad.size} bytes differ, first at offset {bad[:4]}"
 
 
+def test_device_plan_and_new_values_with_values_of_every_magnitude():
+    """The parts of a value on the device (build and refresh) against the host's: subnormal, large, infinite and no numbers."""
+    import torch
+    import paper_2406_10181_amd as L
+    m, n, r, d = 40, 2500, 96, 8
+    rng = np.random.default_rng(8899)
+    P_idx, P_val = syn.ell_projector(m, r, d, rng)
+    Q_idx, Q_val = syn.ell_projector(n, r, d, rng)
+    wide = (np.ldexp(rng.uniform(1.0, 2.0, (n, d)), rng.integers(-150, 128, (n, d))) * rng.choice([-1.0, 1.0], (n, d))).astype(np.float32)
+    wide.reshape(-1)[:8] = np.array([0, 0x80000000, 1, 0x7F7FFFFF, 0x7F800000, 0xFF800000, 0x7F800001, 0xFFC12345], np.uint32).view(np.float32)
+    print("[case] device plan, values of every magnitude", flush=True)
+    nb = L.lsp_plan_bytes(m, n, r, d)
+    host = np.zeros(nb, dtype=np.uint8)
+    assert L.lsp_plan_build_host(P_idx, P_val, Q_idx, wide, m, n, r, d, host, nb, check=False) == 0
+    P_idx, P_val, Q_idx, Q_val, wide = [torch.from_numpy(x).cuda() for x in (P_idx, P_val, Q_idx, Q_val, wide)]
+    stream = torch.cuda.current_stream()
+    for values in (wide, Q_val):
+        plan = torch.empty(nb, dtype=torch.uint8, device="cuda")
+        L.lsp_plan_build(P_idx, P_val, Q_idx, values, m, n, r, d, plan, nb, stream)
+        if values is Q_val:
+            L.lsp_plan_refresh_values(plan, P_val, wide, m, n, r, d, stream)
+        torch.cuda.synchronize()
+        assert np.array_equal(plan.cpu().numpy(), host)
+
+
 def test_device_plan_reports_skew_and_bad_indices():
     import torch
     import paper_2406_10181_amd as L
