@@ -302,6 +302,60 @@ __device__ __forceinline__ void deal_p(uint8_t* __restrict__ plan, const PlanLay
     }
 }
 
+// Sorts the lists of a chunk by length, longest first and equal lengths in their order, as the host's stable sort does: a stable radix sort
+// over the length, 8 bits at a time (lengths are at most `most`, hardly ever 256 or more).  Wave w has places (w per + i) 64 + lane, i < per, before and
+// after; a key is length * kLists + list.  What bounds it is the chain of barriers (seven a round).  The bitonic sorts before it had 45 stages for
+// 512 lists and 66, a barrier each, for 2048: the build for 4096 x 4096, r = 2048, d = 8 took 53 us with them.
+constexpr int kLists = kMaxSlots * kThreadsGQ, kSortBits = 8;
+__device__ __forceinline__ void sort_by_length(uint32_t (&key)[kMaxSlots], int per, int most, uint32_t* s_key, int32_t* s_count, int32_t* part) {
+    constexpr int kBins = 1 << kSortBits, kEach = kBins * kWavesGQ / kThreadsGQ;
+    static_assert(kBins * kWavesGQ % kThreadsGQ == 0, "every thread sums up the same number of counts");
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    for (int shift = 0, bits = 32 - __builtin_clz(most | 1); bits > 0; shift += kSortBits, bits -= kSortBits) {
+        const int now = min(bits, kSortBits);
+        // counts by (digit, the largest first; wave)
+        auto count_of = [&](uint32_t k) { return s_count + ((kBins - 1 - (int)((k / kLists) >> shift & (kBins - 1))) * kWavesGQ + w); };
+        for (int k = tid; k < kBins * kWavesGQ; k += kThreadsGQ) s_count[k] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kMaxSlots; ++i)
+            if (i < per) atomicAdd(count_of(key[i]), 1);
+        __syncthreads();
+        int32_t sum = 0, total;
+#pragma unroll
+        for (int k = 0; k < kEach; ++k) sum += s_count[tid * kEach + k];
+        int32_t at = block_exclusive<kWavesGQ>(sum, part, total);
+#pragma unroll
+        for (int k = 0; k < kEach; ++k) {
+            const int32_t x = s_count[tid * kEach + k];
+            s_count[tid * kEach + k] = at;
+            at += x;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kMaxSlots; ++i)
+            if (i < per) {
+                uint64_t same = ~(uint64_t)0;
+                for (int k = 0; k < now; ++k) {
+                    const bool bit = (key[i] / kLists) >> (shift + k) & 1;
+                    const uint64_t with = __ballot(bit);
+                    same &= bit ? with : ~with;
+                }
+                const int rank = __builtin_popcountll(same & (((uint64_t)1 << lane) - 1));
+                int32_t* next = count_of(key[i]);
+                const int32_t first = *next;
+                s_key[first + rank] = key[i];
+                __builtin_amdgcn_wave_barrier();
+                if (rank == 0) *next = first + __builtin_popcountll(same);
+                __builtin_amdgcn_wave_barrier();                     // the next 64 keys read what this step has left
+            }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kMaxSlots; ++i)
+            if (i < per) key[i] = s_key[(w * per + i) * kWave + lane];
+    }
+}
+
 // One workgroup of 512 threads per chunk, one for P, and, if there are to be tiles, one more per chunk for their tables (in the first
 // one they would be another 1.3 of then 10 us).  Every chunk's workgroup finds the owners of all columns (they
 // depend on all chunks) and the virtual columns, then deals its chunk's lists to the waves, or sorts them into tiles; the first one also writes
@@ -310,10 +364,11 @@ __device__ __forceinline__ void deal_p(uint8_t* __restrict__ plan, const PlanLay
 __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ plan, PlanLayout L, BuildScratch s, int m, int n, int r, int d, int nchunks,
                                                           int ptiles, int cap, int32_t* __restrict__ status_out) {
     __shared__ int32_t s_own[LSP_MAX_R], s_first[LSP_MAX_R], s_part[kWavesGQ];
-    __shared__ int16_t s_vcol[kMaxSlots * kThreadsGQ];
-    __shared__ int32_t s_vown[kMaxSlots * kThreadsGQ], s_longest[kThreadsGQ];
+    __shared__ int16_t s_vcol[kLists], s_vown[kLists];
+    __shared__ int32_t s_longest[kThreadsGQ];
     __shared__ int32_t s_start[LSP_MAX_R], s_end[LSP_MAX_R];         // this chunk's lists
-    __shared__ uint32_t s_key[kThreadsGQ], s_all[kMaxSlots * kThreadsGQ];
+    __shared__ uint32_t s_key[kLists];
+    __shared__ int32_t s_count[(1 << kSortBits) * kWavesGQ];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     if ((int)blockIdx.x == nchunks) { deal_p(plan, L, s, r, nchunks, ptiles, s_part); return; }
     const bool for_tiles = (int)blockIdx.x > nchunks;                 // this workgroup writes the chunk's tile tables, otherwise its lists'
@@ -389,14 +444,14 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
     }
     shared = __syncthreads_or(shared);
     bad = __syncthreads_or(bad);
-    const int32_t status = bad ? LSP_ERR_INDEX : V > kMaxSlots * kThreadsGQ ? LSP_ERR_SKEW : LSP_OK;
+    const int32_t status = bad ? LSP_ERR_INDEX : V > kLists ? LSP_ERR_SKEW : LSP_OK;
     const bool first_one = c == 0 && !for_tiles;
     if (status_out && first_one && tid == 0) *status_out = status;
     if (status != LSP_OK) return;                                    // the magic has been cleared with the rest of the header
-    for (int v = tid; v < kMaxSlots * kThreadsGQ; v += kThreadsGQ) { s_vcol[v] = -1; s_vown[v] = 0; }
+    for (int v = tid; v < kLists; v += kThreadsGQ) { s_vcol[v] = -1; s_vown[v] = 0; }
     __syncthreads();
     for (int b = tid; b < r; b += kThreadsGQ)
-        for (int o = 0; o < s_own[b]; ++o) { s_vcol[s_first[b] + o] = (int16_t)b; s_vown[s_first[b] + o] = o; }
+        for (int o = 0; o < s_own[b]; ++o) { s_vcol[s_first[b] + o] = (int16_t)b; s_vown[s_first[b] + o] = (int16_t)o; }
     __syncthreads();
     const int nslots = max(1, (V + kThreadsGQ - 1) / kThreadsGQ);
     if (first_one) {
@@ -432,30 +487,22 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
     const bool permuted = nslots == 1;
     const int k_of_w = w < kWavesGQ / 2 ? w : kWavesGQ + kWavesGQ / 2 - 1 - w;      // group of 64 lists that wave w walks
     int32_t lo, hi;
-    list_of(tid, lo, hi);
-    // longest first; equal lengths keep their order: a bitonic sort of distinct keys
-    uint32_t key = permuted ? ((uint32_t)(hi - lo) << 9) | (uint32_t)(kThreadsGQ - 1 - tid) : (uint32_t)(kThreadsGQ - 1 - tid);
-    if (permuted) {
-        for (int size = 2; size <= kThreadsGQ; size <<= 1)
-            for (int step = size >> 1; step > 0; step >>= 1) {
-                uint32_t other;
-                if (step < kWave) {
-                    other = (uint32_t)__shfl_xor((int)key, step);
-                } else {
-                    __syncthreads();
-                    s_key[tid] = key;
-                    __syncthreads();
-                    other = s_key[tid ^ step];
-                }
-                const bool larger = ((tid & step) == 0) == ((tid & size) == 0);     // this place takes the larger of the two
-                key = (key > other) == larger ? key : other;
-            }
+    // by length: with one slot for both kinds of lists, with several for the tiles only
+    if (permuted || for_tiles) {
+        uint32_t key[kMaxSlots];
+#pragma unroll
+        for (int i = 0; i < kMaxSlots; ++i) {
+            const int v = (w * nslots + i) * kWave + lane;
+            lo = hi = 0;
+            if (i < nslots) list_of(v, lo, hi);
+            key[i] = (uint32_t)(hi - lo) * kLists + (uint32_t)v;
+        }
+        sort_by_length(key, nslots, min(cap, kChunk * d), s_key, s_count, s_part);
+        __syncthreads();
     }
-    __syncthreads();
-    s_key[tid] = key;
-    __syncthreads();
+    auto by_len = [&](int place) -> int { return (int)(s_key[place] % kLists); };      // virtual column at a place of the sorted order
     if (!for_tiles) {
-        const int walked_p = kThreadsGQ - 1 - (int)(s_key[k_of_w * kWave + lane] & (kThreadsGQ - 1));
+        const int walked_p = permuted ? by_len(k_of_w * kWave + lane) : k_of_w * kWave + lane;
         perm[(size_t)c * kThreadsGQ + tid] = (uint16_t)walked_p;
         for (int slot = 0; slot < nslots; ++slot) {
             list_of(permuted ? walked_p : slot * kThreadsGQ + tid, lo, hi);
@@ -463,40 +510,18 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
             s.seg_lo[at] = lo;
             s.seg_n[at] = hi - lo;
             int32_t longest = hi - lo;
-    #pragma unroll
+#pragma unroll
             for (int off = 32; off > 0; off >>= 1) longest = max(longest, __shfl_xor(longest, off));
             if (lane == 0) seg[((size_t)c * nslots + slot) * kWavesGQ + w] = (uint32_t)((longest + kSegBatch - 1) / kSegBatch * kSegBatch);
         }
         return;
     }
-    // tiles of 32 lists: all lists by length.  With one slot they have just been sorted; several slots' lists are sorted here.
-    const int sorted = nslots == 1 ? kThreadsGQ : nslots == 2 ? 2 * kThreadsGQ : kMaxSlots * kThreadsGQ;
-    if (!permuted) {
-        for (int v = tid; v < sorted; v += kThreadsGQ) {
-            lo = hi = 0;
-            if (v < nslots * kThreadsGQ) list_of(v, lo, hi);
-            s_all[v] = ((uint32_t)(hi - lo) << 11) | (uint32_t)(kMaxSlots * kThreadsGQ - 1 - v);
-        }
-        for (int size = 2; size <= sorted; size <<= 1)
-            for (int step = size >> 1; step > 0; step >>= 1) {
-                __syncthreads();
-                for (int pair = tid; pair < sorted / 2; pair += kThreadsGQ) {
-                    const int i = 2 * pair - (pair & (step - 1)), j = i + step;
-                    const uint32_t x = s_all[i], y = s_all[j];
-                    if ((x < y) == ((i & size) == 0)) { s_all[i] = y; s_all[j] = x; }
-                }
-            }
-        __syncthreads();
-    }
-    auto by_len = [&](int place) -> int {                             // virtual column at a place of the sorted order
-        return permuted ? kThreadsGQ - 1 - (int)(s_key[place] & (kThreadsGQ - 1)) : kMaxSlots * kThreadsGQ - 1 - (int)(s_all[place] & (kMaxSlots * kThreadsGQ - 1));
-    };
-    auto length_at = [&](int place) -> int { return (int)(permuted ? s_key[place] >> 9 : s_all[place] >> 11); };
+    // tiles of 32 lists
     const int ntiles = (V + kTileCols - 1) / kTileCols;
     for (int place = tid; place < ntiles * kTileCols; place += kThreadsGQ) {
         lo = hi = 0;
         if (place < V) list_of(by_len(place), lo, hi);
-        const size_t at = (size_t)c * kMaxSlots * kThreadsGQ + place;
+        const size_t at = (size_t)c * kLists + place;
         s.by_len_lo[at] = lo;
         s.by_len_n[at] = hi - lo;
     }
@@ -515,7 +540,7 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
 #pragma unroll
         for (int i = 0; i < kWaveTiles; ++i) {
             const int t = tile_of_wave(i, tid);
-            sg.len[i] = (uint16_t)(t < ntiles ? (length_at(t * kTileCols) + kStepEntries - 1) / kStepEntries : 0);
+            sg.len[i] = (uint16_t)(t < ntiles ? (s_key[t * kTileCols] / kLists + kStepEntries - 1) / kStepEntries : 0);
             sg.steps += sg.len[i];
         }
         reinterpret_cast<TileSeg*>(plan + L.off_m_seg)[(size_t)c * kWavesMM + tid] = sg;   // (first_step: k_plan_rows)
@@ -569,7 +594,7 @@ __device__ __forceinline__ void plan_tiles(uint8_t* __restrict__ plan, const Pla
                 end += sg.len[i];
                 if (step >= end) { tile = i + 1; before = end; }
             }
-            const size_t place = (size_t)c * kMaxSlots * kThreadsGQ + (size_t)tile_of_wave(tile, w) * kTileCols + bb;
+            const size_t place = (size_t)c * kLists + (size_t)tile_of_wave(tile, w) * kTileCols + bb;
             const int lo = s.by_len_lo[place], n = s.by_len_n[place], e0 = (step - before) * kStepEntries;
 #pragma unroll
             for (int k = 0; k < kStepEntries; ++k) src[k] = e0 + k < n ? sorted[lo + e0 + k] : kNoSource;

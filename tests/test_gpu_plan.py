@@ -58,6 +58,10 @@ def test_device_plan_equals_host_plan(m, n, r, d, dist):
     (257, 2304, 1, 1, "uniform"),       # one column: every entry of a step of 64 meets every other
     (300, 2303, 2048, 64, "uniform"),   # the most columns and the most entries a tile can have
     (4097, 513, 512, 3, "zipf"),        # three tiles of P, parts that end inside a step
+    (9, 4100, 64, 64, "distinct"),      # by length: 512 lists of 256 entries, and of one or none in the last chunk
+    (9, 4200, 600, 64, "uniform"),      # two slots, lists on both sides of 256 entries
+    (9, 2200, 1000, 40, "zipf"),        # three or four slots of lists of all lengths
+    (9, 2100, 1500, 2, "zipf"),         # mostly empty lists
 ])
 def test_device_plan_at_the_edges_of_the_sort(m, n, r, d, dist):
     print(f"[case] device plan m={m} n={n} r={r} d={d} {dist}", flush=True)
