@@ -14,10 +14,12 @@
 // What bounds a build is not bytes (a few MB) but the chain of launches and of dependent loads inside them, so the
 // work is cut into few kernels, and small sums are taken again by every workgroup that needs them.  The form before
 // this one (64-bit keys, two device-wide radix sorts, 17 to 23 launches) took 96 us of host time alone for a
-// 4096 x 4096 matrix with r = 512 and d = 8; this one is done after 26 us (24 of them before there were tiles).
-// The sums that are taken again (all chunks' longest lists in k_plan_deal, all segments in k_plan_rows) grow with the square of
-// the chunks, and show only far beyond weight matrices: n = 131072 (64 chunks) 62 us, 1M 0.44 ms, 4M 2.5 ms (r = 512, d = 8; the
-// form before: 275 us, 1.0 ms, 3.6 ms), and 16.8M (8192 chunks, r = 64, d = 2) 12.3 ms against 11.1.
+// 4096 x 4096 matrix with r = 512 and d = 8; this one is done after 23 us (4096 x 11008: 27, r = 2048: 34).  The tiles are part of every plan, whatever
+// the type of G that comes later, and cost a build 0 to 2 us there, 4 at r = 2048 (without them: 23, 25.5 and 29.6 us, lists sorted by bitonic sorts).
+// The sums that are taken again (all chunks' longest lists in k_plan_deal, all segments and all steps of tiles in k_plan_rows) grow with the square of
+// the chunks, and show only far beyond weight matrices: n = 131072 (64 chunks) 77 us, 1M 0.63 ms, 4M 4.2 ms (r = 512, d = 8; the
+// form before: 275 us, 1.0 ms, 3.6 ms), and 16.8M (8192 chunks, r = 64, d = 2) 27 ms against 11.1.  With the steps summed up per chunk that is 22 ms,
+// but the builds of weight matrices take 0.4 us longer.
 // Errors that only the data can show (an index outside [0, r), columns too skewed for a plan) are
 // left in a device status word and invalidate the plan's magic, so that a later compress call
 // with it fills S with NaN instead of following it.
@@ -31,7 +33,8 @@
 namespace lsp {
 
 // What bounds it is the launch and one chain of three trips to memory (header, positions, values), so a thread takes four values at a time
-// and all are in flight: 4096 x 4096, d = 8 stays at 4 us (one value a thread in the lists and four in the tiles, the lists' copy for bf16: 4.7).
+// and all are in flight: 4096 x 4096, d = 8 3.7 us from call to call, with the tiles as without them (one value a thread in the lists and four in the tiles: 4.7);
+// 4096 x 131072 16 us, without tiles 7.7.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_plan_refresh(uint8_t* __restrict__ plan, const float* __restrict__ P_val,
                                                       const float* __restrict__ Q_val, int m, int n, int r, int d) {
