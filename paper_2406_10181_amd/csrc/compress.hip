@@ -25,14 +25,14 @@ namespace lsp {
 // row of P^T and one stripe of 256 columns, one column per thread.
 constexpr int kThreadsB = 256;
 constexpr int kStripeQuads = 64;                              // column quads (float4) per stripe
-__global__ __launch_bounds__(kThreadsB) void k_compress_pt(const CompressGroup grp, int r, int d, int nstripes) {
+__global__ __launch_bounds__(kThreadsB) void k_compress_pt(const CompressGroup grp, int r, int d, int nstripes, bool tiles) {
     const CompressProblem pr = group_pick(grp, (int)blockIdx.x, true);
     const uint8_t* __restrict__ plan = pr.plan;
     const float* __restrict__ T = pr.T;
     float* __restrict__ S = pr.S;
     const int block = pr.block_pt;
     PlanHeaderPtr H = as_const<PlanHeader>(plan);
-    if (!plan_matches(H, pr.m, pr.n, r, d)) return;                   // kernel A has filled S with NaN
+    if (!plan_matches(H, pr.m, pr.n, r, d, tiles)) return;                   // kernel A has filled S with NaN
     const int stripe = block % nstripes, item = block / nstripes;
     if (item >= H->p_nitems) return;
     const auto* itp = as_const<int32_t>(plan + H->off_p_item) + 4 * item;    // RowItem, field by field
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt(const CompressGroup g
 // exchanges in a fixed order.  A row's last quad starts at r - 4 when r is no multiple of 4 and stores only what the
 // quad before it has not (3001 rows, r = 250, d = 5: 26 us one column a thread, now 6).
 template <int LG>
-__global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup grp, int r, int d, int sq) {
+__global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup grp, int r, int d, int sq, bool tiles) {
     constexpr int NG = kWave / LG;                            // entry groups per wave
     const CompressProblem pr = group_pick(grp, (int)blockIdx.x, true);
     const uint8_t* __restrict__ plan = pr.plan;
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup 
     float* __restrict__ S = pr.S;
     const int block = pr.block_pt;
     PlanHeaderPtr H = as_const<PlanHeader>(plan);
-    if (!plan_matches(H, pr.m, pr.n, r, d)) return;                   // kernel A has filled S with NaN
+    if (!plan_matches(H, pr.m, pr.n, r, d, tiles)) return;                   // kernel A has filled S with NaN
     const int stripe = block & 7;
     const int item = (block >> 3) * (kThreadsB / kWave) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (item >= H->p_nitems) return;
@@ -140,11 +140,13 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup 
 }
 
 // ----------------------------------------------------------------------------------------------
+static bool walks_tiles(lsp_dtype dtype, const RawCall& raw) { return dtype == LSP_BF16 && !raw.status; }   // (plans of raw calls have no tiles)
+
 static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, lsp_dtype dtype, hipStream_t st) {
     switch (dtype) {
         case LSP_F32:  return launch_gq_f32(g, r, d, raw, st);
         case LSP_F16:  return launch_gq_f16(g, r, d, raw, st);
-        default:       return raw.status ? launch_gq_bf16(g, r, d, raw, st) : launch_mm_bf16(g, r, d, st);   // (plans of raw calls have no tiles)
+        default:       return walks_tiles(dtype, raw) ? launch_mm_bf16(g, r, d, st) : launch_gq_bf16(g, r, d, raw, st);
     }
 }
 
@@ -162,7 +164,7 @@ static void longest_first(CompressGroup& g) {
 
 hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st, const RawCall& raw) {
     const int nstripes = (r + kStripeQuads * 4 - 1) / (kStripeQuads * 4);
-    const bool striped = r >= 4;
+    const bool striped = r >= 4, tiles = walks_tiles(dtype, raw);
     longest_first(g);
     g.first_pt[0] = 0;
     for (int p = 0; p < g.count; ++p) {
@@ -174,12 +176,12 @@ hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_d
     const unsigned blocks = (unsigned)g.first_pt[g.count];
     if (striped) {
         const int sq = ((r + 3) / 4 + 7) / 8;
-        if (sq <= 16)      hipLaunchKernelGGL(k_compress_pt8<16>, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, sq);
-        else if (sq <= 32) hipLaunchKernelGGL(k_compress_pt8<32>, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, sq);
-        else               hipLaunchKernelGGL(k_compress_pt8<64>, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, sq);
+        if (sq <= 16)      hipLaunchKernelGGL(k_compress_pt8<16>, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, sq, tiles);
+        else if (sq <= 32) hipLaunchKernelGGL(k_compress_pt8<32>, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, sq, tiles);
+        else               hipLaunchKernelGGL(k_compress_pt8<64>, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, sq, tiles);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_compress_pt, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, nstripes);
+    hipLaunchKernelGGL(k_compress_pt, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, nstripes, tiles);
     return hipGetLastError();
 }
 

@@ -15,8 +15,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // index S and T with the call's r and m, so a plan built for other sizes (or a buffer that holds no
 // plan at all) must not be walked.  Kernel A then fills S with NaN, which is how the caller sees
 // the mistake (or takes the scatter form, raw calls), and kernel B does nothing; all kernels exit normally.
-__device__ __forceinline__ bool plan_matches(PlanHeaderPtr H, int m, int n, int r, int d) {
-    return H->magic == kPlanMagic && H->m == m && H->n == n && H->r == r && H->d == d;
+// tiles: kernel A of this call walks the tiles, so there must be some; kernel B asks for the same, or it would put what lies in T in the place of the NaN.
+__device__ __forceinline__ bool plan_matches(PlanHeaderPtr H, int m, int n, int r, int d, bool tiles) {
+    return H->magic == kPlanMagic && H->m == m && H->n == n && H->r == r && H->d == d && (!tiles || H->m_total_steps != 0);
 }
 __device__ __forceinline__ void fill_s(float* __restrict__ S, float x, int r, int block, int nblocks, int tid, int nthreads) {
     const int64_t total = (int64_t)r * r;

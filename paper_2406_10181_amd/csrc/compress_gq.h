@@ -415,7 +415,7 @@ __global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGro
     ChunkStager<D, WHOLE> stg;
     stg.fetch(G, i0, m, n, 0, tid);                             // in flight while the plan's header arrives
     PlanHeaderPtr H = as_const<PlanHeader>(plan);
-    if (!plan_matches(H, m, n, r, d)) {                               // not a plan for this problem
+    if (!plan_matches(H, m, n, r, d, false)) {                               // not a plan for this problem
         if constexpr (RAW) scatter_blocks<D>(G, raw, S, reinterpret_cast<float*>(smem), m, n, r, d, block, nblocks, tid, kThreadsGQ);
         else fill_s(S, __builtin_nanf(""), r, block, nblocks, tid, kThreadsGQ);
         return;

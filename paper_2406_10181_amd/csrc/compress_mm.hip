@@ -339,7 +339,7 @@ template <int NP, bool HALVES> struct BlockWalk {
         for (block = from; block < blocks; block += gridDim.x) {
             pr = problem_of(block);
             H = as_const<PlanHeader>(pr.plan);
-            const bool planned = plan_matches(H, pr.m, pr.n, r, d) && H->m_format == kTileFormat;
+            const bool planned = plan_matches(H, pr.m, pr.n, r, d, true);
             visit(pr, H, planned);
             if (!planned) continue;
             nchunks = H->nchunks;

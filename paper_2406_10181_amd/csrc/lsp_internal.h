@@ -112,11 +112,11 @@ struct PlanHeader {            // first 256 bytes of the plan buffer
                                // that fill up the last tile count on from nvcols
     uint64_t off_m_steps;      // uint4[m_total_steps][64]
     uint64_t off_m_src;        // uint32[m_total_steps][2][16][4]     flat ELL position of entry k of list 16 h + b; kNoSource: none
-    uint32_t m_total_steps;    // kStepsAhead readable ones behind the last included
-    uint32_t m_format;         // kTileFormat if there are tiles
+    uint32_t m_total_steps;    // kStepsAhead readable ones behind the last included; 0: no tiles (raw calls)
+    uint32_t pad2;
 };
 static_assert(sizeof(PlanHeader) == 216, "PlanHeader layout");
-constexpr uint32_t kPlanMagic = 0x4C535038u;   // "LSP8"
+constexpr uint32_t kPlanMagic = 0x4C535039u;   // "LSP9"; another one for every change of the layout, so that kept plans of an older one are refused
 constexpr uint32_t kNoSource = 0xFFFFFFFFu;    // q_src of a padding pair
 constexpr size_t   kPlanHeaderBytes = 256;
 
@@ -134,7 +134,6 @@ __host__ __device__ static inline int tile_of_wave(int i, int w) { return kWaves
 // overflow only where those of v could): exact for |v| >= 2^-125, and for smaller ones but for a last bit of 2^-149.  (Not scaled, the parts of
 // values below 2^-110 would lose what lies under the smallest bf16, 2^-133.)  An infinity or NaN is its first part.
 constexpr int kPartShift[3] = {0, 7, 15};
-constexpr uint32_t kTileFormat = 1;            // PlanHeader::m_format of tiles with parts of this kind
 // (Without a loop or a branch: the parts of a loop the compiler kept in LDS, and lsp_plan_refresh_values took 11 us instead of 4 on 4096 x 4096, d = 8.)
 __host__ __device__ static inline uint32_t bits_of(float x) { uint32_t u; __builtin_memcpy(&u, &x, 4); return u; }
 __host__ __device__ static inline float without_low_half(float x) {

@@ -242,7 +242,6 @@ int build_plan_host(const int32_t* P_idx, const float* P_val, const int32_t* Q_i
 
     // ---- tiles of 32 lists (bf16) -----------------------------------------------------------------
     H->off_m_seg = L.off_m_seg; H->off_m_cols = L.off_m_cols; H->off_m_steps = L.off_m_steps; H->off_m_src = L.off_m_src;
-    H->m_format = kTileFormat;
     TileSeg*  mseg = reinterpret_cast<TileSeg*>(out + L.off_m_seg);
     uint16_t* mcols = reinterpret_cast<uint16_t*>(out + L.off_m_cols);
     uint16_t* msteps = reinterpret_cast<uint16_t*>(out + L.off_m_steps);

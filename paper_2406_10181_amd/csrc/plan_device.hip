@@ -41,7 +41,7 @@ __global__ __launch_bounds__(256) void k_plan_refresh(uint8_t* __restrict__ plan
     const PlanHeader* H = reinterpret_cast<const PlanHeader*>(plan);
     if (H->magic != kPlanMagic || H->m != m || H->n != n || H->r != r || H->d != d) return;   // not this problem's plan
     const int64_t nq = (int64_t)H->q_total_rows * kWave / 4, np = (int64_t)m * d, np4 = (np + 3) / 4;
-    const int64_t nt = H->m_format == kTileFormat ? (int64_t)H->m_total_steps * kTileCols : 0;
+    const int64_t nt = (int64_t)H->m_total_steps * kTileCols;
     uint2* rows = reinterpret_cast<uint2*>(plan + H->off_q_rows);
     const uint4* qsrc = reinterpret_cast<const uint4*>(plan + H->off_q_src);
     uint2* pent = reinterpret_cast<uint2*>(plan + H->off_p_ent);
@@ -475,7 +475,6 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
             H->off_q_src = L.off_q_src; H->off_p_src = L.off_p_src;
             if (gridDim.x > (unsigned)nchunks + 1) {                 // (the header has been cleared)
                 H->off_m_seg = L.off_m_seg; H->off_m_cols = L.off_m_cols; H->off_m_steps = L.off_m_steps; H->off_m_src = L.off_m_src;
-                H->m_format = kTileFormat;
             }
         }
     }

@@ -144,6 +144,32 @@ def test_bf16_compress_with_a_foreign_plan_in_a_group(foreign):
             assert np.array_equal(singles[k], grouped[k])
 
 
+@pytest.mark.parametrize("kind,r,dtype", [("older layout", 64, "bf16"), ("older layout", 3, "bf16"), ("older layout", 64, "f16"), ("older layout", 64, "f32"),
+                                          ("no tiles", 64, "bf16"), ("no tiles", 3, "bf16")])
+def test_compress_refuses_a_plan_it_cannot_follow(kind, r, dtype):
+    """A plan of this very problem, but of an older layout, or the one that a raw call makes in its workspace, which has no tiles: S is NaN
+    throughout (kernel B may not put sums over what lies in T in its place) and T is untouched."""
+    import torch
+    import gpu_util as gu
+    import paper_2406_10181_amd as L
+    pb = syn.make_problem("refused", 300, 2100, r, 2, dtype, seed=7550 + r, g_std=1.0)
+    print(f"[case] plan refused: {kind} r={r} {dtype}", flush=True)
+    dp = gu.DeviceProblem(pb)
+    dp.build_plan()
+    if kind == "older layout":
+        dp.plan[:4].view(torch.int32).fill_(0x4C535038)
+    else:
+        dp.compress_raw()
+        at = (pb.m * r * 4 + 255) // 256 * 256
+        dp.plan = dp.ws[at:at + dp.plan_bytes].clone()
+        assert dp.plan[:4].view(torch.int32).item() == 0x4C535039, "the plan of the raw call"
+    dp.ws.fill_(0x5A)
+    dp.S.fill_(1.0)
+    L.lsp_compress_planned(dp.G, dp.plan, pb.m, pb.n, r, 2, dp.S, dp.code, dp.ws, dp.ws_bytes, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    assert bool(dp.S.isnan().all()) and bool((dp.ws == 0x5A).all())
+
+
 @pytest.mark.parametrize("g_exp,v_exp", [
     (0, -100), (60, -118), (60, -124),        # values whose lower parts, as they are, would be subnormal or gone
     (100, -132), (100, -140),                 # subnormal values

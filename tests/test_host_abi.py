@@ -185,7 +185,7 @@ def _replay_plan(buf, pb):
     slot, each segment's length from the table; lane l of wave w in slot s walks the list of virtual
     column s*512 + w*64 + l, or, with one slot, of the virtual column the per-chunk table names."""
     hdr32 = buf[:48].view(np.int32)
-    assert hdr32[0] == 0x4C535038
+    assert hdr32[0] == 0x4C535039
     m, n, r, d, nchunks, nslots, nvcols, total_rows, nitems, any_split, cap = [int(x) for x in hdr32[1:12]]
     assert (m, n, r, d) == (pb.m, pb.n, pb.r, pb.d) and nchunks == -(-n // CHUNK)
     assert 1 <= nslots <= 4 and nvcols <= nslots * 512
