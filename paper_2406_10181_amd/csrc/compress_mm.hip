@@ -203,7 +203,8 @@ __device__ __forceinline__ void walk_tiles(WaveChunk& w, uint8_t* sums, bool fir
             }
         }
         // An infinity in G meets zeros among the lower parts, and above the unit vectors' zeros: then the rows are added up one by one,
-        // and where the sum is no number the first part alone says what becomes of it.
+        // and where the sum is no number the first part alone says what becomes of it.  (Nothing says it for values below 2^-133, whose first part
+        // is zero: an infinity times one of them is NaN.)  An infinite sum stays one: the first part may be finite where the value's product is not.
         if (__builtin_expect(__any(!(odd < __builtin_inff())), 0)) {
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -216,7 +217,7 @@ __device__ __forceinline__ void walk_tiles(WaveChunk& w, uint8_t* sums, bool fir
                         own = q == 0 || part == q ? sum : own;
                         head = q == 0 || part == q ? first : head;
                     }
-                    keep[h][p] = fabsf(own) < __builtin_inff() ? own : head;
+                    keep[h][p] = own == own ? own : head;
                 }
         }
         *dst[0] = keep[0] + before[0];

@@ -84,6 +84,41 @@ def test_bf16_compress_with_infinities_and_nan(m, n, r, dist):
     assert (np.abs(got[finite] - S[finite]) <= (terms + 4) * 2.0 ** -24 * B[finite] + 1e-35).all()
 
 
+@pytest.mark.parametrize("m,n,r", [(40, 2500, 2048), (4096, 300, 1024)])
+def test_bf16_compress_keeps_infinities_and_their_signs(m, n, r):
+    """Blocks of 8 rows and of 16, and as many rows in every row of P^T as kernel B takes at a time, so that it adds no zeros: an infinity stays
+    one, and only sums of both infinities, or with a NaN, are NaN."""
+    import gpu_util as gu
+    pb = _problem(m, n, r, 7150 + m, "uniform")
+    rng = np.random.default_rng(m)
+    for bits in (0x7F80, 0xFF80, 0x7FC0):
+        for _ in range(40):
+            pb.G[rng.integers(m), rng.integers(n)] = bits
+    pb.Q_val[:40] = np.float32(0.5)                                   # (lower parts that are zero)
+    pb.G[m - 1, :40] = 0x7F80
+    print(f"[case] mm signs of infinities m={m} n={n} r={r}", flush=True)
+    S, _, _ = _exact(pb)
+    got = gu.DeviceProblem(pb).compress_planned().astype(np.float64)
+    for kind in (np.isposinf, np.isneginf, np.isnan):
+        assert kind(S).any() and np.array_equal(kind(got), kind(S)), kind.__name__
+
+
+def test_bf16_compress_that_overflows_is_infinite():
+    """The largest bf16 number times values whose first part is one: only the lower parts take the product beyond fp32."""
+    import gpu_util as gu
+    m, n, r = 40, 600, 2048
+    pb = _problem(m, n, r, 7160, "uniform")
+    pb.Q_idx[:, 0] = np.arange(n)
+    pb.Q_val[:, 0] = np.where(np.arange(n) % 2, np.float32(1.0077), np.float32(1.0))
+    pb.G[:] = np.where(np.arange(m)[:, None] % 3 == 0, 0xFF7F, 0x7F7F)
+    print("[case] mm overflow", flush=True)
+    got = gu.DeviceProblem(pb).compress_planned()
+    with np.errstate(over="ignore"):
+        want = (syn.storage_to_f64(pb.G, "bf16") * pb.Q_val[:, 0].astype(np.float64)).astype(np.float32)
+    assert np.isinf(want).any() and np.isfinite(want).any()
+    assert np.array_equal(got[:m, :n], want) and not got[m:].any() and not got[:, n:].any()
+
+
 @pytest.mark.parametrize("m,n,r,d,dist", [(2049, 520, 64, 8, "uniform"), (33, 4103, 512, 16, "zipf"), (50, 2500, 2048, 4, "uniform"), (4100, 264, 96, 3, "zipf")])
 def test_bf16_compress_with_several_entries_a_row(m, n, r, d, dist):
     import gpu_util as gu
