@@ -127,13 +127,14 @@ def test_device_plan_reports_skew_and_bad_indices():
     assert int(plan[:4].view(torch.int32).item()) == 0
 
 
-@pytest.mark.parametrize("m,r,dtype", [(1, 2048, "bf16"), (16, 2046, "f32"), (17, 2048, "f16"), (75, 2047, "bf16")])
-def test_raw_entry_on_columns_too_skewed_for_a_plan(m, r, dtype):
-    """The scatter form by blocks of 16 rows: one row, a whole block, one row more, five blocks."""
+@pytest.mark.parametrize("m,n,r,dtype", [(1, 2500, 2048, "bf16"), (8, 2500, 2046, "f32"), (9, 2500, 2048, "f16"), (16, 2500, 2046, "f32"), (17, 2500, 2048, "f16"),
+                                         (75, 2500, 2047, "bf16"), (8195, 2000, 2048, "f16")])
+def test_raw_entry_on_columns_too_skewed_for_a_plan(m, n, r, dtype):
+    """The scatter form by blocks of 8 rows: one row, a whole block, one row more, two blocks and three, ten, and three blocks a workgroup."""
     import gpu_util as gu
     import oracle
     import paper_2406_10181_amd as L
-    n, d = 2500, 4
+    d = 4
     rng = np.random.default_rng(9000 + m)
     P_idx, P_val = syn.ell_projector(m, r, d, rng)
     Q_idx, Q_val = syn.ell_projector(n, r, d, rng)
