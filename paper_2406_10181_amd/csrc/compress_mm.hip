@@ -153,11 +153,12 @@ template <int R> __device__ __forceinline__ uint8_t* piece_of(uint8_t* sums, uin
     return sums + v * (R * 4) + ((x + v / (256 / (R * 4))) & 3) * R;
 }
 
-// The sum of a list from the sums over the parts of its values.  (Not two FMAs: with those the 16-row form spilled 16 registers, and
-// seven matrices of a 6.7B-style layer took 50 us more.)
-__device__ __forceinline__ float sum_of_parts(float first, float second, float third) {
+// The sum of a list from the sums over the parts of its values, with the other sign: an FMA that subtracts is not written onto its addend, and as one
+// that adds it kept the registers beside it from being used (the 16-row form spilled 16 of them, 50 us more on seven matrices of a 6.7B-style layer;
+// ldexp and an addition instead: 1 % of a compress call).
+__device__ __forceinline__ float minus_sum_of_parts(float first, float second, float third) {
     const float rest = fmaf(third, 1.0f / (1 << (kPartShift[2] - kPartShift[1])), second);
-    return __builtin_amdgcn_ldexpf(rest, -kPartShift[1]) + first;
+    return fmaf(rest, -1.0f / (1 << kPartShift[1]), -first);
 }
 
 // A wave's tiles of one staged chunk.
@@ -185,7 +186,7 @@ __device__ __forceinline__ void walk_tiles(WaveChunk& w, uint8_t* sums, bool fir
         if (!first_chunk) { before[0] = *dst[0]; before[1] = *dst[1]; }
     };
     auto flush = [&]() {
-        Piece keep[2];
+        Piece minus[2];
         float odd = 0.0f;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -198,8 +199,8 @@ __device__ __forceinline__ void walk_tiles(WaveChunk& w, uint8_t* sums, bool fir
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
-                keep[h][p] = sum_of_parts(X[p][0], X[p][1], X[p][2]);
-                odd += fabsf(keep[h][p]);
+                minus[h][p] = minus_sum_of_parts(X[p][0], X[p][1], X[p][2]);
+                odd += fabsf(minus[h][p]);
             }
         }
         // An infinity in G meets zeros among the lower parts, and above the unit vectors' zeros: then the rows are added up one by one,
@@ -213,15 +214,15 @@ __device__ __forceinline__ void walk_tiles(WaveChunk& w, uint8_t* sums, bool fir
                     float own, head;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const float y = D[h][p][q], first = quad_lane<0>(y), sum = sum_of_parts(first, quad_lane<1>(y), quad_lane<2>(y));
+                        const float y = D[h][p][q], first = quad_lane<0>(y), sum = minus_sum_of_parts(first, quad_lane<1>(y), quad_lane<2>(y));
                         own = q == 0 || part == q ? sum : own;
                         head = q == 0 || part == q ? first : head;
                     }
-                    keep[h][p] = own == own ? own : head;
+                    minus[h][p] = own == own ? own : -head;
                 }
         }
-        *dst[0] = keep[0] + before[0];
-        *dst[1] = keep[1] + before[1];
+        *dst[0] = before[0] - minus[0];
+        *dst[1] = before[1] - minus[1];
         ++t;
     };
     const uint32_t pick = (part & 1 ? 0x0C0C0302u : 0x0C0C0100u) + (part & 2 ? 0x0404u : 0u);   // bytes of this lane's offset among the four
@@ -507,6 +508,9 @@ static bool narrow_blocks(const CompressGroup& g, int32_t r) {
 //   5120 x 4096  38.9 and 36.9, zipf 54.1 and 63.7, r = 256, d = 4 28.2 and 32.0, r = 1024, d = 4 39.5 and 42.2
 //   5120 x 13824 89.1 and 80.4, zipf 113.7 and 118.8, r = 256, d = 4 59.2 and 72.5, r = 1024, d = 4 82.9 and 83.1
 //   6500 x 4096  40.1 and 41.0; 9000 x 2048 38.5 and 38.6; seven matrices of 5120 and 13824 rows and columns 292 and 319
+// Beyond r = 1024, where the lists are a few steps long, it is on a par with k_compress_gq, and behind it for short lists on 4096 and 8192 rows: r = 2048,
+//   4096 x 4096  d = 4 53.3 and 49.9, d = 8 58.8 and 55.4, d = 16 73.2 and 71.2; 5120 x 5120 77.0 and 80.1, 87.5 and 88.1, 109.4 and 113.3
+//   4096 x 16384 110 and 103, 120 and 114, 153 and 156; r = 1536, d = 8 4096 x 4096 47.9 and 50.9, 8192 x 8192 128 and 133
 hipError_t launch_mm_bf16(CompressGroup& g, int32_t r, int32_t d, hipStream_t st) {
     return narrow_blocks(g, r) ? launch_mm_rows<2>(g, r, d, st) : launch_mm_rows<4>(g, r, d, st);
 }
