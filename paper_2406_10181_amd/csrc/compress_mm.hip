@@ -492,22 +492,32 @@ template <int NP> static hipError_t launch_mm_rows(CompressGroup& g, int32_t r, 
 }
 
 // Blocks of 16 rows read the plan half as often as blocks of 8 and share each value between twice the rows (4096 x 4096, d = 8, with
-// kernel B: r = 512 28.2 us, with 8 rows 29.6; r = 1024 34.6 and 38.6; seven matrices of a 6.7B layer 216 and 265).  8 rows are better where
-// there is at most one block of 8 for a CU, so that the blocks of 16 would leave CUs idle (2048 rows 18.4 us, with 16 22.8; 3001 rows 22.2
-// and 20.9), and beyond r = 1024, where the sums of 16 rows do not fit the LDS (r = 1536 50.1 and 52.6, r = 2048 57.0 and 60.6).
+// kernel B: r = 512 28.2 us, with 8 rows 29.6; r = 1024 34.6 and 38.6; seven matrices of a 6.7B layer 216 and 265).  8 rows are better
+//   where there is at most one block of 8 for a CU, so that the blocks of 16 would leave CUs idle (2048 rows 18.4 us, with 16 22.8; 3001 rows 22.2
+//   and 20.9);
+//   where they take three rounds of one for every CU and the blocks of 16 two, the last of them little more than half full or less: 4097 to 6144 rows (us with 8
+//   and with 16 rows: 5120 x 5120, r = 512, d = 8 45.5 and 47.2, zipf 61.8 and 64.1; r = 1024, d = 16 75.0 and 79.6; 6144 x 4096, r = 256, d = 16 56.7 and 60.9, r = 1024,
+//   d = 4 41.3 and 45.0; in the mean of 36 such calls 3 % less, with zipf columns even: 4200 x 2048, r = 1024, d = 8 61.8 and 56.8); with five rounds and three
+//   they are not (9000 x 2048, r = 512, d = 8 41.4 and 40.5);
+//   and beyond r = 1024, where the sums of 16 rows do not fit the LDS (r = 1536 50.1 and 52.6, r = 2048 57.0 and 60.6).
 static bool narrow_blocks(const CompressGroup& g, int32_t r) {
-    int64_t blocks = 0;
-    for (int p = 0; p < g.count; ++p) blocks += (g.m[p] + 7) / 8;
-    return r > 1024 || blocks <= kResidentMM;
+    int64_t of8 = 0, of16 = 0;
+    for (int p = 0; p < g.count; ++p) {
+        of8 += (g.m[p] + 7) / 8;
+        of16 += (g.m[p] + 15) / 16;
+    }
+    const auto rounds = [](int64_t blocks) { return (blocks + kResidentMM - 1) / kResidentMM; };
+    return r > 1024 || rounds(of8) == 1 || (rounds(of8) == 3 && rounds(of16) == 2);
 }
 
 // Every bf16 call with a kept plan comes here, whatever its rows: the sums of a row do not depend on the blocks it is in, so a matrix has the same
-// result alone and in any group, which a second kernel with sums in another order would end.  The blocks of 16 go in rounds of one for every CU, and
-// where the last round is nearly empty, k_compress_gq with its finer grain (8 rows, two workgroups a CU) is up to 12 % faster if the lists are
-// long and even, and 10 to 30 % slower otherwise (us with kernel B, here and there; single matrices, r = 512, d = 8 unless said otherwise):
-//   5120 x 4096  38.9 and 36.9, zipf 54.1 and 63.7, r = 256, d = 4 28.2 and 32.0, r = 1024, d = 4 39.5 and 42.2
-//   5120 x 13824 89.1 and 80.4, zipf 113.7 and 118.8, r = 256, d = 4 59.2 and 72.5, r = 1024, d = 4 82.9 and 83.1
-//   6500 x 4096  40.1 and 41.0; 9000 x 2048 38.5 and 38.6; seven matrices of 5120 and 13824 rows and columns 292 and 319
+// result alone and in any group, which a second kernel with sums in another order would end.  Where the last round is nearly empty, k_compress_gq with
+// its finer grain (8 rows, two workgroups a CU) is up to 16 % faster if the lists are long and even, and 4 to 30 % slower otherwise: 7 % slower in the mean of
+// 40 calls with random sizes, counts and columns whose last round is less than 80 % full (us with kernel B, here and there; single matrices, uniform and zipf columns):
+//   5120 x 5120  r = 512, d = 8 45.5 and 43.5, 61.8 and 70.9; r = 512, d = 4 37.5 and 36.9, 52.5 and 61.3; r = 1024, d = 8 57.7 and 57.1, 88.5 and 99.0
+//   5120 x 13824 r = 512, d = 8 90.1 and 79.2, 111 and 120; r = 1024, d = 8 108 and 104, 151 and 151; d = 16 147 and 143, 191 and 199
+//   6144 x 4096  r = 256, d = 4 28.6 and 34.2, 38.5 and 48.4; d = 16 56.7 and 52.5, 76.7 and 68.6; r = 512, d = 8 40.3 and 39.5, 56.1 and 65.4
+//   9000 x 2048  r = 512, d = 8 40.5 and 39.9, 60.6 and 73.2; seven matrices of 5120 and 13824 rows and columns 292 and 319
 // Beyond r = 1024, where the lists are a few steps long, it is on a par with k_compress_gq, and behind it for short lists on 4096 and 8192 rows: r = 2048,
 //   4096 x 4096  d = 4 53.3 and 49.9, d = 8 58.8 and 55.4, d = 16 73.2 and 71.2; 5120 x 5120 77.0 and 80.1, 87.5 and 88.1, 109.4 and 113.3
 //   4096 x 16384 110 and 103, 120 and 114, 153 and 156; r = 1536, d = 8 4096 x 4096 47.9 and 50.9, 8192 x 8192 128 and 133

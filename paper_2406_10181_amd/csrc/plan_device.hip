@@ -307,7 +307,7 @@ __device__ __forceinline__ void deal_p(uint8_t* __restrict__ plan, const PlanLay
 
 // Sorts the lists of a chunk by length, longest first and equal lengths in their order, as the host's stable sort does: a stable radix sort
 // over the length, 8 bits at a time (lengths are at most `most`, hardly ever 256 or more).  Wave w has places (w per + i) 64 + lane, i < per, before and
-// after; a key is length * kLists + list.  What bounds it is the chain of barriers (seven a round).  The bitonic sorts before it had 45 stages for
+// after; a key is length * kLists + list.  What bounds it is the chain of barriers (six a round).  The bitonic sorts before it had 45 stages for
 // 512 lists and 66, a barrier each, for 2048: the build for 4096 x 4096, r = 2048, d = 8 took 53 us with them.
 constexpr int kLists = kMaxSlots * kThreadsGQ, kSortBits = 8;
 __device__ __forceinline__ void sort_by_length(uint32_t (&key)[kMaxSlots], int per, int most, uint32_t* s_key, int32_t* s_count, int32_t* part) {

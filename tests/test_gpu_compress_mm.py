@@ -47,7 +47,8 @@ SHAPES = [
     (40, 2500, 2048, "uniform"), (50, 4096, 20, "zipf"),          # all tiles of a wave; shared columns
     (2048, 264, 48, "uniform"), (2049, 264, 48, "zipf"),          # the last with blocks of 8 rows, the first with blocks of 16
     (4081, 520, 64, "uniform"), (4096, 2056, 96, "zipf"),         # one 16-row block a workgroup
-    (4097, 300, 33, "uniform"), (6544, 67, 33, "uniform"),        # a last round of one block, and a little over half full
+    (4097, 300, 33, "uniform"), (6144, 67, 33, "uniform"),        # three rounds of 8-row blocks, where those of 16 would take two: the first rows and the last
+    (6145, 67, 33, "uniform"), (6544, 67, 33, "uniform"),         # two rounds of 16-row blocks, a little over half full
     (6545, 67, 33, "uniform"), (8192, 264, 48, "zipf"),           # two 16-row blocks a workgroup, not for all and for all; n % 8 != 0
     (4096, 300, 1024, "uniform"), (4096, 2100, 1024, "zipf"),     # the most columns 16-row blocks are used for; some of them shared
     (2061, 10245, 1024, "hot"),                                   # more than 1535 lists: the sums of 16 rows do not fit the LDS, blocks go in halves
@@ -142,7 +143,8 @@ def _group(dps, r, d, plans=None):
 
 
 @pytest.mark.parametrize("shapes,r,d", [
-    ([(5120, 264, "uniform")] * 2, 48, 1),                                           # the second round of the 16-row blocks: a quarter full, and half
+    ([(5120, 264, "uniform")] * 2, 48, 1),                                           # 8-row blocks alone, three rounds of 16-row blocks together
+    ([(2500, 264, "uniform"), (2600, 300, "zipf")], 96, 4),                          # 16-row blocks alone, three rounds of 8-row blocks together
     ([(5120, 2056, "zipf"), (2112, 264, "uniform"), (2112, 2050, "uniform")], 512, 8),   # a round of 8-row blocks each; n % 8 != 0 for one
     ([(40, 2500, "uniform"), (2048, 264, "uniform"), (4096, 300, "uniform")], 1024, 2),   # 8-row blocks alone, 16-row blocks together
     ([(300, 520, "uniform"), (1001, 10240, "hot"), (4096, 264, "uniform")], 1024, 1),    # sums of 16 rows that fit the LDS, and some that go in halves
