@@ -1,10 +1,10 @@
 // Compress, kernel A for bf16: T = G Q on the matrix cores.  See compress.hip for the path as a whole.
 //
 // A column of T is a sum over a list of (column of G, value), and the lists share nothing, so this is no matrix product.  But
-// v_mfma_f32_4x4x4_16b_bf16 is 16 independent products [4 x 4] [4 x 4], and each can serve a list: its A operand is four columns of G
-// from the list (4 rows; gathered by transposing LDS reads, which hand a lane one row's four values), its B operand their four values
-// as three bf16 parts that add up, each times its power of two, to the fp32 value exactly (in three of its columns).  So a product of 16 bits by 24 is taken exactly, and
-// the three sums are added at the end: the error against 64 bits is 0.3 to 0.6 of that of a chain of fp32 FMAs.  An instruction does
+// v_mfma_f32_4x4x4_16b_bf16 is 16 independent products [4 x 4] [4 x 4], and each can serve a list: its A operand is four values from the list
+// as three bf16 parts that add up, each times its power of two, to the fp32 value exactly (in three of its rows), its B operand their four columns
+// of G (4 rows; gathered by transposing LDS reads, which hand a lane one row's four values).  So a product of 16 bits by 24 is taken exactly, and
+// the three sums, which a lane has for its row side by side, are added at the end: the error against 64 bits is 0.3 to 0.6 of that of a chain of fp32 FMAs.  An instruction does
 // 4 rows x 64 entries; the vector ALUs took 8 widenings and FMAs for 8 rows x 64 entries.
 //
 // One workgroup a CU, persistent: 8 waves walk the lists (the plan's tiles: lsp_internal.h), 4 fetch and stage the next chunk of G.
@@ -169,8 +169,9 @@ __device__ __forceinline__ void walk_tiles(WaveChunk& w, uint8_t* sums, bool fir
     const int part = lane & 3;
     f32x4 D[2][NP];                                                   // [set of 16 lists][plane]
     int t = 0;
-    // The tile's sums join those of the chunks before.  Lanes 0 to 2 of a 4-lane group have the sums over the three parts of the values,
-    // four rows of each plane.  Products with the unit vectors turn lanes into registers, so that lane q has the three sums of row q.
+    // The tile's sums join those of the chunks before.  Lane q of a 4-lane group has the sums over the three parts of the values for row q of each plane, in three
+    // registers (the fourth holds what the offsets gave).  With G as the A operand the parts would lie in three lanes, and took 16 more products a set to be brought
+    // together: seven matrices of a 6.7B layer 403 -> 393 us, 4096 x 16384, skewed columns, 76.7 -> 73.3, 4096 x 4096, r = 2048, 98.1 -> 94.2 (steps and compress calls).
     Piece* dst[2];
     Piece before[2];                                                  // asked for when the tile begins
     auto begin = [&]() {
@@ -189,37 +190,20 @@ __device__ __forceinline__ void walk_tiles(WaveChunk& w, uint8_t* sums, bool fir
         Piece minus[2];
         float odd = 0.0f;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            f32x4 X[NP];
-#pragma unroll
-            for (int q = 0; q < 4; ++q)                               // (plane by plane they would wait for each other)
-#pragma unroll
-                for (int p = 0; p < NP; ++p)
-                    X[p] = __builtin_amdgcn_mfma_f32_4x4x1f32(D[h][p][q], part == q ? 1.0f : 0.0f, q == 0 ? f32x4{0.0f, 0.0f, 0.0f, 0.0f} : X[p], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int p = 0; p < NP; ++p) {
-                minus[h][p] = minus_sum_of_parts(X[p][0], X[p][1], X[p][2]);
+                minus[h][p] = minus_sum_of_parts(D[h][p][0], D[h][p][1], D[h][p][2]);
                 odd += fabsf(minus[h][p]);
             }
-        }
-        // An infinity in G meets zeros among the lower parts, and above the unit vectors' zeros: then the rows are added up one by one,
-        // and where the sum is no number the first part alone says what becomes of it.  (Nothing says it for values below 2^-133, whose first part
-        // is zero: an infinity times one of them is NaN.)  An infinite sum stays one: the first part may be finite where the value's product is not.
+        // An infinity in G meets zeros among the lower parts: where the sum is no number the first part alone says what becomes of it.  (Nothing says
+        // it for values below 2^-133, whose first part is zero: an infinity times one of them is NaN.)  An infinite sum stays one: the first part may
+        // be finite where the value's product is not.
         if (__builtin_expect(__any(!(odd < __builtin_inff())), 0)) {
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int p = 0; p < NP; ++p) {
-                    float own, head;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float y = D[h][p][q], first = quad_lane<0>(y), sum = minus_sum_of_parts(first, quad_lane<1>(y), quad_lane<2>(y));
-                        own = q == 0 || part == q ? sum : own;
-                        head = q == 0 || part == q ? first : head;
-                    }
-                    minus[h][p] = own == own ? own : -head;
-                }
+                for (int p = 0; p < NP; ++p) minus[h][p] = minus[h][p] == minus[h][p] ? minus[h][p] : -D[h][p][0];
         }
         *dst[0] = before[0] - minus[0];
         *dst[1] = before[1] - minus[1];
@@ -251,7 +235,7 @@ __device__ __forceinline__ void walk_tiles(WaveChunk& w, uint8_t* sums, bool fir
             s16x4 v;
             __builtin_memcpy(&v, &x, 8);
 #pragma unroll
-            for (int p = 0; p < NP; ++p) D[h][p] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(g[k & 1][h][p], v, D[h][p], 0, 0, 0);
+            for (int p = 0; p < NP; ++p) D[h][p] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(v, g[k & 1][h][p], D[h][p], 0, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
         if (refill) w.ring[k] = w.ahead[k * kWave];

@@ -74,7 +74,7 @@ __host__ __device__ static inline uint32_t chunk_unit_offset(uint32_t j) { retur
 // tiles of 32; they are dealt to 8 waves in rounds, some backwards (tile_of_wave), so that the waves get about the same number of
 // steps.  A step is four entries of every list of a tile: 64 x 16 bytes, the first 8 for lists 0..15 and the others for 16..31.
 // In each half, with 4-lane group b = lane / 4 and s = lane % 4:
-//   s < 3    part s of the values of list b's four entries (value_parts, bf16 each: the B operand as it is)
+//   s < 3    part s of the values of list b's four entries (value_parts, bf16 each: the A operand as it is)
 //   s = 3    the LDS offsets of entry b % 4 of the four lists b / 4 * 4 .. + 3 (the transposing LDS read takes the entries of
 //            a list from lanes 4 apart)
 // A list shorter than the tile's longest is filled up with zero values at the always-zero unit.
