@@ -7,13 +7,17 @@
 // the three sums, which a lane has for its row side by side, are added at the end: the error against 64 bits is 0.3 to 0.6 of that of a chain of fp32 FMAs.  An instruction does
 // 4 rows x 64 entries; the vector ALUs took 8 widenings and FMAs for 8 rows x 64 entries.
 //
-// One workgroup a CU, persistent: 8 waves walk the lists (the plan's tiles: lsp_internal.h), 4 fetch and stage the next chunk of G.
-// 4096 x 16384, r = 512, d = 8, skewed columns: 91.0 -> 77.9 us with kernel B; 4096 x 11008: 52.6 -> 50.7; a 6.7B layer's seven matrices
-// 234 -> 216; 3001 x 2999, r = 250, d = 5: 22.7 -> 20.9.
-// What bounds it (11008 x 4096, cycles of a chunk, some 14000): the walk 10700, of it LDS reads at random 8-byte units, 7.6 cycles each instead of
-// 2.7 (alone 8700), the plan from L2 behind the loads of G (alone 7500), adding up the tiles 1900; staging 900; storing T 1000 a block.
-// Entries ordered against bank conflicts make the reads 1.7 times as fast and the kernel 3 to 4 % (the plan's loads remain), for a plan build
-// that costs more than it gives; 512 threads and 8 rows, twice a CU, or 12 walking waves and narrower tiles were 2 to 8 % slower.
+// One workgroup a CU, persistent: 8 waves walk the lists (the plan's tiles: lsp_internal.h), 4 fetch and stage the next chunk of G and look up what the
+// walkers have to know of it.  A block's 16 rows of a column lie side by side in LDS, 32 bytes: the values of a list are given to four blocks of the
+// instruction (cbsz, abid), each with four of the rows, so that 16 lanes gather from four units instead of 16, and meet on a bank less often (5.1 cycles a
+// read; from planes of 8 bytes a column 7.1, without conflicts 2.5).
+// 11008 x 4096, cycles of a chunk, some 11300: staging 1300, with the walkers idle; the walk 7700 to 9000 (the two walking waves of a SIMD do not keep step), of it
+// the LDS 5900, 1300 for two or three tiles' ends, some 40 instructions a step and wave; storing T 1250 a block.  No single thing bounds it: of 158 us for the
+// seven matrices of a 6.7B layer 24 go without G, 18 without the plan's loads, 15 without bank conflicts, 14 without the ends of tiles, 11 without products, 10 without
+// LDS reads; and under it the clock goes down from 2.4 to 1.95 GHz, so that whatever is left out helps the rest.  How far ahead the plan is asked for does not matter (4
+// to 10 steps).  (us with that kernel alone, before -> with 32-byte units, chunks that begin with their steps in registers, and notes: 166 -> 155; 4096 x 16384, r = 512, d = 8,
+// skewed columns 65.5 -> 64; 4096 x 4096, r = 2048 33.5 -> 29; 4096 x 11008 42.4 -> 39.)
+// 512 threads and 8 rows, twice a CU, or 12 walking waves and narrower tiles were 2 to 8 % slower; LDS atomics for the sums twice as slow.
 #include <algorithm>
 
 #include "compress_common.h"
@@ -22,16 +26,36 @@ namespace lsp {
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 #define LSP_LDS_AS __attribute__((address_space(3)))
+#define LSP_GLOBAL_AS __attribute__((address_space(1)))               // (of addresses that went through LDS the compiler would not know it)
 
-constexpr int kPlaneBytes = (kChunk + 1) * 8;                         // 8-byte units of a plane; the last one stays zero
 constexpr int kLdsMM = 160 * 1024;
 constexpr int kWalkers = kWavesMM * kWave;                            // threads that walk the lists
 constexpr int kFetchers = kChunk / 8;                                 // threads that fetch and stage G
 constexpr int kThreadsMM = kWalkers + kFetchers;
 constexpr int kResidentMM = 256;                                      // one workgroup a CU
 
-template <int NP> constexpr int kRowsMM = 4 * NP;                     // rows of a block: NP planes of 4
-template <int NP> constexpr int kTileBase = (NP * kPlaneBytes + 15) / 16 * 16;   // LDS offset of the sums
+// A block is 4 NP rows.  In LDS a column of a chunk is a unit of 8 NP bytes (its rows side by side); a unit behind the last one stays zero.
+template <int NP> constexpr int kRowsMM = 4 * NP;
+template <int NP> constexpr int kUnitBytes = 8 * NP;
+template <int NP> constexpr int kNoteBase = (kChunk + 1) * kUnitBytes<NP>;       // LDS offset of the notes on the present chunk and the next
+// What the fetching waves, which have the time to look it up, tell the walking ones about a chunk: found out by the walkers themselves, one dependent scalar load
+// after the other, it took them 2000 cycles a block and 300 a chunk (of some 11000).
+struct ChunkNote {
+    uint32_t cols[kWavesMM][kSetCols][kWaveTiles];                    // as in the plan (off_m_cols)
+    TileSeg seg[kWavesMM];                                            // as in the plan (off_m_seg)
+    uint64_t steps[2][kWavesMM];                                      // where each wave's steps lie: of the chunk after it, and its own
+    float* T;                                                         // the block's rows
+    const uint8_t* plan;
+    uint32_t vcol, vcnt;                                              // offsets of these tables in the plan
+    int32_t rows, pad0;                                               // rows of the block inside the matrix
+    int32_t nvcols;                                                   // virtual columns
+    uint32_t flags, pad1[2];
+};
+constexpr uint32_t kFirstChunk = 1, kLastChunk = 2, kMoreChunks = 4, kSharedColumns = 8;
+static_assert(sizeof(ChunkNote) % 16 == 0 && sizeof(TileSeg) == 32, "read in pieces of 16 bytes");
+template <int NP> constexpr int kSumsBase = kNoteBase<NP> + 2 * (int)sizeof(ChunkNote);   // ... and of the sums
+// Floats from a row of the sums to the next: 16 rows of a column lie in 16 different banks, and four columns are 16 bytes.
+__device__ __forceinline__ int sums_stride(int nvcols) { return (nvcols + kTileCols - 1) / kTileCols * kTileCols + 4; }
 
 // Rows 2k and 2k+1 of two adjacent columns sit in the dwords a (row 2k) and b (row 2k+1); the unit
 // of the even column takes their low halves, that of the odd column their high halves (one byte permute).
@@ -102,55 +126,38 @@ template <int NH, bool WHOLE> struct RowStager {
                 for (int k = 0; k < 2; ++k) unit[p][q][k] = row_pair(pre[4 * p + 2 * k][q >> 1], pre[4 * p + 2 * k + 1][q >> 1], q & 1);
     }
 };
-template <int NH> __device__ __forceinline__ void put_units(uint8_t* smem, const u32x2 (&unit)[NH][8], int tid) {
+template <int NP> __device__ __forceinline__ void zero_unit(uint8_t* smem, int tid) {
+    if (tid < NP) *reinterpret_cast<u32x2*>(smem + kChunk * kUnitBytes<NP> + tid * 8) = u32x2{0, 0};
+}
+// rows 4 NH half .. of a block's NP planes
+template <int NP, int NH> __device__ __forceinline__ void put_units(uint8_t* smem, const u32x2 (&unit)[NH][8], int half, int tid) {
+    static_assert(NH == 1 || NH == 2, "8 or 16 bytes");
 #pragma unroll
-    for (int p = 0; p < NH; ++p)
-#pragma unroll
-        for (int q = 0; q < 8; ++q)                                   // local column 8 tid + q
-            *reinterpret_cast<u32x2*>(smem + p * kPlaneBytes + (q * (kChunk / 8) + tid) * 8) = unit[p][q];
+    for (int q = 0; q < 8; ++q) {                                     // local column 8 tid + q
+        uint8_t* dst = smem + (q * (kChunk / 8) + tid) * kUnitBytes<NP> + half * (NH * 8);
+        if constexpr (NH == 2) *reinterpret_cast<u32x4*>(dst) = u32x4{unit[0][q].x, unit[0][q].y, unit[1][q].x, unit[1][q].y};
+        else *reinterpret_cast<u32x2*>(dst) = unit[0][q];
+    }
 }
 
-template <int CTRL> __device__ __forceinline__ float quad_lane(float x) {   // x of lane CTRL of this lane's four
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL * 0x55, 0xF, 0xF, true));
-}
 template <int CTRL> __device__ __forceinline__ uint32_t quad_lane(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL * 0x55, 0xF, 0xF, true);
 }
 
-// What a wave does in one chunk, with its first steps in registers.
-struct WaveChunk {
-    const u32x4* ahead;                                               // this lane's place kStepsAhead steps further on
-    int steps;
-    uint64_t len_lo, len_hi;                                          // steps of each of its tiles, 16 bits each
-    u32x4 col_lo, col_hi;                                             // virtual columns of lists lane / 4 and 16 + lane / 4 of each tile, 16 bits each
-    u32x4 ring[kStepsAhead];
-    __device__ __forceinline__ void look_up(const uint8_t* plan, PlanHeaderPtr H, int c, int wave, int lane) {
-        const auto* seg = as_const<uint64_t>(plan + H->off_m_seg) + ((size_t)c * kWavesMM + wave) * (sizeof(TileSeg) / 8);
-        const u32x4* cols = reinterpret_cast<const u32x4*>(plan + H->off_m_cols) + (((size_t)c * kWavesMM + wave) * kSetCols + (lane >> 2)) * (kWaveTiles / 4);
-        const uint64_t where = seg[0];
-        len_lo = seg[1]; len_hi = seg[2];
-        steps = (int)(where >> 32);
-        const u32x4* at = reinterpret_cast<const u32x4*>(plan + H->off_m_steps) + (size_t)(uint32_t)where * kWave + lane;
-#pragma unroll
-        for (int q = 0; q < kStepsAhead; ++q) ring[q] = at[q * kWave];
-        col_lo = cols[0]; col_hi = cols[1];
-        ahead = at + kStepsAhead * kWave;
-    }
-    __device__ __forceinline__ int length(int t) const {              // (uniform)
-        static_assert(kWaveTiles == 8, "two words");
-        return t < kWaveTiles ? (int)(((t < 4 ? len_lo : len_hi) >> (16 * (t & 3))) & 0xFFFF) : 0;
-    }
-    __device__ __forceinline__ uint32_t columns(int t) const {
-        const u32x4 x = t & 4 ? col_hi : col_lo;
-        const uint32_t a = t & 1 ? x.y : x.x, b = t & 1 ? x.w : x.z;
-        return t & 2 ? b : a;
-    }
-};
+// One of the two offsets in a word, times SCALE, plus add: one instruction.
+template <int SCALE, bool HIGH> __device__ __forceinline__ uint32_t unit_at(uint32_t two, uint32_t add) {
+    uint32_t at;
+    if constexpr (HIGH) asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(at) : "v"(two), "n"(SCALE), "v"(add));
+    else asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(at) : "v"(two), "n"(SCALE), "v"(add));
+    return at;
+}
 
-// Piece x (rows x, x + 4, ...) of a virtual column's sums, in LDS: the four pieces side by side, rotated so that the lanes of a
-// wave that read the same piece of neighbouring columns meet all banks.
-template <int R> __device__ __forceinline__ uint8_t* piece_of(uint8_t* sums, uint32_t v, uint32_t x) {
-    return sums + v * (R * 4) + ((x + v / (256 / (R * 4))) & 3) * R;
+// Of the 16 values x that the 4-lane groups hold (one each: lists 0 .. 15), that of list NP (lane / (4 NP)) + a: list a of the NP lists
+// that share a lane's 4 NP rows.
+template <int NP, int A> __device__ __forceinline__ uint32_t list_of(uint32_t x) {
+    if constexpr (NP == 4) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x150 + 4 * A, 0xF, 0xF, true);          // row_newbcast
+    else if constexpr (A == 0) return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x114, 0xF, 0xA, false);   // row_shr:4, odd groups
+    else return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x104, 0xF, 0x5, false);                         // row_shl:4, even groups
 }
 
 // The sum of a list from the sums over the parts of its values, with the other sign: an FMA that subtracts is not written onto its addend, and as one
@@ -161,145 +168,40 @@ __device__ __forceinline__ float minus_sum_of_parts(float first, float second, f
     return fmaf(rest, -1.0f / (1 << kPartShift[1]), -first);
 }
 
-// A wave's tiles of one staged chunk.
-template <int NP>
-__device__ __forceinline__ void walk_tiles(WaveChunk& w, uint8_t* sums, bool first_chunk, int mytiles, int lane) {
-    constexpr int R = kRowsMM<NP>;
-    typedef float Piece __attribute__((ext_vector_type(NP)));
-    const int part = lane & 3;
-    f32x4 D[2][NP];                                                   // [set of 16 lists][plane]
-    int t = 0;
-    // The tile's sums join those of the chunks before.  Lane q of a 4-lane group has the sums over the three parts of the values for row q of each plane, in three
-    // registers (the fourth holds what the offsets gave).  With G as the A operand the parts would lie in three lanes, and took 16 more products a set to be brought
-    // together: seven matrices of a 6.7B layer 403 -> 393 us, 4096 x 16384, skewed columns, 76.7 -> 73.3, 4096 x 4096, r = 2048, 98.1 -> 94.2 (steps and compress calls).
-    Piece* dst[2];
-    Piece before[2];                                                  // asked for when the tile begins
-    auto begin = [&]() {
-        const s16x4 none = {0, 0, 0, 0};
-        const uint32_t cols = w.columns(t);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-#pragma unroll
-            for (int p = 0; p < NP; ++p) D[h][p] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(none, none, f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);   // (one instruction, not four)
-            dst[h] = reinterpret_cast<Piece*>(piece_of<R>(sums, h ? cols >> 16 : cols & 0xFFFFu, (uint32_t)part));
-            before[h] = Piece(0.0f);
-        }
-        if (!first_chunk) { before[0] = *dst[0]; before[1] = *dst[1]; }
-    };
-    auto flush = [&]() {
-        Piece minus[2];
-        float odd = 0.0f;
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int p = 0; p < NP; ++p) {
-                minus[h][p] = minus_sum_of_parts(D[h][p][0], D[h][p][1], D[h][p][2]);
-                odd += fabsf(minus[h][p]);
-            }
-        // An infinity in G meets zeros among the lower parts: where the sum is no number the first part alone says what becomes of it.  (Nothing says
-        // it for values below 2^-133, whose first part is zero: an infinity times one of them is NaN.)  An infinite sum stays one: the first part may
-        // be finite where the value's product is not.
-        if (__builtin_expect(__any(!(odd < __builtin_inff())), 0)) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int p = 0; p < NP; ++p) minus[h][p] = minus[h][p] == minus[h][p] ? minus[h][p] : -D[h][p][0];
-        }
-        *dst[0] = before[0] - minus[0];
-        *dst[1] = before[1] - minus[1];
-        ++t;
-    };
-    const uint32_t pick = (part & 1 ? 0x0C0C0302u : 0x0C0C0100u) + (part & 2 ? 0x0404u : 0u);   // bytes of this lane's offset among the four
-    // The gathers of a step are asked for before the products of the step before; a slot is free, and takes the step kStepsAhead further
-    // on, when its values have been used.  The barriers keep the compiler from waiting for each gather by itself and from giving
-    // the refills registers of their own, which a loop would have to move.
-    s16x4 g[2][2][NP];
-    auto gather = [&](int k) {
-        uint32_t off[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) off[h] = __builtin_amdgcn_perm(quad_lane<3>(w.ring[k][2 * h + 1]), quad_lane<3>(w.ring[k][2 * h]), pick);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            LSP_LDS_AS uint8_t* src = (LSP_LDS_AS uint8_t*)(uintptr_t)off[h];   // (the planes start where the LDS starts)
-#pragma unroll
-            for (int p = 0; p < NP; ++p) g[k & 1][h][p] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LSP_LDS_AS s16x4*)(src + p * kPlaneBytes));
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0xC07F | (2 * NP << 8));           // lgkmcnt(2 NP): what was asked for before is there
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto multiply = [&](int k, bool refill, uint32_t ends) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const u32x2 x = {w.ring[k][2 * h], w.ring[k][2 * h + 1]};
-            s16x4 v;
-            __builtin_memcpy(&v, &x, 8);
-#pragma unroll
-            for (int p = 0; p < NP; ++p) D[h][p] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(v, g[k & 1][h][p], D[h][p], 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (refill) w.ring[k] = w.ahead[k * kWave];
-        if (__builtin_expect((ends >> k) & 1, 0)) {
-            flush();
-            begin();
-        }
-    };
-    // which of the next kStepsAhead steps are the last of their tiles
-    int end = w.length(0), coming = 1;                                // the present tile's last step from here on, counted from 1
-    auto tile_ends = [&]() {
-        uint32_t ends = 0;
-        while (end <= kStepsAhead) {
-            ends |= 1u << (end - 1);
-            const int len = w.length(coming++);
-            if (len == 0) { end = 1 << 30; break; }
-            end += len;
-        }
-        end -= kStepsAhead;
-        return ends;
-    };
-    begin();
-    if (w.steps > 0) gather(0);
-    for (int n = (w.steps - 1) / kStepsAhead; n > 0; --n) {
-        const uint32_t ends = tile_ends();
-#pragma unroll
-        for (int k = 0; k < kStepsAhead; ++k) {
-            gather((k + 1) % kStepsAhead);
-            multiply(k, true, ends);
-        }
-        w.ahead += kStepsAhead * kWave;
-    }
-    const int rest = w.steps > 0 ? (w.steps - 1) % kStepsAhead + 1 : 0;
-    const uint32_t ends = rest > 0 ? tile_ends() : 0;
-#pragma unroll
-    for (int k = 0; k < kStepsAhead; ++k) {
-        if (k + 1 < rest) gather((k + 1) % kStepsAhead);
-        if (k < rest) multiply(k, false, ends);
-    }
-    if (first_chunk)
-        while (t < mytiles) { flush(); begin(); }                     // tiles without an entry in this chunk: their sums start at zero
-}
-
-// The sums of a block go out: a thread has one of the four pieces of a column at a time.
+// The sums of a block go out: a wave a row at a time, or, where columns have several owners (which lie side by side, and are added in their order), a thread a quarter of a column.
 template <int R>
-__device__ __forceinline__ void store_sums(uint8_t* sums, const uint8_t* plan, PlanHeaderPtr H, float* __restrict__ T, int64_t i0, int m, int r, int tid) {
-    constexpr int Q = R / 4;
-    typedef float Piece __attribute__((ext_vector_type(Q)));
-    const bool shared = H->q_any_shared != 0;
-    const auto* vcol = as_const<uint16_t>(plan + H->off_q_vcol);
-    const auto* vcnt = as_const<uint16_t>(plan + H->off_q_vcnt);
-    const int x = tid / (kWalkers / 4), V = H->nvcols;
-    for (int v = tid % (kWalkers / 4); v < V; v += kWalkers / 4) {
-        Piece out = *reinterpret_cast<const Piece*>(piece_of<R>(sums, v, x));
-        int b = v;
-        if (shared) {                                                 // the owners of a column sit side by side: added in their order
-            const int owners = vcnt[v];
+__device__ __forceinline__ void store_sums(const float* sums, int stride, float LSP_GLOBAL_AS* T, const uint16_t LSP_GLOBAL_AS* vcol, const uint16_t LSP_GLOBAL_AS* vcnt,
+                                           bool shared, int V, int rows, int r, int tid) {
+    if (shared) {
+        constexpr int Q = R / 4;
+        const int row0 = tid / (kWalkers / 4) * Q;
+        sums += row0 * stride;
+        T += row0 * (int64_t)r;
+        for (int v = tid % (kWalkers / 4); v < V; v += kWalkers / 4) {
+            const int owners = vcnt[v], b = vcol[v] & 0x7FFF;
             if (owners == 0) continue;
-            b = vcol[v] & 0x7FFF;
-            for (int o = 1; o < owners; ++o) out += *reinterpret_cast<const Piece*>(piece_of<R>(sums, v + o, x));
-        }
+            float out[Q];
 #pragma unroll
-        for (int q = 0; q < Q; ++q)
-            if (i0 + 4 * q + x < m) T[(i0 + 4 * q + x) * (int64_t)r + b] = out[q];
+            for (int q = 0; q < Q; ++q) out[q] = sums[q * stride + v];
+#pragma unroll 4
+            for (int o = 1; o < owners; ++o)
+#pragma unroll
+                for (int q = 0; q < Q; ++q) out[q] += sums[q * stride + v + o];
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (row0 + q < rows) T[q * (int64_t)r + b] = out[q];
+        }
+        return;
+    }
+    const int lane = tid & (kWave - 1);
+    for (int row = tid / kWave; row < R && row < rows; row += kWavesMM) {
+        const float* src = sums + row * stride;
+        float LSP_GLOBAL_AS* dst = T + row * (int64_t)r;
+        if ((r & 3) == 0) {
+            for (int v = lane * 4; v < V; v += kWave * 4) *(f32x4 LSP_GLOBAL_AS*)(dst + v) = *reinterpret_cast<const f32x4*>(src + v);
+        } else {
+            for (int v = lane; v < V; v += kWave) dst[v] = src[v];
+        }
     }
 }
 
@@ -329,7 +231,7 @@ template <int NP, bool HALVES> struct BlockWalk {
             visit(pr, H, planned);
             if (!planned) continue;
             nchunks = H->nchunks;
-            const bool fits = (H->nvcols + kTileCols - 1) / kTileCols * kTileCols * (kRowsMM<NP> * 4) <= kLdsMM - kTileBase<NP>;
+            const bool fits = sums_stride(H->nvcols) * (kRowsMM<NP> * 4) <= kLdsMM - kSumsBase<NP>;
             if (fits != HALVES) return;
         }
     }
@@ -341,53 +243,132 @@ template <int NP, bool HALVES> struct BlockWalk {
 template <int NP, bool WHOLE>
 __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, int d, int tid) {
     constexpr int R = kRowsMM<NP>, NH = NP / 2;
-    auto none = [](const RowBlocks&, PlanHeaderPtr, bool) {};
+    // (every block is passed by or taken here, and its part of S cleared where that is to be done)
+    auto clear_s = [&](const RowBlocks& pr, PlanHeaderPtr H, bool planned) {
+        if (!planned) {                                               // not a plan for this problem
+            fill_s(pr.S, __builtin_nanf(""), r, pr.block, pr.blocks, tid, kFetchers);
+        } else if (H->p_any_split) fill_s(pr.S, 0.0f, r, pr.block, pr.blocks, tid, kFetchers);
+    };
     BlockWalk<NP, false> w;
     int c = 0;
     auto advance = [&]() {
-        if (++c >= w.nchunks) { c = 0; w.find(w.block + gridDim.x, blocks, r, d, none); }
+        if (++c >= w.nchunks) { c = 0; w.find(w.block + gridDim.x, blocks, r, d, clear_s); }
     };
     RowStager<NH, WHOLE> lo, hi;
     u32x2 ulo[NH][8], uhi[NH][8];
+
+    // The coming chunk's note, with the table of its columns: found out while the chunk before is walked.
+    u32x4 cols, seg;                                                  // this thread's part of the tables
+    uint32_t first_step = 0;                                          // threads 0 .. 7: a wave's first step in the chunk after, 8 .. 15: in this one
+    const uint8_t *steps_here, *steps_after;
+    struct { float* T; const uint8_t* plan; uint32_t vcol, vcnt, flags; int32_t rows, nvcols; } head;
+    int turn = 0;
+    static_assert(sizeof(ChunkNote::cols) == kFetchers * 16 && sizeof(ChunkNote::seg) == 16 * 16, "16 bytes a thread");
+    auto segs = [](const RowBlocks& pr, PlanHeaderPtr H, int chunk) { return pr.plan + H->off_m_seg + (size_t)chunk * (kWavesMM * sizeof(TileSeg)); };
+    auto look_up = [&](const RowBlocks& pr, PlanHeaderPtr H, int nchunks, int chunk, int rows_of, int row0) {
+        cols = reinterpret_cast<const u32x4*>(pr.plan + H->off_m_cols)[(size_t)chunk * kFetchers + tid];
+        const uint8_t* here = segs(pr, H, chunk);
+        if (tid < 16) seg = reinterpret_cast<const u32x4*>(here)[tid];
+        if (tid >= kWavesMM && tid < 2 * kWavesMM) first_step = reinterpret_cast<const TileSeg*>(here)[tid - kWavesMM].first_step;
+        steps_here = steps_after = pr.plan + H->off_m_steps;
+        head.T = pr.T + (int64_t)row0 * r;
+        head.plan = pr.plan;
+        head.vcol = (uint32_t)H->off_q_vcol; head.vcnt = (uint32_t)H->off_q_vcnt;
+        head.rows = pr.m - row0 < rows_of ? pr.m - row0 : rows_of;
+        head.nvcols = H->nvcols;
+        head.flags = (chunk == 0 ? kFirstChunk : 0) | (chunk + 1 == nchunks ? kLastChunk : 0) | (H->q_any_shared ? kSharedColumns : 0);
+    };
+    auto look_after = [&](const RowBlocks& pr, PlanHeaderPtr H, int chunk) {   // the chunk after the one above
+        if (tid < kWavesMM) first_step = reinterpret_cast<const TileSeg*>(segs(pr, H, chunk))[tid].first_step;
+        steps_after = pr.plan + H->off_m_steps;
+        head.flags |= kMoreChunks;
+    };
+    auto put_note = [&]() {
+        ChunkNote* note = reinterpret_cast<ChunkNote*>(smem + kNoteBase<NP>) + turn;
+        turn ^= 1;
+        reinterpret_cast<u32x4*>(note->cols)[tid] = cols;
+        if (tid < 16) {
+            reinterpret_cast<u32x4*>(note->seg)[tid] = seg;
+            (&note->steps[0][0])[tid] = (uint64_t)(uintptr_t)((tid < kWavesMM ? steps_after : steps_here) + (size_t)first_step * (kWave * 16));
+        }
+        if (tid == 0) {
+            note->T = head.T; note->plan = head.plan; note->vcol = head.vcol; note->vcnt = head.vcnt;
+            note->rows = head.rows; note->nvcols = head.nvcols; note->flags = head.flags;
+        }
+    };
+
     const RowBlocks start = problem_of(blockIdx.x);                   // nearly always the first: its rows are asked for before its plan is looked at
     lo.fetch(static_cast<const uint16_t*>(start.G), (int64_t)start.block * R, start.m, start.n, 0, tid);
     hi.fetch(static_cast<const uint16_t*>(start.G), (int64_t)start.block * R + R / 2, start.m, start.n, 0, tid);
-    w.find(blockIdx.x, blocks, r, d, none);
+    w.find(blockIdx.x, blocks, r, d, clear_s);
     bool have = w.block < blocks;
     if (have) {
         if (w.block != (int)blockIdx.x) {
             lo.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R, w.pr.m, w.pr.n, c, tid);
             hi.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R + R / 2, w.pr.m, w.pr.n, c, tid);
         }
+        look_up(w.pr, w.H, w.nchunks, c, R, w.pr.block * R);
         lo.arrange(ulo); hi.arrange(uhi);
         advance();
-        if (w.block < blocks) lo.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R, w.pr.m, w.pr.n, c, tid);
+        if (w.block < blocks) {
+            look_after(w.pr, w.H, c);
+            lo.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R, w.pr.m, w.pr.n, c, tid);
+        }
+        put_note();
+        __syncthreads();                                              // the first note is there
     }
     while (have) {
-        put_units<NH>(smem, ulo, tid);
-        put_units<NH>(smem + NH * kPlaneBytes, uhi, tid);
+        put_units<NP, NH>(smem, ulo, 0, tid);
+        put_units<NP, NH>(smem, uhi, 1, tid);
         __syncthreads();                                              // staged
         have = w.block < blocks;
         if (have) {
+            look_up(w.pr, w.H, w.nchunks, c, R, w.pr.block * R);
             hi.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R + R / 2, w.pr.m, w.pr.n, c, tid);
             lo.arrange(ulo);
             advance();
+            const bool more = w.block < blocks;
+            if (more) look_after(w.pr, w.H, c);
             hi.arrange(uhi);
-            if (w.block < blocks) lo.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R, w.pr.m, w.pr.n, c, tid);
+            put_note();
+            if (more) lo.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R, w.pr.m, w.pr.n, c, tid);
         }
         __syncthreads();                                              // no longer read
     }
     if constexpr (NP == 4) {
-        BlockWalk<NP, true> h;
-        for (h.find(blockIdx.x, blocks, r, d, none); h.block < blocks; h.find(h.block + gridDim.x, blocks, r, d, none))
-            for (int part = 0; part < 2; ++part)
-                for (int k = 0; k < h.nchunks; ++k) {
-                    lo.fetch(static_cast<const uint16_t*>(h.pr.G), (int64_t)h.pr.block * R + part * (R / 2), h.pr.m, h.pr.n, k, tid);
-                    lo.arrange(ulo);
-                    put_units<NH>(smem, ulo, tid);
-                    __syncthreads();
-                    __syncthreads();
+        auto none = [](const RowBlocks&, PlanHeaderPtr, bool) {};
+        BlockWalk<NP, true> h, following;                             // the present block and the one after it
+        int part = 0, k = 0;
+        h.find(blockIdx.x, blocks, r, d, none);
+        if (h.block >= blocks) return;
+        following.find(h.block + gridDim.x, blocks, r, d, none);
+        turn = 0;
+        auto tell = [&]() {
+            look_up(h.pr, h.H, h.nchunks, k, R / 2, h.pr.block * R + part * (R / 2));
+            if (k + 1 < h.nchunks) look_after(h.pr, h.H, k + 1);
+            else if (part == 0) look_after(h.pr, h.H, 0);
+            else if (following.block < blocks) look_after(following.pr, following.H, 0);
+            put_note();
+        };
+        __syncthreads();                                              // nobody reads the last note of the other blocks any more
+        tell();
+        __syncthreads();                                              // the first note is there
+        while (h.block < blocks) {
+            lo.fetch(static_cast<const uint16_t*>(h.pr.G), (int64_t)h.pr.block * R + part * (R / 2), h.pr.m, h.pr.n, k, tid);
+            lo.arrange(ulo);
+            put_units<2, 2>(smem, ulo, 0, tid);
+            zero_unit<2>(smem, tid);                                  // (inside the larger units)
+            __syncthreads();                                          // staged
+            if (++k == h.nchunks) {
+                k = 0;
+                if (part ^= 1; part == 0) {
+                    h = following;
+                    if (h.block < blocks) following.find(h.block + gridDim.x, blocks, r, d, none);
                 }
+            }
+            if (h.block < blocks) tell();
+            __syncthreads();                                          // no longer read
+        }
     }
 }
 
@@ -398,48 +379,235 @@ __device__ __forceinline__ int tiles_of_wave(int V, int wave) {
     return count;
 }
 
-// Waves that walk the lists.
-template <int NP>
-__device__ __forceinline__ void walk_blocks(uint8_t* sums, int blocks, int r, int d, int tid) {
-    constexpr int R = kRowsMM<NP>;
-    const int lane = tid & (kWave - 1);
+constexpr int kRing = 8;                                              // steps of the plan a wave holds in registers (even)
+static_assert(kRing % 2 == 0 && kRing <= kStepsAhead, "the gathers take turns; so many steps are readable behind a plan's last");
+template <typename F, int... k> __device__ __forceinline__ void every_slot(F& f, std::integer_sequence<int, k...>) { (f(std::integral_constant<int, k>{}), ...); }
+
+// Waves that walk the lists, in blocks of 4 NP rows; HALVES: in blocks whose sums do not fit the LDS, of which they take 8 rows, then the other 8.
+//
+template <int NP, bool HALVES>
+__device__ __forceinline__ void walk_blocks(uint8_t* smem, int blocks, int r, int d, int tid) {
+    constexpr int NW = HALVES ? 2 : NP;                               // lists that share a lane's rows
+    constexpr int R = kRowsMM<NW>;
+    constexpr int kGroup = NW == 4 ? 2 : 1;                           // log2 of the blocks that one list's values go to
+    const int lane = tid & (kWave - 1), part = lane & 3;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    auto clear_s = [&](const RowBlocks& pr, PlanHeaderPtr H, bool planned) {
-        if (!planned) {                                               // not a plan for this problem
-            fill_s(pr.S, __builtin_nanf(""), r, pr.block, pr.blocks, tid, kWalkers);
-        } else if (H->p_any_split) fill_s(pr.S, 0.0f, r, pr.block, pr.blocks, tid, kWalkers);
+    float* const sums = reinterpret_cast<float*>(smem + kSumsBase<NP>);
+    const ChunkNote* note = reinterpret_cast<const ChunkNote*>(smem + kNoteBase<NP>);
+    auto column = [&](int i) { return note->cols[wave][lane >> 2][i]; };   // of this 4-lane group's two lists in tile i
+    BlockWalk<NP, HALVES> w;
+    w.find(blockIdx.x, blocks, r, d, [](const RowBlocks&, PlanHeaderPtr, bool) {});
+    if (w.block >= blocks) return;
+
+    // A chunk's steps lie one behind the other.  ring: the next kRing, from slot 0 on; those of the next chunk take the places of the last ones.
+    u32x4 ring[kRing];
+    const uint32_t lane16 = lane * 16;
+    auto step_at = [&](uint64_t steps, int k) { return *(const u32x4 LSP_GLOBAL_AS*)(steps + (uint64_t)k * (kWave * 16) + lane16); };
+    int stride, t = 0, steps;
+    uint32_t flags;
+    uint64_t ahead, next;                                                 // the present chunk's step that the next round begins with; the next chunk's first
+    uint64_t len_lo, len_hi;                                          // steps of each tile of the chunk, 16 bits each
+    auto length = [&](int i) {                                        // (uniform)
+        static_assert(kWaveTiles == 8, "two words");
+        return i < kWaveTiles ? (int)(((i < 4 ? len_lo : len_hi) >> (16 * (i & 3))) & 0xFFFF) : 0;
     };
-    WaveChunk t;
-    BlockWalk<NP, false> w, next;
-    w.find(blockIdx.x, blocks, r, d, clear_s);
-    if (w.block < blocks) t.look_up(w.pr.plan, w.H, 0, wave, lane);
-    while (w.block < blocks) {
-        const int mytiles = tiles_of_wave(w.H->nvcols, wave);
-        for (int c = 0; c < w.nchunks; ++c) {
-            const bool last = c + 1 == w.nchunks;
-            if (last) next.find(w.block + gridDim.x, blocks, r, d, clear_s);
-            __syncthreads();                                          // the chunk is staged
-            walk_tiles<NP>(t, sums, c == 0, mytiles, lane);
-            if (!last) t.look_up(w.pr.plan, w.H, c + 1, wave, lane);  // in flight while the next chunk is staged
-            else if (next.block < blocks) t.look_up(next.pr.plan, next.H, 0, wave, lane);
-            __syncthreads();                                          // all sums are there
+    // A tile's sums join those of the chunks before.  Lane l has the sums over the three parts of the values for row l % R of lists NW (l / R) + a, in three
+    // registers (the fourth holds what the offsets gave).  With G as the A operand the parts would lie in three lanes, and took 16 more products a set to be brought
+    // together: seven matrices of a 6.7B layer 403 -> 393 us, 4096 x 16384, skewed columns, 76.7 -> 73.3, 4096 x 4096, r = 2048, 98.1 -> 94.2 (steps and compress calls).
+    f32x4 D[2][NW];                                                   // [set of 16 lists][list of the NW that share these lanes' rows]
+    float LSP_LDS_AS* dst[2][NW];
+    float before[2][NW];                                              // asked for when the tile begins
+    uint32_t own_cols;                                                // columns of this 4-lane group's two lists in the next tile
+    auto places = [&](uint32_t both) {
+        const uint32_t mine = (uint32_t)kSumsBase<NP> + (lane & (R - 1)) * stride * 4;   // (LDS address)
+        auto place = [&](auto which) {
+            constexpr int a = decltype(which)::value;
+            const uint32_t x = list_of<NW, a>(both);
+            dst[0][a] = (float LSP_LDS_AS*)(uintptr_t)unit_at<4, false>(x, mine);
+            dst[1][a] = (float LSP_LDS_AS*)(uintptr_t)unit_at<4, true>(x, mine);
+        };
+        place(std::integral_constant<int, 0>{});
+        place(std::integral_constant<int, 1>{});
+        if constexpr (NW == 4) {
+            place(std::integral_constant<int, 2>{});
+            place(std::integral_constant<int, 3>{});
         }
-        store_sums<R>(sums, w.pr.plan, w.H, w.pr.T, (int64_t)w.pr.block * R, w.pr.m, r, tid);
-        w = next;
-    }
-    if constexpr (NP == 4) {                                          // more sums than the LDS has room for: 8 rows, then 8 rows
-        auto none = [](const RowBlocks&, PlanHeaderPtr, bool) {};
-        BlockWalk<NP, true> h;
-        for (h.find(blockIdx.x, blocks, r, d, none); h.block < blocks; h.find(h.block + gridDim.x, blocks, r, d, none))
-            for (int part = 0; part < 2; ++part) {
-                for (int c = 0; c < h.nchunks; ++c) {
-                    t.look_up(h.pr.plan, h.H, c, wave, lane);
-                    __syncthreads();
-                    walk_tiles<2>(t, sums, c == 0, tiles_of_wave(h.H->nvcols, wave), lane);
-                    __syncthreads();
-                }
-                store_sums<R / 2>(sums, h.pr.plan, h.H, h.pr.T, (int64_t)h.pr.block * R + part * (R / 2), h.pr.m, r, tid);
+    };
+    auto begin = [&]() {
+        const s16x4 none = {0, 0, 0, 0};
+        places(own_cols);
+        own_cols = column((t + 1) & (kWaveTiles - 1));
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int a = 0; a < NW; ++a) D[h][a] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(none, none, f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int a = 0; a < NW; ++a) before[h][a] = 0.0f;
+        if (!(flags & kFirstChunk)) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int a = 0; a < NW; ++a) before[h][a] = *dst[h][a];
+        }
+    };
+    auto flush = [&]() {
+        float minus[2][NW];
+        float odd = 0.0f;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int a = 0; a < NW; ++a) {
+                minus[h][a] = minus_sum_of_parts(D[h][a][0], D[h][a][1], D[h][a][2]);
+                odd += fabsf(minus[h][a]);
             }
+        // An infinity in G meets zeros among the lower parts: where the sum is no number the first part alone says what becomes of it.  (Nothing says
+        // it for values below 2^-133, whose first part is zero: an infinity times one of them is NaN.)  An infinite sum stays one: the first part may
+        // be finite where the value's product is not.
+        if (__builtin_expect(__any(!(odd < __builtin_inff())), 0)) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int a = 0; a < NW; ++a) minus[h][a] = minus[h][a] == minus[h][a] ? minus[h][a] : -D[h][a][0];
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int a = 0; a < NW; ++a) *dst[h][a] = before[h][a] - minus[h][a];
+    };
+
+    // The transposing read takes entry e of a list from lanes 4 e .. 4 e + 3 of 16, lane 4 e + s the s-th 8 bytes, and hands lane l the l-th row's four values:
+    // with NW = 4 all of one unit, with NW = 2 of the units of two lists.  The offsets of entry e of the 16 lanes' four lists are in the fourth lane of their 4-lane group.
+    const uint32_t piece = (part & (NW - 1)) * 8;
+    s16x4 g[2][2][NW];
+    auto gather = [&](auto slot) {
+        constexpr int k = decltype(slot)::value;
+        auto read = [&](int h, int a, uint32_t two, auto high) {      // (the units start where the LDS starts)
+            const uint32_t off = unit_at<(1 << kGroup), decltype(high)::value>(two, piece);
+            g[k & 1][h][a] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LSP_LDS_AS s16x4*)(uintptr_t)off);
+        };
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t lo = quad_lane<3>(ring[k][2 * h]), hi = quad_lane<3>(ring[k][2 * h + 1]);
+            const uint32_t x = NW == 4 || !(part & 2) ? lo : hi;
+            read(h, 0, x, std::false_type{});
+            read(h, 1, x, std::true_type{});
+            if constexpr (NW == 4) {
+                read(h, 2, hi, std::false_type{});
+                read(h, 3, hi, std::true_type{});
+            }
+        }
+    };
+    auto multiply = [&](auto slot, uint64_t refill) {
+        constexpr int k = decltype(slot)::value;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const u32x2 x = {ring[k][2 * h], ring[k][2 * h + 1]};
+            const s16x4 (&y)[NW] = g[k & 1][h];
+            s16x4 v;
+            __builtin_memcpy(&v, &x, 8);
+            D[h][0] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(v, y[0], D[h][0], kGroup, 0, 0);
+            D[h][1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(v, y[1], D[h][1], kGroup, 1, 0);
+            if constexpr (NW == 4) {
+                D[h][2] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(v, y[2], D[h][2], kGroup, 2, 0);
+                D[h][3] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(v, y[3], D[h][3], kGroup, 3, 0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        ring[k] = step_at(refill, k);
+    };
+    // The gathers of a step are asked for before the products of the one before.  The barriers keep the compiler from waiting for each gather by itself and from
+    // giving the refills registers of their own, which a loop would have to move.
+    auto slots = [](auto&& f) {                                       // f of every slot of the ring, in turn
+        every_slot(f, std::make_integer_sequence<int, kRing>{});
+    };
+    // The steps of a chunk, of which the first is in slot 0: whole rounds, then the rest as nested conditions.  A way out of the middle of a loop would cost the compiler its
+    // knowledge of what is in flight; for the same reason the last step also gathers for a step behind it, for nothing, and a tile begins behind the last one.
+    auto walk_chunk = [&]() {
+        int left = length(0), remaining = steps;                      // steps of the tile, and of the chunk
+        auto step = [&](auto slot, uint64_t refill) {
+            constexpr int k = decltype(slot)::value;
+            gather(std::integral_constant<int, (k + 1) % kRing>{});
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0xC07F | (2 * NW << 8));       // lgkmcnt(2 NW): what was asked for before is there
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(slot, refill);
+            if (__builtin_expect(--left == 0, 0)) {
+                flush();
+                left = length(++t);
+                begin();
+            }
+        };
+        gather(std::integral_constant<int, 0>{});
+        begin();
+        for (; remaining > kRing; ahead += kRing * kWave * 16)
+            slots([&](auto slot) { step(slot, remaining-- > kRing ? ahead : next); });
+        auto rest = [&](auto&& self, auto slot) -> void {
+            constexpr int k = decltype(slot)::value;
+            if (k < remaining) {
+                step(slot, next);
+                if constexpr (k + 1 < kRing) self(self, std::integral_constant<int, k + 1>{});
+            }
+        };
+        rest(rest, std::integral_constant<int, 0>{});
+    };
+
+    auto ring_of = [&](uint64_t from) {
+        slots([&](auto slot) { ring[decltype(slot)::value] = step_at(from, decltype(slot)::value); });
+    };
+    // A chunk's first steps are waited for all together (the last of them was asked for before the chunk was staged).  Without this the compiler, which cannot know
+    // how many loads lie behind them, would wait for every load in flight in every round of the ring.
+    auto wait_for_loads = []() {
+        __builtin_amdgcn_s_waitcnt(0x0F70);                           // vmcnt(0)
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    ring_of((uint64_t)(uintptr_t)w.pr.plan + w.H->off_m_steps + (uint64_t)as_const<TileSeg>(w.pr.plan + w.H->off_m_seg)[wave].first_step * (kWave * 16));
+    const auto uniform = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
+    const auto uniform2 = [&](uint32_t lo, uint32_t hi) { return (uint64_t)uniform(hi) << 32 | uniform(lo); };
+    const auto piece16 = [&](const void* p) { return *static_cast<const u32x4*>(p); };
+    if (HALVES) __syncthreads();                                      // the other blocks' last note has been read
+    __syncthreads();                                                  // the first note is there
+    for (;;) {
+        const u32x4 seg0 = piece16(&note->seg[wave]), seg1 = piece16(reinterpret_cast<const uint8_t*>(&note->seg[wave]) + 16);
+        const u32x2 after = *reinterpret_cast<const u32x2*>(&note->steps[0][wave]), here = *reinterpret_cast<const u32x2*>(&note->steps[1][wave]);
+        const u32x2 head = *reinterpret_cast<const u32x2*>(&note->nvcols);
+        own_cols = column(0);
+        steps = (int)uniform(seg0.y);
+        len_lo = uniform2(seg0.z, seg0.w); len_hi = uniform2(seg1.x, seg1.y);
+        next = uniform2(after.x, after.y);
+        ahead = uniform2(here.x, here.y) + kRing * (kWave * 16);
+        const int nvcols = (int)uniform(head.x);
+        flags = uniform(head.y);
+        stride = sums_stride(nvcols);
+        __syncthreads();                                              // the chunk is staged
+        wait_for_loads();
+        t = 0;
+        if (steps > 0) walk_chunk();
+        if (steps < kRing)
+            slots([&](auto slot) {
+                constexpr int k = decltype(slot)::value;
+                if (k >= steps) ring[k] = step_at(next, k);
+            });
+        if (flags & kFirstChunk)
+            for (const int mytiles = tiles_of_wave(nvcols, wave); t < mytiles; ++t) {   // tiles without an entry in a block's first chunk: their sums start at zero
+                places(column(t));
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int a = 0; a < NW; ++a) *dst[h][a] = 0.0f;
+            }
+        __syncthreads();                                              // no longer read; all sums are there
+        if (flags & kLastChunk) {
+            int thread = tid;                                         // (opaque, so that nothing of this is made outside the loop, and kept in registers all along)
+            asm volatile("" : "+v"(thread));
+            const u32x4 head0 = piece16(&note->T), head1 = piece16(&note->vcol);
+            const uint64_t plan = uniform2(head0.z, head0.w);
+            store_sums<R>(sums, stride, (float LSP_GLOBAL_AS*)uniform2(head0.x, head0.y), (const uint16_t LSP_GLOBAL_AS*)(plan + uniform(head1.x)),
+                          (const uint16_t LSP_GLOBAL_AS*)(plan + uniform(head1.y)), (flags & kSharedColumns) != 0, nvcols, (int)uniform(head1.z), r, thread);
+        }
+        if (!(flags & kMoreChunks)) break;
+        note = reinterpret_cast<const ChunkNote*>(smem + kNoteBase<NP>) + (note == reinterpret_cast<const ChunkNote*>(smem + kNoteBase<NP>));
     }
 }
 
@@ -447,9 +615,12 @@ template <int NP, bool WHOLE>
 __global__ __launch_bounds__(kThreadsMM) void k_compress_mm(const CompressGroup grp, int r, int d, int blocks) {
     extern __shared__ __align__(16) uint8_t smem[];
     const int tid = threadIdx.x;
-    if (tid < NP) *reinterpret_cast<u32x2*>(smem + tid * kPlaneBytes + kChunk * 8) = u32x2{0, 0};
+    zero_unit<NP>(smem, tid);
     if (__builtin_amdgcn_readfirstlane(tid) >= kWalkers) fetch_blocks<NP, WHOLE>(smem, blocks, r, d, tid - kWalkers);
-    else walk_blocks<NP>(smem + kTileBase<NP>, blocks, r, d, tid);
+    else {
+        walk_blocks<NP, false>(smem, blocks, r, d, tid);
+        if constexpr (NP == 4) walk_blocks<NP, true>(smem, blocks, r, d, tid);   // more sums than the LDS has room for: 8 rows, then 8 rows
+    }
 }
 
 template <int NP> static hipError_t launch_mm_rows(CompressGroup& g, int32_t r, int32_t d, hipStream_t st) {
