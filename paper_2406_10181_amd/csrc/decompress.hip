@@ -69,14 +69,12 @@ __device__ __forceinline__ void block_sum2(float x, float y, float2* red, float2
 // Phase 1, for d = DD (or, with DD = 0, any d), AHEAD loads in flight: the R * d (row of S, value) pairs of the tile go to LDS first, then every
 // work item (row of the tile, 4 consecutive columns b) issues its 128-bit loads of S back to back, so the whole gather
 // costs few memory round trips.  A row's last quad starts at r - 4 when r is no multiple of 4: some columns are then
-// made twice, with the same result.  Us[plane][b] is a float4 over the plane's 4 rows: element (b, t) lives at float
-// index 4 b + t.
-template <int RG, int DD, int AHEAD, int PS, int NT>
-__device__ __forceinline__ void build_u_tile(uint8_t* smem, int2* pent, const float* __restrict__ S,
+// made twice, with the same result.  place(row, b, c): where element (row, b + c) of the tile lives (c < 4, a constant).
+template <int R, int DD, int AHEAD, bool STRIPES, int NT, typename Place>
+__device__ __forceinline__ void build_u_tile(Place&& place, int2* pent, const float* __restrict__ S,
                                              const int32_t* __restrict__ P_idx, const float* __restrict__ P_val,
                                              int64_t i0, int m, int r, int dim) {
     typedef f32x4 loose __attribute__((aligned(4)));
-    constexpr int R = 4 * RG;
     const int d = DD > 0 ? DD : dim;
     for (int q = threadIdx.x; q < R * d; q += NT) {
         const int64_t at = i0 * d + q;
@@ -90,7 +88,7 @@ __device__ __forceinline__ void build_u_tile(uint8_t* smem, int2* pent, const fl
             const int row = q / r, b = q - row * r;
             float u = 0.0f;
             for (int k = 0; k < d; ++k) u = fmaf(__int_as_float(pent[row * d + k].y), S[pent[row * d + k].x * r + b], u);
-            reinterpret_cast<float*>(smem + (row >> 2) * PS)[b * 4 + (row & 3)] = u;
+            *place(row, b, 0) = u;
         }
         return;
     }
@@ -102,8 +100,8 @@ __device__ __forceinline__ void build_u_tile(uint8_t* smem, int2* pent, const fl
     // last stripe would leave more than an eighth of the lanes idle (r = 1100: 32.4, with stripes 32.7); at r = 1024 and below it is even.
     constexpr int WAVES = NT / kWave;
     static_assert(R % WAVES == 0, "every wave has the same number of rows of a stripe");
-    // (PS: so the rest has no code for it)
-    const bool stripes = PS > 16384 && r > 1024 && (quads + kWave - 1) / kWave * kWave * 8 <= quads * 9;
+    // (STRIPES: so the rest has no code for it)
+    const bool stripes = STRIPES && r > 1024 && (quads + kWave - 1) / kWave * kWave * 8 <= quads * 9;
     const int row0 = stripes ? (int)threadIdx.x / kWave : (int)threadIdx.x / quads;
     int row = row0, b4 = stripes ? (int)threadIdx.x % kWave : (int)threadIdx.x - row0 * quads;
     int row_step = stripes ? WAVES : R, b4_step = 0;                 // (one item a thread: no second division)
@@ -118,8 +116,7 @@ __device__ __forceinline__ void build_u_tile(uint8_t* smem, int2* pent, const fl
         } else if (b4 >= quads) { b4 -= quads; ++row; }
     };
     auto store = [&](int at_row, int b, const f32x4& u) {
-        float* dst = reinterpret_cast<float*>(smem + (at_row >> 2) * PS) + b * 4 + (at_row & 3);
-        dst[0] = u.x; dst[4] = u.y; dst[8] = u.z; dst[12] = u.w;
+        *place(at_row, b, 0) = u.x; *place(at_row, b, 1) = u.y; *place(at_row, b, 2) = u.z; *place(at_row, b, 3) = u.w;
     };
     // d < AHEAD: several items at a time, while there are more than one for every thread (the step of the MLP pair, fp16, d = 4: 75.7 us one by
     // one, now 75.0; where a thread has one item only it would be work for nothing: the attention matrices 22.1, with two items 22.6)
@@ -180,6 +177,12 @@ __device__ __forceinline__ void build_u_tile(uint8_t* smem, int2* pent, const fl
         store(row, b, u);
     }
 }
+
+// Planes of 4 rows, PS bytes apart: element (row, b) is number row % 4 of the b-th float4 of its plane.
+template <int PS> struct PlanePlace {
+    uint8_t* smem;
+    __device__ __forceinline__ float* operator()(int row, int b, int c) const { return reinterpret_cast<float*>(smem + (row >> 2) * PS) + (b + c) * 4 + (row & 3); }
+};
 
 // The rows of a block of W (or G) as buffers of their own: lanes past a row's end load zero and store nothing, and so does
 // a whole row past the matrix, without a branch.  Branches around loads and stores are what the kernel below must not have: the
@@ -334,7 +337,7 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
 #pragma unroll
     for (int t = 0; t < R; ++t) load_w(t, col);                     // in flight while the U tile is built
     load_q(col);
-    build_u_tile<RG, DD, (D::size == 4 && (RG > 2 || DD == 8) ? 4 : 8), PS, NT>(smem, pent, S, P_idx, P_val, i0, m, r, DD);
+    build_u_tile<R, DD, (D::size == 4 && (RG > 2 || DD == 8) ? 4 : 8), (PS > 16384), NT>(PlanePlace<PS>{smem}, pent, S, P_idx, P_val, i0, m, r, DD);
     __syncthreads();
     for (int p = 1; p < npass; ++p) {
         const int next = pass_col(p);
@@ -342,6 +345,251 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
         col = next;
     }
     if (npass > 0) pass(col, col, std::false_type{});
+    if constexpr (NORMS) block_sum2<NT>(num, den, reinterpret_cast<float2*>(smem), partial + blockIdx.x);
+}
+
+#define LSP_LDS_AS __attribute__((address_space(3)))
+// Wide kernel: n % 8 == 0, r % 4 == 0.  LP neighbouring lanes (4; 2 in blocks of 8 rows) work on the same columns, each on four rows of a plane of 4 LP: a column of U
+// is a unit of 16 LP bytes in LDS, and a gather of theirs reads one whole.  The 16 lanes that an LDS read serves at a time then ask for 4 units instead of 16, so fewer
+// meet on a bank, whatever the order of Q's entries (k_decompress on columns in random order: 186 us for four matrices 4096 x 11008, r = 512, d = 8, bf16, 176 with Q
+// reordered; here 167 and 166).  A thread holds the entries of 2 columns of Q (1 for d = 16 and in fp32) and gets those of the others from its neighbours by
+// DPP moves; its patch of W is 4 rows x 8 (4) columns of each plane, moved in 16 bytes a row (pieces of 8 bytes, with the patch reloaded in halves: 202 us).  Each entry
+// gives an address for all planes, and half or a quarter of the entries leave d = 16 at 128 registers, so that two workgroups share a CU.
+//   DEEP: on grids of one workgroup a CU, which may have 256 registers: the next pass's entries and patch are asked for when a pass begins (4096 x 16384,
+//   r = 512, d = 8 72.4 -> 64.2 us).  Otherwise they take the registers that the pass has left, Q first, because loads return in order (the other way round: 176 for 166 us).
+// What bounds it, 4096 x 11008 four times (166 us): HBM at 4.3 TB/s of the 5.3 to 5.8 that its pattern allows; the LDS reads take some 85 us of it.
+
+// Units of U in LDS: the 16-byte pieces of a unit and the units of a block of 256 bytes trade places by the block's number, so that the stores of the build, where a
+// wave has one row of 256 neighbouring columns, fall on all banks.
+template <int LP> __device__ __forceinline__ uint32_t unit_of(uint32_t b) {
+    if constexpr (LP == 4) return (b << 6) ^ ((b << 2) & 0xF0u);
+    else return (b << 5) ^ ((b << 1) & 0x70u);
+}
+template <int LP, int PLANE> struct UnitPlace {
+    uint8_t* smem;
+    // b a multiple of 4
+    __device__ __forceinline__ float* operator()(int row, int b, int c) const {
+        const uint32_t at = (unit_of<LP>((uint32_t)b) ^ (((uint32_t)row >> 2 & (LP - 1)) << 4)) + ((uint32_t)row & 3) * 4;
+        return reinterpret_cast<float*>(smem + (row / (4 * LP)) * PLANE + (at ^ ((uint32_t)c * (16 * LP))));
+    }
+};
+// x of lane S of the LP neighbouring lanes that share a unit
+template <int LP, int S> __device__ __forceinline__ uint32_t of_lane(uint32_t x) {
+    constexpr int ctrl = LP == 4 ? S * 0x55 : S == 0 ? 0xA0 : 0xF5;   // quad_perm
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, ctrl, 0xF, 0xF, true);
+}
+
+template <typename D, int G, int LP, int DD, bool BIG, int NT, bool NORMS, bool DEEP>
+__global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const ApplyGroup grp, int r, float2* __restrict__ partial) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    constexpr int CPT = DD == 16 || D::size == 4 ? 1 : 2;                           // columns whose entries of Q a thread holds
+    constexpr int PR = 4 * LP;                                      // rows of a plane of units
+    constexpr int R = G * PR, PLANE = G > 1 ? 32768 : 0;
+    constexpr int COLS = CPT * LP;                                  // columns of a thread's patch, LP threads have the same
+    constexpr int NE = CPT * DD;
+    constexpr int DW = COLS * D::size / 4;                          // dwords of a row of it
+    constexpr int VW = DW < 4 ? DW : 4, NV = DW / VW;               // in loads of VW
+    typedef uint32_t Vec __attribute__((ext_vector_type(VW)));
+    const int prob = group_find(grp.first, grp.count, (int)blockIdx.x);
+    const int unit = (int)blockIdx.x - grp.first[prob], parts = grp.parts[prob];
+    const int block = parts > 1 ? unit / parts : unit, part = unit - block * parts;
+    const float* __restrict__ S = grp.S[prob];
+    const int32_t* __restrict__ P_idx = grp.P_idx[prob];
+    const float* __restrict__ P_val = grp.P_val[prob];
+    const int32_t* __restrict__ Q_idx = grp.Q_idx[prob];
+    const float* __restrict__ Q_val = grp.Q_val[prob];
+    const int m = grp.m[prob], n = grp.n[prob];
+    const int64_t i0 = (int64_t)block * R;
+    int2* pent = reinterpret_cast<int2*>(smem + (G > 1 ? G * PLANE : r * (16 * LP)));
+
+    constexpr int step = NT * CPT;
+    const Passes passes(n, step, block, part, parts);
+    const int npass = passes.count;
+    auto pass_col = [&](int p) -> int { return passes.at(p) * step; };
+    const int own_col = (int)threadIdx.x * CPT;                     // of the pass: the first column whose entries this thread holds
+    const int lane_col = (int)threadIdx.x / LP * COLS;              // and the first of its patch
+    const uint32_t p4 = threadIdx.x & (LP - 1);                     // rows 4 p4 .. of a plane are this thread's
+    const uint32_t piece = p4 << 4;
+    const int rows = m - i0 < R ? (int)(m - i0) : R;
+    char* const base = static_cast<char*>(grp.W[prob]) + i0 * n * D::size;
+    const uint32_t stride = (uint32_t)n * D::size;                  // (host: 16 rows are less than 2^31 bytes)
+    const uint32_t lane_off = p4 * 4 * stride + (uint32_t)lane_col * D::size;
+    // row t of the thread's four in plane g: what lies behind the matrix's last row is past the buffer's end, and a thread past the last column goes there too
+    auto buffer = [&](int g, int t, int col) {
+        const int row = g * PR + t;
+        const uint32_t left = rows > row ? (uint32_t)min(rows - row, PR) * stride - (uint32_t)col * D::size : 0u;
+        return __builtin_amdgcn_make_buffer_rsrc(base + (int64_t)row * stride + (int64_t)col * D::size, 0, left, 0x00027000);
+    };
+    auto offset = [&](int col) { return lane_col < n - col ? lane_off : 0x80000000u; };
+
+    constexpr int NB = DEEP ? 2 : 1;                                // sets of registers that passes take in turn
+    uint32_t w_[NB][G][4][DW];
+    uint32_t at_[NB][NE];                                           // units of the entries
+    float qv_[NB][NE];
+    auto load_w = [&](int s, int g, int t, int col, uint32_t off) {
+        auto& w = w_[s];
+        const RowBuffer b = buffer(g, t, col);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            Vec x;
+            if constexpr (VW == 4) x = __builtin_amdgcn_raw_buffer_load_b128(b, (int)off + v * 16, 0, kNonTemporal);
+            else if constexpr (VW == 2) x = __builtin_amdgcn_raw_buffer_load_b64(b, (int)off + v * 8, 0, kNonTemporal);
+            else x[0] = __builtin_amdgcn_raw_buffer_load_b32(b, (int)off, 0, kNonTemporal);
+#pragma unroll
+            for (int k = 0; k < VW; ++k) w[g][t][v * VW + k] = x[k];
+        }
+    };
+    auto store_w = [&](int s, int g, int t, int col, uint32_t off) {
+        auto& w = w_[s];
+        const RowBuffer b = buffer(g, t, col);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            Vec x;
+#pragma unroll
+            for (int k = 0; k < VW; ++k) x[k] = w[g][t][v * VW + k];
+            if constexpr (VW == 4) __builtin_amdgcn_raw_buffer_store_b128(x, b, (int)off + v * 16, 0, kNonTemporal);
+            else if constexpr (VW == 2) __builtin_amdgcn_raw_buffer_store_b64(x, b, (int)off + v * 8, 0, kNonTemporal);
+            else __builtin_amdgcn_raw_buffer_store_b32(x[0], b, (int)off, 0, kNonTemporal);
+        }
+    };
+    auto load_q = [&](int s, int col) {
+        auto &at = at_[s]; auto &qv = qv_[s];
+        const int jq = col < n - own_col ? col + own_col : n - CPT;
+        typedef uint32_t Ints __attribute__((ext_vector_type(NE % 4 == 0 ? 4 : 2)));
+        typedef float Floats __attribute__((ext_vector_type(NE % 4 == 0 ? 4 : 2)));
+        constexpr int E = NE % 4 == 0 ? 4 : 2;
+        const Ints* qip = reinterpret_cast<const Ints*>(Q_idx + (int64_t)jq * DD);
+        const Floats* qvp = reinterpret_cast<const Floats*>(Q_val + (int64_t)jq * DD);
+#pragma unroll
+        for (int k = 0; k < NE / E; ++k) {
+            const Ints i = qip[k];
+            const Floats v = qvp[k];
+#pragma unroll
+            for (int e = 0; e < E; ++e) { at[k * E + e] = i[e]; qv[k * E + e] = v[e]; }
+        }
+    };
+    float num = 0.0f, den = 0.0f;
+    auto pass = [&](auto set, int col, int next, bool go_on, auto more) {
+        constexpr int s = decltype(set)::value;
+        auto& w = w_[s];
+        auto& at = at_[s];
+        auto& qv = qv_[s];
+        const uint32_t off = offset(col), next_off = go_on ? offset(next) : 0x80000000u;
+        if constexpr (DEEP) {
+            load_q(1 - s, next);
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) load_w(1 - s, g, t, next, next_off);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e) at[e] = unit_of<LP>(at[e]);
+        auto columns = [&](auto which) {                            // columns 2 C and 2 C + 1 of the patch
+            constexpr int C = decltype(which)::value;
+            float acc[G][4][2];
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[g][t][0] = acc[g][t][1] = 0.0f;
+            auto column = [&](auto second) {
+                constexpr int c = decltype(second)::value;
+                constexpr int src = CPT == 2 ? C : 2 * C + c, e0 = CPT == 2 ? c * DD : 0;
+#pragma unroll
+                for (int k = 0; k < DD; ++k) {
+                    const uint32_t here = of_lane<LP, src>(at[e0 + k]) ^ piece;
+                    const float v = __uint_as_float(of_lane<LP, src>(__float_as_uint(qv[e0 + k])));
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const f32x4 u = *(const f32x4 LSP_LDS_AS*)(uintptr_t)(here + g * PLANE);
+                        acc[g][0][c] = fmaf(v, u.x, acc[g][0][c]);
+                        acc[g][1][c] = fmaf(v, u.y, acc[g][1][c]);
+                        acc[g][2][c] = fmaf(v, u.z, acc[g][2][c]);
+                        acc[g][3][c] = fmaf(v, u.w, acc[g][3][c]);
+                    }
+                    if constexpr (DD * G >= 8) if (k % (8 / G) == 8 / G - 1) __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            column(std::integral_constant<int, 0>{});
+            column(std::integral_constant<int, 1>{});
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    float x[2];
+                    if constexpr (D::size == 4) { x[0] = __uint_as_float(w[g][t][2 * C]); x[1] = __uint_as_float(w[g][t][2 * C + 1]); }
+                    else {
+                        uint32_t both = w[g][t][C];
+                        asm volatile("" : "+v"(both));                // (or it is widened long before, fp16)
+                        pair_widen<D>(both, x[0], x[1]);
+                    }
+                    if constexpr (NORMS) {
+                        const bool on = lane_col < n - col && g * PR + (int)p4 * 4 + t < rows;
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) {
+                            const float diff = acc[g][t][c] - x[c];
+                            num = on ? fmaf(diff, diff, num) : num;
+                            den = on ? fmaf(x[c], x[c], den) : den;
+                        }
+                    } else {
+                        x[0] -= acc[g][t][0]; x[1] -= acc[g][t][1];
+                        if constexpr (D::size == 4) { w[g][t][2 * C] = __float_as_uint(x[0]); w[g][t][2 * C + 1] = __float_as_uint(x[1]); }
+                        else w[g][t][C] = pair_narrow<D>(x[0], x[1]);
+                    }
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        columns(std::integral_constant<int, 0>{});
+        if constexpr (COLS > 2) columns(std::integral_constant<int, 1>{});
+        if constexpr (COLS > 4) {
+            columns(std::integral_constant<int, 2>{});
+            columns(std::integral_constant<int, 3>{});
+        }
+        if constexpr (!NORMS) {
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) store_w(s, g, t, col, off);
+        }
+        if constexpr (!DEEP && decltype(more)::value) {               // (loads return in order: what is needed first)
+            load_q(s, next);
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) load_w(s, g, t, next, next_off);
+        }
+    };
+
+    int col = pass_col(0);
+    load_q(0, col);
+    {
+        const uint32_t off = offset(col);
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) load_w(0, g, t, col, off);     // in flight while the U tile is built
+    }
+    build_u_tile<R, DD, (D::size == 4 && (R > 8 || DD == 8) ? 4 : 8), BIG, NT>(UnitPlace<LP, PLANE>{smem}, pent, S, P_idx, P_val, i0, m, r, DD);
+    __syncthreads();
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, NB - 1> odd{};
+    if constexpr (DEEP) {
+        for (int p = 0; p < npass;) {
+            int next = pass_col(min(p + 1, npass - 1));
+            pass(even, col, next, p + 1 < npass, std::false_type{});
+            if (++p >= npass) break;
+            col = next; next = pass_col(min(p + 1, npass - 1));
+            pass(odd, col, next, p + 1 < npass, std::false_type{});
+            ++p; col = next;
+        }
+    } else {
+        for (int p = 1; p < npass; ++p) {
+            const int next = pass_col(p);
+            pass(even, col, next, true, std::true_type{});
+            col = next;
+        }
+        if (npass > 0) pass(even, col, col, true, std::false_type{});
+    }
     if constexpr (NORMS) block_sum2<NT>(num, den, reinterpret_cast<float2*>(smem), partial + blockIdx.x);
 }
 
@@ -420,7 +668,7 @@ __global__ __launch_bounds__(NT, (NORMS ? 3 : 4)) void k_decompress_any(const Ap
     int col = pass_col(0);
     load_q(0, col, 0);
     load_w(col);
-    build_u_tile<RG, 0, 0, PS, NT>(smem, reinterpret_cast<int2*>(smem + RG * PS), grp.S[prob], grp.P_idx[prob], grp.P_val[prob], i0, m, r, d);
+    build_u_tile<R, 0, 0, (PS > 16384), NT>(PlanePlace<PS>{smem}, reinterpret_cast<int2*>(smem + RG * PS), grp.S[prob], grp.P_idx[prob], grp.P_val[prob], i0, m, r, d);
     __syncthreads();
     for (int p = 0; p < npass; ++p) {
 #pragma unroll
@@ -485,6 +733,23 @@ __global__ __launch_bounds__(256) void k_bias_finish(const float2* __restrict__ 
 // The fast kernel needs an even n and d in {2, 4, 8, 16}; a group takes it only if all of its problems qualify.
 static bool fast_shape(int32_t n, int32_t d) { return (n % 2) == 0 && (d == 2 || d == 4 || d == 8 || d == 16); }
 
+// k_decompress_wide (us; k_decompress and it; apply of one matrix unless said otherwise; uniform columns, Q not reordered).  It takes whole pieces of 8 columns and
+// whole units of 4, every matrix of the group, or the group goes to k_decompress, with the same result.  Where both can, it is used
+//   for d = 16, where two columns' entries of Q in a thread leave k_decompress 192 registers: 4096 x 16384, r = 1024, bf16, zipf 129 and 101; 4096 x 4096, r = 1024, fp32 53.0 and
+//     43.6; 2048 x 2048, r = 256, bf16 (8 rows) 15.3 and 12.4; bias pass 4096 x 4096, r = 512, bf16 77 and 67, with the compress call before it;
+//   for 16 bits in blocks of 16 and 32 rows: four matrices 4096 x 11008, r = 512, d = 8 187 and 167 (176 and 166 with Q reordered); 4096 x 16384, r = 512, d = 8 74.6 and 66.0;
+//     4096 x 8192, r = 256, d = 2 30.3 and 28.6; 16384 x 4096, d = 4 57.1 and 55.4; it is even on 4096 x 4096 and 4096 x 8192, d = 8;
+//   for fp32 where the grid fits the chip at once (deep) and in the bias pass: 4096 x 4096, r = 512, d = 8 31.9 and 30.7; 4096 x 8192, d = 4 56.4 and 54.0; 3072 x 3072, r = 1024,
+//     d = 8 27.5 and 25.8; two calls with a bias pass, 8192 x 2048, r = 256, d = 4 62.3 and 53.6.
+// Elsewhere k_decompress is ahead: fp32 on larger grids (8192 x 4096, r = 512, d = 8 58.4 and 66.5; with 16 rows a thread has half as many registers in flight), and d <= 8 in
+// blocks of 8 rows, whose pieces are 8 bytes (2048 x 2048, r = 512, d = 8, bf16 8.8 and 9.5; 4096 x 4096, r = 2048, d = 8 44.5 and 46.8).
+constexpr unsigned kResidentDeep = 256;                              // workgroups of the deep form, one a CU
+static bool wide_group(const ApplyGroup& g, int32_t r) {
+    bool wide = r >= 4 && r % 4 == 0;
+    for (int p = 0; p < g.count; ++p) wide = wide && g.n[p] % 8 == 0 && g.n[p] <= 1 << 24;   // (32-bit offsets inside a plane of rows)
+    return wide;
+}
+
 template <typename D, int RG, int PS, int NT, bool NORMS = false>
 static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipStream_t st, float2* partial = nullptr) {
     // widest matrices first: workgroups are started in index order as CUs fall free, and a workgroup's
@@ -505,6 +770,33 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
     }
     const unsigned grid = (unsigned)g.first[g.count];
     hipError_t e;
+    if (fast && wide_group(g, r)) {
+        constexpr int LP = RG == 2 ? 2 : 4, G = RG == 2 ? 1 : RG / 4;
+#define LSP_LAUNCH_WIDE(DDV, DEEPV)                                                                            \
+    do {                                                                                                       \
+        constexpr auto kern = k_decompress_wide<D, G, LP, DDV, (PS > 16384), NT, NORMS, DEEPV>;                \
+        constexpr size_t ents = (size_t)RG * 4 * DDV * sizeof(int2);                                           \
+        if ((e = allow_dynamic_lds<kern>((size_t)RG * PS + ents)) != hipSuccess) return e;                     \
+        const size_t lds = (G > 1 ? (size_t)RG * PS : (size_t)r * 16 * LP) + ents;                             \
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, g, (int)r, partial);                           \
+        return hipGetLastError();                                                                              \
+    } while (0)
+#define LSP_WIDE(DDV)                                                                                          \
+    do {                                                                                                       \
+        if constexpr (G == 1 && NT == 512)                                                                     \
+            if (grid <= kResidentDeep) LSP_LAUNCH_WIDE(DDV, (G == 1 && NT == 512));                            \
+        if constexpr (D::size == 2 || DDV == 16 || NORMS) LSP_LAUNCH_WIDE(DDV, false);                         \
+    } while (0)
+        if constexpr (LP == 4) {
+            if (d == 2) LSP_WIDE(2);
+            if (d == 4) LSP_WIDE(4);
+            if (d == 8) LSP_WIDE(8);
+        }
+        if constexpr (NT == 512)
+            if (d == 16) LSP_WIDE(16);
+#undef LSP_WIDE
+#undef LSP_LAUNCH_WIDE
+    }
 #define LSP_LAUNCH_FAST(DDV)                                                                                   \
     do {                                                                                                       \
         constexpr auto kern = k_decompress<D, RG, DDV, PS, NT, NORMS>;                                         \
@@ -575,7 +867,7 @@ static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_
         return r <= 256 ? launch_d<D, 2, 4096, 512>(g, r, d, kAll, st) : r <= 512 ? launch_d<D, 2, 8192, 512>(g, r, d, kAll, st)
                                                                                  : launch_d<D, 2, 16384, 512>(g, r, d, kAll, st);
     if constexpr (D::size == 2)
-        if (fast && d <= 8 && blocks >= 1024 && 256 < r && r <= 512) return launch_d<D, 8, 8192, 512>(g, r, d, kAll, st);
+        if (fast && (d <= 8 || wide_group(g, r)) && blocks >= 1024 && 256 < r && r <= 512) return launch_d<D, 8, 8192, 512>(g, r, d, kAll, st);
     if (fast && d <= 8 && blocks >= 512 && r <= 512)
         return r <= 256 ? launch_d<D, 4, 4096, 256>(g, r, d, 8, st) : launch_d<D, 4, 8192, 256>(g, r, d, 8, st);
     return r <= 256 ? launch_d<D, 4, 4096, 512>(g, r, d, kAll, st) : r <= 512 ? launch_d<D, 4, 8192, 512>(g, r, d, kAll, st)

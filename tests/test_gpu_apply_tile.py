@@ -21,3 +21,26 @@ def test_apply_with_few_and_many_items_a_thread(m, r, d, dtype):
     print(f"[case] tile m={m} r={r} d={d} {dtype}", flush=True)
     Wp, Wr = oracle.decompress_apply(pb.W, dtype, pb.S_in, pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val)
     gu.check_decompress(gu.DeviceProblem(pb).decompress(pb.S_in), pb.W, Wp, Wr, dtype, pb.name)
+
+
+# What the kernel for whole pieces of 8 columns does at its edges: one piece, a pass and a bit, less than a block of rows more; blocks of 8 rows (m = 13), of 16 on one workgroup
+# a CU (2069) and on more (4100), of 32 (16390).  Against the oracle, and bit for bit what the other kernel makes of the same matrix: a group with a ragged matrix goes there.
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("d", [2, 4, 8, 16])
+@pytest.mark.parametrize("m,n,r", [(13, 8, 16), (13, 1032, 132), (13, 520, 1540), (2069, 8, 20), (2069, 520, 260), (2069, 1544, 1024), (4100, 72, 512), (16390, 24, 260), (16390, 520, 512)])
+def test_apply_in_whole_pieces(m, n, r, d, dtype):
+    import torch
+    import gpu_util as gu
+    import paper_2406_10181_amd as lsp
+    print(f"[case] pieces m={m} n={n} r={r} d={d} {dtype}", flush=True)
+    pb = syn.make_problem("pieces", m, n, r, d, dtype, seed=9500 + m + n + r + d, g_std=1.0)
+    Wp, Wr = oracle.decompress_apply(pb.W, dtype, pb.S_in, pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val)
+    dp = gu.DeviceProblem(pb)
+    single = dp.decompress(pb.S_in)
+    gu.check_decompress(single, pb.W, Wp, Wr, dtype, pb.name)
+    other = gu.DeviceProblem(syn.make_problem("ragged", 33, 66, r, d, dtype, seed=1, g_std=1.0))
+    S = gu.to_device(pb.S_in)
+    items = [(x.W, S, x.P_idx, x.P_val, x.Q_idx, x.Q_val, x.pb.m, x.pb.n) for x in (dp, other)]
+    lsp.lsp_decompress_apply_grouped(lsp.apply_items(items), 2, r, d, dp.code, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    assert (gu.to_host(dp.W, dtype) == single).all()
