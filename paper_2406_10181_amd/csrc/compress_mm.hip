@@ -140,6 +140,21 @@ template <int NP, int NH> __device__ __forceinline__ void put_units(uint8_t* sme
     }
 }
 
+// All rows of a block, n % 8 == 0: four lanes write the first halves of their units while the next four write the second ones, so that a write falls on more banks (with
+// kernel B: four matrices 4096 x 11008, r = 512, d = 8 158.8 -> 157.7 us; 4096 x 16384, r = 256, d = 2 48.6 -> 48.15; where pieces are loose the selects spill: 19.8 -> 20.5).
+template <int NP, int NH> __device__ __forceinline__ void put_block(uint8_t* smem, const u32x2 (&lo)[NH][8], const u32x2 (&hi)[NH][8], int tid) {
+    static_assert(NH == 2, "units of 32 bytes");
+    const bool swap = (tid >> 2 & 1) != 0;
+    uint8_t* const first = smem + tid * kUnitBytes<NP> + (swap ? 16 : 0);
+    uint8_t* const second = smem + tid * kUnitBytes<NP> + (swap ? 0 : 16);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const u32x4 l = {lo[0][q].x, lo[0][q].y, lo[1][q].x, lo[1][q].y}, h = {hi[0][q].x, hi[0][q].y, hi[1][q].x, hi[1][q].y};
+        *reinterpret_cast<u32x4*>(first + q * (kChunk / 8) * kUnitBytes<NP>) = swap ? h : l;
+        *reinterpret_cast<u32x4*>(second + q * (kChunk / 8) * kUnitBytes<NP>) = swap ? l : h;
+    }
+}
+
 template <int CTRL> __device__ __forceinline__ uint32_t quad_lane(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL * 0x55, 0xF, 0xF, true);
 }
@@ -318,8 +333,11 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
         __syncthreads();                                              // the first note is there
     }
     while (have) {
-        put_units<NP, NH>(smem, ulo, 0, tid);
-        put_units<NP, NH>(smem, uhi, 1, tid);
+        if constexpr (WHOLE && NP == 4) put_block<NP, NH>(smem, ulo, uhi, tid);
+        else {
+            put_units<NP, NH>(smem, ulo, 0, tid);
+            put_units<NP, NH>(smem, uhi, 1, tid);
+        }
         __syncthreads();                                              // staged
         have = w.block < blocks;
         if (have) {
