@@ -472,7 +472,7 @@ static hipError_t launch_gq(const CompressGroup& g, int32_t r, int32_t d, const 
     std::conditional_t<RAW, RawCall, NoRawCall> args{};
     if constexpr (RAW) args = raw;
     hipError_t e;
-    if ((e = allow_dynamic_lds<k_compress_gq<D, WHOLE, RAW>>(lds)) != hipSuccess) return e;
+    if ((e = allow_dynamic_lds<k_compress_gq<D, WHOLE, RAW>, lds>()) != hipSuccess) return e;
     hipLaunchKernelGGL((k_compress_gq<D, WHOLE, RAW>), dim3((unsigned)g.first_gq[g.count]), dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, args);
     return hipGetLastError();
 }

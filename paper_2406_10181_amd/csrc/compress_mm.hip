@@ -655,10 +655,10 @@ template <int NP> static hipError_t launch_mm_rows(CompressGroup& g, int32_t r, 
     const dim3 grid((unsigned)std::min(blocks, kResidentMM));
     hipError_t e;
     if (whole) {
-        if ((e = allow_dynamic_lds<k_compress_mm<NP, true>>(lds)) != hipSuccess) return e;
+        if ((e = allow_dynamic_lds<k_compress_mm<NP, true>, lds>()) != hipSuccess) return e;
         hipLaunchKernelGGL((k_compress_mm<NP, true>), grid, dim3(kThreadsMM), lds, st, g, (int)r, (int)d, blocks);
     } else {
-        if ((e = allow_dynamic_lds<k_compress_mm<NP, false>>(lds)) != hipSuccess) return e;
+        if ((e = allow_dynamic_lds<k_compress_mm<NP, false>, lds>()) != hipSuccess) return e;
         hipLaunchKernelGGL((k_compress_mm<NP, false>), grid, dim3(kThreadsMM), lds, st, g, (int)r, (int)d, blocks);
     }
     return hipGetLastError();

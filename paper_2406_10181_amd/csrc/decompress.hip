@@ -776,8 +776,9 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
     do {                                                                                                       \
         constexpr auto kern = k_decompress_wide<D, G, LP, DDV, (PS > 16384), NT, NORMS, DEEPV>;                \
         constexpr size_t ents = (size_t)RG * 4 * DDV * sizeof(int2);                                           \
-        if ((e = allow_dynamic_lds<kern>((size_t)RG * PS + ents)) != hipSuccess) return e;                     \
-        const size_t lds = (G > 1 ? (size_t)RG * PS : (size_t)r * 16 * LP) + ents;                             \
+        constexpr size_t units = G > 1 ? (size_t)RG * PS : (size_t)(PS > 16384 ? 2048 : 1024) * 16 * LP;       \
+        if ((e = allow_dynamic_lds<kern, units + ents>()) != hipSuccess) return e;                             \
+        const size_t lds = (G > 1 ? units : (size_t)r * 16 * LP) + ents;                                       \
         hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, g, (int)r, partial);                           \
         return hipGetLastError();                                                                              \
     } while (0)
@@ -801,7 +802,7 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
     do {                                                                                                       \
         constexpr auto kern = k_decompress<D, RG, DDV, PS, NT, NORMS>;                                         \
         constexpr size_t lds = (size_t)RG * PS + (size_t)RG * 4 * DDV * sizeof(int2);                          \
-        if ((e = allow_dynamic_lds<kern>(lds)) != hipSuccess) return e;                                        \
+        if ((e = allow_dynamic_lds<kern, lds>()) != hipSuccess) return e;                                        \
         hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, g, (int)r, partial);                            \
         return hipGetLastError();                                                                              \
     } while (0)
@@ -813,7 +814,7 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
 #define LSP_LAUNCH_ANY(PAIRV)                                                                                  \
     do {                                                                                                       \
         constexpr auto kern = k_decompress_any<D, RG, PS, NT, PAIRV, NORMS>;                                   \
-        if ((e = allow_dynamic_lds<kern>((size_t)RG * PS + (size_t)RG * 4 * LSP_MAX_D * sizeof(int2))) != hipSuccess) return e; \
+        if ((e = allow_dynamic_lds<kern, (size_t)RG * PS + (size_t)RG * 4 * LSP_MAX_D * sizeof(int2)>()) != hipSuccess) return e; \
         hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), (size_t)RG * PS + (size_t)RG * 4 * d * sizeof(int2), st, g, (int)r, (int)d, partial); \
         return hipGetLastError();                                                                              \
     } while (0)

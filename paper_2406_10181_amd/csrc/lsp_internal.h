@@ -302,17 +302,18 @@ struct F16 { using elem = uint16_t; static constexpr int size = 2; };
 struct BF16{ using elem = uint16_t; static constexpr int size = 2; };
 
 #if defined(__HIPCC__)
-// Lets kernel `Kern` use up to `bytes` of dynamic LDS.  The attribute belongs to the (kernel, device)
-// pair and does not change afterwards, so the runtime is asked once per pair, not on every launch of
-// the per-step path.
-template <auto Kern>
-static inline hipError_t allow_dynamic_lds(size_t bytes) {
+// Lets kernel `Kern` use up to `Bytes` of dynamic LDS: the most that any launch of it asks for, a constant, so that it does not depend on which
+// call comes first.  The attribute belongs to the (kernel, device) pair and does not change afterwards, so the runtime is asked once per pair,
+// not on every launch of the per-step path.
+template <auto Kern, size_t Bytes>
+static inline hipError_t allow_dynamic_lds() {
+    static_assert(Bytes <= 160 * 1024, "the LDS of a CU");
     static std::atomic<uint64_t> done{0};                   // bit k: set on device k (devices >= 64: always asked)
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 64 && ((done.load(std::memory_order_acquire) >> dev) & 1u)) return hipSuccess;
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(Kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(Kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)Bytes);
     if (e == hipSuccess && dev < 64) done.fetch_or((uint64_t)1 << dev, std::memory_order_release);
     return e;
 }

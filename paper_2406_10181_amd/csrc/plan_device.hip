@@ -752,7 +752,7 @@ hipError_t launch_plan_build(const int32_t* P_idx, const float* P_val, const int
     const int64_t max_rows = (int64_t)plan_max_rows(n, r, d);
     hipError_t e;
     const size_t lds = (size_t)(2 + kWavesSort) * r * sizeof(int32_t);
-    if ((e = allow_dynamic_lds<k_plan_sort>((size_t)(2 + kWavesSort) * LSP_MAX_R * sizeof(int32_t))) != hipSuccess) return e;
+    if ((e = allow_dynamic_lds<k_plan_sort, (size_t)(2 + kWavesSort) * LSP_MAX_R * sizeof(int32_t)>()) != hipSuccess) return e;
     const unsigned clear = (unsigned)std::min<size_t>((L.off_q_rows + (L.off_p_ent - L.off_p_item)) / (4 * kThreadsSort) + 1, 256);
     hipLaunchKernelGGL(k_plan_sort, dim3((unsigned)(nchunks + ptiles) * kSubTiles + clear), dim3(kThreadsSort), lds, st, plan, L, s, P_idx, Q_idx,
                        (int)m, (int)n, (int)r, (int)d, nchunks, ptiles, max_rows);
