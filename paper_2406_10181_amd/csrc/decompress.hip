@@ -782,11 +782,12 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
         hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, g, (int)r, partial);                           \
         return hipGetLastError();                                                                              \
     } while (0)
+// (8 rows at d = 16 and r <= 1024: at most 128 blocks of 16 rows, so the grid is never beyond that of the deep form)
 #define LSP_WIDE(DDV)                                                                                          \
     do {                                                                                                       \
         if constexpr (G == 1 && NT == 512)                                                                     \
             if (grid <= kResidentDeep) LSP_LAUNCH_WIDE(DDV, (G == 1 && NT == 512));                            \
-        if constexpr (D::size == 2 || DDV == 16 || NORMS) LSP_LAUNCH_WIDE(DDV, false);                         \
+        if constexpr ((D::size == 2 || DDV == 16 || NORMS) && (LP == 4 || PS > 16384)) LSP_LAUNCH_WIDE(DDV, false);   \
     } while (0)
         if constexpr (LP == 4) {
             if (d == 2) LSP_WIDE(2);

@@ -4,6 +4,8 @@ import os
 import subprocess
 import sys
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 STAND_IN = r"""
@@ -70,8 +72,10 @@ sys.stdout.flush()
 """
 
 
-def _outcome(tmp_path):
-    src, so = tmp_path / "stand_in.cpp", tmp_path / "stand_in.so"
+@pytest.fixture(scope="module")
+def outcome(tmp_path_factory):
+    where = tmp_path_factory.mktemp("stand_in")
+    src, so = where / "stand_in.cpp", where / "stand_in.so"
     src.write_text(STAND_IN)
     subprocess.run([os.environ.get("CXX", "g++"), "-O1", "-std=c++17", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
     out = subprocess.run([sys.executable, "-c", CALLS, str(so), ROOT], capture_output=True, text=True, timeout=300)
@@ -79,6 +83,9 @@ def _outcome(tmp_path):
     return out.stdout
 
 
-def test_no_launch_asks_for_more_lds_than_its_kernel_was_allowed(tmp_path):
-    text = _outcome(tmp_path)
-    assert "launches True beyond 0" in text, text[-2000:]
+def test_no_launch_asks_for_more_lds_than_its_kernel_was_allowed(outcome):
+    assert "launches True beyond 0" in outcome, outcome[-2000:]
+
+
+def test_every_kernel_of_the_expand_side_is_launched_for_some_shape(outcome):
+    assert "never launched" not in outcome, outcome[-2000:]
