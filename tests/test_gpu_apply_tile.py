@@ -44,3 +44,26 @@ def test_apply_in_whole_pieces(m, n, r, d, dtype):
     lsp.lsp_decompress_apply_grouped(lsp.apply_items(items), 2, r, d, dp.code, torch.cuda.current_stream())
     torch.cuda.synchronize()
     assert (gu.to_host(dp.W, dtype) == single).all()
+
+
+# d = 16 in blocks of 8 rows on more workgroups than CUs (r > 1024 only), against the oracle.
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("m,n,r", [(2100, 520, 1540), (2053, 1032, 2048)])
+def test_apply_and_bias_with_a_large_tile_of_8_rows(m, n, r, dtype):
+    import gpu_util as gu
+    from test_gpu_parity import _bias_check
+    print(f"[case] large tile m={m} n={n} r={r} {dtype}", flush=True)
+    pb = syn.make_problem("large tile", m, n, r, 16, dtype, seed=9700 + m + n + r, g_std=1.0)
+    Wp, Wr = oracle.decompress_apply(pb.W, dtype, pb.S_in, pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val)
+    gu.check_decompress(gu.DeviceProblem(pb).decompress(pb.S_in), pb.W, Wp, Wr, dtype, pb.name)
+    _bias_check(pb)
+
+
+# The bias pass in the same kernel: one piece, part passes, last blocks that are not whole (a lane past the last column still has sums, which must not
+# count), on one workgroup a CU (2069) and on more (4100, 8200).
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("d", [2, 4, 8, 16])
+@pytest.mark.parametrize("m,n,r", [(13, 8, 16), (13, 1032, 132), (2069, 8, 20), (2069, 520, 260), (2069, 1544, 1024), (4100, 72, 512), (4100, 1544, 256), (8200, 264, 1024)])
+def test_bias_in_whole_pieces(m, n, r, d, dtype):
+    from test_gpu_parity import _bias_check
+    _bias_check(syn.make_problem("bias pieces", m, n, r, d, dtype, seed=9600 + m + n + r + d, g_std=1.0))
