@@ -379,6 +379,10 @@ template <int LP, int S> __device__ __forceinline__ uint32_t of_lane(uint32_t x)
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, ctrl, 0xF, 0xF, true);
 }
 
+// f(0), f(1), ... of constants
+template <typename F, int... k> __device__ __forceinline__ void every_of(F& f, std::integer_sequence<int, k...>) { (f(std::integral_constant<int, k>{}), ...); }
+template <int N, typename F> __device__ __forceinline__ void every(F&& f) { every_of(f, std::make_integer_sequence<int, N>{}); }
+
 template <typename D, int G, int LP, int DD, bool BIG, int NT, bool NORMS, bool DEEP>
 __global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const ApplyGroup grp, int r, float2* __restrict__ partial) {
     extern __shared__ __align__(16) uint8_t smem[];
@@ -389,6 +393,10 @@ __global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const Appl
     constexpr int NE = CPT * DD;
     constexpr int DW = COLS * D::size / 4;                          // dwords of a row of it
     constexpr int VW = DW < 4 ? DW : 4, NV = DW / VW;               // in loads of VW
+    // Units of U are asked for 8 (4) ahead of the FMAs: with two waves a SIMD the compiler's own order, one or two ahead, left the reads' latency bare (us before and with it;
+    // 4096 x 4096, r = 512, d = 8, bf16, Q reordered or not: 22.5 and 21.7, bias pass 22.0 and 21.1; 4096 x 11008 50.1 and 48.3, 40.9 and 39.1; 4096 x 4096, r = 1024, d = 16, fp32
+    // 44.3 and 42.5; bias pass 4096 x 16384, r = 1024, d = 16, bf16 95 and 87).  16 bits at d = 16 are bound by the reads themselves: 4096 x 16384 103 and 104.5.
+    constexpr bool AHEAD = DEEP && !(LP == 4 && DD == 16 && D::size == 2 && !NORMS);
     typedef uint32_t Vec __attribute__((ext_vector_type(VW)));
     const int prob = group_find(grp.first, grp.count, (int)blockIdx.x);
     const int unit = (int)blockIdx.x - grp.first[prob], parts = grp.parts[prob];
@@ -485,33 +493,11 @@ __global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const Appl
         }
 #pragma unroll
         for (int e = 0; e < NE; ++e) at[e] = unit_of<LP>(at[e]);
-        auto columns = [&](auto which) {                            // columns 2 C and 2 C + 1 of the patch
+        // (deep: sums of a pass and row, so that what lies outside the matrix is left out once a pass and not element by element)
+        float pass_num[4] = {0.0f, 0.0f, 0.0f, 0.0f}, pass_den[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        // columns 2 C and 2 C + 1 of the patch take their sums
+        auto combine = [&](auto which, const float (&acc)[G][4][2]) {
             constexpr int C = decltype(which)::value;
-            float acc[G][4][2];
-#pragma unroll
-            for (int g = 0; g < G; ++g)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) acc[g][t][0] = acc[g][t][1] = 0.0f;
-            auto column = [&](auto second) {
-                constexpr int c = decltype(second)::value;
-                constexpr int src = CPT == 2 ? C : 2 * C + c, e0 = CPT == 2 ? c * DD : 0;
-#pragma unroll
-                for (int k = 0; k < DD; ++k) {
-                    const uint32_t here = of_lane<LP, src>(at[e0 + k]) ^ piece;
-                    const float v = __uint_as_float(of_lane<LP, src>(__float_as_uint(qv[e0 + k])));
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        const f32x4 u = *(const f32x4 LSP_LDS_AS*)(uintptr_t)(here + g * PLANE);
-                        acc[g][0][c] = fmaf(v, u.x, acc[g][0][c]);
-                        acc[g][1][c] = fmaf(v, u.y, acc[g][1][c]);
-                        acc[g][2][c] = fmaf(v, u.z, acc[g][2][c]);
-                        acc[g][3][c] = fmaf(v, u.w, acc[g][3][c]);
-                    }
-                    if constexpr (DD * G >= 8) if (k % (8 / G) == 8 / G - 1) __builtin_amdgcn_sched_barrier(0);
-                }
-            };
-            column(std::integral_constant<int, 0>{});
-            column(std::integral_constant<int, 1>{});
 #pragma unroll
             for (int g = 0; g < G; ++g)
 #pragma unroll
@@ -523,7 +509,14 @@ __global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const Appl
                         asm volatile("" : "+v"(both));                // (or it is widened long before, fp16)
                         pair_widen<D>(both, x[0], x[1]);
                     }
-                    if constexpr (NORMS) {
+                    if constexpr (NORMS && AHEAD) {
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) {
+                            const float diff = acc[g][t][c] - x[c];
+                            pass_num[t] = fmaf(diff, diff, pass_num[t]);
+                            pass_den[t] = fmaf(x[c], x[c], pass_den[t]);
+                        }
+                    } else if constexpr (NORMS) {
                         const bool on = lane_col < n - col && g * PR + (int)p4 * 4 + t < rows;
 #pragma unroll
                         for (int c = 0; c < 2; ++c) {
@@ -537,13 +530,66 @@ __global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const Appl
                         else w[g][t][C] = pair_narrow<D>(x[0], x[1]);
                     }
                 }
-            __builtin_amdgcn_sched_barrier(0);
         };
-        columns(std::integral_constant<int, 0>{});
-        if constexpr (COLS > 2) columns(std::integral_constant<int, 1>{});
-        if constexpr (COLS > 4) {
-            columns(std::integral_constant<int, 2>{});
-            columns(std::integral_constant<int, 3>{});
+        auto zero = [](float (&acc)[G][4][2]) {
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[g][t][0] = acc[g][t][1] = 0.0f;
+        };
+        // entry k of column c of pair C, of the lane that holds it
+        auto unit = [&](auto C, auto c, int k) { return of_lane<LP, (CPT == 2 ? C() : 2 * C() + c())>(at[(CPT == 2 ? c() * DD : 0) + k]) ^ piece; };
+        auto value = [&](auto C, auto c, int k) { return __uint_as_float(of_lane<LP, (CPT == 2 ? C() : 2 * C() + c())>(__float_as_uint(qv[(CPT == 2 ? c() * DD : 0) + k]))); };
+        auto add = [](float (&acc)[G][4][2], int g, int c, float v, f32x4 u) {
+            acc[g][0][c] = fmaf(v, u.x, acc[g][0][c]);
+            acc[g][1][c] = fmaf(v, u.y, acc[g][1][c]);
+            acc[g][2][c] = fmaf(v, u.z, acc[g][2][c]);
+            acc[g][3][c] = fmaf(v, u.w, acc[g][3][c]);
+        };
+        if constexpr (AHEAD) {
+            // A units ahead: one is asked for when one has been used.
+            constexpr int N = COLS * DD, A = DD == 16 && D::size == 2 ? 4 : 8;
+            f32x4 u[A];
+            float acc[G][4][2];
+            auto ask = [&](auto entry) {
+                constexpr int e = decltype(entry)::value, column = e / DD;
+                u[e % A] = *(const f32x4 LSP_LDS_AS*)(uintptr_t)unit(std::integral_constant<int, column / 2>{}, std::integral_constant<int, column & 1>{}, e % DD);
+            };
+            every<A>(ask);
+            every<N>([&](auto entry) {
+                constexpr int e = decltype(entry)::value, column = e / DD, k = e % DD;
+                constexpr std::integral_constant<int, column / 2> C{};
+                constexpr std::integral_constant<int, column & 1> c{};
+                if constexpr (c() == 0 && k == 0) zero(acc);
+                add(acc, 0, c(), value(C, c, k), u[e % A]);
+                if constexpr (e + A < N) ask(std::integral_constant<int, e + A>{});
+                if constexpr (c() == 1 && k == DD - 1) combine(C, acc);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+            if constexpr (NORMS)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const bool on = lane_col < n - col && (int)p4 * 4 + t < rows;
+                    num += on ? pass_num[t] : 0.0f;
+                    den += on ? pass_den[t] : 0.0f;
+                }
+        } else {
+            every<COLS / 2>([&](auto C) {
+                float acc[G][4][2];
+                zero(acc);
+                every<2>([&](auto c) {
+#pragma unroll
+                    for (int k = 0; k < DD; ++k) {
+                        const uint32_t here = unit(C, c, k);
+                        const float v = value(C, c, k);
+#pragma unroll
+                        for (int g = 0; g < G; ++g) add(acc, g, c(), v, *(const f32x4 LSP_LDS_AS*)(uintptr_t)(here + g * PLANE));
+                        if constexpr (DD * G >= 8) if (k % (8 / G) == 8 / G - 1) __builtin_amdgcn_sched_barrier(0);
+                    }
+                });
+                combine(C, acc);
+                __builtin_amdgcn_sched_barrier(0);
+            });
         }
         if constexpr (!NORMS) {
 #pragma unroll
