@@ -355,8 +355,12 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
 // reordered; here 167 and 166).  A thread holds the entries of 2 columns of Q (1 for d = 16 and in fp32) and gets those of the others from its neighbours by
 // DPP moves; its patch of W is 4 rows x 8 (4) columns of each plane, moved in 16 bytes a row (pieces of 8 bytes, with the patch reloaded in halves: 202 us).  Each entry
 // gives an address for all planes, and half or a quarter of the entries leave d = 16 at 128 registers, so that two workgroups share a CU.
-//   DEEP: on grids of one workgroup a CU, which may have 256 registers: the next pass's entries and patch are asked for when a pass begins (4096 x 16384,
-//   r = 512, d = 8 72.4 -> 64.2 us).  Otherwise they take the registers that the pass has left, Q first, because loads return in order (the other way round: 176 for 166 us).
+// Three forms, by what is asked for ahead (loads return in order, so within a pass what is needed first goes first):
+//   kDeep, on grids of one workgroup a CU, which may have 256 registers: the next pass's entries and patch when a pass begins (4096 x 16384, r = 512, d = 8 72.4 -> 64.2 us);
+//   kTwo: the next patch when a pass begins, the entries with it if a thread has at most 8, at its end otherwise (bf16, beside kPlain: 8192 x 4096, r = 512, d = 4 32.7 -> 30.7 us,
+//     d = 8 39.0 -> 38.7; 16384 x 2048, r = 256, d = 4 31.4 -> 30.2; bias pass 11008 x 4096, r = 512, d = 8 46.0 -> 44.4);
+//   kPlain: both at the end of a pass; for 32 rows, whose second patch would not fit 128 registers, and where two passes or fewer on at most two workgroups a CU leave little to
+//     fetch ahead for (5120 x 2048, r = 512, d = 8 21.7, kTwo 22.8; 5120 x 768, r = 256, d = 2 8.2 and 8.8).
 // What bounds it, 4096 x 11008 four times (166 us): HBM at 4.3 TB/s of the 5.3 to 5.8 that its pattern allows; the LDS reads take some 85 us of it.
 
 // Units of U in LDS: the 16-byte pieces of a unit and the units of a block of 256 bytes trade places by the block's number, so that the stores of the build, where a
@@ -383,8 +387,9 @@ template <int LP, int S> __device__ __forceinline__ uint32_t of_lane(uint32_t x)
 template <typename F, int... k> __device__ __forceinline__ void every_of(F& f, std::integer_sequence<int, k...>) { (f(std::integral_constant<int, k>{}), ...); }
 template <int N, typename F> __device__ __forceinline__ void every(F&& f) { every_of(f, std::make_integer_sequence<int, N>{}); }
 
-template <typename D, int G, int LP, int DD, bool BIG, int NT, bool NORMS, bool DEEP>
-__global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const ApplyGroup grp, int r, float2* __restrict__ partial) {
+enum WideForm { kPlain, kTwo, kDeep };
+template <typename D, int G, int LP, int DD, bool BIG, int NT, bool NORMS, WideForm FORM>
+__global__ __launch_bounds__(NT, FORM == kDeep ? 2 : 4) void k_decompress_wide(const ApplyGroup grp, int r, float2* __restrict__ partial) {
     extern __shared__ __align__(16) uint8_t smem[];
     constexpr int CPT = DD == 16 || D::size == 4 ? 1 : 2;                           // columns whose entries of Q a thread holds
     constexpr int PR = 4 * LP;                                      // rows of a plane of units
@@ -393,10 +398,11 @@ __global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const Appl
     constexpr int NE = CPT * DD;
     constexpr int DW = COLS * D::size / 4;                          // dwords of a row of it
     constexpr int VW = DW < 4 ? DW : 4, NV = DW / VW;               // in loads of VW
+    constexpr bool DEEP = FORM == kDeep, TWO = FORM != kPlain, TWO_Q = DEEP || (TWO && NE <= 8);   // two sets of registers, which passes take in turn, for the patch of W and the entries
     // Units of U are asked for 8 (4) ahead of the FMAs: with two waves a SIMD the compiler's own order, one or two ahead, left the reads' latency bare (us before and with it;
     // 4096 x 4096, r = 512, d = 8, bf16, Q reordered or not: 22.5 and 21.7, bias pass 22.0 and 21.1; 4096 x 11008 50.1 and 48.3, 40.9 and 39.1; 4096 x 4096, r = 1024, d = 16, fp32
     // 44.3 and 42.5; bias pass 4096 x 16384, r = 1024, d = 16, bf16 95 and 87).  16 bits at d = 16 are bound by the reads themselves: 4096 x 16384 103 and 104.5.
-    constexpr bool AHEAD = DEEP && !(LP == 4 && DD == 16 && D::size == 2 && !NORMS);
+    constexpr bool AHEAD = TWO && !(LP == 4 && DD == 16 && D::size == 2 && !NORMS);
     typedef uint32_t Vec __attribute__((ext_vector_type(VW)));
     const int prob = group_find(grp.first, grp.count, (int)blockIdx.x);
     const int unit = (int)blockIdx.x - grp.first[prob], parts = grp.parts[prob];
@@ -430,10 +436,9 @@ __global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const Appl
     };
     auto offset = [&](int col) { return lane_col < n - col ? lane_off : 0x80000000u; };
 
-    constexpr int NB = DEEP ? 2 : 1;                                // sets of registers that passes take in turn
-    uint32_t w_[NB][G][4][DW];
-    uint32_t at_[NB][NE];                                           // units of the entries
-    float qv_[NB][NE];
+    uint32_t w_[TWO ? 2 : 1][G][4][DW];
+    uint32_t at_[TWO_Q ? 2 : 1][NE];                                // units of the entries
+    float qv_[TWO_Q ? 2 : 1][NE];
     auto load_w = [&](int s, int g, int t, int col, uint32_t off) {
         auto& w = w_[s];
         const RowBuffer b = buffer(g, t, col);
@@ -460,35 +465,40 @@ __global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const Appl
             else __builtin_amdgcn_raw_buffer_store_b32(x[0], b, (int)off, 0, kNonTemporal);
         }
     };
-    auto load_q = [&](int s, int col) {
+    // Past the last column, and past the last pass, a buffer's end keeps entries from being read (4096 x 1536, r = 256, d = 2, bf16 9.65 -> 9.1 us; 11008 x 4096, r = 512, d = 8
+    // 54.9 -> 53.6), but for long rows of few blocks at d = 8 in 16 bits addresses are the faster way (3000 x 11008, r = 256 45.8 and 45.1; 4096 x 4096, r = 512 even).
+    auto load_q = [&](int s, int col, bool go_on) {
         auto &at = at_[s]; auto &qv = qv_[s];
-        const int jq = col < n - own_col ? col + own_col : n - CPT;
-        typedef uint32_t Ints __attribute__((ext_vector_type(NE % 4 == 0 ? 4 : 2)));
-        typedef float Floats __attribute__((ext_vector_type(NE % 4 == 0 ? 4 : 2)));
+        constexpr bool BOUNDED = !(DEEP && DD >= 8 && D::size == 2);
         constexpr int E = NE % 4 == 0 ? 4 : 2;
-        const Ints* qip = reinterpret_cast<const Ints*>(Q_idx + (int64_t)jq * DD);
-        const Floats* qvp = reinterpret_cast<const Floats*>(Q_val + (int64_t)jq * DD);
+        typedef uint32_t Words __attribute__((ext_vector_type(E)));
+        const int j = BOUNDED || col < n - own_col ? col + own_col : n - CPT;
+        const int bytes = go_on ? n * (DD * 4) : 0;
+        const RowBuffer ib = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(Q_idx), 0, bytes, 0x00027000);
+        const RowBuffer vb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Q_val), 0, bytes, 0x00027000);
+        auto load = [&](RowBuffer buf, const void* base, int k) {
+            if constexpr (!BOUNDED) return reinterpret_cast<const Words*>(static_cast<const uint32_t*>(base) + (int64_t)j * DD)[k];
+            else if constexpr (E == 4) return __builtin_amdgcn_raw_buffer_load_b128(buf, j * (DD * 4) + k * 16, 0, 0);
+            else return __builtin_amdgcn_raw_buffer_load_b64(buf, j * (DD * 4) + k * 8, 0, 0);
+        };
 #pragma unroll
         for (int k = 0; k < NE / E; ++k) {
-            const Ints i = qip[k];
-            const Floats v = qvp[k];
+            const Words i = load(ib, Q_idx, k), v = load(vb, Q_val, k);
 #pragma unroll
-            for (int e = 0; e < E; ++e) { at[k * E + e] = i[e]; qv[k * E + e] = v[e]; }
+            for (int e = 0; e < E; ++e) { at[k * E + e] = i[e]; qv[k * E + e] = __uint_as_float(v[e]); }
         }
     };
     float num = 0.0f, den = 0.0f;
     auto pass = [&](auto set, int col, int next, bool go_on, auto more) {
         constexpr int s = decltype(set)::value;
         auto& w = w_[s];
-        auto& at = at_[s];
-        auto& qv = qv_[s];
+        auto& at = at_[TWO_Q ? s : 0];
+        auto& qv = qv_[TWO_Q ? s : 0];
         const uint32_t off = offset(col), next_off = go_on ? offset(next) : 0x80000000u;
-        if constexpr (DEEP) {
-            load_q(1 - s, next);
+        if constexpr (TWO_Q) load_q(1 - s, next, go_on);
+        if constexpr (TWO) {
 #pragma unroll
-            for (int g = 0; g < G; ++g)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) load_w(1 - s, g, t, next, next_off);
+            for (int t = 0; t < 4; ++t) load_w(1 - s, 0, t, next, next_off);
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
@@ -548,7 +558,7 @@ __global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const Appl
         };
         if constexpr (AHEAD) {
             // A units ahead: one is asked for when one has been used.
-            constexpr int N = COLS * DD, A = DD == 16 && D::size == 2 ? 4 : 8;
+            constexpr int N = COLS * DD, A = !DEEP || (DD == 16 && D::size == 2) ? 4 : 8;
             f32x4 u[A];
             float acc[G][4][2];
             auto ask = [&](auto entry) {
@@ -597,8 +607,8 @@ __global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const Appl
 #pragma unroll
                 for (int t = 0; t < 4; ++t) store_w(s, g, t, col, off);
         }
-        if constexpr (!DEEP && decltype(more)::value) {               // (loads return in order: what is needed first)
-            load_q(s, next);
+        if constexpr (!TWO_Q && decltype(more)::value) load_q(0, next, go_on);   // (loads return in order: what is needed first)
+        if constexpr (!TWO && decltype(more)::value) {
 #pragma unroll
             for (int g = 0; g < G; ++g)
 #pragma unroll
@@ -607,7 +617,7 @@ __global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const Appl
     };
 
     int col = pass_col(0);
-    load_q(0, col);
+    load_q(0, col, true);
     {
         const uint32_t off = offset(col);
 #pragma unroll
@@ -618,14 +628,14 @@ __global__ __launch_bounds__(NT, DEEP ? 2 : 4) void k_decompress_wide(const Appl
     build_u_tile<R, DD, (D::size == 4 && (R > 8 || DD == 8) ? 4 : 8), BIG, NT>(UnitPlace<LP, PLANE>{smem}, pent, S, P_idx, P_val, i0, m, r, DD);
     __syncthreads();
     constexpr std::integral_constant<int, 0> even{};
-    constexpr std::integral_constant<int, NB - 1> odd{};
-    if constexpr (DEEP) {
+    if constexpr (TWO) {
+        constexpr std::integral_constant<int, 1> odd{};
         for (int p = 0; p < npass;) {
             int next = pass_col(min(p + 1, npass - 1));
-            pass(even, col, next, p + 1 < npass, std::false_type{});
+            pass(even, col, next, p + 1 < npass, std::true_type{});
             if (++p >= npass) break;
             col = next; next = pass_col(min(p + 1, npass - 1));
-            pass(odd, col, next, p + 1 < npass, std::false_type{});
+            pass(odd, col, next, p + 1 < npass, std::true_type{});
             ++p; col = next;
         }
     } else {
@@ -783,10 +793,11 @@ static bool fast_shape(int32_t n, int32_t d) { return (n % 2) == 0 && (d == 2 ||
 // whole units of 4, every matrix of the group, or the group goes to k_decompress, with the same result.  Where both can, it is used
 //   for d = 16, where two columns' entries of Q in a thread leave k_decompress 192 registers: 4096 x 16384, r = 1024, bf16, zipf 129 and 101; 4096 x 4096, r = 1024, fp32 53.0 and
 //     43.6; 2048 x 2048, r = 256, bf16 (8 rows) 15.3 and 12.4; bias pass 4096 x 4096, r = 512, bf16 77 and 67, with the compress call before it;
-//   for 16 bits in blocks of 16 and 32 rows: four matrices 4096 x 11008, r = 512, d = 8 187 and 167 (176 and 166 with Q reordered); 4096 x 16384, r = 512, d = 8 74.6 and 66.0;
-//     4096 x 8192, r = 256, d = 2 30.3 and 28.6; 16384 x 4096, d = 4 57.1 and 55.4; it is even on 4096 x 4096 and 4096 x 8192, d = 8;
-//   for fp32 where the grid fits the chip at once (deep) and in the bias pass: 4096 x 4096, r = 512, d = 8 31.9 and 30.7; 4096 x 8192, d = 4 56.4 and 54.0; 3072 x 3072, r = 1024,
-//     d = 8 27.5 and 25.8; two calls with a bias pass, 8192 x 2048, r = 256, d = 4 62.3 and 53.6.
+//   for 16 bits in blocks of 16 and 32 rows: four matrices 4096 x 11008, r = 512, d = 8 187 and 167 (176 and 166 with Q reordered); 4096 x 16384, r = 512, d = 8 75.7 and 66.8;
+//     4096 x 8192, r = 256, d = 2 31.6 and 28.9; 16384 x 4096, d = 4 57.8 and 56.2; 4096 x 4096, r = 512, d = 8 22.2 and 21.6 (21.7 and 21.6 reordered); bias pass, r = 512, d = 8, 4096
+//     x 4096 22.2 and 21.3 (20.6 and 21.0 reordered), 4096 x 11008 44.5 and 39.6 (40.4 and 38.9), 11008 x 4096 51.7 and 44.3 (46.1 and 43.8);
+//   for fp32 where the grid fits the chip at once (deep) and in the bias pass: 4096 x 4096, r = 512, d = 8 32.9 and 30.6; 4096 x 2048, r = 256, d = 4 25.1 and 16.7; bias pass
+//     8192 x 2048, r = 256, d = 4 27.6 and 18.4, 8192 x 4096, r = 512, d = 8 43.0 and 38.2.
 // Elsewhere k_decompress is ahead: fp32 on larger grids (8192 x 4096, r = 512, d = 8 58.4 and 66.5; with 16 rows a thread has half as many registers in flight), and d <= 8 in
 // blocks of 8 rows, whose pieces are 8 bytes (2048 x 2048, r = 512, d = 8, bf16 8.8 and 9.5; 4096 x 4096, r = 2048, d = 8 44.5 and 46.8).
 constexpr unsigned kResidentDeep = 256;                              // workgroups of the deep form, one a CU
@@ -794,6 +805,21 @@ static bool wide_group(const ApplyGroup& g, int32_t r) {
     bool wide = r >= 4 && r % 4 == 0;
     for (int p = 0; p < g.count; ++p) wide = wide && g.n[p] % 8 == 0 && g.n[p] <= 1 << 24;   // (32-bit offsets inside a plane of rows)
     return wide;
+}
+// Small work where k_decompress is ahead all the same (blocks of 16 rows of 512 threads, d <= 8; grid: workgroups, n: the widest matrix).  In a call of one pass nothing covers
+// the lane moves, two of the six VALU instructions of an entry, and k_decompress makes the tile faster where a thread has one item of it (r <= 128).  (us, k_decompress and k_decompress_wide.)
+//   One workgroup a CU, n <= 1024, bf16: 4096 x 768, r = 128, d = 2 5.8 and 6.5; r = 256 7.2 and 7.0; d = 4 7.0 and 7.3; 4096 x 512, r = 256, d = 8 7.7 and 8.3; 4096 x 1024, r = 512,
+//     d = 4 8.7 and 8.4; from 1280 columns on it is ahead (4096 x 1280, r = 128, d = 4 9.5 and 8.5).  fp32: 4096 x 1024, r = 256, d = 2 9.6 and 10.5, d = 4 10.3 and 10.8, d = 8 12.2
+//     and 11.9; in its bias pass it is ahead (d = 4 12.1 and 10.7).
+//   257 to 511 blocks, r <= 128: 5120 x 1280, d = 2 10.5 and 11.4, d = 4 12.1 and 13.0, d = 8 16.0 and 15.8; r = 256 13.0 and 12.2, 13.7 and 13.1; bias pass 5120 x 4096, r = 128, d = 2
+//     16.8 and 17.3, d = 4 22.0 and 21.0.
+static bool narrow_call(unsigned grid, int32_t n, int32_t r, int32_t d, int elem_size, bool norms) {
+    if (grid <= kResidentDeep) {
+        if (n > 1024) return false;
+        return elem_size == 2 ? r <= 64 * d : !norms && d <= 4;
+    }
+    if (grid >= 512) return false;
+    return r <= 128 && d <= (norms ? 2 : 4);
 }
 
 template <typename D, int RG, int PS, int NT, bool NORMS = false>
@@ -816,11 +842,12 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
     }
     const unsigned grid = (unsigned)g.first[g.count];
     hipError_t e;
-    if (fast && wide_group(g, r)) {
+    const bool narrow = RG == 4 && NT == 512 && d <= 8 && narrow_call(grid, g.n[0], r, d, D::size, NORMS);   // (the matrices are in the order of their widths)
+    if (fast && !narrow && wide_group(g, r)) {
         constexpr int LP = RG == 2 ? 2 : 4, G = RG == 2 ? 1 : RG / 4;
-#define LSP_LAUNCH_WIDE(DDV, DEEPV)                                                                            \
+#define LSP_LAUNCH_WIDE(DDV, FORM)                                                                             \
     do {                                                                                                       \
-        constexpr auto kern = k_decompress_wide<D, G, LP, DDV, (PS > 16384), NT, NORMS, DEEPV>;                \
+        constexpr auto kern = k_decompress_wide<D, G, LP, DDV, (PS > 16384), NT, NORMS, FORM>;                 \
         constexpr size_t ents = (size_t)RG * 4 * DDV * sizeof(int2);                                           \
         constexpr size_t units = G > 1 ? (size_t)RG * PS : (size_t)(PS > 16384 ? 2048 : 1024) * 16 * LP;       \
         if ((e = allow_dynamic_lds<kern, units + ents>()) != hipSuccess) return e;                             \
@@ -832,8 +859,10 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
 #define LSP_WIDE(DDV)                                                                                          \
     do {                                                                                                       \
         if constexpr (G == 1 && NT == 512)                                                                     \
-            if (grid <= kResidentDeep) LSP_LAUNCH_WIDE(DDV, (G == 1 && NT == 512));                            \
-        if constexpr ((D::size == 2 || DDV == 16 || NORMS) && (LP == 4 || PS > 16384)) LSP_LAUNCH_WIDE(DDV, false);   \
+            if (grid <= kResidentDeep) LSP_LAUNCH_WIDE(DDV, kDeep);                                            \
+        if constexpr (G == 1 && NT == 512 && DDV <= 8 && D::size == 2 && !NORMS)                               \
+            if (grid < 512 && g.n[0] <= 2048) LSP_LAUNCH_WIDE(DDV, kPlain);                                    \
+        if constexpr ((D::size == 2 || DDV == 16 || NORMS) && (LP == 4 || PS > 16384)) LSP_LAUNCH_WIDE(DDV, (G == 1 ? kTwo : kPlain));   \
     } while (0)
         if constexpr (LP == 4) {
             if (d == 2) LSP_WIDE(2);

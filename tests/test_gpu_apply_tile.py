@@ -67,3 +67,13 @@ def test_apply_and_bias_with_a_large_tile_of_8_rows(m, n, r, dtype):
 def test_bias_in_whole_pieces(m, n, r, d, dtype):
     from test_gpu_parity import _bias_check
     _bias_check(syn.make_problem("bias pieces", m, n, r, d, dtype, seed=9600 + m + n + r + d, g_std=1.0))
+
+
+# Passes that take turns with two sets of registers: one to four of them, on one workgroup a CU (2069), on one or two (4100) and on workgroups of 256 threads (8200).
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("d", [2, 4, 8])
+@pytest.mark.parametrize("m,n,r", [(2069, 3080, 260), (4100, 2056, 260), (4100, 3072, 132), (8200, 264, 132), (8200, 1032, 132), (8200, 2048, 260)])
+def test_apply_and_bias_over_several_passes(m, n, r, d, dtype):
+    from test_gpu_parity import _bias_check
+    test_apply_in_whole_pieces(m, n, r, d, dtype)
+    _bias_check(syn.make_problem("bias passes", m, n, r, d, dtype, seed=9800 + m + n + r + d, g_std=1.0))
