@@ -230,6 +230,13 @@ __device__ __forceinline__ RowBlocks problem_of(int block) {
     return RowBlocks{g->G[p], g->plan[p], g->T[p], g->S[p], g->m[p], g->n[p], block - g->first_gq[p], g->first_gq[p + 1] - g->first_gq[p]};
 }
 
+// Blocks begin with different chunks, and go around: rows a power of two apart would have all workgroups on the same few memory channels at a time (4096 x 16384, r = 256, d = 2 46.1 -> 39.5 us, r = 512, d = 8 58.4 -> 55.2; 8192 x 8192, r = 512, d = 8 62.6 -> 60.5; with two chunks it does nothing).  Which one is a matter of the
+// row alone, so that the sums of a row do not depend on the blocks it is in.  (Golden-ratio steps, so that neighbouring blocks of 16 rows spread evenly.)
+__device__ __forceinline__ int chunk_at(int k, int row0, int nchunks) {
+    const int at = k + (nchunks > 2 ? (int)__umulhi((uint32_t)(row0 >> 4) * 0x9E3779B9u, (uint32_t)nchunks) : 0);
+    return at < nchunks ? at : at - nchunks;
+}
+
 // The row blocks of a workgroup, one after the other, as both kinds of waves see them; they meet at the same barriers.
 // kind: blocks whose sums fit the LDS (whole), or the others.
 template <int NP, bool HALVES> struct BlockWalk {
@@ -265,7 +272,8 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
         } else if (H->p_any_split) fill_s(pr.S, 0.0f, r, pr.block, pr.blocks, tid, kFetchers);
     };
     BlockWalk<NP, false> w;
-    int c = 0;
+    int c = 0;                                                        // the how manieth chunk of the block
+    auto chunk = [&]() { return chunk_at(c, w.pr.block * R, w.nchunks); };
     auto advance = [&]() {
         if (++c >= w.nchunks) { c = 0; w.find(w.block + gridDim.x, blocks, r, d, clear_s); }
     };
@@ -274,27 +282,28 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
 
     // The coming chunk's note, with the table of its columns: found out while the chunk before is walked.
     u32x4 cols, seg;                                                  // this thread's part of the tables
-    uint32_t first_step = 0;                                          // threads 0 .. 7: a wave's first step in the chunk after, 8 .. 15: in this one
+    uint32_t step_after = 0, step_here = 0;                           // threads 0 .. 7: a wave's first step in the chunk after, 8 .. 15: in this one
     const uint8_t *steps_here, *steps_after;
     struct { float* T; const uint8_t* plan; uint32_t vcol, vcnt, flags; int32_t rows, nvcols; } head;
     int turn = 0;
     static_assert(sizeof(ChunkNote::cols) == kFetchers * 16 && sizeof(ChunkNote::seg) == 16 * 16, "16 bytes a thread");
     auto segs = [](const RowBlocks& pr, PlanHeaderPtr H, int chunk) { return pr.plan + H->off_m_seg + (size_t)chunk * (kWavesMM * sizeof(TileSeg)); };
-    auto look_up = [&](const RowBlocks& pr, PlanHeaderPtr H, int nchunks, int chunk, int rows_of, int row0) {
+    auto look_up = [&](const RowBlocks& pr, PlanHeaderPtr H, int nchunks, int k, int rows_of, int row0) {
+        const int chunk = chunk_at(k, row0, nchunks);
         cols = reinterpret_cast<const u32x4*>(pr.plan + H->off_m_cols)[(size_t)chunk * kFetchers + tid];
         const uint8_t* here = segs(pr, H, chunk);
         if (tid < 16) seg = reinterpret_cast<const u32x4*>(here)[tid];
-        if (tid >= kWavesMM && tid < 2 * kWavesMM) first_step = reinterpret_cast<const TileSeg*>(here)[tid - kWavesMM].first_step;
+        if (tid >= kWavesMM && tid < 2 * kWavesMM) step_here = reinterpret_cast<const TileSeg*>(here)[tid - kWavesMM].first_step;
         steps_here = steps_after = pr.plan + H->off_m_steps;
         head.T = pr.T + (int64_t)row0 * r;
         head.plan = pr.plan;
         head.vcol = (uint32_t)H->off_q_vcol; head.vcnt = (uint32_t)H->off_q_vcnt;
         head.rows = pr.m - row0 < rows_of ? pr.m - row0 : rows_of;
         head.nvcols = H->nvcols;
-        head.flags = (chunk == 0 ? kFirstChunk : 0) | (chunk + 1 == nchunks ? kLastChunk : 0) | (H->q_any_shared ? kSharedColumns : 0);
+        head.flags = (k == 0 ? kFirstChunk : 0) | (k + 1 == nchunks ? kLastChunk : 0) | (H->q_any_shared ? kSharedColumns : 0);
     };
     auto look_after = [&](const RowBlocks& pr, PlanHeaderPtr H, int chunk) {   // the chunk after the one above
-        if (tid < kWavesMM) first_step = reinterpret_cast<const TileSeg*>(segs(pr, H, chunk))[tid].first_step;
+        if (tid < kWavesMM) step_after = reinterpret_cast<const TileSeg*>(segs(pr, H, chunk))[tid].first_step;
         steps_after = pr.plan + H->off_m_steps;
         head.flags |= kMoreChunks;
     };
@@ -304,7 +313,7 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
         reinterpret_cast<u32x4*>(note->cols)[tid] = cols;
         if (tid < 16) {
             reinterpret_cast<u32x4*>(note->seg)[tid] = seg;
-            (&note->steps[0][0])[tid] = (uint64_t)(uintptr_t)((tid < kWavesMM ? steps_after : steps_here) + (size_t)first_step * (kWave * 16));
+            (&note->steps[0][0])[tid] = (uint64_t)(uintptr_t)((tid < kWavesMM ? steps_after : steps_here) + (size_t)(tid < kWavesMM ? step_after : step_here) * (kWave * 16));
         }
         if (tid == 0) {
             note->T = head.T; note->plan = head.plan; note->vcol = head.vcol; note->vcnt = head.vcnt;
@@ -313,44 +322,65 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
     };
 
     const RowBlocks start = problem_of(blockIdx.x);                   // nearly always the first: its rows are asked for before its plan is looked at
-    lo.fetch(static_cast<const uint16_t*>(start.G), (int64_t)start.block * R, start.m, start.n, 0, tid);
-    hi.fetch(static_cast<const uint16_t*>(start.G), (int64_t)start.block * R + R / 2, start.m, start.n, 0, tid);
+    lo.fetch(static_cast<const uint16_t*>(start.G), (int64_t)start.block * R, start.m, start.n, chunk_at(0, start.block * R, (int)(((uint32_t)start.n + kChunk - 1) / kChunk)), tid);
+    hi.fetch(static_cast<const uint16_t*>(start.G), (int64_t)start.block * R + R / 2, start.m, start.n, chunk_at(0, start.block * R, (int)(((uint32_t)start.n + kChunk - 1) / kChunk)), tid);
     w.find(blockIdx.x, blocks, r, d, clear_s);
-    bool have = w.block < blocks;
-    if (have) {
-        if (w.block != (int)blockIdx.x) {
-            lo.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R, w.pr.m, w.pr.n, c, tid);
-            hi.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R + R / 2, w.pr.m, w.pr.n, c, tid);
-        }
-        look_up(w.pr, w.H, w.nchunks, c, R, w.pr.block * R);
-        lo.arrange(ulo); hi.arrange(uhi);
-        advance();
-        if (w.block < blocks) {
-            look_after(w.pr, w.H, c);
-            lo.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R, w.pr.m, w.pr.n, c, tid);
-        }
-        put_note();
-        __syncthreads();                                              // the first note is there
-    }
-    while (have) {
+    auto fetch_lo = [&]() { lo.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R, w.pr.m, w.pr.n, chunk(), tid); };
+    auto fetch_hi = [&]() { hi.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R + R / 2, w.pr.m, w.pr.n, chunk(), tid); };
+    auto look_up_here = [&]() { look_up(w.pr, w.H, w.nchunks, c, R, w.pr.block * R); };
+    // Arranges a half now: the compiler, which would rather do it where the units are stored, would have the next loads in other registers then, and wait for them to move them.
+    auto arrange = [&](RowStager<NH, WHOLE>& half, u32x2 (&unit)[NH][8]) {
+        half.arrange(unit);
+#pragma unroll
+        for (int p = 0; p < NH; ++p)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) asm volatile("" : "+v"(unit[p][q]));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto put = [&]() {
         if constexpr (WHOLE && NP == 4) put_block<NP, NH>(smem, ulo, uhi, tid);
         else {
             put_units<NP, NH>(smem, ulo, 0, tid);
             put_units<NP, NH>(smem, uhi, 1, tid);
         }
-        __syncthreads();                                              // staged
-        have = w.block < blocks;
-        if (have) {
-            look_up(w.pr, w.H, w.nchunks, c, R, w.pr.block * R);
-            hi.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R + R / 2, w.pr.m, w.pr.n, c, tid);
-            lo.arrange(ulo);
-            advance();
-            const bool more = w.block < blocks;
-            if (more) look_after(w.pr, w.H, c);
-            hi.arrange(uhi);
-            put_note();
-            if (more) lo.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R, w.pr.m, w.pr.n, c, tid);
+    };
+    if (w.block < blocks) {
+        if (w.block != (int)blockIdx.x) {
+            fetch_lo();
+            fetch_hi();
         }
+        look_up_here();
+        arrange(lo, ulo);
+        arrange(hi, uhi);
+        advance();
+        const bool more = w.block < blocks;
+        if (more) look_after(w.pr, w.H, chunk());
+        put_note();
+        __syncthreads();                                              // the first note is there
+        put();
+        if (more) {
+            fetch_lo();
+            for (;;) {                                                // a chunk is staged, the first half of the rows of the next is on its way
+                __syncthreads();                                      // staged
+                look_up_here();
+                fetch_hi();
+                arrange(lo, ulo);
+                advance();
+                if (w.block >= blocks) break;                         // (what a round fetches for the next it fetches always: what may stay as it was is moved as well)
+                look_after(w.pr, w.H, chunk());
+                fetch_lo();
+                __builtin_amdgcn_sched_barrier(0);
+                arrange(hi, uhi);
+                put_note();
+                __syncthreads();                                      // no longer read
+                put();
+            }
+            arrange(hi, uhi);
+            put_note();
+            __syncthreads();                                          // no longer read
+            put();
+        }
+        __syncthreads();                                              // staged
         __syncthreads();                                              // no longer read
     }
     if constexpr (NP == 4) {
@@ -363,16 +393,16 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
         turn = 0;
         auto tell = [&]() {
             look_up(h.pr, h.H, h.nchunks, k, R / 2, h.pr.block * R + part * (R / 2));
-            if (k + 1 < h.nchunks) look_after(h.pr, h.H, k + 1);
-            else if (part == 0) look_after(h.pr, h.H, 0);
-            else if (following.block < blocks) look_after(following.pr, following.H, 0);
+            if (k + 1 < h.nchunks) look_after(h.pr, h.H, chunk_at(k + 1, h.pr.block * R, h.nchunks));
+            else if (part == 0) look_after(h.pr, h.H, chunk_at(0, h.pr.block * R, h.nchunks));
+            else if (following.block < blocks) look_after(following.pr, following.H, chunk_at(0, following.pr.block * R, following.nchunks));
             put_note();
         };
         __syncthreads();                                              // nobody reads the last note of the other blocks any more
         tell();
         __syncthreads();                                              // the first note is there
         while (h.block < blocks) {
-            lo.fetch(static_cast<const uint16_t*>(h.pr.G), (int64_t)h.pr.block * R + part * (R / 2), h.pr.m, h.pr.n, k, tid);
+            lo.fetch(static_cast<const uint16_t*>(h.pr.G), (int64_t)h.pr.block * R + part * (R / 2), h.pr.m, h.pr.n, chunk_at(k, h.pr.block * R, h.nchunks), tid);
             lo.arrange(ulo);
             put_units<2, 2>(smem, ulo, 0, tid);
             zero_unit<2>(smem, tid);                                  // (inside the larger units)
@@ -580,7 +610,7 @@ __device__ __forceinline__ void walk_blocks(uint8_t* smem, int blocks, int r, in
         __builtin_amdgcn_s_waitcnt(0x0F70);                           // vmcnt(0)
         __builtin_amdgcn_sched_barrier(0);
     };
-    ring_of((uint64_t)(uintptr_t)w.pr.plan + w.H->off_m_steps + (uint64_t)as_const<TileSeg>(w.pr.plan + w.H->off_m_seg)[wave].first_step * (kWave * 16));
+    ring_of((uint64_t)(uintptr_t)w.pr.plan + w.H->off_m_steps + (uint64_t)as_const<TileSeg>(w.pr.plan + w.H->off_m_seg)[chunk_at(0, w.pr.block * kRowsMM<NP>, w.nchunks) * kWavesMM + wave].first_step * (kWave * 16));
     const auto uniform = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
     const auto uniform2 = [&](uint32_t lo, uint32_t hi) { return (uint64_t)uniform(hi) << 32 | uniform(lo); };
     const auto piece16 = [&](const void* p) { return *static_cast<const u32x4*>(p); };
