@@ -53,7 +53,8 @@ struct ChunkNote {
 };
 constexpr uint32_t kFirstChunk = 1, kLastChunk = 2, kMoreChunks = 4, kSharedColumns = 8;
 static_assert(sizeof(ChunkNote) % 16 == 0 && sizeof(TileSeg) == 32, "read in pieces of 16 bytes");
-template <int NP> constexpr int kSumsBase = kNoteBase<NP> + 2 * (int)sizeof(ChunkNote);   // ... and of the sums
+template <int NP> constexpr int kSecondBase = kNoteBase<NP> + 2 * (int)sizeof(ChunkNote);   // ... of a second chunk where there is room for two
+template <int NP> __host__ __device__ constexpr int sums_base(bool two) { return kSecondBase<NP> + (two ? kNoteBase<NP> : 0); }   // ... and of the sums
 // Floats from a row of the sums to the next: 16 rows of a column lie in 16 different banks, and four columns are 16 bytes.
 __device__ __forceinline__ int sums_stride(int nvcols) { return (nvcols + kTileCols - 1) / kTileCols * kTileCols + 4; }
 
@@ -230,6 +231,24 @@ __device__ __forceinline__ RowBlocks problem_of(int block) {
     return RowBlocks{g->G[p], g->plan[p], g->T[p], g->S[p], g->m[p], g->n[p], block - g->first_gq[p], g->first_gq[p + 1] - g->first_gq[p]};
 }
 
+__device__ __forceinline__ bool sums_fit(int nvcols, int rows, int base) { return sums_stride(nvcols) * rows * 4 <= kLdsMM - base; }
+
+// Whether the LDS has room for two chunks beside the sums of every matrix of the call (16 rows: up to 352 virtual columns; 8 rows: always).  H: the plan of one of them.
+template <int NP> __device__ __forceinline__ bool two_chunks(PlanHeaderPtr H) {
+    static_assert((kMaxSlots * kThreadsGQ + 4) * kRowsMM<2> * 4 <= kLdsMM - sums_base<2>(true), "8 rows");
+    if constexpr (NP == 2) return true;
+    const auto* g = (const LSP_CONST_AS CompressGroup*)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t most = (uint32_t)H->nvcols;
+    if (g->count > 1) {
+#pragma unroll
+        for (int p = 0; p < kMaxGroup; ++p) {                         // (all of them asked for before the first is looked at)
+            const uint32_t v = (uint32_t)as_const<PlanHeader>(g->plan[p < g->count ? p : 0])->nvcols;
+            most = v > most ? v : most;
+        }
+    }
+    return most <= (uint32_t)(kMaxSlots * kThreadsGQ) && sums_fit((int)most, kRowsMM<NP>, sums_base<NP>(true));
+}
+
 // Blocks begin with different chunks, and go around: rows a power of two apart would have all workgroups on the same few memory channels at a time (4096 x 16384, r = 256, d = 2 46.1 -> 39.5 us, r = 512, d = 8 58.4 -> 55.2; 8192 x 8192, r = 512, d = 8 62.6 -> 60.5; with two chunks it does nothing).  Which one is a matter of the
 // row alone, so that the sums of a row do not depend on the blocks it is in.  (Golden-ratio steps, so that neighbouring blocks of 16 rows spread evenly.)
 __device__ __forceinline__ int chunk_at(int k, int row0, int nchunks) {
@@ -253,8 +272,7 @@ template <int NP, bool HALVES> struct BlockWalk {
             visit(pr, H, planned);
             if (!planned) continue;
             nchunks = H->nchunks;
-            const bool fits = sums_stride(H->nvcols) * (kRowsMM<NP> * 4) <= kLdsMM - kSumsBase<NP>;
-            if (fits != HALVES) return;
+            if (sums_fit(H->nvcols, kRowsMM<NP>, sums_base<NP>(NP == 2)) != HALVES) return;
         }
     }
 };
@@ -337,51 +355,53 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
             for (int q = 0; q < 8; ++q) asm volatile("" : "+v"(unit[p][q]));
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto put = [&]() {
-        if constexpr (WHOLE && NP == 4) put_block<NP, NH>(smem, ulo, uhi, tid);
+    auto put = [&](uint8_t* units) {
+        if constexpr (WHOLE && NP == 4) put_block<NP, NH>(units, ulo, uhi, tid);
         else {
-            put_units<NP, NH>(smem, ulo, 0, tid);
-            put_units<NP, NH>(smem, uhi, 1, tid);
+            put_units<NP, NH>(units, ulo, 0, tid);
+            put_units<NP, NH>(units, uhi, 1, tid);
         }
     };
+    // Where there is room for two chunks, one is staged beside the one that is walked, and all waves meet once a chunk: it is staged, and the one before has been walked; and once more
+    // after a block's last chunk: all sums are there.  Otherwise they meet twice: the chunk before is no longer read, then the new one is staged.
     if (w.block < blocks) {
         if (w.block != (int)blockIdx.x) {
             fetch_lo();
             fetch_hi();
         }
+        const bool two = two_chunks<NP>(w.H);
+        bool after_last = false;
         look_up_here();
-        arrange(lo, ulo);
-        arrange(hi, uhi);
-        advance();
-        const bool more = w.block < blocks;
-        if (more) look_after(w.pr, w.H, chunk());
-        put_note();
-        __syncthreads();                                              // the first note is there
-        put();
-        if (more) {
-            fetch_lo();
-            for (;;) {                                                // a chunk is staged, the first half of the rows of the next is on its way
-                __syncthreads();                                      // staged
-                look_up_here();
-                fetch_hi();
-                arrange(lo, ulo);
-                advance();
-                if (w.block >= blocks) break;                         // (what a round fetches for the next it fetches always: what may stay as it was is moved as well)
-                look_after(w.pr, w.H, chunk());
-                fetch_lo();
-                __builtin_amdgcn_sched_barrier(0);
-                arrange(hi, uhi);
-                put_note();
-                __syncthreads();                                      // no longer read
-                put();
-            }
+        auto stage = [&]() {
+            uint8_t* const units = smem + (two ? turn * kSecondBase<NP> : 0);
             arrange(hi, uhi);
             put_note();
-            __syncthreads();                                          // no longer read
-            put();
+            if (!two) __syncthreads();                                // no longer read (at first: the first note is there)
+            put(units);
+        };
+        auto meet = [&]() {
+            if (two && after_last) __syncthreads();                   // the sums of a block are there
+            __syncthreads();                                          // staged
+        };
+        for (;;) {
+            arrange(lo, ulo);
+            const bool last = c + 1 == w.nchunks;
+            advance();
+            if (w.block >= blocks) break;                             // (what a round fetches for the next it fetches always: what may stay as it was is moved as well)
+            look_after(w.pr, w.H, chunk());
+            fetch_lo();
+            __builtin_amdgcn_sched_barrier(0);
+            stage();
+            if (!two) meet();
+            __builtin_amdgcn_sched_barrier(0);
+            fetch_hi();                                               // (some 900 cycles)
+            look_up_here();
+            if (two) meet();
+            after_last = last;
         }
-        __syncthreads();                                              // staged
-        __syncthreads();                                              // no longer read
+        stage();
+        meet();
+        __syncthreads();                                              // no longer read; the sums of the last block are there
     }
     if constexpr (NP == 4) {
         auto none = [](const RowBlocks&, PlanHeaderPtr, bool) {};
@@ -440,12 +460,14 @@ __device__ __forceinline__ void walk_blocks(uint8_t* smem, int blocks, int r, in
     constexpr int kGroup = NW == 4 ? 2 : 1;                           // log2 of the blocks that one list's values go to
     const int lane = tid & (kWave - 1), part = lane & 3;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    float* const sums = reinterpret_cast<float*>(smem + kSumsBase<NP>);
-    const ChunkNote* note = reinterpret_cast<const ChunkNote*>(smem + kNoteBase<NP>);
+    const ChunkNote* const first_note = reinterpret_cast<const ChunkNote*>(smem + kNoteBase<NP>);
+    const ChunkNote* note = first_note;
     auto column = [&](int i) { return note->cols[wave][lane >> 2][i]; };   // of this 4-lane group's two lists in tile i
     BlockWalk<NP, HALVES> w;
     w.find(blockIdx.x, blocks, r, d, [](const RowBlocks&, PlanHeaderPtr, bool) {});
     if (w.block >= blocks) return;
+    const bool two = !HALVES && two_chunks<NP>(w.H);                  // (see fetch_blocks)
+    const uint32_t sums_at = (uint32_t)sums_base<NP>(two);
 
     // A chunk's steps lie one behind the other.  ring: the next kRing, from slot 0 on; those of the next chunk take the places of the last ones.
     u32x4 ring[kRing];
@@ -467,7 +489,7 @@ __device__ __forceinline__ void walk_blocks(uint8_t* smem, int blocks, int r, in
     float before[2][NW];                                              // asked for when the tile begins
     uint32_t own_cols;                                                // columns of this 4-lane group's two lists in the next tile
     auto places = [&](uint32_t both) {
-        const uint32_t mine = (uint32_t)kSumsBase<NP> + (lane & (R - 1)) * stride * 4;   // (LDS address)
+        const uint32_t mine = sums_at + (lane & (R - 1)) * stride * 4;   // (LDS address)
         auto place = [&](auto which) {
             constexpr int a = decltype(which)::value;
             const uint32_t x = list_of<NW, a>(both);
@@ -527,7 +549,7 @@ __device__ __forceinline__ void walk_blocks(uint8_t* smem, int blocks, int r, in
 
     // The transposing read takes entry e of a list from lanes 4 e .. 4 e + 3 of 16, lane 4 e + s the s-th 8 bytes, and hands lane l the l-th row's four values:
     // with NW = 4 all of one unit, with NW = 2 of the units of two lists.  The offsets of entry e of the 16 lanes' four lists are in the fourth lane of their 4-lane group.
-    const uint32_t piece = (part & (NW - 1)) * 8;
+    uint32_t piece = (part & (NW - 1)) * 8;                           // (of the present chunk)
     s16x4 g[2][2][NW];
     auto gather = [&](auto slot) {
         constexpr int k = decltype(slot)::value;
@@ -615,8 +637,9 @@ __device__ __forceinline__ void walk_blocks(uint8_t* smem, int blocks, int r, in
     const auto uniform2 = [&](uint32_t lo, uint32_t hi) { return (uint64_t)uniform(hi) << 32 | uniform(lo); };
     const auto piece16 = [&](const void* p) { return *static_cast<const u32x4*>(p); };
     if (HALVES) __syncthreads();                                      // the other blocks' last note has been read
-    __syncthreads();                                                  // the first note is there
-    for (;;) {
+    if (!two) __syncthreads();                                        // the first note is there
+    int nvcols;
+    auto read_note = [&]() {
         const u32x4 seg0 = piece16(&note->seg[wave]), seg1 = piece16(reinterpret_cast<const uint8_t*>(&note->seg[wave]) + 16);
         const u32x2 after = *reinterpret_cast<const u32x2*>(&note->steps[0][wave]), here = *reinterpret_cast<const u32x2*>(&note->steps[1][wave]);
         const u32x2 head = *reinterpret_cast<const u32x2*>(&note->nvcols);
@@ -625,10 +648,14 @@ __device__ __forceinline__ void walk_blocks(uint8_t* smem, int blocks, int r, in
         len_lo = uniform2(seg0.z, seg0.w); len_hi = uniform2(seg1.x, seg1.y);
         next = uniform2(after.x, after.y);
         ahead = uniform2(here.x, here.y) + kRing * (kWave * 16);
-        const int nvcols = (int)uniform(head.x);
+        nvcols = (int)uniform(head.x);
         flags = uniform(head.y);
         stride = sums_stride(nvcols);
+    };
+    for (;;) {
+        if (!two) read_note();
         __syncthreads();                                              // the chunk is staged
+        if (two) read_note();
         wait_for_loads();
         t = 0;
         if (steps > 0) walk_chunk();
@@ -645,17 +672,19 @@ __device__ __forceinline__ void walk_blocks(uint8_t* smem, int blocks, int r, in
 #pragma unroll
                     for (int a = 0; a < NW; ++a) *dst[h][a] = 0.0f;
             }
-        __syncthreads();                                              // no longer read; all sums are there
+        if (!two || (flags & kLastChunk)) __syncthreads();            // no longer read; all sums are there
         if (flags & kLastChunk) {
             int thread = tid;                                         // (opaque, so that nothing of this is made outside the loop, and kept in registers all along)
             asm volatile("" : "+v"(thread));
             const u32x4 head0 = piece16(&note->T), head1 = piece16(&note->vcol);
             const uint64_t plan = uniform2(head0.z, head0.w);
-            store_sums<R>(sums, stride, (float LSP_GLOBAL_AS*)uniform2(head0.x, head0.y), (const uint16_t LSP_GLOBAL_AS*)(plan + uniform(head1.x)),
+            store_sums<R>(reinterpret_cast<const float*>(smem + sums_at), stride, (float LSP_GLOBAL_AS*)uniform2(head0.x, head0.y), (const uint16_t LSP_GLOBAL_AS*)(plan + uniform(head1.x)),
                           (const uint16_t LSP_GLOBAL_AS*)(plan + uniform(head1.y)), (flags & kSharedColumns) != 0, nvcols, (int)uniform(head1.z), r, thread);
         }
         if (!(flags & kMoreChunks)) break;
-        note = reinterpret_cast<const ChunkNote*>(smem + kNoteBase<NP>) + (note == reinterpret_cast<const ChunkNote*>(smem + kNoteBase<NP>));
+        const bool second = note == first_note;
+        note = first_note + second;
+        if (two) piece = (part & (NW - 1)) * 8 + (second ? (uint32_t)kSecondBase<NP> : 0u);
     }
 }
 
@@ -664,6 +693,7 @@ __global__ __launch_bounds__(kThreadsMM) void k_compress_mm(const CompressGroup 
     extern __shared__ __align__(16) uint8_t smem[];
     const int tid = threadIdx.x;
     zero_unit<NP>(smem, tid);
+    zero_unit<NP>(smem + kSecondBase<NP>, tid);                       // (where there is no second chunk, sums of later on)
     if (__builtin_amdgcn_readfirstlane(tid) >= kWalkers) fetch_blocks<NP, WHOLE>(smem, blocks, r, d, tid - kWalkers);
     else {
         walk_blocks<NP, false>(smem, blocks, r, d, tid);
