@@ -51,7 +51,7 @@ struct ChunkNote {
     int32_t nvcols;                                                   // virtual columns
     uint32_t flags, pad1[2];
 };
-constexpr uint32_t kFirstChunk = 1, kLastChunk = 2, kMoreChunks = 4, kSharedColumns = 8;
+constexpr uint32_t kFirstChunk = 1, kLastChunk = 2, kMoreChunks = 4, kSharedColumns = 8, kHalvesFollow = 16;
 static_assert(sizeof(ChunkNote) % 16 == 0 && sizeof(TileSeg) == 32, "read in pieces of 16 bytes");
 template <int NP> constexpr int kSecondBase = kNoteBase<NP> + 2 * (int)sizeof(ChunkNote);   // ... of a second chunk where there is room for two
 template <int NP> __host__ __device__ constexpr int sums_base(bool two) { return kSecondBase<NP> + (two ? kNoteBase<NP> : 0); }   // ... and of the sums
@@ -260,6 +260,7 @@ __device__ __forceinline__ int chunk_at(int k, int row0, int nchunks) {
 // kind: blocks whose sums fit the LDS (whole), or the others.
 template <int NP, bool HALVES> struct BlockWalk {
     int block;                                                        // past the last one: no more
+    bool others = false;                                              // blocks of the other kind were passed by
     RowBlocks pr;
     PlanHeaderPtr H;
     int nchunks;
@@ -273,6 +274,7 @@ template <int NP, bool HALVES> struct BlockWalk {
             if (!planned) continue;
             nchunks = H->nchunks;
             if (sums_fit(H->nvcols, kRowsMM<NP>, sums_base<NP>(NP == 2)) != HALVES) return;
+            others = true;
         }
     }
 };
@@ -399,11 +401,13 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
             if (two) meet();
             after_last = last;
         }
+        if (w.others) head.flags |= kHalvesFollow;
         stage();
         meet();
         __syncthreads();                                              // no longer read; the sums of the last block are there
     }
     if constexpr (NP == 4) {
+        if (!w.others) return;
         auto none = [](const RowBlocks&, PlanHeaderPtr, bool) {};
         BlockWalk<NP, true> h, following;                             // the present block and the one after it
         int part = 0, k = 0;
@@ -453,8 +457,9 @@ template <typename F, int... k> __device__ __forceinline__ void every_slot(F& f,
 
 // Waves that walk the lists, in blocks of 4 NP rows; HALVES: in blocks whose sums do not fit the LDS, of which they take 8 rows, then the other 8.
 //
+// Returns whether there may be blocks of the other kind (looking for them takes 1000 cycles).
 template <int NP, bool HALVES>
-__device__ __forceinline__ void walk_blocks(uint8_t* smem, int blocks, int r, int d, int tid) {
+__device__ __forceinline__ bool walk_blocks(uint8_t* smem, int blocks, int r, int d, int tid) {
     constexpr int NW = HALVES ? 2 : NP;                               // lists that share a lane's rows
     constexpr int R = kRowsMM<NW>;
     constexpr int kGroup = NW == 4 ? 2 : 1;                           // log2 of the blocks that one list's values go to
@@ -465,7 +470,7 @@ __device__ __forceinline__ void walk_blocks(uint8_t* smem, int blocks, int r, in
     auto column = [&](int i) { return note->cols[wave][lane >> 2][i]; };   // of this 4-lane group's two lists in tile i
     BlockWalk<NP, HALVES> w;
     w.find(blockIdx.x, blocks, r, d, [](const RowBlocks&, PlanHeaderPtr, bool) {});
-    if (w.block >= blocks) return;
+    if (w.block >= blocks) return w.others;
     const bool two = !HALVES && two_chunks<NP>(w.H);                  // (see fetch_blocks)
     const uint32_t sums_at = (uint32_t)sums_base<NP>(two);
 
@@ -681,7 +686,7 @@ __device__ __forceinline__ void walk_blocks(uint8_t* smem, int blocks, int r, in
             store_sums<R>(reinterpret_cast<const float*>(smem + sums_at), stride, (float LSP_GLOBAL_AS*)uniform2(head0.x, head0.y), (const uint16_t LSP_GLOBAL_AS*)(plan + uniform(head1.x)),
                           (const uint16_t LSP_GLOBAL_AS*)(plan + uniform(head1.y)), (flags & kSharedColumns) != 0, nvcols, (int)uniform(head1.z), r, thread);
         }
-        if (!(flags & kMoreChunks)) break;
+        if (!(flags & kMoreChunks)) return (flags & kHalvesFollow) != 0;
         const bool second = note == first_note;
         note = first_note + second;
         if (two) piece = (part & (NW - 1)) * 8 + (second ? (uint32_t)kSecondBase<NP> : 0u);
@@ -696,8 +701,9 @@ __global__ __launch_bounds__(kThreadsMM) void k_compress_mm(const CompressGroup 
     zero_unit<NP>(smem + kSecondBase<NP>, tid);                       // (where there is no second chunk, sums of later on)
     if (__builtin_amdgcn_readfirstlane(tid) >= kWalkers) fetch_blocks<NP, WHOLE>(smem, blocks, r, d, tid - kWalkers);
     else {
-        walk_blocks<NP, false>(smem, blocks, r, d, tid);
-        if constexpr (NP == 4) walk_blocks<NP, true>(smem, blocks, r, d, tid);   // more sums than the LDS has room for: 8 rows, then 8 rows
+        const bool others = walk_blocks<NP, false>(smem, blocks, r, d, tid);
+        if constexpr (NP == 4)
+            if (others) walk_blocks<NP, true>(smem, blocks, r, d, tid);   // more sums than the LDS has room for: 8 rows, then 8 rows
     }
 }
 
