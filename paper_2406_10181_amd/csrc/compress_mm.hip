@@ -11,12 +11,12 @@
 // walkers have to know of it.  A block's 16 rows of a column lie side by side in LDS, 32 bytes: the values of a list are given to four blocks of the
 // instruction (cbsz, abid), each with four of the rows, so that 16 lanes gather from four units instead of 16, and meet on a bank less often (5.1 cycles a
 // read; from planes of 8 bytes a column 7.1, without conflicts 2.5).
-// 11008 x 4096, cycles of a chunk, some 11300: staging 1300, with the walkers idle; the walk 7700 to 9000 (the two walking waves of a SIMD do not keep step), of it
-// the LDS 5900, 1300 for two or three tiles' ends, some 40 instructions a step and wave; storing T 1250 a block.  No single thing bounds it: of 158 us for the
-// seven matrices of a 6.7B layer 24 go without G, 18 without the plan's loads, 15 without bank conflicts, 14 without the ends of tiles, 11 without products, 10 without
-// LDS reads; and under it the clock goes down from 2.4 to 1.95 GHz, so that whatever is left out helps the rest.  How far ahead the plan is asked for does not matter (4
-// to 10 steps).  (us with that kernel alone, before -> with 32-byte units, chunks that begin with their steps in registers, and notes: 166 -> 155; 4096 x 16384, r = 512, d = 8,
-// skewed columns 65.5 -> 64; 4096 x 4096, r = 2048 33.5 -> 29; 4096 x 11008 42.4 -> 39.)
+// What bounds it: with long lists (r = 512, d = 8, 11008 x 4096) no single thing: some 10000 cycles a chunk, of them 1100 of staging, with the walkers idle, 7700 to 9000 of walking (the two
+// walking waves of a SIMD do not keep step), of it the LDS 5900, 1300 for two or three tiles' ends, some 40 instructions a step and wave; storing T 1250 a block; the clock is down from
+// 2.4 to 1.95 GHz.  With short ones (4096 x 16384, r = 256, d = 2) the reads of G, at about 4.6 TB/s.
+// (us, with kernel B: planes of 8 bytes -> 32-byte units, chunks that begin with their steps in registers, and notes -> loads that stay in flight, other chunks first, two chunks in LDS,
+// steps ahead by the length of the lists: 4096 x 4096, r = 512, d = 8 27.4 -> 26.1 -> 25.6; 4096 x 16384 62.2 -> 58.1 -> 53.4; r = 256, d = 2 43.4 -> 46.5 -> 34.0, zipf 49.3 -> 54.2 -> 42.2;
+// 4096 x 4096, r = 2048 59.0 -> 49.0 -> 48.2.)
 // 512 threads and 8 rows, twice a CU, or 12 walking waves and narrower tiles were 2 to 8 % slower; LDS atomics for the sums twice as slow.
 #include <algorithm>
 
@@ -281,7 +281,7 @@ template <int NP, bool HALVES> struct BlockWalk {
 
 // Waves that fetch: chunks of G are on their way while the other waves walk the present one.
 // They are waves of their own because loads return in order: behind a load of G from HBM the walkers' loads of the plan would wait.
-// The first half of the rows of a chunk is asked for a chunk earlier than the second, so that loads are in flight at any time.
+// The first half of the rows of a chunk is asked for a chunk earlier than the second (where two chunks take turns, both), so that loads are in flight at any time.
 template <int NP, bool WHOLE>
 __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, int d, int tid) {
     constexpr int R = kRowsMM<NP>, NH = NP / 2;
@@ -451,15 +451,14 @@ __device__ __forceinline__ int tiles_of_wave(int V, int wave) {
     return count;
 }
 
-constexpr int kRing = 8;                                              // steps of the plan a wave holds in registers (even)
-static_assert(kRing % 2 == 0 && kRing <= kStepsAhead, "the gathers take turns; so many steps are readable behind a plan's last");
 template <typename F, int... k> __device__ __forceinline__ void every_slot(F& f, std::integer_sequence<int, k...>) { (f(std::integral_constant<int, k>{}), ...); }
 
 // Waves that walk the lists, in blocks of 4 NP rows; HALVES: in blocks whose sums do not fit the LDS, of which they take 8 rows, then the other 8.
 //
-// Returns whether there may be blocks of the other kind (looking for them takes 1000 cycles).
-template <int NP, bool HALVES>
+// RING: steps of the plan a wave holds in registers.  Returns whether there may be blocks of the other kind (looking for them takes 1000 cycles).
+template <int NP, int RING, bool HALVES>
 __device__ __forceinline__ bool walk_blocks(uint8_t* smem, int blocks, int r, int d, int tid) {
+    static_assert(RING % 2 == 0 && RING <= kStepsAhead, "the gathers take turns; so many steps are readable behind a plan's last");
     constexpr int NW = HALVES ? 2 : NP;                               // lists that share a lane's rows
     constexpr int R = kRowsMM<NW>;
     constexpr int kGroup = NW == 4 ? 2 : 1;                           // log2 of the blocks that one list's values go to
@@ -474,8 +473,8 @@ __device__ __forceinline__ bool walk_blocks(uint8_t* smem, int blocks, int r, in
     const bool two = !HALVES && two_chunks<NP>(w.H);                  // (see fetch_blocks)
     const uint32_t sums_at = (uint32_t)sums_base<NP>(two);
 
-    // A chunk's steps lie one behind the other.  ring: the next kRing, from slot 0 on; those of the next chunk take the places of the last ones.
-    u32x4 ring[kRing];
+    // A chunk's steps lie one behind the other.  ring: the next RING, from slot 0 on; those of the next chunk take the places of the last ones.
+    u32x4 ring[RING];
     const uint32_t lane16 = lane * 16;
     auto step_at = [&](uint64_t steps, int k) { return *(const u32x4 LSP_GLOBAL_AS*)(steps + (uint64_t)k * (kWave * 16) + lane16); };
     int stride, t = 0, steps;
@@ -595,7 +594,7 @@ __device__ __forceinline__ bool walk_blocks(uint8_t* smem, int blocks, int r, in
     // The gathers of a step are asked for before the products of the one before.  The barriers keep the compiler from waiting for each gather by itself and from
     // giving the refills registers of their own, which a loop would have to move.
     auto slots = [](auto&& f) {                                       // f of every slot of the ring, in turn
-        every_slot(f, std::make_integer_sequence<int, kRing>{});
+        every_slot(f, std::make_integer_sequence<int, RING>{});
     };
     // The steps of a chunk, of which the first is in slot 0: whole rounds, then the rest as nested conditions.  A way out of the middle of a loop would cost the compiler its
     // knowledge of what is in flight; for the same reason the last step also gathers for a step behind it, for nothing, and a tile begins behind the last one.
@@ -603,7 +602,7 @@ __device__ __forceinline__ bool walk_blocks(uint8_t* smem, int blocks, int r, in
         int left = length(0), remaining = steps;                      // steps of the tile, and of the chunk
         auto step = [&](auto slot, uint64_t refill) {
             constexpr int k = decltype(slot)::value;
-            gather(std::integral_constant<int, (k + 1) % kRing>{});
+            gather(std::integral_constant<int, (k + 1) % RING>{});
             __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_s_waitcnt(0xC07F | (2 * NW << 8));       // lgkmcnt(2 NW): what was asked for before is there
             __builtin_amdgcn_sched_barrier(0);
@@ -616,13 +615,13 @@ __device__ __forceinline__ bool walk_blocks(uint8_t* smem, int blocks, int r, in
         };
         gather(std::integral_constant<int, 0>{});
         begin();
-        for (; remaining > kRing; ahead += kRing * kWave * 16)
-            slots([&](auto slot) { step(slot, remaining-- > kRing ? ahead : next); });
+        for (; remaining > RING; ahead += RING * kWave * 16)
+            slots([&](auto slot) { step(slot, remaining-- > RING ? ahead : next); });
         auto rest = [&](auto&& self, auto slot) -> void {
             constexpr int k = decltype(slot)::value;
             if (k < remaining) {
                 step(slot, next);
-                if constexpr (k + 1 < kRing) self(self, std::integral_constant<int, k + 1>{});
+                if constexpr (k + 1 < RING) self(self, std::integral_constant<int, k + 1>{});
             }
         };
         rest(rest, std::integral_constant<int, 0>{});
@@ -652,7 +651,7 @@ __device__ __forceinline__ bool walk_blocks(uint8_t* smem, int blocks, int r, in
         steps = (int)uniform(seg0.y);
         len_lo = uniform2(seg0.z, seg0.w); len_hi = uniform2(seg1.x, seg1.y);
         next = uniform2(after.x, after.y);
-        ahead = uniform2(here.x, here.y) + kRing * (kWave * 16);
+        ahead = uniform2(here.x, here.y) + RING * (kWave * 16);
         nvcols = (int)uniform(head.x);
         flags = uniform(head.y);
         stride = sums_stride(nvcols);
@@ -664,7 +663,7 @@ __device__ __forceinline__ bool walk_blocks(uint8_t* smem, int blocks, int r, in
         wait_for_loads();
         t = 0;
         if (steps > 0) walk_chunk();
-        if (steps < kRing)
+        if (steps < RING)
             slots([&](auto slot) {
                 constexpr int k = decltype(slot)::value;
                 if (k >= steps) ring[k] = step_at(next, k);
@@ -693,7 +692,7 @@ __device__ __forceinline__ bool walk_blocks(uint8_t* smem, int blocks, int r, in
     }
 }
 
-template <int NP, bool WHOLE>
+template <int NP, int RING, bool WHOLE>
 __global__ __launch_bounds__(kThreadsMM) void k_compress_mm(const CompressGroup grp, int r, int d, int blocks) {
     extern __shared__ __align__(16) uint8_t smem[];
     const int tid = threadIdx.x;
@@ -701,13 +700,13 @@ __global__ __launch_bounds__(kThreadsMM) void k_compress_mm(const CompressGroup 
     zero_unit<NP>(smem + kSecondBase<NP>, tid);                       // (where there is no second chunk, sums of later on)
     if (__builtin_amdgcn_readfirstlane(tid) >= kWalkers) fetch_blocks<NP, WHOLE>(smem, blocks, r, d, tid - kWalkers);
     else {
-        const bool others = walk_blocks<NP, false>(smem, blocks, r, d, tid);
+        const bool others = walk_blocks<NP, RING, false>(smem, blocks, r, d, tid);
         if constexpr (NP == 4)
-            if (others) walk_blocks<NP, true>(smem, blocks, r, d, tid);   // more sums than the LDS has room for: 8 rows, then 8 rows
+            if (others) walk_blocks<NP, RING, true>(smem, blocks, r, d, tid);   // more sums than the LDS has room for: 8 rows, then 8 rows
     }
 }
 
-template <int NP> static hipError_t launch_mm_rows(CompressGroup& g, int32_t r, int32_t d, hipStream_t st) {
+template <int NP, int RING> static hipError_t launch_mm_rows(CompressGroup& g, int32_t r, int32_t d, hipStream_t st) {
     constexpr int R = kRowsMM<NP>;
     constexpr size_t lds = kLdsMM;
     bool whole = true;
@@ -721,24 +720,23 @@ template <int NP> static hipError_t launch_mm_rows(CompressGroup& g, int32_t r, 
     const dim3 grid((unsigned)std::min(blocks, kResidentMM));
     hipError_t e;
     if (whole) {
-        if ((e = allow_dynamic_lds<k_compress_mm<NP, true>, lds>()) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_compress_mm<NP, true>), grid, dim3(kThreadsMM), lds, st, g, (int)r, (int)d, blocks);
+        if ((e = allow_dynamic_lds<k_compress_mm<NP, RING, true>, lds>()) != hipSuccess) return e;
+        hipLaunchKernelGGL((k_compress_mm<NP, RING, true>), grid, dim3(kThreadsMM), lds, st, g, (int)r, (int)d, blocks);
     } else {
-        if ((e = allow_dynamic_lds<k_compress_mm<NP, false>, lds>()) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_compress_mm<NP, false>), grid, dim3(kThreadsMM), lds, st, g, (int)r, (int)d, blocks);
+        if ((e = allow_dynamic_lds<k_compress_mm<NP, RING, false>, lds>()) != hipSuccess) return e;
+        hipLaunchKernelGGL((k_compress_mm<NP, RING, false>), grid, dim3(kThreadsMM), lds, st, g, (int)r, (int)d, blocks);
     }
     return hipGetLastError();
 }
 
-// Blocks of 16 rows read the plan half as often as blocks of 8 and share each value between twice the rows (4096 x 4096, d = 8, with
-// kernel B: r = 512 28.2 us, with 8 rows 29.6; r = 1024 34.6 and 38.6; seven matrices of a 6.7B layer 216 and 265).  8 rows are better
-//   where there is at most one block of 8 for a CU, so that the blocks of 16 would leave CUs idle (2048 rows 18.4 us, with 16 22.8; 3001 rows 22.2
-//   and 20.9);
+// Blocks of 16 rows read the plan half as often as blocks of 8 and share each value between twice the rows (us with kernel B, 16 and 8 rows: 4096 x 4096, d = 8, r = 512 25.6 and 27.3,
+// r = 1024 35.2 and 36.1; 3001 x 3001, r = 512, d = 8 22.2 and 24.0; 9000 x 2048 36.4 and 38.5, zipf 54.5 and 58.0; 4096 x 1024, r = 64, d = 2 14.1 and 15.3).  8 rows are better
+//   where there is at most one block of 8 for a CU, so that the blocks of 16 would leave CUs idle (2048 x 4096, r = 512, d = 8 16.9 us, with 16 20.9; 1024 x 1024, r = 128, d = 4 10.1 and 12.0);
 //   where they take three rounds of one for every CU and the blocks of 16 two, the last of them little more than half full or less: 4097 to 6144 rows (us with 8
-//   and with 16 rows: 5120 x 5120, r = 512, d = 8 45.5 and 47.2, zipf 61.8 and 64.1; r = 1024, d = 16 75.0 and 79.6; 6144 x 4096, r = 256, d = 16 56.7 and 60.9, r = 1024,
-//   d = 4 41.3 and 45.0; in the mean of 36 such calls 3 % less, with zipf columns even: 4200 x 2048, r = 1024, d = 8 61.8 and 56.8); with five rounds and three
-//   they are not (9000 x 2048, r = 512, d = 8 41.4 and 40.5);
-//   and beyond r = 1024, where the sums of 16 rows do not fit the LDS (r = 1536 50.1 and 52.6, r = 2048 57.0 and 60.6).
+//   and with 16 rows: 5120 x 5120, r = 512, d = 8 40.2 and 41.3, zipf 55.1 and 55.6; r = 1024, d = 8 48.4 and 53.2; d = 16 66.8 and 71.1; 6144 x 4096, r = 512, d = 8 even, r = 1024,
+//   d = 4 37.3 and 40.1, r = 256, d = 4 29.1 and 28.4; 4200 x 2048, r = 1024, d = 8, zipf 53.9 and 51.6);
+//   and beyond r = 1024, where the sums of 16 rows do not fit the LDS (4096 x 4096, d = 8, r = 1536 43.5 and 46.0, r = 2048 49.2 and 51.5, d = 16 65.7 and 64.9; 5120 x 5120, r = 2048,
+//   d = 8 69.6 and 89.3).
 static bool narrow_blocks(const CompressGroup& g, int32_t r) {
     int64_t of8 = 0, of16 = 0;
     for (int p = 0; p < g.count; ++p) {
@@ -750,18 +748,19 @@ static bool narrow_blocks(const CompressGroup& g, int32_t r) {
 }
 
 // Every bf16 call with a kept plan comes here, whatever its rows: the sums of a row do not depend on the blocks it is in, so a matrix has the same
-// result alone and in any group, which a second kernel with sums in another order would end.  Where the last round is nearly empty, k_compress_gq with
-// its finer grain (8 rows, two workgroups a CU) is up to 16 % faster if the lists are long and even, and 4 to 30 % slower otherwise: 7 % slower in the mean of
-// 40 calls with random sizes, counts and columns whose last round is less than 80 % full (us with kernel B, here and there; single matrices, uniform and zipf columns):
-//   5120 x 5120  r = 512, d = 8 45.5 and 43.5, 61.8 and 70.9; r = 512, d = 4 37.5 and 36.9, 52.5 and 61.3; r = 1024, d = 8 57.7 and 57.1, 88.5 and 99.0
-//   5120 x 13824 r = 512, d = 8 90.1 and 79.2, 111 and 120; r = 1024, d = 8 108 and 104, 151 and 151; d = 16 147 and 143, 191 and 199
-//   6144 x 4096  r = 256, d = 4 28.6 and 34.2, 38.5 and 48.4; d = 16 56.7 and 52.5, 76.7 and 68.6; r = 512, d = 8 40.3 and 39.5, 56.1 and 65.4
-//   9000 x 2048  r = 512, d = 8 40.5 and 39.9, 60.6 and 73.2; seven matrices of 5120 and 13824 rows and columns 292 and 319
-// Beyond r = 1024, where the lists are a few steps long, it is on a par with k_compress_gq, and behind it for short lists on 4096 and 8192 rows: r = 2048,
-//   4096 x 4096  d = 4 53.3 and 49.9, d = 8 58.8 and 55.4, d = 16 73.2 and 71.2; 5120 x 5120 77.0 and 80.1, 87.5 and 88.1, 109.4 and 113.3
-//   4096 x 16384 110 and 103, 120 and 114, 153 and 156; r = 1536, d = 8 4096 x 4096 47.9 and 50.9, 8192 x 8192 128 and 133
+// result alone and in any group, which a second kernel with sums in another order would end.  k_compress_gq is behind nearly everywhere (us with kernel B, here and there):
+//   5120 x 5120  r = 512, d = 8 40.3 and 43.6, zipf 55.1 and 72.6; r = 512, d = 4 33.1 and 36.1; r = 1024, d = 8 48.4 and 57.9; r = 2048, d = 8 70.0 and 88.1
+//   5120 x 13824 r = 512, d = 8 78.2 and 81.2; r = 1024, d = 16 131.9 and 144.4      6144 x 4096 r = 256, d = 4 29.0 and 35.4, d = 16 53.5 and 52.3, zipf 67.2 and 71.9
+//   4096 x 4096  r = 2048, d = 4 41.6 and 50.9, d = 8 49.4 and 55.9, d = 16 66.0 and 72.1      9000 x 2048 r = 512, d = 8 37.1 and 40.6
+// Steps of the plan that a wave holds in registers: eight hide the plan's latency behind the loads of G, but a chunk loads as many of the next one's, whether it has them or not (some
+// 2 d steps a wave and chunk).  us with 8, 6 and 4: 4096 x 16384, r = 512, d = 2 40.8, 38.8 and 37.5, d = 4 41.4, 42.3 and 44.1, d = 8 53.2, 53.7 and 55.9; 4096 x 1024, r = 64, d = 2
+// 14.6, 14.4 and 14.0.  Blocks of 8 rows: 2048 x 8192, r = 512, d = 4 19.8, 19.7 and 20.2; 5120 x 5120 34.2, 33.5 and 33.6, d = 8 40.6, 40.6 and 42.0; 2048 x 2048, r = 512, d = 8 13.9,
+// 13.8 and 13.7; 1024 x 4096, r = 128, d = 4 13.7, 13.9 and 13.4.
 hipError_t launch_mm_bf16(CompressGroup& g, int32_t r, int32_t d, hipStream_t st) {
-    return narrow_blocks(g, r) ? launch_mm_rows<2>(g, r, d, st) : launch_mm_rows<4>(g, r, d, st);
+    bool few_chunks = true;
+    for (int p = 0; p < g.count; ++p) few_chunks = few_chunks && g.n[p] <= 2 * kChunk;
+    if (narrow_blocks(g, r)) return d <= 2 || few_chunks ? launch_mm_rows<2, 4>(g, r, d, st) : launch_mm_rows<2, 6>(g, r, d, st);
+    return d <= 2 ? launch_mm_rows<4, 4>(g, r, d, st) : launch_mm_rows<4, 8>(g, r, d, st);
 }
 
 }  // namespace lsp

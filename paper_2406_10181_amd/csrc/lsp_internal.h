@@ -29,7 +29,7 @@ constexpr int kTileCols   = 2 * kSetCols;
 constexpr int kStepEntries = 4;    // entries of every list a step takes: the K of a block
 constexpr int kWavesMM    = 8;     // waves of that kernel that walk the lists
 constexpr int kWaveTiles  = kMaxSlots * kThreadsGQ / kTileCols / kWavesMM;   // most tiles of a wave in one chunk
-constexpr int kStepsAhead = 10;     // steps a wave holds in registers (8: 1.5 % slower on a 6.7B layer, 12: spills); so many readable ones follow the last
+constexpr int kStepsAhead = 10;     // so many readable steps follow the last one of a plan; a wave may ask for as many ahead
 constexpr uint32_t kNoColumn = 0xFFFFu;      // virtual column slot without a column
 constexpr uint32_t kSharedColumn = 0x8000u;  // flag: the column is owned by several lanes
 
@@ -45,7 +45,7 @@ __host__ __device__ static inline uint32_t chunk_col_offset(uint32_t j) {
     return (((j & 7u) * (kChunk / 8)) + (j >> 3)) * 16u;
 }
 
-// The same for the bf16 kernel, whose chunks lie in planes of 4 rows x 16 bits: a column is an 8-byte unit of each plane.
+// The same for the bf16 kernel, for units of 8 bytes: it has a column's 8 or 16 rows side by side, 16 or 32 bytes, and multiplies the offset by 2 or 4 as it reads it.
 __host__ __device__ static inline uint32_t chunk_unit_offset(uint32_t j) { return chunk_col_offset(j) / 2; }
 
 // ------------------------------------------------------------------------------------------

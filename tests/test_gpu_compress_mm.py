@@ -51,7 +51,7 @@ SHAPES = [
     (6145, 67, 33, "uniform"), (6544, 67, 33, "uniform"),         # two rounds of 16-row blocks, a little over half full
     (6545, 67, 33, "uniform"), (8192, 264, 48, "zipf"),           # two 16-row blocks a workgroup, not for all and for all; n % 8 != 0
     (4096, 300, 1024, "uniform"), (4096, 2100, 1024, "zipf"),     # the most columns 16-row blocks are used for; some of them shared
-    (2061, 10245, 1024, "hot"),                                   # more than 1535 lists: the sums of 16 rows do not fit the LDS, blocks go in halves
+    (2061, 10245, 1024, "hot"),                                   # more than 1376 lists: the sums of 16 rows do not fit the LDS, blocks go in halves
 ]
 
 
@@ -157,6 +157,23 @@ def test_bf16_compress_in_a_group_is_that_of_the_single_calls(shapes, r, d):
     singles = [dp.compress_planned() for dp in dps]
     for single, grouped in zip(singles, _group(dps, r, d)):
         assert np.isfinite(single).all() and np.array_equal(single, grouped), np.abs(single - grouped).max()
+
+
+# More than two chunks: blocks begin with different ones.  Two blocks in halves for a workgroup; two chunks in LDS at a time, with one block a workgroup, two, and blocks of 8 rows.
+@pytest.mark.parametrize("m,n,r,dist", [(6160, 6150, 1024, "hot"), (6545, 6151, 33, "uniform"), (2500, 8195, 33, "uniform"), (300, 8195, 250, "zipf"), (520, 6152, 512, "uniform")])
+def test_bf16_compress_over_many_chunks(m, n, r, dist):
+    test_bf16_compress_at_the_edges(m, n, r, dist)
+
+
+# The same rows in blocks of 8 and of 16, and beside matrices whose sums leave no room for two chunks.
+@pytest.mark.parametrize("shapes,r,d", [
+    ([(5120, 6152, "uniform")] * 2, 48, 1),
+    ([(2500, 8200, "uniform"), (2600, 6150, "zipf")], 96, 4),
+    ([(40, 6150, "uniform"), (2048, 8192, "uniform"), (4096, 6152, "zipf")], 1000, 2),
+    ([(300, 6152, "uniform"), (2500, 10240, "hot"), (4096, 264, "uniform")], 320, 1),
+])
+def test_bf16_compress_over_many_chunks_in_a_group(shapes, r, d):
+    test_bf16_compress_in_a_group_is_that_of_the_single_calls(shapes, r, d)
 
 
 @pytest.mark.parametrize("foreign", [0, 1, 2])
