@@ -249,10 +249,12 @@ template <int NP> __device__ __forceinline__ bool two_chunks(PlanHeaderPtr H) {
     return most <= (uint32_t)(kMaxSlots * kThreadsGQ) && sums_fit((int)most, kRowsMM<NP>, sums_base<NP>(true));
 }
 
-// Blocks begin with different chunks, and go around: rows a power of two apart would have all workgroups on the same few memory channels at a time (4096 x 16384, r = 256, d = 2 46.1 -> 39.5 us, r = 512, d = 8 58.4 -> 55.2; 8192 x 8192, r = 512, d = 8 62.6 -> 60.5; with two chunks it does nothing).  Which one is a matter of the
-// row alone, so that the sums of a row do not depend on the blocks it is in.  (Golden-ratio steps, so that neighbouring blocks of 16 rows spread evenly.)
-__device__ __forceinline__ int chunk_at(int k, int row0, int nchunks) {
-    const int at = k + (nchunks > 2 ? (int)__umulhi((uint32_t)(row0 >> 4) * 0x9E3779B9u, (uint32_t)nchunks) : 0);
+// Blocks begin with different chunks, and go around: rows a power of two apart would have all workgroups on the same few memory channels at a time (4096 x 16384, r = 256, d = 2
+// 46.1 -> 39.5 us, r = 512, d = 8 58.4 -> 55.2; 8192 x 8192, r = 512, d = 8 62.6 -> 60.5; 3001 x 11008, r = 512, d = 4 32.9 -> 32.1).  With three chunks it does nothing, and where rows
+// are few, workgroups that read the same part of the plan at a time are worth more (1106 x 6144, r = 512, d = 8 18.2 us, 18.7 with it; 2048 x 16384 36.9 and 35.2).
+// Which one is a matter of the row and its matrix alone, so that the sums of a row do not depend on the blocks it is in.  (Golden-ratio steps: neighbouring blocks of 16 rows spread evenly.)
+__device__ __forceinline__ int chunk_at(int k, int row0, int m, int nchunks) {
+    const int at = k + (nchunks > 3 && m > 1536 ? (int)__umulhi((uint32_t)(row0 >> 4) * 0x9E3779B9u, (uint32_t)nchunks) : 0);
     return at < nchunks ? at : at - nchunks;
 }
 
@@ -293,7 +295,7 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
     };
     BlockWalk<NP, false> w;
     int c = 0;                                                        // the how manieth chunk of the block
-    auto chunk = [&]() { return chunk_at(c, w.pr.block * R, w.nchunks); };
+    auto chunk = [&]() { return chunk_at(c, w.pr.block * R, w.pr.m, w.nchunks); };
     auto advance = [&]() {
         if (++c >= w.nchunks) { c = 0; w.find(w.block + gridDim.x, blocks, r, d, clear_s); }
     };
@@ -309,7 +311,7 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
     static_assert(sizeof(ChunkNote::cols) == kFetchers * 16 && sizeof(ChunkNote::seg) == 16 * 16, "16 bytes a thread");
     auto segs = [](const RowBlocks& pr, PlanHeaderPtr H, int chunk) { return pr.plan + H->off_m_seg + (size_t)chunk * (kWavesMM * sizeof(TileSeg)); };
     auto look_up = [&](const RowBlocks& pr, PlanHeaderPtr H, int nchunks, int k, int rows_of, int row0) {
-        const int chunk = chunk_at(k, row0, nchunks);
+        const int chunk = chunk_at(k, row0, pr.m, nchunks);
         cols = reinterpret_cast<const u32x4*>(pr.plan + H->off_m_cols)[(size_t)chunk * kFetchers + tid];
         const uint8_t* here = segs(pr, H, chunk);
         if (tid < 16) seg = reinterpret_cast<const u32x4*>(here)[tid];
@@ -342,8 +344,8 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
     };
 
     const RowBlocks start = problem_of(blockIdx.x);                   // nearly always the first: its rows are asked for before its plan is looked at
-    lo.fetch(static_cast<const uint16_t*>(start.G), (int64_t)start.block * R, start.m, start.n, chunk_at(0, start.block * R, (int)(((uint32_t)start.n + kChunk - 1) / kChunk)), tid);
-    hi.fetch(static_cast<const uint16_t*>(start.G), (int64_t)start.block * R + R / 2, start.m, start.n, chunk_at(0, start.block * R, (int)(((uint32_t)start.n + kChunk - 1) / kChunk)), tid);
+    lo.fetch(static_cast<const uint16_t*>(start.G), (int64_t)start.block * R, start.m, start.n, chunk_at(0, start.block * R, start.m, (int)(((uint32_t)start.n + kChunk - 1) / kChunk)), tid);
+    hi.fetch(static_cast<const uint16_t*>(start.G), (int64_t)start.block * R + R / 2, start.m, start.n, chunk_at(0, start.block * R, start.m, (int)(((uint32_t)start.n + kChunk - 1) / kChunk)), tid);
     w.find(blockIdx.x, blocks, r, d, clear_s);
     auto fetch_lo = [&]() { lo.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R, w.pr.m, w.pr.n, chunk(), tid); };
     auto fetch_hi = [&]() { hi.fetch(static_cast<const uint16_t*>(w.pr.G), (int64_t)w.pr.block * R + R / 2, w.pr.m, w.pr.n, chunk(), tid); };
@@ -417,16 +419,16 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
         turn = 0;
         auto tell = [&]() {
             look_up(h.pr, h.H, h.nchunks, k, R / 2, h.pr.block * R + part * (R / 2));
-            if (k + 1 < h.nchunks) look_after(h.pr, h.H, chunk_at(k + 1, h.pr.block * R, h.nchunks));
-            else if (part == 0) look_after(h.pr, h.H, chunk_at(0, h.pr.block * R, h.nchunks));
-            else if (following.block < blocks) look_after(following.pr, following.H, chunk_at(0, following.pr.block * R, following.nchunks));
+            if (k + 1 < h.nchunks) look_after(h.pr, h.H, chunk_at(k + 1, h.pr.block * R, h.pr.m, h.nchunks));
+            else if (part == 0) look_after(h.pr, h.H, chunk_at(0, h.pr.block * R, h.pr.m, h.nchunks));
+            else if (following.block < blocks) look_after(following.pr, following.H, chunk_at(0, following.pr.block * R, following.pr.m, following.nchunks));
             put_note();
         };
         __syncthreads();                                              // nobody reads the last note of the other blocks any more
         tell();
         __syncthreads();                                              // the first note is there
         while (h.block < blocks) {
-            lo.fetch(static_cast<const uint16_t*>(h.pr.G), (int64_t)h.pr.block * R + part * (R / 2), h.pr.m, h.pr.n, chunk_at(k, h.pr.block * R, h.nchunks), tid);
+            lo.fetch(static_cast<const uint16_t*>(h.pr.G), (int64_t)h.pr.block * R + part * (R / 2), h.pr.m, h.pr.n, chunk_at(k, h.pr.block * R, h.pr.m, h.nchunks), tid);
             lo.arrange(ulo);
             put_units<2, 2>(smem, ulo, 0, tid);
             zero_unit<2>(smem, tid);                                  // (inside the larger units)
@@ -636,7 +638,7 @@ __device__ __forceinline__ bool walk_blocks(uint8_t* smem, int blocks, int r, in
         __builtin_amdgcn_s_waitcnt(0x0F70);                           // vmcnt(0)
         __builtin_amdgcn_sched_barrier(0);
     };
-    ring_of((uint64_t)(uintptr_t)w.pr.plan + w.H->off_m_steps + (uint64_t)as_const<TileSeg>(w.pr.plan + w.H->off_m_seg)[chunk_at(0, w.pr.block * kRowsMM<NP>, w.nchunks) * kWavesMM + wave].first_step * (kWave * 16));
+    ring_of((uint64_t)(uintptr_t)w.pr.plan + w.H->off_m_steps + (uint64_t)as_const<TileSeg>(w.pr.plan + w.H->off_m_seg)[chunk_at(0, w.pr.block * kRowsMM<NP>, w.pr.m, w.nchunks) * kWavesMM + wave].first_step * (kWave * 16));
     const auto uniform = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
     const auto uniform2 = [&](uint32_t lo, uint32_t hi) { return (uint64_t)uniform(hi) << 32 | uniform(lo); };
     const auto piece16 = [&](const void* p) { return *static_cast<const u32x4*>(p); };
