@@ -801,9 +801,10 @@ static bool fast_shape(int32_t n, int32_t d) { return (n % 2) == 0 && (d == 2 ||
 // Elsewhere k_decompress is ahead: fp32 on larger grids (8192 x 4096, r = 512, d = 8 58.4 and 66.5; with 16 rows a thread has half as many registers in flight), and d <= 8 in
 // blocks of 8 rows, whose pieces are 8 bytes (2048 x 2048, r = 512, d = 8, bf16 8.8 and 9.5; 4096 x 4096, r = 2048, d = 8 44.5 and 46.8).
 constexpr unsigned kResidentDeep = 256;                              // workgroups of the deep form, one a CU
+static bool wide_shape(int64_t n, int32_t r) { return r >= 4 && r % 4 == 0 && n % 8 == 0 && n <= 1 << 24; }   // (32-bit offsets inside a plane of rows)
 static bool wide_group(const ApplyGroup& g, int32_t r) {
-    bool wide = r >= 4 && r % 4 == 0;
-    for (int p = 0; p < g.count; ++p) wide = wide && g.n[p] % 8 == 0 && g.n[p] <= 1 << 24;   // (32-bit offsets inside a plane of rows)
+    bool wide = true;
+    for (int p = 0; p < g.count; ++p) wide = wide && wide_shape(g.n[p], r);
     return wide;
 }
 // Small work where k_decompress is ahead all the same (blocks of 16 rows of 512 threads, d <= 8; grid: workgroups, n: the widest matrix).  In a call of one pass nothing covers
@@ -902,33 +903,42 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
     return hipErrorInvalidValue;
 }
 
-// Workgroups of 8 rows instead of 16, given the number of blocks of 16 rows (n: the widest matrix).  With 8 rows there are twice as
-// many workgroups, but each reads all of Q.  (us, 8 rows | 16 rows, apply and bias pass, W and G from HBM.)
+// Workgroups of 8 rows instead of 16, given the number of blocks of 16 rows (n: the widest matrix; wide: k_decompress_wide's shapes).  With 8 rows there are
+// twice as many workgroups, but each reads all of Q, and d <= 8 goes to k_decompress.  (us, 8 rows | 16 rows, apply and bias pass, W and G from HBM.)
 //   * At most 128 blocks, half of the CUs idle otherwise: 8 rows.
-//       1000 x 2048, r = 128, d = 2, bf16     6.8 |  7.5     9.1 |  9.6        2048 x 2048, r = 512, d = 8, bf16    10.9 | 14.0    13.1 | 16.3
-//       2048 x 16384, r = 256, d = 4, bf16   30.9 | 45.8    27.8 | 40.2        2048 x 8192, r = 256, d = 16, fp32   55.7 | 69.6    53.9 | 70.9
-//       2048 x 2047, r = 250, d = 5, bf16    10.1 | 12.6    11.4 | 14.8        2040 x 8191, r = 900, d = 7, bf16    35.4 | 50.0    32.8 | 44.9
-//     (Rows of 16 KB are the exception: 2048 x 4096, r = 512, d = 8, fp32     28.6 | 26.0    22.5 | 23.0.)
+//       1000 x 2048, r = 128, d = 2, bf16     6.2 |  8.0     8.3 |  9.4        2048 x 2048, r = 512, d = 8, bf16    11.5 | 13.6    13.7 | 15.7
+//       2048 x 16384, r = 256, d = 4, bf16   31.3 | 46.3    27.3 | 32.9        2048 x 8192, r = 256, d = 16, fp32   42.9 | 60.1    36.9 | 45.4
+//       2048 x 2048, r = 256, d = 16, bf16   13.4 | 19.5    15.8 | 20.0        1000 x 4096, r = 512, d = 16, bf16   21.3 | 32.8    22.8 | 30.7
+//       2048 x 2047, r = 250, d = 5, bf16    10.5 | 13.3    12.1 | 15.3        2040 x 8191, r = 900, d = 7, bf16    38.3 | 53.5    36.3 | 49.0
+//     (Rows of 16 KB are the exception: 2048 x 4096, r = 512, d = 8, fp32     29.5 | 26.6    23.3 | 21.5.)
 //   * 129 to 255 blocks: some CUs have two workgroups of 8 rows and others one.  16 rows, the more so the larger d is:
-//       2064 x 4096, r = 512, d = 8, bf16    22.5 | 20.4    22.6 | 21.7        3072 x 16384, r = 512, d = 8, bf16   73.5 | 67.4    60.6 | 57.6
-//       4080 x 4096, r = 512, d = 8, fp32    45.8 | 33.0    33.4 | 24.1        4080 x 8192, r = 256, d = 16, bf16   90.8 | 67.5    94.9 | 69.5
-//       4073 x 8191, r = 250, d = 3, bf16        (general kernel)  32.0 | 29.3     d = 7    49.1 | 39.8
-//     but 8 rows where the passes are short, or the bias pass has few gathers and no stores to cover its loads with:
-//       4080 x 2048, r = 128, d = 2, fp32    16.1 | 23.8    12.8 | 17.7        4080 x 3072, r = 256, d = 4, fp32    23.0 | 27.0    16.0 | 17.5
-//       2064 x 8192, r = 128, d = 2, bf16       (bias)      15.7 | 19.0        3072 x 16384, r = 256, d = 4, bf16   (bias)         38.1 | 40.7
-static bool eight_rows(int64_t blocks, int64_t n, int32_t r, int32_t d, int elem_size, bool fast, bool norms) {
+//       2064 x 4096, r = 512, d = 8, bf16    23.3 | 19.9    23.8 | 21.0        3072 x 16384, r = 512, d = 8, bf16   76.0 | 63.1    62.5 | 50.6
+//       4080 x 4096, r = 512, d = 8, fp32    45.9 | 31.4    34.7 | 24.5        4080 x 8192, r = 256, d = 16, bf16   90.7 | 58.3    95.8 | 49.6
+//       3072 x 2048, r = 512, d = 8, fp32    20.7 | 18.1    20.5 | 16.3        3072 x 2048, r = 256, d = 4, fp32    16.1 | 15.1    14.5 | 12.7
+//       4080 x 4096, r = 256, d = 4, bf16       (bias)      18.3 | 16.2        4073 x 8191, r = 250, d = 7, bf16    67.1 | 52.9    50.4 | 41.0
+//     but 8 rows in fp32 below 4096 columns where the lists are short and the tile small (r <= 64 d), in the apply step up to 1024 columns whatever d is:
+//       4080 x 1024, r = 256, d = 4, fp32     9.8 | 11.0    11.7 | 11.0        3072 x 1024, r = 512, d = 2, fp32    10.7 |  9.4    13.1 | 10.7
+//       2064 x 3072, r = 128, d = 2, fp32    17.0 | 17.3    12.8 | 14.8        4080 x 2048, r = 128, d = 2, fp32    16.2 | 15.9    12.7 | 12.5
+//     and in the bias pass of long rows in 16 bits at d = 2 and r <= 256: 2064 x 8192, r = 128 16.4 | 17.9; 4080 x 16384, r = 256 30.7 | 31.1; r = 512 33.8 | 31.3.  Where 16 rows
+//     would be k_decompress as well they are even or behind at d <= 4: 2064 x 3074, r = 256, d = 4, fp32 20.7 | 22.1, bias 16.6 | 17.6 (3072 rows 19.2 | 18.4); 2064 x 8194, bf16 (bias) 24.2 | 25.7.
+static bool eight_rows(int64_t blocks, int64_t n, int32_t r, int32_t d, int elem_size, bool fast, bool wide, bool norms) {
     if (r > 1024 || blocks <= 128) return true;                     // (r > 1024: 16 rows of U would take the whole LDS)
-    if (blocks > 255 || r > 512 || !fast) return false;
-    return elem_size == 4 ? n < 4096 && d <= 8 : norms && n >= 4096 && d <= 4;
+    if (blocks > 255 || r > 512 || !fast || d > 8) return false;
+    if (elem_size == 2) return norms && (wide ? n >= 8192 && d <= 2 && r <= 256 : n >= 4096 && d <= 4);
+    if (n >= 4096) return false;
+    return wide ? r <= 64 * d && (d <= 2 || (!norms && n <= 1024)) : d <= 4;
 }
 
 // Rows per workgroup: 16 (four planes of U in LDS) or 8 (above), and 512 threads, except
 //   * 1024 or more blocks, 16-bit storage, 256 < r <= 512: 32 rows, so that the rows of Q are streamed from L2 half as
-//     often (the seven matrices of a 6.7B-style layer, one call: 220 us, with 16 rows of 256 threads 235, of 512 threads 226;
-//     16384 x 4096, r = 512, d = 8: 69, 74, 76); fp32 patches of 32 rows would not fit the registers;
+//     often (the seven matrices of a 6.7B-style layer, d = 8, one call: 202 us, with 16 rows 227; d = 16 325 and 335; 16384 x 4096, r = 512, d = 8 67.2 and 73.3; where
+//     k_decompress_wide does not serve, d = 4, 16384 x 4098 96.1 and 100.3); fp32 patches of 32 rows would not fit the registers.
+//     With few entries of Q in k_decompress_wide 16 rows are the faster ones, which ask ahead and end more evenly: d = 2, from 2048 columns on: the layer 161.5 and 148.7 us,
+//     16384 x 4096 53.9 and 51.3, 20000 x 8192 156 and 118 (1024 columns 17.4 and 17.8); d = 4, 2048 to 8192 columns: 16384 x 4096 57.6 and 56.1, 20000 x 8192 162 and 130, but
+//     four matrices 4096 x 11008 153.7 and 157.4;
 //   * 512 or more blocks and r <= 512: 256 threads with at most eight passes each; four such workgroups share a CU and
-//     cover each other's set-up.  It is even with 512 threads in 16 bits at d = 8 (11008 x 4096, r = 512: 55.6 | 56.0; 8192 x 4096:
-//     40.3 | 39.6), ahead in fp32 (81.0 | 83.4; 16384 x 4096: 112 | 116) and behind at d = 4 (16384 x 4096, r = 256: 59.1 | 55.8).
+//     cover each other's set-up.  It is even with 512 threads in 16 bits (11008 x 4096, r = 512, d = 8 55.9 | 54.7; 8192 x 4096
+//     40.5 | 40.8; 16384 x 4096, r = 256, d = 4 53.8 | 54.3; 8192 x 2048, r = 512, d = 4 20.8 | 19.9) and ahead in fp32 (82.6 | 84.7; 16384 x 4096: 114 | 117.5).
 template <typename D>
 static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_t st) {
     constexpr int kAll = 1 << 30;                                   // no row block is shared
@@ -940,11 +950,13 @@ static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_
         fast = fast && fast_shape(g.n[p], d);
     }
     if (r > 1024) return launch_d<D, 2, 32768, 512>(g, r, d, kAll, st);
-    if (eight_rows(blocks, widest, r, d, D::size, fast, false))
+    const bool wide = wide_group(g, r);
+    if (eight_rows(blocks, widest, r, d, D::size, fast, wide, false))
         return r <= 256 ? launch_d<D, 2, 4096, 512>(g, r, d, kAll, st) : r <= 512 ? launch_d<D, 2, 8192, 512>(g, r, d, kAll, st)
                                                                                  : launch_d<D, 2, 16384, 512>(g, r, d, kAll, st);
     if constexpr (D::size == 2)
-        if (fast && (d <= 8 || wide_group(g, r)) && blocks >= 1024 && 256 < r && r <= 512) return launch_d<D, 8, 8192, 512>(g, r, d, kAll, st);
+        if (fast && (d <= 8 || wide) && blocks >= 1024 && 256 < r && r <= 512 && !(wide && d <= 4 && widest >= 2048 && (d <= 2 || widest <= 8192)))
+            return launch_d<D, 8, 8192, 512>(g, r, d, kAll, st);
     if (fast && d <= 8 && blocks >= 512 && r <= 512)
         return r <= 256 ? launch_d<D, 4, 4096, 256>(g, r, d, 8, st) : launch_d<D, 4, 8192, 256>(g, r, d, 8, st);
     return r <= 256 ? launch_d<D, 4, 4096, 512>(g, r, d, kAll, st) : r <= 512 ? launch_d<D, 4, 8192, 512>(g, r, d, kAll, st)
@@ -953,7 +965,7 @@ static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_
 
 // Estimation bias: one problem, one pair of sums per workgroup.
 static bool bias_eight_rows(int64_t m, int64_t n, int32_t r, int32_t d, int elem_size) {
-    return eight_rows((m + 15) / 16, n, r, d, elem_size, fast_shape((int32_t)n, d), true);
+    return eight_rows((m + 15) / 16, n, r, d, elem_size, fast_shape((int32_t)n, d), wide_shape(n, r), true);
 }
 int64_t bias_blocks(int64_t m, int64_t n, int32_t r, int32_t d) {
     return bias_eight_rows(m, n, r, d, 2) || bias_eight_rows(m, n, r, d, 4) ? (m + 7) / 8 : (m + 15) / 16;

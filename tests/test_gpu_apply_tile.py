@@ -77,3 +77,15 @@ def test_apply_and_bias_over_several_passes(m, n, r, d, dtype):
     from test_gpu_parity import _bias_check
     test_apply_in_whole_pieces(m, n, r, d, dtype)
     _bias_check(syn.make_problem("bias passes", m, n, r, d, dtype, seed=9800 + m + n + r + d, g_std=1.0))
+
+
+# Both sides of the rules for the rows of a workgroup where k_decompress_wide serves: 129 to 255 blocks of 16 rows, and 1024 and more.
+@pytest.mark.parametrize("m,n,r,d,dtype", [
+    (2069, 1024, 128, 2, "f32"), (2069, 1032, 260, 4, "f32"), (2069, 1032, 128, 2, "f32"), (2069, 1024, 132, 2, "f32"),
+    (2069, 8192, 256, 2, "bf16"), (2069, 8192, 260, 2, "f16"), (2069, 8184, 256, 2, "bf16"), (2069, 8192, 256, 4, "bf16"),
+    (16390, 2040, 260, 2, "bf16"), (16390, 2048, 260, 2, "f16"), (16390, 2048, 260, 4, "bf16"), (16390, 2048, 260, 8, "f16"),
+])
+def test_apply_and_bias_on_both_sides_of_the_rules_for_whole_pieces(m, n, r, d, dtype):
+    from test_gpu_parity import _bias_check
+    test_apply_in_whole_pieces(m, n, r, d, dtype)
+    _bias_check(syn.make_problem("bias rules", m, n, r, d, dtype, seed=9900 + m + n + r + d, g_std=1.0))
