@@ -756,12 +756,10 @@ static bool narrow_blocks(const CompressGroup& g, int32_t r) {
 //   4096 x 4096  r = 2048, d = 4 41.6 and 50.9, d = 8 49.4 and 55.9, d = 16 66.0 and 72.1      9000 x 2048 r = 512, d = 8 37.1 and 40.6
 // Steps of the plan that a wave holds in registers: eight hide the plan's latency behind the loads of G, but a chunk loads as many of the next one's, whether it has them or not (some
 // 2 d steps a wave and chunk).  us with 8, 6 and 4: 4096 x 16384, r = 512, d = 2 40.8, 38.8 and 37.5, d = 4 41.4, 42.3 and 44.1, d = 8 53.2, 53.7 and 55.9; 4096 x 1024, r = 64, d = 2
-// 14.6, 14.4 and 14.0.  Blocks of 8 rows: 2048 x 8192, r = 512, d = 4 19.8, 19.7 and 20.2; 5120 x 5120 34.2, 33.5 and 33.6, d = 8 40.6, 40.6 and 42.0; 2048 x 2048, r = 512, d = 8 13.9,
-// 13.8 and 13.7; 1024 x 4096, r = 128, d = 4 13.7, 13.9 and 13.4.
+// 14.6, 14.4 and 14.0.  Blocks of 8 rows: 2048 x 8192, r = 512, d = 4 19.8, 19.7 and 20.2; 5120 x 5120 34.2, 33.5 and 33.6, d = 8 40.6, 40.6 and 42.0; with 6 and 4, two chunks and fewer:
+// 5120 x 4096, r = 512, d = 8 33.3 and 34.4; 4096 x 4096, r = 2048, d = 8 49.0 and 49.6, d = 16 62.6 and 64.8; 2048 x 4096, r = 128, d = 4 15.6 and 15.9; 264 x 657, r = 21, d = 3 10.9 and 10.8.
 hipError_t launch_mm_bf16(CompressGroup& g, int32_t r, int32_t d, hipStream_t st) {
-    bool few_chunks = true;
-    for (int p = 0; p < g.count; ++p) few_chunks = few_chunks && g.n[p] <= 2 * kChunk;
-    if (narrow_blocks(g, r)) return d <= 2 || few_chunks ? launch_mm_rows<2, 4>(g, r, d, st) : launch_mm_rows<2, 6>(g, r, d, st);
+    if (narrow_blocks(g, r)) return d <= 2 ? launch_mm_rows<2, 4>(g, r, d, st) : launch_mm_rows<2, 6>(g, r, d, st);
     return d <= 2 ? launch_mm_rows<4, 4>(g, r, d, st) : launch_mm_rows<4, 8>(g, r, d, st);
 }
 
