@@ -372,7 +372,7 @@ def main():
                      "algorithmic_bytes_per_launch_avg": int(cbytes / len(layers)),
                      "per_matrix_calls": {"achieved": round(comp_gbs, 1), "frac": round(comp_gbs / HBM_PEAK_GBS, 4),
                                           "avg_launch_us": round(ms_comp * 1e3 / nlaunch, 2), "traffic": traffic_c}},
-        "roofline_decompress": {"kernel": "k_decompress<bf16,d=8,r<=512> (one lsp_decompress_apply_grouped call, 7 matrices)",
+        "roofline_decompress": {"kernel": "k_decompress_wide<bf16,d=8>, 32 rows a workgroup (one lsp_decompress_apply_grouped call, 7 matrices)",
                                 "bound": "hbm", "achieved": round(dbytes / (ms_gdeco1 * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBS,
                                 "unit": "GB/s", "frac": round(dbytes / (ms_gdeco1 * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                                 "traffic": traffic_gd, "traffic_source": "profiles/traffic_decompress_cfg4.json (rocprofv3 --pmc runs, not live)",
@@ -381,7 +381,7 @@ def main():
                                 "per_matrix_calls": {"achieved": round(deco_gbs, 1), "frac": round(deco_gbs / HBM_PEAK_GBS, 4),
                                                      "avg_launch_us": round(ms_deco * 1e3 / nlaunch, 2), "traffic": traffic_d}},
         # next row beyond the step (not part of `value`): the bias pass of Def. 2, one call per matrix
-        "estimation_bias": {"kernel": "k_decompress<..., NORMS> + k_bias_finish (one lsp_estimation_bias call per matrix)",
+        "estimation_bias": {"kernel": "k_decompress_wide<..., NORMS> + k_bias_finish (one lsp_estimation_bias call per matrix)",
                             "ms_per_pass": round(ms_bias, 4), "GB/s": round(bbytes / (ms_bias * 1e-3) / 1e9, 1),
                             "frac_of_hbm_peak": round(bbytes / (ms_bias * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                             "avg_call_us": round(ms_bias * 1e3 / nlaunch, 2)},

@@ -1,15 +1,14 @@
 // Decompress and apply:  W <- rn(W - P S Q^T)  (Alg. 1, apply step; Alg. 3, last step of the
-// layer loop).  One kernel, one fused read-modify-write pass over W:
+// layer loop).  One launch, one fused read-modify-write pass over W:
 //   phase 1  U = P S for the workgroup's R rows of W (gathers d rows of S per row, S stays in
-//            L2), stored in LDS as [4-row plane][column b][4 rows] fp32;
-//   phase 2  every thread owns two columns j, has the d (column, value) pairs of their rows of Q
-//            in registers, and for each 4-row plane gathers U with one 128-bit LDS read per pair;
-//            W is read, updated in fp32 and rounded once.
+//            L2), stored in LDS in fp32, the rows of a column in units of 4 rows (k_decompress and k_decompress_any), 8 or 16 (k_decompress_wide);
+//   phase 2  every thread has the d (column, value) pairs of its columns' rows of Q in registers
+//            and gathers U with one 128-bit LDS read per pair and 4 rows; W is read, updated in fp32 and rounded once.
 // The bytes that have to move are the read and the write of W; no matrix cores (sparse gather + fp32 FMA).
-// What bounds it: no single thing.  In the launch of the seven matrices of a 6.7B-style layer (bf16, r = 512, d = 8;
-// 207 us) HBM moves 942 MB (4.5 TB/s, two thirds of a plain read-modify-write pass), the LDS works 52 % of the cycles
-// (more than half of that for bank conflicts), the vector ALUs 40 %, L2 hands out 1.39 GB (rows of W, Q and S); 3.1 waves a
-// SIMD are resident on average (4 fit), and they wait for data 45 % of their time and for their turn to issue 33 %.
+// What bounds it: no single thing.  In the launch of the seven matrices of a 6.7B-style layer (bf16, r = 512, d = 8, k_decompress_wide in blocks of 32 rows;
+// 199 us, 207 with k_decompress) HBM moves 921 MB (4.6 TB/s, 70 % of a plain read-modify-write pass), the LDS works 48 % of the cycles
+// (half of that for bank conflicts), the vector ALUs 47 %, L2 hands out 1.41 GB (rows of W, Q and S); 2.9 waves a
+// SIMD are resident on average (4 fit), and they wait for data 29 % of their time and for their turn to issue 50 %.
 //
 // The same kernels, built with NORMS, serve the estimation bias of Def. 2 (the test MaybeUpdate
 // makes in Alg. 1): with S = P^T G Q they rebuild P S Q^T tile by tile in registers, read G where
