@@ -103,7 +103,7 @@ int lsp_compress(const void* G, const int32_t* P_idx, const float* P_val, const 
     if (e != hipSuccess) return fail_launch(e);
     lsp::CompressGroup g;
     std::memset(&g, 0, sizeof(g));
-    g.count = 1; g.G[0] = G; g.plan[0] = plan; g.T[0] = T; g.S[0] = S; g.m[0] = (int32_t)m; g.n[0] = (int32_t)n;
+    g.count = 1; g.p[0].G = G; g.p[0].plan = plan; g.p[0].T = T; g.p[0].S = S; g.p[0].m = (int32_t)m; g.p[0].n = (int32_t)n;
     e = lsp::launch_compress_planned(g, r, d, dtype, st, lsp::RawCall{P_idx, P_val, Q_idx, Q_val, status});
     return e == hipSuccess ? LSP_OK : fail_launch(e);
 }
@@ -195,9 +195,9 @@ int lsp_compress_planned_grouped(const lsp_compress_item* items, int32_t count, 
         if (!aligned16(it.G) || !aligned16(it.S)) return LSP_ERR_ALIGN;
         for (int q = 0; q < p; ++q)                            // problems of a group run concurrently
             if (items[q].workspace == it.workspace || items[q].S == it.S) return LSP_ERR_WORKSPACE;
-        g.G[p] = it.G; g.plan[p] = static_cast<const uint8_t*>(it.plan);
-        g.T[p] = static_cast<float*>(it.workspace); g.S[p] = it.S;
-        g.m[p] = (int32_t)it.m; g.n[p] = (int32_t)it.n;
+        lsp::CompressProblem& x = g.p[p];
+        x.G = it.G; x.plan = static_cast<const uint8_t*>(it.plan); x.T = static_cast<float*>(it.workspace); x.S = it.S;
+        x.m = (int32_t)it.m; x.n = (int32_t)it.n;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = lsp::launch_compress_planned(g, r, d, dtype, st);
@@ -231,8 +231,7 @@ int lsp_decompress_apply_grouped(const lsp_apply_item* items, int32_t count, int
             return LSP_ERR_ALIGN;
         for (int q = 0; q < p; ++q)
             if (items[q].W == it.W) return LSP_ERR_SHAPE;      // one matrix twice in a group would race
-        g.W[p] = it.W; g.S[p] = it.S; g.P_idx[p] = it.P_idx; g.P_val[p] = it.P_val; g.Q_idx[p] = it.Q_idx; g.Q_val[p] = it.Q_val;
-        g.m[p] = (int32_t)it.m; g.n[p] = (int32_t)it.n;
+        g.p[p] = lsp::ApplyProblem{it.W, it.S, it.P_idx, it.P_val, it.Q_idx, it.Q_val, (int32_t)it.m, (int32_t)it.n, 0, 0};
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipError_t e = lsp::launch_decompress(g, r, d, dtype, st);
@@ -269,9 +268,8 @@ int lsp_estimation_bias(const void* G, const float* S, const int32_t* P_idx, con
     lsp::ApplyGroup g;
     std::memset(&g, 0, sizeof(g));
     g.count = 1;
-    g.W[0] = const_cast<void*>(G);                 // read only: the kernels built for the norms store nothing
-    g.S[0] = S; g.P_idx[0] = P_idx; g.P_val[0] = P_val; g.Q_idx[0] = Q_idx; g.Q_val[0] = Q_val;
-    g.m[0] = (int32_t)m; g.n[0] = (int32_t)n;
+    // (G is read only: the kernels built for the norms store nothing)
+    g.p[0] = lsp::ApplyProblem{const_cast<void*>(G), S, P_idx, P_val, Q_idx, Q_val, (int32_t)m, (int32_t)n, 0, 0};
     hipError_t e = lsp::launch_bias(g, r, d, dtype, static_cast<float*>(workspace), out, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? LSP_OK : fail_launch(e);
 }

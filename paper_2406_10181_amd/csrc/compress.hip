@@ -25,18 +25,23 @@ namespace lsp {
 // row of P^T and one stripe of 256 columns, one column per thread.
 constexpr int kThreadsB = 256;
 constexpr int kStripeQuads = 64;                              // column quads (float4) per stripe
-__global__ __launch_bounds__(kThreadsB) void k_compress_pt(const CompressGroup grp, int r, int d, int nstripes, bool tiles) {
-    const CompressProblem pr = group_pick(grp, (int)blockIdx.x, true);
+__global__ __launch_bounds__(kThreadsB) void k_compress_pt(const CompressGroup) {
+    const auto* grp = group_args<CompressGroup>();
+    const auto pick = pick_problem(grp, grp->first_pt, (int)blockIdx.x);
+    const CompressProblem& pr = pick.p;
+    const int r = pick.r, d = pick.d, nstripes = pick.quads;
+    const bool tiles = pick.tiles != 0;
     const uint8_t* __restrict__ plan = pr.plan;
     const float* __restrict__ T = pr.T;
     float* __restrict__ S = pr.S;
-    const int block = pr.block_pt;
-    PlanHeaderPtr H = as_const<PlanHeader>(plan);
+    const int block = (int)blockIdx.x - pr.first_pt;
+    const LoadedHeader H = load_header(plan);
     if (!plan_matches(H, pr.m, pr.n, r, d, tiles)) return;                   // kernel A has filled S with NaN
     const int stripe = block % nstripes, item = block / nstripes;
     if (item >= H->p_nitems) return;
-    const auto* itp = as_const<int32_t>(plan + H->off_p_item) + 4 * item;    // RowItem, field by field
-    const RowItem it{itp[0], itp[1], itp[2], itp[3]};
+    words4 fields = scalar_load<words4>(as_const<RowItem>(plan + H->off_p_item) + item);
+    arrived(fields);
+    const RowItem it{(int32_t)fields[0], (int32_t)fields[1], (int32_t)fields[2], (int32_t)fields[3]};
     const uint2* ent = reinterpret_cast<const uint2*>(plan + H->off_p_ent) + it.start;
     for (int b = stripe * kStripeQuads * 4 + threadIdx.x; b < min(r, (stripe + 1) * kStripeQuads * 4); b += kThreadsB) {
         float acc = 0.0f;
@@ -58,20 +63,25 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt(const CompressGroup g
 // exchanges in a fixed order.  A row's last quad starts at r - 4 when r is no multiple of 4 and stores only what the
 // quad before it has not (3001 rows, r = 250, d = 5: 26 us one column a thread, now 6).
 template <int LG>
-__global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup grp, int r, int d, int sq, bool tiles) {
+__global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup) {
     constexpr int NG = kWave / LG;                            // entry groups per wave
-    const CompressProblem pr = group_pick(grp, (int)blockIdx.x, true);
+    const auto* grp = group_args<CompressGroup>();
+    const auto pick = pick_problem(grp, grp->first_pt, (int)blockIdx.x);
+    const CompressProblem& pr = pick.p;
+    const int r = pick.r, d = pick.d, sq = pick.quads;
+    const bool tiles = pick.tiles != 0;
     const uint8_t* __restrict__ plan = pr.plan;
     const float* __restrict__ T = pr.T;
     float* __restrict__ S = pr.S;
-    const int block = pr.block_pt;
-    PlanHeaderPtr H = as_const<PlanHeader>(plan);
+    const int block = (int)blockIdx.x - pr.first_pt;
+    const LoadedHeader H = load_header(plan);
     if (!plan_matches(H, pr.m, pr.n, r, d, tiles)) return;                   // kernel A has filled S with NaN
     const int stripe = block & 7;
     const int item = (block >> 3) * (kThreadsB / kWave) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (item >= H->p_nitems) return;
-    const auto* itp = as_const<int32_t>(plan + H->off_p_item) + 4 * item;    // RowItem, field by field
-    const RowItem it{itp[0], itp[1], itp[2], itp[3]};
+    words4 fields = scalar_load<words4>(as_const<RowItem>(plan + H->off_p_item) + item);
+    arrived(fields);
+    const RowItem it{(int32_t)fields[0], (int32_t)fields[1], (int32_t)fields[2], (int32_t)fields[3]};
     const uint2* ent = reinterpret_cast<const uint2*>(plan + H->off_p_ent) + it.start;
     const int lane = threadIdx.x & 63;
     const int grp_e = lane / LG, ql = lane % LG;
@@ -142,11 +152,11 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup 
 // ----------------------------------------------------------------------------------------------
 static bool walks_tiles(lsp_dtype dtype, const RawCall& raw) { return dtype == LSP_BF16 && !raw.status; }   // (plans of raw calls have no tiles)
 
-static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, lsp_dtype dtype, hipStream_t st) {
+static hipError_t launch_gq(CompressGroup& g, const RawCall& raw, lsp_dtype dtype, hipStream_t st) {
     switch (dtype) {
-        case LSP_F32:  return launch_gq_f32(g, r, d, raw, st);
-        case LSP_F16:  return launch_gq_f16(g, r, d, raw, st);
-        default:       return walks_tiles(dtype, raw) ? launch_mm_bf16(g, r, d, st) : launch_gq_bf16(g, r, d, raw, st);
+        case LSP_F32:  return launch_gq_f32(g, raw, st);
+        case LSP_F16:  return launch_gq_f16(g, raw, st);
+        default:       return walks_tiles(dtype, raw) ? launch_mm_bf16(g, st) : launch_gq_bf16(g, raw, st);
     }
 }
 
@@ -156,32 +166,33 @@ static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, const RawCal
 // short ones fill in behind them.
 static void longest_first(CompressGroup& g) {
     for (int a = 1; a < g.count; ++a)
-        for (int b = a; b > 0 && g.n[b] > g.n[b - 1]; --b) {
-            std::swap(g.G[b], g.G[b - 1]); std::swap(g.plan[b], g.plan[b - 1]); std::swap(g.T[b], g.T[b - 1]);
-            std::swap(g.S[b], g.S[b - 1]); std::swap(g.m[b], g.m[b - 1]); std::swap(g.n[b], g.n[b - 1]);
-        }
+        for (int b = a; b > 0 && g.p[b].n > g.p[b - 1].n; --b) std::swap(g.p[b], g.p[b - 1]);
 }
 
 hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st, const RawCall& raw) {
     const int nstripes = (r + kStripeQuads * 4 - 1) / (kStripeQuads * 4);
     const bool striped = r >= 4, tiles = walks_tiles(dtype, raw);
     longest_first(g);
-    g.first_pt[0] = 0;
-    for (int p = 0; p < g.count; ++p) {
-        const int32_t items = (int32_t)plan_max_items(g.m[p], r, d);
-        g.first_pt[p + 1] = g.first_pt[p] + (striped ? ((items + 3) / 4) * 8 : items * nstripes);
+    const int sq = ((r + 3) / 4 + 7) / 8;
+    g.r = r; g.d = d; g.tiles = tiles ? 1 : 0;
+    g.quads = striped ? sq : nstripes;
+    int32_t blocks = 0;
+    for (int p = 0; p < kMaxGroup; ++p) {
+        g.first_pt[p] = INT32_MAX;
+        if (p >= g.count) continue;
+        const int32_t items = (int32_t)plan_max_items(g.p[p].m, r, d);
+        g.first_pt[p] = g.p[p].first_pt = blocks;
+        blocks += striped ? ((items + 3) / 4) * 8 : items * nstripes;
     }
-    hipError_t e = launch_gq(g, r, d, raw, dtype, st);
+    hipError_t e = launch_gq(g, raw, dtype, st);
     if (e != hipSuccess) return e;
-    const unsigned blocks = (unsigned)g.first_pt[g.count];
     if (striped) {
-        const int sq = ((r + 3) / 4 + 7) / 8;
-        if (sq <= 16)      hipLaunchKernelGGL(k_compress_pt8<16>, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, sq, tiles);
-        else if (sq <= 32) hipLaunchKernelGGL(k_compress_pt8<32>, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, sq, tiles);
-        else               hipLaunchKernelGGL(k_compress_pt8<64>, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, sq, tiles);
+        if (sq <= 16)      hipLaunchKernelGGL(k_compress_pt8<16>, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
+        else if (sq <= 32) hipLaunchKernelGGL(k_compress_pt8<32>, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
+        else               hipLaunchKernelGGL(k_compress_pt8<64>, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_compress_pt, dim3(blocks), dim3(kThreadsB), 0, st, g, (int)r, (int)d, nstripes, tiles);
+    hipLaunchKernelGGL(k_compress_pt, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
     return hipGetLastError();
 }
 

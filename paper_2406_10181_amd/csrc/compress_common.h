@@ -16,8 +16,13 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // plan at all) must not be walked.  Kernel A then fills S with NaN, which is how the caller sees
 // the mistake (or takes the scatter form, raw calls), and kernel B does nothing; all kernels exit normally.
 // tiles: kernel A of this call walks the tiles, so there must be some; kernel B asks for the same, or it would put what lies in T in the place of the NaN.
-__device__ __forceinline__ bool plan_matches(PlanHeaderPtr H, int m, int n, int r, int d, bool tiles) {
-    return H->magic == kPlanMagic && H->m == m && H->n == n && H->r == r && H->d == d && (!tiles || H->m_total_steps != 0);
+// (One condition and no chain of them: each would wait for the one before.)
+__device__ __forceinline__ bool same_problem(uint32_t magic, int32_t hm, int32_t hn, int32_t hr, int32_t hd, int m, int n, int r, int d) {
+    return ((magic ^ kPlanMagic) | (uint32_t)(hm ^ m) | (uint32_t)(hn ^ n) | (uint32_t)(hr ^ r) | (uint32_t)(hd ^ d)) == 0;
+}
+__device__ __forceinline__ bool plan_matches(const LoadedHeader& H, int m, int n, int r, int d, bool tiles) {
+    const uint32_t steps = tiles ? H->m_total_steps : 1u;
+    return same_problem(H->magic, H->m, H->n, H->r, H->d, m, n, r, d) && steps != 0;
 }
 __device__ __forceinline__ void fill_s(float* __restrict__ S, float x, int r, int block, int nblocks, int tid, int nthreads) {
     const int64_t total = (int64_t)r * r;
@@ -68,7 +73,7 @@ constexpr int kBatchLoads = kSegBatch / 2;                    // 128-bit loads p
 // sums in owner order (they sit side by side) and stores the column of T.  No atomics, so the
 // result does not depend on timing.  Called by all threads of the workgroup.
 template <int NS, int R>
-__device__ __forceinline__ void write_tile_shared(uint8_t* smem, const uint8_t* plan, PlanHeaderPtr H, float* __restrict__ T,
+__device__ __forceinline__ void write_tile_shared(uint8_t* smem, const uint8_t* plan, const LoadedHeader& H, float* __restrict__ T,
                                                   const float (&acc)[NS][R], int nslots, int64_t i0, int m, int r, int tid) {
     __syncthreads();                                                  // the staged chunk is no longer read
     float* Tl = reinterpret_cast<float*>(smem);
@@ -122,11 +127,11 @@ __device__ __forceinline__ void swap_owner(uint8_t* area, float (&acc)[R], uint3
     __syncthreads();
 }
 
-// Launchers of kernel A (they fill in first_gq and blocks_gq): one workgroup = a block of rows of G at a time, 512 threads, one lane
+// Launchers of kernel A (they fill in first_gq, wgs_gq and blocks_gq; r and d are set): one workgroup = a block of rows of G at a time, 512 threads, one lane
 // per (virtual) column of T.
-hipError_t launch_gq_bf16(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st);
-hipError_t launch_gq_f16(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st);
-hipError_t launch_gq_f32(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st);
-hipError_t launch_mm_bf16(CompressGroup& g, int32_t r, int32_t d, hipStream_t st);   // kept plans (compress_mm.hip)
+hipError_t launch_gq_bf16(CompressGroup& g, const RawCall& raw, hipStream_t st);
+hipError_t launch_gq_f16(CompressGroup& g, const RawCall& raw, hipStream_t st);
+hipError_t launch_gq_f32(CompressGroup& g, const RawCall& raw, hipStream_t st);
+hipError_t launch_mm_bf16(CompressGroup& g, hipStream_t st);   // kept plans (compress_mm.hip)
 
 }  // namespace lsp

@@ -150,13 +150,13 @@ __device__ __forceinline__ void fma_pair(const u32x4 e, const u32x4 (&x)[2], flo
 // tail of a block cost nothing but for the first and the last one).
 template <typename D, bool WHOLE>
 __device__ __forceinline__ void gq_one_slot(ChunkStager<D, WHOLE>& stg, uint8_t* smem, const typename D::elem* __restrict__ G,
-                                              const uint8_t* __restrict__ plan, PlanHeaderPtr H,
+                                              const uint8_t* __restrict__ plan, const LoadedHeader& H,
                                               float* __restrict__ T, int64_t i0, int nblk, int m, int n, int r,
                                               int tid, int lane, int wave) {
     constexpr int R = kRowsGQ<D>;
     const int nchunks = H->nchunks;
     const auto* seg = as_const<uint32_t>(plan + H->off_q_seg) + wave;
-    const u32x4* rp0 = reinterpret_cast<const u32x4*>(plan + H->off_q_rows) + (size_t)(H->q_stream_row[wave] >> 1) * kWave + lane;
+    const u32x4* rp0 = reinterpret_cast<const u32x4*>(plan + H->off_q_rows) + (size_t)(as_const<PlanHeader>(plan)->q_stream_row[wave] >> 1) * kWave + lane;
     const u32x4* rp = rp0;
     const uint32_t mycol = as_const<uint16_t>(plan + H->off_q_vcol)[tid];
     const bool shared = H->q_any_shared != 0;
@@ -274,13 +274,13 @@ __device__ __forceinline__ void gq_one_slot(ChunkStager<D, WHOLE>& stg, uint8_t*
 // the sums of NS columns per lane would not fit through LDS cheaply).
 template <typename D, int NS, bool WHOLE>
 __device__ __forceinline__ void gq_multi_slot(ChunkStager<D, WHOLE>& stg, uint8_t* smem, const typename D::elem* __restrict__ G,
-                                                const uint8_t* __restrict__ plan, PlanHeaderPtr H,
+                                                const uint8_t* __restrict__ plan, const LoadedHeader& H,
                                                 float* __restrict__ T, int64_t i0, int nblk, int m, int n, int r,
                                                 int tid, int lane, int wave) {
     constexpr int R = kRowsGQ<D>;
     const int nchunks = H->nchunks, nslots = H->nslots;
     const auto* seg = as_const<uint32_t>(plan + H->off_q_seg) + wave;
-    const u32x4* rp0 = reinterpret_cast<const u32x4*>(plan + H->off_q_rows) + (size_t)(H->q_stream_row[wave] >> 1) * kWave + lane;
+    const u32x4* rp0 = reinterpret_cast<const u32x4*>(plan + H->off_q_rows) + (size_t)(as_const<PlanHeader>(plan)->q_stream_row[wave] >> 1) * kWave + lane;
     const u32x4* rp = rp0;
     const auto* vcol = as_const<uint16_t>(plan + H->off_q_vcol);
     const bool shared = H->q_any_shared != 0;
@@ -396,16 +396,19 @@ __device__ __forceinline__ void gq_multi_slot(ChunkStager<D, WHOLE>& stg, uint8_
 struct NoRawCall {};
 // RAW: for a call on raw ELL arrays.  (With the scatter form in the one kernel for all, the planned calls lost 1 %.)
 template <typename D, bool WHOLE, bool RAW>
-__global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGroup grp, int r, int d, const std::conditional_t<RAW, RawCall, NoRawCall> raw) {
+__global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGroup, const std::conditional_t<RAW, RawCall, NoRawCall> raw) {
     constexpr int R = kRowsGQ<D>;
     extern __shared__ __align__(16) uint8_t smem[];
-    const CompressProblem pr = group_pick(grp, (int)blockIdx.x, false);
+    const auto* grp = group_args<CompressGroup>();
+    const auto pick = pick_problem(grp, grp->first_gq, (int)blockIdx.x);
+    const CompressProblem& pr = pick.p;
+    const int r = pick.r, d = pick.d;
     const typename D::elem* __restrict__ G = static_cast<const typename D::elem*>(pr.G);
     const uint8_t* __restrict__ plan = pr.plan;
     float* __restrict__ T = pr.T;
     float* __restrict__ S = pr.S;
     const int m = pr.m, n = pr.n;
-    const int block = pr.block_gq, nblocks = pr.nblocks_gq, blocks_per_wg = pr.blocks_gq;
+    const int block = (int)blockIdx.x - pr.first_gq, nblocks = pr.wgs_gq, blocks_per_wg = pr.blocks_gq;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -414,7 +417,8 @@ __global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGro
 
     ChunkStager<D, WHOLE> stg;
     stg.fetch(G, i0, m, n, 0, tid);                             // in flight while the plan's header arrives
-    PlanHeaderPtr H = as_const<PlanHeader>(plan);
+    asm volatile("" ::: "memory");                                    // (or they would be asked for behind the comparisons below)
+    const LoadedHeader H = load_header(plan);
     if (!plan_matches(H, m, n, r, d, false)) {                               // not a plan for this problem
         if constexpr (RAW) scatter_blocks<D>(G, raw, S, reinterpret_cast<float*>(smem), m, n, r, d, block, nblocks, tid, kThreadsGQ);
         else fill_s(S, __builtin_nanf(""), r, block, nblocks, tid, kThreadsGQ);
@@ -437,21 +441,27 @@ __global__ __launch_bounds__(kThreadsGQ, 4) void k_compress_gq(const CompressGro
 // 66.0 -> 61.7).  Shares of more than eight chunks are halved and so on, because the two workgroups of a CU do not
 // advance at the same speed.  Otherwise the workgroups are taken up as CUs fall free, and small ones even out the end:
 // two blocks each on big grids, else one.
-template <int R> static void share_blocks(CompressGroup& g) {
+// Returns the number of workgroups.
+template <int R> static unsigned share_blocks(CompressGroup& g) {
     constexpr int64_t kResident = 512;                                // two on each of 256 CUs
-    int64_t work = 0, rows = 0;
+    int64_t work = 0, rows = 0, grid = 0;
     for (int p = 0; p < g.count; ++p) {
-        work += (int64_t)((g.m[p] + R - 1) / R) * ((g.n[p] + kChunk - 1) / kChunk);
-        rows += g.m[p];
+        work += (int64_t)((g.p[p].m + R - 1) / R) * ((g.p[p].n + kChunk - 1) / kChunk);
+        rows += g.p[p].m;
     }
     auto fill = [&](auto&& blocks_of) {
         int64_t longest = 0;
-        g.first_gq[0] = 0;
-        for (int p = 0; p < g.count; ++p) {
-            const int64_t chunks = (g.n[p] + kChunk - 1) / kChunk, blocks = (g.m[p] + R - 1) / R;
+        grid = 0;
+        for (int p = 0; p < kMaxGroup; ++p) {
+            CompressProblem& x = g.p[p];
+            g.first_gq[p] = INT32_MAX;
+            if (p >= g.count) continue;
+            const int64_t chunks = (x.n + kChunk - 1) / kChunk, blocks = (x.m + R - 1) / R;
             const int64_t each = blocks_of(chunks);
-            g.blocks_gq[p] = (int32_t)each;
-            g.first_gq[p + 1] = g.first_gq[p] + (int32_t)((blocks + each - 1) / each);
+            x.blocks_gq = (int32_t)each;
+            x.wgs_gq = (int32_t)((blocks + each - 1) / each);
+            g.first_gq[p] = x.first_gq = (int32_t)grid;
+            grid += x.wgs_gq;
             longest = std::max(longest, each * chunks);
         }
         return longest;
@@ -460,30 +470,31 @@ template <int R> static void share_blocks(CompressGroup& g) {
         const int64_t share = (work + rounds * kResident - 1) / (rounds * kResident);
         if (share > 8) continue;
         const int64_t longest = fill([&](int64_t chunks) { return (share + chunks - 1) / chunks; });
-        if (g.first_gq[g.count] <= rounds * kResident && longest * 8 <= share * 9) return;
+        if (grid <= rounds * kResident && longest * 8 <= share * 9) return (unsigned)grid;
     }
     fill([&](int64_t) { return (int64_t)(rows >= 16384 ? 2 : 1); });
+    return (unsigned)grid;
 }
 
 template <typename D, bool WHOLE, bool RAW>
-static hipError_t launch_gq(const CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st) {
+static hipError_t launch_gq(const CompressGroup& g, unsigned grid, const RawCall& raw, hipStream_t st) {
     constexpr size_t lds = (size_t)2 * kPlaneStride;                  // two chunk buffers
     static_assert(lds >= (size_t)kScatterRows * LSP_MAX_R * sizeof(float), "room for scatter_blocks");
     std::conditional_t<RAW, RawCall, NoRawCall> args{};
     if constexpr (RAW) args = raw;
     hipError_t e;
     if ((e = allow_dynamic_lds<k_compress_gq<D, WHOLE, RAW>, lds>()) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_compress_gq<D, WHOLE, RAW>), dim3((unsigned)g.first_gq[g.count]), dim3(kThreadsGQ), lds, st, g, (int)r, (int)d, args);
+    hipLaunchKernelGGL((k_compress_gq<D, WHOLE, RAW>), dim3(grid), dim3(kThreadsGQ), lds, st, g, args);
     return hipGetLastError();
 }
 
 template <typename D>
-static hipError_t launch_gq(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st) {
+static hipError_t launch_gq(CompressGroup& g, const RawCall& raw, hipStream_t st) {
     bool whole = true;
-    share_blocks<kRowsGQ<D>>(g);
-    for (int p = 0; p < g.count; ++p) whole = whole && g.n[p] % 4 == 0;
+    const unsigned grid = share_blocks<kRowsGQ<D>>(g);
+    for (int p = 0; p < g.count; ++p) whole = whole && g.p[p].n % 4 == 0;
     if constexpr (!std::is_same_v<D, BF16>)                           // bf16 with a kept plan: compress_mm.hip
-        if (!raw.status) return whole ? launch_gq<D, true, false>(g, r, d, raw, st) : launch_gq<D, false, false>(g, r, d, raw, st);
-    return whole ? launch_gq<D, true, true>(g, r, d, raw, st) : launch_gq<D, false, true>(g, r, d, raw, st);
+        if (!raw.status) return whole ? launch_gq<D, true, false>(g, grid, raw, st) : launch_gq<D, false, false>(g, grid, raw, st);
+    return whole ? launch_gq<D, true, true>(g, grid, raw, st) : launch_gq<D, false, true>(g, grid, raw, st);
 }
 }  // namespace lsp

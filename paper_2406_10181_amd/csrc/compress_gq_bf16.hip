@@ -3,7 +3,7 @@
 #include "compress_gq.h"
 
 namespace lsp {
-hipError_t launch_gq_bf16(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st) {
-    return launch_gq<BF16>(g, r, d, raw, st);
+hipError_t launch_gq_bf16(CompressGroup& g, const RawCall& raw, hipStream_t st) {
+    return launch_gq<BF16>(g, raw, st);
 }
 }  // namespace lsp

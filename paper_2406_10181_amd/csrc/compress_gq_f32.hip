@@ -2,7 +2,7 @@
 #include "compress_gq.h"
 
 namespace lsp {
-hipError_t launch_gq_f32(CompressGroup& g, int32_t r, int32_t d, const RawCall& raw, hipStream_t st) {
-    return launch_gq<F32>(g, r, d, raw, st);
+hipError_t launch_gq_f32(CompressGroup& g, const RawCall& raw, hipStream_t st) {
+    return launch_gq<F32>(g, raw, st);
 }
 }  // namespace lsp

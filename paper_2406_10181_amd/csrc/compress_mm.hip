@@ -26,7 +26,6 @@ namespace lsp {
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 #define LSP_LDS_AS __attribute__((address_space(3)))
-#define LSP_GLOBAL_AS __attribute__((address_space(1)))               // (of addresses that went through LDS the compiler would not know it)
 
 constexpr int kLdsMM = 160 * 1024;
 constexpr int kWalkers = kWavesMM * kWave;                            // threads that walk the lists
@@ -221,30 +220,36 @@ __device__ __forceinline__ void store_sums(const float* sums, int stride, float 
     }
 }
 
-// The problem of a row block, read from the kernel's arguments with a run-time index (scalar loads): a workgroup looks several
-// up, and group_pick's selects over all problems would keep the whole group in registers.
+// The problem of a row block.
 struct RowBlocks { const void* G; const uint8_t* plan; float* T; float* S; int32_t m, n, block, blocks; };
-__device__ __forceinline__ RowBlocks problem_of(int block) {
-    const auto* g = (const LSP_CONST_AS CompressGroup*)__builtin_amdgcn_kernarg_segment_ptr();   // the kernel's first argument
-    int p = 0;
-    while (p + 1 < g->count && block >= g->first_gq[p + 1]) ++p;
-    return RowBlocks{g->G[p], g->plan[p], g->T[p], g->S[p], g->m[p], g->n[p], block - g->first_gq[p], g->first_gq[p + 1] - g->first_gq[p]};
+__device__ __forceinline__ RowBlocks row_blocks_of(int block) {
+    const auto* g = group_args<CompressGroup>();
+    const CompressProblem p = pick_problem(g, g->first_gq, block).p;
+    return RowBlocks{p.G, p.plan, p.T, p.S, p.m, p.n, block - p.first_gq, p.wgs_gq};
 }
 
 __device__ __forceinline__ bool sums_fit(int nvcols, int rows, int base) { return sums_stride(nvcols) * rows * 4 <= kLdsMM - base; }
 
-// Whether the LDS has room for two chunks beside the sums of every matrix of the call (16 rows: up to 352 virtual columns; 8 rows: always).  H: the plan of one of them.
-template <int NP> __device__ __forceinline__ bool two_chunks(PlanHeaderPtr H) {
+// Whether the LDS has room for two chunks beside the sums of every matrix of the call (16 rows: up to 352 virtual columns; 8 rows: always).  nvcols: those of one of them.
+template <int NP> __device__ __forceinline__ bool two_chunks(int nvcols) {
     static_assert((kMaxSlots * kThreadsGQ + 4) * kRowsMM<2> * 4 <= kLdsMM - sums_base<2>(true), "8 rows");
     if constexpr (NP == 2) return true;
-    const auto* g = (const LSP_CONST_AS CompressGroup*)__builtin_amdgcn_kernarg_segment_ptr();
-    uint32_t most = (uint32_t)H->nvcols;
-    if (g->count > 1) {
+    const auto* g = group_args<CompressGroup>();
+    uint32_t most = (uint32_t)nvcols;
+    const int count = g->count;
+    if (count > 1) {                                                  // (of all of them the pointers, then the numbers)
+        uint64_t plan[kMaxGroup];
+        uint32_t v[kMaxGroup];
 #pragma unroll
-        for (int p = 0; p < kMaxGroup; ++p) {                         // (all of them asked for before the first is looked at)
-            const uint32_t v = (uint32_t)as_const<PlanHeader>(g->plan[p < g->count ? p : 0])->nvcols;
-            most = v > most ? v : most;
-        }
+        for (int p = 0; p < kMaxGroup; ++p) plan[p] = *(const LSP_CONST_AS uint64_t*)&g->p[p < count ? p : 0].plan;
+#pragma unroll
+        for (int p = 0; p < kMaxGroup; ++p) arrived(plan[p]);
+#pragma unroll
+        for (int p = 0; p < kMaxGroup; ++p) v[p] = (uint32_t)((PlanHeaderPtr)plan[p])->nvcols;
+#pragma unroll
+        for (int p = 0; p < kMaxGroup; ++p) arrived(v[p]);
+#pragma unroll
+        for (int p = 0; p < kMaxGroup; ++p) most = v[p] > most ? v[p] : most;
     }
     return most <= (uint32_t)(kMaxSlots * kThreadsGQ) && sums_fit((int)most, kRowsMM<NP>, sums_base<NP>(true));
 }
@@ -265,17 +270,21 @@ template <int NP, bool HALVES> struct BlockWalk {
     bool others = false;                                              // blocks of the other kind were passed by
     RowBlocks pr;
     PlanHeaderPtr H;
-    int nchunks;
+    int nchunks, nvcols;
     // the first of the blocks from `block` on that is of this kind; visit: called for every block passed by or taken
     template <typename Visit> __device__ __forceinline__ void find(int from, int blocks, int r, int d, Visit&& visit) {
         for (block = from; block < blocks; block += gridDim.x) {
-            pr = problem_of(block);
+            pr = row_blocks_of(block);
             H = as_const<PlanHeader>(pr.plan);
-            const bool planned = plan_matches(H, pr.m, pr.n, r, d, true);
+            words8 head = scalar_load<words8>(H);
+            uint32_t steps = H->m_total_steps;
+            arrived(head, steps);
+            const bool planned = same_problem(head[0], (int)head[1], (int)head[2], (int)head[3], (int)head[4], pr.m, pr.n, r, d) && steps != 0;
             visit(pr, H, planned);
             if (!planned) continue;
-            nchunks = H->nchunks;
-            if (sums_fit(H->nvcols, kRowsMM<NP>, sums_base<NP>(NP == 2)) != HALVES) return;
+            nchunks = (int)head[5];
+            nvcols = (int)head[7];
+            if (sums_fit(nvcols, kRowsMM<NP>, sums_base<NP>(NP == 2)) != HALVES) return;
             others = true;
         }
     }
@@ -343,7 +352,7 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
         }
     };
 
-    const RowBlocks start = problem_of(blockIdx.x);                   // nearly always the first: its rows are asked for before its plan is looked at
+    const RowBlocks start = row_blocks_of(blockIdx.x);                   // nearly always the first: its rows are asked for before its plan is looked at
     lo.fetch(static_cast<const uint16_t*>(start.G), (int64_t)start.block * R, start.m, start.n, chunk_at(0, start.block * R, start.m, (int)(((uint32_t)start.n + kChunk - 1) / kChunk)), tid);
     hi.fetch(static_cast<const uint16_t*>(start.G), (int64_t)start.block * R + R / 2, start.m, start.n, chunk_at(0, start.block * R, start.m, (int)(((uint32_t)start.n + kChunk - 1) / kChunk)), tid);
     w.find(blockIdx.x, blocks, r, d, clear_s);
@@ -373,7 +382,7 @@ __device__ __forceinline__ void fetch_blocks(uint8_t* smem, int blocks, int r, i
             fetch_lo();
             fetch_hi();
         }
-        const bool two = two_chunks<NP>(w.H);
+        const bool two = two_chunks<NP>(w.nvcols);
         bool after_last = false;
         look_up_here();
         auto stage = [&]() {
@@ -472,7 +481,7 @@ __device__ __forceinline__ bool walk_blocks(uint8_t* smem, int blocks, int r, in
     BlockWalk<NP, HALVES> w;
     w.find(blockIdx.x, blocks, r, d, [](const RowBlocks&, PlanHeaderPtr, bool) {});
     if (w.block >= blocks) return w.others;
-    const bool two = !HALVES && two_chunks<NP>(w.H);                  // (see fetch_blocks)
+    const bool two = !HALVES && two_chunks<NP>(w.nvcols);                  // (see fetch_blocks)
     const uint32_t sums_at = (uint32_t)sums_base<NP>(two);
 
     // A chunk's steps lie one behind the other.  ring: the next RING, from slot 0 on; those of the next chunk take the places of the last ones.
@@ -695,8 +704,10 @@ __device__ __forceinline__ bool walk_blocks(uint8_t* smem, int blocks, int r, in
 }
 
 template <int NP, int RING, bool WHOLE>
-__global__ __launch_bounds__(kThreadsMM) void k_compress_mm(const CompressGroup grp, int r, int d, int blocks) {
+__global__ __launch_bounds__(kThreadsMM) void k_compress_mm(const CompressGroup) {
     extern __shared__ __align__(16) uint8_t smem[];
+    words4 head = scalar_load<words4>(group_args<CompressGroup>());
+    const int r = (int)head[1], d = (int)head[2], blocks = (int)head[3];
     const int tid = threadIdx.x;
     zero_unit<NP>(smem, tid);
     zero_unit<NP>(smem + kSecondBase<NP>, tid);                       // (where there is no second chunk, sums of later on)
@@ -708,25 +719,29 @@ __global__ __launch_bounds__(kThreadsMM) void k_compress_mm(const CompressGroup 
     }
 }
 
-template <int NP, int RING> static hipError_t launch_mm_rows(CompressGroup& g, int32_t r, int32_t d, hipStream_t st) {
+template <int NP, int RING> static hipError_t launch_mm_rows(CompressGroup& g, hipStream_t st) {
     constexpr int R = kRowsMM<NP>;
     constexpr size_t lds = kLdsMM;
     bool whole = true;
-    g.first_gq[0] = 0;
-    for (int p = 0; p < g.count; ++p) {
-        whole = whole && g.n[p] % 8 == 0;
-        g.blocks_gq[p] = 1;
-        g.first_gq[p + 1] = g.first_gq[p] + (g.m[p] + R - 1) / R;
+    g.blocks = 0;
+    for (int p = 0; p < kMaxGroup; ++p) {
+        CompressProblem& x = g.p[p];
+        g.first_gq[p] = INT32_MAX;
+        if (p >= g.count) continue;
+        whole = whole && x.n % 8 == 0;
+        x.blocks_gq = 1;
+        x.wgs_gq = (x.m + R - 1) / R;
+        g.first_gq[p] = x.first_gq = g.blocks;
+        g.blocks += x.wgs_gq;
     }
-    const int blocks = g.first_gq[g.count];
-    const dim3 grid((unsigned)std::min(blocks, kResidentMM));
+    const dim3 grid((unsigned)std::min(g.blocks, kResidentMM));
     hipError_t e;
     if (whole) {
         if ((e = allow_dynamic_lds<k_compress_mm<NP, RING, true>, lds>()) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_compress_mm<NP, RING, true>), grid, dim3(kThreadsMM), lds, st, g, (int)r, (int)d, blocks);
+        hipLaunchKernelGGL((k_compress_mm<NP, RING, true>), grid, dim3(kThreadsMM), lds, st, g);
     } else {
         if ((e = allow_dynamic_lds<k_compress_mm<NP, RING, false>, lds>()) != hipSuccess) return e;
-        hipLaunchKernelGGL((k_compress_mm<NP, RING, false>), grid, dim3(kThreadsMM), lds, st, g, (int)r, (int)d, blocks);
+        hipLaunchKernelGGL((k_compress_mm<NP, RING, false>), grid, dim3(kThreadsMM), lds, st, g);
     }
     return hipGetLastError();
 }
@@ -739,14 +754,14 @@ template <int NP, int RING> static hipError_t launch_mm_rows(CompressGroup& g, i
 //   d = 4 37.3 and 40.1, r = 256, d = 4 29.1 and 28.4; 4200 x 2048, r = 1024, d = 8, zipf 53.9 and 51.6);
 //   and beyond r = 1024, where the sums of 16 rows do not fit the LDS (4096 x 4096, d = 8, r = 1536 43.5 and 46.0, r = 2048 49.2 and 51.5, d = 16 65.7 and 64.9; 5120 x 5120, r = 2048,
 //   d = 8 69.6 and 89.3).
-static bool narrow_blocks(const CompressGroup& g, int32_t r) {
+static bool narrow_blocks(const CompressGroup& g) {
     int64_t of8 = 0, of16 = 0;
     for (int p = 0; p < g.count; ++p) {
-        of8 += (g.m[p] + 7) / 8;
-        of16 += (g.m[p] + 15) / 16;
+        of8 += (g.p[p].m + 7) / 8;
+        of16 += (g.p[p].m + 15) / 16;
     }
     const auto rounds = [](int64_t blocks) { return (blocks + kResidentMM - 1) / kResidentMM; };
-    return r > 1024 || rounds(of8) == 1 || (rounds(of8) == 3 && rounds(of16) == 2);
+    return g.r > 1024 || rounds(of8) == 1 || (rounds(of8) == 3 && rounds(of16) == 2);
 }
 
 // Every bf16 call with a kept plan comes here, whatever its rows: the sums of a row do not depend on the blocks it is in, so a matrix has the same
@@ -758,9 +773,9 @@ static bool narrow_blocks(const CompressGroup& g, int32_t r) {
 // 2 d steps a wave and chunk).  us with 8, 6 and 4: 4096 x 16384, r = 512, d = 2 40.8, 38.8 and 37.5, d = 4 41.4, 42.3 and 44.1, d = 8 53.2, 53.7 and 55.9; 4096 x 1024, r = 64, d = 2
 // 14.6, 14.4 and 14.0.  Blocks of 8 rows: 2048 x 8192, r = 512, d = 4 19.8, 19.7 and 20.2; 5120 x 5120 34.2, 33.5 and 33.6, d = 8 40.6, 40.6 and 42.0; with 6 and 4, two chunks and fewer:
 // 5120 x 4096, r = 512, d = 8 33.3 and 34.4; 4096 x 4096, r = 2048, d = 8 49.0 and 49.6, d = 16 62.6 and 64.8; 2048 x 4096, r = 128, d = 4 15.6 and 15.9; 264 x 657, r = 21, d = 3 10.9 and 10.8.
-hipError_t launch_mm_bf16(CompressGroup& g, int32_t r, int32_t d, hipStream_t st) {
-    if (narrow_blocks(g, r)) return d <= 2 ? launch_mm_rows<2, 4>(g, r, d, st) : launch_mm_rows<2, 6>(g, r, d, st);
-    return d <= 2 ? launch_mm_rows<4, 4>(g, r, d, st) : launch_mm_rows<4, 8>(g, r, d, st);
+hipError_t launch_mm_bf16(CompressGroup& g, hipStream_t st) {
+    if (narrow_blocks(g)) return g.d <= 2 ? launch_mm_rows<2, 4>(g, st) : launch_mm_rows<2, 6>(g, st);
+    return g.d <= 2 ? launch_mm_rows<4, 4>(g, st) : launch_mm_rows<4, 8>(g, st);
 }
 
 }  // namespace lsp

@@ -243,7 +243,7 @@ struct Passes {
 // plane just finished has left, so a whole pass is in flight at any time at the cost of one patch; the rows of Q follow
 // at the end of the pass.
 template <typename D, int RG, int DD, int PS, int NT, bool NORMS>
-__global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const ApplyGroup grp, int r, float2* __restrict__ partial) {
+__global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const ApplyGroup) {
     extern __shared__ __align__(16) uint8_t smem[];
     constexpr int CPT = 2;
     constexpr int R = 4 * RG;
@@ -251,15 +251,18 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
     static_assert(NE % 4 == 0, "entries are loaded 4 at a time");
     typedef Pair<D> Patch;
     // a row block is shared by `parts` workgroups, each with its share of the passes (all build the tile of U)
-    const int prob = group_find(grp.first, grp.count, (int)blockIdx.x);
-    const int unit = (int)blockIdx.x - grp.first[prob], parts = grp.parts[prob];
+    const auto* grp = group_args<ApplyGroup>();
+    const auto pick = pick_problem(grp, grp->first, (int)blockIdx.x);
+    const ApplyProblem& pr = pick.p;
+    const int r = pick.r;
+    const int unit = (int)blockIdx.x - pr.first, parts = pr.parts;
     const int block = parts > 1 ? unit / parts : unit, part = unit - block * parts;
-    const float* __restrict__ S = grp.S[prob];
-    const int32_t* __restrict__ P_idx = grp.P_idx[prob];
-    const float* __restrict__ P_val = grp.P_val[prob];
-    const int32_t* __restrict__ Q_idx = grp.Q_idx[prob];
-    const float* __restrict__ Q_val = grp.Q_val[prob];
-    const int m = grp.m[prob], n = grp.n[prob];
+    const float* __restrict__ S = pr.S;
+    const int32_t* __restrict__ P_idx = pr.P_idx;
+    const float* __restrict__ P_val = pr.P_val;
+    const int32_t* __restrict__ Q_idx = pr.Q_idx;
+    const float* __restrict__ Q_val = pr.Q_val;
+    const int m = pr.m, n = pr.n;
     const int64_t i0 = (int64_t)block * R;
     int2* pent = reinterpret_cast<int2*>(smem + RG * PS);
     const f32x4* Us4 = reinterpret_cast<const f32x4*>(smem);
@@ -269,7 +272,7 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
     const int npass = passes.count;
     auto pass_col = [&](int p) -> int { return passes.at(p) * step; };   // the pass's first column
     const int lane_col = (int)threadIdx.x * CPT;                    // of the pass; past n: nothing there for this thread
-    const RowBlock<D> rows{static_cast<char*>(grp.W[prob]) + i0 * n * D::size, (int64_t)n * D::size, m - i0 < R ? (int)(m - i0) : R, n};
+    const RowBlock<D> rows{static_cast<char*>(pr.W) + i0 * n * D::size, (int64_t)n * D::size, m - i0 < R ? (int)(m - i0) : R, n};
 
     Patch w[R];
     int4 qi[NE / 4];
@@ -344,7 +347,7 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
         col = next;
     }
     if (npass > 0) pass(col, col, std::false_type{});
-    if constexpr (NORMS) block_sum2<NT>(num, den, reinterpret_cast<float2*>(smem), partial + blockIdx.x);
+    if constexpr (NORMS) block_sum2<NT>(num, den, reinterpret_cast<float2*>(smem), reinterpret_cast<float2*>(grp->partial) + blockIdx.x);
 }
 
 #define LSP_LDS_AS __attribute__((address_space(3)))
@@ -388,7 +391,7 @@ template <int N, typename F> __device__ __forceinline__ void every(F&& f) { ever
 
 enum WideForm { kPlain, kTwo, kDeep };
 template <typename D, int G, int LP, int DD, bool BIG, int NT, bool NORMS, WideForm FORM>
-__global__ __launch_bounds__(NT, FORM == kDeep ? 2 : 4) void k_decompress_wide(const ApplyGroup grp, int r, float2* __restrict__ partial) {
+__global__ __launch_bounds__(NT, FORM == kDeep ? 2 : 4) void k_decompress_wide(const ApplyGroup) {
     extern __shared__ __align__(16) uint8_t smem[];
     constexpr int CPT = DD == 16 || D::size == 4 ? 1 : 2;                           // columns whose entries of Q a thread holds
     constexpr int PR = 4 * LP;                                      // rows of a plane of units
@@ -403,15 +406,18 @@ __global__ __launch_bounds__(NT, FORM == kDeep ? 2 : 4) void k_decompress_wide(c
     // 44.3 and 42.5; bias pass 4096 x 16384, r = 1024, d = 16, bf16 95 and 87).  16 bits at d = 16 are bound by the reads themselves: 4096 x 16384 103 and 104.5.
     constexpr bool AHEAD = TWO && !(LP == 4 && DD == 16 && D::size == 2 && !NORMS);
     typedef uint32_t Vec __attribute__((ext_vector_type(VW)));
-    const int prob = group_find(grp.first, grp.count, (int)blockIdx.x);
-    const int unit = (int)blockIdx.x - grp.first[prob], parts = grp.parts[prob];
+    const auto* grp = group_args<ApplyGroup>();
+    const auto pick = pick_problem(grp, grp->first, (int)blockIdx.x);
+    const ApplyProblem& pr = pick.p;
+    const int r = pick.r;
+    const int unit = (int)blockIdx.x - pr.first, parts = pr.parts;
     const int block = parts > 1 ? unit / parts : unit, part = unit - block * parts;
-    const float* __restrict__ S = grp.S[prob];
-    const int32_t* __restrict__ P_idx = grp.P_idx[prob];
-    const float* __restrict__ P_val = grp.P_val[prob];
-    const int32_t* __restrict__ Q_idx = grp.Q_idx[prob];
-    const float* __restrict__ Q_val = grp.Q_val[prob];
-    const int m = grp.m[prob], n = grp.n[prob];
+    const float* __restrict__ S = pr.S;
+    const int32_t* __restrict__ P_idx = pr.P_idx;
+    const float* __restrict__ P_val = pr.P_val;
+    const int32_t* __restrict__ Q_idx = pr.Q_idx;
+    const float* __restrict__ Q_val = pr.Q_val;
+    const int m = pr.m, n = pr.n;
     const int64_t i0 = (int64_t)block * R;
     int2* pent = reinterpret_cast<int2*>(smem + (G > 1 ? G * PLANE : r * (16 * LP)));
 
@@ -424,7 +430,7 @@ __global__ __launch_bounds__(NT, FORM == kDeep ? 2 : 4) void k_decompress_wide(c
     const uint32_t p4 = threadIdx.x & (LP - 1);                     // rows 4 p4 .. of a plane are this thread's
     const uint32_t piece = p4 << 4;
     const int rows = m - i0 < R ? (int)(m - i0) : R;
-    char* const base = static_cast<char*>(grp.W[prob]) + i0 * n * D::size;
+    char* const base = static_cast<char*>(pr.W) + i0 * n * D::size;
     const uint32_t stride = (uint32_t)n * D::size;                  // (host: 16 rows are less than 2^31 bytes)
     const uint32_t lane_off = p4 * 4 * stride + (uint32_t)lane_col * D::size;
     // row t of the thread's four in plane g: what lies behind the matrix's last row is past the buffer's end, and a thread past the last column goes there too
@@ -645,25 +651,28 @@ __global__ __launch_bounds__(NT, FORM == kDeep ? 2 : 4) void k_decompress_wide(c
         }
         if (npass > 0) pass(even, col, col, true, std::false_type{});
     }
-    if constexpr (NORMS) block_sum2<NT>(num, den, reinterpret_cast<float2*>(smem), partial + blockIdx.x);
+    if constexpr (NORMS) block_sum2<NT>(num, den, reinterpret_cast<float2*>(smem), reinterpret_cast<float2*>(grp->partial) + blockIdx.x);
 }
 
 // General kernel: any n and d.  A thread has two columns of a pass: neighbours (PAIR, n even), or columns 64 apart, each
 // loaded and stored by itself.  The entries of Q are taken four at a time for the whole patch (R x 2 sums in registers),
 // the next four in flight; the next pass's first four are asked for before its patch of W, because loads return in order.
 template <typename D, int RG, int PS, int NT, bool PAIR, bool NORMS>
-__global__ __launch_bounds__(NT, (NORMS ? 3 : 4)) void k_decompress_any(const ApplyGroup grp, int r, int d, float2* __restrict__ partial) {
+__global__ __launch_bounds__(NT, (NORMS ? 3 : 4)) void k_decompress_any(const ApplyGroup) {
     extern __shared__ __align__(16) uint8_t smem[];
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
     typedef i32x4 loose_i __attribute__((aligned(4)));
     typedef f32x4 loose_f __attribute__((aligned(4)));
     constexpr int R = 4 * RG;
-    const int prob = group_find(grp.first, grp.count, (int)blockIdx.x);
-    const int unit = (int)blockIdx.x - grp.first[prob], parts = grp.parts[prob];
+    const auto* grp = group_args<ApplyGroup>();
+    const auto pick = pick_problem(grp, grp->first, (int)blockIdx.x);
+    const ApplyProblem& pr = pick.p;
+    const int r = pick.r, d = pick.d;
+    const int unit = (int)blockIdx.x - pr.first, parts = pr.parts;
     const int block = parts > 1 ? unit / parts : unit, part = unit - block * parts;
-    const int32_t* __restrict__ Q_idx = grp.Q_idx[prob];
-    const float* __restrict__ Q_val = grp.Q_val[prob];
-    const int m = grp.m[prob], n = grp.n[prob];
+    const int32_t* __restrict__ Q_idx = pr.Q_idx;
+    const float* __restrict__ Q_val = pr.Q_val;
+    const int m = pr.m, n = pr.n;
     const int64_t i0 = (int64_t)block * R;
     const f32x4* Us4 = reinterpret_cast<const f32x4*>(smem);
     constexpr int step = NT * 2;
@@ -672,7 +681,7 @@ __global__ __launch_bounds__(NT, (NORMS ? 3 : 4)) void k_decompress_any(const Ap
     auto pass_col = [&](int p) -> int { return passes.at(p) * step; };   // the pass's first column
     const int lane_col = PAIR ? (int)threadIdx.x * 2 : ((int)threadIdx.x >> 6) * 128 + ((int)threadIdx.x & 63);
     constexpr int kApart = PAIR ? 1 : kWave;                        // from the first column to the second
-    const RowBlock<D> rows{static_cast<char*>(grp.W[prob]) + i0 * n * D::size, (int64_t)n * D::size, m - i0 < R ? (int)(m - i0) : R, n};
+    const RowBlock<D> rows{static_cast<char*>(pr.W) + i0 * n * D::size, (int64_t)n * D::size, m - i0 < R ? (int)(m - i0) : R, n};
 
     typedef typename std::conditional<PAIR, Pair<D>, typename D::elem>::type Piece;
     constexpr int NP = PAIR ? 1 : 2;
@@ -723,7 +732,7 @@ __global__ __launch_bounds__(NT, (NORMS ? 3 : 4)) void k_decompress_any(const Ap
     int col = pass_col(0);
     load_q(0, col, 0);
     load_w(col);
-    build_u_tile<R, 0, 0, (PS > 16384), NT>(PlanePlace<PS>{smem}, reinterpret_cast<int2*>(smem + RG * PS), grp.S[prob], grp.P_idx[prob], grp.P_val[prob], i0, m, r, d);
+    build_u_tile<R, 0, 0, (PS > 16384), NT>(PlanePlace<PS>{smem}, reinterpret_cast<int2*>(smem + RG * PS), pr.S, pr.P_idx, pr.P_val, i0, m, r, d);
     __syncthreads();
     for (int p = 0; p < npass; ++p) {
 #pragma unroll
@@ -764,7 +773,7 @@ __global__ __launch_bounds__(NT, (NORMS ? 3 : 4)) void k_decompress_any(const Ap
         if (p + 1 < npass) load_w(next);
         col = next;
     }
-    if constexpr (NORMS) block_sum2<NT>(num, den, reinterpret_cast<float2*>(smem), partial + blockIdx.x);
+    if constexpr (NORMS) block_sum2<NT>(num, den, reinterpret_cast<float2*>(smem), reinterpret_cast<float2*>(grp->partial) + blockIdx.x);
 }
 
 // Adds the workgroups' sums in order (in double) and forms the bias:
@@ -803,7 +812,7 @@ constexpr unsigned kResidentDeep = 256;                              // workgrou
 static bool wide_shape(int64_t n, int32_t r) { return r >= 4 && r % 4 == 0 && n % 8 == 0 && n <= 1 << 24; }   // (32-bit offsets inside a plane of rows)
 static bool wide_group(const ApplyGroup& g, int32_t r) {
     bool wide = true;
-    for (int p = 0; p < g.count; ++p) wide = wide && wide_shape(g.n[p], r);
+    for (int p = 0; p < g.count; ++p) wide = wide && wide_shape(g.p[p].n, r);
     return wide;
 }
 // Small work where k_decompress is ahead all the same (blocks of 16 rows of 512 threads, d <= 8; grid: workgroups, n: the widest matrix).  In a call of one pass nothing covers
@@ -823,26 +832,26 @@ static bool narrow_call(unsigned grid, int32_t n, int32_t r, int32_t d, int elem
 }
 
 template <typename D, int RG, int PS, int NT, bool NORMS = false>
-static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipStream_t st, float2* partial = nullptr) {
+static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipStream_t st, float* partial = nullptr) {
     // widest matrices first: workgroups are started in index order as CUs fall free, and a workgroup's
     // run time grows with n, so the long ones should not be the last to start
     for (int a = 1; a < g.count; ++a)
-        for (int b = a; b > 0 && g.n[b] > g.n[b - 1]; --b) {
-            std::swap(g.W[b], g.W[b - 1]); std::swap(g.S[b], g.S[b - 1]); std::swap(g.P_idx[b], g.P_idx[b - 1]);
-            std::swap(g.P_val[b], g.P_val[b - 1]); std::swap(g.Q_idx[b], g.Q_idx[b - 1]); std::swap(g.Q_val[b], g.Q_val[b - 1]);
-            std::swap(g.m[b], g.m[b - 1]); std::swap(g.n[b], g.n[b - 1]);
-        }
+        for (int b = a; b > 0 && g.p[b].n > g.p[b - 1].n; --b) std::swap(g.p[b], g.p[b - 1]);
     bool fast = true, pair = true;
-    g.first[0] = 0;
-    for (int p = 0; p < g.count; ++p) {                             // about `passes` passes for every workgroup
-        fast = fast && fast_shape(g.n[p], d);
-        pair = pair && g.n[p] % 2 == 0;
-        g.parts[p] = (int32_t)((((int64_t)g.n[p] + 2 * NT - 1) / (2 * NT) + passes - 1) / passes);
-        g.first[p + 1] = g.first[p] + (g.m[p] + RG * 4 - 1) / (RG * 4) * g.parts[p];
+    g.r = r; g.d = d; g.partial = partial;
+    unsigned grid = 0;
+    for (int p = 0; p < kMaxGroup; ++p) {                           // about `passes` passes for every workgroup
+        ApplyProblem& x = g.p[p];
+        g.first[p] = INT32_MAX;
+        if (p >= g.count) continue;
+        fast = fast && fast_shape(x.n, d);
+        pair = pair && x.n % 2 == 0;
+        x.parts = (int32_t)((((int64_t)x.n + 2 * NT - 1) / (2 * NT) + passes - 1) / passes);
+        g.first[p] = x.first = (int32_t)grid;
+        grid += (unsigned)((x.m + RG * 4 - 1) / (RG * 4) * x.parts);
     }
-    const unsigned grid = (unsigned)g.first[g.count];
     hipError_t e;
-    const bool narrow = RG == 4 && NT == 512 && d <= 8 && narrow_call(grid, g.n[0], r, d, D::size, NORMS);   // (the matrices are in the order of their widths)
+    const bool narrow = RG == 4 && NT == 512 && d <= 8 && narrow_call(grid, g.p[0].n, r, d, D::size, NORMS);   // (the matrices are in the order of their widths)
     if (fast && !narrow && wide_group(g, r)) {
         constexpr int LP = RG == 2 ? 2 : 4, G = RG == 2 ? 1 : RG / 4;
 #define LSP_LAUNCH_WIDE(DDV, FORM)                                                                             \
@@ -852,7 +861,7 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
         constexpr size_t units = G > 1 ? (size_t)RG * PS : (size_t)(PS > 16384 ? 2048 : 1024) * 16 * LP;       \
         if ((e = allow_dynamic_lds<kern, units + ents>()) != hipSuccess) return e;                             \
         const size_t lds = (G > 1 ? units : (size_t)r * 16 * LP) + ents;                                       \
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, g, (int)r, partial);                           \
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, g);                           \
         return hipGetLastError();                                                                              \
     } while (0)
 // (8 rows at d = 16 and r <= 1024: at most 128 blocks of 16 rows, so the grid is never beyond that of the deep form)
@@ -861,7 +870,7 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
         if constexpr (G == 1 && NT == 512)                                                                     \
             if (grid <= kResidentDeep) LSP_LAUNCH_WIDE(DDV, kDeep);                                            \
         if constexpr (G == 1 && NT == 512 && DDV <= 8 && D::size == 2 && !NORMS)                               \
-            if (grid < 512 && g.n[0] <= 2048) LSP_LAUNCH_WIDE(DDV, kPlain);                                    \
+            if (grid < 512 && g.p[0].n <= 2048) LSP_LAUNCH_WIDE(DDV, kPlain);                                    \
         if constexpr ((D::size == 2 || DDV == 16 || NORMS) && (LP == 4 || PS > 16384)) LSP_LAUNCH_WIDE(DDV, (G == 1 ? kTwo : kPlain));   \
     } while (0)
         if constexpr (LP == 4) {
@@ -879,7 +888,7 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
         constexpr auto kern = k_decompress<D, RG, DDV, PS, NT, NORMS>;                                         \
         constexpr size_t lds = (size_t)RG * PS + (size_t)RG * 4 * DDV * sizeof(int2);                          \
         if ((e = allow_dynamic_lds<kern, lds>()) != hipSuccess) return e;                                        \
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, g, (int)r, partial);                            \
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, g);                            \
         return hipGetLastError();                                                                              \
     } while (0)
     if (fast && d == 2) LSP_LAUNCH_FAST(2);
@@ -891,7 +900,7 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
     do {                                                                                                       \
         constexpr auto kern = k_decompress_any<D, RG, PS, NT, PAIRV, NORMS>;                                   \
         if ((e = allow_dynamic_lds<kern, (size_t)RG * PS + (size_t)RG * 4 * LSP_MAX_D * sizeof(int2)>()) != hipSuccess) return e; \
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), (size_t)RG * PS + (size_t)RG * 4 * d * sizeof(int2), st, g, (int)r, (int)d, partial); \
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), (size_t)RG * PS + (size_t)RG * 4 * d * sizeof(int2), st, g); \
         return hipGetLastError();                                                                              \
     } while (0)
         if (pair) LSP_LAUNCH_ANY(true);
@@ -944,9 +953,9 @@ static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_
     int64_t blocks = 0, widest = 0;
     bool fast = true;
     for (int p = 0; p < g.count; ++p) {
-        blocks += (g.m[p] + 15) / 16;
-        widest = g.n[p] > widest ? g.n[p] : widest;
-        fast = fast && fast_shape(g.n[p], d);
+        blocks += (g.p[p].m + 15) / 16;
+        widest = g.p[p].n > widest ? g.p[p].n : widest;
+        fast = fast && fast_shape(g.p[p].n, d);
     }
     if (r > 1024) return launch_d<D, 2, 32768, 512>(g, r, d, kAll, st);
     const bool wide = wide_group(g, r);
@@ -971,10 +980,10 @@ int64_t bias_blocks(int64_t m, int64_t n, int32_t r, int32_t d) {
 }
 
 template <typename D>
-static hipError_t launch_bias_shape(ApplyGroup& g, int32_t r, int32_t d, float2* partial, float* out, hipStream_t st) {
+static hipError_t launch_bias_shape(ApplyGroup& g, int32_t r, int32_t d, float* partial, float* out, hipStream_t st) {
     constexpr int kAll = 1 << 30;
-    const int64_t m = g.m[0];
-    const bool eight = bias_eight_rows(m, g.n[0], r, d, D::size);
+    const int64_t m = g.p[0].m;
+    const bool eight = bias_eight_rows(m, g.p[0].n, r, d, D::size);
     hipError_t e;
     if (r > 1024)   e = launch_d<D, 2, 32768, 512, true>(g, r, d, kAll, st, partial);
     else if (eight) e = r <= 256 ? launch_d<D, 2, 4096, 512, true>(g, r, d, kAll, st, partial) : r <= 512 ? launch_d<D, 2, 8192, 512, true>(g, r, d, kAll, st, partial)
@@ -982,16 +991,15 @@ static hipError_t launch_bias_shape(ApplyGroup& g, int32_t r, int32_t d, float2*
     else            e = r <= 256 ? launch_d<D, 4, 4096, 512, true>(g, r, d, kAll, st, partial) : r <= 512 ? launch_d<D, 4, 8192, 512, true>(g, r, d, kAll, st, partial)
                                                                                                      : launch_d<D, 4, 16384, 512, true>(g, r, d, kAll, st, partial);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bias_finish, dim3(1), dim3(256), 0, st, partial, (int)(eight ? (m + 7) / 8 : (m + 15) / 16), out);
+    hipLaunchKernelGGL(k_bias_finish, dim3(1), dim3(256), 0, st, reinterpret_cast<float2*>(partial), (int)(eight ? (m + 7) / 8 : (m + 15) / 16), out);
     return hipGetLastError();
 }
 
 hipError_t launch_bias(ApplyGroup& g, int32_t r, int32_t d, lsp_dtype dtype, float* partial, float* out, hipStream_t st) {
-    float2* part = reinterpret_cast<float2*>(partial);
     switch (dtype) {
-        case LSP_F32:  return launch_bias_shape<F32>(g, r, d, part, out, st);
-        case LSP_F16:  return launch_bias_shape<F16>(g, r, d, part, out, st);
-        default:       return launch_bias_shape<BF16>(g, r, d, part, out, st);
+        case LSP_F32:  return launch_bias_shape<F32>(g, r, d, partial, out, st);
+        case LSP_F16:  return launch_bias_shape<F16>(g, r, d, partial, out, st);
+        default:       return launch_bias_shape<BF16>(g, r, d, partial, out, st);
     }
 }
 

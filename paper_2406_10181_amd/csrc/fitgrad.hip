@@ -17,11 +17,9 @@
 #include <cstring>
 #include <type_traits>
 
-#include "lsp_internal.h"
+#include "compress_common.h"
 
 namespace lsp {
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // Y[j][a] = sum over the entries (i, v) of row a of P^T of v * G[i][j]: a wave has one piece of a row of P^T and a tile of
 // 256 columns; a lane loads 16 bytes of a row of G, and with 16-bit storage the two halves of the wave take every
@@ -45,8 +43,8 @@ __global__ __launch_bounds__(kThreadsY) void k_gather_rows(const typename D::ele
     __shared__ __align__(16) float part[kWavesY][kLead + kTileY];
     typedef typename D::elem Piece __attribute__((ext_vector_type(VEC)));
     typedef Piece Loose __attribute__((aligned(D::size)));
-    PlanHeaderPtr H = as_const<PlanHeader>(plan);
-    if (H->magic != kPlanMagic || H->m != m || H->n != n || H->r != r || H->d != d) return;
+    const LoadedHeader H = load_header(plan);
+    if (!plan_matches(H, m, n, r, d, false)) return;
     const int seq = blockIdx.x / kXcds;                             // position in this XCD's sequence: items fastest
     const int item0 = (seq % item_groups) * kWavesY, tile = (seq / item_groups) * kXcds + blockIdx.x % kXcds;
     const int nitems = H->p_nitems;
@@ -221,7 +219,7 @@ hipError_t launch_fitgrad(const void* G, const uint8_t* plan, const int32_t* P_i
     // reaches every output)
     CompressGroup g;
     memset(&g, 0, sizeof(g));
-    g.count = 1; g.G[0] = G; g.plan[0] = plan; g.T[0] = T; g.S[0] = S; g.m[0] = (int32_t)m; g.n[0] = (int32_t)n;
+    g.count = 1; g.p[0].G = G; g.p[0].plan = plan; g.p[0].T = T; g.p[0].S = S; g.p[0].m = (int32_t)m; g.p[0].n = (int32_t)n;
     if ((e = launch_compress_planned(g, r, d, dtype, st)) != hipSuccess) return e;
     // C_P = P^T P, C_Q = Q^T Q
     GramBatch grams{};

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "lsp.h"
 
@@ -177,60 +178,105 @@ int build_plan_host(const int32_t* P_idx, const float* P_val, const int32_t* Q_i
 
 // ------------------------------------------------------------------------------------------
 // Groups: several independent problems (same r, d, dtype) served by one launch per kernel, so that
-// workgroups of different matrices fill the CUs together.  Passed to the kernels by value.
-// first[p] .. first[p+1] are the workgroups of problem p.
+// workgroups of different matrices fill the CUs together.  Passed to the kernels by value, as their first argument.
+// A kernel's first work is a chain of dependent scalar loads, each a trip to memory, so everything that it needs to know of a problem is one record of 64
+// bytes, and what is the same for all lies before the first of them: a call of one problem has it all from one trip, a group from two.  (One array per
+// field took four to ten trips, which were 0.7 to 1.7 us of every launch.)
 // ------------------------------------------------------------------------------------------
 constexpr int kMaxGroup = LSP_MAX_GROUP;
+struct CompressProblem {
+    const void*    G;
+    const uint8_t* plan;
+    float*         T;
+    float*         S;
+    int32_t        m, n;
+    int32_t        first_gq, wgs_gq;             // workgroups of the T = G Q kernel (bf16: row blocks): the first, and how many
+    int32_t        blocks_gq;                    // row blocks of each of them
+    int32_t        first_pt;                     // first workgroup of the S = P^T T kernel
+    int32_t        pad[2];
+};
 struct CompressGroup {
-    const void*    G[kMaxGroup];
-    const uint8_t* plan[kMaxGroup];
-    float*         T[kMaxGroup];
-    float*         S[kMaxGroup];
-    int32_t        m[kMaxGroup], n[kMaxGroup];
-    int32_t        first_gq[kMaxGroup + 1];      // workgroups of the T = G Q kernel (bf16: row blocks)
-    int32_t        blocks_gq[kMaxGroup];         // row blocks of each of them
-    int32_t        first_pt[kMaxGroup + 1];      // workgroups of the S = P^T T kernel
-    int32_t        count;
+    int32_t         count, r, d;
+    int32_t         blocks;                      // all row blocks (bf16)
+    int32_t         quads;                       // column quads of a stripe (k_compress_pt8), stripes (k_compress_pt)
+    int32_t         tiles;                       // whether kernel A of this call walks the tiles
+    int32_t         pad[10];
+    CompressProblem p[kMaxGroup];
+    int32_t         first_gq[kMaxGroup], first_pt[kMaxGroup];   // those of the problems once more; past the last problem INT32_MAX
+};
+struct ApplyProblem {
+    void*          W;
+    const float*   S;
+    const int32_t* P_idx;
+    const float*   P_val;
+    const int32_t* Q_idx;
+    const float*   Q_val;
+    int32_t        m, n;
+    int32_t        first;                        // first workgroup
+    int32_t        parts;                        // workgroups that share a row block
 };
 struct ApplyGroup {
-    void*          W[kMaxGroup];
-    const float*   S[kMaxGroup];
-    const int32_t* P_idx[kMaxGroup];
-    const float*   P_val[kMaxGroup];
-    const int32_t* Q_idx[kMaxGroup];
-    const float*   Q_val[kMaxGroup];
-    int32_t        m[kMaxGroup], n[kMaxGroup];
-    int32_t        first[kMaxGroup + 1];
-    int32_t        parts[kMaxGroup];             // workgroups that share a row block
-    int32_t        count;
+    int32_t      count, r, d;
+    int32_t      pad0[5];
+    float*       partial;                        // bias: a pair of sums for every workgroup
+    int32_t      pad[6];
+    ApplyProblem p[kMaxGroup];
+    int32_t      first[kMaxGroup];               // those of the problems once more; past the last problem INT32_MAX
 };
+static_assert(kMaxGroup == 16 && sizeof(CompressProblem) == 64 && sizeof(ApplyProblem) == 64 && offsetof(CompressGroup, p) == 64 && offsetof(ApplyGroup, p) == 64,
+              "records of 64 bytes, loaded whole");
 
 #if defined(__HIPCC__)
-// The problem that owns workgroup `block`, picked with compile-time indices only: indexing the
-// by-value group with a run-time index would make the compiler copy it to scratch memory and turn
-// every address derived from it into a per-lane (vector) value, so that the small uniform loads of
-// the kernels (plan header, segment table) would go through the vector memory path and wait for
-// all the data loads in flight.  Everything returned is wave-uniform and lives in scalar registers.
-struct CompressProblem { const void* G; const uint8_t* plan; float* T; float* S; int32_t m, n, block_gq, nblocks_gq, blocks_gq, block_pt; };
-__device__ __forceinline__ CompressProblem group_pick(const CompressGroup& g, int block, bool kernel_b) {
-    CompressProblem o{g.G[0], g.plan[0], g.T[0], g.S[0], g.m[0], g.n[0], block, g.first_gq[1], g.blocks_gq[0], block};
-#pragma unroll
-    for (int p = 1; p < kMaxGroup; ++p) {
-        const bool hit = p < g.count && block >= (kernel_b ? g.first_pt[p] : g.first_gq[p]);
-        if (hit) {
-            o.G = g.G[p]; o.plan = g.plan[p]; o.T = g.T[p]; o.S = g.S[p]; o.m = g.m[p]; o.n = g.n[p];
-            o.blocks_gq = g.blocks_gq[p]; o.block_gq = block - g.first_gq[p]; o.nblocks_gq = g.first_gq[p + 1] - g.first_gq[p];
-            o.block_pt = block - g.first_pt[p];
-        }
-    }
-    return o;
+// Read-only tables (kernel arguments; the plan's header, segment lengths, column tables) are read through the
+// constant address space: the kernels never write them, and a uniform load from that address
+// space is a scalar load, which does not share the counter (and the waits) of the vector loads
+// that stream G and the plan rows.
+#define LSP_CONST_AS __attribute__((address_space(4)))
+template <typename T> __device__ __forceinline__ const LSP_CONST_AS T* as_const(const void* p) {
+    return (const LSP_CONST_AS T*)(uintptr_t)p;
 }
-// index of the problem that owns workgroup `block` (uniform; count <= kMaxGroup); the decompress
-// kernels use this run-time index: they have no small uniform loads to protect, and measured faster
-__device__ __forceinline__ int group_find(const int32_t* first, int count, int block) {
-    int p = 0;
-    while (p + 1 < count && block >= first[p + 1]) ++p;
-    return p;
+#define LSP_GLOBAL_AS __attribute__((address_space(1)))               // (of addresses that come out of memory the compiler would not know it)
+template <typename T> __device__ __forceinline__ T* global_pointer(T* p) { return (T*)(T LSP_GLOBAL_AS*)(uintptr_t)p; }
+// Scalar loads that are waited for together, and not where each is first used: one trip to memory.
+typedef uint32_t words16 __attribute__((ext_vector_type(16)));
+typedef uint32_t words8 __attribute__((ext_vector_type(8)));
+typedef uint32_t words4 __attribute__((ext_vector_type(4)));
+typedef uint32_t words2 __attribute__((ext_vector_type(2)));
+template <typename V> __device__ __forceinline__ V scalar_load(const LSP_CONST_AS void* p, int word = 0) {
+    return *(const LSP_CONST_AS V*)((const LSP_CONST_AS uint32_t*)p + word);
+}
+template <typename V> __device__ __forceinline__ void arrived(V& x) { asm volatile("" : "+s"(x)); }
+template <typename V, typename... W> __device__ __forceinline__ void arrived(V& x, W&... rest) { arrived(x); arrived(rest...); }
+// A kernel's first argument
+template <typename Group> __device__ __forceinline__ const LSP_CONST_AS Group* group_args() {
+    return (const LSP_CONST_AS Group*)__builtin_amdgcn_kernarg_segment_ptr();
+}
+__device__ __forceinline__ void know_pointers(CompressProblem& p) {
+    p.G = global_pointer(p.G); p.plan = global_pointer(p.plan); p.T = global_pointer(p.T); p.S = global_pointer(p.S);
+}
+__device__ __forceinline__ void know_pointers(ApplyProblem& p) {
+    p.W = global_pointer(p.W); p.S = global_pointer(p.S);
+    p.P_idx = global_pointer(p.P_idx); p.P_val = global_pointer(p.P_val); p.Q_idx = global_pointer(p.Q_idx); p.Q_val = global_pointer(p.Q_val);
+}
+// The group's first words, and the problem that owns workgroup (or row block) `block`; first: where each problem begins.  Uniform, and in scalar registers.
+template <typename Problem> struct Picked { int32_t count, r, d, blocks, quads, tiles; Problem p; };
+template <typename Group> __device__ __forceinline__ auto pick_problem(const LSP_CONST_AS Group* g, const LSP_CONST_AS int32_t (&first)[kMaxGroup], int block) {
+    words8 head = scalar_load<words8>(g);
+    words16 record = scalar_load<words16>(&g->p[0]);
+    arrived(head, record);
+    if ((int)head[0] > 1) {
+        typedef int32_t i16 __attribute__((ext_vector_type(16)));
+        const i16 f = scalar_load<i16>(&first[0]);
+        int k = 0;
+#pragma unroll
+        for (int p = 1; p < kMaxGroup; ++p) k += block >= f[p] ? 1 : 0;
+        record = scalar_load<words16>(&g->p[k]);
+    }
+    Picked<std::remove_cv_t<std::remove_reference_t<decltype(Group::p[0])>>> out;
+    out.count = (int)head[0]; out.r = (int)head[1]; out.d = (int)head[2]; out.blocks = (int)head[3]; out.quads = (int)head[4]; out.tiles = (int)head[5];
+    __builtin_memcpy(&out.p, &record, 64);
+    know_pointers(out.p);
+    return out;
 }
 #endif
 
@@ -332,15 +378,23 @@ template <typename V> __device__ __forceinline__ V stream_load(const V* p) {
     return out;
 }
 
-// Read-only tables of the plan (header, segment lengths, column tables) are read through the
-// constant address space: the kernels never write the plan, and a uniform load from that address
-// space is a scalar load, which does not share the counter (and the waits) of the vector loads
-// that stream G and the plan rows.
-#define LSP_CONST_AS __attribute__((address_space(4)))
-template <typename T> __device__ __forceinline__ const LSP_CONST_AS T* as_const(const void* p) {
-    return (const LSP_CONST_AS T*)(uintptr_t)p;
-}
 typedef const LSP_CONST_AS PlanHeader* PlanHeaderPtr;
+// A plan's header, loaded at once.  (The offsets in it are followed only when plan_matches says that it is this problem's.)
+struct LoadedHeader {
+    PlanHeader h;
+    __device__ __forceinline__ const PlanHeader* operator->() const { return &h; }
+};
+__device__ __forceinline__ LoadedHeader load_header(const uint8_t* plan) {
+    const auto* p = as_const<uint32_t>(plan);
+    words16 a = scalar_load<words16>(p), b = scalar_load<words16>(p, 16), c = scalar_load<words16>(p, 32);
+    words4 e = scalar_load<words4>(p, 48);
+    words2 f = scalar_load<words2>(p, 52);
+    arrived(a, b, c, e, f);
+    LoadedHeader H;
+    char* o = reinterpret_cast<char*>(&H.h);
+    __builtin_memcpy(o, &a, 64); __builtin_memcpy(o + 64, &b, 64); __builtin_memcpy(o + 128, &c, 64); __builtin_memcpy(o + 192, &e, 16); __builtin_memcpy(o + 208, &f, 8);
+    return H;
+}
 
 template <typename D> __device__ __forceinline__ float widen(typename D::elem x);
 template <> __device__ __forceinline__ float widen<F32>(float x) { return x; }

@@ -66,8 +66,8 @@ int lsp_compress_planned_static(const void* G, const void* plan, int64_t m, int6
     lsp::CompressGroup g;
     std::memset(&g, 0, sizeof(g));
     g.count = 1;
-    g.G[0] = G; g.plan[0] = static_cast<const uint8_t*>(plan); g.T[0] = static_cast<float*>(T); g.S[0] = S;
-    g.m[0] = (int32_t)m; g.n[0] = (int32_t)n;
+    g.p[0].G = G; g.p[0].plan = static_cast<const uint8_t*>(plan); g.p[0].T = static_cast<float*>(T); g.p[0].S = S;
+    g.p[0].m = (int32_t)m; g.p[0].n = (int32_t)n;
     e = lsp::launch_compress_planned(g, r, d, dtype, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? LSP_OK : lsp::note_hip_error(e);
 }

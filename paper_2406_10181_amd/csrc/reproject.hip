@@ -120,7 +120,7 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(const GramBatch batch, in
     __syncthreads();
     for (int q = threadIdx.x; q < mine; q += kGramThreads) P.C[(int64_t)a0 * r + q] = acc[q];
     if (clear.p) {
-        PlanHeaderPtr H = as_const<PlanHeader>(clear.plan);
+        const auto* H = as_const<PlanHeader>(clear.plan);
         if (H->magic == kPlanMagic && H->p_any_split)
             for (int64_t k = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kGramThreads + threadIdx.x; k < clear.count;
                  k += (int64_t)gridDim.x * gridDim.y * kGramThreads)
