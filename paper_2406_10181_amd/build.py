@@ -16,7 +16,8 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "liblsp_hip.so")
 CALL_MODULE = os.path.join(PKG, "_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 OBJDIR = os.path.join(PKG, "_build")
-SOURCES = ["compress_mm.hip", "compress_gq_bf16.hip", "compress_gq_f16.hip", "compress_gq_f32.hip", "plan_device.hip", "decompress.hip",
+SOURCES = ["compress_mm.hip", "compress_gq_bf16.hip", "compress_gq_f16.hip", "compress_gq_f32.hip", "plan_device.hip",
+           "decompress_bf16.hip", "decompress_f16.hip", "decompress_f32.hip", "decompress_loose_bf16.hip", "decompress_loose_f16.hip", "decompress_loose_f32.hip", "decompress.hip",
            "compress.hip", "api.cpp", "plan.cpp", "reproject.hip", "dense.hip", "fitgrad.hip", "noalloc.hip", "probe.hip"]
 
 HIPCC_FLAGS = [
