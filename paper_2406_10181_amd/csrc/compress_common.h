@@ -16,10 +16,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // plan at all) must not be walked.  Kernel A then fills S with NaN, which is how the caller sees
 // the mistake (or takes the scatter form, raw calls), and kernel B does nothing; all kernels exit normally.
 // tiles: kernel A of this call walks the tiles, so there must be some; kernel B asks for the same, or it would put what lies in T in the place of the NaN.
-// (One condition and no chain of them: each would wait for the one before.)
-__device__ __forceinline__ bool same_problem(uint32_t magic, int32_t hm, int32_t hn, int32_t hr, int32_t hd, int m, int n, int r, int d) {
-    return ((magic ^ kPlanMagic) | (uint32_t)(hm ^ m) | (uint32_t)(hn ^ n) | (uint32_t)(hr ^ r) | (uint32_t)(hd ^ d)) == 0;
-}
 __device__ __forceinline__ bool plan_matches(const LoadedHeader& H, int m, int n, int r, int d, bool tiles) {
     const uint32_t steps = tiles ? H->m_total_steps : 1u;
     return same_problem(H->magic, H->m, H->n, H->r, H->d, m, n, r, d) && steps != 0;

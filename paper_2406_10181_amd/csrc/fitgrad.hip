@@ -124,20 +124,31 @@ __global__ __launch_bounds__(kThreadsY) void k_gather_rows(const typename D::ele
 // together, so that their loads overlap; lane k' < d also carries the k'-th term of the first sum (d <= 64).  The eight
 // sums meet in ten lane exchanges: each of the first three steps also halves the number of sums a lane has.
 // (4096 x 4096, r = 512, d = 8: 33 us with a kernel of its own for each side and a merge of partial lists, now 20.)
-struct GradSide { const float* X; const float* D; const float* M; const int32_t* idx; const float* val; float* g; int32_t rows; };
-__global__ __launch_bounds__(256) void k_grad(const GradSide left, const GradSide right, int left_blocks, int r, int d) {
+struct GradSide { const float* X; const float* D; const float* M; const int32_t* idx; const float* val; float* g; int32_t rows; int32_t pad[3]; };
+struct GradArgs { int32_t left_blocks, r, d, pad[13]; GradSide left, right; };
+static_assert(sizeof(GradSide) == 64 && sizeof(GradArgs) == 192, "records of 64 bytes, loaded whole");
+__global__ __launch_bounds__(256) void k_grad(const GradArgs) {
     typedef f32x4 loose __attribute__((aligned(4)));
     constexpr int KC = 8;
+    const auto* args = group_args<GradArgs>();
+    words4 head = scalar_load<words4>(args);
+    words16 left = scalar_load<words16>(&args->left), right = scalar_load<words16>(&args->right);
+    arrived(head, left, right);
+    const int left_blocks = (int)head[0], r = (int)head[1], d = (int)head[2];
     const bool is_left = (int)blockIdx.x < left_blocks;
-    const GradSide& s = is_left ? left : right;
+    GradSide s;
+    const words16 side = is_left ? left : right;
+    __builtin_memcpy(&s, &side, 64);
+    s.X = global_pointer(s.X); s.D = global_pointer(s.D); s.M = global_pointer(s.M); s.idx = global_pointer(s.idx); s.val = global_pointer(s.val); s.g = global_pointer(s.g);
     const int lane = threadIdx.x & 63;
     const int64_t i = (int64_t)__builtin_amdgcn_readfirstlane(((int)blockIdx.x - (is_left ? 0 : left_blocks)) * 4 + (int)(threadIdx.x >> 6));
     if (i >= s.rows) return;
     const float* __restrict__ X = s.X + i * r;
     const float* __restrict__ Dm = s.D;
     const bool mine = lane < d;
-    const float pv = mine ? s.val[i * d + lane] : 0.0f;
-    const int my_idx = mine ? s.idx[i * d + lane] : 0;
+    const int64_t own = i * d + min(lane, d - 1);                   // (every lane reads: a load that some lanes leave out would be waited for where it stands)
+    const float pv = s.val[own];
+    const int own_idx = s.idx[own], my_idx = mine ? own_idx : 0;
     const float* __restrict__ Mrow = s.M + (int64_t)my_idx * r;
     const int quads = r >> 2;
     for (int k0 = 0; k0 < d; k0 += KC) {
@@ -147,8 +158,10 @@ __global__ __launch_bounds__(256) void k_grad(const GradSide left, const GradSid
         for (int q = 0; q < KC; ++q) {
             const int a = __builtin_amdgcn_readlane(my_idx, min(k0 + q, d - 1));
             row[q] = (int64_t)a * r;
-            acc[q] = mine ? pv * Mrow[a] : 0.0f;
+            acc[q] = Mrow[a];
         }
+#pragma unroll
+        for (int q = 0; q < KC; ++q) acc[q] = mine ? pv * acc[q] : 0.0f;
 #pragma unroll 2
         for (int b4 = lane; b4 < quads; b4 += 64) {
             const f32x4 x = *reinterpret_cast<const loose*>(X + b4 * 4);
@@ -223,17 +236,17 @@ hipError_t launch_fitgrad(const void* G, const uint8_t* plan, const int32_t* P_i
     if ((e = launch_compress_planned(g, r, d, dtype, st)) != hipSuccess) return e;
     // C_P = P^T P, C_Q = Q^T Q
     GramBatch grams{};
-    grams.p[0] = GramPair{P_idx, P_val, P_idx, P_val, m, CP};
-    grams.p[1] = GramPair{Q_idx, Q_val, Q_idx, Q_val, n, CQ};
+    grams.p[0] = GramPair{P_idx, P_val, P_idx, P_val, m, CP, {}};
+    grams.p[1] = GramPair{Q_idx, Q_val, Q_idx, Q_val, n, CQ, {}};
     const GramClear clear{plan, Y, (int64_t)r * n};                  // (pieces of rows of P^T add up in Y)
     if ((e = launch_gram(grams, 2, d, r, &clear, st)) != hipSuccess) return e;
     // the r x r chain: two launches of independent products
     GemmBatch first{}, second{};
-    first.p[0] = GemmProblem{S, CQ, S1, nullptr, 0.0f, 0, nullptr};                                               // S1 = S C_Q
-    first.p[1] = GemmProblem{CP, S, X, nullptr, 0.0f, 0, nullptr};                                                // X  = C_P S
-    second.p[0] = GemmProblem{CP, S1, Dm, S, -2.0f, 0, Dt};                                                  // D  = C_P S1 - 2 S
-    second.p[1] = GemmProblem{S1, S, M1, nullptr, 0.0f, kGemmTB, nullptr};                                        // M1 = S1 S^T
-    second.p[2] = GemmProblem{S, X, M2, nullptr, 0.0f, kGemmTA, nullptr};                                         // M2 = S^T X
+    first.p[0] = GemmProblem{S, CQ, S1, nullptr, 0.0f, 0, nullptr, {}};                                               // S1 = S C_Q
+    first.p[1] = GemmProblem{CP, S, X, nullptr, 0.0f, 0, nullptr, {}};                                                // X  = C_P S
+    second.p[0] = GemmProblem{CP, S1, Dm, S, -2.0f, 0, Dt, {}};                                                  // D  = C_P S1 - 2 S
+    second.p[1] = GemmProblem{S1, S, M1, nullptr, 0.0f, kGemmTB, nullptr, {}};                                        // M1 = S1 S^T
+    second.p[2] = GemmProblem{S, X, M2, nullptr, 0.0f, kGemmTA, nullptr, {}};                                         // M2 = S^T X
     if ((e = launch_gemm_rr_batch(first, 2, r, st)) != hipSuccess) return e;
     if ((e = launch_gemm_rr_batch(second, 3, r, st)) != hipSuccess) return e;
     // Y = G^T P
@@ -243,9 +256,12 @@ hipError_t launch_fitgrad(const void* G, const uint8_t* plan, const int32_t* P_i
         default:       e = launch_gather<BF16>(G, plan, Y, m, n, r, d, st); break;
     }
     if (e != hipSuccess) return e;
-    const GradSide left{T, Dm, M1, P_idx, P_val, gP, (int32_t)m}, right{Y, Dt, M2, Q_idx, Q_val, gQ, (int32_t)n};
     const int left_blocks = (int)((m + 3) / 4), right_blocks = (int)((n + 3) / 4);
-    hipLaunchKernelGGL(k_grad, dim3((unsigned)(left_blocks + right_blocks)), dim3(256), 0, st, left, right, left_blocks, (int)r, (int)d);
+    GradArgs grad{};
+    grad.left_blocks = left_blocks; grad.r = r; grad.d = d;
+    grad.left = GradSide{T, Dm, M1, P_idx, P_val, gP, (int32_t)m, {}};
+    grad.right = GradSide{Y, Dt, M2, Q_idx, Q_val, gQ, (int32_t)n, {}};
+    hipLaunchKernelGGL(k_grad, dim3((unsigned)(left_blocks + right_blocks)), dim3(256), 0, st, grad);
     return hipGetLastError();
 }
 

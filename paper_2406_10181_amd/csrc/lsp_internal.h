@@ -251,6 +251,15 @@ template <typename V, typename... W> __device__ __forceinline__ void arrived(V& 
 template <typename Group> __device__ __forceinline__ const LSP_CONST_AS Group* group_args() {
     return (const LSP_CONST_AS Group*)__builtin_amdgcn_kernarg_segment_ptr();
 }
+// Brings the first N x 64 bytes of a kernel's arguments into the scalar cache in one trip; what is loaded of them later, where it is used, is there.
+template <int N> __device__ __forceinline__ void touch_args() {
+    const auto* p = group_args<uint32_t>();
+    uint32_t x[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) x[k] = p[16 * k];
+#pragma unroll
+    for (int k = 0; k < N; ++k) arrived(x[k]);
+}
 __device__ __forceinline__ void know_pointers(CompressProblem& p) {
     p.G = global_pointer(p.G); p.plan = global_pointer(p.plan); p.T = global_pointer(p.T); p.S = global_pointer(p.S);
 }
@@ -324,12 +333,13 @@ hipError_t launch_plan_build(const int32_t* P_idx, const float* P_val, const int
 // operand (not both), square an operand element by element; E may be null.
 constexpr int kMaxGemmBatch = 3;
 constexpr int kGemmTA = 1, kGemmTB = 2, kGemmSqA = 4, kGemmSqB = 8;
-struct GemmProblem { const float* A; const float* B; float* C; const float* E; float beta; int32_t flags; float* Ct; };   // Ct: a transposed copy of C, may be null
-struct GemmBatch { GemmProblem p[kMaxGemmBatch]; };
+struct GemmProblem { const float* A; const float* B; float* C; const float* E; float beta; int32_t flags; float* Ct; int32_t pad[4]; };   // Ct: a transposed copy of C, may be null
+struct GemmBatch { int32_t r, pad[15]; GemmProblem p[kMaxGemmBatch]; };   // (r: the launcher fills it in)
+static_assert(sizeof(GemmProblem) == 64, "a record, loaded whole");
 hipError_t launch_gemm_rr_batch(const GemmBatch& batch, int count, int32_t r, hipStream_t st);
 // C = L^T R (r x r, overwritten) for two ELL matrices with the same number of rows; one or two independent
 // pairs per launch.
-struct GramPair { const int32_t* L_idx; const float* L_val; const int32_t* R_idx; const float* R_val; int64_t rows; float* C; };
+struct GramPair { const int32_t* L_idx; const float* L_val; const int32_t* R_idx; const float* R_val; int64_t rows; float* C; int32_t pad[4]; };
 struct GramBatch { GramPair p[2]; };
 // `clear` (may be null): floats to set to zero if the plan cuts rows of P^T into pieces.
 struct GramClear { const uint8_t* plan; float* p; int64_t count; };
@@ -394,6 +404,11 @@ __device__ __forceinline__ LoadedHeader load_header(const uint8_t* plan) {
     char* o = reinterpret_cast<char*>(&H.h);
     __builtin_memcpy(o, &a, 64); __builtin_memcpy(o + 64, &b, 64); __builtin_memcpy(o + 128, &c, 64); __builtin_memcpy(o + 192, &e, 16); __builtin_memcpy(o + 208, &f, 8);
     return H;
+}
+
+// Whether a header names this problem.  (One condition and no chain of them: each would wait for the one before.)
+__device__ __forceinline__ bool same_problem(uint32_t magic, int32_t hm, int32_t hn, int32_t hr, int32_t hd, int m, int n, int r, int d) {
+    return ((magic ^ kPlanMagic) | (uint32_t)(hm ^ m) | (uint32_t)(hn ^ n) | (uint32_t)(hr ^ r) | (uint32_t)(hd ^ d)) == 0;
 }
 
 template <typename D> __device__ __forceinline__ float widen(typename D::elem x);

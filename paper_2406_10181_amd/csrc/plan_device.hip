@@ -38,8 +38,8 @@ namespace lsp {
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_plan_refresh(uint8_t* __restrict__ plan, const float* __restrict__ P_val,
                                                       const float* __restrict__ Q_val, int m, int n, int r, int d) {
-    const PlanHeader* H = reinterpret_cast<const PlanHeader*>(plan);
-    if (H->magic != kPlanMagic || H->m != m || H->n != n || H->r != r || H->d != d) return;   // not this problem's plan
+    const LoadedHeader H = load_header(plan);
+    if (!same_problem(H->magic, H->m, H->n, H->r, H->d, m, n, r, d)) return;   // not this problem's plan
     const int64_t nq = (int64_t)H->q_total_rows * kWave / 4, np = (int64_t)m * d, np4 = (np + 3) / 4;
     const int64_t nt = (int64_t)H->m_total_steps * kTileCols;
     uint2* rows = reinterpret_cast<uint2*>(plan + H->off_q_rows);
@@ -54,8 +54,11 @@ __global__ __launch_bounds__(256) void k_plan_refresh(uint8_t* __restrict__ plan
             const uint32_t src[kStepEntries] = {x.x, x.y, x.z, x.w};
             if (src[0] == kNoSource) continue;                       // (a list's entries come first)
             uint16_t parts[kStepEntries][3];
+            float val[kStepEntries];                                 // (loads without a condition, so that they do not wait for one another)
 #pragma unroll
-            for (int e = 0; e < kStepEntries; ++e) value_parts(src[e] != kNoSource ? Q_val[src[e]] : 0.0f, parts[e]);
+            for (int e = 0; e < kStepEntries; ++e) val[e] = Q_val[src[e] != kNoSource ? src[e] : 0u];
+#pragma unroll
+            for (int e = 0; e < kStepEntries; ++e) value_parts(src[e] != kNoSource ? val[e] : 0.0f, parts[e]);
             const int b = (int)(k % kSetCols), h = (int)(k / kSetCols % 2);
             uint16_t* out = msteps + k / kTileCols * kWave * 8 + h * 4;
 #pragma unroll
@@ -66,15 +69,18 @@ __global__ __launch_bounds__(256) void k_plan_refresh(uint8_t* __restrict__ plan
             const uint32_t src[4] = {x.x, x.y, x.z, x.w};
             float val[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) val[e] = src[e] != kNoSource ? Q_val[src[e]] : 0.0f;
+            for (int e = 0; e < 4; ++e) val[e] = Q_val[src[e] != kNoSource ? src[e] : 0u];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (src[e] != kNoSource) rows[(k - nt) * 4 + e].y = __float_as_uint(val[e]);
         } else {
             const int64_t p0 = (k - nt - nq) * 4;
+            uint32_t at[4];
             float val[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) val[e] = p0 + e < np ? P_val[psrc[p0 + e]] : 0.0f;
+            for (int e = 0; e < 4; ++e) at[e] = psrc[p0 + e < np ? p0 + e : np - 1];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) val[e] = P_val[at[e]];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (p0 + e < np) pent[p0 + e].y = __float_as_uint(val[e]);
@@ -163,6 +169,7 @@ __global__ __launch_bounds__(kThreadsSort) void k_plan_sort(uint8_t* __restrict_
                                                             int nchunks, int ptiles, int64_t max_rows) {
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ int32_t s_part[kWavesSort];
+    touch_args<4>();
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int tile = blockIdx.x / kSubTiles, sub = blockIdx.x % kSubTiles;
     if (tile >= nchunks + ptiles) {
@@ -197,7 +204,7 @@ __global__ __launch_bounds__(kThreadsSort) void k_plan_sort(uint8_t* __restrict_
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) {
             const int e = e0 + k * kThreadsSort + tid;
-            b[k] = e < count ? idx[base + e] : 0;
+            b[k] = idx[base + (e < count ? e : count - 1)];
         }
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) {
@@ -242,8 +249,8 @@ __global__ __launch_bounds__(kThreadsSort) void k_plan_sort(uint8_t* __restrict_
     for (int e0 = my_lo + w * run; e0 < min(my_lo + (w + 1) * run, my_hi); e0 += kWave) {
         const int e = e0 + lane;
         const bool live = e < my_hi;
-        int32_t b = live ? idx[base + e] : 0;
-        if (b < 0 || b >= r) b = 0;
+        int32_t b = idx[base + (live ? e : my_hi - 1)];
+        if (!live || b < 0 || b >= r) b = 0;
         uint64_t same = __ballot(live);
         for (int k = 0; k < bits; ++k) {
             const bool bit = (b >> k) & 1;
@@ -278,7 +285,16 @@ __device__ __forceinline__ void deal_p(uint8_t* __restrict__ plan, const PlanLay
         const int a = a0 + tid;
         int32_t len = 0;
         if (a < r)
-            for (int t = 0; t < ptiles; ++t) len += (int32_t)(start[(size_t)t * (r + 1) + a + 1] - start[(size_t)t * (r + 1) + a]);
+            for (int t0 = 0; t0 < ptiles; t0 += 4) {
+                uint32_t lo[4], hi[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint32_t* st = start + (size_t)min(t0 + u, ptiles - 1) * (r + 1) + a;
+                    lo[u] = st[0]; hi[u] = st[1];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) len += t0 + u < ptiles ? (int32_t)(hi[u] - lo[u]) : 0;
+            }
         int32_t total;
         const int32_t s0 = entries + block_exclusive<kWavesGQ>(len, part, total);
         entries += total;
@@ -383,12 +399,19 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
         const int b = b0 + tid;
         int32_t longest = 0;
         if (b < r) {
-#pragma unroll 8
-            for (int k = 0; k < nchunks; ++k) {
-                const uint32_t* st = s.start + (size_t)k * (r + 1) + b;
-                const int32_t lo = (int32_t)st[0], hi = (int32_t)st[1];
-                longest = max(longest, hi - lo);
-                if (k == c) { s_start[b] = lo; s_end[b] = hi; }
+            constexpr int kAhead = 8;                                // (loads without a condition, so that they do not wait for one another)
+            for (int k0 = 0; k0 < nchunks; k0 += kAhead) {
+                int32_t lo[kAhead], hi[kAhead];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const uint32_t* st = s.start + (size_t)min(k0 + u, nchunks - 1) * (r + 1) + b;
+                    lo[u] = (int32_t)st[0]; hi[u] = (int32_t)st[1];
+                }
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    longest = max(longest, hi[u] - lo[u]);
+                    if (k0 + u == c) { s_start[b] = lo[u]; s_end[b] = hi[u]; }
+                }
             }
         }
         const int32_t own = b < r ? max(1, (longest + cap - 1) / cap) : 0;
@@ -587,7 +610,8 @@ __device__ __forceinline__ void plan_tiles(uint8_t* __restrict__ plan, const Pla
     uint32_t first = 0;
     for (int step0 = tile_part * kRun; step0 == tile_part * kRun || step0 < (int)sg.steps; step0 += kTileParts * kRun) {
         const int step = step0 + (int)threadIdx.x / kTileCols;
-        uint32_t src[kStepEntries] = {kNoSource, kNoSource, kNoSource, kNoSource};
+        uint32_t src[kStepEntries] = {0, 0, 0, 0};
+        bool has[kStepEntries] = {false, false, false, false};
         float val[kStepEntries];
         if (step < (int)sg.steps) {
             int tile = 0, before = 0, end = 0;                        // before: steps of the tiles before
@@ -599,10 +623,17 @@ __device__ __forceinline__ void plan_tiles(uint8_t* __restrict__ plan, const Pla
             const size_t place = (size_t)c * kLists + (size_t)tile_of_wave(tile, w) * kTileCols + bb;
             const int lo = s.by_len_lo[place], n = s.by_len_n[place], e0 = (step - before) * kStepEntries;
 #pragma unroll
-            for (int k = 0; k < kStepEntries; ++k) src[k] = e0 + k < n ? sorted[lo + e0 + k] : kNoSource;
+            for (int k = 0; k < kStepEntries; ++k) has[k] = e0 + k < n;
+#pragma unroll
+            for (int k = 0; k < kStepEntries; ++k) src[k] = sorted[has[k] ? lo + e0 + k : 0];
         }
 #pragma unroll
-        for (int k = 0; k < kStepEntries; ++k) val[k] = src[k] != kNoSource ? Q_val[src[k]] : 0.0f;
+        for (int k = 0; k < kStepEntries; ++k) val[k] = Q_val[src[k]];
+#pragma unroll
+        for (int k = 0; k < kStepEntries; ++k) {
+            val[k] = has[k] ? val[k] : 0.0f;
+            src[k] = has[k] ? src[k] : kNoSource;
+        }
         if (step0 == tile_part * kRun) {                              // all threads are here
             int32_t total;
             (void)block_exclusive<kThreadsRows / kWave>(sum, part, total);
@@ -630,6 +661,7 @@ __device__ __forceinline__ void plan_tiles(uint8_t* __restrict__ plan, const Pla
 __global__ __launch_bounds__(kThreadsRows) void k_plan_rows(uint8_t* __restrict__ plan, PlanLayout L, BuildScratch s, const int32_t* __restrict__ P_idx,
                                                             const float* __restrict__ P_val, const float* __restrict__ Q_val, int m, int r, int d,
                                                             int nchunks, int pblocks, int64_t max_rows, bool with_tiles, float* __restrict__ zero) {
+    touch_args<4>();
     PlanHeader* H = reinterpret_cast<PlanHeader*>(plan);
     if (H->magic != kPlanMagic) {
         if (zero)
@@ -662,17 +694,26 @@ __global__ __launch_bounds__(kThreadsRows) void k_plan_rows(uint8_t* __restrict_
         for (int q0 = 0; q0 < len / 2 * kWave; q0 += kAhead * kThreadsRows) {
             uint32_t src[kAhead][2];
             float val[kAhead][2];
+            bool has[kAhead][2];
 #pragma unroll
             for (int k = 0; k < kAhead; ++k) {
                 const int q = q0 + k * kThreadsRows + tid, lane = q % kWave, e = q / kWave * 2;
                 const bool in = e < len;
-                src[k][0] = in && e < s_n[lane] ? sorted[s_lo[lane] + e] : kNoSource;
-                src[k][1] = in && e + 1 < s_n[lane] ? sorted[s_lo[lane] + e + 1] : kNoSource;
+                const int lo = s_lo[lane], n = s_n[lane];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    has[k][h] = in && e + h < n;
+                    src[k][h] = sorted[has[k][h] ? lo + e + h : 0];  // (loads without a condition, so that they do not wait for one another)
+                }
             }
 #pragma unroll
             for (int k = 0; k < kAhead; ++k)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) val[k][h] = src[k][h] != kNoSource ? Q_val[src[k][h]] : 0.0f;
+                for (int h = 0; h < 2; ++h) {
+                    const float v = Q_val[src[k][h]];
+                    val[k][h] = has[k][h] ? v : 0.0f;
+                    src[k][h] = has[k][h] ? src[k][h] : kNoSource;
+                }
 #pragma unroll
             for (int k = 0; k < kAhead; ++k) {
                 const int q = q0 + k * kThreadsRows + tid, lane = q % kWave, e = q / kWave * 2;

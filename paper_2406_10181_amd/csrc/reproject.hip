@@ -3,7 +3,7 @@
 //     M <- (P^T P_prev) M (Q_prev^T Q),      V <- (P^T P_prev)^2 V (Q_prev^T Q)^2,
 // the squares taken element by element.  Two steps:
 //   1. A = P^T P_prev and B = Q_prev^T Q, r x r: products of two ELL matrices with the same rows;
-//      row i adds its d x d products val * val' at (idx, idx'), with fp32 atomics in LDS on a block
+//      row i adds its d x d products val * val' at (idx, idx'), with fp64 atomics in LDS on a block
 //      of rows of the result that a workgroup owns.
 //   2. four dense r x r products in fp32 on the matrix cores (v_mfma_f32_32x32x2_f32): X = A M,
 //      X2 = (A o A) V, then M = X B, V = X2 (B o B); the squares are taken while the tiles are staged,
@@ -20,111 +20,159 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // C = L^T R for two ELL matrices with the same rows: C[L_idx[i][k]][R_idx[i][k']] += L_val[i][k] * R_val[i][k'].
 // Global fp32 atomics are slow here (they go past the per-XCD L2), so a workgroup owns a block of rows of C
-// in LDS.  It scans the column index of every entry (i, k) of L and queues, in LDS, those that fall in its
-// block; then one thread per (queued entry, k') adds the product with an LDS atomic; then the block is
+// in LDS.  It scans the column index of every entry (i, k) of L; a wave queues those that fall in its
+// block, in LDS; then a lane per (queued entry, k') adds the product with an LDS atomic; then the block is
 // written (C needs no clearing).  Scanning and adding are separate so that neither is a chain of dependent
-// loads.  An entry that finds the queue full is added by the thread that found it (correct, slow: only
-// heavily skewed projectors get there).  blockIdx.y picks one of two independent pairs.  Entries with an
-// index outside [0, r) are skipped.  The order of the LDS additions varies: results can differ in the last
+// loads.  An entry that finds the wave's queue full is added by the lane that found it (correct, slow: only
+// heavily skewed projectors get there).  Two independent pairs may share a launch; each has about one workgroup in 256 for its share of all entries.
+// Entries with an index outside [0, r) are skipped.  The order of the LDS additions varies: results can differ in the last
 // bits from run to run.
-constexpr int kGramThreads = 1024, kGramAccFloats = 12288, kGramQueue = 4096, kGramInFlight = 8;
-__global__ __launch_bounds__(kGramThreads) void k_gram(const GramBatch batch, int d, int r, int block_rows, const GramClear clear) {
-    __shared__ float acc[kGramAccFloats];
-    __shared__ int queue[kGramQueue];
-    __shared__ int queued;
-    GramPair P = batch.p[0];
-    if (blockIdx.y == 1) P = batch.p[1];
-    const int a0 = blockIdx.x * block_rows, a1 = min(r, a0 + block_rows);
+// What bounds it: the scan, which every workgroup makes of all entries (issue, and 64 bytes a cycle from L2), and trips to memory.  The next 32 entries a thread are on their way while
+// 32 are looked at, no load has a condition (the compiler waits for one that has), and nothing is divided by d.
+// The sums are taken in 64 bits, because ds_add_f32 serves one lane in 3 cycles, wherever the lanes' addresses lie (192 cycles a wave), and ds_add_f64 a wave in 20: 4096 and 11008 rows,
+// r = 512, d = 8 18.9 -> 11.6 us, 4096 and 4096 11.4 -> 8.9.
+constexpr int kGramThreads = 1024, kGramSums = 12288, kGramQueue = 256, kGramInFlight = 8;   // (a wave's queue)
+constexpr size_t kGramLds = (size_t)kGramThreads / kWave * kGramQueue * sizeof(int);               // ... and the sums
+struct GramArgs {
+    int32_t r, d;
+    uint32_t d_inverse;                                             // ceil(2^32 / d); 0: d = 1
+    int32_t block_rows[2], first[2];                                // rows of C a workgroup has of each pair; the pair's first workgroup
+    int32_t pad[9];
+    GramPair p[2];
+    GramClear clear;
+};
+static_assert(sizeof(GramPair) == 64 && offsetof(GramArgs, p) == 64, "records of 64 bytes, loaded whole");
+__device__ __forceinline__ uint32_t divided(uint32_t x, uint32_t d, uint32_t d_inverse) {
+    if (d_inverse == 0) return x;
+    const uint32_t q = __umulhi(x, d_inverse);                      // or one more
+    return q * d > x ? q - 1 : q;
+}
+__global__ __launch_bounds__(kGramThreads) void k_gram(const GramArgs) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    double* const acc = reinterpret_cast<double*>(smem + kGramLds);
+    const auto* args = group_args<GramArgs>();
+    words8 head = scalar_load<words8>(args);
+    words16 pair0 = scalar_load<words16>(&args->p[0]), pair1 = scalar_load<words16>(&args->p[1]);
+    arrived(head, pair0, pair1);
+    const int r = (int)head[0], d = (int)head[1];
+    const uint32_t d_inverse = head[2];
+    const bool second = (int)blockIdx.x >= (int)head[6];
+    const int block_rows = (int)(second ? head[4] : head[3]), block = (int)blockIdx.x - (second ? (int)head[6] : 0);
+    GramPair P;
+    const words16 pair = second ? pair1 : pair0;
+    __builtin_memcpy(&P, &pair, 64);
+    P.L_idx = global_pointer(P.L_idx); P.L_val = global_pointer(P.L_val); P.R_idx = global_pointer(P.R_idx); P.R_val = global_pointer(P.R_val); P.C = global_pointer(P.C);
+    const int a0 = block * block_rows, a1 = min(r, a0 + block_rows);
     const int mine = (a1 - a0) * r;
     const int lane = threadIdx.x & 63;
-    for (int q = threadIdx.x; q < mine; q += kGramThreads) acc[q] = 0.0f;
-    if (threadIdx.x == 0) queued = 0;
-    __syncthreads();
-    auto add_entry = [&](int t, int a, int k2) {
-        const float v = P.L_val[t];
-        const int row = t / d * d;
-        const int b = P.R_idx[row + k2];
-        const float x = P.R_val[row + k2];
-        if (v != 0.0f && (unsigned)b < (unsigned)r) atomicAdd(&acc[(a - a0) * r + b], v * x);
-    };
     const int total = (int)(P.rows * d);                            // < 2^31, checked by the host
     typedef int i32x4 __attribute__((ext_vector_type(4)));
     typedef i32x4 loose __attribute__((aligned(4)));
-    const int whole = total >> 2, rest = total & 3, quads = whole + (rest ? 1 : 0);   // (total + 3 could pass 2^31 - 1)
     static_assert(4 * kGramInFlight == 32, "one bit for every entry of a batch");
+    // Entries 4 q .. 4 q + 3; the last ones begin at total - 4 at the latest, what they have twice counts once (fewer than 4 entries: one by one).
+    const int quads = (int)(((int64_t)total + 3) / 4);
+    auto fetch = [&](i32x4 (&a)[kGramInFlight], int t0) {
+        if (total < 4) {
+#pragma unroll
+            for (int u = 0; u < kGramInFlight; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) a[u][q] = P.L_idx[q < total ? q : 0];
+            return;
+        }
+#pragma unroll
+        for (int u = 0; u < kGramInFlight; ++u) {
+            const int t = t0 + u * kGramThreads + (int)threadIdx.x, at = t < quads ? 4 * t : 0;
+            a[u] = *reinterpret_cast<const loose*>(P.L_idx + (at < total - 4 ? at : total - 4));
+        }
+    };
+    auto entry_of = [&](int quad, int q) { return (total >= 4 && 4 * quad > total - 4 ? total - 4 : 4 * quad) + q; };
+    i32x4 now[kGramInFlight], next[kGramInFlight];
+    fetch(now, 0);
+    for (int q = threadIdx.x; q < mine; q += kGramThreads) acc[q] = 0.0;
+    __syncthreads();
+    int* const queue = reinterpret_cast<int*>(smem) + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave) * kGramQueue;
+    int queued = 0;                                                 // (uniform over the wave)
+    auto add_entry = [&](int t, int a, int k2) {
+        const float v = P.L_val[t];
+        const int row = (int)divided((uint32_t)t, (uint32_t)d, d_inverse) * d;
+        const int b = P.R_idx[row + k2];
+        const float x = P.R_val[row + k2];
+        if (v != 0.0f && (unsigned)b < (unsigned)r) unsafeAtomicAdd(&acc[(a - a0) * r + b], (double)v * (double)x);
+    };
     for (int t0 = 0; t0 < quads; t0 += kGramThreads * kGramInFlight) {       // uniform trip count: the exchanges need whole waves
-        i32x4 a[kGramInFlight];
+        const bool more = t0 + kGramThreads * kGramInFlight < quads;
+        if (more) fetch(next, t0 + kGramThreads * kGramInFlight);
+        if (t0 + kGramThreads * kGramInFlight >= quads) {           // the last entries are among these: none of the block's rows for what is not one, or was the quad's before
+            const int extra = 4 * quads - total;
 #pragma unroll
-        for (int u = 0; u < kGramInFlight; ++u) {
-            const int t = t0 + u * kGramThreads + (int)threadIdx.x;
-            a[u] = i32x4{-1, -1, -1, -1};
-            if (t < whole) a[u] = *reinterpret_cast<const loose*>(P.L_idx + 4 * (int64_t)t);
-            else if (t == whole)
+            for (int u = 0; u < kGramInFlight; ++u) {
+                const int t = t0 + u * kGramThreads + (int)threadIdx.x;
+                const int from = t >= quads ? 4 : t == quads - 1 && total >= 4 ? extra : 0, to = t == quads - 1 && total < 4 ? total : 4;
 #pragma unroll
-                for (int q = 0; q < 3; ++q)
-                    if (q < rest) a[u][q] = P.L_idx[4 * (int64_t)t + q];
-        }
-        uint32_t hits = 0;
-#pragma unroll
-        for (int u = 0; u < kGramInFlight; ++u)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) hits |= (unsigned)(a[u][q] - a0) < (unsigned)(a1 - a0) ? 1u << (4 * u + q) : 0u;
-        if (__ballot(hits != 0) == 0) continue;
-        // a wave takes its places in the queue at once (one per entry that falls in the block, by an addition of its
-        // own each, cost more than the scan)
-        const int have = __popc(hits);
-        int at = have;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int y = __shfl_up(at, off);
-            if (lane >= off) at += y;
-        }
-        int base = 0;
-        if (lane == kWave - 1) base = atomicAdd(&queued, at);
-        at += __shfl(base, kWave - 1) - have;
-        while (hits) {
-            const int k = __ffs((int)hits) - 1;
-            hits &= hits - 1;
-            const int t = 4 * (t0 + (k >> 2) * kGramThreads + (int)threadIdx.x) + (k & 3);
-            if (at < kGramQueue) queue[at] = t;
-            else {
-                const int row = P.L_idx[t];
-                for (int k2 = 0; k2 < d; ++k2) add_entry(t, row, k2);
+                for (int q = 0; q < 4; ++q) now[u][q] = q >= from && q < to ? now[u][q] : -1;
             }
-            ++at;
         }
-    }
-    __syncthreads();
-    const int work = min(queued, kGramQueue) * d;
-    for (int w0 = threadIdx.x; w0 < work; w0 += kGramThreads * kGramInFlight) {
-        // every load of a batch is issued before the first addition: otherwise each item waits for its own
-        int t[kGramInFlight], a[kGramInFlight], b[kGramInFlight];
-        float v[kGramInFlight], x[kGramInFlight];
+        uint32_t late = 0;                                          // entries that found the queue full
 #pragma unroll
         for (int u = 0; u < kGramInFlight; ++u) {
-            const int w = w0 + u * kGramThreads;
-            t[u] = w < work ? queue[w / d] : -1;
-        }
+            const int quad = t0 + u * kGramThreads + (int)threadIdx.x;
 #pragma unroll
-        for (int u = 0; u < kGramInFlight; ++u) {
-            const int tt = max(t[u], 0), k2 = (w0 + u * kGramThreads) % d;
-            a[u] = P.L_idx[tt];
-            v[u] = P.L_val[tt];
-            b[u] = P.R_idx[tt / d * d + k2];
-            x[u] = P.R_val[tt / d * d + k2];
+            for (int q = 0; q < 4; ++q) {
+                const bool hit = (unsigned)(now[u][q] - a0) < (unsigned)(a1 - a0);
+                const uint64_t hits = __ballot(hit);
+                if (hits == 0) continue;
+                const int place = queued + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
+                if (hit) {
+                    if (place < kGramQueue) queue[place] = entry_of(quad, q);
+                    else late |= 1u << (4 * u + q);
+                }
+                queued += __builtin_popcountll(hits);
+            }
         }
+        while (late) {
+            const int k = __ffs((int)late) - 1;
+            late &= late - 1;
+            const int t = entry_of(t0 + (k >> 2) * kGramThreads + (int)threadIdx.x, k & 3), row = P.L_idx[t];
+            for (int k2 = 0; k2 < d; ++k2) add_entry(t, row, k2);
+        }
+        queued = min(queued, kGramQueue);
+        if (queued > kGramQueue / 2 || !more) {                     // what is queued joins the sums
+            __builtin_amdgcn_wave_barrier();
+            const int work = queued * d;
+            for (int w0 = lane; w0 < work; w0 += kWave * kGramInFlight) {
+                // every load of a batch is issued before the first addition: otherwise each item waits for its own
+                int a[kGramInFlight], b[kGramInFlight];
+                float v[kGramInFlight], x[kGramInFlight];
 #pragma unroll
-        for (int u = 0; u < kGramInFlight; ++u)
-            if (t[u] >= 0 && v[u] != 0.0f && (unsigned)b[u] < (unsigned)r) atomicAdd(&acc[(a[u] - a0) * r + b[u]], v[u] * x[u]);
+                for (int u = 0; u < kGramInFlight; ++u) {
+                    const uint32_t w = (uint32_t)min(w0 + u * kWave, work - 1), e = divided(w, (uint32_t)d, d_inverse);
+                    const int t = queue[e];
+                    const int other = (int)(divided((uint32_t)t, (uint32_t)d, d_inverse) * (uint32_t)d + w - e * (uint32_t)d);
+                    a[u] = P.L_idx[t];
+                    v[u] = P.L_val[t];
+                    b[u] = P.R_idx[other];
+                    x[u] = P.R_val[other];
+                }
+#pragma unroll
+                for (int u = 0; u < kGramInFlight; ++u)
+                    if (w0 + u * kWave < work && v[u] != 0.0f && (unsigned)b[u] < (unsigned)r) unsafeAtomicAdd(&acc[(a[u] - a0) * r + b[u]], (double)v[u] * (double)x[u]);
+            }
+            queued = 0;
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (more)
+#pragma unroll
+            for (int u = 0; u < kGramInFlight; ++u) now[u] = next[u];
     }
     __syncthreads();
-    for (int q = threadIdx.x; q < mine; q += kGramThreads) P.C[(int64_t)a0 * r + q] = acc[q];
-    if (clear.p) {
-        const auto* H = as_const<PlanHeader>(clear.plan);
-        if (H->magic == kPlanMagic && H->p_any_split)
-            for (int64_t k = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kGramThreads + threadIdx.x; k < clear.count;
-                 k += (int64_t)gridDim.x * gridDim.y * kGramThreads)
-                clear.p[k] = 0.0f;
+    for (int q = threadIdx.x; q < mine; q += kGramThreads) P.C[(int64_t)a0 * r + q] = (float)acc[q];
+    if (args->clear.p) {
+        const auto* H = as_const<PlanHeader>(args->clear.plan);
+        if (H->magic == kPlanMagic && H->p_any_split) {
+            float* const p = global_pointer(args->clear.p);
+            const int64_t count = args->clear.count;
+            for (int64_t k = (int64_t)blockIdx.x * kGramThreads + threadIdx.x; k < count; k += (int64_t)gridDim.x * kGramThreads) p[k] = 0.0f;
+        }
     }
 }
 
@@ -138,16 +186,25 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(const GramBatch batch, in
 // A[i = l % 32][k = l / 32] and B[k = l / 32][j = l % 32] and holds
 // C[8 (v / 4) + 4 (l / 32) + v % 4][l % 32] in accumulator register v -- and their four partial
 // tiles are added through LDS at the end, in wave order.
+__device__ __forceinline__ GemmProblem gemm_problem(int& r) {
+    const auto* args = group_args<GemmBatch>();
+    words2 head = scalar_load<words2>(args);
+    words16 record = scalar_load<words16>(&args->p[blockIdx.z]);
+    arrived(head, record);
+    r = (int)head[0];
+    GemmProblem P;
+    __builtin_memcpy(&P, &record, 64);
+    P.A = global_pointer(P.A); P.B = global_pointer(P.B); P.C = global_pointer(P.C); P.E = global_pointer(P.E); P.Ct = global_pointer(P.Ct);
+    return P;
+}
 constexpr int kTileMN = 32, kTileK = 128;
 constexpr int kTileElems = kTileMN * kTileK / 256;                  // elements of each tile a thread stages
-__global__ __launch_bounds__(256) void k_gemm_rr(const GemmBatch batch, int r) {
+__global__ __launch_bounds__(256) void k_gemm_rr(const GemmBatch) {
     __shared__ float As[kTileMN][kTileK + 1];
     __shared__ float Bs[kTileK][kTileMN + 1];
     __shared__ float Cs[4][16][64];
-    GemmProblem P = batch.p[0];
-#pragma unroll
-    for (int z = 1; z < kMaxGemmBatch; ++z)
-        if ((int)blockIdx.z == z) P = batch.p[z];
+    int r;
+    const GemmProblem P = gemm_problem(r);
     const float* __restrict__ A = P.A;
     const float* __restrict__ B = P.B;
     const bool ta = P.flags & kGemmTA, tb = P.flags & kGemmTB, sqa = P.flags & kGemmSqA, sqb = P.flags & kGemmSqB;
@@ -224,14 +281,12 @@ __global__ __launch_bounds__(256) void k_gemm_rr(const GemmBatch batch, int r) {
 constexpr int kTileRow4 = kTileK + 4;                               // floats per LDS row
 constexpr int kTileGroups = kTileMN * kTileK / 4 / 256;             // 16-byte groups of each tile a thread stages
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-__global__ __launch_bounds__(256) void k_gemm_rr4(const GemmBatch batch, int r) {
+__global__ __launch_bounds__(256) void k_gemm_rr4(const GemmBatch) {
     __shared__ __align__(16) float As[kTileMN * kTileRow4];
     __shared__ __align__(16) float Bs[kTileMN * kTileRow4];
     __shared__ float Cs[4][16][64];
-    GemmProblem P = batch.p[0];
-#pragma unroll
-    for (int z = 1; z < kMaxGemmBatch; ++z)
-        if ((int)blockIdx.z == z) P = batch.p[z];
+    int r;
+    const GemmProblem P = gemm_problem(r);
     const float* __restrict__ A = P.A;
     const float* __restrict__ B = P.B;
     const bool ta = P.flags & kGemmTA, tb = P.flags & kGemmTB, sqa = P.flags & kGemmSqA, sqb = P.flags & kGemmSqB;
@@ -320,14 +375,31 @@ __global__ __launch_bounds__(256) void k_gemm_rr4(const GemmBatch batch, int r) 
 }
 
 hipError_t launch_gram(const GramBatch& batch, int count, int32_t d, int32_t r, const GramClear* clear, hipStream_t st) {
-    if (count < 1 || count > 2 || r > kGramAccFloats) return hipErrorInvalidValue;
-    for (int z = 0; z < count; ++z)
+    if (count < 1 || count > 2 || r > kGramSums) return hipErrorInvalidValue;
+    int64_t entries = 0;
+    for (int z = 0; z < count; ++z) {
         if (batch.p[z].rows * d > INT32_MAX) return hipErrorInvalidValue;
-    // LDS fp32 atomics go at a few cycles each per CU, so the rows of C are spread over about one workgroup
-    // per CU rather than packed into as few as LDS allows (each workgroup scans all of L_idx either way)
-    const int block_rows = std::max(1, std::min(kGramAccFloats / (int)r, ((int)r * count + 255) / 256));
-    hipLaunchKernelGGL(k_gram, dim3((unsigned)((r + block_rows - 1) / block_rows), (unsigned)count), dim3(kGramThreads), 0, st,
-                       batch, (int)d, (int)r, block_rows, clear ? *clear : GramClear{});
+        entries += batch.p[z].rows * d;
+    }
+    // The rows of C are spread over about one workgroup
+    // per CU rather than packed into as few as LDS allows (each workgroup scans all of L_idx either way); the pair with more entries has more of the workgroups.
+    GramArgs args{};
+    args.r = r; args.d = d;
+    args.d_inverse = d == 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + (uint64_t)d - 1) / (uint64_t)d);
+    args.first[1] = INT32_MAX;
+    int grid = 0;
+    for (int z = 0; z < count; ++z) {
+        const int share = (int)std::max<int64_t>(1, std::min<int64_t>(224, 256 * batch.p[z].rows * d / entries));
+        args.p[z] = batch.p[z];
+        args.block_rows[z] = std::max(1, std::min(kGramSums / (int)r, ((int)r + share - 1) / share));
+        args.first[z] = grid;
+        grid += ((int)r + args.block_rows[z] - 1) / args.block_rows[z];
+    }
+    if (clear) args.clear = *clear;
+    hipError_t e;
+    if ((e = allow_dynamic_lds<k_gram, kGramLds + kGramSums * sizeof(double)>()) != hipSuccess) return e;
+    const size_t lds = kGramLds + (size_t)std::max(args.block_rows[0], args.block_rows[1]) * r * sizeof(double);
+    hipLaunchKernelGGL(k_gram, dim3((unsigned)grid), dim3(kGramThreads), lds, st, args);
     return hipGetLastError();
 }
 
@@ -339,8 +411,10 @@ hipError_t launch_gemm_rr_batch(const GemmBatch& batch, int count, int32_t r, hi
     bool by16 = r % 4 == 0;                                          // the 16-byte path: whole groups, aligned operands
     for (int z = 0; z < count; ++z)
         by16 = by16 && reinterpret_cast<uintptr_t>(batch.p[z].A) % 16 == 0 && reinterpret_cast<uintptr_t>(batch.p[z].B) % 16 == 0;
-    if (by16) hipLaunchKernelGGL(k_gemm_rr4, grid, dim3(256), 0, st, batch, (int)r);
-    else      hipLaunchKernelGGL(k_gemm_rr, grid, dim3(256), 0, st, batch, (int)r);
+    GemmBatch args = batch;
+    args.r = r;
+    if (by16) hipLaunchKernelGGL(k_gemm_rr4, grid, dim3(256), 0, st, args);
+    else      hipLaunchKernelGGL(k_gemm_rr, grid, dim3(256), 0, st, args);
     return hipGetLastError();
 }
 
@@ -353,17 +427,17 @@ hipError_t launch_reproject(const int32_t* P_idx, const float* P_val, const int3
     float* B = workspace + rr;
     float* X = workspace + 2 * rr;
     GramBatch grams{};
-    grams.p[0] = GramPair{P_idx, P_val, Pp_idx, Pp_val, m, A};
-    grams.p[1] = GramPair{Qp_idx, Qp_val, Q_idx, Q_val, n, B};
+    grams.p[0] = GramPair{P_idx, P_val, Pp_idx, Pp_val, m, A, {}};
+    grams.p[1] = GramPair{Qp_idx, Qp_val, Q_idx, Q_val, n, B, {}};
     hipError_t e = launch_gram(grams, 2, d, r, nullptr, st);
     if (e != hipSuccess) return e;
     // X = A M and X2 = (A o A) V in one launch, then M = X B and V = X2 (B o B) in another
     float* X2 = workspace + 3 * rr;
     GemmBatch left{}, right{};
-    left.p[0] = GemmProblem{A, M, X, nullptr, 0.0f, 0, nullptr};
-    left.p[1] = GemmProblem{A, V, X2, nullptr, 0.0f, kGemmSqA, nullptr};
-    right.p[0] = GemmProblem{X, B, M, nullptr, 0.0f, 0, nullptr};
-    right.p[1] = GemmProblem{X2, B, V, nullptr, 0.0f, kGemmSqB, nullptr};
+    left.p[0] = GemmProblem{A, M, X, nullptr, 0.0f, 0, nullptr, {}};
+    left.p[1] = GemmProblem{A, V, X2, nullptr, 0.0f, kGemmSqA, nullptr, {}};
+    right.p[0] = GemmProblem{X, B, M, nullptr, 0.0f, 0, nullptr, {}};
+    right.p[1] = GemmProblem{X2, B, V, nullptr, 0.0f, kGemmSqB, nullptr, {}};
     if ((e = launch_gemm_rr_batch(left, V ? 2 : 1, r, st)) != hipSuccess) return e;
     return launch_gemm_rr_batch(right, V ? 2 : 1, r, st);
 }
