@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cstring>
 #include <type_traits>
+#include <utility>
 
 #include "compress_common.h"
 
@@ -27,16 +28,58 @@ namespace lsp {
 // of consecutive a, so that they write 16 bytes of a row of Y together.  Rows cut into pieces (heavily skewed projectors)
 // add up with atomics on a Y that was cleared.
 // Every row of G is wanted by d rows of P^T, so G goes from L2 to the CUs d times: that traffic (268 MB at
-// 4096 x 4096, d = 8, 16-bit) is what the kernel's time is made of.  HBM sees G once: workgroup b runs on XCD b % 8 (the
-// dispatcher deals workgroups round-robin), and the grid is laid out so that one XCD takes every a for a column tile
+// 4096 x 4096, d = 8, 16-bit) is what the kernel's time is made of.  HBM sees G once: an XCD takes every a for a column tile
 // before its next tile, so a tile of G (m rows of 256 elements, 2 MB at m = 4096) stays in that XCD's L2 for its
-// d visits.  With a workgroup a piece (four waves, a quarter of the entries each, 8 bytes a lane) it took 34 us there, now 23 (24 with the address of a row made anew for every load: BELOW_4G, a 32-bit offset).
+// d visits.  With a workgroup a piece (four waves, a quarter of the entries each, 8 bytes a lane) it took 34 us there, 23 with a wave a piece (24 with the address of a row made anew for every load: BELOW_4G,
+// a 32-bit offset), now 21.5: rows and values of the entries by DPP moves and not by exchanges through LDS.  L2 hands out 12 of the 17 TB/s that it can (64 bytes a cycle and channel);
+// the products on the matrix cores instead of the vector ALUs took 22.0.
 // A row's last piece starts at n - VEC when n is no multiple of VEC, up to VEC - 1 columns before its tile if the tile has
 // fewer than VEC columns: the wave's sums have room for them in front.  n < VEC: one column a lane (VEC = 1).
 constexpr int kThreadsY = 256, kWavesY = kThreadsY / kWave, kXcds = 8, kTileY = 256;
+// The work is (tile of columns, four pieces), the pieces fastest, and each XCD has an eighth of it, one after the other (workgroup b runs on XCD b % 8), so that it has hardly more than one tile of G
+// at a time, and all XCDs the same amount (a tile for an XCD at a time, 4096 x 4160, r = 512, d = 8, fp16 28.3 us, 4096 x 4096 21.7).
+__device__ __forceinline__ bool place_in_y(int nitems, int tiles, int& item0, int& tile) {
+    const int groups = (nitems + kWavesY - 1) / kWavesY;
+    const uint32_t units = (uint32_t)groups * (uint32_t)tiles, each = (units + kXcds - 1) / kXcds, seq = blockIdx.x / kXcds, unit = blockIdx.x % kXcds * each + seq;
+    if (seq >= each || unit >= units) return false;
+    tile = (int)(unit / (uint32_t)groups);
+    item0 = (int)(unit - (uint32_t)tile * (uint32_t)groups) * kWavesY;
+    return true;
+}
+
+// The sums of a workgroup's four pieces go to Y: part[w * stride + c] for column tile0 + c, c < WIDTH.
+template <int WIDTH>
+__device__ __forceinline__ void store_y(const float* part, int stride, const uint8_t* plan, const LoadedHeader& H, float* __restrict__ Y, int item0, int nitems, int tile0, int n, int r) {
+    __syncthreads();
+    const int c = threadIdx.x, j = tile0 + c;
+    if (j >= n || c >= WIDTH) return;
+    float* out = Y + (int64_t)j * r;
+    int a[kWavesY];
+    bool plain = true;                                              // four whole rows of P^T in a row
+#pragma unroll
+    for (int w = 0; w < kWavesY; ++w) {
+        const auto* p = as_const<int32_t>(plan + H->off_p_item) + 4 * min(item0 + w, nitems - 1);
+        a[w] = item0 + w < nitems ? p[0] : -1;
+        plain = plain && a[w] == a[0] + w && p[3] == 0;
+    }
+    if (plain && ((a[0] | r) & 3) == 0) {
+        *reinterpret_cast<f32x4*>(out + a[0]) = f32x4{part[c], part[stride + c], part[2 * stride + c], part[3 * stride + c]};
+        return;
+    }
+#pragma unroll
+    for (int w = 0; w < kWavesY; ++w) {
+        if (a[w] < 0) continue;
+        const auto* p = as_const<int32_t>(plan + H->off_p_item) + 4 * (item0 + w);
+        if (p[3]) atomicAdd(out + a[w], part[w * stride + c]);
+        else out[a[w]] = part[w * stride + c];
+    }
+}
+
+template <int K> __device__ __forceinline__ uint32_t row_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x150 + K, 0xF, 0xF, true); }   // of each 16 lanes (row_newbcast)
+template <typename F, int... k> __device__ __forceinline__ void each_of(const F& f, std::integer_sequence<int, k...>) { (f(std::integral_constant<int, k>{}), ...); }
 template <typename D, int VEC, bool BELOW_4G>
 __global__ __launch_bounds__(kThreadsY) void k_gather_rows(const typename D::elem* __restrict__ G, const uint8_t* __restrict__ plan,
-                                                          float* __restrict__ Y, int m, int n, int r, int d, int item_groups, int tiles) {
+                                                          float* __restrict__ Y, int m, int n, int r, int d, int tiles) {
     constexpr int LG = VEC == 1 ? kWave : kTileY / VEC < kWave ? kTileY / VEC : kWave;   // lanes of an entry
     constexpr int NG = kWave / LG;                                  // entries a wave takes at a time
     constexpr int kLead = VEC;                                      // room in front of a tile (VEC - 1, rounded up to whole pieces)
@@ -45,10 +88,9 @@ __global__ __launch_bounds__(kThreadsY) void k_gather_rows(const typename D::ele
     typedef Piece Loose __attribute__((aligned(D::size)));
     const LoadedHeader H = load_header(plan);
     if (!plan_matches(H, m, n, r, d, false)) return;
-    const int seq = blockIdx.x / kXcds;                             // position in this XCD's sequence: items fastest
-    const int item0 = (seq % item_groups) * kWavesY, tile = (seq / item_groups) * kXcds + blockIdx.x % kXcds;
     const int nitems = H->p_nitems;
-    if (item0 >= nitems || tile >= tiles) return;
+    int item0, tile;
+    if (!place_in_y(nitems, tiles, item0, tile)) return;
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const auto* itp = as_const<int32_t>(plan + H->off_p_item) + 4 * min(item0 + wave, nitems - 1);
     const RowItem it{itp[0], itp[1], itp[2], itp[3]};
@@ -60,31 +102,37 @@ __global__ __launch_bounds__(kThreadsY) void k_gather_rows(const typename D::ele
     float acc[VEC];
 #pragma unroll
     for (int q = 0; q < VEC; ++q) acc[q] = 0.0f;
-    for (int base = 0; base < it.len; base += kWave) {
-        uint2 mine = ent[min(base + lane, it.len - 1)];              // behind the last entry: its row again, times zero
-        if (base + lane >= it.len) mine.y = 0u;
+    // Lanes 16 x + i hold entry NG i + (which of the NG this lane's part of the wave takes) of a batch, so that a lane has each entry's row and value by a DPP move.
+    constexpr int kSteps = 16, kBatch = kSteps * NG, kInFlight = 8;
+    const int mine_of_batch = NG * (lane & 15) + grp;
+    uint2 next = ent[min(mine_of_batch, max(it.len - 1, 0))];
+    for (int base = 0; base < it.len; base += kBatch) {
+        uint2 mine = next;                                           // behind the last entry: its row again, times zero
+        if (base + mine_of_batch >= it.len) mine.y = 0u;
+        next = ent[min(base + kBatch + mine_of_batch, it.len - 1)];
         if constexpr (BELOW_4G) mine.x *= (uint32_t)n * D::size;     // the row's offset in G, once per entry and not per load
-        const int steps = (min(it.len - base, (int)kWave) + NG - 1) / NG;
-        constexpr int kInFlight = 8;
-        static_assert(kWave / NG % kInFlight == 0, "the loads of a batch all have an entry");
-        for (int k0 = 0; k0 < steps; k0 += kInFlight) {
+        const int steps = (min(it.len - base, kBatch) + NG - 1) / NG;
+        auto take = [&](auto which) {
+            constexpr int k0 = decltype(which)::value * kInFlight;
+            if (k0 >= steps) return;                                  // (uniform)
             Piece x[kInFlight];
-            float v[kInFlight];
-#pragma unroll
-            for (int u = 0; u < kInFlight; ++u) {
-                const int src = (k0 + u) * NG + grp;
-                const uint32_t row = (uint32_t)__shfl((int)mine.x, src);
-                v[u] = __uint_as_float((uint32_t)__shfl((int)mine.y, src));
+            auto load = [&](auto step) {
+                constexpr int u = decltype(step)::value;
+                const uint32_t row = row_lane<k0 + u>(mine.x);
                 if constexpr (BELOW_4G) x[u] = *reinterpret_cast<const Loose*>(reinterpret_cast<const char*>(G) + (row + (uint32_t)at * D::size));
                 else x[u] = *reinterpret_cast<const Loose*>(G + at + (int64_t)row * n);
-            }
+            };
+            each_of(load, std::make_integer_sequence<int, kInFlight>{});
+            __builtin_amdgcn_sched_barrier(0);                        // all of them in flight before the first is used
+            auto add = [&](auto step) {
+                constexpr int u = decltype(step)::value;
+                const float v = __uint_as_float(row_lane<k0 + u>(mine.y));
 #pragma unroll
-            for (int u = 0; u < kInFlight; ++u)
-#pragma unroll
-                for (int q = 0; q < VEC; ++q) {
-                    acc[q] = fmaf(v[u], widen<D>(x[u][q]), acc[q]);
-                }
-        }
+                for (int q = 0; q < VEC; ++q) acc[q] = fmaf(v, widen<D>(x[u][q]), acc[q]);
+            };
+            each_of(add, std::make_integer_sequence<int, kInFlight>{});
+        };
+        each_of(take, std::make_integer_sequence<int, kSteps / kInFlight>{});
     }
     if constexpr (NG > 1) {
 #pragma unroll
@@ -94,29 +142,7 @@ __global__ __launch_bounds__(kThreadsY) void k_gather_rows(const typename D::ele
 #pragma unroll
         for (int q = 0; q < VEC; ++q) part[wave][kLead + at - tile0 + q] = acc[q];   // (the same sums where pieces overlap)
     }
-    __syncthreads();
-    const int c = threadIdx.x, j = tile0 + c;
-    if (j >= n || c >= (VEC == 1 ? kWave : kTileY)) return;
-    float* out = Y + (int64_t)j * r;
-    int a[kWavesY];
-    bool plain = true;                                              // four whole rows of P^T in a row
-#pragma unroll
-    for (int w = 0; w < kWavesY; ++w) {
-        const auto* p = as_const<int32_t>(plan + H->off_p_item) + 4 * min(item0 + w, nitems - 1);
-        a[w] = item0 + w < nitems ? p[0] : -1;
-        plain = plain && a[w] == a[0] + w && p[3] == 0;
-    }
-    if (plain && ((a[0] | r) & 3) == 0) {
-        *reinterpret_cast<f32x4*>(out + a[0]) = f32x4{part[0][kLead + c], part[1][kLead + c], part[2][kLead + c], part[3][kLead + c]};
-        return;
-    }
-#pragma unroll
-    for (int w = 0; w < kWavesY; ++w) {
-        if (a[w] < 0) continue;
-        const auto* p = as_const<int32_t>(plan + H->off_p_item) + 4 * (item0 + w);
-        if (p[3]) atomicAdd(out + a[w], part[w][kLead + c]);
-        else out[a[w]] = part[w][kLead + c];
-    }
+    store_y<VEC == 1 ? kWave : kTileY>(&part[0][kLead], kLead + kTileY, plan, H, Y, item0, nitems, tile0, n, r);
 }
 
 // Both gradients: g[i][k] = sum_k' val[i][k'] M[idx[i][k']][a] + sum_b X[i][b] D[a][b],  a = idx[i][k] (left: X = T, D, M1; right:
@@ -200,22 +226,17 @@ size_t fitgrad_workspace_floats(int64_t m, int64_t n, int32_t r, int32_t d) {
 
 template <typename D>
 static hipError_t launch_gather(const void* G, const uint8_t* plan, float* Y, int64_t m, int64_t n, int32_t r, int32_t d, hipStream_t st) {
-    using E = typename D::elem;
-    const int groups = ((int)plan_max_items(m, r, d) + kWavesY - 1) / kWavesY;
-    auto launch = [&](auto vec) {
-        constexpr int VEC = decltype(vec)::value;
-        const int tiles = (int)((n + kTileY - 1) / kTileY);          // (VEC = 1: one tile of n < 8 columns)
-        const int64_t grid = (int64_t)groups * ((tiles + kXcds - 1) / kXcds) * kXcds;
-        if (grid > INT32_MAX) return hipErrorInvalidValue;
-        auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreadsY), 0, st, static_cast<const E*>(G), plan, Y, (int)m, (int)n, (int)r, (int)d, groups, tiles);
-            return hipGetLastError();
-        };
-        return m * n * D::size <= (int64_t)UINT32_MAX ? go(k_gather_rows<D, VEC, true>) : go(k_gather_rows<D, VEC, false>);
+    const int groups = ((int)plan_max_items(m, r, d) + kWavesY - 1) / kWavesY, tiles = (int)((n + kTileY - 1) / kTileY);   // (one column a lane: one tile)
+    const int64_t grid = ((int64_t)groups * tiles + kXcds - 1) / kXcds * kXcds;
+    if (grid > INT32_MAX) return hipErrorInvalidValue;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreadsY), 0, st, static_cast<const typename D::elem*>(G), plan, Y, (int)m, (int)n, (int)r, (int)d, tiles);
+        return hipGetLastError();
     };
+    const bool below = m * n * D::size <= (int64_t)UINT32_MAX;
     constexpr int kPiece = 16 / D::size;
-    if (n >= kPiece) return launch(std::integral_constant<int, kPiece>{});
-    return launch(std::integral_constant<int, 1>{});
+    if (n >= kPiece) return below ? go(k_gather_rows<D, kPiece, true>) : go(k_gather_rows<D, kPiece, false>);
+    return below ? go(k_gather_rows<D, 1, true>) : go(k_gather_rows<D, 1, false>);
 }
 
 hipError_t launch_fitgrad(const void* G, const uint8_t* plan, const int32_t* P_idx, const float* P_val,
