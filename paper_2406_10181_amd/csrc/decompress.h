@@ -16,6 +16,7 @@
 // workgroup leaves its two sums in a list that k_bias_finish adds in a fixed order.
 #pragma once
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -101,7 +102,7 @@ __device__ __forceinline__ void build_u_tile(const Place& place, int2* pent, con
     // shared in L2 (4096 x 4096, r = 2048, d = 8, bf16: 47.7 -> 44.9 us; r = 1536, d = 16, fp16, 1000 x 2048: 24.5 -> 24.0).  Not where the
     // last stripe would leave more than an eighth of the lanes idle (r = 1100: 32.4, with stripes 32.7); at r = 1024 and below it is even.
     constexpr int WAVES = NT / kWave;
-    static_assert(R % WAVES == 0, "every wave has the same number of rows of a stripe");
+    static_assert(!STRIPES || R % WAVES == 0, "every wave has the same number of rows of a stripe");
     // (STRIPES: so the rest has no code for it)
     const bool stripes = STRIPES && r > 1024 && (quads + kWave - 1) / kWave * kWave * 8 <= quads * 9;
     const int row0 = stripes ? (int)threadIdx.x / kWave : (int)threadIdx.x / quads;
@@ -656,7 +657,7 @@ __device__ __forceinline__ void decompress_wide() {
         constexpr int kRest = COLS - 1;
         static_assert(kRest * R <= 2 * kWave, "two waves");
         const int e = (int)threadIdx.x - (NT - 2 * kWave), at_row = e / COLS, c = e % COLS;
-        if (e >= 0 && at_row < rows && patched + c < n) {
+        if (part == 0 && e >= 0 && at_row < rows && patched + c < n) {
             const int64_t j = patched + c;
             typename D::elem* const w = reinterpret_cast<typename D::elem*>(base + at_row * (int64_t)stride) + j;
             uint32_t b[DD];
@@ -906,8 +907,8 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
     }
     hipError_t e;
     const bool narrow = RG == 4 && NT == 512 && d <= 8 && narrow_call(grid, g.p[0].n, r, d, D::size, NORMS);   // (the matrices are in the order of their widths)
-    if (fast && !narrow && wide_group(g, r)) {
-        constexpr int LP = RG == 2 ? 2 : 4, G = RG == 2 ? 1 : RG / 4;
+    if (RG > 1 && fast && !narrow && wide_group(g, r)) {
+        constexpr int LP = RG <= 2 ? 2 : 4, G = RG <= 2 ? 1 : RG / 4;
 #define LSP_LAUNCH_WIDE(DDV, FORM)                                                                             \
     do {                                                                                                       \
         constexpr auto kern = k_decompress_wide<D, G, LP, DDV, (PS > 16384), NT, NORMS, FORM>;                 \
@@ -932,12 +933,12 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
             if (d == 4) LSP_WIDE(4);
             if (d == 8) LSP_WIDE(8);
         }
-        if constexpr (NT == 512)
+        if constexpr (NT == 512 && RG > 1)
             if (d == 16) LSP_WIDE(16);
 #undef LSP_WIDE
 #undef LSP_LAUNCH_WIDE
     }
-    if constexpr (RG <= 4 && NT == 512 && PS <= 16384) {
+    if constexpr (RG <= 4 && RG > 1 && NT == 512 && PS <= 16384) {
         if (!(fast && wide_group(g, r)) && loose_group(g, d) && loose_call(grid, g.p[0].n, d, D::size, fast, RG == 2)) return launch_loose<D>(g, grid, RG == 2, NORMS, st);
     }
 #define LSP_LAUNCH_FAST(DDV)                                                                                   \
@@ -952,7 +953,8 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
     if (fast && d == 4) LSP_LAUNCH_FAST(4);
     if (fast && d == 8) LSP_LAUNCH_FAST(8);
     if constexpr (RG <= 4 && NT == 512) {                           // the others are for the fast kernel at d <= 8
-        if (fast && d == 16) LSP_LAUNCH_FAST(16);
+        if constexpr (RG > 1)                                       // (4 rows: d <= 8)
+            if (fast && d == 16) LSP_LAUNCH_FAST(16);
 #define LSP_LAUNCH_ANY(PAIRV)                                                                                  \
     do {                                                                                                       \
         constexpr auto kern = k_decompress_any<D, RG, PS, NT, PAIRV, NORMS>;                                   \
@@ -994,6 +996,19 @@ inline bool eight_rows(int64_t blocks, int64_t n, int32_t r, int32_t d, int elem
     return wide ? r <= 64 * d && (d <= 2 || (!norms && n <= 1024)) : d <= 4;
 }
 
+// The apply step with at most 64 blocks of 16 rows, where blocks of 8 would leave half of the CUs idle: blocks of 4 rows in k_decompress and k_decompress_any, or of 8 in the two kernels
+// that share units between lanes, and a row block's passes shared by as many workgroups as there are CUs for (each makes the tile of U).  (us, 8 rows and with this; bf16 and fp32.)
+//   4 rows: 1024 x 1024, r = 128, d = 4 4.9 and 3.6, 5.4 and 3.9; 1024 x 4096, r = 512, d = 8 13.6 and 10.6, 20.1 and 13.7; 768 x 3072, r = 384, d = 4 8.2 and 6.2, 10.5 and 7.7; 1024 x 2048,
+//     r = 1000, d = 8 10.9 and 9.1, 13.2 and 10.3; n odd 1001 x 701, r = 100, d = 5 5.1 and 4.6, 5.2 and 4.7; fp32 1001 x 2999, r = 250, d = 5 12.6 and 10.6.
+//   Passes shared: 512 x 2048, r = 128, d = 8 7.3 (4 rows 6.0) and 4.8, 8.7 (6.9) and 5.0.
+//   8 rows: d = 16 (4 rows: 1024 x 4096, r = 512 19.7 and 23.4); 16 bits, n odd, more than 1024 columns (1001 x 2003, r = 120, d = 3 6.2 and 6.8).
+// fp32 with 113 to 128 blocks and r <= 512, two workgroups of 4 rows on nearly every CU: 2048 x 4096, r = 512, d = 8 29.2 and 23.1, 2048 x 2048, r = 256, d = 4 10.6 and 9.9; with fewer some CUs have one (1500 x
+// 3000, r = 256, d = 8 14.5 and 16.5), and in 16 bits 8 rows are the better ones (2048 x 4096 16.2 and 17.4).
+inline bool few_blocks(int64_t blocks, int32_t r, int32_t d, int elem_size, bool fast) {
+    if (r > 1024) return false;
+    return blocks <= 64 || (elem_size == 4 && fast && d <= 8 && r <= 512 && blocks > 112 && blocks <= 128);
+}
+
 // Rows per workgroup: 16 (four planes of U in LDS) or 8 (above), and 512 threads, except
 //   * 1024 or more blocks, 16-bit storage, 256 < r <= 512: 32 rows, so that the rows of Q are streamed from L2 half as
 //     often (the seven matrices of a 6.7B-style layer, d = 8, one call: 202 us, with 16 rows 227; d = 16 325 and 335; 16384 x 4096, r = 512, d = 8 67.2 and 73.3; where
@@ -1016,6 +1031,18 @@ static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_
     }
     if (r > 1024) return launch_d<D, 2, 32768, 512>(g, r, d, kAll, st);
     const bool wide = wide_group(g, r);
+    const bool loose8 = !(fast && wide) && loose_group(g, d) && loose_call((unsigned)(2 * blocks), (int32_t)widest, d, D::size, fast, true);
+    if (few_blocks(blocks, r, d, D::size, fast)) {
+        const bool eight = blocks <= 64 && (fast ? d > 8 : loose8 && D::size == 2);
+        int64_t each = 0;                                           // row blocks
+        for (int p = 0; p < g.count; ++p) each += eight ? (g.p[p].m + 7) / 8 : (g.p[p].m + 3) / 4;
+        const int64_t passes = (widest + 1023) / 1024, share = std::max<int64_t>(1, kResidentDeep / each);
+        const int most = (int)((passes + share - 1) / share);
+        if (eight) return r <= 256 ? launch_d<D, 2, 4096, 512>(g, r, d, most, st) : r <= 512 ? launch_d<D, 2, 8192, 512>(g, r, d, most, st)
+                                                                                            : launch_d<D, 2, 16384, 512>(g, r, d, most, st);
+        return r <= 256 ? launch_d<D, 1, 4096, 512>(g, r, d, most, st) : r <= 512 ? launch_d<D, 1, 8192, 512>(g, r, d, most, st)
+                                                                                  : launch_d<D, 1, 16384, 512>(g, r, d, most, st);
+    }
     if (eight_rows(blocks, widest, r, d, D::size, fast, wide, false))
         return r <= 256 ? launch_d<D, 2, 4096, 512>(g, r, d, kAll, st) : r <= 512 ? launch_d<D, 2, 8192, 512>(g, r, d, kAll, st)
                                                                                  : launch_d<D, 2, 16384, 512>(g, r, d, kAll, st);

@@ -63,7 +63,7 @@ sys.path.insert(0, sys.argv[2])
 import paper_2406_10181_amd as L
 fake, big = 0x1000, 1 << 40
 for r in (16, 1024, 300):
-    for m in (300, 3000, 9000):
+    for m in (300, 2000, 3000, 9000):
         for n in (301, 4099):
             for d in range(1, 17):
                 for code in (0, 1, 2):
@@ -79,3 +79,31 @@ sys.stdout.flush()
     subprocess.run([os.environ.get("CXX", "g++"), "-O1", "-std=c++17", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
     out = subprocess.run([sys.executable, "-c", calls, str(so), ROOT], capture_output=True, text=True, timeout=300)
     assert out.returncode == 0 and "beyond 0" in out.stdout and "never launched" not in out.stdout, (out.stdout[-2000:], out.stderr[-2000:])
+
+
+# The apply step with few rows: blocks of 4 (and of 8: d = 16, and 16 bits with odd rows) whose passes are shared by up to as many workgroups as there are passes; both sides of the rule
+# (64 and 65 blocks of 16 rows; fp32 112, 113, 128 and 129).
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,r,d,dtype", [
+    (m, n, r, d, dtype) for dtype in ("bf16", "f16", "f32")
+    for m, n, r, d in [(1, 8, 4, 2), (3, 2056, 16, 4), (5, 4104, 260, 8), (255, 1024, 300, 8), (257, 3080, 700, 2), (1024, 1032, 128, 4), (1025, 1032, 128, 4), (16, 5128, 20, 16),
+                       (130, 3072, 600, 16), (7, 3077, 31, 5), (129, 2051, 300, 13), (66, 4099, 50, 1), (40, 2050, 1000, 8), (33, 6151, 90, 12)]
+] + [(1792, 520, 60, 4, "f32"), (1793, 520, 60, 4, "f32"), (2048, 1032, 260, 8, "f32"), (2049, 520, 600, 2, "f32"), (2048, 520, 516, 4, "f32")])
+def test_apply_with_few_rows(m, n, r, d, dtype):
+    import torch
+    import gpu_util as gu
+    import paper_2406_10181_amd as lsp
+    print(f"[case] few rows m={m} n={n} r={r} d={d} {dtype}", flush=True)
+    pb = syn.make_problem("few rows", m, n, r, d, dtype, seed=9970 + m + n + r + d, g_std=1.0)
+    Wp, Wr = oracle.decompress_apply(pb.W, dtype, pb.S_in, pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val)
+    dp = gu.DeviceProblem(pb)
+    single = dp.decompress(pb.S_in)
+    gu.check_decompress(single, pb.W, Wp, Wr, dtype, pb.name)
+    # in a group with a larger matrix other kernels make the same bits
+    other = gu.DeviceProblem(syn.make_problem("larger", 2100, 40, r, d, dtype, seed=2, g_std=1.0))
+    dp.W.copy_(gu.to_device(pb.W, dtype))
+    S = gu.to_device(pb.S_in)
+    items = [(x.W, S, x.P_idx, x.P_val, x.Q_idx, x.Q_val, x.pb.m, x.pb.n) for x in (dp, other)]
+    lsp.lsp_decompress_apply_grouped(lsp.apply_items(items), 2, r, d, dp.code, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    assert (gu.to_host(dp.W, dtype) == single).all()
