@@ -236,16 +236,16 @@ template <int NP> __device__ __forceinline__ bool two_chunks(int nvcols) {
     if constexpr (NP == 2) return true;
     const auto* g = group_args<CompressGroup>();
     uint32_t most = (uint32_t)nvcols;
-    const int count = g->count;
-    if (count > 1) {                                                  // (of all of them the pointers, then the numbers)
-        uint64_t plan[kMaxGroup];
+    if (g->count > 1) {                                               // (of all of them the pointers, then the numbers)
+        words16 lo = scalar_load<words16>(&g->plans[0]), hi = scalar_load<words16>(&g->plans[kMaxGroup / 2]);
+        arrived(lo, hi);
         uint32_t v[kMaxGroup];
+        auto nvcols_of = [](uint32_t a, uint32_t b) { return (uint32_t)((PlanHeaderPtr)((uint64_t)b << 32 | a))->nvcols; };
 #pragma unroll
-        for (int p = 0; p < kMaxGroup; ++p) plan[p] = *(const LSP_CONST_AS uint64_t*)&g->p[p < count ? p : 0].plan;
-#pragma unroll
-        for (int p = 0; p < kMaxGroup; ++p) arrived(plan[p]);
-#pragma unroll
-        for (int p = 0; p < kMaxGroup; ++p) v[p] = (uint32_t)((PlanHeaderPtr)plan[p])->nvcols;
+        for (int p = 0; p < kMaxGroup / 2; ++p) {
+            v[p] = nvcols_of(lo[2 * p], lo[2 * p + 1]);
+            v[kMaxGroup / 2 + p] = nvcols_of(hi[2 * p], hi[2 * p + 1]);
+        }
 #pragma unroll
         for (int p = 0; p < kMaxGroup; ++p) arrived(v[p]);
 #pragma unroll
@@ -727,6 +727,7 @@ template <int NP, int RING> static hipError_t launch_mm_rows(CompressGroup& g, h
     for (int p = 0; p < kMaxGroup; ++p) {
         CompressProblem& x = g.p[p];
         g.first_gq[p] = INT32_MAX;
+        g.plans[p] = g.p[p < g.count ? p : 0].plan;
         if (p >= g.count) continue;
         whole = whole && x.n % 8 == 0;
         x.blocks_gq = 1;
