@@ -73,18 +73,22 @@ __device__ __forceinline__ void block_sum2(float x, float y, float2* red, float2
 // costs few memory round trips.  A row's last quad is read from r - 4 on when r is no multiple of 4: some columns are then
 // made twice, with the same result; or, where the tile's columns lie in whole quads (Place::kQuads), it is turned into its place, with
 // whatever behind the last column.  place(row, b, c): where element (row, b + c) of the tile lives (c < 4).
+// The pairs are asked for first of all (tile_entry: a thread's first one; nearly always it has no other): loads return in order, and behind those of W the build would wait for HBM
+// once more.  Rows past m: value 0, row 0 of S.
+__device__ __forceinline__ int2 tile_entry(const int32_t* __restrict__ P_idx, const float* __restrict__ P_val, int64_t i0, int m, int d, int q) {
+    const int64_t at = i0 * d + q, count = (int64_t)m * d, there = at < count ? at : count - 1;
+    const int idx = P_idx[there];
+    const float val = P_val[there];
+    return at < count ? make_int2(idx, __float_as_int(val)) : make_int2(0, 0);
+}
 template <int R, int DD, int AHEAD, bool STRIPES, int NT, typename Place>
-__device__ __forceinline__ void build_u_tile(const Place& place, int2* pent, const float* __restrict__ S,
+__device__ __forceinline__ void build_u_tile(const Place& place, int2* pent, const int2 first_entry, const float* __restrict__ S,
                                              const int32_t* __restrict__ P_idx, const float* __restrict__ P_val,
                                              int64_t i0, int m, int r, int dim) {
     typedef f32x4 loose __attribute__((aligned(4)));
     const int d = DD > 0 ? DD : dim;
-    for (int q = threadIdx.x; q < R * d; q += NT) {
-        const int64_t at = i0 * d + q;
-        int2 e = make_int2(0, 0);                                   // rows past m: value 0, row 0 of S
-        if (at < (int64_t)m * d) e = make_int2(P_idx[at], __float_as_int(P_val[at]));
-        pent[q] = e;
-    }
+    if ((int)threadIdx.x < R * d) pent[threadIdx.x] = first_entry;
+    for (int q = threadIdx.x + NT; q < R * d; q += NT) pent[q] = tile_entry(P_idx, P_val, i0, m, d, q);
     __syncthreads();
     if (r < 4) {
         for (int q = threadIdx.x; q < R * r; q += NT) {
@@ -350,10 +354,12 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
     };
 
     int col = pass_col(0);
+    const int2 first_entry = tile_entry(P_idx, P_val, i0, m, DD, (int)threadIdx.x);
+    asm volatile("" ::: "memory");                                    // (in this order)
 #pragma unroll
     for (int t = 0; t < R; ++t) load_w(t, col);                     // in flight while the U tile is built
     load_q(col);
-    build_u_tile<R, DD, (D::size == 4 && (RG > 2 || DD == 8) ? 4 : 8), (PS > 16384), NT>(PlanePlace<PS>{smem}, pent, S, P_idx, P_val, i0, m, r, DD);
+    build_u_tile<R, DD, (D::size == 4 && (RG > 2 || DD == 8) ? 4 : 8), (PS > 16384), NT>(PlanePlace<PS>{smem}, pent, first_entry, S, P_idx, P_val, i0, m, r, DD);
     __syncthreads();
     for (int p = 1; p < npass; ++p) {
         const int next = pass_col(p);
@@ -643,7 +649,10 @@ __device__ __forceinline__ void decompress_wide() {
     };
 
     int col = pass_col(0);
+    const int2 first_entry = tile_entry(P_idx, P_val, i0, m, DD, (int)threadIdx.x);
+    asm volatile("" ::: "memory");                                    // (in this order)
     load_q(0, col, true);
+    __builtin_amdgcn_sched_barrier(0);                                // (the same order as at the end of a pass, or every pass would wait for W where it wants the last entries)
     {
         const uint32_t off = offset(col);
 #pragma unroll
@@ -651,7 +660,7 @@ __device__ __forceinline__ void decompress_wide() {
 #pragma unroll
             for (int t = 0; t < 4; ++t) load_w(0, g, t, col, off);     // in flight while the U tile is built
     }
-    build_u_tile<R, DD, (D::size == 4 && (R > 8 || DD == 8) ? 4 : 8), BIG, NT>(UnitPlace<LP, PLANE>{smem}, pent, S, P_idx, P_val, i0, m, r, DD);
+    build_u_tile<R, DD, (D::size == 4 && (R > 8 || DD == 8) ? 4 : 8), BIG, NT>(UnitPlace<LP, PLANE>{smem}, pent, first_entry, S, P_idx, P_val, i0, m, r, DD);
     __syncthreads();
     if constexpr (LOOSE) {                                          // the columns behind the last whole patch
         constexpr int kRest = COLS - 1;
@@ -782,9 +791,11 @@ __global__ __launch_bounds__(NT, (NORMS ? 3 : 4)) void k_decompress_any(const Ap
         }
     };
     int col = pass_col(0);
+    const int2 first_entry = tile_entry(pr.P_idx, pr.P_val, i0, m, d, (int)threadIdx.x);
+    asm volatile("" ::: "memory");                                    // (in this order)
     load_q(0, col, 0);
     load_w(col);
-    build_u_tile<R, 0, 0, (PS > 16384), NT>(PlanePlace<PS>{smem}, reinterpret_cast<int2*>(smem + RG * PS), pr.S, pr.P_idx, pr.P_val, i0, m, r, d);
+    build_u_tile<R, 0, 0, (PS > 16384), NT>(PlanePlace<PS>{smem}, reinterpret_cast<int2*>(smem + RG * PS), first_entry, pr.S, pr.P_idx, pr.P_val, i0, m, r, d);
     __syncthreads();
     for (int p = 0; p < npass; ++p) {
 #pragma unroll
