@@ -16,6 +16,8 @@
 // kept plan the matrix cores take the sums over (compress_mm.hip).  For fp16 they do not yet: three fp16 parts of an fp32 value are exact only if each has
 // a power of two of its own (in a column of its own that is possible) and the values lie within 2^29 of the largest.  fp32 has no such instruction.
 
+#include <algorithm>
+
 #include "compress_common.h"
 
 namespace lsp {
@@ -60,7 +62,8 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt(const CompressGroup) 
 // once per use (each row of T is used by d rows of S).  Each of the 4 waves of a workgroup takes
 // one piece of a row of P^T; its 64 lanes form 64/LG groups of LG lanes (LG = 16, 32 or 64 >= quads
 // per stripe), group g takes entries g, g + groups, ...; the groups' sums meet through lane
-// exchanges in a fixed order.  A row's last quad starts at r - 4 when r is no multiple of 4 and stores only what the
+// exchanges in a fixed order.  Where a slice would be larger than the L2 has room for beside what else it holds, each XCD takes its columns in two or four rounds (rounds_of).
+// A row's last quad starts at r - 4 when r is no multiple of 4 and stores only what the
 // quad before it has not (3001 rows, r = 250, d = 5: 26 us one column a thread, now 6).
 template <int LG>
 __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup) {
@@ -76,8 +79,10 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup)
     const int block = (int)blockIdx.x - pr.first_pt;
     const LoadedHeader H = load_header(plan);
     if (!plan_matches(H, pr.m, pr.n, r, d, tiles)) return;                   // kernel A has filled S with NaN
-    const int stripe = block & 7;
-    const int item = (block >> 3) * (kThreadsB / kWave) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    int round = 0, at_block = block;
+    while (at_block >= pr.round_pt) { at_block -= pr.round_pt; ++round; }   // (at most three times)
+    const int stripe = (at_block & 7) + 8 * round;
+    const int item = (at_block >> 3) * (kThreadsB / kWave) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (item >= H->p_nitems) return;
     words4 fields = scalar_load<words4>(as_const<RowItem>(plan + H->off_p_item) + item);
     arrived(fields);
@@ -169,31 +174,46 @@ static void longest_first(CompressGroup& g) {
         for (int b = a; b > 0 && g.p[b].n > g.p[b - 1].n; --b) std::swap(g.p[b], g.p[b - 1]);
 }
 
+constexpr int kMostRounds = 4;
+// Rounds of kernel B: one where a slice of T, m rows of r / 8 columns, is no larger than an XCD's L2 (4 MB); otherwise so many that a round's is no larger than 2.5 MB, as long as stripes have
+// 64 columns and more, 16 lanes' work.  (us, with kernel A, one round and this, bf16: 8192 x 4096, r = 2048, d = 8 90.1 and 80.7; 16384 x 4096, r = 1024, d = 8 99.8 and 88.8; 8192 x 8192,
+// r = 2048, d = 4 90.5 and 87.8; a slice of 4 MB in two rounds: 4096 x 4096, r = 2048 44.9 and 45.6, r = 1536 37.9 and 38.6, 8192 x 4096, r = 1024 48.7 and 47.8.)
+static int rounds_of(int64_t rows, int32_t r) {
+    int rounds = 1;
+    if (rows * r * 4 / 8 <= (4 << 20)) return rounds;
+    while (rounds < kMostRounds && rows * r * 4 / (8 * rounds) > (5 << 19) && r / (8 * 2 * rounds) >= 64) rounds *= 2;
+    return rounds;
+}
+
 hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st, const RawCall& raw) {
     const int nstripes = (r + kStripeQuads * 4 - 1) / (kStripeQuads * 4);
     const bool striped = r >= 4, tiles = walks_tiles(dtype, raw);
     longest_first(g);
-    const int sq = ((r + 3) / 4 + 7) / 8;
     g.r = r; g.d = d; g.tiles = tiles ? 1 : 0;
-    g.quads = striped ? sq : nstripes;
-    int32_t blocks = 0;
-    for (int p = 0; p < kMaxGroup; ++p) {
-        g.first_pt[p] = INT32_MAX;
-        if (p >= g.count) continue;
-        const int32_t items = (int32_t)plan_max_items(g.p[p].m, r, d);
-        g.first_pt[p] = g.p[p].first_pt = blocks;
-        blocks += striped ? ((items + 3) / 4) * 8 : items * nstripes;
-    }
     hipError_t e = launch_gq(g, raw, dtype, st);
     if (e != hipSuccess) return e;
-    if (striped) {
-        if (sq <= 16)      hipLaunchKernelGGL(k_compress_pt8<16>, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
+    // (a launch for each number of rounds that there is, nearly always one: the order of a sum depends on it, and is a matter of the matrix alone)
+    for (int rounds = 1; rounds <= (striped ? kMostRounds : 1); rounds *= 2) {
+        const int sq = ((r + 3) / 4 + 8 * rounds - 1) / (8 * rounds);
+        g.quads = striped ? sq : nstripes;
+        int32_t blocks = 0;
+        for (int p = 0; p < kMaxGroup; ++p) {
+            g.first_pt[p] = INT32_MAX;
+            if (p >= g.count) continue;
+            const int32_t items = (int32_t)plan_max_items(g.p[p].m, r, d);
+            g.first_pt[p] = g.p[p].first_pt = blocks;
+            g.p[p].round_pt = (items + 3) / 4 * 8;
+            if (!striped) blocks += items * nstripes;
+            else if (rounds_of(g.p[p].m, r) == rounds) blocks += g.p[p].round_pt * rounds;
+        }
+        if (blocks == 0) continue;
+        if (!striped)      hipLaunchKernelGGL(k_compress_pt, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
+        else if (sq <= 16) hipLaunchKernelGGL(k_compress_pt8<16>, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
         else if (sq <= 32) hipLaunchKernelGGL(k_compress_pt8<32>, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
         else               hipLaunchKernelGGL(k_compress_pt8<64>, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
-        return hipGetLastError();
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_compress_pt, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace lsp

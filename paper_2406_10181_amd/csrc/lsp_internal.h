@@ -193,7 +193,8 @@ struct CompressProblem {
     int32_t        first_gq, wgs_gq;             // workgroups of the T = G Q kernel (bf16: row blocks): the first, and how many
     int32_t        blocks_gq;                    // row blocks of each of them
     int32_t        first_pt;                     // first workgroup of the S = P^T T kernel
-    int32_t        pad[2];
+    int32_t        round_pt;                     // workgroups of one of its rounds (k_compress_pt8)
+    int32_t        pad;
 };
 struct CompressGroup {
     int32_t         count, r, d;

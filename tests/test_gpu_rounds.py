@@ -1,0 +1,35 @@
+"""Kernel B of compress where its slices of T are larger than an XCD's L2: two and four rounds over the columns, with a last stripe that is not whole, beside a matrix of one round in a group."""
+import pytest
+
+import lsp_synth as syn
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,n,r,d,dtype,dist", [
+    (4104, 24, 2048, 2, "bf16", "uniform"),      # just over 4 MB a slice: two rounds of 32 quads
+    (8200, 40, 2047, 3, "f16", "uniform"),       # four rounds of 16, the last one not whole
+    (16400, 16, 1030, 2, "f32", "uniform"),      # two rounds of 17 quads, stripes without a column
+    (20000, 8, 520, 4, "f32", "uniform"),        # stripes of 64 columns at the least: one round
+    (9000, 40, 1100, 4, "f32", "zipf"),          # rows of P^T cut into pieces
+])
+def test_compress_in_rounds(m, n, r, d, dtype, dist):
+    import gpu_util as gu
+    print(f"[case] rounds m={m} n={n} r={r} d={d} {dtype}", flush=True)
+    pb = syn.make_problem("rounds", m, n, r, d, dtype, seed=9900 + r, g_std=1.0, index_dist=dist)
+    dp = gu.DeviceProblem(pb)
+    S_o = oracle.compress(pb.G, pb.dtype, pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val, pb.r)
+    S = dp.compress_planned()
+    gu.check_compress(S, S_o, "rounds")
+    if dist == "uniform":                         # (nothing added with atomics)
+        import torch
+        import paper_2406_10181_amd as lsp
+        small = gu.DeviceProblem(syn.make_problem("one round", 700, n + 1, r, d, dtype, seed=3, g_std=1.0))
+        small.build_plan()
+        items = [(x.G, x.plan, x.S, x.ws, x.ws_bytes, x.pb.m, x.pb.n) for x in (small, dp)]
+        lsp.lsp_compress_planned_grouped(lsp.compress_items(items), 2, r, d, dp.code, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        assert (dp.S.cpu().numpy() == S).all()
+        together = small.S.cpu().numpy()
+        assert (small.compress_planned() == together).all()
