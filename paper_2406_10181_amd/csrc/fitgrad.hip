@@ -18,7 +18,7 @@
 #include <type_traits>
 #include <utility>
 
-#include "compress_common.h"
+#include "products.h"
 
 namespace lsp {
 
@@ -31,17 +31,18 @@ namespace lsp {
 // 4096 x 4096, d = 8, 16-bit) is what the kernel's time is made of.  HBM sees G once: an XCD takes every a for a column tile
 // before its next tile, so a tile of G (m rows of 256 elements, 2 MB at m = 4096) stays in that XCD's L2 for its
 // d visits.  With a workgroup a piece (four waves, a quarter of the entries each, 8 bytes a lane) it took 34 us there, 23 with a wave a piece (24 with the address of a row made anew for every load: BELOW_4G,
-// a 32-bit offset), now 21.5: rows and values of the entries by DPP moves and not by exchanges through LDS.  L2 hands out 12 of the 17 TB/s that it can (64 bytes a cycle and channel);
+// a 32-bit offset), now 22.6, fp16 21.8: rows and values of the entries by DPP moves and not by exchanges through LDS.  L2 hands out 12 of the 17 TB/s that it can (64 bytes a cycle and channel);
 // the products on the matrix cores instead of the vector ALUs took 22.0.
 // A row's last piece starts at n - VEC when n is no multiple of VEC, up to VEC - 1 columns before its tile if the tile has
 // fewer than VEC columns: the wave's sums have room for them in front.  n < VEC: one column a lane (VEC = 1).
 constexpr int kThreadsY = 256, kWavesY = kThreadsY / kWave, kXcds = 8, kTileY = 256;
 // The work is (tile of columns, four pieces), the pieces fastest, and each XCD has an eighth of it, one after the other (workgroup b runs on XCD b % 8), so that it has hardly more than one tile of G
-// at a time, and all XCDs the same amount (a tile for an XCD at a time, 4096 x 4160, r = 512, d = 8, fp16 28.3 us, 4096 x 4096 21.7).
-__device__ __forceinline__ bool place_in_y(int nitems, int tiles, int& item0, int& tile) {
+// at a time, and all XCDs the same amount (a tile for an XCD at a time, 4096 x 4160, r = 512, d = 8, fp16 28.3 us, so 23.8).
+__device__ __forceinline__ bool place_in_y(int block, bool later, int nitems, int tiles, int& item0, int& tile) {
     const int groups = (nitems + kWavesY - 1) / kWavesY;
-    const uint32_t units = (uint32_t)groups * (uint32_t)tiles, each = (units + kXcds - 1) / kXcds, seq = blockIdx.x / kXcds, unit = blockIdx.x % kXcds * each + seq;
-    if (seq >= each || unit >= units) return false;
+    const uint32_t units = (uint32_t)groups * (uint32_t)tiles, each = (units + kXcds - 1) / kXcds, half = (each + 1) / 2, seq = (uint32_t)block / kXcds + (later ? half : 0);
+    const uint32_t unit = (uint32_t)block % kXcds * each + seq;
+    if (seq >= (later ? each : half) || unit >= units) return false;
     tile = (int)(unit / (uint32_t)groups);
     item0 = (int)(unit - (uint32_t)tile * (uint32_t)groups) * kWavesY;
     return true;
@@ -77,20 +78,46 @@ __device__ __forceinline__ void store_y(const float* part, int stride, const uin
 
 template <int K> __device__ __forceinline__ uint32_t row_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x150 + K, 0xF, 0xF, true); }   // of each 16 lanes (row_newbcast)
 template <typename F, int... k> __device__ __forceinline__ void each_of(const F& f, std::integer_sequence<int, k...>) { (f(std::integral_constant<int, k>{}), ...); }
-template <typename D, int VEC, bool BELOW_4G>
-__global__ __launch_bounds__(kThreadsY) void k_gather_rows(const typename D::elem* __restrict__ G, const uint8_t* __restrict__ plan,
-                                                          float* __restrict__ Y, int m, int n, int r, int d, int tiles) {
+// The gather and the r x r products have nothing of each other: a product is a chain of latencies on a workgroup or two a CU, the gather a matter of L2's rate.  So each of the two launches
+// of products has half of the gather behind it (4096 x 4096, r = 512, d = 8, bf16: products 10 and 12 us and the gather 22, now 18 and 21; the call 98 -> 87 us).  The products come first, so that no
+// chain begins late; with registers for five or six waves a SIMD the 64 x 64 tiles spill (r = 1024: 193 us, 243 and 330).  r no multiple of 4: the products have launches of their own.
+struct GatherArgs { const void* G; const uint8_t* plan; float* Y; int32_t r, d, m, n, tiles, first, side, products, later, pad; GemmProblem p[kMaxGemmBatch]; };
+static_assert(sizeof(GatherArgs) == 256 && kMaxGemmBatch == 3, "records of 64 bytes, loaded whole");
+template <typename D, int VEC, bool BELOW_4G, bool WIDE>
+__global__ __launch_bounds__(kThreadsY, 4) void k_gather_rows(const GatherArgs) {
     constexpr int LG = VEC == 1 ? kWave : kTileY / VEC < kWave ? kTileY / VEC : kWave;   // lanes of an entry
     constexpr int NG = kWave / LG;                                  // entries a wave takes at a time
     constexpr int kLead = VEC;                                      // room in front of a tile (VEC - 1, rounded up to whole pieces)
-    __shared__ __align__(16) float part[kWavesY][kLead + kTileY];
+    constexpr int kPart = kLead + kTileY;
+    __shared__ __align__(16) float lds[std::max(kWavesY * kPart, WIDE ? kTileFloats4<64, 32> : kTileFloats4<32, 32>)];
+    const auto* args = group_args<GatherArgs>();
+    words16 head = scalar_load<words16>(args);
+    arrived(head);
+    struct { const typename D::elem* G; const uint8_t* plan; float* Y; int32_t r, d, m, n, tiles, first, side, products, later, pad; } a;
+    __builtin_memcpy(&a, &head, 64);
+    if ((int)blockIdx.x < a.first) {
+        const int tile = (int)(blockIdx.x / (unsigned)a.side), z = tile / a.side;
+        if (z >= a.products) return;
+        words16 record = scalar_load<words16>(&args->p[z]);
+        arrived(record);
+        const GemmProblem P = gemm_problem(record);
+        const int row = tile - z * a.side, col = (int)blockIdx.x - tile * a.side;
+        if constexpr (WIDE) product_tile4<64, 32>(P, a.r, row * 64, col * 64, lds);
+        else                product_tile4<32, 32>(P, a.r, row * 32, col * 32, lds);
+        return;
+    }
+    const typename D::elem* __restrict__ G = global_pointer(a.G);
+    const uint8_t* __restrict__ plan = global_pointer(a.plan);
+    float* __restrict__ Y = global_pointer(a.Y);
+    const int m = a.m, n = a.n, r = a.r, d = a.d;
+    float (*part)[kPart] = reinterpret_cast<float (*)[kPart]>(lds);
     typedef typename D::elem Piece __attribute__((ext_vector_type(VEC)));
     typedef Piece Loose __attribute__((aligned(D::size)));
     const LoadedHeader H = load_header(plan);
     if (!plan_matches(H, m, n, r, d, false)) return;
     const int nitems = H->p_nitems;
     int item0, tile;
-    if (!place_in_y(nitems, tiles, item0, tile)) return;
+    if (!place_in_y((int)blockIdx.x - a.first, a.later != 0, nitems, a.tiles, item0, tile)) return;
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const auto* itp = as_const<int32_t>(plan + H->off_p_item) + 4 * min(item0 + wave, nitems - 1);
     const RowItem it{itp[0], itp[1], itp[2], itp[3]};
@@ -224,19 +251,38 @@ size_t fitgrad_workspace_floats(int64_t m, int64_t n, int32_t r, int32_t d) {
     return align_up((size_t)m * r, 64) + 9 * align_up(rr, 64) + align_up((size_t)r * (size_t)n, 64);
 }
 
+// Y = G^T P, the first half of it or the later one, and beside it the products of `batch`.
 template <typename D>
-static hipError_t launch_gather(const void* G, const uint8_t* plan, float* Y, int64_t m, int64_t n, int32_t r, int32_t d, hipStream_t st) {
-    const int groups = ((int)plan_max_items(m, r, d) + kWavesY - 1) / kWavesY, tiles = (int)((n + kTileY - 1) / kTileY);   // (one column a lane: one tile)
-    const int64_t grid = ((int64_t)groups * tiles + kXcds - 1) / kXcds * kXcds;
+static hipError_t launch_gather(const void* G, const uint8_t* plan, float* Y, int64_t m, int64_t n, int32_t r, int32_t d, bool later, const GemmBatch& batch, int products, hipStream_t st) {
+    GatherArgs args{G, plan, Y, r, d, (int32_t)m, (int32_t)n};
+    args.tiles = (int)((n + kTileY - 1) / kTileY);                   // (one column a lane: one tile)
+    const bool wide = wide_products(r);
+    args.side = wide ? (r + 63) / 64 : (r + 31) / 32;
+    args.later = later;
+    if (r % 4 == 0) {
+        args.products = products;
+        args.first = (products * args.side * args.side + kXcds - 1) / kXcds * kXcds;
+        for (int z = 0; z < products; ++z) args.p[z] = batch.p[z];
+    } else {
+        const hipError_t e = launch_gemm_rr_batch(batch, products, r, st);
+        if (e != hipSuccess) return e;
+    }
+    const int64_t groups = ((int)plan_max_items(m, r, d) + kWavesY - 1) / kWavesY, each = (groups * args.tiles + kXcds - 1) / kXcds;
+    const int64_t grid = args.first + (each + 1) / 2 * kXcds;
     if (grid > INT32_MAX) return hipErrorInvalidValue;
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreadsY), 0, st, static_cast<const typename D::elem*>(G), plan, Y, (int)m, (int)n, (int)r, (int)d, tiles);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreadsY), 0, st, args);
         return hipGetLastError();
     };
     const bool below = m * n * D::size <= (int64_t)UINT32_MAX;
     constexpr int kPiece = 16 / D::size;
-    if (n >= kPiece) return below ? go(k_gather_rows<D, kPiece, true>) : go(k_gather_rows<D, kPiece, false>);
-    return below ? go(k_gather_rows<D, 1, true>) : go(k_gather_rows<D, 1, false>);
+    auto pick = [&](auto vec, auto below_4g) {
+        constexpr int V = decltype(vec)::value;
+        constexpr bool B = decltype(below_4g)::value;
+        return wide ? go(k_gather_rows<D, V, B, true>) : go(k_gather_rows<D, V, B, false>);
+    };
+    if (n >= kPiece) return below ? pick(std::integral_constant<int, kPiece>{}, std::true_type{}) : pick(std::integral_constant<int, kPiece>{}, std::false_type{});
+    return below ? pick(std::integral_constant<int, 1>{}, std::true_type{}) : pick(std::integral_constant<int, 1>{}, std::false_type{});
 }
 
 hipError_t launch_fitgrad(const void* G, const uint8_t* plan, const int32_t* P_idx, const float* P_val,
@@ -268,15 +314,16 @@ hipError_t launch_fitgrad(const void* G, const uint8_t* plan, const int32_t* P_i
     second.p[0] = GemmProblem{CP, S1, Dm, S, -2.0f, 0, Dt, {}};                                                  // D  = C_P S1 - 2 S
     second.p[1] = GemmProblem{S1, S, M1, nullptr, 0.0f, kGemmTB, nullptr, {}};                                        // M1 = S1 S^T
     second.p[2] = GemmProblem{S, X, M2, nullptr, 0.0f, kGemmTA, nullptr, {}};                                         // M2 = S^T X
-    if ((e = launch_gemm_rr_batch(first, 2, r, st)) != hipSuccess) return e;
-    if ((e = launch_gemm_rr_batch(second, 3, r, st)) != hipSuccess) return e;
-    // Y = G^T P
-    switch (dtype) {
-        case LSP_F32:  e = launch_gather<F32>(G, plan, Y, m, n, r, d, st); break;
-        case LSP_F16:  e = launch_gather<F16>(G, plan, Y, m, n, r, d, st); break;
-        default:       e = launch_gather<BF16>(G, plan, Y, m, n, r, d, st); break;
-    }
-    if (e != hipSuccess) return e;
+    // ... and beside them Y = G^T P
+    auto beside = [&](bool later, const GemmBatch& batch, int products) {
+        switch (dtype) {
+            case LSP_F32:  return launch_gather<F32>(G, plan, Y, m, n, r, d, later, batch, products, st);
+            case LSP_F16:  return launch_gather<F16>(G, plan, Y, m, n, r, d, later, batch, products, st);
+            default:       return launch_gather<BF16>(G, plan, Y, m, n, r, d, later, batch, products, st);
+        }
+    };
+    if ((e = beside(false, first, 2)) != hipSuccess) return e;
+    if ((e = beside(true, second, 3)) != hipSuccess) return e;
     const int left_blocks = (int)((m + 3) / 4), right_blocks = (int)((n + 3) / 4);
     GradArgs grad{};
     grad.left_blocks = left_blocks; grad.r = r; grad.d = d;

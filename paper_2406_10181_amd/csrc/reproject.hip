@@ -12,11 +12,10 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "lsp_internal.h"
+#include "products.h"
 
 namespace lsp {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // C = L^T R for two ELL matrices with the same rows: C[L_idx[i][k]][R_idx[i][k']] += L_val[i][k] * R_val[i][k'].
 // Global fp32 atomics are slow here (they go past the per-XCD L2), so a workgroup owns a block of rows of C
@@ -186,25 +185,18 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(const GramArgs) {
 // A[i = l % 32][k = l / 32] and B[k = l / 32][j = l % 32] and holds
 // C[8 (v / 4) + 4 (l / 32) + v % 4][l % 32] in accumulator register v -- and their four partial
 // tiles are added through LDS at the end, in wave order.
-__device__ __forceinline__ GemmProblem gemm_problem(int& r) {
-    const auto* args = group_args<GemmBatch>();
-    words2 head = scalar_load<words2>(args);
-    words16 record = scalar_load<words16>(&args->p[blockIdx.z]);
-    arrived(head, record);
-    r = (int)head[0];
-    GemmProblem P;
-    __builtin_memcpy(&P, &record, 64);
-    P.A = global_pointer(P.A); P.B = global_pointer(P.B); P.C = global_pointer(P.C); P.E = global_pointer(P.E); P.Ct = global_pointer(P.Ct);
-    return P;
-}
 constexpr int kTileMN = 32, kTileK = 128;
 constexpr int kTileElems = kTileMN * kTileK / 256;                  // elements of each tile a thread stages
 __global__ __launch_bounds__(256) void k_gemm_rr(const GemmBatch) {
     __shared__ float As[kTileMN][kTileK + 1];
     __shared__ float Bs[kTileK][kTileMN + 1];
     __shared__ float Cs[4][16][64];
-    int r;
-    const GemmProblem P = gemm_problem(r);
+    const auto* args = group_args<GemmBatch>();
+    words2 head = scalar_load<words2>(args);
+    words16 record = scalar_load<words16>(&args->p[blockIdx.z]);
+    arrived(head, record);
+    const int r = (int)head[0];
+    const GemmProblem P = gemm_problem(record);
     const float* __restrict__ A = P.A;
     const float* __restrict__ B = P.B;
     const bool ta = P.flags & kGemmTA, tb = P.flags & kGemmTB, sqa = P.flags & kGemmSqA, sqb = P.flags & kGemmSqB;
@@ -271,107 +263,14 @@ __global__ __launch_bounds__(256) void k_gemm_rr(const GemmBatch) {
     }
 }
 
-// The same product for r % 4 == 0, which is what the training configurations use: everything moves in groups
-// of four floats.  Both tiles lie in LDS with k running along the rows (As[i][k], Bs[j][k], rows padded by 16
-// bytes); a thread fetches 4 + 4 groups of 16 bytes per K tile -- four consecutive k of one row where the operand
-// has k contiguous in memory (A as it is, B transposed: one 16-byte LDS store), else four consecutive rows of
-// one k (four 4-byte LDS stores).  Within 8 consecutive k the lanes of half h = l / 32 take k = 4 h .. 4 h + 3
-// with one 16-byte LDS load per operand, and the matrix instruction number s of the group multiplies element s of
-// both: it sums over k = s and k = 4 + s, and the four of them over all eight.
-constexpr int kTileRow4 = kTileK + 4;                               // floats per LDS row
-constexpr int kTileGroups = kTileMN * kTileK / 4 / 256;             // 16-byte groups of each tile a thread stages
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <int MN, int K>
 __global__ __launch_bounds__(256) void k_gemm_rr4(const GemmBatch) {
-    __shared__ __align__(16) float As[kTileMN * kTileRow4];
-    __shared__ __align__(16) float Bs[kTileMN * kTileRow4];
-    __shared__ float Cs[4][16][64];
-    int r;
-    const GemmProblem P = gemm_problem(r);
-    const float* __restrict__ A = P.A;
-    const float* __restrict__ B = P.B;
-    const bool ta = P.flags & kGemmTA, tb = P.flags & kGemmTB, sqa = P.flags & kGemmSqA, sqb = P.flags & kGemmSqB;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int row0 = blockIdx.y * kTileMN, col0 = blockIdx.x * kTileMN;
-    f32x16 acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-    // Group q = tid + 256 e of a tile.  k contiguous in memory: row q / 32, k = 4 (q % 32) .. + 3 (rows step by 8
-    // with e).  Rows contiguous in memory: a wave takes 16 rows (four groups) of 16 k, so that it reads 64-byte pieces and
-    // its 4-byte stores meet no bank twice (with 32 rows of 8 k: four lanes to a bank); k steps by 32 with e.
-    const bool a_kc = !ta, b_kc = tb;
-    const int t_mn = 4 * ((lane & 3) + 4 * (wave & 1)), t_k = (lane >> 2) + 16 * (wave >> 1);
-    const int a_mn = a_kc ? tid / 32 : t_mn, a_k = a_kc ? 4 * (tid % 32) : t_k;
-    const int b_mn = b_kc ? tid / 32 : t_mn, b_k = b_kc ? 4 * (tid % 32) : t_k;
-    const int a_off = a_kc ? (row0 + a_mn) * r + a_k : a_k * r + row0 + a_mn;    // r * r < 2^31
-    const int b_off = b_kc ? (col0 + b_mn) * r + b_k : b_k * r + col0 + b_mn;
-    const int a_step = (a_kc ? 8 : 32) * r, b_step = (b_kc ? 8 : 32) * r;
-    const int a_kstep = a_kc ? 1 : r, b_kstep = b_kc ? 1 : r;
-    float* const as0 = As + a_mn * kTileRow4 + a_k;
-    float* const bs0 = Bs + b_mn * kTileRow4 + b_k;
-    const int as_step = a_kc ? 8 * kTileRow4 : 32, bs_step = b_kc ? 8 * kTileRow4 : 32;
-    f32x4 an[2][kTileGroups], bn[2][kTileGroups];                   // the next two tiles
-    const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-    auto fetch = [&](auto set, int k0) {
-        constexpr int Z = decltype(set)::value;
-#pragma unroll
-        for (int e = 0; e < kTileGroups; ++e) {
-            const bool aok = row0 + a_mn + (a_kc ? 8 * e : 0) < r && k0 + a_k + (a_kc ? 0 : 32 * e) < r;
-            an[Z][e] = aok ? *reinterpret_cast<const f32x4*>(A + a_off + e * a_step + k0 * a_kstep) : zero4;
-            const bool bok = col0 + b_mn + (b_kc ? 8 * e : 0) < r && k0 + b_k + (b_kc ? 0 : 32 * e) < r;
-            bn[Z][e] = bok ? *reinterpret_cast<const f32x4*>(B + b_off + e * b_step + k0 * b_kstep) : zero4;
-        }
-    };
-    const float* ap = As + (lane & 31) * kTileRow4 + wave * (kTileK / 4) + 4 * (lane >> 5);
-    const float* bp = Bs + (lane & 31) * kTileRow4 + wave * (kTileK / 4) + 4 * (lane >> 5);
-    auto tile = [&](auto set, int k0) {
-        constexpr int Z = decltype(set)::value;
-#pragma unroll
-        for (int e = 0; e < kTileGroups; ++e) {
-            const f32x4 a = sqa ? an[Z][e] * an[Z][e] : an[Z][e], b = sqb ? bn[Z][e] * bn[Z][e] : bn[Z][e];
-            if (a_kc) *reinterpret_cast<f32x4*>(as0 + e * as_step) = a;
-            else {
-#pragma unroll
-                for (int s = 0; s < 4; ++s) as0[e * as_step + s * kTileRow4] = a[s];
-            }
-            if (b_kc) *reinterpret_cast<f32x4*>(bs0 + e * bs_step) = b;
-            else {
-#pragma unroll
-                for (int s = 0; s < 4; ++s) bs0[e * bs_step + s * kTileRow4] = b[s];
-            }
-        }
-        __syncthreads();
-        fetch(set, k0 + 2 * kTileK);                                // past r: nothing is read
-#pragma unroll
-        for (int g = 0; g < kTileK / 4 / 8; ++g) {                  // a wave's quarter of the tile, 8 k at a time
-            const f32x4 a = *reinterpret_cast<const f32x4*>(ap + 8 * g);
-            const f32x4 b = *reinterpret_cast<const f32x4*>(bp + 8 * g);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b[s], acc, 0, 0, 0);
-        }
-        __syncthreads();
-    };
-    constexpr std::integral_constant<int, 0> kEven{};
-    constexpr std::integral_constant<int, 1> kOdd{};
-    fetch(kEven, 0);
-    fetch(kOdd, kTileK);
-    for (int k0 = 0; k0 < r; k0 += 2 * kTileK) {
-        tile(kEven, k0);
-        tile(kOdd, k0 + kTileK);                                    // past r: all zeros
-    }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) Cs[wave][v][lane] = acc[v];
-    __syncthreads();
-    const int j = col0 + (lane & 31);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {                                   // a wave adds up a quarter of the tile
-        const int v = 4 * wave + q, i = row0 + 8 * wave + 4 * (lane >> 5) + q;
-        float sum = ((Cs[0][v][lane] + Cs[1][v][lane]) + Cs[2][v][lane]) + Cs[3][v][lane];
-        if (i < r && j < r) {
-            if (P.E) sum = fmaf(P.beta, P.E[(int64_t)i * r + j], sum);
-            P.C[(int64_t)i * r + j] = sum;
-            if (P.Ct) P.Ct[(int64_t)j * r + i] = sum;
-        }
-    }
+    __shared__ __align__(16) float lds[kTileFloats4<MN, K>];
+    const auto* args = group_args<GemmBatch>();
+    words2 head = scalar_load<words2>(args);
+    words16 record = scalar_load<words16>(&args->p[blockIdx.z]);
+    arrived(head, record);
+    product_tile4<MN, K>(gemm_problem(record), (int)head[0], blockIdx.y * MN, blockIdx.x * MN, lds);
 }
 
 hipError_t launch_gram(const GramBatch& batch, int count, int32_t d, int32_t r, const GramClear* clear, hipStream_t st) {
@@ -413,7 +312,9 @@ hipError_t launch_gemm_rr_batch(const GemmBatch& batch, int count, int32_t r, hi
         by16 = by16 && reinterpret_cast<uintptr_t>(batch.p[z].A) % 16 == 0 && reinterpret_cast<uintptr_t>(batch.p[z].B) % 16 == 0;
     GemmBatch args = batch;
     args.r = r;
-    if (by16) hipLaunchKernelGGL(k_gemm_rr4, grid, dim3(256), 0, st, args);
+    const dim3 wide((unsigned)((r + 63) / 64), (unsigned)((r + 63) / 64), (unsigned)count);
+    if (by16 && wide_products(r)) hipLaunchKernelGGL((k_gemm_rr4<64, 32>), wide, dim3(256), 0, st, args);
+    else if (by16) hipLaunchKernelGGL((k_gemm_rr4<32, 32>), grid, dim3(256), 0, st, args);
     else      hipLaunchKernelGGL(k_gemm_rr, grid, dim3(256), 0, st, args);
     return hipGetLastError();
 }
