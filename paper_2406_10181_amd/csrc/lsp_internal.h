@@ -275,9 +275,9 @@ template <typename Group> __device__ __forceinline__ auto pick_problem(const LSP
     words8 head = scalar_load<words8>(g);
     words16 record = scalar_load<words16>(&g->p[0]);
     arrived(head, record);
-    if ((int)head[0] > 1) {                                           // (no more of the arguments than is needed: each line is one more to wait for, 0.3 us)
+    if ((int)head[0] > 1) {                                           // (one problem: nothing but the head and its record is read)
         const words16 f = scalar_load<words16>(&first[0]);
-        // (the number of problems that begin at this workgroup or before, less one: by sums of signs, a third of the instructions of comparisons)
+        // (the number of problems that begin at this workgroup or before, less one, by sums of signs; the second half only where the first does not tell)
         int before = 0;
 #pragma unroll
         for (int p = 1; p < kMaxGroup / 2; ++p) before += (block - (int)f[p]) >> 31;

@@ -29,7 +29,7 @@ namespace lsp {
 // What bounds it: the scan, which every workgroup makes of all entries (issue, and 64 bytes a cycle from L2), and trips to memory.  The next 32 entries a thread are on their way while
 // 32 are looked at, no load has a condition (the compiler waits for one that has), and nothing is divided by d.
 // The sums are taken in 64 bits, because ds_add_f32 serves one lane in 3 cycles, wherever the lanes' addresses lie (192 cycles a wave), and ds_add_f64 a wave in 20: 4096 and 11008 rows,
-// r = 512, d = 8 18.9 -> 11.6 us, 4096 and 4096 11.4 -> 8.9.
+// r = 512, d = 8 18.9 -> 16.5 us, 4096 and 4096 11.4 -> 10.1; with the loads as they are now 18.2 -> 13.8 and 10.2 -> 9.7.
 constexpr int kGramThreads = 1024, kGramSums = 12288, kGramQueue = 256, kGramInFlight = 8;   // (a wave's queue)
 constexpr size_t kGramLds = (size_t)kGramThreads / kWave * kGramQueue * sizeof(int);               // ... and the sums
 struct GramArgs {
