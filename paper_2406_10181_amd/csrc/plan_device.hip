@@ -375,6 +375,64 @@ __device__ __forceinline__ void sort_by_length(uint32_t (&key)[kMaxSlots], int p
     }
 }
 
+// The lanes left over go, as the host hands them out one at a time, to the column whose owners have the longest share (ties: the lower column), as long as that
+// share is at least 64 pairs: the k-th owner of a column with a list of L pairs is given away for a share of L / k, so the lanes go to the `spare` greatest of the shares L / k,
+// k = owners so far and up.  The level above which all of them are given away is searched, each wave with a level of its own; then the shares just below it, which are all
+// equal, in the order of the columns.  A share is taken as floor(2^s L / k): k is at most the greatest L / 64, so with 2^s above the square of that shares
+// that differ do so in this number too (two fractions are 1 / k k' apart).
+// (One after the other in a wave, with eight divisions and six exchanges each, 256 lanes took 180 us: this kernel for 4096 x 4096, r = 256, d = 8 190 us, now 11, d = 16 250 and 12; a raw compress there 239 us, now 53.)
+__device__ __forceinline__ void give_spare_lanes(int32_t* s_own, const int32_t* s_longest, int r, int spare, int32_t* s_level, int32_t* part) {
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    constexpr int kCols = kThreadsGQ / kWave;
+    int own[kCols], longest[kCols], most = 0;
+#pragma unroll
+    for (int q = 0; q < kCols; ++q) {                                // every wave has all columns
+        const int b = lane + kWave * q;
+        own[q] = b < r ? s_own[b] : 1; longest[q] = b < r ? s_longest[b] : 0;
+        most = max(most, longest[q]);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) most = max(most, __shfl_xor(most, off));
+    if (most < 64) return;                                           // (uniform over the workgroup)
+    const int scale = 2 * (32 - __builtin_clz((unsigned)most >> 6));
+    auto shares_from = [&](int own, int longest, uint64_t level) {   // how many of a column's are at the level or above it
+        // (both numbers are below 2^53, and a quotient that is no whole number is further from one than its rounding)
+        return max(0, (int)((double)((uint64_t)longest << scale) / (double)level) - own + 1);
+    };
+    auto all_from = [&](uint64_t level) {
+        int sum = 0;
+#pragma unroll
+        for (int q = 0; q < kCols; ++q) sum += shares_from(own[q], longest[q], level);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+        return sum;
+    };
+    // the least level from 64 on with no more than `spare` shares at it or above it
+    uint64_t low = (uint64_t)64 << scale, high = ((uint64_t)most << scale) + 1;
+    const uint64_t least = low;
+    for (int turn = 0; low < high; turn ^= kWavesGQ) {
+        const uint64_t width = high - low;
+        const int at_level = all_from(low + width * (unsigned)w / kWavesGQ);
+        if (lane == 0) s_level[turn + w] = at_level;
+        __syncthreads();
+        uint64_t below = low, above = high;                          // levels with too many, and one more; with few enough
+#pragma unroll
+        for (int k = kWavesGQ - 1; k >= 0; --k) {
+            const uint64_t level = low + width * (unsigned)k / kWavesGQ;
+            if (s_level[turn + k] <= spare) above = level;
+            else { below = level + 1; break; }
+        }
+        low = below; high = above;
+    }
+    const int mine = tid < r ? s_own[tid] : 1, length = tid < r ? s_longest[tid] : 0;
+    const int given = shares_from(mine, length, high);
+    const int next = high > least ? shares_from(mine, length, high - 1) - given : 0;   // one or none
+    int32_t total, equal;
+    (void)block_exclusive<kWavesGQ>(given, part, total);
+    const int place = block_exclusive<kWavesGQ>(next, part, equal);
+    if (tid < r) s_own[tid] = mine + given + (next && place < spare - total ? 1 : 0);
+}
+
 // One workgroup of 512 threads per chunk, one for P, and, if there are to be tiles, one more per chunk for their tables (in the first
 // one they would be another 1.3 of then 10 us).  Every chunk's workgroup finds the owners of all columns (they
 // depend on all chunks) and the virtual columns, then deals its chunk's lists to the waves, or sorts them into tiles; the first one also writes
@@ -422,40 +480,7 @@ __global__ __launch_bounds__(kThreadsGQ) void k_plan_deal(uint8_t* __restrict__ 
         vneed += total;
     }
     __syncthreads();
-    // lanes left over go, one at a time, to the column whose owners have the longest share (ties: the lower
-    // column), as long as that share is at least 64 pairs.  One wave does it, each lane keeping its columns
-    // (b = lane + 64 q; r < 512 here, because every column has an owner already) in registers.
-    if (vneed < kThreadsGQ && tid < kWave) {
-        int own_l[8], long_l[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int b = tid + kWave * q;
-            own_l[q] = b < r ? s_own[b] : 1; long_l[q] = b < r ? s_longest[b] : -1;
-        }
-        for (int spare = kThreadsGQ - vneed; spare > 0; --spare) {
-            double best = -1.0; int best_b = 0x7FFFFFFF;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int b = tid + kWave * q;
-                const double sh = (double)long_l[q] / (double)own_l[q];
-                if (b < r && (sh > best || (sh == best && b < best_b))) { best = sh; best_b = b; }
-            }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                const double ob = __shfl_xor(best, off); const int obb = __shfl_xor(best_b, off);
-                if (ob > best || (ob == best && obb < best_b)) { best = ob; best_b = obb; }
-            }
-            if (best < 64.0) break;                                  // uniform over the wave
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (best_b == tid + kWave * q) own_l[q]++;
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int b = tid + kWave * q;
-            if (b < r) s_own[b] = own_l[q];
-        }
-    }
+    if (vneed < kThreadsGQ) give_spare_lanes(s_own, s_longest, r, kThreadsGQ - vneed, s_count, s_part);   // (r < 512 here, because every column has an owner already)
     __syncthreads();
     int32_t V = 0;
     int shared = 0;
