@@ -80,16 +80,16 @@ template <int K> __device__ __forceinline__ uint32_t row_lane(uint32_t x) { retu
 template <typename F, int... k> __device__ __forceinline__ void each_of(const F& f, std::integer_sequence<int, k...>) { (f(std::integral_constant<int, k>{}), ...); }
 // The gather and the r x r products have nothing of each other: a product is a chain of latencies on a workgroup or two a CU, the gather a matter of L2's rate.  So each of the two launches
 // of products has half of the gather behind it (4096 x 4096, r = 512, d = 8, bf16: products 10 and 12 us and the gather 22, now 18 and 21; the call 98 -> 87 us).  The products come first, so that no
-// chain begins late; with registers for five or six waves a SIMD the 64 x 64 tiles spill (r = 1024: 193 us, 243 and 330).  r no multiple of 4: the products have launches of their own.
+// chain begins late; with registers for five or six waves a SIMD the 64 x 64 tiles spill (r = 1024: 193 us, 243 and 330).
 struct GatherArgs { const void* G; const uint8_t* plan; float* Y; int32_t r, d, m, n, tiles, first, side, products, later, pad; GemmProblem p[kMaxGemmBatch]; };
 static_assert(sizeof(GatherArgs) == 256 && kMaxGemmBatch == 3, "records of 64 bytes, loaded whole");
-template <typename D, int VEC, bool BELOW_4G, bool WIDE>
+template <typename D, int VEC, bool BELOW_4G, int SIDE, int GROUP>
 __global__ __launch_bounds__(kThreadsY, 4) void k_gather_rows(const GatherArgs) {
     constexpr int LG = VEC == 1 ? kWave : kTileY / VEC < kWave ? kTileY / VEC : kWave;   // lanes of an entry
     constexpr int NG = kWave / LG;                                  // entries a wave takes at a time
     constexpr int kLead = VEC;                                      // room in front of a tile (VEC - 1, rounded up to whole pieces)
     constexpr int kPart = kLead + kTileY;
-    __shared__ __align__(16) float lds[std::max(kWavesY * kPart, WIDE ? kTileFloats4<64, 32> : kTileFloats4<32, 32>)];
+    __shared__ __align__(16) float lds[std::max(kWavesY * kPart, kTileFloats<SIDE, 32>)];
     const auto* args = group_args<GatherArgs>();
     words16 head = scalar_load<words16>(args);
     arrived(head);
@@ -102,8 +102,7 @@ __global__ __launch_bounds__(kThreadsY, 4) void k_gather_rows(const GatherArgs) 
         arrived(record);
         const GemmProblem P = gemm_problem(record);
         const int row = tile - z * a.side, col = (int)blockIdx.x - tile * a.side;
-        if constexpr (WIDE) product_tile4<64, 32>(P, a.r, row * 64, col * 64, lds);
-        else                product_tile4<32, 32>(P, a.r, row * 32, col * 32, lds);
+        product_tile<SIDE, 32, GROUP>(P, a.r, row * SIDE, col * SIDE, lds);
         return;
     }
     const typename D::elem* __restrict__ G = global_pointer(a.G);
@@ -256,17 +255,16 @@ template <typename D>
 static hipError_t launch_gather(const void* G, const uint8_t* plan, float* Y, int64_t m, int64_t n, int32_t r, int32_t d, bool later, const GemmBatch& batch, int products, hipStream_t st) {
     GatherArgs args{G, plan, Y, r, d, (int32_t)m, (int32_t)n};
     args.tiles = (int)((n + kTileY - 1) / kTileY);                   // (one column a lane: one tile)
-    const bool wide = wide_products(r);
+    bool by16 = r % 4 == 0;                                          // groups of 16 bytes: whole ones, aligned operands
+    for (int z = 0; z < products; ++z) {
+        args.p[z] = batch.p[z];
+        by16 = by16 && reinterpret_cast<uintptr_t>(batch.p[z].A) % 16 == 0 && reinterpret_cast<uintptr_t>(batch.p[z].B) % 16 == 0;
+    }
+    const bool wide = by16 && wide_products(r);
     args.side = wide ? (r + 63) / 64 : (r + 31) / 32;
     args.later = later;
-    if (r % 4 == 0) {
-        args.products = products;
-        args.first = (products * args.side * args.side + kXcds - 1) / kXcds * kXcds;
-        for (int z = 0; z < products; ++z) args.p[z] = batch.p[z];
-    } else {
-        const hipError_t e = launch_gemm_rr_batch(batch, products, r, st);
-        if (e != hipSuccess) return e;
-    }
+    args.products = products;
+    args.first = (products * args.side * args.side + kXcds - 1) / kXcds * kXcds;
     const int64_t groups = ((int)plan_max_items(m, r, d) + kWavesY - 1) / kWavesY, each = (groups * args.tiles + kXcds - 1) / kXcds;
     const int64_t grid = args.first + (each + 1) / 2 * kXcds;
     if (grid > INT32_MAX) return hipErrorInvalidValue;
@@ -279,7 +277,7 @@ static hipError_t launch_gather(const void* G, const uint8_t* plan, float* Y, in
     auto pick = [&](auto vec, auto below_4g) {
         constexpr int V = decltype(vec)::value;
         constexpr bool B = decltype(below_4g)::value;
-        return wide ? go(k_gather_rows<D, V, B, true>) : go(k_gather_rows<D, V, B, false>);
+        return !by16 ? go(k_gather_rows<D, V, B, 32, 1>) : wide ? go(k_gather_rows<D, V, B, 64, 4>) : go(k_gather_rows<D, V, B, 32, 4>);
     };
     if (n >= kPiece) return below ? pick(std::integral_constant<int, kPiece>{}, std::true_type{}) : pick(std::integral_constant<int, kPiece>{}, std::false_type{});
     return below ? pick(std::integral_constant<int, 1>{}, std::true_type{}) : pick(std::integral_constant<int, 1>{}, std::false_type{});

@@ -1,4 +1,4 @@
-// What the launches of r x r products share: the tile of a product for r % 4 == 0, in a kernel of its own (reproject.hip) and beside the gather of the fitting gradient (fitgrad.hip).
+// What the launches of r x r products share: a tile of a product, in a kernel of its own (reproject.hip) and beside the gather of the fitting gradient (fitgrad.hip).
 #pragma once
 #include <algorithm>
 #include <type_traits>
@@ -15,30 +15,33 @@ __device__ __forceinline__ GemmProblem gemm_problem(const words16& record) {
 }
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// An MN x MN tile of a product for r % 4 == 0, which is what the training configurations use, by 256 threads: everything moves in groups
-// of four floats.  K goes by in tiles of K.  Both tiles lie in LDS with k running along the rows (As[i][k], Bs[j][k], rows padded by 16
-// bytes); a thread fetches groups of 16 bytes -- four consecutive k of one row where the operand
+// An MN x MN tile of a product by 256 threads.  K goes by in tiles of K.  Everything moves in groups of VEC floats: four where r is a multiple of 4 and the operands are aligned, as in the
+// training configurations, otherwise one.  Both tiles lie in LDS with k running along the rows (As[i][k], Bs[j][k], rows padded by 16
+// bytes); a group is four consecutive k of one row where the operand
 // has k contiguous in memory (A as it is, B transposed: one 16-byte LDS store), else four consecutive rows of
-// one k (four 4-byte LDS stores).  Within 8 consecutive k the lanes of half h = l / 32 take k = 4 h .. 4 h + 3
-// with one 16-byte LDS load per operand, and the matrix instruction number s of the group multiplies element s of
+// one k (four 4-byte LDS stores).  The matrix instruction is v_mfma_f32_32x32x2_f32: lane l supplies A[i = l % 32][k = l / 32] and B[k = l / 32][j = l % 32] and holds
+// C[8 (v / 4) + 4 (l / 32) + v % 4][l % 32] in register v.  Within 8 consecutive k the lanes of half h = l / 32 take k = 4 h .. 4 h + 3
+// with one 16-byte LDS load per operand, and the instruction number s of the group multiplies element s of
 // both: it sums over k = s and k = 4 + s, and the four of them over all eight.
 // MN = 32: the four waves share each tile's k, and their four sums meet in LDS.  MN = 64: a wave has a quadrant, all k of it in four sums one after the other (the rounding of four short
 // sums and not of one long), which takes half as much from L2 for a result and a chain of latencies four times as long.
 // Short tiles are faster, as more of them are in flight on a CU: 512 x 512, d = 8, two launches of two products each, the whole re-projection of a 4096 x 11008 matrix 109.0 us with K = 128 and 108.2 with 32;
 // r = 768 131.9 and 121.9, r = 1024 (MN = 32) 197 with K = 128, 187 with 64.  Two buffers in LDS, one barrier a tile: no better (r = 1024 193).
-template <int K> constexpr int kTileRow4 = K + 4;                    // floats per LDS row
-template <int MN, int K> constexpr int kTileFloats4 = std::max(2 * MN * kTileRow4<K>, MN == 32 ? 4 * 16 * 64 : 0);   // of LDS: both tiles, afterwards the waves' sums
+// (VEC = 1 had K = 128 and loads with conditions: fitting 3001 x 2999, r = 250, d = 5 80.2 us, now 61.0; 1262 x 2000, r = 527, d = 3 108.4 and 76.2.)
+template <int K> constexpr int kTileRow = K + 4;                     // floats per LDS row
+template <int MN, int K> constexpr int kTileFloats = std::max(2 * MN * kTileRow<K>, MN == 32 ? 4 * 16 * 64 : 0);   // of LDS: both tiles, afterwards the waves' sums
 // 64 x 64 tiles where 256 CUs have one each of a product, and less from L2 is worth more than many short chains (us, 4096 x 4096, d = 8, 32 and 64: r = 512 fitting 93 and 101, r = 768 refresh 132 and 150,
 // fitting 183 and 182, r = 1024 refresh 197 and 184, fitting 213 and 200; all with K = 64 for 32 x 32).
 inline bool wide_products(int r) { return r >= 1024; }
-template <int MN, int K>
-__device__ __forceinline__ void product_tile4(const GemmProblem& P, int r, int row0, int col0, float* lds) {
-    constexpr int kTileRow4 = lsp::kTileRow4<K>, kTileGroups = MN * K / 4 / 256;   // 16-byte groups of each tile a thread stages
-    constexpr int kAlong = K / 4, kDown = 256 / kAlong;             // where k is contiguous: groups of a row, rows of 256 groups
-    constexpr int kStepK = MN == 32 ? 32 : 16;                      // where rows are: k of 256 groups
-    static_assert((MN == 32 || MN == 64) && kTileGroups * 256 * 4 == MN * K, "whole groups for every thread");
+template <int MN, int K, int VEC>
+__device__ __forceinline__ void product_tile(const GemmProblem& P, int r, int row0, int col0, float* lds) {
+    constexpr int kTileRow = lsp::kTileRow<K>, kTileGroups = MN * K / VEC / 256;   // groups of VEC floats of each tile a thread stages
+    constexpr int kAlong = K / VEC, kDown = 256 / kAlong;             // where k is contiguous: groups of a row, rows of 256 groups
+    constexpr int kStepK = VEC == 1 ? 256 / MN : MN == 32 ? 32 : 16; // where rows are: k of 256 groups
+    static_assert((MN == 32 || MN == 64) && (VEC == 1 || VEC == 4) && kTileGroups * 256 * VEC == MN * K, "whole groups for every thread");
+    typedef float group __attribute__((ext_vector_type(VEC)));
     float* const As = lds;
-    float* const Bs = lds + MN * kTileRow4;
+    float* const Bs = lds + MN * kTileRow;
     const float* __restrict__ A = P.A;
     const float* __restrict__ B = P.B;
     const bool ta = P.flags & kGemmTA, tb = P.flags & kGemmTB, sqa = P.flags & kGemmSqA, sqb = P.flags & kGemmSqB;
@@ -50,33 +53,33 @@ __device__ __forceinline__ void product_tile4(const GemmProblem& P, int r, int r
     // with e).  Rows contiguous in memory: a wave takes 16 rows (four groups) of 16 k, so that it reads 64-byte pieces and
     // its 4-byte stores meet no bank twice (with 32 rows of 8 k: four lanes to a bank); k steps by 32 with e.
     const bool a_kc = !ta, b_kc = tb;
-    const int t_mn = 4 * ((lane & 3) + 4 * (MN == 32 ? wave & 1 : wave)), t_k = (lane >> 2) + (MN == 32 ? 16 * (wave >> 1) : 0);
-    const int a_mn = a_kc ? tid / kAlong : t_mn, a_k = a_kc ? 4 * (tid % kAlong) : t_k;
-    const int b_mn = b_kc ? tid / kAlong : t_mn, b_k = b_kc ? 4 * (tid % kAlong) : t_k;
-    float* const as0 = As + a_mn * kTileRow4 + a_k;
-    float* const bs0 = Bs + b_mn * kTileRow4 + b_k;
-    const int as_step = a_kc ? kDown * kTileRow4 : kStepK, bs_step = b_kc ? kDown * kTileRow4 : kStepK;
-    f32x4 an[2][kTileGroups], bn[2][kTileGroups];                   // the next two tiles
+    const int t_mn = VEC == 1 ? tid % MN : 4 * ((lane & 3) + 4 * (MN == 32 ? wave & 1 : wave)), t_k = VEC == 1 ? tid / MN : (lane >> 2) + (MN == 32 ? 16 * (wave >> 1) : 0);
+    const int a_mn = a_kc ? tid / kAlong : t_mn, a_k = a_kc ? VEC * (tid % kAlong) : t_k;
+    const int b_mn = b_kc ? tid / kAlong : t_mn, b_k = b_kc ? VEC * (tid % kAlong) : t_k;
+    float* const as0 = As + a_mn * kTileRow + a_k;
+    float* const bs0 = Bs + b_mn * kTileRow + b_k;
+    const int as_step = a_kc ? kDown * kTileRow : kStepK, bs_step = b_kc ? kDown * kTileRow : kStepK;
+    group an[2][kTileGroups], bn[2][kTileGroups];                   // the next two tiles
     // Every lane loads, past the last row and k the last ones once more: loads that some lanes leave out would be waited for one by one.  (r * r < 2^31)
     int a_row[kTileGroups], b_row[kTileGroups];
 #pragma unroll
     for (int e = 0; e < kTileGroups; ++e) {
-        a_row[e] = a_kc ? min(row0 + a_mn + kDown * e, r - 1) * r : min(row0 + a_mn, r - 4);
-        b_row[e] = b_kc ? min(col0 + b_mn + kDown * e, r - 1) * r : min(col0 + b_mn, r - 4);
+        a_row[e] = a_kc ? min(row0 + a_mn + kDown * e, r - 1) * r : min(row0 + a_mn, r - VEC);
+        b_row[e] = b_kc ? min(col0 + b_mn + kDown * e, r - 1) * r : min(col0 + b_mn, r - VEC);
     }
-    const int a_last = r - (a_kc ? 4 : 1), b_last = r - (b_kc ? 4 : 1), a_kstep = a_kc ? 1 : r, b_kstep = b_kc ? 1 : r;
+    const int a_last = r - (a_kc ? VEC : 1), b_last = r - (b_kc ? VEC : 1), a_kstep = a_kc ? 1 : r, b_kstep = b_kc ? 1 : r;
     auto fetch = [&](auto set, int k0) {
         constexpr int Z = decltype(set)::value;
 #pragma unroll
         for (int e = 0; e < kTileGroups; ++e) {
-            an[Z][e] = *reinterpret_cast<const f32x4*>(A + a_row[e] + min(k0 + a_k + (a_kc ? 0 : kStepK * e), a_last) * a_kstep);
-            bn[Z][e] = *reinterpret_cast<const f32x4*>(B + b_row[e] + min(k0 + b_k + (b_kc ? 0 : kStepK * e), b_last) * b_kstep);
+            an[Z][e] = *reinterpret_cast<const group*>(A + a_row[e] + min(k0 + a_k + (a_kc ? 0 : kStepK * e), a_last) * a_kstep);
+            bn[Z][e] = *reinterpret_cast<const group*>(B + b_row[e] + min(k0 + b_k + (b_kc ? 0 : kStepK * e), b_last) * b_kstep);
         }
     };
     const int wave_row = MN == 32 ? 0 : 32 * (wave >> 1), wave_col = MN == 32 ? 0 : 32 * (wave & 1), wave_k = MN == 32 ? wave * (K / 4) : 0;
     constexpr int kWaveK = MN == 32 ? K / 4 : K;
-    const float* ap = As + (wave_row + (lane & 31)) * kTileRow4 + wave_k + 4 * (lane >> 5);
-    const float* bp = Bs + (wave_col + (lane & 31)) * kTileRow4 + wave_k + 4 * (lane >> 5);
+    const float* ap = As + (wave_row + (lane & 31)) * kTileRow + wave_k + 4 * (lane >> 5);
+    const float* bp = Bs + (wave_col + (lane & 31)) * kTileRow + wave_k + 4 * (lane >> 5);
     f32x16 total;                                                   // MN = 64: the quarters of K that are done
 #pragma unroll
     for (int v = 0; v < 16; ++v) total[v] = 0.0f;
@@ -86,20 +89,20 @@ __device__ __forceinline__ void product_tile4(const GemmProblem& P, int r, int r
         constexpr int Z = decltype(set)::value;
 #pragma unroll
         for (int e = 0; e < kTileGroups; ++e) {
-            f32x4 a = an[Z][e], b = bn[Z][e];
-            if (k0 + a_k + (a_kc ? 0 : kStepK * e) >= r) a = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (k0 + b_k + (b_kc ? 0 : kStepK * e) >= r) b = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            group a = an[Z][e], b = bn[Z][e];
+            if (k0 + a_k + (a_kc ? 0 : kStepK * e) >= r) a = 0.0f;
+            if (k0 + b_k + (b_kc ? 0 : kStepK * e) >= r) b = 0.0f;
             if (sqa) a *= a;
             if (sqb) b *= b;
-            if (a_kc) *reinterpret_cast<f32x4*>(as0 + e * as_step) = a;
+            if (a_kc) *reinterpret_cast<group*>(as0 + e * as_step) = a;
             else {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) as0[e * as_step + s * kTileRow4] = a[s];
+                for (int s = 0; s < VEC; ++s) as0[e * as_step + s * kTileRow] = a[s];
             }
-            if (b_kc) *reinterpret_cast<f32x4*>(bs0 + e * bs_step) = b;
+            if (b_kc) *reinterpret_cast<group*>(bs0 + e * bs_step) = b;
             else {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) bs0[e * bs_step + s * kTileRow4] = b[s];
+                for (int s = 0; s < VEC; ++s) bs0[e * bs_step + s * kTileRow] = b[s];
             }
         }
         __syncthreads();

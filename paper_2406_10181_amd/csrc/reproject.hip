@@ -179,98 +179,14 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(const GramArgs) {
 // operand (ta, tb) while its tiles are staged.  A launch takes up to kMaxGemmBatch independent products of
 // one size (blockIdx.z picks one): a product alone is 256 small workgroups at r = 512, one per CU and each a
 // chain of load latencies, so independent products share the chip.
-// A workgroup of four waves makes a 32 x 32 tile of C (many small tiles: r is a few hundred, and
-// every CU should get one).  The K range goes by in 128-wide tiles staged through LDS; inside a
-// tile the four waves take 32 consecutive k each with v_mfma_f32_32x32x2_f32 -- lane l supplies
-// A[i = l % 32][k = l / 32] and B[k = l / 32][j = l % 32] and holds
-// C[8 (v / 4) + 4 (l / 32) + v % 4][l % 32] in accumulator register v -- and their four partial
-// tiles are added through LDS at the end, in wave order.
-constexpr int kTileMN = 32, kTileK = 128;
-constexpr int kTileElems = kTileMN * kTileK / 256;                  // elements of each tile a thread stages
+template <int MN, int VEC>
 __global__ __launch_bounds__(256) void k_gemm_rr(const GemmBatch) {
-    __shared__ float As[kTileMN][kTileK + 1];
-    __shared__ float Bs[kTileK][kTileMN + 1];
-    __shared__ float Cs[4][16][64];
+    __shared__ __align__(16) float lds[kTileFloats<MN, 32>];
     const auto* args = group_args<GemmBatch>();
     words2 head = scalar_load<words2>(args);
     words16 record = scalar_load<words16>(&args->p[blockIdx.z]);
     arrived(head, record);
-    const int r = (int)head[0];
-    const GemmProblem P = gemm_problem(record);
-    const float* __restrict__ A = P.A;
-    const float* __restrict__ B = P.B;
-    const bool ta = P.flags & kGemmTA, tb = P.flags & kGemmTB, sqa = P.flags & kGemmSqA, sqb = P.flags & kGemmSqB;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int row0 = blockIdx.y * kTileMN, col0 = blockIdx.x * kTileMN;
-    f32x16 acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-    // A thread stages elements q = tid + 256 e of each tile; consecutive threads read consecutive addresses
-    // whichever way the operand lies in memory.  Element e sits at (row, k) = (ar + e dar, ak + e dak) of the
-    // A tile and at (k, col) = (bk + e dbk, bc + e dbc) of the B tile: one base and one step per operand.
-    const int ar = ta ? tid % kTileMN : tid / kTileK, ak = ta ? tid / kTileMN : tid % kTileK;
-    const int dar = ta ? 0 : 256 / kTileK, dak = ta ? 256 / kTileMN : 0;
-    const int bk = tb ? tid % kTileK : tid / kTileMN, bc = tb ? tid / kTileK : tid % kTileMN;
-    const int dbk = tb ? 0 : 256 / kTileMN, dbc = tb ? 256 / kTileK : 0;
-    const int a_off = ta ? ak * r + row0 + ar : (row0 + ar) * r + ak;      // r * r < 2^31
-    const int a_step = ta ? dak * r : dar * r, a_kstep = ta ? r : 1;
-    const int b_off = tb ? (col0 + bc) * r + bk : bk * r + col0 + bc;
-    const int b_step = tb ? dbc * r : dbk * r, b_kstep = tb ? 1 : r;
-    float* const as0 = &As[0][0] + ar * (kTileK + 1) + ak;
-    float* const bs0 = &Bs[0][0] + bk * (kTileMN + 1) + bc;
-    const int as_step = dar * (kTileK + 1) + dak, bs_step = dbk * (kTileMN + 1) + dbc;
-    // the next pair of tiles is fetched into registers while the matrix cores work on the current one
-    float an[kTileElems], bn[kTileElems];
-    auto fetch = [&](int k0) {
-#pragma unroll
-        for (int e = 0; e < kTileElems; ++e) {
-            const bool aok = row0 + ar + e * dar < r && k0 + ak + e * dak < r;
-            const float a = aok ? A[a_off + e * a_step + k0 * a_kstep] : 0.0f;
-            an[e] = sqa ? a * a : a;
-            const bool bok = k0 + bk + e * dbk < r && col0 + bc + e * dbc < r;
-            const float b = bok ? B[b_off + e * b_step + k0 * b_kstep] : 0.0f;
-            bn[e] = sqb ? b * b : b;
-        }
-    };
-    fetch(0);
-    for (int k0 = 0; k0 < r; k0 += kTileK) {
-#pragma unroll
-        for (int e = 0; e < kTileElems; ++e) {
-            as0[e * as_step] = an[e];
-            bs0[e * bs_step] = bn[e];
-        }
-        __syncthreads();
-        if (k0 + kTileK < r) fetch(k0 + kTileK);
-#pragma unroll
-        for (int kk = wave * (kTileK / 4); kk < (wave + 1) * (kTileK / 4); kk += 2)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[lane & 31][kk + (lane >> 5)],
-                                                       Bs[kk + (lane >> 5)][lane & 31], acc, 0, 0, 0);
-        __syncthreads();
-    }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) Cs[wave][v][lane] = acc[v];
-    __syncthreads();
-    const int j = col0 + (lane & 31);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {                                   // a wave adds up a quarter of the tile
-        const int v = 4 * wave + q, i = row0 + 8 * wave + 4 * (lane >> 5) + q;
-        float sum = ((Cs[0][v][lane] + Cs[1][v][lane]) + Cs[2][v][lane]) + Cs[3][v][lane];
-        if (i < r && j < r) {
-            if (P.E) sum = fmaf(P.beta, P.E[(int64_t)i * r + j], sum);
-            P.C[(int64_t)i * r + j] = sum;
-            if (P.Ct) P.Ct[(int64_t)j * r + i] = sum;
-        }
-    }
-}
-
-template <int MN, int K>
-__global__ __launch_bounds__(256) void k_gemm_rr4(const GemmBatch) {
-    __shared__ __align__(16) float lds[kTileFloats4<MN, K>];
-    const auto* args = group_args<GemmBatch>();
-    words2 head = scalar_load<words2>(args);
-    words16 record = scalar_load<words16>(&args->p[blockIdx.z]);
-    arrived(head, record);
-    product_tile4<MN, K>(gemm_problem(record), (int)head[0], blockIdx.y * MN, blockIdx.x * MN, lds);
+    product_tile<MN, 32, VEC>(gemm_problem(record), (int)head[0], blockIdx.y * MN, blockIdx.x * MN, lds);
 }
 
 hipError_t launch_gram(const GramBatch& batch, int count, int32_t d, int32_t r, const GramClear* clear, hipStream_t st) {
@@ -306,16 +222,18 @@ hipError_t launch_gemm_rr_batch(const GemmBatch& batch, int count, int32_t r, hi
     if (count < 1 || count > kMaxGemmBatch) return hipErrorInvalidValue;
     for (int z = 0; z < count; ++z)
         if ((batch.p[z].flags & kGemmTA) && (batch.p[z].flags & kGemmTB)) return hipErrorInvalidValue;   // not needed anywhere
-    const dim3 grid((unsigned)((r + kTileMN - 1) / kTileMN), (unsigned)((r + kTileMN - 1) / kTileMN), (unsigned)count);
-    bool by16 = r % 4 == 0;                                          // the 16-byte path: whole groups, aligned operands
+    bool by16 = r % 4 == 0;                                          // groups of 16 bytes: whole ones, aligned operands
     for (int z = 0; z < count; ++z)
         by16 = by16 && reinterpret_cast<uintptr_t>(batch.p[z].A) % 16 == 0 && reinterpret_cast<uintptr_t>(batch.p[z].B) % 16 == 0;
     GemmBatch args = batch;
     args.r = r;
-    const dim3 wide((unsigned)((r + 63) / 64), (unsigned)((r + 63) / 64), (unsigned)count);
-    if (by16 && wide_products(r)) hipLaunchKernelGGL((k_gemm_rr4<64, 32>), wide, dim3(256), 0, st, args);
-    else if (by16) hipLaunchKernelGGL((k_gemm_rr4<32, 32>), grid, dim3(256), 0, st, args);
-    else      hipLaunchKernelGGL(k_gemm_rr, grid, dim3(256), 0, st, args);
+    auto go = [&](auto kernel, int tile) {
+        const unsigned side = (unsigned)((r + tile - 1) / tile);
+        hipLaunchKernelGGL(kernel, dim3(side, side, (unsigned)count), dim3(256), 0, st, args);
+    };
+    if (!by16)                 go(k_gemm_rr<32, 1>, 32);
+    else if (wide_products(r)) go(k_gemm_rr<64, 4>, 64);
+    else                       go(k_gemm_rr<32, 4>, 32);
     return hipGetLastError();
 }
 

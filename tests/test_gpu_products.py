@@ -1,4 +1,4 @@
-"""The r x r products of re-projection and fitting (r % 4 == 0) at the edges of their tiles: one, two, three and many tiles of K, last tiles of four rows, both sizes of tile, and the gather of fitting beside them."""
+"""The r x r products of re-projection and fitting at the edges of their tiles: one, two, three and many tiles of K, last tiles of four rows, both sizes of tile, and the gather of fitting beside them."""
 import numpy as np
 import pytest
 
@@ -13,7 +13,7 @@ def _dense(idx, val, r):
     return out
 
 
-@pytest.mark.parametrize("r", [4, 28, 32, 36, 64, 68, 100, 132, 1020, 1024, 1028])
+@pytest.mark.parametrize("r", [2, 4, 28, 30, 32, 33, 36, 64, 68, 97, 100, 132, 1020, 1024, 1027, 1028])
 def test_reproject_products(r):
     import torch
     import paper_2406_10181_amd as L
@@ -42,6 +42,7 @@ def test_reproject_products(r):
     (70, 24, 4, 1, "f16"),           # one workgroup a product: the gather's first is number 8
     (300, 520, 100, 4, "bf16"),      # 16 tiles of a product, the last four rows and columns wide
     (520, 300, 1028, 2, "f32"),      # 64 x 64 tiles
+    (260, 310, 33, 3, "f32"),        # r no multiple of 4: floats one by one
     (64, 6, 36, 2, "bf16"),          # fewer columns than a 16-byte piece of G
 ])
 def test_gradient_with_products_beside_the_gather(m, n, r, d, dtype):
