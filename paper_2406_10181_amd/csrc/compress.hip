@@ -60,11 +60,13 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt(const CompressGroup) 
 // workgroups are dealt to the 8 XCDs round-robin, so with stripe = blockIdx % 8 an XCD only ever
 // touches its own m x r/8 slice of T, which fits its 4 MB L2 -- T comes from HBM once instead of
 // once per use (each row of T is used by d rows of S).  Each of the 4 waves of a workgroup takes
-// one piece of a row of P^T; its 64 lanes form 64/LG groups of LG lanes (LG = 16, 32 or 64 >= quads
+// one piece of a row of P^T; its 64 lanes form 64/LG groups of LG lanes (LG = 8, 16, 32 or 64 >= quads
 // per stripe), group g takes entries g, g + groups, ...; the groups' sums meet through lane
 // exchanges in a fixed order.  Where a slice would be larger than the L2 has room for beside what else it holds, each XCD takes its columns in two or four rounds (rounds_of).
 // A row's last quad starts at r - 4 when r is no multiple of 4 and stores only what the
 // quad before it has not (3001 rows, r = 250, d = 5: 26 us one column a thread, now 6).
+// With r up to 256, eight lanes a group and not sixteen, half of them without a column, make one trip to L2 of 64 entries and not two (us, both kernels of compress, sixteen and
+// eight: 4096 x 4096, r = 256, d = 8, bf16 23.8 and 22.5; 2048 x 2048, r = 128, d = 8, fp16 14.2 and 13.2; 320 x 1216, r = 16, d = 8 12.3 and 10.9).
 template <int LG>
 __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup) {
     constexpr int NG = kWave / LG;                            // entry groups per wave
@@ -126,12 +128,14 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup)
         }
     };
     int base = 0;
+    uint2 next = ent[min(lane, max(it.len - 1, 0))];                            // the next 64 entries come with the rows of these
     for (; base + kWave <= it.len; base += kWave) {
-        const uint2 mine = ent[base + lane];
+        const uint2 mine = next;
+        next = ent[min(base + kWave + lane, it.len - 1)];
         for (int k0 = 0; k0 < kSteps; k0 += kAhead) take(mine, k0, k0 + kAhead);
     }
     if (base < it.len) {
-        uint2 mine = ent[min(base + lane, it.len - 1)];
+        uint2 mine = next;
         if (base + lane >= it.len) mine.y = 0u;
         const int steps = (it.len - base + NG - 1) / NG;
         for (int k0 = 0; k0 < steps; k0 += kAhead) take(mine, k0, steps);
@@ -208,6 +212,7 @@ hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_d
         }
         if (blocks == 0) continue;
         if (!striped)      hipLaunchKernelGGL(k_compress_pt, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
+        else if (sq <= 8) hipLaunchKernelGGL(k_compress_pt8<8>, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
         else if (sq <= 16) hipLaunchKernelGGL(k_compress_pt8<16>, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
         else if (sq <= 32) hipLaunchKernelGGL(k_compress_pt8<32>, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);
         else               hipLaunchKernelGGL(k_compress_pt8<64>, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);

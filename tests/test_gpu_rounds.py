@@ -1,4 +1,4 @@
-"""Kernel B of compress where its slices of T are larger than an XCD's L2: two and four rounds over the columns, with a last stripe that is not whole, beside a matrix of one round in a group."""
+"""Kernel B of compress where its slices of T are larger than an XCD's L2: two and four rounds over the columns, with a last stripe that is not whole, beside a matrix of one round in a group; and its groups of eight lanes."""
 import pytest
 
 import lsp_synth as syn
@@ -33,3 +33,19 @@ def test_compress_in_rounds(m, n, r, d, dtype, dist):
         assert (dp.S.cpu().numpy() == S).all()
         together = small.S.cpu().numpy()
         assert (small.compress_planned() == together).all()
+
+
+@pytest.mark.parametrize("m,n,r,d,dtype,dist", [
+    (40, 24, 4, 1, "f32", "uniform"),            # one stripe has a column; rows of some ten entries
+    (520, 40, 16, 8, "bf16", "uniform"),         # pieces of 256 entries: whole batches of 64, and a last one
+    (700, 24, 33, 3, "f16", "zipf"),             # the last quad overlaps the one before
+    (130, 24, 255, 2, "f32", "uniform"),         # eight lanes, the last quad short; rows without an entry
+    (64, 300, 256, 64, "bf16", "uniform"),
+    (130, 24, 257, 4, "f32", "uniform"),         # nine quads a stripe: sixteen lanes
+])
+def test_compress_with_eight_lanes_a_row(m, n, r, d, dtype, dist):
+    import gpu_util as gu
+    print(f"[case] eight lanes m={m} n={n} r={r} d={d} {dtype} {dist}", flush=True)
+    pb = syn.make_problem("eight", m, n, r, d, dtype, seed=9950 + r, g_std=1.0, index_dist=dist)
+    dp = gu.DeviceProblem(pb)
+    gu.check_compress(dp.compress_planned(), oracle.compress(pb.G, pb.dtype, pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val, pb.r), "eight")
