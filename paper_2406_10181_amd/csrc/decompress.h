@@ -74,7 +74,8 @@ __device__ __forceinline__ void block_sum2(float x, float y, float2* red, float2
 // made twice, with the same result; or, where the tile's columns lie in whole quads (Place::kQuads), it is turned into its place, with
 // whatever behind the last column.  place(row, b, c): where element (row, b + c) of the tile lives (c < 4).
 // The pairs are asked for first of all (tile_entry: a thread's first one; nearly always it has no other): loads return in order, and behind those of W the build would wait for HBM
-// once more.  Rows past m: value 0, row 0 of S.
+// once more.  At d = 16 the rows of Q before them are as much as W, and they wait for their turn (2048 x 2048, r = 256, d = 16 12.0 us first of all, 11.7 in turn; 4096 x 16384, r = 1024 103.1 and 102.5).
+// Rows past m: value 0, row 0 of S.
 __device__ __forceinline__ int2 tile_entry(const int32_t* __restrict__ P_idx, const float* __restrict__ P_val, int64_t i0, int m, int d, int q) {
     const int64_t at = i0 * d + q, count = (int64_t)m * d, there = at < count ? at : count - 1;
     const int idx = P_idx[there];
@@ -87,8 +88,9 @@ __device__ __forceinline__ void build_u_tile(const Place& place, int2* pent, con
                                              int64_t i0, int m, int r, int dim) {
     typedef f32x4 loose __attribute__((aligned(4)));
     const int d = DD > 0 ? DD : dim;
-    if ((int)threadIdx.x < R * d) pent[threadIdx.x] = first_entry;
-    for (int q = threadIdx.x + NT; q < R * d; q += NT) pent[q] = tile_entry(P_idx, P_val, i0, m, d, q);
+    constexpr bool kAsked = DD != 16;
+    if (kAsked && (int)threadIdx.x < R * d) pent[threadIdx.x] = first_entry;
+    for (int q = threadIdx.x + (kAsked ? NT : 0); q < R * d; q += NT) pent[q] = tile_entry(P_idx, P_val, i0, m, d, q);
     __syncthreads();
     if (r < 4) {
         for (int q = threadIdx.x; q < R * r; q += NT) {
@@ -354,8 +356,11 @@ __global__ __launch_bounds__(NT, (DD == 16 ? 2 : 4)) void k_decompress(const App
     };
 
     int col = pass_col(0);
-    const int2 first_entry = tile_entry(P_idx, P_val, i0, m, DD, (int)threadIdx.x);
-    asm volatile("" ::: "memory");                                    // (in this order)
+    int2 first_entry = make_int2(0, 0);
+    if constexpr (DD != 16) {
+        first_entry = tile_entry(P_idx, P_val, i0, m, DD, (int)threadIdx.x);
+        asm volatile("" ::: "memory");                                // (in this order)
+    }
 #pragma unroll
     for (int t = 0; t < R; ++t) load_w(t, col);                     // in flight while the U tile is built
     load_q(col);
@@ -649,10 +654,13 @@ __device__ __forceinline__ void decompress_wide() {
     };
 
     int col = pass_col(0);
-    const int2 first_entry = tile_entry(P_idx, P_val, i0, m, DD, (int)threadIdx.x);
-    asm volatile("" ::: "memory");                                    // (in this order)
+    int2 first_entry = make_int2(0, 0);
+    if constexpr (DD != 16) {
+        first_entry = tile_entry(P_idx, P_val, i0, m, DD, (int)threadIdx.x);
+        asm volatile("" ::: "memory");                                // (in this order)
+    }
     load_q(0, col, true);
-    __builtin_amdgcn_sched_barrier(0);                                // (the same order as at the end of a pass, or every pass would wait for W where it wants the last entries)
+    if constexpr (DD != 16) __builtin_amdgcn_sched_barrier(0);        // (the same order as at the end of a pass, or every pass would wait for W where it wants the last entries)
     {
         const uint32_t off = offset(col);
 #pragma unroll
