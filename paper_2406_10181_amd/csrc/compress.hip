@@ -100,21 +100,23 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup)
     f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
     // The piece's entries are loaded once, 64 at a time (one per lane), and handed to the groups by
     // lane exchange, so that the loads of T do not each wait for a load of their entry and can
-    // all be in flight together.  Groups without an entry in the last step take the last entry's row again, times zero: with a row
-    // of another piece an infinity there would reach this row of S.
-    // Eight loads of T in flight per lane: 56 to 68 registers, seven waves a SIMD.  (Sixteen take 100 and more and leave four: the step over
+    // all be in flight together.  Groups without an entry in the last step load the last entry's row again and take zeros in its place (times
+    // zero, an infinity there would be a NaN).
+    // Eight loads of T in flight per lane: 57 to 71 registers, seven or eight waves a SIMD.  (Sixteen take 100 and more and leave four: the step over
     // seven matrices of a 6.7B-style layer 428 instead of 418 us; 4096 x 4096, r = 2048, d = 8, compress alone 60.9 -> 55.4.)
     constexpr int kSteps = kWave / NG, kAhead = 8;
     static_assert(kSteps % kAhead == 0, "a block of steps ends with the wave's entries");
-    auto take = [&](const uint2 mine, int k0, int steps) {                       // steps k0 .. k0 + kAhead - 1 of the 64 entries, less than `steps`
+    // Steps k0, k0 + 1, ... of the 64 entries, those below `last`, at most kAhead - 1; then, in a place of its own, number min(k0 + kAhead - 1, last): where that is the piece's last one, some groups may
+    // have none of the `left` entries.  (Looked for in every step: attention matrices, both directions, 17.41 and 17.54 us.)
+    auto take = [&](const uint2 mine, int k0, int last, int left) {
         f32x4 x[kAhead];
         float v[kAhead];
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) {
             x[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
             v[k] = 0.0f;
-            if (k0 + k < steps) {                                               // uniform over the wave
-                const int src = (k0 + k) * NG + grp_e;                          // lane holding entry base + (k0+k)*NG + grp
+            if (k == kAhead - 1 || k0 + k < last) {                             // uniform over the wave
+                const int src = (k == kAhead - 1 ? min(k0 + k, last) : k0 + k) * NG + grp_e;   // lane holding entry base + step * NG + grp
                 const uint32_t row = (uint32_t)__shfl((int)mine.x, src);
                 v[k] = __uint_as_float((uint32_t)__shfl((int)mine.y, src));
                 x[k] = *reinterpret_cast<const loose*>(Tcol + (int64_t)row * r);
@@ -123,6 +125,10 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup)
         __builtin_amdgcn_sched_barrier(0);                                      // all of them in flight before the first is used
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) {
+            if (NG > 1 && k == kAhead - 1) {
+                const bool has = min(k0 + k, last) * NG + grp_e < left;
+                x[k].x = has ? x[k].x : 0.0f; x[k].y = has ? x[k].y : 0.0f; x[k].z = has ? x[k].z : 0.0f; x[k].w = has ? x[k].w : 0.0f;
+            }
             acc.x = fmaf(v[k], x[k].x, acc.x); acc.y = fmaf(v[k], x[k].y, acc.y);
             acc.z = fmaf(v[k], x[k].z, acc.z); acc.w = fmaf(v[k], x[k].w, acc.w);
         }
@@ -132,13 +138,13 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup)
     for (; base + kWave <= it.len; base += kWave) {
         const uint2 mine = next;
         next = ent[min(base + kWave + lane, it.len - 1)];
-        for (int k0 = 0; k0 < kSteps; k0 += kAhead) take(mine, k0, k0 + kAhead);
+        for (int k0 = 0; k0 < kSteps; k0 += kAhead) take(mine, k0, kSteps, kWave);
     }
     if (base < it.len) {
         uint2 mine = next;
         if (base + lane >= it.len) mine.y = 0u;
-        const int steps = (it.len - base + NG - 1) / NG;
-        for (int k0 = 0; k0 < steps; k0 += kAhead) take(mine, k0, steps);
+        const int left = it.len - base, last = (left - 1) / NG;
+        for (int k0 = 0; k0 <= last; k0 += kAhead) take(mine, k0, last, left);
     }
 #pragma unroll
     for (int step = LG; step < kWave; step *= 2) {            // group g adds group g ^ (step / LG)
