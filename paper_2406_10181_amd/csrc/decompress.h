@@ -872,17 +872,43 @@ inline bool loose_group(const ApplyGroup& g, int32_t d) {
     for (int p = 0; p < g.count; ++p) loose = loose && g.p[p].n <= 1 << 24;
     return loose;
 }
-// Where k_decompress_wide cannot be used, k_expand_loose or the two kernels with units of 4 rows (k_decompress for n even and d = 2, 4, 8, 16: fast; else k_decompress_any).
-// grid: workgroups of 512 threads, n: the widest matrix, eight: 8 rows a workgroup.  (us, k_decompress(_any) and k_expand_loose; apply of one matrix.)
-//   Not fast: 3001 x 2999, r = 250, d = 5, bf16 18.3 and 16.9, fp32 24.0 and 22.5; 6001 x 2500, r = 333, d = 6 31.7 and 23.5, fp32 42.2 and 35.7; 2047 x 4097, r = 300, d = 9 22.8 and
-//   18.0; 4001 x 4095, r = 500, d = 12 39.8 and 30.7, fp32 46.4 and 36.8.  One pass, or one and a bit in more workgroups than the chip holds, leaves nothing that covers the lane moves:
-//   4501 x 601, d = 5 8.5 and 9.6, 4501 x 1101 14.3 and 15.7 (9001 x 1801 29.1 and 28.3; 3001 x 1101, d = 9 13.4 and 12.1); fp32, where a pass has 512 columns, 3001 x 701 7.2 and 7.9,
-//   3001 x 301 5.9 and 5.0; d = 1, 4501 x 1101 10.6 and 12.5, so there is no kernel for it.
-//   Fast: 4096 x 4098, r = 512, d = 8, bf16 27.3 and 26.1, fp32 39.7 and 34.8; 9000 x 4100, r = 600, d = 8 69.9 and 58.9; 6000 x 3002, r = 300, d = 2 23.6 and 22.4; not in 8 rows (1000 x
-//   4098, d = 8 15.5 and 15.8), nor in fp32 below 4096 columns (3002 x 2998, d = 4 21.1 and 22.4).
-inline bool loose_call(unsigned grid, int32_t n, int32_t d, int elem_size, bool fast, bool eight) {
-    if (elem_size == 2) return !(fast && eight) && n > (grid > kResidentDeep ? 1536 : 1024);
-    return fast ? n >= 4096 : n > 1024 || (n <= 512 && grid <= kResidentDeep);
+// Where k_decompress_wide cannot be used, k_expand_loose or the two kernels with units of 4 rows (k_decompress for n even and d = 2, 4, 8, 16: fast; else k_decompress_any, which has two
+// neighbouring columns a thread where n is even: pair).  grid: workgroups of 512 threads, n: the widest matrix, eight: 8 rows a workgroup.  (us, k_decompress(_any) and k_expand_loose; one matrix after
+// another, W and G from HBM.  "1.05 times": k_expand_loose is so many times as fast.)
+//   16 bits, fast: 4002 x 4098, r = 500, d = 8 26.3 and 24.9, 9000 x 4098, r = 600 69.2 and 61.0, 6002 x 2502, r = 333, d = 2 21.2 and 20.5; not in 8 rows (1500 x 2302, d = 8 0.95 times), nor where rows
+//     are one pass, or one and a bit in more workgroups than the chip holds.
+//   16 bits, not fast: even rows 5002 x 1602 and longer 1.07 to 2 times; odd ones, one workgroup a CU, 3001 x 2999, r = 250, d = 5 18.2 and 17.4, 4001 x 4095, r = 500, d = 12 38.3 and 30.8, in 8 rows
+//     2001 x 4095, r = 300, d = 9 21.7 and 16.9.  With 257 to 447 workgroups some CUs have two and others one, which short lists do not cover: 5000 x 1601, r = 300, d = 2 15.8 and 19.0, d = 8 21.8 and
+//     24.4, d = 10 27.2 and 25.5; 6001 x 2501, r = 333, d = 4 25.5 and 28.1, d = 7 33.8 and 31.0; 4500 to 6001 x 3071 0.81 to 1.02 times with d <= 5 and 8, x 3501 0.92 to 1.06 but for d = 4, where the
+//     entries of k_decompress_any come in one piece (4500 x 4099, r = 1000 40.2 and 42.4).  On more workgroups the line is a second pass that is mostly empty: 16001 x 1535, d = 5 0.95 times, x 1801 1.03.
+//   fp32, where k_decompress(_any) reaches 4.2 TB/s of HBM and k_expand_loose 3.3: there the shorter the lists, and the more there is to move, the worse it does (4001 x 8191, r = 500, d = 4 62.1 and
+//     79.9, d = 8 67.4 and 81.4).  An odd d costs k_decompress_any more than d + 1, and so do even rows: list_weight; the longest rows for each weight, at about 0.95 times: in 8 rows 2040 x 5001 0.94 to
+//     1.10 times, x 8191 0.84 to 1.02; one workgroup a CU, d <= 4 4001 x 2301 0.98 to 1.03, x 3071 0.90 to 0.96, d = 5 to 8 3001 x 6001 0.98 to 1.09, 4001 x 8191 0.82 to 0.89; more of them, d <= 4 16001 x
+//     1535 0.95 to 0.97, x 2047 0.91 to 0.95, d = 5 7500 x 2301 1.03, x 3071 0.98, d = 6 and 8 x 3501 1.03, x 6001 0.95, d = 7 x 6001 0.99, x 8191 0.93; 9000 x 4099, r = 600, d = 12 123 and 113.
+//     (W in the cache behind L2: 3001 x 2999, r = 250, d = 6 24.9 and 22.0, 4001 x 8191, r = 500, d = 4 1.07 times.)  Fast, only in 8 rows just beyond 4096 columns, a stride that 8 rows of k_decompress
+//     fare badly with (1500 x 4098 1.07 to 1.11 times; x 6002 0.95; 4002 x 8194, r = 500, d = 2 61 and 79).
+//     Up to 512 columns half of the threads of the others have none: one workgroup a CU (3001 x 401 1.01 to 1.16 times), and elsewhere where the tile is large as well (9000 x 301, r = 1024, d = 4 23.7
+//     and 18.5; 16001 x 301, r = 16 0.86 to 0.96 times).
+//   Bias pass, where nothing is written: 9000 x 4099, r = 600, d = 5, bf16 65.1 and 43.3, fp32 69.5 and 47.6; 5000 x 1601, r = 300, d = 2, bf16 19.8 and 14.6; fast fp32 from 4096 columns on (4002 x 8194,
+//     d = 8 39.5 and 36.3, d = 2 28.0 and 28.9; 3002 x 2998, d = 2 13.3 and 15.0).
+//   d = 1, 4501 x 1101 10.6 and 12.5, so there is no kernel for it.
+inline int list_weight(int32_t d, bool pair) {
+    const int weight = d <= 4 ? 0 : d == 5 ? 1 : d == 7 ? 3 : d <= 8 ? 2 : 4;
+    return pair && weight > 0 && weight < 4 ? weight + 1 : weight;
+}
+inline bool loose_call(unsigned grid, int32_t n, int32_t r, int32_t d, int elem_size, bool fast, bool pair, bool eight, bool norms) {
+    const bool deep = grid <= kResidentDeep;
+    if (elem_size == 2) {
+        if (fast) return !eight && n > (deep ? 1024 : 1536);
+        if (norms || deep || pair || d >= 9) return n > (deep ? 1024 : 1536);
+        if (grid >= 448) return n > 1664;
+        return d != 4 && n > (d == 6 || d == 7 ? 2176 : 3328);
+    }
+    if (fast) return norms ? n >= 4096 : eight && n >= 4096 && n < 5120;
+    if (n <= 1024) return n <= 512 && (deep || (r > 512 && !norms));
+    constexpr int kAny = 1 << 30;
+    constexpr int kLongest[3][5] = {{7168, 7168, 7168, kAny, kAny}, {2560, 7168, 7168, kAny, kAny}, {1536, 2560, 3840, 7168, kAny}};
+    return norms || n <= kLongest[!deep ? 2 : eight ? 0 : 1][list_weight(d, pair)];
 }
 inline bool wide_group(const ApplyGroup& g, int32_t r) {
     bool wide = true;
@@ -958,7 +984,7 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
 #undef LSP_LAUNCH_WIDE
     }
     if constexpr (RG <= 4 && RG > 1 && NT == 512 && PS <= 16384) {
-        if (!(fast && wide_group(g, r)) && loose_group(g, d) && loose_call(grid, g.p[0].n, d, D::size, fast, RG == 2)) return launch_loose<D>(g, grid, RG == 2, NORMS, st);
+        if (!(fast && wide_group(g, r)) && loose_group(g, d) && loose_call(grid, g.p[0].n, r, d, D::size, fast, pair, RG == 2, NORMS)) return launch_loose<D>(g, grid, RG == 2, NORMS, st);
     }
 #define LSP_LAUNCH_FAST(DDV)                                                                                   \
     do {                                                                                                       \
@@ -1042,15 +1068,16 @@ template <typename D>
 static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_t st) {
     constexpr int kAll = 1 << 30;                                   // no row block is shared
     int64_t blocks = 0, widest = 0;
-    bool fast = true;
+    bool fast = true, pair = true;
     for (int p = 0; p < g.count; ++p) {
         blocks += (g.p[p].m + 15) / 16;
+        pair = pair && g.p[p].n % 2 == 0;
         widest = g.p[p].n > widest ? g.p[p].n : widest;
         fast = fast && fast_shape(g.p[p].n, d);
     }
     if (r > 1024) return launch_d<D, 2, 32768, 512>(g, r, d, kAll, st);
     const bool wide = wide_group(g, r);
-    const bool loose8 = !(fast && wide) && loose_group(g, d) && loose_call((unsigned)(2 * blocks), (int32_t)widest, d, D::size, fast, true);
+    const bool loose8 = !(fast && wide) && loose_group(g, d) && loose_call((unsigned)(2 * blocks), (int32_t)widest, r, d, D::size, fast, pair, true, false);
     if (few_blocks(blocks, r, d, D::size, fast)) {
         const bool eight = blocks <= 64 && (fast ? d > 8 : loose8 && D::size == 2);
         int64_t each = 0;                                           // row blocks
@@ -1065,7 +1092,7 @@ static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_
     if (eight_rows(blocks, widest, r, d, D::size, fast, wide, false))
         return r <= 256 ? launch_d<D, 2, 4096, 512>(g, r, d, kAll, st) : r <= 512 ? launch_d<D, 2, 8192, 512>(g, r, d, kAll, st)
                                                                                  : launch_d<D, 2, 16384, 512>(g, r, d, kAll, st);
-    const bool loose = !(fast && wide) && loose_group(g, d) && loose_call((unsigned)blocks, (int32_t)widest, d, D::size, fast, false);
+    const bool loose = !(fast && wide) && loose_group(g, d) && loose_call((unsigned)blocks, (int32_t)widest, r, d, D::size, fast, pair, false, false);
     if constexpr (D::size == 2)
         if (fast && !loose && (d <= 8 || wide) && blocks >= 1024 && 256 < r && r <= 512 && !(wide && d <= 4 && widest >= 2048 && (d <= 2 || widest <= 8192)))
             return launch_d<D, 8, 8192, 512>(g, r, d, kAll, st);
