@@ -1047,11 +1047,14 @@ inline bool eight_rows(int64_t blocks, int64_t n, int32_t r, int32_t d, int elem
 //     r = 1000, d = 8 10.9 and 9.1, 13.2 and 10.3; n odd 1001 x 701, r = 100, d = 5 5.1 and 4.6, 5.2 and 4.7; fp32 1001 x 2999, r = 250, d = 5 12.6 and 10.6.
 //   Passes shared: 512 x 2048, r = 128, d = 8 7.3 (4 rows 6.0) and 4.8, 8.7 (6.9) and 5.0.
 //   8 rows: d = 16 (4 rows: 1024 x 4096, r = 512 19.7 and 23.4); 16 bits, n odd, more than 1024 columns (1001 x 2003, r = 120, d = 3 6.2 and 6.8).
-// fp32 with 113 to 128 blocks and r <= 512, two workgroups of 4 rows on nearly every CU: 2048 x 4096, r = 512, d = 8 29.2 and 23.1, 2048 x 2048, r = 256, d = 4 10.6 and 9.9; with fewer some CUs have one (1500 x
-// 3000, r = 256, d = 8 14.5 and 16.5), and in 16 bits 8 rows are the better ones (2048 x 4096 16.2 and 17.4).
-inline bool few_blocks(int64_t blocks, int32_t r, int32_t d, int elem_size, bool fast) {
+//   More than 12 entries a row, which k_decompress_any reads from L2 for every block: 8 rows too (bf16, 8 rows, 4 and 8 with the passes shared: 1024 x 2048, r = 341, d = 32 1, 1.19 and 0.75 of the time, 513 x
+//     4099, r = 171, d = 14 1, 0.82 and 0.55), unless there is half a pass at the most, with nothing to share (1024 x 131, d = 20 1, 0.89 and 0.98).
+// fp32 with 113 to 128 blocks and r <= 512, two workgroups of 4 rows on nearly every CU, of which 4 rows read Q twice as often as 8: d <= 4 up to 6144 columns (8 rows and 4, times: 2048 x 2048, r = 512 1.23 with
+// d = 2 and 1.10 with d = 4, 2048 x 6144 1.09 and 1.00, 8192 columns 0.86 and 0.81), and rows of 16 KB, 8 of which fare badly together (2048 x 4096, r = 512, d = 8 29.2 and 23.1 us; 4000 columns 0.86 times,
+// 4104 0.89, 12288 0.88); with fewer blocks some CUs have one (1500 x 3000, r = 256, d = 8 14.5 and 16.5 us), and in 16 bits 8 rows are the better ones (2048 x 4096 16.2 and 17.4).
+inline bool few_blocks(int64_t blocks, int64_t n, int32_t r, int32_t d, int elem_size, bool fast) {
     if (r > 1024) return false;
-    return blocks <= 64 || (elem_size == 4 && fast && d <= 8 && r <= 512 && blocks > 112 && blocks <= 128);
+    return blocks <= 64 || (elem_size == 4 && fast && r <= 512 && blocks > 112 && blocks <= 128 && ((d <= 4 && n <= 6144) || (d <= 8 && n == 4096)));
 }
 
 // Rows per workgroup: 16 (four planes of U in LDS) or 8 (above), and 512 threads, except
@@ -1078,8 +1081,8 @@ static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_
     if (r > 1024) return launch_d<D, 2, 32768, 512>(g, r, d, kAll, st);
     const bool wide = wide_group(g, r);
     const bool loose8 = !(fast && wide) && loose_group(g, d) && loose_call((unsigned)(2 * blocks), (int32_t)widest, r, d, D::size, fast, pair, true, false);
-    if (few_blocks(blocks, r, d, D::size, fast)) {
-        const bool eight = blocks <= 64 && (fast ? d > 8 : loose8 && D::size == 2);
+    if (few_blocks(blocks, widest, r, d, D::size, fast)) {
+        const bool eight = blocks <= 64 && (fast ? d > 8 : d > kLooseEntries ? widest > 512 : loose8 && D::size == 2);
         int64_t each = 0;                                           // row blocks
         for (int p = 0; p < g.count; ++p) each += eight ? (g.p[p].m + 7) / 8 : (g.p[p].m + 3) / 4;
         const int64_t passes = (widest + 1023) / 1024, share = std::max<int64_t>(1, kResidentDeep / each);

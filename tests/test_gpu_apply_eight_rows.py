@@ -31,3 +31,24 @@ def test_apply_in_blocks_of_8_rows(m, n, r, d, dtype):
     pb = syn.make_problem("8 rows", m, n, r, d, dtype, seed=9200 + m + n + r + d, g_std=1.0)
     Wp, Wr = oracle.decompress_apply(pb.W, dtype, pb.S_in, pb.P_idx, pb.P_val, pb.Q_idx, pb.Q_val)
     gu.check_decompress(gu.DeviceProblem(pb).decompress(pb.S_in), pb.W, Wp, Wr, dtype, pb.name)
+
+
+# Blocks of 4 rows or of 8: at most 64 blocks of 16 with lists of more than 12 entries, whose passes are shared, and fp32 with 113 to 128 blocks: (m, n, r, d, dtype, rows, workgroups a block)
+FOUR_OR_EIGHT = [
+    (1000, 513, 60, 13, "bf16", 8, 1), (1000, 512, 60, 13, "f32", 4, 1), (1000, 2049, 60, 20, "f16", 8, 2), (100, 5003, 70, 64, "f32", 8, 5), (100, 5003, 70, 12, "f32", 4, 5), (37, 4099, 300, 17, "bf16", 8, 5),
+    (5, 6001, 600, 33, "bf16", 8, 6), (513, 3075, 900, 14, "f32", 8, 2),
+    (2048, 6144, 260, 4, "f32", 4, 1), (2048, 6146, 260, 4, "f32", 8, 1), (2048, 4096, 260, 8, "f32", 4, 1), (2048, 5122, 258, 8, "f32", 8, 1), (1793, 4094, 60, 8, "f32", 8, 1),
+]
+
+
+def test_which_kernel_has_blocks_of_4_rows_and_of_8(tmp_path):
+    from launch_routes import launches
+    for (m, n, r, d, dtype, rows, parts), calls in zip(FOUR_OR_EIGHT, launches([("apply", [(m, n)], r, d, dtype) for m, n, r, d, dtype, _, _ in FOUR_OR_EIGHT], str(tmp_path))):
+        kernel = f"k_decompress_any<{dtype.upper()}, {rows // 4}, " if d > 8 else f"k_decompress<{dtype.upper()}, {rows // 4}, {d}, "
+        assert len(calls) == 1 and calls[0][0].startswith(kernel) and calls[0][1] == (m + rows - 1) // rows * parts, (m, n, r, d, dtype, calls)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,r,d,dtype,rows,parts", FOUR_OR_EIGHT)
+def test_apply_in_blocks_of_4_rows_and_of_8(m, n, r, d, dtype, rows, parts):
+    test_apply_in_blocks_of_8_rows(m, n, r, d, dtype)
