@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt(const CompressGroup) 
 // once per use (each row of T is used by d rows of S).  Each of the 4 waves of a workgroup takes
 // one piece of a row of P^T; its 64 lanes form 64/LG groups of LG lanes (LG = 8, 16, 32 or 64 >= quads
 // per stripe), group g takes entries g, g + groups, ...; the groups' sums meet through lane
-// exchanges in a fixed order.  Where a slice would be larger than the L2 has room for beside what else it holds, each XCD takes its columns in two or four rounds (rounds_of).
+// exchanges in a fixed order.  Where a slice would be larger than the L2, each XCD may take its columns in two rounds (rounds_of).
 // A row's last quad starts at r - 4 when r is no multiple of 4 and stores only what the
 // quad before it has not (3001 rows, r = 250, d = 5: 26 us one column a thread, now 6).
 // With r up to 256, eight lanes a group and not sixteen, half of them without a column, make one trip to L2 of 64 entries and not two (us, both kernels of compress, sixteen and
@@ -81,9 +81,9 @@ __global__ __launch_bounds__(kThreadsB) void k_compress_pt8(const CompressGroup)
     const int block = (int)blockIdx.x - pr.first_pt;
     const LoadedHeader H = load_header(plan);
     if (!plan_matches(H, pr.m, pr.n, r, d, tiles)) return;                   // kernel A has filled S with NaN
-    int round = 0, at_block = block;
-    while (at_block >= pr.round_pt) { at_block -= pr.round_pt; ++round; }   // (at most three times)
-    const int stripe = (at_block & 7) + 8 * round;
+    const bool second = block >= pr.round_pt;
+    const int at_block = second ? block - pr.round_pt : block;
+    const int stripe = (at_block & 7) + (second ? 8 : 0);
     const int item = (at_block >> 3) * (kThreadsB / kWave) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (item >= H->p_nitems) return;
     words4 fields = scalar_load<words4>(as_const<RowItem>(plan + H->off_p_item) + item);
@@ -184,15 +184,15 @@ static void longest_first(CompressGroup& g) {
         for (int b = a; b > 0 && g.p[b].n > g.p[b - 1].n; --b) std::swap(g.p[b], g.p[b - 1]);
 }
 
-constexpr int kMostRounds = 4;
-// Rounds of kernel B: one where a slice of T, m rows of r / 8 columns, is no larger than an XCD's L2 (4 MB); otherwise so many that a round's is no larger than 2.5 MB, as long as stripes have
-// 64 columns and more, 16 lanes' work.  (us, with kernel A, one round and this, bf16: 8192 x 4096, r = 2048, d = 8 90.1 and 80.7; 16384 x 4096, r = 1024, d = 8 99.8 and 88.8; 8192 x 8192,
-// r = 2048, d = 4 90.5 and 87.8; a slice of 4 MB in two rounds: 4096 x 4096, r = 2048 44.9 and 45.6, r = 1536 37.9 and 38.6, 8192 x 4096, r = 1024 48.7 and 47.8.)
-static int rounds_of(int64_t rows, int32_t r) {
-    int rounds = 1;
-    if (rows * r * 4 / 8 <= (4 << 20)) return rounds;
-    while (rounds < kMostRounds && rows * r * 4 / (8 * rounds) > (5 << 19) && r / (8 * 2 * rounds) >= 64) rounds *= 2;
-    return rounds;
+constexpr int kMostRounds = 2;
+// Rounds of kernel B: two where a slice of T, m rows of r / 8 columns, is larger than an XCD's L2 (4 MB) and half of it is made of whole lines of 128 bytes (r a multiple of 512; then no fewer of the lanes of a group
+// have a column either); without whole lines only where half of it is not much larger than the L2, most lanes have a column all the same, and every row of T is wanted more than twice.  (us, with kernel A on 512
+// columns, fp16, one round and two: r = 2048 8192 rows, d = 8 77.0 and 62.6, d = 2 52.0 and 51.0, 5120 rows 52.0 and 49.5, 28000 rows 326 and 294; r = 1536 8192 rows 67 and 61, 28000 rows 270 and 278; r = 1024 16384 rows
+// 80 and 67, d = 2 52 and 50.  r = 1920 8192 rows, d = 8 85 and 80, d = 2 53 and 54, 16384 rows, d = 8 195 and 210; r = 1664 8192 rows 75 and 70, 12000 rows 119 and 121; r = 1040 16384 rows 120 and 132, r = 1280 128 and
+// 139.  Four rounds: r = 2048 8192 rows, d = 8 67.  A slice of 4 MB: 4096 x 4096, r = 2048, bf16 44.9 and 45.6, r = 1536 37.9 and 38.6, 8192 x 4096, r = 1024 48.7 and 47.8.)
+static int rounds_of(int64_t rows, int32_t r, int32_t d) {
+    const int64_t slice = rows * r * 4 / 8;
+    return slice > (4 << 20) && r >= 1024 && (r % 512 == 0 || (r > 1536 && d >= 4 && slice <= (9 << 20))) ? 2 : 1;
 }
 
 hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_dtype dtype, hipStream_t st, const RawCall& raw) {
@@ -214,7 +214,7 @@ hipError_t launch_compress_planned(CompressGroup& g, int32_t r, int32_t d, lsp_d
             g.first_pt[p] = g.p[p].first_pt = blocks;
             g.p[p].round_pt = (items + 3) / 4 * 8;
             if (!striped) blocks += items * nstripes;
-            else if (rounds_of(g.p[p].m, r) == rounds) blocks += g.p[p].round_pt * rounds;
+            else if (rounds_of(g.p[p].m, r, d) == rounds) blocks += g.p[p].round_pt * rounds;
         }
         if (blocks == 0) continue;
         if (!striped)      hipLaunchKernelGGL(k_compress_pt, dim3((unsigned)blocks), dim3(kThreadsB), 0, st, g);

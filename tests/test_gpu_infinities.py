@@ -26,8 +26,9 @@ def _problem(m, n, r, dtype, seed):
     (1500, 24, 260, "f32"), (2500, 24, 512, "bf16"), (2500, 33, 511, "f16"),                                             # four
     (2600, 24, 600, "f16"), (4100, 24, 1024, "bf16"),                                                                     # two
     (4100, 24, 2000, "bf16"),                                                                                             # one
-    (9000, 24, 2048, "f32"), (8400, 24, 2048, "bf16"),                                                                    # four rounds: four groups
-    (6000, 24, 2047, "f16"),                                                                                              # two rounds: two groups
+    (6000, 24, 2047, "f16"),
+    (9000, 24, 2048, "f32"), (8400, 24, 2048, "bf16"),                                                                    # two rounds: two groups
+    (8400, 24, 1024, "f16"),                                                                                              # four
 ])
 def test_infinities_and_their_signs(m, n, r, dtype):
     import gpu_util as gu
