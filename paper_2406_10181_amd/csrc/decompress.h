@@ -668,6 +668,16 @@ __device__ __forceinline__ void decompress_wide() {
 #pragma unroll
             for (int t = 0; t < 4; ++t) load_w(0, g, t, col, off);     // in flight while the U tile is built
     }
+    // Plain form, where one or two passes are all there is: with more of S than of the patch to come, its rows would stand in line behind all of W, so W arrives first.
+    // (us without and with the wait, bf16, from HBM; 16 rows a block: 5120 x 1024, r = 512, d = 2 10.0 and 8.8, d = 4 11.5 and 10.4, d = 8 16.3 and 14.5; 5120 x 2048, d = 4 17.3 and 16.6; but r = 128, d = 8
+    // 11.0 and 11.6.  32 rows, one pass: 28160 x 1024, r = 352, d = 4 35.2 and 31.9, d = 8 45.5 and 43.5; 16384 x 640, r = 352, d = 4 16.0 and 14.9; d = 2 is even, 20000 x 640, r = 288 16.6 and 17.6.)
+    if constexpr (FORM == kPlain && (G == 1 || DD != 2)) {
+        if (G == 1 ? r >= 256 : npass <= 1) {
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0x0F70);                       // vmcnt(0)
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
     build_u_tile<R, DD, (D::size == 4 && (R > 8 || DD == 8) ? 4 : 8), BIG, NT>(UnitPlace<LP, PLANE>{smem}, pent, first_entry, S, P_idx, P_val, i0, m, r, DD);
     __syncthreads();
     if constexpr (LOOSE) {                                          // the columns behind the last whole patch
