@@ -883,7 +883,7 @@ inline bool loose_group(const ApplyGroup& g, int32_t d) {
     return loose;
 }
 // Where k_decompress_wide cannot be used, k_expand_loose or the two kernels with units of 4 rows (k_decompress for n even and d = 2, 4, 8, 16: fast; else k_decompress_any, which has two
-// neighbouring columns a thread where n is even: pair).  grid: workgroups of 512 threads, n: the widest matrix, eight: 8 rows a workgroup.  (us, k_decompress(_any) and k_expand_loose; one matrix after
+// neighbouring columns a thread where n is even: pair).  lines: every row of W is whole lines of 128 bytes (fp32: n % 32 == 0).  grid: workgroups of 512 threads, n: the widest matrix, eight: 8 rows a workgroup.  (us, k_decompress(_any) and k_expand_loose; one matrix after
 // another, W and G from HBM.  "1.05 times": k_expand_loose is so many times as fast.)
 //   16 bits, fast: 4002 x 4098, r = 500, d = 8 26.3 and 24.9, 9000 x 4098, r = 600 69.2 and 61.0, 6002 x 2502, r = 333, d = 2 21.2 and 20.5; not in 8 rows (1500 x 2302, d = 8 0.95 times), nor where rows
 //     are one pass, or one and a bit in more workgroups than the chip holds.
@@ -895,6 +895,8 @@ inline bool loose_group(const ApplyGroup& g, int32_t d) {
 //     79.9, d = 8 67.4 and 81.4).  An odd d costs k_decompress_any more than d + 1, and so do even rows: list_weight; the longest rows for each weight, at about 0.95 times: in 8 rows 2040 x 5001 0.94 to
 //     1.10 times, x 8191 0.84 to 1.02; one workgroup a CU, d <= 4 4001 x 2301 0.98 to 1.03, x 3071 0.90 to 0.96, d = 5 to 8 3001 x 6001 0.98 to 1.09, 4001 x 8191 0.82 to 0.89; more of them, d <= 4 16001 x
 //     1535 0.95 to 0.97, x 2047 0.91 to 0.95, d = 5 7500 x 2301 1.03, x 3071 0.98, d = 6 and 8 x 3501 1.03, x 6001 0.95, d = 7 x 6001 0.99, x 8191 0.93; 9000 x 4099, r = 600, d = 12 123 and 113.
+//     Rows of whole lines cost k_expand_loose no line twice, and it is ahead at any length: 2048 x 16384, r = 224, d = 5 71.0 and 61.4, 5120 x 4096, r = 1024, d = 5 54.9 and 50.8, 6464 x 14400, r = 976, d = 6
+//     217 and 178; 2040 to 16001 rows of 8192 and 8224, d = 3 0.93 to 1.02 times, of 16384 1.22.  (Whole halves of a line are not enough: x 4104 and x 12004 0.78 to 1.05 times.)
 //     (W in the cache behind L2: 3001 x 2999, r = 250, d = 6 24.9 and 22.0, 4001 x 8191, r = 500, d = 4 1.07 times.)  Fast, only in 8 rows just beyond 4096 columns, a stride that 8 rows of k_decompress
 //     fare badly with (1500 x 4098 1.07 to 1.11 times; x 6002 0.95; 4002 x 8194, r = 500, d = 2 61 and 79).
 //     Up to 512 columns half of the threads of the others have none: one workgroup a CU (3001 x 401 1.01 to 1.16 times), and elsewhere where the tile is large as well (9000 x 301, r = 1024, d = 4 23.7
@@ -906,7 +908,7 @@ inline int list_weight(int32_t d, bool pair) {
     const int weight = d <= 4 ? 0 : d == 5 ? 1 : d == 7 ? 3 : d <= 8 ? 2 : 4;
     return pair && weight > 0 && weight < 4 ? weight + 1 : weight;
 }
-inline bool loose_call(unsigned grid, int32_t n, int32_t r, int32_t d, int elem_size, bool fast, bool pair, bool eight, bool norms) {
+inline bool loose_call(unsigned grid, int32_t n, int32_t r, int32_t d, int elem_size, bool fast, bool pair, bool lines, bool eight, bool norms) {
     const bool deep = grid <= kResidentDeep;
     if (elem_size == 2) {
         if (fast) return !eight && n > (deep ? 1024 : 1536);
@@ -918,7 +920,7 @@ inline bool loose_call(unsigned grid, int32_t n, int32_t r, int32_t d, int elem_
     if (n <= 1024) return n <= 512 && (deep || (r > 512 && !norms));
     constexpr int kAny = 1 << 30;
     constexpr int kLongest[3][5] = {{7168, 7168, 7168, kAny, kAny}, {2560, 7168, 7168, kAny, kAny}, {1536, 2560, 3840, 7168, kAny}};
-    return norms || n <= kLongest[!deep ? 2 : eight ? 0 : 1][list_weight(d, pair)];
+    return norms || lines || n <= kLongest[!deep ? 2 : eight ? 0 : 1][list_weight(d, pair)];
 }
 inline bool wide_group(const ApplyGroup& g, int32_t r) {
     bool wide = true;
@@ -947,7 +949,7 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
     // run time grows with n, so the long ones should not be the last to start
     for (int a = 1; a < g.count; ++a)
         for (int b = a; b > 0 && g.p[b].n > g.p[b - 1].n; --b) std::swap(g.p[b], g.p[b - 1]);
-    bool fast = true, pair = true;
+    bool fast = true, pair = true, lines = true;
     g.r = r; g.d = d; g.partial = partial;
     unsigned grid = 0;
     for (int p = 0; p < kMaxGroup; ++p) {                           // about `passes` passes for every workgroup
@@ -956,6 +958,7 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
         if (p >= g.count) continue;
         fast = fast && fast_shape(x.n, d);
         pair = pair && x.n % 2 == 0;
+        lines = lines && x.n % 32 == 0;
         x.parts = (int32_t)((((int64_t)x.n + 2 * NT - 1) / (2 * NT) + passes - 1) / passes);
         g.first[p] = x.first = (int32_t)grid;
         grid += (unsigned)((x.m + RG * 4 - 1) / (RG * 4) * x.parts);
@@ -994,7 +997,7 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
 #undef LSP_LAUNCH_WIDE
     }
     if constexpr (RG <= 4 && RG > 1 && NT == 512 && PS <= 16384) {
-        if (!(fast && wide_group(g, r)) && loose_group(g, d) && loose_call(grid, g.p[0].n, r, d, D::size, fast, pair, RG == 2, NORMS)) return launch_loose<D>(g, grid, RG == 2, NORMS, st);
+        if (!(fast && wide_group(g, r)) && loose_group(g, d) && loose_call(grid, g.p[0].n, r, d, D::size, fast, pair, lines, RG == 2, NORMS)) return launch_loose<D>(g, grid, RG == 2, NORMS, st);
     }
 #define LSP_LAUNCH_FAST(DDV)                                                                                   \
     do {                                                                                                       \
@@ -1081,16 +1084,17 @@ template <typename D>
 static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_t st) {
     constexpr int kAll = 1 << 30;                                   // no row block is shared
     int64_t blocks = 0, widest = 0;
-    bool fast = true, pair = true;
+    bool fast = true, pair = true, lines = true;
     for (int p = 0; p < g.count; ++p) {
         blocks += (g.p[p].m + 15) / 16;
         pair = pair && g.p[p].n % 2 == 0;
+        lines = lines && g.p[p].n % 32 == 0;
         widest = g.p[p].n > widest ? g.p[p].n : widest;
         fast = fast && fast_shape(g.p[p].n, d);
     }
     if (r > 1024) return launch_d<D, 2, 32768, 512>(g, r, d, kAll, st);
     const bool wide = wide_group(g, r);
-    const bool loose8 = !(fast && wide) && loose_group(g, d) && loose_call((unsigned)(2 * blocks), (int32_t)widest, r, d, D::size, fast, pair, true, false);
+    const bool loose8 = !(fast && wide) && loose_group(g, d) && loose_call((unsigned)(2 * blocks), (int32_t)widest, r, d, D::size, fast, pair, lines, true, false);
     if (few_blocks(blocks, widest, r, d, D::size, fast)) {
         const bool eight = blocks <= 64 && (fast ? d > 8 : d > kLooseEntries ? widest > 512 : loose8 && D::size == 2);
         int64_t each = 0;                                           // row blocks
@@ -1105,7 +1109,7 @@ static hipError_t launch_d_shape(ApplyGroup& g, int32_t r, int32_t d, hipStream_
     if (eight_rows(blocks, widest, r, d, D::size, fast, wide, false))
         return r <= 256 ? launch_d<D, 2, 4096, 512>(g, r, d, kAll, st) : r <= 512 ? launch_d<D, 2, 8192, 512>(g, r, d, kAll, st)
                                                                                  : launch_d<D, 2, 16384, 512>(g, r, d, kAll, st);
-    const bool loose = !(fast && wide) && loose_group(g, d) && loose_call((unsigned)blocks, (int32_t)widest, r, d, D::size, fast, pair, false, false);
+    const bool loose = !(fast && wide) && loose_group(g, d) && loose_call((unsigned)blocks, (int32_t)widest, r, d, D::size, fast, pair, lines, false, false);
     if constexpr (D::size == 2)
         if (fast && !loose && (d <= 8 || wide) && blocks >= 1024 && 256 < r && r <= 512 && !(wide && d <= 4 && widest >= 2048 && (d <= 2 || widest <= 8192)))
             return launch_d<D, 8, 8192, 512>(g, r, d, kAll, st);

@@ -39,6 +39,8 @@ LINES = [
     (4100, 1535, 30, 4, "f32", True), (4100, 1537, 30, 4, "f32", False), (4100, 2559, 30, 5, "f32", True), (4100, 2561, 30, 5, "f32", False), (4100, 3839, 30, 8, "f32", True),
     (4100, 3841, 30, 6, "f32", False), (4100, 3841, 30, 7, "f32", True), (4100, 3841, 30, 9, "f32", True), (4100, 3840, 30, 5, "f32", True), (4100, 3842, 30, 5, "f32", False),
     (1040, 4098, 30, 4, "f32", True), (1040, 5122, 30, 4, "f32", False), (2069, 4098, 30, 4, "f32", False),
+    (2069, 8192, 30, 3, "f32", True), (2069, 8208, 30, 3, "f32", False), (4100, 7200, 30, 6, "f32", True), (4100, 7184, 30, 6, "f32", False), (1040, 7200, 30, 5, "f32", True), (1040, 7184, 30, 5, "f32", False),
+    (4100, 8224, 30, 9, "f32", True), (4100, 8224, 30, 4, "f32", False),                                                                                    # rows of whole lines, or not
     (2069, 511, 30, 3, "f32", True), (2069, 513, 30, 3, "f32", False), (4100, 511, 513, 3, "f32", True), (4100, 511, 512, 3, "f32", False),
 ]
 
