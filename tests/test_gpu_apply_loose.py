@@ -1,6 +1,6 @@
 """The apply step and the bias pass where rows begin anywhere or d is none of 2, 4, 8, 16 (k_expand_loose), at its edges: columns behind the last whole patch (8 of 16 bits, 4 of
-fp32; 4 and 2 in blocks of 8 rows) from none to the most, a pass and a bit, r with a last quad of every length, blocks of 8 rows (m = 13), of 16 on one workgroup a CU
-(2069) and on more (4100), last blocks that are not whole."""
+fp32; 4 and 2 in blocks of 8 rows) from none to the most, a pass and a bit, r with a last quad of every length, few rows (m = 13: blocks of 8; in the fp32 apply
+step blocks of 4 in the kernel with units of 4), blocks of 16 on one workgroup a CU (2069) and on more (4100), last blocks that are not whole."""
 import pytest
 
 import lsp_synth as syn

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f16", "f32"])
 @pytest.mark.parametrize("d", [2, 4, 8])
 @pytest.mark.parametrize("m,r", [
-    (13, 9), (13, 255), (13, 256), (13, 257), (13, 514), (13, 1021),     # 8 rows: up to 256 columns there is one item a thread
+    (13, 9), (13, 255), (13, 256), (13, 257), (13, 514), (13, 1021),     # 4 rows
     (2069, 9), (2069, 128), (2069, 130), (2069, 384), (2069, 511),      # 16 rows: up to 128 columns
     (13, 1025), (13, 1100), (13, 1400), (13, 2047), (13, 2048), (2069, 1536),   # row by row, or in stripes of 256 columns
 ])
@@ -23,8 +23,8 @@ def test_apply_with_few_and_many_items_a_thread(m, r, d, dtype):
     gu.check_decompress(gu.DeviceProblem(pb).decompress(pb.S_in), pb.W, Wp, Wr, dtype, pb.name)
 
 
-# What the kernel for whole pieces of 8 columns does at its edges: one piece, a pass and a bit, less than a block of rows more; blocks of 8 rows (m = 13), of 16 on one workgroup
-# a CU (2069) and on more (4100), of 32 (16390).  Against the oracle, and bit for bit what the other kernel makes of the same matrix: a group with a ragged matrix goes there.
+# What the kernel for whole pieces of 8 columns does at its edges: one piece, a pass and a bit, less than a block of rows more; blocks of 4 rows (m = 13, d <= 8, r <= 1024;
+# k_decompress) or 8 (m = 13, other d and r), of 16 on one workgroup a CU (2069) and on more (4100), of 32 (16390).  Against the oracle, and bit for bit what the other kernel makes of the same matrix: a group with a ragged matrix goes there.
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
 @pytest.mark.parametrize("d", [2, 4, 8, 16])
 @pytest.mark.parametrize("m,n,r", [(13, 8, 16), (13, 1032, 132), (13, 520, 1540), (2069, 8, 20), (2069, 520, 260), (2069, 1544, 1024), (4100, 72, 512), (16390, 24, 260), (16390, 520, 512)])

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
     (4096, 500, 16, "uniform"),     # few lanes, shares on both sides of the level
     (3000, 100, 64, "steps"),       # shares of many kinds, several lanes a column
     (4096, 64, 64, "one"),          # one column has half of all
-    (2048, 300, 8, "uniform"),      # no share of 64
+    (2048, 300, 8, "uniform"),      # few shares of 64 and more (38 of 300)
     (70, 1, 1, "uniform"),          # a list of 70 to share
     (63, 1, 1, "uniform"),          # and one too short
 ])

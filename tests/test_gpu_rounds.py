@@ -1,4 +1,4 @@
-"""Kernel B of compress where its slices of T are larger than an XCD's L2: two and four rounds over the columns, with a last stripe that is not whole, beside a matrix of one round in a group; and its groups of eight lanes."""
+"""Kernel B of compress where its slices of T are larger than an XCD's L2, in one round over the columns or two, with a last stripe that is not whole, beside a matrix of one round in a group; and its groups of eight lanes."""
 import pytest
 
 import lsp_synth as syn
@@ -9,8 +9,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("m,n,r,d,dtype,dist", [
     (4104, 24, 2048, 2, "bf16", "uniform"),      # just over 4 MB a slice: two rounds of 32 quads
-    (8200, 40, 2047, 3, "f16", "uniform"),       # four rounds of 16, the last one not whole
-    (16400, 16, 1030, 2, "f32", "uniform"),      # two rounds of 17 quads, stripes without a column
+    (8200, 40, 2047, 3, "f16", "uniform"),       # one round of 64, its last stripe not whole (r is no multiple of 512, and d < 4)
+    (16400, 16, 1030, 2, "f32", "uniform"),      # one round of 33 quads, 27 in the last stripe
     (20000, 8, 520, 4, "f32", "uniform"),        # stripes of 64 columns at the least: one round
     (9000, 40, 1100, 4, "f32", "zipf"),          # rows of P^T cut into pieces
 ])
