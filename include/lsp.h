@@ -312,8 +312,8 @@ size_t lsp_estimation_bias_workspace_bytes(int64_t m, int64_t n, int32_t r, int3
  *   V              device, r*r fp32, read and overwritten; may be NULL (no second moment); not M
  *   workspace      device scratch of at least lsp_reproject_state_workspace_bytes(r) bytes,
  *                  16-byte aligned; contents undefined afterwards
- * The two r x r products of sparse matrices are accumulated with fp32 atomics: the result can
- * differ in the last bits from run to run.  The dense r x r products run in fp32 on the matrix
+ * The two r x r products of sparse matrices are summed in fp64 in an order that is not fixed, and
+ * rounded to fp32 once: the result can differ in the last bits from run to run.  The dense r x r products run in fp32 on the matrix
  * cores.  Errors as for the other calls; asynchronous on `stream`.
  */
 int lsp_reproject_state(const int32_t* P_idx, const float* P_val,
@@ -345,8 +345,8 @@ size_t lsp_reproject_state_workspace_bytes(int32_t r);
  *   gP, gQ       device, [m][d] and [n][d] fp32, overwritten
  *   workspace    device scratch of at least lsp_bias_gradient_workspace_bytes(m,n,r,d) bytes, 16-byte
  *                aligned; afterwards its first m*r floats hold T = G Q and the next r*r floats S = P^T G Q
- * The r x r products of sparse matrices inside use fp32 atomics (results can differ in the last bits from
- * run to run).  Errors as for lsp_estimation_bias.  Asynchronous on `stream`.
+ * The r x r products of sparse matrices inside are summed in fp64 in an order that is not fixed, and rounded
+ * to fp32 once (results can differ in the last bits from run to run).  Errors as for lsp_estimation_bias.  Asynchronous on `stream`.
  */
 int lsp_bias_gradient(const void* G, const void* plan,
                       const int32_t* P_idx, const float* P_val,

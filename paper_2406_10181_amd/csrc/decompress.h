@@ -487,6 +487,9 @@ __device__ __forceinline__ void decompress_wide() {
             for (int k = 0; k < VW; ++k) w[g][t][v * VW + k] = x[k];
         }
     };
+    // Rows that begin anywhere leave lines of W half written, which are whole in L2 a pass or a neighbour later: temporal stores, but for the deep form in 16 bits (us, non-temporal and temporal: fp32 3001 x 2999 24.9
+    // and 23.7, 4501 x 1601 25.0 and 23.7, 16001 x 2047 71.7 and 67.8, 9000 x 4100 97.4 and 100.1; 16 bits on more workgroups 8001 x 8190 75.2 and 73.8; the deep form 3001 x 2999, d = 5 17.6 and 19.1, 4096 x 4098
+    // 25.2 and 26.4).  Rows of whole pieces: non-temporal.
     constexpr int kStorePolicy = LOOSE && !(DEEP && D::size == 2) ? 0 : kNonTemporal;
     auto store_w = [&](int s, int g, int t, int col, uint32_t off) {
         auto& w = w_[s];
@@ -858,6 +861,7 @@ __global__ __launch_bounds__(NT, (NORMS ? 3 : 4)) void k_decompress_any(const Ap
 }
 
 // k_expand_loose, one instantiation file a storage type (decompress_loose.h): d from 2 to kLooseEntries, rows of up to 2^24 columns; grid: workgroups of 8 rows (eight) or 16.
+// (On more than one workgroup a CU d = 11 and 12 spill 12 to 52 bytes a lane in 16 bits, and beside k_decompress_any they are 1.13 to 1.54 times as fast, in fp32 1.08 to 1.8.)
 constexpr int kLooseEntries = 12;
 template <typename D> hipError_t launch_loose(const ApplyGroup& g, unsigned grid, bool eight, bool norms, hipStream_t st);
 
@@ -865,7 +869,7 @@ template <typename D> hipError_t launch_loose(const ApplyGroup& g, unsigned grid
 inline bool fast_shape(int32_t n, int32_t d) { return (n % 2) == 0 && (d == 2 || d == 4 || d == 8 || d == 16); }
 
 // k_decompress_wide (us; k_decompress and it; apply of one matrix unless said otherwise; uniform columns, Q not reordered).  It takes whole pieces of 8 columns and
-// whole units of 4, every matrix of the group, or the group goes to k_decompress, with the same result.  Where both can, it is used
+// whole units of 4, every matrix of the group, or the group goes to k_expand_loose or k_decompress (loose_call), with the same result.  Where it and k_decompress can, it is used
 //   for d = 16, where two columns' entries of Q in a thread leave k_decompress 192 registers: 4096 x 16384, r = 1024, bf16, zipf 129 and 101; 4096 x 4096, r = 1024, fp32 53.0 and
 //     43.6; 2048 x 2048, r = 256, bf16 (8 rows) 15.3 and 12.4; bias pass 4096 x 4096, r = 512, bf16 77 and 67, with the compress call before it;
 //   for 16 bits in blocks of 16 and 32 rows: four matrices 4096 x 11008, r = 512, d = 8 187 and 167 (176 and 166 with Q reordered); 4096 x 16384, r = 512, d = 8 75.7 and 66.8;
@@ -1034,13 +1038,14 @@ static hipError_t launch_d(ApplyGroup& g, int32_t r, int32_t d, int passes, hipS
 //       1000 x 2048, r = 128, d = 2, bf16     6.2 |  8.0     8.3 |  9.4        2048 x 2048, r = 512, d = 8, bf16    11.5 | 13.6    13.7 | 15.7
 //       2048 x 16384, r = 256, d = 4, bf16   31.3 | 46.3    27.3 | 32.9        2048 x 8192, r = 256, d = 16, fp32   42.9 | 60.1    36.9 | 45.4
 //       2048 x 2048, r = 256, d = 16, bf16   13.4 | 19.5    15.8 | 20.0        1000 x 4096, r = 512, d = 16, bf16   21.3 | 32.8    22.8 | 30.7
-//       2048 x 2047, r = 250, d = 5, bf16    10.5 | 13.3    12.1 | 15.3        2040 x 8191, r = 900, d = 7, bf16    38.3 | 53.5    36.3 | 49.0
+//       2048 x 2047, r = 250, d = 5, bf16     8.6 | 12.2    10.7 | 12.8        2040 x 8191, r = 900, d = 7, bf16    26.7 | 39.8    23.2 | 29.9
+//       2048 x 2047, r = 250, d = 5, fp32    11.7 | 14.6                       2040 x 8191, r = 900, d = 7, fp32    42.7 | 53.9
 //     (Rows of 16 KB are the exception: 2048 x 4096, r = 512, d = 8, fp32     29.5 | 26.6    23.3 | 21.5.)
 //   * 129 to 255 blocks: some CUs have two workgroups of 8 rows and others one.  16 rows, the more so the larger d is:
 //       2064 x 4096, r = 512, d = 8, bf16    23.3 | 19.9    23.8 | 21.0        3072 x 16384, r = 512, d = 8, bf16   76.0 | 63.1    62.5 | 50.6
 //       4080 x 4096, r = 512, d = 8, fp32    45.9 | 31.4    34.7 | 24.5        4080 x 8192, r = 256, d = 16, bf16   90.7 | 58.3    95.8 | 49.6
 //       3072 x 2048, r = 512, d = 8, fp32    20.7 | 18.1    20.5 | 16.3        3072 x 2048, r = 256, d = 4, fp32    16.1 | 15.1    14.5 | 12.7
-//       4080 x 4096, r = 256, d = 4, bf16       (bias)      18.3 | 16.2        4073 x 8191, r = 250, d = 7, bf16    67.1 | 52.9    50.4 | 41.0
+//       4080 x 4096, r = 256, d = 4, bf16       (bias)      18.3 | 16.2        4073 x 8191, r = 250, d = 7, bf16    46.7 | 44.1    35.7 | 29.0
 //     but 8 rows in fp32 below 4096 columns where the lists are short and the tile small (r <= 64 d), in the apply step up to 1024 columns whatever d is:
 //       4080 x 1024, r = 256, d = 4, fp32     9.8 | 11.0    11.7 | 11.0        3072 x 1024, r = 512, d = 2, fp32    10.7 |  9.4    13.1 | 10.7
 //       2064 x 3072, r = 128, d = 2, fp32    17.0 | 17.3    12.8 | 14.8        4080 x 2048, r = 128, d = 2, fp32    16.2 | 15.9    12.7 | 12.5
@@ -1072,8 +1077,8 @@ inline bool few_blocks(int64_t blocks, int64_t n, int32_t r, int32_t d, int elem
 
 // Rows per workgroup: 16 (four planes of U in LDS) or 8 (above), and 512 threads, except
 //   * 1024 or more blocks, 16-bit storage, 256 < r <= 512: 32 rows, so that the rows of Q are streamed from L2 half as
-//     often (the seven matrices of a 6.7B-style layer, d = 8, one call: 202 us, with 16 rows 227; d = 16 325 and 335; 16384 x 4096, r = 512, d = 8 67.2 and 73.3; where
-//     k_decompress_wide does not serve, d = 4, 16384 x 4098 96.1 and 100.3); fp32 patches of 32 rows would not fit the registers.
+//     often (the seven matrices of a 6.7B-style layer, d = 8, one call: 202 us, with 16 rows 227; d = 16 325 and 335; 16384 x 4096, r = 512, d = 8 67.2 and 73.3); fp32 patches of 32
+//     rows would not fit the registers.  Nor where k_expand_loose serves (16384 x 4098, d = 4), which has 16;
 //     With few entries of Q in k_decompress_wide 16 rows are the faster ones, which ask ahead and end more evenly: d = 2, from 2048 columns on: the layer 161.5 and 148.7 us,
 //     16384 x 4096 53.9 and 51.3, 20000 x 8192 156 and 118 (1024 columns 17.4 and 17.8); d = 4, 2048 to 8192 columns: 16384 x 4096 57.6 and 56.1, 20000 x 8192 162 and 130, but
 //     four matrices 4096 x 11008 153.7 and 157.4;
